@@ -1189,8 +1189,14 @@ size_t gemm_splitk_scratch_bytes(const GemmArgs& a) { return gemm_mfma_supported
 bool gemm_mfma_supported(const GemmArgs& a) {
   if (a.in_dtype != kBF16) return false;
   if (a.M <= 0 || a.N <= 0 || a.K <= 0) return false;
-  if (a.lda % 8 || a.ldb % 8 || a.K % 8) return false;
-  if (a.A2 && (a.K2 <= 0 || a.K2 % 8 || !a.B2 || a.k_dev)) return false;
+  if (a.lda % 8 || a.ldb % 8) return false;
+  // A K-major operand is read in 16-byte pieces along K.  With both operands row-major over K (TN) a k-row is either
+  // loaded or, past K, lies outside the buffer and loads zeros, so any K will do: it is the number of rows of a batch
+  // there, which need not be a multiple of anything (a packed batch, an odd sequence length).  On the shape-agnostic
+  // kernel 4096 x 12288 x 3999 took 6.36 ms, on this one 0.33 ms (and 28 instead of 1.3 ms for a 128256-entry dW_lm).
+  const bool any_k = a.layout == kTN;
+  if (!any_k && a.K % 8) return false;
+  if (a.A2 && (a.K2 <= 0 || (!any_k && a.K2 % 8) || !a.B2 || a.k_dev)) return false;
   if (((uintptr_t)a.A | (uintptr_t)a.B | (uintptr_t)a.A2 | (uintptr_t)a.B2) & 15) return false;
   // 32-bit byte offsets inside one tile
   const int64_t lim = (int64_t)1 << 21;
