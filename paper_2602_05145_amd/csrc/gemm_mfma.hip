@@ -1253,7 +1253,7 @@ hipError_t launch_layout(const MfmaParams& p, hipStream_t s) {
 }
 
 const char* gemm_kernel_name(const GemmArgs& a) {
-  if (!gemm_mfma_supported(a)) return "gemm_simple";
+  if (!gemm_mfma_supported(a)) return a.in_dtype == kF32 && a.out_dtype == kF32 ? "gemm_fp32" : "gemm_simple";
   const bool big = use_big_tiles(a.M, a.N);
   const bool f32 = a.out_dtype == kF32;
   switch (a.layout) {
@@ -1304,7 +1304,7 @@ hipError_t launch_gemm(const GemmArgs& a, hipStream_t s) {
   if (a.m_dev) prof_dynamic(a.m_dev, a.m_off, a.M);
   else if (a.k_dev) prof_dynamic(a.k_dev, a.k_off, a.K);
   if (gemm_mfma_supported(a)) return launch_gemm_mfma(a, s);
-  return launch_gemm_simple(a, s);
+  return a.in_dtype == kF32 && a.out_dtype == kF32 ? launch_gemm_fp32(a, s) : launch_gemm_simple(a, s);
 }
 
 // ------------------------------------------------------------------------------------------------

@@ -1,7 +1,6 @@
 // Shape-agnostic GEMM for gfx950: any sizes, strides and dtype (fp32 or bf16 storage, fp32 FMA
-// arithmetic).  It is the whole GEMM path of fp32 mode (where the step is latency-bound and exactness
-// matters) and the fallback of bf16 mode for shapes the MFMA kernel does not take (unaligned leading
-// dimensions).  64x64 output tile per 256-thread block, 4x4 micro-tile per thread, LDS-staged K slabs.
+// arithmetic).  It is the fallback of bf16 mode for shapes the MFMA kernel does not take (unaligned leading
+// dimensions) and of fp32 mode for sizes of 2^30 and more.  64x64 output tile per 256-thread block, 4x4 micro-tile per thread, LDS-staged K slabs.
 #include "kernels.h"
 #include "tide_common.h"
 

@@ -11,7 +11,7 @@ enum : int { kNT = 0, kNN = 1, kTN = 2 };
 
 inline size_t dtype_size(int dt) { return dt == kBF16 ? 2 : 4; }
 
-// ---- gemm_mfma.hip / gemm_simple.hip ---------------------------------------------------------
+// ---- gemm_mfma.hip / gemm_fp32.hip / gemm_simple.hip ---------------------------------------------------------
 // C[M,N] (ldc) = alpha * sum over operand pairs of op(A) op(B)  (+ residual) (+ C if accumulate)
 // layout NT: A[M,K] lda, B[N,K] ldb.  NN: A[M,K], B[K,N].  TN: A[K,M], B[K,N].
 // A second operand pair (A2,B2,K2; same layout and leading dims) extends the contraction.
@@ -40,8 +40,9 @@ struct GemmArgs {
 bool gemm_mfma_supported(const GemmArgs& a);
 size_t gemm_splitk_scratch_bytes(const GemmArgs& a);   // 0 when the launch would not be split
 hipError_t launch_gemm_mfma(const GemmArgs& a, hipStream_t s);
+hipError_t launch_gemm_fp32(const GemmArgs& a, hipStream_t s);     // fp32 operands and result
 hipError_t launch_gemm_simple(const GemmArgs& a, hipStream_t s);
-hipError_t launch_gemm(const GemmArgs& a, hipStream_t s);  // picks the MFMA path when supported
+hipError_t launch_gemm(const GemmArgs& a, hipStream_t s);  // picks among the three
 
 // ---- elementwise.hip ------------------------------------------------------------------------
 // Row plan of the LM head.  keep_t = mask_t != 0 and 0 <= token_t < V.  scal[0] = N = max(1, #keep),

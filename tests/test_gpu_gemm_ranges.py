@@ -47,3 +47,22 @@ def test_weight_gradient_over_any_number_of_rows(B, M, N, K, accumulate):
     _gemm(B, B.LAYOUT_TN, M, N, K, a, b, c, "bf16", "fp32", accumulate=accumulate)
     ref = ref + (0.5 if accumulate else 0.0)
     assert float((c.double() - ref).abs().max()) < 2e-5 * float(ref.abs().max())
+
+
+@pytest.mark.parametrize("layout", [0, 1, 2])
+@pytest.mark.parametrize("M,N,K", [(1, 1, 1), (33, 31, 7), (40, 100, 515), (128, 256, 4096),     # split over waves
+                                   (897, 832, 37), (1000, 1001, 130),                             # tiles of 64
+                                   (2048, 2060, 96), (2050, 2047, 33)])                           # tiles of 128
+def test_fp32_products_at_the_edges_of_their_tiles(B, layout, M, N, K):
+    """fp32 operands on the three forms of the fp32 kernel: aligned rows (16-byte loads) and odd ones, ragged tiles and K
+    remainders, with residual, accumulation and alpha."""
+    a, b, ref = _operands(B, layout, M, N, K, "fp32", M + K)
+    g = torch.Generator(device=DEV).manual_seed(5)
+    res, c0 = torch.randn(M, N, device=DEV, generator=g), torch.randn(M, N, device=DEV, generator=g)
+    c = torch.full((M, N), float("nan"), device=DEV)
+    _gemm(B, layout, M, N, K, a, b, c, "fp32", "fp32")
+    assert float((c.double() - ref).abs().max()) < 2e-6 * max(1.0, float(ref.abs().max()))
+    c = c0.clone()
+    _gemm(B, layout, M, N, K, a, b, c, "fp32", "fp32", alpha=-1.5, residual=res, accumulate=1)
+    want = -1.5 * ref + res.double() + c0.double()
+    assert float((c.double() - want).abs().max()) < 2e-6 * max(1.0, float(want.abs().max()))
