@@ -1,4 +1,4 @@
-// Flash-style causal grouped-query attention for gfx950, head_dim 128, bf16 storage, fp32 softmax and
+// Flash-style causal grouped-query attention for gfx950, head_dim 128 or 64, bf16 storage, fp32 softmax and
 // accumulation, v_mfma_f32_32x32x16_bf16 throughout.  Three kernels: forward, dQ, and dK/dV.  The
 // [S,S] score matrix never exists; only the per-row log-sum-exp is kept for the backward pass.
 //
@@ -45,8 +45,9 @@ typedef unsigned u32x2_t __attribute__((ext_vector_type(2)));
 
 namespace {
 
-constexpr int D = 128;          // head_dim
-constexpr int PITCH = D + 8;    // LDS row pitch in elements (272 B = 4 banks past a multiple of 64)
+// LDS row pitch in elements, D = head_dim (128 or 64): 272 B = 4 banks past a multiple of 64, resp. 144 B = 36 banks.
+// The rows of a 16-row read then start on 16 different groups of 4 banks, and rows 4 apart 16 banks apart.
+constexpr int pitch(int D) { return D + 8; }
 // Streamed tiles (K, V, Q, dO) keep row r of the tile in LDS row perm(r): inside every group of 16 rows the two
 // 2-bit fields of the row number are exchanged.  A row read (16 lanes = 16 consecutive tile rows, 16 bytes each)
 // still meets 16 different LDS rows, 4 banks apart: all 64 banks once.  A transposing read (32 lanes = 4
@@ -66,21 +67,23 @@ __device__ __forceinline__ f32x16_t mfma(u32x4_t a, u32x4_t b, f32x16_t c) {
 
 // A/B operand whose contraction index is contiguous in the LDS tile: tile row row0 + r with row0 a multiple of 16
 // and prow = perm(r) (computed once per lane)
+template <int D>
 __device__ __forceinline__ u32x4_t frag(const bf16_t* tile, int row0, int prow, int kofs) {
-  return *reinterpret_cast<const u32x4_t*>(tile + (row0 + prow) * PITCH + kofs);
+  return *reinterpret_cast<const u32x4_t*>(tile + (row0 + prow) * pitch(D) + kofs);
 }
 
-// A operand taken from the tile TRANSPOSED: tile is [k][PITCH] (k = contraction index, 16 rows starting
+// A operand taken from the tile TRANSPOSED: tile is [k][pitch] (k = contraction index, 16 rows starting
 // at kbase), the operand row is the tile column nbase + lane % 32, and the 8 contraction values of the
 // lane are k = kbase + {4g..4g+3, 8+4g..8+4g+3}.
+template <int D>
 __device__ __forceinline__ u32x4_t frag_tr(const bf16_t* tile, int kbase, int nbase, int lane) {
   const int g = lane >> 5;
   const int l16 = lane & 15;
   const int col = nbase + ((lane >> 4) & 1) * 16 + (l16 & 3) * 4;
   const int row = kbase + ((l16 >> 2) << 2) + g;   // perm(kbase + 4 g + (l16 >> 2)); kbase is a multiple of 16
   typedef __attribute__((address_space(3))) s16x4_t* lds_ptr_t;
-  const bf16_t* p0 = tile + row * PITCH + col;
-  const bf16_t* p1 = p0 + 2 * PITCH;                // perm of the tile row 8 further on
+  const bf16_t* p0 = tile + row * pitch(D) + col;
+  const bf16_t* p1 = p0 + 2 * pitch(D);                // perm of the tile row 8 further on
   s16x4_t lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_ptr_t)(p0));
   s16x4_t hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_ptr_t)(p1));
   u32x2_t a = __builtin_bit_cast(u32x2_t, lo), b = __builtin_bit_cast(u32x2_t, hi);
@@ -102,15 +105,37 @@ __device__ __forceinline__ u32x4_t pack_half(const f32x16_t& v, int half) {
   return r;
 }
 
+// Probabilities and score gradients enter their products as bf16.  At head size 128 that is one value, rounded.  At
+// head size 64, which was served in fp32 arithmetic, each is the sum of two (the rounded value and the rounded rest, 16
+// bits of mantissa together): with one the results were 1.25 to 1.4 times as far from fp64 as in fp32 arithmetic, with
+// two they are as close (0.17 %, their own rounding); 16 x 2048, 32 / 8 heads: 0.38 + 1.53 ms with one, 0.52 + 1.89 with two.
+constexpr int parts(int D) { return D == 64 ? 2 : 1; }
+template <int NP>
+__device__ __forceinline__ void pack_parts(const f32x16_t& v, int half, u32x4_t (&r)[NP]) {
+  r[0] = pack_half(v, half);
+  if constexpr (NP == 2) {
+#pragma unroll
+    for (int w = 0; w < 4; ++w)
+      r[1][w] = pack2(v[half * 8 + 2 * w] - __uint_as_float(r[0][w] << 16), v[half * 8 + 2 * w + 1] - __uint_as_float(r[0][w] & 0xFFFF0000u));
+  }
+}
+// acc + a * (sum of the parts of b), the small part first
+template <int NP>
+__device__ __forceinline__ f32x16_t mfma_parts(u32x4_t a, const u32x4_t (&b)[NP], f32x16_t acc) {
+#pragma unroll
+  for (int i = NP - 1; i >= 0; --i) acc = mfma(a, b[i], acc);
+  return acc;
+}
+
 // row index (0..31) that accumulator register q of this lane holds
 __device__ __forceinline__ int acc_row(int q, int g) { return 8 * (q >> 2) + 4 * g + (q & 3); }
 
-// Staging of a tile of 64 or 32 rows x 128 columns (bf16) of a row-major global matrix in LDS, without registers:
+// Staging of a tile of 64 or 32 rows x D columns (bf16) of a row-major global matrix in LDS, without registers:
 // LDS-DMA loads (16 bytes per lane straight into LDS, written as instructions so that the waits are this file's
-// own: the compiler does not see that they write LDS).  A 64-row tile with its 272-byte
-// pitch is 17 chunks of 1 KiB of consecutive LDS bytes; wave w issues the chunks w, w + 4, ... and lane l of chunk c
+// own: the compiler does not see that they write LDS).  A 64-row tile with its 272-byte (D = 64: 144-byte)
+// pitch is 17 (9) chunks of 1 KiB of consecutive LDS bytes; wave w issues the chunks w, w + 4, ... and lane l of chunk c
 // fills the bytes c * 1024 + 16 l .. + 16, i.e. LDS row (c * 1024 + 16 l) / 272 = tile row perm(LDS row), 16-byte
-// piece ((c * 1024 + 16 l) % 272) / 16; the 17th piece of a row is its padding and loads from beyond the buffer
+// piece ((c * 1024 + 16 l) % 272) / 16; the last piece of a row is its padding and loads from beyond the buffer
 // (zeros).  Rows past the end of the sequence lie beyond the buffer as well.
 __device__ __forceinline__ i32x4_t rsrc_words(const void* base, uint32_t bytes) {
   const uint64_t a = (uint64_t)base;
@@ -125,11 +150,12 @@ __device__ __forceinline__ uint32_t lds_address(const bf16_t* p) {
   typedef __attribute__((address_space(3))) const bf16_t* lds_p;
   return (uint32_t)(uintptr_t)(lds_p)p;
 }
-template <int ROWS>   // rows of the tile (64, or 32: 8.5 chunks, the second half of the ninth is not part of the tile)
+template <int ROWS, int D>   // rows of the tile (64, or 32: 8.5 or 4.5 chunks, the second half of the last is not part of the tile)
 struct TileDma {
+  static constexpr int PITCH = pitch(D);
   static constexpr int BYTES = ROWS * PITCH * 2;
-  static constexpr int CHUNKS = (BYTES + 1023) / 1024;   // 17 / 9
-  static constexpr int PER_WAVE = (CHUNKS + 3) / 4;      // 5 / 3 (the last only in wave 0)
+  static constexpr int CHUNKS = (BYTES + 1023) / 1024;   // D = 128: 17 / 9, D = 64: 9 / 5
+  static constexpr int PER_WAVE = (CHUNKS + 3) / 4;      // 5 / 3 and 3 / 2 (the last only in wave 0)
   uint32_t voff[PER_WAVE];   // byte offset of the lane's piece from the tile's first element (beyond any buffer: padding)
   __device__ __forceinline__ void init(int ld, int wave, int lane) {
 #pragma unroll
@@ -137,7 +163,7 @@ struct TileDma {
       const int o = (wave + 4 * i) * 1024 + lane * 16;
       const int R = o / (PITCH * 2), piece = (o % (PITCH * 2)) / 16;
       // 2^31 plus any offset inside a sequence (below 2^31, see attn_mfma_supported) stays beyond the buffer and does not wrap
-      voff[i] = (piece < 16 && o < BYTES) ? (uint32_t)(perm(R) * ld + piece * 8) * 2u : 0x80000000u;
+      voff[i] = (piece < D / 8 && o < BYTES) ? (uint32_t)(perm(R) * ld + piece * 8) * 2u : 0x80000000u;
     }
   }
   // tile_bytes: byte offset of the tile's first element in the buffer; wave_s: the wave index as a scalar
@@ -150,38 +176,45 @@ struct TileDma {
 };
 #define TIDE_ATTN_WAIT_DMA() __builtin_amdgcn_s_waitcnt(0x0F70)   /* vmcnt(0) */
 
-// Write a wave's 32 x 128 result, held transposed in 4 accumulators (acc[ct] = rows ct*32.., column =
-// lane % 32 = the wave-local output row), into an LDS tile [128][PITCH] at rows wave*32.. as bf16.
-__device__ __forceinline__ void stage_out(bf16_t* tile, const f32x16_t (&acc)[4], float mul, int wave, int lane) {
+// Write a wave's 32 x D result, held transposed in D / 32 accumulators (acc[ct] = rows ct*32.., column =
+// lane % 32 = the wave-local output row), into an LDS tile [128][pitch] at rows wave*32.. as bf16.
+template <int D>
+__device__ __forceinline__ void stage_out(bf16_t* tile, const f32x16_t (&acc)[D / 32], float mul, int wave, int lane) {
   const int g = lane >> 5, r = wave * 32 + (lane & 31);
 #pragma unroll
-  for (int ct = 0; ct < 4; ++ct)
+  for (int ct = 0; ct < D / 32; ++ct)
 #pragma unroll
     for (int qq = 0; qq < 4; ++qq) {
       const int c = ct * 32 + 8 * qq + 4 * g;
       uint2 v;
       v.x = pack2(acc[ct][qq * 4 + 0] * mul, acc[ct][qq * 4 + 1] * mul);
       v.y = pack2(acc[ct][qq * 4 + 2] * mul, acc[ct][qq * 4 + 3] * mul);
-      *reinterpret_cast<uint2*>(tile + r * PITCH + c) = v;
+      *reinterpret_cast<uint2*>(tile + r * pitch(D) + c) = v;
     }
 }
 
-// Copy the staged [128][128] tile to global rows row0.. (< row_end) of a matrix with leading dim ld.
+// Copy the staged [128][D] tile to global rows row0.. (< row_end) of a matrix with leading dim ld.
+template <int D>
 __device__ __forceinline__ void copy_out(const bf16_t* tile, bf16_t* dst, int64_t row0, int64_t row_end, int ld,
                                          int col0, int tid) {
 #pragma unroll
-  for (int i = 0; i < 8; ++i) {
+  for (int i = 0; i < D / 16; ++i) {
     const int p = tid + i * 256;
-    const int row = p >> 4, piece = p & 15;
+    const int row = p / (D / 8), piece = p % (D / 8);
     if (row0 + row < row_end)
       *reinterpret_cast<i32x4_t*>(dst + (size_t)(row0 + row) * ld + col0 + piece * 8) =
-          *reinterpret_cast<const i32x4_t*>(tile + row * PITCH + piece * 8);
+          *reinterpret_cast<const i32x4_t*>(tile + row * pitch(D) + piece * 8);
   }
 }
 
 constexpr int BQ = 128, BKV = 64;
-constexpr int KV_TILE = BKV * PITCH;  // elements
+constexpr int kv_tile(int D) { return BKV * pitch(D); }  // elements
 
+// Head size 64 halves the operand and accumulator registers and the LDS tiles: 116 / 165 / 125 / 144 registers for the
+// forward, dQ, dV and dK kernels, i.e. 4, 3, 4 and 3 blocks per CU (held to 4, 4, 5 and 3 the dQ and dV kernels spill:
+// backward 1.53 -> 2.73 ms at 16 x 2048, 32 / 8 heads, with one bf16 value per probability).  Against the one-wave-per-row kernels (attention_simple.hip) that
+// served this head size: 6 x 777, 16 / 4 heads, forward + backward 17.55 -> 0.21 ms; 16 x 2048, 32 / 8: 0.38 + 1.53 ms.
+constexpr int blocks_per_cu(int D, int at64, int at128) { return D == 64 ? at64 : at128; }
 // Depth of the operand-fragment rings of the three kernels (0 in the dQ kernel: the plain loop).  Measured when the tiles
 // were still staged through registers, backward at 16 x 2048 / 2 x 16384: dQ 0 / dK-dV 4: 3.56 / 21.4 ms; 2 / 4: 3.48 /
 // 21.0; 4 / 4: 3.79 / 22.7 (the dQ kernel, then at 256 registers, spilled with a ring of four); 0 / 2: 3.60 / 21.2;
@@ -227,9 +260,12 @@ __device__ __forceinline__ Work3 xcd_group_work(int nx, int ny, int nz, int gy) 
 // ------------------------------------------------------------------------------------------------
 // forward
 // ------------------------------------------------------------------------------------------------
-__global__ __launch_bounds__(256, 2) void attn_fwd_mfma_kernel(const bf16_t* __restrict__ qkv, bf16_t* __restrict__ out,
+template <int D>
+__global__ __launch_bounds__(256, blocks_per_cu(D, 4, 2)) void attn_fwd_mfma_kernel(const bf16_t* __restrict__ qkv, bf16_t* __restrict__ out,
                                                             float* __restrict__ lse, int Smax, int nh, int nkv,
                                                             const int* __restrict__ cu, int64_t T, int nseq) {
+  constexpr int NK = D / 16, NC = D / 32;   // k16 steps of a score product, 32-column tiles of a result
+  constexpr int KV_TILE = kv_tile(D);
   extern __shared__ __attribute__((aligned(16))) bf16_t smem[];
   bf16_t* sK = smem;                 // [2][KV_TILE]
   bf16_t* sV = smem + 2 * KV_TILE;   // [2][KV_TILE]
@@ -250,14 +286,14 @@ __global__ __launch_bounds__(256, 2) void attn_fwd_mfma_kernel(const bf16_t* __r
   const int kcol = (nh + kh) * D, vcol = (nh + nkv + kh) * D;
   const float c = kLog2e / sqrtf((float)D);
 
-  u32x4_t qf[8];
+  u32x4_t qf[NK];
 #pragma unroll
-  for (int kk = 0; kk < 8; ++kk)
+  for (int kk = 0; kk < NK; ++kk)
     qf[kk] = __builtin_bit_cast(u32x4_t, __builtin_amdgcn_raw_buffer_load_b128(rs, ((uint32_t)iq * (uint32_t)ld + (uint32_t)(h * D + kk * 16 + g * 8)) * 2u, 0, 0));
 
-  f32x16_t o[4];
+  f32x16_t o[NC];
 #pragma unroll
-  for (int ct = 0; ct < 4; ++ct)
+  for (int ct = 0; ct < NC; ++ct)
 #pragma unroll
     for (int q = 0; q < 16; ++q) o[ct][q] = 0.f;
   float m = -INFINITY, l = 0.f;
@@ -266,7 +302,7 @@ __global__ __launch_bounds__(256, 2) void attn_fwd_mfma_kernel(const bf16_t* __r
   const int nt = (kv_end + BKV - 1) / BKV;
   const i32x4_t rsw = rsrc_words(base, (uint32_t)((size_t)S * ld * 2));
   const int wave_s = __builtin_amdgcn_readfirstlane(wave);
-  TileDma<64> dma;
+  TileDma<64, D> dma;
   dma.init(ld, wave, lane);
   dma.issue(rsw, sK, (uint32_t)kcol * 2u, wave_s);
   dma.issue(rsw, sV, (uint32_t)vcol * 2u, wave_s);
@@ -294,17 +330,17 @@ __global__ __launch_bounds__(256, 2) void attn_fwd_mfma_kernel(const bf16_t* __r
 #pragma unroll
         for (int q = 0; q < 16; ++q) s[jt][q] = 0.f;
       {
-        // the 16 K fragments of the tile through a ring of TIDE_ATTN_KRING registers sets: a fragment is requested
+        // the 2 NK K fragments of the tile through a ring of TIDE_ATTN_KRING registers sets: a fragment is requested
         // that many MFMAs before its own (read, wait, MFMA one after the other leaves the LDS latency, three
         // MFMA times, exposed at every step)
         constexpr int RING = TIDE_ATTN_KRING;
         u32x4_t kb[RING];
 #pragma unroll
-        for (int i = 0; i < RING; ++i) kb[i] = frag(K, (i >> 3) * 32, plr, (i & 7) * 16 + g * 8);
+        for (int i = 0; i < RING; ++i) kb[i] = frag<D>(K, (i / NK) * 32, plr, (i % NK) * 16 + g * 8);
 #pragma unroll
-        for (int i = 0; i < 16; ++i) {
-          s[i >> 3] = mfma(kb[i % RING], qf[i & 7], s[i >> 3]);
-          if (i + RING < 16) kb[i % RING] = frag(K, ((i + RING) >> 3) * 32, plr, ((i + RING) & 7) * 16 + g * 8);
+        for (int i = 0; i < 2 * NK; ++i) {
+          s[i / NK] = mfma(kb[i % RING], qf[i % NK], s[i / NK]);
+          if (i + RING < 2 * NK) kb[i % RING] = frag<D>(K, ((i + RING) / NK) * 32, plr, ((i + RING) % NK) * 16 + g * 8);
           __builtin_amdgcn_sched_barrier(0);
         }
       }
@@ -338,36 +374,39 @@ __global__ __launch_bounds__(256, 2) void attn_fwd_mfma_kernel(const bf16_t* __r
       m = mn;
       if (__builtin_amdgcn_ballot_w64(alpha != 1.0f) != 0) {   // wave-uniform: some row's running max moved
 #pragma unroll
-        for (int ct = 0; ct < 4; ++ct)
+        for (int ct = 0; ct < NC; ++ct)
 #pragma unroll
           for (int q = 0; q < 16; ++q) o[ct][q] *= alpha;
       }
-      u32x4_t pf[4];
+      u32x4_t pf[4][parts(D)];
 #pragma unroll
-      for (int ks = 0; ks < 4; ++ks) pf[ks] = pack_half(s[ks >> 1], ks & 1);
+      for (int ks = 0; ks < 4; ++ks) pack_parts(s[ks >> 1], ks & 1, pf[ks]);
 #pragma unroll
-      for (int ct = 0; ct < 4; ++ct)
+      for (int ct = 0; ct < NC; ++ct)
 #pragma unroll
-        for (int ks = 0; ks < 4; ++ks) o[ct] = mfma(frag_tr(V, ks * 16, ct * 32, lane), pf[ks], o[ct]);
+        for (int ks = 0; ks < 4; ++ks) o[ct] = mfma_parts(frag_tr<D>(V, ks * 16, ct * 32, lane), pf[ks], o[ct]);
     }
     TIDE_ATTN_WAIT_DMA();
     __syncthreads();
   }
 
   const float inv = 1.0f / l;
-  stage_out(smem, o, inv, wave, lane);
+  stage_out<D>(smem, o, inv, wave, lane);
   if (g == 0 && iq < S) lse[stat_index(cu, T, sv, b, h, nh, Smax, iq)] = m * (1.0f / sqrtf((float)D)) + logf(l);
   __syncthreads();
-  copy_out(smem, out, sv.row0 + q0, sv.row0 + min(S, q0 + BQ), nh * D, h * D, tid);
+  copy_out<D>(smem, out, sv.row0 + q0, sv.row0 + min(S, q0 + BQ), nh * D, h * D, tid);
 }
 
 // ------------------------------------------------------------------------------------------------
 // backward, dQ: same streaming structure as the forward pass
 // ------------------------------------------------------------------------------------------------
-__global__ __launch_bounds__(256, 2) void attn_dq_mfma_kernel(const bf16_t* __restrict__ qkv, const bf16_t* __restrict__ dout,
+template <int D>
+__global__ __launch_bounds__(256, blocks_per_cu(D, 3, 2)) void attn_dq_mfma_kernel(const bf16_t* __restrict__ qkv, const bf16_t* __restrict__ dout,
                                                            const float* __restrict__ lse, const float* __restrict__ delta,
                                                            bf16_t* __restrict__ dqkv, int Smax, int nh, int nkv,
                                                            const int* __restrict__ cu, int64_t T, int nseq) {
+  constexpr int NK = D / 16, NC = D / 32;   // k16 steps of a score product, 32-column tiles of a result
+  constexpr int KV_TILE = kv_tile(D);
   extern __shared__ __attribute__((aligned(16))) bf16_t smem[];
   bf16_t* sK = smem;
   bf16_t* sV = smem + 2 * KV_TILE;
@@ -389,9 +428,9 @@ __global__ __launch_bounds__(256, 2) void attn_dq_mfma_kernel(const bf16_t* __re
   const float scale = 1.0f / sqrtf((float)D);
   const float c = kLog2e * scale;
 
-  u32x4_t qf[8], dof[8];
+  u32x4_t qf[NK], dof[NK];
 #pragma unroll
-  for (int kk = 0; kk < 8; ++kk) {
+  for (int kk = 0; kk < NK; ++kk) {
     qf[kk] = __builtin_bit_cast(u32x4_t, __builtin_amdgcn_raw_buffer_load_b128(rs, ((uint32_t)iq * (uint32_t)ld + (uint32_t)(h * D + kk * 16 + g * 8)) * 2u, 0, 0));
     dof[kk] = __builtin_bit_cast(u32x4_t, __builtin_amdgcn_raw_buffer_load_b128(rso, ((uint32_t)iq * (uint32_t)ldo + (uint32_t)(h * D + kk * 16 + g * 8)) * 2u, 0, 0));
   }
@@ -400,9 +439,9 @@ __global__ __launch_bounds__(256, 2) void attn_dq_mfma_kernel(const bf16_t* __re
   const float lse_i = valid ? lse[stat_index(cu, T, sv, b, h, nh, Smax, iq)] * kLog2e : 0.f;
   const float del_i = valid ? delta[stat_index(cu, T, sv, b, h, nh, Smax, iq)] : 0.f;
 
-  f32x16_t dq[4];
+  f32x16_t dq[NC];
 #pragma unroll
-  for (int ct = 0; ct < 4; ++ct)
+  for (int ct = 0; ct < NC; ++ct)
 #pragma unroll
     for (int q = 0; q < 16; ++q) dq[ct][q] = 0.f;
 
@@ -410,7 +449,7 @@ __global__ __launch_bounds__(256, 2) void attn_dq_mfma_kernel(const bf16_t* __re
   const int nt = (kv_end + BKV - 1) / BKV;
   const i32x4_t rsw = rsrc_words(qkv + (size_t)sv.row0 * ld, (uint32_t)((size_t)S * ld * 2));
   const int wave_s = __builtin_amdgcn_readfirstlane(wave);
-  TileDma<64> dma;
+  TileDma<64, D> dma;
   dma.init(ld, wave, lane);
   dma.issue(rsw, sK, (uint32_t)kcol * 2u, wave_s);
   dma.issue(rsw, sV, (uint32_t)vcol * 2u, wave_s);
@@ -429,7 +468,7 @@ __global__ __launch_bounds__(256, 2) void attn_dq_mfma_kernel(const bf16_t* __re
       const bf16_t* K = sK + st * KV_TILE;
       const bf16_t* V = sV + st * KV_TILE;
       const bool diag = j0 + BKV - 1 > qw;
-      u32x4_t dsf[4];
+      u32x4_t dsf[4][parts(D)];
 #pragma unroll
       for (int jt = 0; jt < 2; ++jt) {
         f32x16_t s, dp;
@@ -437,23 +476,23 @@ __global__ __launch_bounds__(256, 2) void attn_dq_mfma_kernel(const bf16_t* __re
         for (int q = 0; q < 16; ++q) { s[q] = 0.f; dp[q] = 0.f; }
 #if TIDE_ATTN_DQ_RING == 0
 #pragma unroll
-        for (int kk = 0; kk < 8; ++kk) {
-          s = mfma(frag(K, jt * 32, plr, kk * 16 + g * 8), qf[kk], s);
-          dp = mfma(frag(V, jt * 32, plr, kk * 16 + g * 8), dof[kk], dp);
+        for (int kk = 0; kk < NK; ++kk) {
+          s = mfma(frag<D>(K, jt * 32, plr, kk * 16 + g * 8), qf[kk], s);
+          dp = mfma(frag<D>(V, jt * 32, plr, kk * 16 + g * 8), dof[kk], dp);
         }
 #else
         {
           // K and V fragments alternately through a ring, each requested TIDE_ATTN_DQ_RING MFMAs ahead (see the forward kernel)
           constexpr int RING = TIDE_ATTN_DQ_RING;
           u32x4_t fb[RING];
-          auto fetch = [&](int i) { return frag((i & 1) ? V : K, jt * 32, plr, (i >> 1) * 16 + g * 8); };
+          auto fetch = [&](int i) { return frag<D>((i & 1) ? V : K, jt * 32, plr, (i >> 1) * 16 + g * 8); };
 #pragma unroll
           for (int i = 0; i < RING; ++i) fb[i] = fetch(i);
 #pragma unroll
-          for (int i = 0; i < 16; ++i) {
+          for (int i = 0; i < 2 * NK; ++i) {
             if (i & 1) dp = mfma(fb[i % RING], dof[i >> 1], dp);
             else s = mfma(fb[i % RING], qf[i >> 1], s);
-            if (i + RING < 16) fb[i % RING] = fetch(i + RING);
+            if (i + RING < 2 * NK) fb[i % RING] = fetch(i + RING);
             __builtin_amdgcn_sched_barrier(0);
           }
         }
@@ -469,20 +508,20 @@ __global__ __launch_bounds__(256, 2) void attn_dq_mfma_kernel(const bf16_t* __re
 #pragma unroll
           for (int q = 0; q < 16; ++q) s[q] = __builtin_amdgcn_exp2f(s[q] * c - lse_i) * (dp[q] - del_i);
         }
-        dsf[2 * jt] = pack_half(s, 0);
-        dsf[2 * jt + 1] = pack_half(s, 1);
+        pack_parts(s, 0, dsf[2 * jt]);
+        pack_parts(s, 1, dsf[2 * jt + 1]);
       }
 #pragma unroll
-      for (int ct = 0; ct < 4; ++ct)
+      for (int ct = 0; ct < NC; ++ct)
 #pragma unroll
-        for (int ks = 0; ks < 4; ++ks) dq[ct] = mfma(frag_tr(K, ks * 16, ct * 32, lane), dsf[ks], dq[ct]);
+        for (int ks = 0; ks < 4; ++ks) dq[ct] = mfma_parts(frag_tr<D>(K, ks * 16, ct * 32, lane), dsf[ks], dq[ct]);
     }
     TIDE_ATTN_WAIT_DMA();
     __syncthreads();
   }
-  stage_out(smem, dq, scale, wave, lane);
+  stage_out<D>(smem, dq, scale, wave, lane);
   __syncthreads();
-  copy_out(smem, dqkv, sv.row0 + q0, sv.row0 + min(S, q0 + BQ), ld, h * D, tid);
+  copy_out<D>(smem, dqkv, sv.row0 + q0, sv.row0 + min(S, q0 + BQ), ld, h * D, tid);
 }
 
 // ------------------------------------------------------------------------------------------------
@@ -498,8 +537,8 @@ namespace {
 #ifndef TIDE_ATTN_DK_ROWS
 #define TIDE_ATTN_DK_ROWS 64
 #endif
-template <int BI> struct DkvStage {
-  static constexpr int Q_TILE = TileDma<BI>::CHUNKS * 512;   // elements: the tile rounded up to whole 1 KiB chunks of the LDS-DMA loads
+template <int BI, int D> struct DkvStage {
+  static constexpr int Q_TILE = TileDma<BI, D>::CHUNKS * 512;   // elements: the tile rounded up to whole 1 KiB chunks of the LDS-DMA loads
   static constexpr int STAGE = 2 * Q_TILE + 4 * BI;          // Q tile, dO tile, then lse[BI] and delta[BI] as floats
 };
 }  // namespace
@@ -507,8 +546,8 @@ template <int BI> struct DkvStage {
 // One gradient per pass (WHICH = 0: dV, 1: dK).  Half the accumulators and, for dV, half the operand
 // registers of the fused kernel: the pass fits 256 VGPRs, two blocks share a CU, and one block's
 // exponentials overlap the other's MFMAs.  The price is that S = Q K^T is computed in both passes.
-template <int WHICH>
-__global__ __launch_bounds__(256, (WHICH == 0 ? 3 : 2)) void attn_dkv_mfma_kernel(const bf16_t* __restrict__ qkv, const bf16_t* __restrict__ dout,
+template <int WHICH, int D>
+__global__ __launch_bounds__(256, WHICH == 0 ? blocks_per_cu(D, 4, 3) : blocks_per_cu(D, 3, 2)) void attn_dkv_mfma_kernel(const bf16_t* __restrict__ qkv, const bf16_t* __restrict__ dout,
                                                             const float* __restrict__ lse, const float* __restrict__ delta,
                                                             bf16_t* __restrict__ dqkv, int Smax, int nh, int nkv,
                                                             const int* __restrict__ cu, int64_t T, int nseq) {
@@ -530,16 +569,17 @@ __global__ __launch_bounds__(256, (WHICH == 0 ? 3 : 2)) void attn_dkv_mfma_kerne
 
   constexpr bool DK = WHICH == 1;
   constexpr int BI = DK ? TIDE_ATTN_DK_ROWS : TIDE_ATTN_DV_ROWS;
-  constexpr int Q_TILE = DkvStage<BI>::Q_TILE, DKV_STAGE = DkvStage<BI>::STAGE;
-  u32x4_t kf[8], vf[DK ? 8 : 1];
+  constexpr int NK = D / 16, NC = D / 32;
+  constexpr int Q_TILE = DkvStage<BI, D>::Q_TILE, DKV_STAGE = DkvStage<BI, D>::STAGE;
+  u32x4_t kf[NK], vf[DK ? NK : 1];
 #pragma unroll
-  for (int kk = 0; kk < 8; ++kk) {
+  for (int kk = 0; kk < NK; ++kk) {
     kf[kk] = __builtin_bit_cast(u32x4_t, __builtin_amdgcn_raw_buffer_load_b128(rs, ((uint32_t)jk * (uint32_t)ld + (uint32_t)(kcol + kk * 16 + g * 8)) * 2u, 0, 0));
     if constexpr (DK) vf[kk] = __builtin_bit_cast(u32x4_t, __builtin_amdgcn_raw_buffer_load_b128(rs, ((uint32_t)jk * (uint32_t)ld + (uint32_t)(vcol + kk * 16 + g * 8)) * 2u, 0, 0));
   }
-  f32x16_t dacc[4];   // dK or dV of this wave's 32 keys
+  f32x16_t dacc[NC];   // dK or dV of this wave's 32 keys
 #pragma unroll
-  for (int ct = 0; ct < 4; ++ct)
+  for (int ct = 0; ct < NC; ++ct)
 #pragma unroll
     for (int q = 0; q < 16; ++q) dacc[ct][q] = 0.f;
 
@@ -550,7 +590,7 @@ __global__ __launch_bounds__(256, (WHICH == 0 ? 3 : 2)) void attn_dkv_mfma_kerne
   const i32x4_t rsq = rsrc_words(qkv + (size_t)sv.row0 * ld, (uint32_t)((size_t)S * ld * 2));
   const i32x4_t rsdo = rsrc_words(dout + (size_t)sv.row0 * ldo, (uint32_t)((size_t)S * ldo * 2));
   const int wave_s = __builtin_amdgcn_readfirstlane(wave);
-  TileDma<BI> dmq, dmo;   // LDS-DMA loads of the Q and the dO tile (their row pitches in memory differ)
+  TileDma<BI, D> dmq, dmo;   // LDS-DMA loads of the Q and the dO tile (their row pitches in memory differ)
   dmq.init(ld, wave, lane);
   dmo.init(ldo, wave, lane);
   float stat = 0.f;  // threads 0..BI-1 carry lse, BI..2BI-1 carry delta of the staged tile
@@ -599,11 +639,11 @@ __global__ __launch_bounds__(256, (WHICH == 0 ? 3 : 2)) void attn_dkv_mfma_kerne
       for (int q = 0; q < 16; ++q) { s[q] = 0.f; dp[q] = 0.f; }
       {
         // Q (and, in the dK pass, dO) fragments through a ring, each requested TIDE_ATTN_DKV_RING MFMAs ahead
-        constexpr int RING = TIDE_ATTN_DKV_RING, NF = DK ? 16 : 8;
+        constexpr int RING = TIDE_ATTN_DKV_RING, NF = DK ? 2 * NK : NK;
         u32x4_t fb[RING];
         auto fetch = [&](int i) {
-          if constexpr (DK) return frag((i & 1) ? dOt : Qt, hf * 32, plr, (i >> 1) * 16 + g * 8);
-          else return frag(Qt, hf * 32, plr, i * 16 + g * 8);
+          if constexpr (DK) return frag<D>((i & 1) ? dOt : Qt, hf * 32, plr, (i >> 1) * 16 + g * 8);
+          else return frag<D>(Qt, hf * 32, plr, i * 16 + g * 8);
         };
 #pragma unroll
         for (int i = 0; i < RING; ++i) fb[i] = fetch(i);
@@ -641,12 +681,14 @@ __global__ __launch_bounds__(256, (WHICH == 0 ? 3 : 2)) void attn_dkv_mfma_kerne
       };
       if (diag) probs(std::true_type{});
       else probs(std::false_type{});
-      const u32x4_t pf[2] = {pack_half(s, 0), pack_half(s, 1)};
+      u32x4_t pf[2][parts(D)];
+      pack_parts(s, 0, pf[0]);
+      pack_parts(s, 1, pf[1]);
       const bf16_t* Xt = DK ? Qt : dOt;   // dK += dS^T Q, dV += P^T dO
 #pragma unroll
-      for (int ct = 0; ct < 4; ++ct)
+      for (int ct = 0; ct < NC; ++ct)
 #pragma unroll
-        for (int ks = 0; ks < 2; ++ks) dacc[ct] = mfma(frag_tr(Xt, hf * 32 + ks * 16, ct * 32, lane), pf[ks], dacc[ct]);
+        for (int ks = 0; ks < 2; ++ks) dacc[ct] = mfma_parts(frag_tr<D>(Xt, hf * 32 + ks * 16, ct * 32, lane), pf[ks], dacc[ct]);
     }
     }
     if (u + 1 < ntiles) sstore(st ^ 1);
@@ -654,17 +696,17 @@ __global__ __launch_bounds__(256, (WHICH == 0 ? 3 : 2)) void attn_dkv_mfma_kerne
     __syncthreads();
   }
   const int64_t r0 = sv.row0 + j0, r1 = sv.row0 + min(S, j0 + 128);
-  stage_out(smem, dacc, DK ? scale : 1.0f, wave, lane);
+  stage_out<D>(smem, dacc, DK ? scale : 1.0f, wave, lane);
   __syncthreads();
-  copy_out(smem, dqkv, r0, r1, ld, DK ? kcol : vcol, tid);
+  copy_out<D>(smem, dqkv, r0, r1, ld, DK ? kcol : vcol, tid);
 }
 
 
 // ------------------------------------------------------------------------------------------------
 bool attn_mfma_supported(const AttnArgs& a) {
-  if (a.dtype != kBF16 || a.dh != D) return false;
+  if (a.dtype != kBF16 || (a.dh != 128 && a.dh != 64)) return false;
   if (a.B <= 0 || a.S <= 0 || a.B > 65535 || a.nh > 65535) return false;
-  const int64_t ld = (int64_t)(a.nh + 2 * a.nkv) * D;
+  const int64_t ld = (int64_t)(a.nh + 2 * a.nkv) * a.dh;
   if ((int64_t)a.S * ld * 2 >= ((int64_t)1 << 31)) return false;   // 32-bit offsets inside one sequence
   if (((uintptr_t)a.qkv | (uintptr_t)a.out | (uintptr_t)a.dout | (uintptr_t)a.dqkv) & 15) return false;
   if ((int64_t)((a.S + BQ - 1) / BQ) * a.nh * a.B >= ((int64_t)1 << 31)) return false;   // 1-D grids
@@ -672,13 +714,12 @@ bool attn_mfma_supported(const AttnArgs& a) {
 }
 
 namespace {
-constexpr size_t kFwdSmem = (size_t)4 * KV_TILE * sizeof(bf16_t);           // 69632 B (>= the 128 x PITCH output tile)
-constexpr size_t kOutTile = (size_t)128 * PITCH * sizeof(bf16_t);
-constexpr size_t dkv_smem(int bi) {
-  const size_t st = (size_t)2 * (bi == 64 ? DkvStage<64>::STAGE : DkvStage<32>::STAGE) * sizeof(bf16_t);
-  return st > kOutTile ? st : kOutTile;
+constexpr size_t fwd_smem(int D) { return (size_t)4 * kv_tile(D) * sizeof(bf16_t); }   // 69632 / 36864 B (>= the 128 x pitch output tile)
+template <int BI, int D>
+constexpr size_t dkv_smem() {
+  const size_t st = (size_t)2 * DkvStage<BI, D>::STAGE * sizeof(bf16_t), out = (size_t)128 * pitch(D) * sizeof(bf16_t);
+  return st > out ? st : out;
 }
-constexpr size_t kDvSmem = dkv_smem(TIDE_ATTN_DV_ROWS), kDkSmem = dkv_smem(TIDE_ATTN_DK_ROWS);
 
 hipError_t set_smem(const void* f, size_t bytes, bool& done) {
   if (done) return hipSuccess;
@@ -686,41 +727,46 @@ hipError_t set_smem(const void* f, size_t bytes, bool& done) {
   if (e == hipSuccess) done = true;
   return e;
 }
-}  // namespace
 
-hipError_t launch_attn_fwd_mfma(const AttnArgs& a, hipStream_t s) {
+template <int D>
+hipError_t launch_fwd(const AttnArgs& a, hipStream_t s) {
   static bool done = false;
-  hipError_t e = set_smem((const void*)attn_fwd_mfma_kernel, kFwdSmem, done);
+  hipError_t e = set_smem((const void*)attn_fwd_mfma_kernel<D>, fwd_smem(D), done);
   if (e != hipSuccess) return e;
   const dim3 grid((unsigned)((int64_t)((a.S + BQ - 1) / BQ) * a.nh * a.B));   // 1-D: the kernel maps blocks to work itself
   ProfScope ps("attn_fwd_mfma", 2.0 * a.B * a.nh * D * (double)a.S * (a.S + 1), 0, s);
-  hipLaunchKernelGGL(attn_fwd_mfma_kernel, grid, dim3(256), kFwdSmem, s, (const bf16_t*)a.qkv, (bf16_t*)a.out, a.lse, a.S, a.nh, a.nkv, a.cu_seqlens, a.total_rows, a.B);
+  hipLaunchKernelGGL(attn_fwd_mfma_kernel<D>, grid, dim3(256), fwd_smem(D), s, (const bf16_t*)a.qkv, (bf16_t*)a.out, a.lse, a.S, a.nh, a.nkv, a.cu_seqlens, a.total_rows, a.B);
   return hipGetLastError();
 }
 
-hipError_t launch_attn_bwd_mfma(const AttnArgs& a, hipStream_t s) {
-  static bool done_q = false;
+template <int D>
+hipError_t launch_bwd(const AttnArgs& a, hipStream_t s) {
+  constexpr size_t kDvSmem = dkv_smem<TIDE_ATTN_DV_ROWS, D>(), kDkSmem = dkv_smem<TIDE_ATTN_DK_ROWS, D>();
+  static bool done_q = false, done_v = false, done_k = false;
   hipError_t e = launch_attn_delta(a, s);
   if (e != hipSuccess) return e;
-  e = set_smem((const void*)attn_dq_mfma_kernel, kFwdSmem, done_q);
+  e = set_smem((const void*)attn_dq_mfma_kernel<D>, fwd_smem(D), done_q);
   if (e != hipSuccess) return e;
   const dim3 gq((unsigned)((int64_t)((a.S + BQ - 1) / BQ) * a.nh * a.B)), gkv((unsigned)((int64_t)((a.S + 127) / 128) * a.nkv * a.B));
   const double pairs = (double)a.B * a.nh * D * (double)a.S * (a.S + 1) / 2.0;  // (query, key, channel) triples
   {
     ProfScope ps("attn_dq_mfma", 6.0 * pairs, 0, s);   // S, dP and dQ products
-    hipLaunchKernelGGL(attn_dq_mfma_kernel, gq, dim3(256), kFwdSmem, s, (const bf16_t*)a.qkv, (const bf16_t*)a.dout, a.lse, a.delta, (bf16_t*)a.dqkv, a.S, a.nh, a.nkv, a.cu_seqlens, a.total_rows, a.B);
+    hipLaunchKernelGGL(attn_dq_mfma_kernel<D>, gq, dim3(256), fwd_smem(D), s, (const bf16_t*)a.qkv, (const bf16_t*)a.dout, a.lse, a.delta, (bf16_t*)a.dqkv, a.S, a.nh, a.nkv, a.cu_seqlens, a.total_rows, a.B);
     e = hipGetLastError();
     if (e != hipSuccess) return e;
   }
-  static bool done_v = false, done_k = false;
-  e = set_smem((const void*)attn_dkv_mfma_kernel<0>, kDvSmem, done_v);
+  e = set_smem((const void*)attn_dkv_mfma_kernel<0, D>, kDvSmem, done_v);
   if (e != hipSuccess) return e;
-  e = set_smem((const void*)attn_dkv_mfma_kernel<1>, kDkSmem, done_k);
+  e = set_smem((const void*)attn_dkv_mfma_kernel<1, D>, kDkSmem, done_k);
   if (e != hipSuccess) return e;
   ProfScope ps("attn_dkv_mfma", 10.0 * pairs, 0, s);   // dV pass: S, dV; dK pass: S, dP, dK
-  hipLaunchKernelGGL(attn_dkv_mfma_kernel<0>, gkv, dim3(256), kDvSmem, s, (const bf16_t*)a.qkv, (const bf16_t*)a.dout, a.lse, a.delta, (bf16_t*)a.dqkv, a.S, a.nh, a.nkv, a.cu_seqlens, a.total_rows, a.B);
-  hipLaunchKernelGGL(attn_dkv_mfma_kernel<1>, gkv, dim3(256), kDkSmem, s, (const bf16_t*)a.qkv, (const bf16_t*)a.dout, a.lse, a.delta, (bf16_t*)a.dqkv, a.S, a.nh, a.nkv, a.cu_seqlens, a.total_rows, a.B);
+  hipLaunchKernelGGL((attn_dkv_mfma_kernel<0, D>), gkv, dim3(256), kDvSmem, s, (const bf16_t*)a.qkv, (const bf16_t*)a.dout, a.lse, a.delta, (bf16_t*)a.dqkv, a.S, a.nh, a.nkv, a.cu_seqlens, a.total_rows, a.B);
+  hipLaunchKernelGGL((attn_dkv_mfma_kernel<1, D>), gkv, dim3(256), kDkSmem, s, (const bf16_t*)a.qkv, (const bf16_t*)a.dout, a.lse, a.delta, (bf16_t*)a.dqkv, a.S, a.nh, a.nkv, a.cu_seqlens, a.total_rows, a.B);
   return hipGetLastError();
 }
+}  // namespace
+
+hipError_t launch_attn_fwd_mfma(const AttnArgs& a, hipStream_t s) { return a.dh == 64 ? launch_fwd<64>(a, s) : launch_fwd<128>(a, s); }
+hipError_t launch_attn_bwd_mfma(const AttnArgs& a, hipStream_t s) { return a.dh == 64 ? launch_bwd<64>(a, s) : launch_bwd<128>(a, s); }
 
 }  // namespace tide

@@ -1,0 +1,77 @@
+"""Matrix-instruction attention at both head sizes (64 and 128) and at the edges of its tiles, forward and backward,
+against attention in fp64 on the same bf16 values; and head size 64 in packed batches.  The outputs are rounded to bf16
+(2^-9 relative) and the probabilities and score gradients to bf16 before their products, each 2^-9 off at most and in
+random directions: 1 % of the largest value bounds what was seen (0.3 %) three times over."""
+import math
+
+import numpy as np
+import pytest
+import torch
+
+from tests.gpu_util import DEV, stream, sync
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def B():
+    from paper_2602_05145_amd import binding
+    return binding
+
+
+def _reference(qkv, dout, n, nh, nkv, dh):
+    x = qkv.double().cpu().requires_grad_()
+    q, k, v = (t.transpose(0, 1) for t in x.view(n, nh + 2 * nkv, dh).split([nh, nkv, nkv], 1))
+    k, v = (t.repeat_interleave(nh // nkv, 0) for t in (k, v))
+    s = q @ k.transpose(1, 2) / math.sqrt(dh)
+    s = s.masked_fill(torch.ones(n, n, dtype=torch.bool).triu(1), -math.inf)
+    o = (torch.softmax(s, -1) @ v).transpose(0, 1).reshape(n, nh * dh)
+    o.backward(dout.double().cpu())
+    return o.detach(), torch.logsumexp(s, -1).detach(), x.grad
+
+
+@pytest.mark.parametrize("dh", [64, 128])
+@pytest.mark.parametrize("S,nh,nkv", [(1, 2, 1), (31, 2, 2), (64, 4, 2), (65, 3, 1), (127, 4, 4), (128, 8, 8), (129, 16, 8), (333, 8, 2), (777, 4, 1)])
+def test_attention_at_the_edges_of_its_tiles(B, dh, S, nh, nkv):
+    bt = 2
+    g = torch.Generator(device=DEV).manual_seed(S * dh + nh)
+    qkv = torch.randn(bt * S, (nh + 2 * nkv) * dh, device=DEV, generator=g).bfloat16()
+    dout = torch.randn(bt * S, nh * dh, device=DEV, generator=g).bfloat16()
+    out, dqkv = torch.full_like(dout, float("nan")), torch.full_like(qkv, float("nan"))
+    lse, delta = (torch.full((bt, nh, S), float("nan"), device=DEV) for _ in range(2))
+    print(f"attention S={S} nh={nh} nkv={nkv} dh={dh}", flush=True)
+    B.tide_attention_fwd(bt, S, nh, nkv, dh, qkv, out, lse, 1, stream())
+    sync()
+    B.tide_attention_bwd(bt, S, nh, nkv, dh, qkv, out, dout, lse, delta, dqkv, 1, stream())
+    sync()
+    for b in range(bt):
+        rows = slice(b * S, (b + 1) * S)
+        ro, rl, rg = _reference(qkv[rows], dout[rows], S, nh, nkv, dh)
+        assert float((out[rows].double().cpu() - ro).abs().max()) < 1e-2 * float(ro.abs().max())
+        assert float((lse[b].double().cpu() - rl).abs().max()) < 1e-5 * max(1.0, float(rl.abs().max()))
+        w = nh * dh
+        for part in (slice(0, w), slice(w, w + nkv * dh), slice(w + nkv * dh, None)):   # dq, dk, dv
+            assert float((dqkv[rows, part].double().cpu() - rg[:, part]).abs().max()) < 1e-2 * max(1e-30, float(rg[:, part].abs().max())) or S == 1
+
+
+@pytest.mark.parametrize("lens,tail", [([200, 56, 129, 3], 12), ([1] * 9 + [250], 5)])
+def test_head_size_64_in_a_packed_training_step(lens, tail):
+    from oracle import tide_oracle as O
+    from paper_2602_05145_amd import runtime, workloads as W
+    T = sum(lens) + tail
+    cfg = W.get_config("small", batch=1, seq=T, target_hidden=256, hidden=256, n_heads=4, n_kv_heads=2, head_dim=64, ffn=512, vocab=2048,
+                       mask="none", seed=77)
+    wl = W.make_workload(cfg)
+    cu = np.concatenate([[0], np.cumsum(lens)]).astype(np.int32)
+    tr = runtime.trainer_from_workload(cfg, wl)
+    tr.set_packed(cu)
+    tr.workspace.fill_(0xFF)
+    print(f"packed head size 64 lens={lens}", flush=True)
+    tr.train_step_packed(cfg["lr"])
+    sync()
+    p0 = {k: np.asarray(v, np.float64) for k, v in wl["params"].items()}
+    loss, grads = O.train_quantities_packed(cfg, p0, wl["hidden"].astype(np.float64), wl["tokens"], wl["mask"], cu)[:2]
+    assert abs(float(tr.loss.item()) - loss) < 1e-2 * abs(loss)
+    for k, ref in grads.items():
+        a, b = tr.host(tr.grads)[k].reshape(-1), ref.reshape(-1)
+        assert a @ b / (np.linalg.norm(a) * np.linalg.norm(b)) > 0.999, k
