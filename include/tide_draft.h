@@ -350,10 +350,9 @@ int64_t tide_draft_workspace_offset(const tide_draft_config *cfg, const char *na
  * in_dtype: dtype of A and B; out_dtype: dtype of C (TIDE_DTYPE_*).  accumulate
  * != 0 adds to C instead of overwriting.  residual (may be NULL) is a [M,N]
  * matrix of out_dtype added to the result.
- * workspace (DEVICE, 16-byte aligned, optional): scratch for the split of a partly filled last round of tiles.
- * A product whose 256 x 256 tiles leave the last round of the 256 compute units at most half full (and whose
- * result is float, without residual) can have those tiles split over K; the partial sums go to the workspace
- * and are added to C in a fixed order by a second small kernel (deterministic).  tide_gemm_workspace_bytes
+ * workspace (DEVICE, 16-byte aligned, optional): scratch for products whose tiles do not fill the 256 compute
+ * units.  Their tiles (all of them, or those of a partly filled last round) are split over K, the partial sums go to
+ * the workspace and are added in a fixed order by a second small kernel (deterministic).  tide_gemm_workspace_bytes
  * gives the bytes that takes (0: the call is never split; bf16 inputs are assumed); with workspace NULL or
  * smaller than that, nothing is split and the result is the same up to the order of the fp32 additions. */
 size_t tide_gemm_workspace_bytes(int layout, int64_t M, int64_t N, int64_t K, int out_dtype);

@@ -4,45 +4,32 @@
 //   TN  C = A[K,M]^T B[K,N]   weight gradients dW = dY^T X  (both operands contracted over rows)
 //
 // Design
-//   * A block computes a BM x BN tile (256x256 with 8 wavefronts = 2 per SIMD, or 128x128 with 4) with
-//     v_mfma_f32_32x32x16_bf16; a wave owns TM x TN MFMA tiles (4x2 or 2x2).  Two waves per SIMD matter:
-//     one wave alone cannot issue MFMAs back to back (measured ~83 % of the multi-wave MFMA rate), and a
-//     four-wave 256x256 variant (128x128 per wave, a third less LDS read traffic) is slower: 10-20 % under the
-//     compiler's schedule, and still 2.5 % (NT), 3 % (NN) and 8 % (TN) with the pinned schedule of the
-//     16x16x32 kernel below (its WAVES_N = 2 instantiation: 256 accumulator registers in AGPRs, no spills).
-//   * K is walked in slabs through an LDS ring that always holds 128 k-columns and is filled by LDS-DMA
-//     buffer loads (global -> LDS without passing through registers, hardware zero-fill outside the valid
-//     extent, so ragged M / N / K need no special code).  What bounds this kernel is the memory side: with
-//     every operand row aliased to one line (all loads hit) the same code runs 25-40 % faster.  The ring
-//     shape of the 32x32x16 kernel follows the operand layout: with a K-major operand the slab is 64 deep
-//     (TWO stages): each of its rows then fetches one whole 128-byte line instead of two 64-byte halves;
-//     when both operands are row-major over K (TN) their rows are contiguous anyway and FOUR stages of 32
-//     win because the loads of slab k+3 are issued while slab k is multiplied.  The 16x16x32 kernel (the
-//     one the large launches use) walks slabs of 64 through five units in every layout (see there).
-//   * Synchronisation is manual: one `s_waitcnt vmcnt(n)` (own DMA of the next slab has landed, younger
-//     slabs stay in flight) and one `s_barrier` per slab.  Each stage is its own __shared__ array and every
-//     read address is "array + per-lane offset + constant": the compiler can then tell that the operand
-//     reads do not alias the DMA writes in flight and does not drain vmcnt before them (it loses that
-//     information on address chains more than a few steps long, and then silently waits).  Slabs past K
-//     are dummies (their loads fall outside the buffer and zero-fill the free stage) so the steady state
-//     has no branches.
-//   * The two-stage loop is software-pipelined across slabs: the barrier of a slab sits before its last
-//     k16 quarter, when every wave holds that quarter's operands in registers; the DMA of slab k+2 and the
-//     first operand reads of slab k+1 are issued in the shadow of that quarter's MFMAs.
-//   * Instruction order inside a k16 quarter is pinned with sched_group_barrier: MFMA / LDS read (or DMA
-//     issue) alternate, so LDS and address traffic hides in the MFMA shadow.
-//   * LDS layout.  A "K-major" operand (contraction index contiguous in memory) is stored [row][BK] with
-//     the 16-byte pieces of a row XOR-swizzled by (row >> 1) & 7 (BK 64) or (row >> 2) & 3 (BK 32): DMA can
-//     only write 1 KiB contiguous per instruction, so padding is impossible, and the swizzle makes the
-//     16-byte operand reads of 16 consecutive rows hit 16 different bank groups.  An operand whose
-//     contraction index is the slow one (B of NN, both operands of TN) is stored as in memory, [k][row],
-//     and transposed on the way to the MFMA by ds_read_b64_tr_b16 (two per MFMA operand: four k each);
-//     the pieces of k-row k are XOR-swizzled by (k & 3) << 2 so that the four k-rows of one such read lie
-//     in different banks.  No transposed copy of an operand ever exists in HBM.
+//   * A block computes a tile of 256 x 256 (8 wavefronts, the block owns its CU) or 128 x 128 (4 wavefronts, two blocks
+//     share a CU) with v_mfma_f32_16x16x32_bf16; a wave owns 128 x 64 or 64 x 64 of it.  Two waves per SIMD either way: one
+//     alone cannot issue MFMAs back to back (measured ~83 % of the multi-wave MFMA rate).
+//   * K is walked in slabs of 64 through five LDS units (see the kernel), filled by LDS-DMA buffer loads (global -> LDS
+//     without passing through registers, hardware zero-fill outside the valid extent, so ragged M / N / K need no special
+//     code).  What bounds the large tile is the memory side next to the matrix pipes: with every operand row aliased to
+//     one line (all loads hit) the same code runs 25-40 % faster; the small tile needs twice the operand bytes per flop and is
+//     bound by their delivery from L2 (1.16 PFLOP/s at 17-19 TB/s).
+//   * Synchronisation is manual: one `s_waitcnt vmcnt(n)` (own DMA of the next slab has landed, younger loads stay in
+//     flight) and one `s_barrier` per slab, before its last quarter.  Each unit is its own __shared__ array and every read
+//     address is "array + per-lane offset + constant": the compiler can then tell that the operand reads do not alias the
+//     DMA writes in flight and does not drain vmcnt before them.  Slabs past K are dummies (their loads fall outside the
+//     buffer and zero-fill the free unit).  The instruction order is pinned: MFMA / LDS read (or DMA issue) alternate, so
+//     LDS and address traffic hides in the MFMA shadow.
+//   * LDS layout.  A "K-major" operand (contraction index contiguous in memory) is stored [row][64] with the 16-byte
+//     pieces of a row XOR-swizzled by (row >> 1) & 7: DMA can only write 1 KiB contiguous per instruction, so padding is
+//     impossible, and the swizzle makes the 16-byte operand reads of 16 consecutive rows hit 16 different bank groups.  An
+//     operand whose contraction index is the slow one (B of NN, both operands of TN) is stored as in memory, [k][row], and
+//     transposed on the way to the MFMA by ds_read_b64_tr_b16 (two per MFMA operand: four k each), swizzled by
+//     TIDE_RSWZ.  No transposed copy of an operand ever exists in HBM.
 //   * The contraction may run over two operand pairs back to back (d b = dGate W_gate + dUp W_up), and
 //     the epilogue fuses alpha (host and device scalar), a residual add, accumulation into C and the cast.
 //     bf16 results without residual/accumulate go through a wave-private LDS patch to leave as 16-byte
-//     row segments; everything else is stored straight from the accumulators (128-byte row segments).
+//     row segments; everything else is stored straight from the accumulators.
+//   * Tiles that do not fill the chip are split over K (two forms, see MfmaParams), and the tile is chosen with that
+//     in mind (tile_edge).
 //   * Work-groups are renumbered so that each of the 8 XCDs (round-robin dispatch) gets a contiguous
 //     range of tiles, walked in groups of 4 tile-rows: neighbouring tiles share A/B panels in that
 //     XCD's L2.
@@ -73,13 +60,54 @@ struct MfmaParams {
   int tiles_m, tiles_n;
   const int* m_dev; int m_off;   // optional device-side M: effective M = clamp(*m_dev - m_off, 0, M)
   const int* k_dev; int k_off;   // optional device-side K (pair 0 only)
-  // Split of the last, partly filled round of tiles over K (fp32 results only): tiles [0, split_full) are whole;
-  // each later tile is worked on by split_s blocks, each over 1/split_s of the slabs; part 0 writes C, part
-  // j > 0 writes its 256 x 256 partial sum to split_scratch[(j - 1) * (tiles - split_full) + tile - split_full],
-  // and splitk_fixup_kernel adds the partial sums to C in a fixed order afterwards.  split_s <= 1: no split.
-  int split_s, split_full;
+  // Split over K.  kSplitTail (256 x 256 tiles, fp32 results): tiles [0, split_full) are whole; each later tile is
+  // worked on by split_s blocks, each over 1/split_s of the slabs; part 0 writes C, part j > 0 writes its 256 x 256
+  // partial sum to split_scratch[(j - 1) * (tiles - split_full) + tile - split_full], and splitk_fixup_kernel adds the
+  // partial sums to C in a fixed order afterwards.  kSplitAll: the tiles from split_all().full on are worked on by
+  // split_all().parts blocks each, every one of which writes its partial sum to split_scratch[part * tail + tile - full];
+  // splitk_reduce_kernel adds them in the order of the parts and does what the epilogue would.  Both kernels take the
+  // number of parts from the sizes they find on the device; with one part the epilogue has written C.
+  int split, split_s, split_full;
   float* split_scratch;
 };
+enum : int { kSplitNone = 0, kSplitTail = 1, kSplitAll = 2 };
+
+// How a launch whose tiles do not fill the chip is split over K.  ns, measured on 256 x 256 and on 128 x 128 tiles:
+//   slab       a slab of 64: 1410, or 550 (750 once blocks share a CU, 870 at two per CU: 1.16 PFLOP/s, the rate
+//              at which L2 delivers the operands of 128 x 128 tiles)
+//   traffic    one tile's partial sum, written and read back at about 8 TB/s: 65 / 16
+//   fixed      the second launch, and what storing an fp32 partial sum takes longer than storing a bf16 result: 12000 / 5000
+// With nk slabs and t tiles to split, n parts save slab nk (1 - 1 / n) - traffic t n, most at n = sqrt(slab nk / (traffic t));
+// that has to exceed the fixed costs, and a part keeps a few slabs.
+struct SplitCost { int slots, min_slabs, slab, traffic, fixed; };
+__host__ __device__ inline constexpr SplitCost split_cost(int BT) {
+  return BT == 256 ? SplitCost{256, 8, 1410, 65, 12000} : SplitCost{512, 4, 550, 16, 5000};
+}
+__host__ __device__ inline int split_parts(int BT, int tiles, int slabs) {
+  const SplitCost c = split_cost(BT);
+  if (tiles <= 0) return 1;
+  const int by_slots = c.slots / tiles, by_k = slabs / c.min_slabs;
+  int lo = 1, hi = by_slots < by_k ? by_slots : by_k;
+  if (hi < 2) return 1;
+  while (lo < hi) {   // largest n with traffic t n^2 <= slab nk
+    const int n = (lo + hi + 1) / 2;
+    if ((int64_t)c.traffic * tiles * n * n <= (int64_t)c.slab * slabs) lo = n; else hi = n - 1;
+  }
+  if (lo < 2) return 1;
+  const int64_t part = (slabs + lo - 1) / lo;
+  const int64_t cost = c.fixed + (int64_t)c.traffic * tiles * lo + (BT == 128 && tiles * lo > 256 ? 250 * part : 0);
+  return c.slab * (slabs - part) > cost ? lo : 1;
+}
+struct SplitAll { int full, parts; };   // tiles that are not split, and the parts of each of the others
+template <int BT>
+__host__ __device__ inline SplitAll split_all(int tiles, int slabs) {
+  // whole rounds of 256 large tiles stay whole (more than 256 small ones are never split)
+  const int full = BT == 256 ? tiles / 256 * 256 : 0;
+  const int n = split_parts(BT, tiles - full, slabs);
+  return n > 1 ? SplitAll{full, n} : SplitAll{tiles, 1};
+}
+// 64-deep slabs of a contraction over one or two operand pairs
+__host__ __device__ inline int split_slabs(int K, int K2) { return (K + 63) / 64 + (K2 + 63) / 64; }
 
 // tile index (XCD-contiguous order, groups of 4 tile rows) -> tile coordinates
 #ifndef TIDE_TILE_GROUP
@@ -103,12 +131,10 @@ __device__ __forceinline__ __amdgpu_buffer_rsrc_t make_rsrc(const void* base, ui
 // wait until at most n of this wave's vector-memory operations are outstanding (vmcnt only)
 #define TIDE_WAIT_VMCNT(n) __builtin_amdgcn_s_waitcnt(((n) & 15) | (((n) >> 4) << 14) | (7 << 4) | (15 << 8))
 
-// swizzle of a row-major stage: 16-byte piece index ^= (k-row & 3) << 2, i.e. the four k-rows that one
-// transposing read touches sit in four different 64-byte bank groups.  The 16x16x32 kernel also flips bit 1 of the
-// piece index with bit 3 of the k-row: there the 16-lane groups of a read differ in k (by 8 rows) and not in the
-// column, and the flip keeps two neighbouring groups on different banks.
-#define TIDE_RSWZ(kq) ((kq) << 2)
-#define TIDE_RSWZ16(krow) ((((krow) & 3) << 2) ^ ((((krow) >> 3) & 1) << 1))
+// swizzle of a row-major stage: 16-byte piece index ^= (k-row & 3) << 2, i.e. the four k-rows that one transposing read
+// touches sit in four different 64-byte bank groups; and bit 1 of the piece index is flipped with bit 3 of the k-row: the
+// 16-lane groups of a read differ in k by 8 rows, and the flip keeps two neighbouring groups on different banks.
+#define TIDE_RSWZ(krow) ((((krow) & 3) << 2) ^ ((((krow) >> 3) & 1) << 1))
 constexpr uint32_t kOobOffset = 0x7FFFFFF0u;  // beyond any buffer extent used here: the load returns zeros
 
 // One LDS-DMA load of 16 bytes per lane, written as an instruction: the 64 lanes' data go to 1 KiB of LDS at
@@ -128,7 +154,7 @@ __device__ __forceinline__ void dma16(i32x4_t rsrc, uint32_t lds_addr, uint32_t 
 }
 
 // One operand (A or B) of one block: R rows (BM or BN) of the tile, either K-major or row-major over K.
-template <int R, int NW, bool RMAJ, int T, int BK, int MI = 32>   // T = 32-row MFMA tiles per wave along this dimension; BK = slab depth; MI = MFMA tile edge
+template <int R, int NW, bool RMAJ, int T16, int BK>   // T16 = 16-row MFMA fragments per wave along this dimension; BK = slab depth
 struct Operand {
   static constexpr int STAGE = R * BK;                                   // elements per stage
   static constexpr int CHUNKS = STAGE * 2 / 1024;                        // 1 KiB DMA instructions per stage
@@ -139,7 +165,6 @@ struct Operand {
   static constexpr int KPIECES = BK / 8;                                 // 16-byte pieces per K-major row (4 or 8)
   static constexpr int KROWS = 64 / KPIECES;                             // K-major rows per DMA chunk (16 or 8)
   static constexpr int SWZ_SHIFT = (BK == 32) ? 2 : 1;                   // swizzle: piece ^= (row >> shift) & (KPIECES-1)
-  static constexpr int kReadsPerQuarter = RMAJ ? 2 * T : T;              // LDS read instructions per k16 quarter
 
   // Stateless on purpose: the tile pointers and extents stay plain kernel locals (SGPRs).  Bundling them
   // in a struct with the per-lane offsets made the compiler keep that struct in scratch memory, the
@@ -150,12 +175,12 @@ struct Operand {
   static __device__ __forceinline__ void lane_offsets(int ld, int wave, int lane, uint32_t (&off)[PER_WAVE],
                                                       int (&piece)[PER_WAVE]) {
     if (RMAJ) {
-      // chunk = RPC k-rows x (R*2) bytes; LDS slot (krow, s) holds piece s ^ ((krow & 3) << 2) of that k-row
+      // chunk = RPC k-rows x (R*2) bytes; LDS slot (krow, s) holds piece s ^ TIDE_RSWZ(krow) of that k-row
       const int kr = lane / PPR, pc = lane % PPR;
 #pragma unroll
       for (int i = 0; i < PER_WAVE; ++i) {
         const int krow = (wave * PER_WAVE + i) * RPC + kr;
-        off[i] = (uint32_t)((krow * ld + (pc ^ (MI == 16 ? TIDE_RSWZ16(krow) : TIDE_RSWZ(krow & 3))) * 8) * 2);
+        off[i] = (uint32_t)((krow * ld + (pc ^ TIDE_RSWZ(krow)) * 8) * 2);
         piece[i] = 0;
       }
     } else {
@@ -170,35 +195,11 @@ struct Operand {
     }
   }
 
-  // Issue the DMA loads of the slab [k0, k0+BK) into `stage`.  tile = operand pointer already offset to
-  // the tile's first row (K-major) or first column (row-major); rows_valid = tile rows inside the matrix
-  // (K-major) ; cols_left = matrix columns from the tile's first column on (row-major); Kc = contraction
-  // length.  A slab with k0 >= Kc is a dummy: every load is out of range and writes zeros.
-  static __device__ __forceinline__ void issue(bf16_t* stage, const bf16_t* tile, int ld, int rows_valid, int cols_left,
-                                               int k0, int Kc, const uint32_t (&off)[PER_WAVE],
-                                               const int (&piece)[PER_WAVE], int wave) {
-    if (RMAJ) {
-      const int kv = min(BK, Kc - k0);   // valid k-rows of this slab (<= 0 for a dummy slab)
-      const bf16_t* base = tile + (size_t)(kv > 0 ? k0 : 0) * ld;
-      const uint32_t bytes = kv > 0 ? (uint32_t)(((int64_t)(kv - 1) * ld + cols_left) * 2) : 0u;
-      const __amdgpu_buffer_rsrc_t rs = make_rsrc(base, bytes);
-#pragma unroll
-      for (int i = 0; i < PER_WAVE; ++i)
-        __builtin_amdgcn_raw_ptr_buffer_load_lds(rs, (lds_vp)(stage + (wave * PER_WAVE + i) * 512), 16, off[i], 0, 0, 0);
-    } else {
-      const uint32_t bytes = (uint32_t)(((int64_t)(rows_valid - 1) * ld + Kc) * 2);
-      const __amdgpu_buffer_rsrc_t rs = make_rsrc(tile, bytes);
-#pragma unroll
-      for (int i = 0; i < PER_WAVE; ++i) {
-        const bool kin = (k0 + piece[i] * 8) < Kc;
-        const uint32_t o = kin ? off[i] + (uint32_t)(k0 * 2) : kOobOffset;
-        __builtin_amdgcn_raw_ptr_buffer_load_lds(rs, (lds_vp)(stage + (wave * PER_WAVE + i) * 512), 16, o, 0, 0, 0);
-      }
-    }
-  }
-
-  // The same loads issued one by one as instructions (dma16): slab_desc is the scalar part of a slab, chunk<I>
-  // issues the wave's I-th chunk into the LDS unit at byte address `unit` (scalar); wave_s is the wave index as a scalar.
+  // The scalar part of the slab [k0, k0+BK).  tile = operand pointer already offset to the tile's first row (K-major)
+  // or first column (row-major); rows_valid = tile rows inside the matrix (K-major); cols_left = matrix columns from
+  // the tile's first column on (row-major); Kc = contraction length.  A slab with k0 >= Kc is a dummy: every load is out of
+  // range and writes zeros.
+  // The loads are issued one by one as instructions (dma16): chunk<I> issues the wave's I-th chunk into the LDS unit at byte address `unit` (scalar); wave_s is the wave index as a scalar.
   struct SlabDesc { i32x4_t rs; int k0, Kc; };
   static __device__ __forceinline__ SlabDesc slab_desc(const bf16_t* tile, int ld, int rows_valid, int cols_left, int k0, int Kc) {
     SlabDesc d;
@@ -232,34 +233,11 @@ struct Operand {
     }
   }
 
-  // Per-lane element offsets of the operand reads inside a stage, computed once.  K-major: one per k16
-  // step (the swizzle is an XOR, not additive in the step); row-major: one per MFMA tile.  The values are
-  // made opaque to the optimiser: every read address is then "stage array + offset + constant", a short
-  // chain that keeps the no-alias information of the stage arrays (longer chains lose it, and a read
-  // without it waits for all DMA writes in flight).
-  static constexpr int NRO = RMAJ ? T : BK / 16;
-  static __device__ __forceinline__ void read_offsets(int wbase, int lane, uint32_t (&ro)[NRO]) {
-    const int lr = lane & 31, lg = lane >> 5;
-    if (RMAJ) {
-      // transposing LDS reads: a group of 16 lanes addresses 4 k-rows x 16 tile rows (lane j: k-row j / 4,
-      // rows 4 * (j % 4) .. +3) and lane i of the group receives tile row i for those 4 k
-      const int hb = (lane >> 4) & 1, kq = (lane >> 2) & 3, rq = lane & 3;
-#pragma unroll
-      for (int i = 0; i < T; ++i) {
-        const int col = wbase + 32 * i + 16 * hb + 4 * rq;
-        ro[i] = (uint32_t)((lg * 8 + kq) * R + ((((col >> 3) ^ TIDE_RSWZ(kq)) << 3) | (col & 7)));
-      }
-    } else {
-      const int sw = (lr >> SWZ_SHIFT) & (KPIECES - 1);
-#pragma unroll
-      for (int kk = 0; kk < NRO; ++kk) ro[kk] = (uint32_t)((wbase + lr) * BK + (((kk * 2 + lg) ^ sw) * 8));
-    }
-#pragma unroll
-    for (int i = 0; i < NRO; ++i) asm("" : "+v"(ro[i]));
-  }
-
+  // Per-lane element offsets of the operand reads inside a stage, computed once.  K-major: one per k32 step (the swizzle
+  // is an XOR, not additive in the step); row-major: one per fragment.  The values are made opaque to the optimiser:
+  // every read address is then "stage array + offset + constant", a short chain that keeps the no-alias information
+  // of the stage arrays (longer chains lose it, and a read without it waits for all DMA writes in flight).
   // ---- 16x16x32 MFMA: a fragment is 16 tile rows x 32 k; lane l holds row l & 15, k = 8 * (l >> 4) .. + 7 ----
-  static constexpr int T16 = 2 * T;                          // 16-row fragments per wave along this dimension
   static constexpr int NRO16 = RMAJ ? T16 : BK / 32;
   static constexpr int kReadsPerFrag16 = RMAJ ? 2 : 1;
   static __device__ __forceinline__ void read_offsets16(int wbase, int lane, uint32_t (&ro)[NRO16]) {
@@ -272,7 +250,7 @@ struct Operand {
       for (int i = 0; i < T16; ++i) {
         const int col = wbase + 16 * i + 4 * rq;
         const int krow = g * 8 + kq;
-        ro[i] = (uint32_t)(krow * R + ((((col >> 3) ^ TIDE_RSWZ16(krow)) << 3) | (col & 7)));
+        ro[i] = (uint32_t)(krow * R + ((((col >> 3) ^ TIDE_RSWZ(krow)) << 3) | (col & 7)));
       }
     } else {
       const int sw = (r16 >> SWZ_SHIFT) & (KPIECES - 1);
@@ -302,375 +280,24 @@ struct Operand {
     }
   }
 
-  // MFMA operand fragments of k16 step `kk` (< BK/16)
-  template <typename StagePtr>
-  static __device__ __forceinline__ void frags(StagePtr stage, int kk, const uint32_t (&ro)[NRO], u32x4_t (&f)[T]) {
-    if (RMAJ) {
-      typedef short s16x4_t __attribute__((ext_vector_type(4)));
-      typedef __attribute__((address_space(3))) s16x4_t* lds_tr_t;
-#pragma unroll
-      for (int i = 0; i < T; ++i) {
-        const s16x4_t lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_tr_t)(stage + ro[i] + (kk * 16) * R));
-        const s16x4_t hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_tr_t)(stage + ro[i] + (kk * 16 + 4) * R));
-        const uint2 a = __builtin_bit_cast(uint2, lo), b2 = __builtin_bit_cast(uint2, hi);
-        f[i][0] = a.x; f[i][1] = a.y; f[i][2] = b2.x; f[i][3] = b2.y;
-      }
-    } else {
-      typedef __attribute__((address_space(3))) const u32x4_t* lds_v4_t;
-#pragma unroll
-      for (int i = 0; i < T; ++i) f[i] = *(lds_v4_t)(stage + ro[kk] + i * 32 * BK);
-    }
-  }
 };
 
 template <int N>
 struct Int : std::integral_constant<int, N> {};
 
-// Pin the instruction order of one k16 quarter: after MFMA number I come its share of NDS LDS reads and
-// of NVM DMA issues.
-template <int I, int NMF, int NDS, int NVM, int SYNC>
-__device__ __forceinline__ void sched_slot() {
-  __builtin_amdgcn_sched_group_barrier(0x008, 1, SYNC);   // MFMA
-  constexpr int nds = NDS / NMF + (I < NDS % NMF ? 1 : 0);
-  if constexpr (nds > 0) __builtin_amdgcn_sched_group_barrier(0x100, nds, SYNC);   // LDS reads
-  constexpr int nvm = NVM / NMF + (I < NVM % NMF ? 1 : 0);
-  if constexpr (nvm > 0) __builtin_amdgcn_sched_group_barrier(0x020, nvm, SYNC);   // DMA issues
-}
-template <int NMF, int NDS, int NVM, int SYNC, int... I>
-__device__ __forceinline__ void sched_slots(std::integer_sequence<int, I...>) {
-  (sched_slot<I, NMF, NDS, NVM, SYNC>(), ...);
-}
-
 }  // namespace
 
-template <int BM, int BN, int NW, bool AMM, bool BNM, typename TO, int BK>
-__global__ __launch_bounds__(NW * 64) void gemm_mfma_kernel(MfmaParams p) {
-  static_assert(BK == 32 || BK == 64, "slab depth");
-  constexpr int NST = (BK == 32) ? 4 : 2;   // LDS stages: the ring always holds 128 k-columns
-  constexpr int WAVES_N = (NW == 8) ? 4 : 2, WAVES_M = NW / WAVES_N;
-  constexpr int WM = BM / WAVES_M, WN = BN / WAVES_N;
-  constexpr int TM = WM / 32, TN = WN / 32;
-  static_assert(TM == 4 || TM == 2, "wave tile height must be 128 or 64");
-  static_assert(TN == 4 || TN == 2, "wave tile width must be 128 or 64");
-  using OpA = Operand<BM, NW, AMM, TM, BK>;
-  using OpB = Operand<BN, NW, BNM, TN, BK>;
-  constexpr int A_STAGE = OpA::STAGE, B_STAGE = OpB::STAGE;
-  constexpr int NVM = OpA::PER_WAVE + OpB::PER_WAVE;            // DMA instructions per wave per slab
-  constexpr int NDS = OpA::kReadsPerQuarter + OpB::kReadsPerQuarter;  // LDS reads per wave per k16 quarter
-  constexpr int NMF = TM * TN;                                        // MFMAs per wave per k16 quarter
-
-  constexpr int STAGE34 = (NST == 4) ? A_STAGE + B_STAGE : 8;   // stages 2, 3 exist only in the four-stage ring
-  __shared__ __attribute__((aligned(1024))) bf16_t s0[A_STAGE + B_STAGE];
-  __shared__ __attribute__((aligned(1024))) bf16_t s1[A_STAGE + B_STAGE];
-  __shared__ __attribute__((aligned(1024))) bf16_t s2[STAGE34];
-  __shared__ __attribute__((aligned(1024))) bf16_t s3[STAGE34];
-  auto stage = [&](auto ST) -> bf16_t* {
-    if constexpr (decltype(ST)::value == 0) return s0;
-    else if constexpr (decltype(ST)::value == 1) return s1;
-    else if constexpr (decltype(ST)::value == 2) return s2;
-    else return s3;
-  };
-  typedef __attribute__((address_space(3))) const bf16_t* lds_bf_t;
-
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int wave_m = wave / WAVES_N, wave_n = wave % WAVES_N;
-  const int lr = lane & 31, lg = lane >> 5;
-
-  // sizes that are only known on the device (block-uniform)
-  if (p.m_dev) p.M = max(0, min(p.M, *p.m_dev - p.m_off));
-  if (p.k_dev) p.K = max(0, min(p.K, *p.k_dev - p.k_off));
-  if (p.K == 0 && p.K2 == 0 && p.accumulate) return;   // nothing to add
-
-  // ---- XCD-aware tile numbering over the tiles that exist for the effective M ----
-  int tile_m, tile_n;
-  {
-    const int tiles_m = (p.M + BM - 1) / BM;   // <= p.tiles_m, the grid's worst case
-    const int nb = tiles_m * p.tiles_n;
-    const int pid = blockIdx.x;
-    if (pid >= nb) return;                     // whole block, before any barrier
-    const int xcd = pid & 7, idx = pid >> 3;
-    const int q = nb >> 3, r = nb & 7;
-    const int v = xcd * q + min(xcd, r) + idx;  // contiguous range per XCD
-    constexpr int GROUP = 4;   // 4 tile rows x 8 tile columns per XCD round measured best (8 x 4: +0.8 %, 16 x 2: +4 %, 2 x 16: +1 % step time)
-    const int per_group = GROUP * p.tiles_n;
-    const int gid = v / per_group;
-    const int first_m = gid * GROUP;
-    const int gsz = min(tiles_m - first_m, GROUP);
-    const int in_g = v - gid * per_group;
-    tile_m = first_m + in_g % gsz;
-    tile_n = in_g / gsz;
-  }
-  const int m0 = tile_m * BM, n0 = tile_n * BN;
-
-  // tile pointers of both operand pairs (uniform) and this lane's DMA offsets
-  const bf16_t* a_tile0 = AMM ? p.A + m0 : p.A + (size_t)m0 * p.lda;
-  const bf16_t* b_tile0 = BNM ? p.B + n0 : p.B + (size_t)n0 * p.ldb;
-  const bf16_t* a_tile1 = p.A2 ? (AMM ? p.A2 + m0 : p.A2 + (size_t)m0 * p.lda) : a_tile0;
-  const bf16_t* b_tile1 = p.B2 ? (BNM ? p.B2 + n0 : p.B2 + (size_t)n0 * p.ldb) : b_tile0;
-  const int a_rows = min(BM, p.M - m0), b_rows = min(BN, p.N - n0);
-  uint32_t a_off[OpA::PER_WAVE], b_off[OpB::PER_WAVE];
-  int a_piece[OpA::PER_WAVE], b_piece[OpB::PER_WAVE];
-  OpA::lane_offsets(p.lda, wave, lane, a_off, a_piece);
-  OpB::lane_offsets(p.ldb, wave, lane, b_off, b_piece);
-
-  f32x16_t acc[TM][TN];
-#pragma unroll
-  for (int i = 0; i < TM; ++i)
-#pragma unroll
-    for (int j = 0; j < TN; ++j)
-#pragma unroll
-      for (int q = 0; q < 16; ++q) acc[i][j][q] = 0.f;
-
-  const int nk1 = (p.K + BK - 1) / BK;
-  const int nkp2 = p.A2 ? (p.K2 + BK - 1) / BK : 0;
-  const int nk = nk1 + nkp2;
-  const int nk_round = (nk + NST - 1) / NST * NST;   // slabs past nk are dummies
-
-  auto issue = [&](auto ST, int kt) {
-    bf16_t* sb = stage(ST);
-    int pr = 0, k0 = kt * BK, Kc = p.K;
-    if (kt >= nk1) {
-      if (kt < nk) { pr = 1; k0 = (kt - nk1) * BK; Kc = p.K2; }
-      else { k0 = p.K + BK; }   // dummy slab: everything out of range
-    }
-    OpA::issue(sb, pr ? a_tile1 : a_tile0, p.lda, a_rows, p.M - m0, k0, Kc, a_off, a_piece, wave);
-    OpB::issue(sb + A_STAGE, pr ? b_tile1 : b_tile0, p.ldb, b_rows, p.N - n0, k0, Kc, b_off, b_piece, wave);
-  };
-  uint32_t a_ro[OpA::NRO], b_ro[OpB::NRO];
-  OpA::read_offsets(wave_m * WM, lane, a_ro);
-  OpB::read_offsets(wave_n * WN, lane, b_ro);
-  auto frags = [&](auto ST, int kk, u32x4_t (&fa)[TM], u32x4_t (&fb)[TN]) {
-    const lds_bf_t sb = (lds_bf_t)stage(ST);
-    OpA::frags(sb, kk, a_ro, fa);
-    OpB::frags(sb + A_STAGE, kk, b_ro, fb);
-  };
-  auto mma = [&](u32x4_t (&fa)[TM], u32x4_t (&fb)[TN]) {
-#pragma unroll
-    for (int i = 0; i < TM; ++i)
-#pragma unroll
-      for (int j = 0; j < TN; ++j)
-        acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8_t, fa[i]),
-                                                            __builtin_bit_cast(bf16x8_t, fb[j]), acc[i][j], 0, 0, 0);
-  };
-
-  u32x4_t fa0[TM], fb0[TN], fa1[TM], fb1[TN];
-  if constexpr (BK == 64) {
-    // ---- two stages of 64 ----
-    // Software-pipelined across slabs: the single barrier of a step sits before its LAST k16 quarter.  By
-    // then every wave holds the operands of that quarter in registers, so the stage is free: the DMA of slab
-    // kt+2 is issued into it and the first operands of slab kt+1 are read, both in the shadow of the last
-    // quarter's MFMAs.  No MFMA ever waits for an LDS read that was issued after a barrier.
-    issue(Int<0>{}, 0);
-    TIDE_WAIT_VMCNT(0);
-    __builtin_amdgcn_s_barrier();
-    __builtin_amdgcn_sched_barrier(0);
-    frags(Int<0>{}, 0, fa0, fb0);
-    issue(Int<1>{}, 1);
-    __builtin_amdgcn_sched_barrier(0);
-    // One step: slab kt lives in stage ST (its quarter-0 operands are already in fa0/fb0), slab kt+1 is in
-    // flight into SO.
-    auto step = [&](auto ST, auto SO, int kt) {
-      frags(ST, 1, fa1, fb1);
-      mma(fa0, fb0);
-      sched_slots<NMF, NDS, 0, 0>(std::make_integer_sequence<int, NMF>{});
-      __builtin_amdgcn_sched_barrier(0);
-      frags(ST, 2, fa0, fb0);
-      mma(fa1, fb1);
-      sched_slots<NMF, NDS, 0, 1>(std::make_integer_sequence<int, NMF>{});
-      __builtin_amdgcn_sched_barrier(0);
-      frags(ST, 3, fa1, fb1);
-      mma(fa0, fb0);
-      sched_slots<NMF, NDS, 0, 2>(std::make_integer_sequence<int, NMF>{});
-      __builtin_amdgcn_sched_barrier(0);
-      // all operand reads of this wave from ST have returned; its part of slab kt+1 has landed
-      __builtin_amdgcn_s_waitcnt(0);
-      __builtin_amdgcn_s_barrier();
-      __builtin_amdgcn_sched_barrier(0);
-      frags(SO, 0, fa0, fb0);
-      issue(ST, kt + 2);
-      mma(fa1, fb1);
-      // all operand reads ahead of the DMA issues: a read that lost its no-alias information on the way
-      // through the compiler would otherwise wait for the loads just issued
-      __builtin_amdgcn_sched_group_barrier(0x100, NDS, 3);
-      sched_slots<NMF, 0, NVM, 3>(std::make_integer_sequence<int, NMF>{});
-      __builtin_amdgcn_sched_barrier(0);
-    };
-    for (int kt = 0; kt < nk_round; kt += 2) {
-      step(Int<0>{}, Int<1>{}, kt);
-      step(Int<1>{}, Int<0>{}, kt + 1);
-    }
-  } else {
-    // ---- four stages of 32: used when both operands are row-major over K (their rows are contiguous
-    // anyway, so the deeper ring is what helps); the loads of slab k+3 are issued while slab k is multiplied
-    issue(Int<0>{}, 0);
-    issue(Int<1>{}, 1);
-    issue(Int<2>{}, 2);
-    TIDE_WAIT_VMCNT(2 * NVM);
-    __builtin_amdgcn_s_barrier();
-    frags(Int<0>{}, 0, fa0, fb0);
-    // One pipeline step: slab kt lives in stage ST, slab kt+1 in SN, and slab kt+3 goes to SP (the stage
-    // slab kt-1 just vacated).  The barrier sits between the two k16 halves so that the operand reads of
-    // the next slab are issued under the MFMAs of this one.
-    auto step = [&](auto ST, auto SN, auto SP, int kt) {
-      frags(ST, 1, fa1, fb1);
-      issue(SP, kt + NST - 1);
-      mma(fa0, fb0);
-      sched_slots<NMF, NDS, NVM, 0>(std::make_integer_sequence<int, NMF>{});
-      __builtin_amdgcn_sched_barrier(0);
-      TIDE_WAIT_VMCNT(2 * NVM);          // this wave's part of slab kt+1 has landed (two younger slabs in flight)
-      __builtin_amdgcn_s_barrier();      // ... and everybody else's; everybody is done reading slab kt-1
-      __builtin_amdgcn_sched_barrier(0);
-      frags(SN, 0, fa0, fb0);
-      mma(fa1, fb1);
-      sched_slots<NMF, NDS, 0, 1>(std::make_integer_sequence<int, NMF>{});
-      __builtin_amdgcn_sched_barrier(0);
-    };
-    for (int kt = 0; kt < nk_round; kt += 4) {
-      step(Int<0>{}, Int<1>{}, Int<3>{}, kt);
-      step(Int<1>{}, Int<2>{}, Int<0>{}, kt + 1);
-      step(Int<2>{}, Int<3>{}, Int<1>{}, kt + 2);
-      step(Int<3>{}, Int<0>{}, Int<2>{}, kt + 3);
-    }
-  }
-  TIDE_WAIT_VMCNT(0);   // the dummy slabs still in flight write LDS: let them land before the block retires
-
-  // ---- epilogue ----
-  float alpha = p.alpha;
-  if (p.alpha_dev) alpha *= *p.alpha_dev;
-  TO* C = (TO*)p.C;
-  const TO* R = (const TO*)p.R;
-  const int wm0 = m0 + wave_m * WM, wn0 = n0 + wave_n * WN;
-
-  // MFMA tile (i, j) of the wave: accumulator register q of lane (lr, lg) is row 8*(q/4) + 4*lg + q%4, column lr.
-  bool staged = false;
-  if constexpr (sizeof(TO) == 2) {
-    if (!R && !p.accumulate && (p.ldc % 8) == 0 && (p.N % 8) == 0) {
-      staged = true;
-      // bf16 result through a wave-private LDS patch so that it leaves as 16-byte row segments.
-      // All stages are free here: every wave waited for its own DMA above, and the barrier below orders the
-      // (unused) operand reads of the final dummy slab before the patch writes.
-      __builtin_amdgcn_s_barrier();
-      constexpr int PP = WN + 8;                       // patch pitch (elements)
-      static_assert((NW / 2) * 32 * PP <= A_STAGE + B_STAGE, "epilogue patches of half the waves must fit in one stage");
-      bf16_t* patch = (wave < NW / 2 ? s0 : s1) + (wave % (NW / 2)) * (32 * PP);   // 32 x WN per wave
-      constexpr int PIECES = WN / 8;                   // 16-byte pieces per patch row
-#pragma unroll
-      for (int i = 0; i < TM; ++i) {
-#pragma unroll
-        for (int j = 0; j < TN; ++j)
-#pragma unroll
-          for (int q = 0; q < 16; ++q) {
-            const int rr = 8 * (q >> 2) + 4 * lg + (q & 3);
-            patch[rr * PP + 32 * j + lr] = f2bf(alpha * acc[i][j][q]);
-          }
-#pragma unroll
-        for (int t = 0; t < 32 * PIECES / 64; ++t) {
-          const int pc = lane + 64 * t;
-          const int row = pc / PIECES, piece = pc % PIECES;
-          const int gm = wm0 + 32 * i + row, gn = wn0 + piece * 8;
-          const u32x4_t val = *reinterpret_cast<const u32x4_t*>(patch + row * PP + piece * 8);
-          if (gm < p.M && gn < p.N)
-            *reinterpret_cast<u32x4_t*>(reinterpret_cast<bf16_t*>(C) + (size_t)gm * p.ldc + gn) = val;
-        }
-      }
-    } else if constexpr ((NW / 2) * 32 * (WN + 4) * 2 <= A_STAGE + B_STAGE) {
-      if (R && !p.accumulate && (p.ldc % 8) == 0 && (p.ldr % 8) == 0 && (p.N % 8) == 0) {
-        staged = true;
-        // bf16 result plus residual: the patch keeps fp32 so that alpha*acc + residual is rounded once, as in
-        // the direct path; residual and result move as 16-byte row segments.
-        __builtin_amdgcn_s_barrier();
-        constexpr int PF = WN + 4;                     // patch pitch (floats)
-        float* patch = reinterpret_cast<float*>(wave < NW / 2 ? s0 : s1) + (wave % (NW / 2)) * (32 * PF);
-        constexpr int PIECES = WN / 8;
-        const bf16_t* Rb = reinterpret_cast<const bf16_t*>(R);
-#pragma unroll
-        for (int i = 0; i < TM; ++i) {
-#pragma unroll
-          for (int j = 0; j < TN; ++j)
-#pragma unroll
-            for (int q = 0; q < 16; ++q) {
-              const int rr = 8 * (q >> 2) + 4 * lg + (q & 3);
-              patch[rr * PF + 32 * j + lr] = alpha * acc[i][j][q];
-            }
-#pragma unroll
-          for (int t = 0; t < 32 * PIECES / 64; ++t) {
-            const int pc = lane + 64 * t;
-            const int row = pc / PIECES, piece = pc % PIECES;
-            const int gm = wm0 + 32 * i + row, gn = wn0 + piece * 8;
-            if (gm < p.M && gn < p.N) {
-              float v[8], r[8];
-              const float4 a0 = *reinterpret_cast<const float4*>(patch + row * PF + piece * 8);
-              const float4 a1 = *reinterpret_cast<const float4*>(patch + row * PF + piece * 8 + 4);
-              v[0] = a0.x; v[1] = a0.y; v[2] = a0.z; v[3] = a0.w; v[4] = a1.x; v[5] = a1.y; v[6] = a1.z; v[7] = a1.w;
-              ld8(Rb, (size_t)gm * p.ldr + gn, r);
-#pragma unroll
-              for (int e = 0; e < 8; ++e) v[e] += r[e];
-              st8(reinterpret_cast<bf16_t*>(C), (size_t)gm * p.ldc + gn, v);
-            }
-          }
-        }
-      }
-    }
-  }
-  if (!staged && p.accumulate && !R) {
-    // C += alpha * acc.  The old values of a 32-row slice are all requested before the first of them is used
-    // (32 or 64 loads in flight per lane instead of a load-add-store chain per element: the compiler cannot
-    // reorder the loads itself, it does not know that the stores of one element leave the next one alone).
-#pragma unroll
-    for (int i = 0; i < TM; ++i) {
-      float old[16][TN];
-#pragma unroll
-      for (int q = 0; q < 16; ++q) {
-        const int gm = wm0 + 32 * i + 8 * (q >> 2) + 4 * lg + (q & 3);
-#pragma unroll
-        for (int j = 0; j < TN; ++j) {
-          const int gn = wn0 + 32 * j + lr;
-          old[q][j] = (gm < p.M && gn < p.N) ? ldf(C, (size_t)gm * p.ldc + gn) : 0.f;
-        }
-      }
-#pragma unroll
-      for (int q = 0; q < 16; ++q) {
-        const int gm = wm0 + 32 * i + 8 * (q >> 2) + 4 * lg + (q & 3);
-#pragma unroll
-        for (int j = 0; j < TN; ++j) {
-          const int gn = wn0 + 32 * j + lr;
-          if (gm < p.M && gn < p.N) stf(C, (size_t)gm * p.ldc + gn, alpha * acc[i][j][q] + old[q][j]);
-        }
-      }
-    }
-  } else if (!staged) {
-#pragma unroll
-    for (int i = 0; i < TM; ++i)
-#pragma unroll
-      for (int q = 0; q < 16; ++q) {
-        const int rr = 8 * (q >> 2) + 4 * lg + (q & 3);
-        const int gm = wm0 + 32 * i + rr;
-        if (gm >= p.M) continue;
-#pragma unroll
-        for (int j = 0; j < TN; ++j) {
-          const int gn = wn0 + 32 * j + lr;
-          if (gn >= p.N) continue;
-          float v = alpha * acc[i][j][q];
-          if (R) v += ldf(R, (size_t)gm * p.ldr + gn);
-          if (p.accumulate) v += ldf(C, (size_t)gm * p.ldc + gn);
-          stf(C, (size_t)gm * p.ldc + gn, v);
-        }
-      }
-  }
-}
-
-
 // ------------------------------------------------------------------------------------------------
-// The 256x256 tile with v_mfma_f32_16x16x32_bf16.  Same ring, DMA, swizzles, synchronisation and epilogues as
-// the kernel above; what changes is the matrix instruction: on this chip the matrix pipes sustain a higher rate
-// under the package power limit with the 16x16x32 form (a pure-MFMA loop on random operands: 2.10 against 1.88
-// PFLOP/s), while the LDS operand traffic per flop stays the same (a 16-row x 32-k fragment is one 16-byte
-// read per lane, like a 32-row x 16-k one).  A wave owns 8 x 4 tiles of 16 x 16 (128 x 64); a "quarter" of the
-// schedule is one k32 step of four of its A fragments against its four B fragments: 16 MFMAs (256 clocks, as the
-// 8 MFMAs of a k16 quarter above), with the A fragments double-buffered per quarter and the B fragments per k32
-// step.  The MFMAs take the B fragment first, so accumulator element q of lane l in tile (i, j) is row
-// 16 i + (l & 15), column 16 j + 4 (l >> 4) + q (see the epilogue).  WAVES_N = 4 is the layout in use; with
-// WAVES_N = 2 the block has four waves of 128 x 128 (one per SIMD), kept as the measured alternative.
+// Tiles of BT x BT with v_mfma_f32_16x16x32_bf16: BT = 256 on eight waves of 128 x 64, BT = 128 on four waves of 64 x 64
+// (whose five LDS units of 16 KiB let two blocks share a CU).  On this chip the matrix pipes sustain a higher rate under
+// the package power limit with this form than with 32x32x16 (a pure-MFMA loop on random operands: 2.10 against 1.88
+// PFLOP/s), while the LDS operand traffic per flop is the same (a 16-row x 32-k fragment is one 16-byte read per lane, like
+// a 32-row x 16-k one).  A wave owns (BT / 32) x 4 tiles of 16 x 16; a "quarter" of the schedule is one k32 step of four of
+// its A fragments against its four B fragments: 16 MFMAs (256 clocks), with the A fragments double-buffered per quarter
+// and the B fragments per k32 step.  A slab is four quarters at BT = 256 and two at BT = 128.  The MFMAs take the B fragment
+// first, so accumulator element q of lane l in tile (i, j) is row 16 i + (l & 15), column 16 j + 4 (l >> 4) + q (see the
+// epilogue).  (Four waves of 128 x 128 at BT = 256, a third less LDS traffic, measured 2.5 to 10 % slower: one wave per SIMD
+// leaves every wait of that wave exposed.)
 // KWHOLE: every slab of the launch is whole (K, and K2 of a second operand pair, multiples of 64 known on the
 // host).  A K-major operand's loads then need neither the per-lane test "is this piece still inside K" nor a
 // per-lane k offset: k0 moves into the buffer descriptor and the lane offsets are loop constants, which takes
@@ -679,16 +306,15 @@ __global__ __launch_bounds__(NW * 64) void gemm_mfma_kernel(MfmaParams p) {
 // ------------------------------------------------------------------------------------------------
 typedef float f32x4_t __attribute__((ext_vector_type(4)));
 
-template <bool AMM, bool BNM, typename TO, int BK, int WAVES_N, bool KWHOLE>
-__global__ __launch_bounds__(2 * WAVES_N * 64) void gemm_mfma16_kernel(MfmaParams p) {
-  constexpr int BM = 256, BN = 256, WAVES_M = 2, NW = WAVES_M * WAVES_N;
-  static_assert(BK == 64, "slab depth");
-  static_assert(WAVES_N == 4 || WAVES_N == 2, "eight waves of 128 x 64 or four of 128 x 128");
-  constexpr int WM = BM / WAVES_M, WN = BN / WAVES_N;   // 128 x 64
-  constexpr int TM = WM / 16, TN = WN / 16;             // 8 x 4 tiles of 16 x 16
+template <int BT, bool AMM, bool BNM, typename TO, bool KWHOLE>
+__global__ __launch_bounds__(2 * BT) void gemm_mfma_kernel(MfmaParams p) {
+  static_assert(BT == 256 || BT == 128, "tile edge");
+  constexpr int BM = BT, BN = BT, BK = 64, WAVES_M = 2, WAVES_N = BT / 64, NW = WAVES_M * WAVES_N;
+  constexpr int WM = BM / WAVES_M, WN = BN / WAVES_N;   // 128 x 64 or 64 x 64
+  constexpr int TM = WM / 16, TN = WN / 16;             // 8 x 4 or 4 x 4 tiles of 16 x 16
   constexpr int GA = 4;                                 // A fragments per quarter
-  using OpA = Operand<BM, NW, AMM, WM / 32, BK, 16>;
-  using OpB = Operand<BN, NW, BNM, WN / 32, BK, 16>;
+  using OpA = Operand<BM, NW, AMM, TM, BK>;
+  using OpB = Operand<BN, NW, BNM, TN, BK>;
   constexpr int A_STAGE = OpA::STAGE, B_STAGE = OpB::STAGE;
   constexpr int NVA = OpA::PER_WAVE, NVB = OpB::PER_WAVE;
   constexpr int NMF = GA * TN;                          // MFMAs per quarter
@@ -700,31 +326,43 @@ __global__ __launch_bounds__(2 * WAVES_N * 64) void gemm_mfma16_kernel(MfmaParam
 
   if (p.m_dev) p.M = max(0, min(p.M, *p.m_dev - p.m_off));
   if (p.k_dev) p.K = max(0, min(p.K, *p.k_dev - p.k_off));
-  if (p.K == 0 && p.K2 == 0 && p.accumulate && p.split_s <= 1) return;
+  if (p.K == 0 && p.K2 == 0 && p.accumulate && p.split != kSplitTail) return;   // nothing to add
 
   int tile_m, tile_n;
-  int part = 0, nparts = 1, tail_index = 0;   // K split of the tiles of the last round (see MfmaParams)
+  int part = 0, nparts = 1, tail_index = 0, ntail = 0;   // split over K (see MfmaParams)
   {
     const int tiles_m = (p.M + BM - 1) / BM;
     const int nb = tiles_m * p.tiles_n;
-    const bool split = p.split_s > 1;        // (never together with a device-side M: nb is then the grid's count)
-    const int items = split ? p.split_full + (nb - p.split_full) * p.split_s : nb;
+    int full = nb;                           // tiles that are not split
+    if (p.split == kSplitTail) { full = p.split_full; nparts = p.split_s; }   // (never with a device-side M)
+    else if (p.split == kSplitAll) {
+      const SplitAll sa = split_all<BT>(nb, split_slabs(p.K, p.A2 ? p.K2 : 0));
+      full = sa.full; nparts = sa.parts;
+    }
+    ntail = nb - full;
+    const int items = full + ntail * nparts;
     int pid = blockIdx.x;
     if (pid >= items) return;
     // Work-groups go to the XCDs round-robin in the order of their index: the whole tiles (a multiple of 256)
     // come first and each XCD gets a contiguous range of them; the parts of the split tiles come last, again
     // spread over all XCDs, so that they fill the last round everywhere.
-    int count = split ? p.split_full : nb, base = 0;
-    if (split && pid >= p.split_full) { base = p.split_full; pid -= base; count = items - base; }
+    int count = full, base = 0;
+    if (pid >= full) { base = full; pid -= full; count = items - full; }
     const int xcd = pid & 7, idx = pid >> 3;
     const int q = count >> 3, r = count & 7;
     int v = base + xcd * q + min(xcd, r) + idx;
-    if (split && v >= p.split_full) {
-      const int u = v - p.split_full;
-      tail_index = u / p.split_s;
-      part = u - tail_index * p.split_s;
-      nparts = p.split_s;
-      v = p.split_full + tail_index;
+    if (v >= full) {
+      const int u = v - full;
+      if (p.split == kSplitAll) {            // part by part: the tiles an XCD works on share the panels of one K range
+        part = u / ntail;
+        tail_index = u - part * ntail;
+      } else {
+        tail_index = u / nparts;
+        part = u - tail_index * nparts;
+      }
+      v = full + tail_index;
+    } else {
+      nparts = 1;
     }
     tile_coords(v, tiles_m, p.tiles_n, tile_m, tile_n);
   }
@@ -785,6 +423,18 @@ __global__ __launch_bounds__(2 * WAVES_N * 64) void gemm_mfma16_kernel(MfmaParam
     TO* C = (TO*)p.C;
     const TO* R = (const TO*)p.R;
     const int wm0 = m0 + wave_m * WM, wn0 = n0 + wave_n * WN;
+    if (p.split == kSplitAll && nparts > 1) {
+      // the partial sum as it is, tile-local; rows and columns past the matrix are not read back
+      float* out = p.split_scratch + ((size_t)part * ntail + tail_index) * (size_t)(BM * BN);
+#pragma unroll
+      for (int i = 0; i < TM; ++i)
+#pragma unroll
+        for (int j = 0; j < TN; ++j) {
+          const int row = wave_m * WM + 16 * i + lc, col = wave_n * WN + 16 * j + 4 * lg;
+          if (m0 + row < p.M && n0 + col < p.N) *reinterpret_cast<f32x4_t*>(out + row * BN + col) = acc[i][j];
+        }
+      return;
+    }
     bool staged = false;
     if constexpr (sizeof(TO) == 2) {
       constexpr int PIECES = WN / 8;
@@ -863,7 +513,6 @@ __global__ __launch_bounds__(2 * WAVES_N * 64) void gemm_mfma16_kernel(MfmaParam
         int mo = 0, no = 0;
         bool add = p.accumulate != 0;
         if (part > 0) {
-          const int ntail = ((p.M + BM - 1) / BM) * p.tiles_n - p.split_full;
           Cf = p.split_scratch + ((size_t)(part - 1) * ntail + tail_index) * (size_t)(BM * BN);
           pitch = BN; mo = m0; no = n0; add = false;
         }
@@ -954,13 +603,17 @@ __global__ __launch_bounds__(2 * WAVES_N * 64) void gemm_mfma16_kernel(MfmaParam
     // A K-major operand can be walked when every slab is whole; one with ragged K keeps the per-slab form
     // because its loads need k0 and K for their per-lane test.
     constexpr bool WALK_A = KWHOLE || AMM, WALK_B = KWHOLE || BNM;
-    const int k_first = kt_lo * BK;                      // a split launch has one operand pair, so this is in pair 0
-    const int k_span0 = min(p.K, (kt_lo + nk) * BK) - k_first;
-    uint64_t a_base = (uint64_t)(a_tile0 + (AMM ? (size_t)k_first * p.lda : (size_t)k_first));
-    uint64_t b_base = (uint64_t)(b_tile0 + (BNM ? (size_t)k_first * p.ldb : (size_t)k_first));
+    // the block's slabs start in the first operand pair, or (a later part of a split tile) in the second
+    const bool in2 = kt_lo >= nk1 && nkp2 > 0;
+    const int k_first = (in2 ? kt_lo - nk1 : kt_lo) * BK, k_last = kt_lo + nk;
+    const int rem0 = in2 ? min(p.K2, (k_last - nk1) * BK) - k_first : min(p.K, k_last * BK) - k_first;
+    const bf16_t* a_first = in2 ? a_tile1 : a_tile0;
+    const bf16_t* b_first = in2 ? b_tile1 : b_tile0;
+    uint64_t a_base = (uint64_t)(a_first + (AMM ? (size_t)k_first * p.lda : (size_t)k_first));
+    uint64_t b_base = (uint64_t)(b_first + (BNM ? (size_t)k_first * p.ldb : (size_t)k_first));
     uint64_t a_next = (uint64_t)a_tile1, b_next = (uint64_t)b_tile1;
-    int a_rem = k_span0, b_rem = k_span0;
-    int a_nrem = nkp2 > 0 ? p.K2 : 0, b_nrem = a_nrem;
+    int a_rem = rem0, b_rem = rem0;
+    int a_nrem = !in2 && k_last > nk1 ? min(p.K2, (k_last - nk1) * BK) : 0, b_nrem = a_nrem;
     const uint32_t a_step = AMM ? (uint32_t)(2 * BK) * (uint32_t)p.lda : (uint32_t)(2 * BK);
     const uint32_t b_step = BNM ? (uint32_t)(2 * BK) * (uint32_t)p.ldb : (uint32_t)(2 * BK);
     // extent of a live slab: row-major over K: (rows of the slab - 1) * ld + columns left; K-major: (tile rows - 1) * ld + k left
@@ -1060,11 +713,34 @@ __global__ __launch_bounds__(2 * WAVES_N * 64) void gemm_mfma16_kernel(MfmaParam
     all_deep(ld1, 1);
     all_shal(ls1, 1);
     __builtin_amdgcn_sched_barrier(0);
+    // (BT = 128: a slab is two quarters, one per k32 step; the barrier sits between them)
     // One slab: deep unit D, shallow unit S (fa0 / fb0 hold its first quarter's operands); the next slab's units
     // are DN, SN; DP is the deep unit the slab before vacated.
     auto step = [&](auto D, auto S, auto DN, auto SN, auto DP, int kt) {
       const bf16_t* ua = unit_a(D, S);
       const bf16_t* ubb = unit_b(D, S);
+      if constexpr (TM == GA) {
+        const auto dd1 = desc_deep(kt + 2);
+        quarter(Int<0>{}, fa0, fb0, [&](auto X) {
+          constexpr int x = decltype(X)::value;
+          if constexpr (x < GA) frag_a(ua, 1, Int<0>{}, X, fa1);
+          else if constexpr (x < GA + TN) frag_b(ubb, 1, Int<x - GA>{}, fb1);
+          else if constexpr (x < GA + TN + NDEEP) dma_deep(Int<x - GA - TN>{}, dd1, deep(DP));
+        });
+        __builtin_amdgcn_s_waitcnt((NDEEP & 15) | ((NDEEP >> 4) << 14));   // as below
+        __builtin_amdgcn_s_barrier();
+        __builtin_amdgcn_sched_barrier(0);
+        const bf16_t* uan = unit_a(DN, SN);
+        const bf16_t* ubn = unit_b(DN, SN);
+        const auto ds = desc_shal(kt + 2);
+        quarter(Int<0>{}, fa1, fb1, [&](auto X) {
+          constexpr int x = decltype(X)::value;
+          if constexpr (x < GA) frag_a(uan, 0, Int<0>{}, X, fa0);
+          else if constexpr (x < GA + TN) frag_b(ubn, 0, Int<x - GA>{}, fb0);
+          else if constexpr (x < GA + TN + NSHAL) dma_shal(Int<x - GA - TN>{}, ds, shal(S));
+        });
+        return;
+      } else {
       quarter(Int<0>{}, fa0, fb0, [&](auto X) {
         if constexpr (decltype(X)::value < GA) frag_a(ua, 0, Int<1>{}, X, fa1);
       });
@@ -1095,6 +771,7 @@ __global__ __launch_bounds__(2 * WAVES_N * 64) void gemm_mfma16_kernel(MfmaParam
         constexpr int s0 = BNM ? GA + TN : GA;
         if constexpr (x >= s0 && x < s0 + NSHAL) dma_shal(Int<x - s0>{}, ds, shal(S));
       });
+      }
     };
     // The unit numbers repeat every six slabs.  The last round skips the slabs past nk one by one (a chain of
     // uniform branches with the single loop exit at the bottom: early exits out of the middle made the compiler
@@ -1158,6 +835,51 @@ __global__ __launch_bounds__(256) void splitk_fixup_kernel(float* __restrict__ C
   }
 }
 
+// C[tile] = alpha * (the partial sums of a tile's parts, in their order) + residual + old value.  A launch that came out
+// as one part per tile has written C itself.  A block covers 2048 elements of a tile; a thread owns 8 consecutive columns.
+template <typename TO, int BT>
+__global__ __launch_bounds__(256) void splitk_reduce_kernel(MfmaParams p) {
+  constexpr int PER_ROW = BT / 8, ROWS = 256 / PER_ROW, BLOCKS = BT / ROWS;
+  if (p.m_dev) p.M = max(0, min(p.M, *p.m_dev - p.m_off));
+  if (p.k_dev) p.K = max(0, min(p.K, *p.k_dev - p.k_off));
+  const int tiles_m = (p.M + BT - 1) / BT, tiles = tiles_m * p.tiles_n;
+  const SplitAll sa = split_all<BT>(tiles, split_slabs(p.K, p.A2 ? p.K2 : 0));
+  const int tail = blockIdx.x / BLOCKS, ntail = tiles - sa.full;
+  if (tail >= ntail) return;
+  int tile_m, tile_n;
+  tile_coords(sa.full + tail, tiles_m, p.tiles_n, tile_m, tile_n);
+  const int row = (blockIdx.x % BLOCKS) * ROWS + threadIdx.x / PER_ROW, col = (threadIdx.x % PER_ROW) * 8;
+  const int gm = tile_m * BT + row, gn = tile_n * BT + col;
+  if (gm >= p.M || gn >= p.N) return;
+  const float* src = p.split_scratch + (size_t)tail * (BT * BT) + row * BT + col;
+  const size_t stride = (size_t)ntail * (BT * BT);
+  float v[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+  for (int j = 0; j < sa.parts; j += 4) {        // four parts' loads in flight at a time
+    Raw8<float> x[4];
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+      x[u].zero();
+      if (j + u < sa.parts) x[u].load(src, (size_t)(j + u) * stride);
+    }
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+      float y[8];
+      x[u].get(y);
+#pragma unroll
+      for (int e = 0; e < 8; ++e) v[e] += y[e];
+    }
+  }
+  float alpha = p.alpha;
+  if (p.alpha_dev) alpha *= *p.alpha_dev;
+  TO* C = (TO*)p.C + (size_t)gm * p.ldc + gn;
+  float r[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f}, old[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+  if (p.R) ld8((const TO*)p.R, (size_t)gm * p.ldr + gn, r);
+  if (p.accumulate) ld8(C, 0, old);
+#pragma unroll
+  for (int e = 0; e < 8; ++e) v[e] = alpha * v[e] + r[e] + old[e];
+  st8(C, 0, v);
+}
+
 namespace {
 // How the last round of a 256 x 256-tile launch is split over K: fp32 results without residual on tiles that do
 // not fill the last round of the 256 CUs (at most half of it: otherwise two parts per tile would not fit the round).
@@ -1184,7 +906,76 @@ SplitPlan plan_split(const GemmArgs& a) {
 }
 }  // namespace
 
-size_t gemm_splitk_scratch_bytes(const GemmArgs& a) { return gemm_mfma_supported(a) ? plan_split(a).bytes : 0; }
+namespace {
+
+// the reduction moves 8 columns at a time
+bool split_possible(const GemmArgs& a) {
+  return a.N % 8 == 0 && a.ldc % 8 == 0 && !((uintptr_t)a.C & 15) && !(a.residual && (a.ldr % 8 || ((uintptr_t)a.residual & 15)));
+}
+
+// Rows a launch whose number of rows is on the device alone is planned for: 85 % of the upper bound, the share of a batch
+// that carries loss when prompts are 15 % of it (60 % in padded batches, 90 to 100 % in packed ones).  The kernels take
+// the true number.
+int64_t planned_rows(const GemmArgs& a) { return a.m_dev ? (a.M * 17 + 19) / 20 : a.M; }
+int64_t tile_count(int64_t M, int64_t N, int e) { return ((M + e - 1) / e) * ((N + e - 1) / e); }
+
+// Which tile a launch takes: 256 x 256 from 200 of them on; below that the cheaper one by the costs above, with or
+// without a split, the small one in doubt.  With t tiles of 128 x 128 the chip runs rounds of 512 at the rate of two per
+// CU (950 ns per slab) and the rest at that of one (580) up to 256, in between (800) up to 400.  Both operands row-major
+// over K (TN) cost two LDS reads per fragment: 1050 / 700 ns, and 1470 on a large tile.  us, small / large tile: NN 2560 x
+// 2048 x 32000: 400 / 258 (80 tiles in three parts), NT 1999 x 4096 x 12288: 191 / 160 (two), NN 2560 x 2048 x 11264: 136 / 102 (three),
+// NN 1665 x 5632 x 2048: 46 / 52 (154 tiles, whole).
+int tile_edge(const GemmArgs& a) {
+  if (tile_count(a.M, a.N, 256) >= 200) return 256;
+  const int64_t rows = planned_rows(a), t256 = tile_count(rows, a.N, 256), t128 = tile_count(rows, a.N, 128);
+  const int slabs = split_slabs((int)a.K, a.A2 ? (int)a.K2 : 0);
+  const bool can = split_possible(a), tn = a.layout == kTN;
+  const SplitCost c2 = split_cost(256), c1 = split_cost(128);   // time in ns
+  const int n256 = can ? split_parts(256, (int)t256, slabs) : 1, n128 = can ? split_parts(128, (int)t128, slabs) : 1;
+  const int64_t p256 = (slabs + n256 - 1) / n256, p128 = (slabs + n128 - 1) / n128, blocks = t128 * n128, rest = blocks % 512;
+  const int64_t time256 = (tn ? 1470 : c2.slab) * p256 + (n256 > 1 ? c2.fixed + c2.traffic * t256 * n256 : a.out_dtype == kF32 ? 14000 : 7000);
+  const int64_t alone = tn ? 700 : 580, shared = tn ? 1050 : 950;
+  const int64_t time128 = p128 * (blocks / 512 * shared + (rest == 0 ? 0 : rest <= 256 ? alone : rest <= 400 ? (alone + shared) / 2 : shared)) +
+                          (n128 > 1 ? c1.fixed + c1.traffic * blocks : 0) + 4000;
+  return time256 * 20 < time128 * 19 ? 256 : 128;
+}
+
+// Grid and scratch of a kSplitAll launch on tiles of BT x BT (blocks 0: it is not split).  With sizes known on the device
+// alone they are the most that any size up to the given ones asks for.
+struct SplitGrid { int64_t blocks, tail; size_t bytes; };
+SplitGrid plan_split_all(const GemmArgs& a, int BT) {
+  SplitGrid sp{0, 0, 0};
+  if (!split_possible(a)) return sp;
+  const int64_t tm = (a.M + BT - 1) / BT, tn = (a.N + BT - 1) / BT;
+  // (a launch of many rounds has little to gain from its last one)
+  if (BT == 256 && tm * tn > 4 * 256) return sp;
+  const int slabs = split_slabs((int)a.K, a.A2 ? (int)a.K2 : 0);
+  // with fewer slabs (a K known on the device alone) there are never more parts
+  auto at = [&](int tiles) { return BT == 256 ? split_all<256>(tiles, slabs) : split_all<128>(tiles, slabs); };
+  if (at((int)((planned_rows(a) + BT - 1) / BT * tn)).parts < 2) return sp;
+  int64_t parts = 0, most = tm * tn;
+  for (int64_t t = a.m_dev ? 1 : tm; t <= tm; ++t) {
+    const int tiles = (int)(t * tn);
+    if (BT == 128 && tiles > split_cost(128).slots / 2) break;   // no room for a second part from here on
+    const SplitAll sa = at(tiles);
+    if (sa.parts < 2) continue;
+    const int64_t tail = tiles - sa.full, n = tail * sa.parts;
+    if (n > parts) parts = n;
+    if (tail > sp.tail) sp.tail = tail;
+    if (sa.full + n > most) most = sa.full + n;
+  }
+  if (parts == 0) return sp;
+  sp.bytes = (size_t)parts * BT * BT * sizeof(float);
+  sp.blocks = most;
+  return sp;
+}
+}  // namespace
+
+size_t gemm_splitk_scratch_bytes(const GemmArgs& a) {
+  if (!gemm_mfma_supported(a)) return 0;
+  const SplitPlan tail = plan_split(a);
+  return tail.s > 1 ? tail.bytes : plan_split_all(a, tile_edge(a)).bytes;
+}
 
 bool gemm_mfma_supported(const GemmArgs& a) {
   if (a.in_dtype != kBF16) return false;
@@ -1211,50 +1002,35 @@ bool gemm_mfma_supported(const GemmArgs& a) {
 
 namespace {
 
-template <int BM, int BN, int NW, bool AMM, bool BNM, typename TO, int BK>
-hipError_t launch_cfg(const MfmaParams& p, hipStream_t s) {
+// split_blocks: grid of a kSplitAll launch, whose tail is at most split_tail tiles
+template <int BT, bool AMM, bool BNM, typename TO>
+hipError_t launch_tiles(const MfmaParams& p, int64_t split_blocks, int64_t split_tail, hipStream_t s) {
   MfmaParams q = p;
-  q.tiles_m = (p.M + BM - 1) / BM;
-  q.tiles_n = (p.N + BN - 1) / BN;
-  hipLaunchKernelGGL((gemm_mfma_kernel<BM, BN, NW, AMM, BNM, TO, BK>), dim3((unsigned)(q.tiles_m * q.tiles_n)), dim3(NW * 64), 0,
-                     s, q);
+  q.tiles_m = (p.M + BT - 1) / BT;
+  q.tiles_n = (p.N + BT - 1) / BT;
+  const int tiles = q.tiles_m * q.tiles_n;
+  const int64_t items = q.split == kSplitAll ? split_blocks
+                      : q.split == kSplitTail ? q.split_full + (int64_t)(tiles - q.split_full) * q.split_s : tiles;
+  // every slab whole (and K known on the host): the DMA loads of a K-major operand take loop-constant lane offsets
+  // (with both operands row-major over K the two forms are the same code: one instantiation)
+  const bool whole = !(AMM && BNM) && !p.k_dev && p.K % 64 == 0 && (!p.A2 || p.K2 % 64 == 0);
+  if (whole) hipLaunchKernelGGL((gemm_mfma_kernel<BT, AMM, BNM, TO, true>), dim3((unsigned)items), dim3(2 * BT), 0, s, q);
+  else hipLaunchKernelGGL((gemm_mfma_kernel<BT, AMM, BNM, TO, false>), dim3((unsigned)items), dim3(2 * BT), 0, s, q);
+  const hipError_t e = hipGetLastError();
+  if (e != hipSuccess || q.split != kSplitAll) return e;
+  hipLaunchKernelGGL((splitk_reduce_kernel<TO, BT>), dim3((unsigned)(split_tail * (BT * BT / 2048))), dim3(256), 0, s, q);
   return hipGetLastError();
 }
 
-bool use_big_tiles(int64_t M, int64_t N) { return ((M + 255) / 256) * ((N + 255) / 256) >= 200; }
-
 template <bool AMM, bool BNM, typename TO>
-hipError_t launch_layout(const MfmaParams& p, hipStream_t s) {
-  // slab depth of the 32x32x16 kernels: 64 (two stages) as soon as one operand is K-major, else 32 (four stages);
-  // the 16x16x32 kernel walks slabs of 64 in every layout
-  constexpr int BK = (AMM && BNM) ? 32 : 64;
-#ifndef TIDE_BIG_TILE_MFMA32
-  if (use_big_tiles(p.M, p.N)) {
-    MfmaParams q = p;
-    q.tiles_m = (p.M + 255) / 256;
-    q.tiles_n = (p.N + 255) / 256;
-    const int tiles = q.tiles_m * q.tiles_n;
-    const int items = q.split_s > 1 ? q.split_full + (tiles - q.split_full) * q.split_s : tiles;
-#ifndef TIDE_GEMM_WAVES_N
-#define TIDE_GEMM_WAVES_N 4
-#endif
-    constexpr int WAVES_N = TIDE_GEMM_WAVES_N;
-    // every slab whole (and K known on the host): the DMA loads of a K-major operand take loop-constant lane offsets
-    // (with both operands row-major over K the two forms are the same code: one instantiation)
-    const bool whole = !(AMM && BNM) && !p.k_dev && p.K % 64 == 0 && (!p.A2 || p.K2 % 64 == 0);
-    if (whole) hipLaunchKernelGGL((gemm_mfma16_kernel<AMM, BNM, TO, 64, WAVES_N, true>), dim3((unsigned)items), dim3(2 * WAVES_N * 64), 0, s, q);
-    else hipLaunchKernelGGL((gemm_mfma16_kernel<AMM, BNM, TO, 64, WAVES_N, false>), dim3((unsigned)items), dim3(2 * WAVES_N * 64), 0, s, q);
-    return hipGetLastError();
-  }
-#endif
-  if (p.split_s > 1) return hipErrorInvalidValue;   // only the 16x16x32 kernel knows the split
-  if (use_big_tiles(p.M, p.N)) return launch_cfg<256, 256, 8, AMM, BNM, TO, BK>(p, s);
-  return launch_cfg<128, 128, 4, AMM, BNM, TO, BK>(p, s);
+hipError_t launch_layout(const MfmaParams& p, int BT, int64_t split_blocks, int64_t split_tail, hipStream_t s) {
+  if (BT == 256) return launch_tiles<256, AMM, BNM, TO>(p, split_blocks, split_tail, s);
+  return launch_tiles<128, AMM, BNM, TO>(p, split_blocks, split_tail, s);
 }
 
 const char* gemm_kernel_name(const GemmArgs& a) {
   if (!gemm_mfma_supported(a)) return a.in_dtype == kF32 && a.out_dtype == kF32 ? "gemm_fp32" : "gemm_simple";
-  const bool big = use_big_tiles(a.M, a.N);
+  const bool big = tile_edge(a) == 256;
   const bool f32 = a.out_dtype == kF32;
   switch (a.layout) {
     case kNT: return big ? (f32 ? "gemm_mfma_nt_256_f32out" : "gemm_mfma_nt_256_bf16out") : (f32 ? "gemm_mfma_nt_128_f32out" : "gemm_mfma_nt_128_bf16out");
@@ -1274,19 +1050,32 @@ hipError_t launch_gemm_mfma(const GemmArgs& a, hipStream_t s) {
   p.lda = (int)a.lda; p.ldb = (int)a.ldb; p.ldc = (int)a.ldc; p.ldr = (int)a.ldr;
   p.alpha = a.alpha; p.accumulate = a.accumulate; p.tiles_m = p.tiles_n = 0;
   p.m_dev = a.m_dev; p.m_off = (int)a.m_off; p.k_dev = a.k_dev; p.k_off = (int)a.k_off;
-  p.split_s = 1; p.split_full = 0; p.split_scratch = nullptr;
-  const SplitPlan sp = plan_split(a);
-  if (sp.s > 1 && a.scratch && a.scratch_bytes >= sp.bytes && (((uintptr_t)a.scratch) & 15) == 0) {
-    p.split_s = sp.s; p.split_full = sp.full; p.split_scratch = (float*)a.scratch;
+  p.split = kSplitNone; p.split_s = 1; p.split_full = 0; p.split_scratch = nullptr;
+  int64_t split_blocks = 0, split_tail = 0;
+  const bool scratch_ok = a.scratch && (((uintptr_t)a.scratch) & 15) == 0;
+  const SplitPlan tail = plan_split(a);
+  int BT = tile_edge(a);
+  if (tail.s > 1) {
+    if (scratch_ok && a.scratch_bytes >= tail.bytes) {
+      p.split = kSplitTail; p.split_s = tail.s; p.split_full = tail.full; p.split_scratch = (float*)a.scratch;
+    }
+  } else {
+    const SplitGrid sp = plan_split_all(a, BT);
+    if (sp.blocks > 0 && scratch_ok && a.scratch_bytes >= sp.bytes) {
+      p.split = kSplitAll; p.split_scratch = (float*)a.scratch;
+      split_blocks = sp.blocks; split_tail = sp.tail;
+    } else if (sp.blocks > 0 && tile_count(a.M, a.N, 256) < 200) {
+      BT = 128;   // chosen for its split: without scratch, too few large tiles to run them whole
+    }
   }
   const bool f32out = a.out_dtype == kF32;
   hipError_t e = hipErrorInvalidValue;
   switch (a.layout) {
-    case kNT: e = f32out ? launch_layout<false, false, float>(p, s) : launch_layout<false, false, bf16_t>(p, s); break;
-    case kNN: e = f32out ? launch_layout<false, true, float>(p, s) : launch_layout<false, true, bf16_t>(p, s); break;
-    case kTN: e = f32out ? launch_layout<true, true, float>(p, s) : launch_layout<true, true, bf16_t>(p, s); break;
+    case kNT: e = f32out ? launch_layout<false, false, float>(p, BT, split_blocks, split_tail, s) : launch_layout<false, false, bf16_t>(p, BT, split_blocks, split_tail, s); break;
+    case kNN: e = f32out ? launch_layout<false, true, float>(p, BT, split_blocks, split_tail, s) : launch_layout<false, true, bf16_t>(p, BT, split_blocks, split_tail, s); break;
+    case kTN: e = f32out ? launch_layout<true, true, float>(p, BT, split_blocks, split_tail, s) : launch_layout<true, true, bf16_t>(p, BT, split_blocks, split_tail, s); break;
   }
-  if (e != hipSuccess || p.split_s <= 1) return e;
+  if (e != hipSuccess || p.split != kSplitTail) return e;
   const int tiles_n = (p.N + 255) / 256;
   const int ntail = ((p.M + 255) / 256) * tiles_n - p.split_full;
   hipLaunchKernelGGL(splitk_fixup_kernel, dim3((unsigned)ntail * 8u), dim3(256), 0, s, (float*)p.C, p.ldc, p.M, p.N, tiles_n,

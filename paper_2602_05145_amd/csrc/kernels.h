@@ -32,9 +32,9 @@ struct GemmArgs {
   // M / K above stay the upper bounds the grid is sized for; tiles past the effective size exit at once.
   const int* m_dev; int64_t m_off;
   const int* k_dev; int64_t k_off;
-  // Optional device scratch (16-byte aligned) of gemm_splitk_scratch_bytes(args) bytes: with it, a launch whose
-  // tiles leave the last round of the 256 CUs at most half full splits those tiles over K (fp32 results only;
-  // the partial sums are added in a fixed order by a second small kernel).  Without it nothing is split.
+  // Optional device scratch (16-byte aligned) of gemm_splitk_scratch_bytes(args) bytes: with it, a launch whose tiles
+  // do not fill the 256 CUs, or leave its last round partly filled, splits those tiles over K (the partial sums are
+  // added in a fixed order by a second small kernel).  Without it nothing is split.
   void* scratch; size_t scratch_bytes;
 };
 bool gemm_mfma_supported(const GemmArgs& a);

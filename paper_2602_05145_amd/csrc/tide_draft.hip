@@ -179,18 +179,28 @@ Plan make_plan(const tide_draft_config* c) {
   p.delta = bwd_take((size_t)c->batch * c->n_heads * c->seq * 4);
   p.dg_partial = bwd_take(rmsnorm_bwd_scratch_bytes(p.T, (int)p.d));
   {
-    // the largest split-K scratch any weight-gradient product of this configuration asks for
-    const int64_t shapes[7][2] = {{p.V, p.d}, {p.d, p.F}, {p.F, p.d}, {p.d, p.nq}, {p.nqkv, p.d}, {p.d, p.KH}, {p.d, 2 * p.d}};
+    // the largest split-K scratch any product of this configuration asks for
     size_t need = 0;
-    for (auto& sh : shapes) {
+    auto ask = [&](int layout, int64_t M, int64_t N, int64_t K, int64_t K2, int64_t lda, int64_t ldb, int64_t ldc, bool rows_on_device) {
       GemmArgs g;
       std::memset(&g, 0, sizeof(g));
-      g.layout = kTN; g.M = sh[0]; g.N = sh[1]; g.K = p.T; g.lda = sh[0]; g.ldb = sh[1]; g.ldc = sh[1];
-      g.in_dtype = c->dtype == TIDE_DTYPE_BF16 ? kBF16 : kF32; g.out_dtype = kF32;
+      g.layout = layout; g.M = M; g.N = N; g.K = K; g.K2 = K2; g.lda = lda; g.ldb = ldb; g.ldc = ldc;
+      g.in_dtype = c->dtype == TIDE_DTYPE_BF16 ? kBF16 : kF32; g.out_dtype = layout == kTN ? kF32 : g.in_dtype;
       g.A = g.B = g.C = (void*)256;   // alignment only
+      if (K2) g.A2 = g.B2 = (void*)256;
+      if (rows_on_device) g.m_dev = (const int*)256;
       const size_t n = gemm_splitk_scratch_bytes(g);
       if (n > need) need = n;
-    }
+    };
+    // weight gradients
+    const int64_t dw[7][3] = {{p.V, p.d, p.ldz}, {p.d, p.F, p.d}, {p.F, p.d, p.F}, {p.d, p.nq, p.d}, {p.nqkv, p.d, p.nqkv}, {p.d, p.KH, p.d}, {p.d, p.d, p.d}};
+    for (auto& sh : dw) ask(kTN, sh[0], sh[1], p.T, 0, sh[2], sh[1], sh[1], false);
+    // forward products and input gradients: over all rows, or over the selected ones (their number is on the device; what
+    // T rows ask for then covers every smaller row block of the LM head)
+    const int64_t fwd[7][4] = {{p.d, p.KH, 0, 0}, {p.d, p.d, p.d, 0}, {p.nqkv, p.d, 0, 0}, {p.d, p.nq, 0, 1}, {p.F, p.d, 0, 1}, {p.d, p.F, 0, 1}, {p.V, p.d, 0, 1}};
+    for (auto& sh : fwd) ask(kNT, p.T, sh[0], sh[1], sh[2], sh[1], sh[2] ? 2 * p.d : sh[1], sh[0] == p.V ? p.ldz : sh[0], sh[3] != 0);
+    const int64_t dx[6][4] = {{p.d, p.V, 0, 1}, {p.F, p.d, 0, 1}, {p.d, p.F, p.F, 1}, {p.nq, p.d, 0, 1}, {p.d, p.nqkv, 0, 0}, {p.d, p.d, 0, 0}};
+    for (auto& sh : dx) ask(kNN, p.T, sh[0], sh[1], sh[2], sh[1] == p.V ? p.ldz : sh[1], sh[0], sh[0], sh[3] != 0);
     p.splitk_bytes = need;
     p.splitk = b.take(need ? need : 16);
   }
@@ -239,6 +249,13 @@ GemmArgs gemm_args(int layout, int64_t M, int64_t N, int64_t K, const void* A, i
   g.A = A; g.lda = lda; g.B = B; g.ldb = ldb; g.C = C; g.ldc = ldc;
   g.alpha = 1.0f; g.in_dtype = in_dt; g.out_dtype = out_dt;
   return g;
+}
+
+// launch_gemm with the workspace's split-K scratch (the products of a call run one after the other on its stream)
+hipError_t run_gemm(GemmArgs g, char* ws, const Plan& p, hipStream_t s) {
+  g.scratch = ws + p.splitk;
+  g.scratch_bytes = p.splitk_bytes;
+  return launch_gemm(g, s);
 }
 
 // How the T = batch * seq rows split into sequences: the fixed layout (cu == nullptr: `n` sequences of
@@ -306,22 +323,22 @@ int enqueue_trunk(const tide_draft_config* c, const tide_draft_tensors* P, const
       TIDE_HIP(launch_embed_rows(T, (int)p.d, tok->embed, tok->embed_rows, tok->input_ids, ws + p.e0, dt, s), "embed rows");
       GemmArgs g = gemm_args(kNT, T, p.d, p.d, ws + p.g0, p.d, tok->w_in, 2 * p.d, ws + p.x0, p.d, dt, dt);
       g.A2 = ws + p.e0; g.B2 = (const char*)tok->w_in + (size_t)p.d * p.es; g.K2 = p.d;
-      TIDE_HIP(launch_gemm(g, s), "gemm in");
+      TIDE_HIP(run_gemm(g, ws, p, s), "gemm in");
     }
   } else if (!tok) {
     // x0 = Hcat W_fc^T
-    TIDE_HIP(launch_gemm(gemm_args(kNT, T, p.d, p.KH, hidden_buf, p.KH, P->w_fc, p.KH, ws + p.x0, p.d, dt, dt), s), "gemm fc");
+    TIDE_HIP(run_gemm(gemm_args(kNT, T, p.d, p.KH, hidden_buf, p.KH, P->w_fc, p.KH, ws + p.x0, p.d, dt, dt), ws, p, s), "gemm fc");
   } else {
     // token-input variant: g = Hcat W_fc^T, e = embed[input_ids], x0 = [g ; e] W_in^T as ONE contraction over
     // the two operand pairs (g, W_in[:, :d]) and (e, W_in[:, d:]); W_in's row stride is 2d for both halves
-    TIDE_HIP(launch_gemm(gemm_args(kNT, T, p.d, p.KH, hidden_buf, p.KH, P->w_fc, p.KH, ws + p.g0, p.d, dt, dt), s), "gemm fc");
+    TIDE_HIP(run_gemm(gemm_args(kNT, T, p.d, p.KH, hidden_buf, p.KH, P->w_fc, p.KH, ws + p.g0, p.d, dt, dt), ws, p, s), "gemm fc");
     TIDE_HIP(launch_embed_rows(T, (int)p.d, tok->embed, tok->embed_rows, tok->input_ids, ws + p.e0, dt, s), "embed rows");
     GemmArgs g = gemm_args(kNT, T, p.d, p.d, ws + p.g0, p.d, tok->w_in, 2 * p.d, ws + p.x0, p.d, dt, dt);
     g.A2 = ws + p.e0; g.B2 = (const char*)tok->w_in + (size_t)p.d * p.es; g.K2 = p.d;
-    TIDE_HIP(launch_gemm(g, s), "gemm in");
+    TIDE_HIP(run_gemm(g, ws, p, s), "gemm in");
   }
   TIDE_HIP(launch_rmsnorm_fwd(T, (int)p.d, ws + p.x0, P->g1, c->rms_eps, ws + p.a, (float*)(ws + p.r1), dt, nullptr, s), "rmsnorm1");
-  TIDE_HIP(launch_gemm(gemm_args(kNT, T, p.nqkv, p.d, ws + p.a, p.d, P->w_qkv, p.d, ws + p.qkv, p.nqkv, dt, dt), s), "gemm qkv");
+  TIDE_HIP(run_gemm(gemm_args(kNT, T, p.nqkv, p.d, ws + p.a, p.d, P->w_qkv, p.d, ws + p.qkv, p.nqkv, dt, dt), ws, p, s), "gemm qkv");
   TIDE_HIP(launch_rope_table(q.max_len + shift, c->head_dim, c->rope_theta, (float*)(ws + p.rope_cs), s), "rope table");
   { const int rc = enqueue_rope(c, q, ws, p, ws + p.qkv, 0, shift, s); if (rc) return rc; }
   // later step of the unroll: keep the step's own key/value pair aside and attend to the step-1 keys/values
@@ -351,16 +368,16 @@ int enqueue_trunk(const tide_draft_config* c, const tide_draft_tensors* P, const
   {
     GemmArgs g = rows_gemm(kNT, p.d, p.nq, ws + p.A_c, p.nq, P->w_o, p.nq, ws + p.x1, p.d);
     g.residual = ws + p.x0_c; g.ldr = p.d;
-    TIDE_HIP(launch_gemm(g, s), "gemm o");
+    TIDE_HIP(run_gemm(g, ws, p, s), "gemm o");
   }
   TIDE_HIP(launch_rmsnorm_fwd(T, (int)p.d, ws + p.x1, P->g2, c->rms_eps, ws + p.bn, (float*)(ws + p.r2), dt, cnt, s), "rmsnorm2");
-  TIDE_HIP(launch_gemm(rows_gemm(kNT, p.F, p.d, ws + p.bn, p.d, P->w_gate, p.d, ws + p.gt, p.F), s), "gemm gate");
-  TIDE_HIP(launch_gemm(rows_gemm(kNT, p.F, p.d, ws + p.bn, p.d, P->w_up, p.d, ws + p.u, p.F), s), "gemm up");
+  TIDE_HIP(run_gemm(rows_gemm(kNT, p.F, p.d, ws + p.bn, p.d, P->w_gate, p.d, ws + p.gt, p.F), ws, p, s), "gemm gate");
+  TIDE_HIP(run_gemm(rows_gemm(kNT, p.F, p.d, ws + p.bn, p.d, P->w_up, p.d, ws + p.u, p.F), ws, p, s), "gemm up");
   TIDE_HIP(launch_swiglu_fwd(T * p.F, ws + p.gt, ws + p.u, ws + p.h, dt, p.F, cnt, s), "swiglu");
   {
     GemmArgs g = rows_gemm(kNT, p.d, p.F, ws + p.h, p.F, P->w_down, p.F, ws + p.x2, p.d);
     g.residual = ws + p.x1; g.ldr = p.d;
-    TIDE_HIP(launch_gemm(g, s), "gemm down");
+    TIDE_HIP(run_gemm(g, ws, p, s), "gemm down");
   }
   TIDE_HIP(launch_rmsnorm_fwd(T, (int)p.d, ws + p.x2, P->g3, c->rms_eps, ws + p.yhat, (float*)(ws + p.r3), dt, cnt, s), "rmsnorm3");
   return TIDE_OK;
@@ -396,7 +413,7 @@ int enqueue_lm_head(const tide_draft_config* c, const tide_draft_tensors* P, tid
     {
       GemmArgs g = gemm_args(kNT, rows, p.V, p.d, yb, p.d, P->w_lm, p.d, z, p.ldz, dt, dt);
       g.m_dev = cnt; g.m_off = r0;
-      TIDE_HIP(launch_gemm(g, s), "gemm lm_head");
+      TIDE_HIP(run_gemm(g, ws, p, s), "gemm lm_head");
     }
     if (train) {
       TIDE_HIP(launch_ce_train(rows, (int)p.V, z, p.ldz, tokens_c + r0, mask_c + r0, lse + r0, loss_rows + r0, cnt, r0, dt, s), "ce train");
@@ -409,7 +426,7 @@ int enqueue_lm_head(const tide_draft_config* c, const tide_draft_tensors* P, tid
       GemmArgs g = gemm_args(kNN, rows, p.d, p.V, z, p.ldz, P->w_lm, p.d, ws + p.dyhat + (size_t)r0 * p.d * p.es, p.d, dt, dt);
       g.alpha = grad_weight; g.alpha_dev = scal + 1;
       g.m_dev = cnt; g.m_off = r0;
-      TIDE_HIP(launch_gemm(g, s), "gemm dyhat");
+      TIDE_HIP(run_gemm(g, ws, p, s), "gemm dyhat");
     }
     if (!all_rows) {
       // dW_lm (+)= (1/N) dZ^T yhat of this block
@@ -417,8 +434,7 @@ int enqueue_lm_head(const tide_draft_config* c, const tide_draft_tensors* P, tid
       g.alpha = grad_weight; g.alpha_dev = scal + 1;
       g.accumulate = blk > 0 || add_to_dw;
       g.k_dev = cnt; g.k_off = r0;
-      g.scratch = ws + p.splitk; g.scratch_bytes = p.splitk_bytes;
-      TIDE_HIP(launch_gemm(g, s), "gemm dW_lm");
+      TIDE_HIP(run_gemm(g, ws, p, s), "gemm dW_lm");
     }
   }
   if (train && all_rows) {
@@ -427,8 +443,7 @@ int enqueue_lm_head(const tide_draft_config* c, const tide_draft_tensors* P, tid
     g.alpha = grad_weight; g.alpha_dev = scal + 1;
     g.accumulate = add_to_dw;
     g.k_dev = cnt; g.k_off = 0;
-    g.scratch = ws + p.splitk; g.scratch_bytes = p.splitk_bytes;
-    TIDE_HIP(launch_gemm(g, s), "gemm dW_lm");
+    TIDE_HIP(run_gemm(g, ws, p, s), "gemm dW_lm");
   }
   TIDE_HIP(launch_loss_reduce(loss_rows, hit_rows, cnt, scal, loss_out, acc_out, (int*)(ws + p.status), s), "loss reduce");
   return TIDE_OK;
@@ -627,33 +642,31 @@ static int enqueue_backward(const tide_draft_config* cfg, const tide_draft_tenso
     GemmArgs g = gemm_args(kTN, M, N, T, A, lda, B, ldb, C, ldc, dt, kF32);
     g.k_dev = cnt;
     g.accumulate = acc;
-    g.scratch = ws + p.splitk; g.scratch_bytes = p.splitk_bytes;
     return g;
   };
   auto full_dw = [&](int64_t M, int64_t N, const void* A, int64_t lda, const void* B, int64_t ldb, void* C, int64_t ldc, int add) {
     GemmArgs g = gemm_args(kTN, M, N, T, A, lda, B, ldb, C, ldc, dt, kF32);
     g.accumulate = add;
-    g.scratch = ws + p.splitk; g.scratch_bytes = p.splitk_bytes;
     return g;
   };
   // final norm (plus, in the unroll, what the step after sends back into x2)
   TIDE_HIP(launch_rmsnorm_bwd(T, (int)p.d, ws + p.dyhat, ws + p.x2, P->g3, (const float*)(ws + p.r3), o.dx2_extra, ws + p.dx2, (float*)G->g3, dgp, dt, cnt, s, acc), "rmsnorm3 bwd");
   // x2 = x1 + h W_down^T
-  TIDE_HIP(launch_gemm(rows_dx(p.F, p.d, ws + p.dx2, p.d, P->w_down, p.F, ws + p.dh, p.F), s), "gemm dh");
-  TIDE_HIP(launch_gemm(rows_dw(p.d, p.F, ws + p.dx2, p.d, ws + p.h, p.F, G->w_down, p.F), s), "gemm dW_down");
+  TIDE_HIP(run_gemm(rows_dx(p.F, p.d, ws + p.dx2, p.d, P->w_down, p.F, ws + p.dh, p.F), ws, p, s), "gemm dh");
+  TIDE_HIP(run_gemm(rows_dw(p.d, p.F, ws + p.dx2, p.d, ws + p.h, p.F, G->w_down, p.F), ws, p, s), "gemm dW_down");
   TIDE_HIP(launch_swiglu_bwd(T * p.F, ws + p.dh, ws + p.gt, ws + p.u, ws + p.gt, ws + p.u, dt, p.F, cnt, s), "swiglu bwd");
   {
     // d bn = dGate W_gate + dUp W_up: one contraction over both operand pairs
     GemmArgs g = rows_dx(p.d, p.F, ws + p.gt, p.F, P->w_gate, p.d, ws + p.dbn, p.d);
     g.A2 = ws + p.u; g.B2 = P->w_up; g.K2 = p.F;
-    TIDE_HIP(launch_gemm(g, s), "gemm dbn");
+    TIDE_HIP(run_gemm(g, ws, p, s), "gemm dbn");
   }
-  TIDE_HIP(launch_gemm(rows_dw(p.F, p.d, ws + p.gt, p.F, ws + p.bn, p.d, G->w_gate, p.d), s), "gemm dW_gate");
-  TIDE_HIP(launch_gemm(rows_dw(p.F, p.d, ws + p.u, p.F, ws + p.bn, p.d, G->w_up, p.d), s), "gemm dW_up");
+  TIDE_HIP(run_gemm(rows_dw(p.F, p.d, ws + p.gt, p.F, ws + p.bn, p.d, G->w_gate, p.d), ws, p, s), "gemm dW_gate");
+  TIDE_HIP(run_gemm(rows_dw(p.F, p.d, ws + p.u, p.F, ws + p.bn, p.d, G->w_up, p.d), ws, p, s), "gemm dW_up");
   TIDE_HIP(launch_rmsnorm_bwd(T, (int)p.d, ws + p.dbn, ws + p.x1, P->g2, (const float*)(ws + p.r2), ws + p.dx2, ws + p.dx1_c, (float*)G->g2, dgp, dt, cnt, s, acc), "rmsnorm2 bwd");
   // x1 = x0 + A W_o^T
-  TIDE_HIP(launch_gemm(rows_dx(p.nq, p.d, ws + p.dx1_c, p.d, P->w_o, p.nq, ws + p.dA_c, p.nq), s), "gemm dA");
-  TIDE_HIP(launch_gemm(rows_dw(p.d, p.nq, ws + p.dx1_c, p.d, ws + p.A_c, p.nq, G->w_o, p.nq), s), "gemm dW_o");
+  TIDE_HIP(run_gemm(rows_dx(p.nq, p.d, ws + p.dx1_c, p.d, P->w_o, p.nq, ws + p.dA_c, p.nq), ws, p, s), "gemm dA");
+  TIDE_HIP(run_gemm(rows_dw(p.d, p.nq, ws + p.dx1_c, p.d, ws + p.A_c, p.nq, G->w_o, p.nq), ws, p, s), "gemm dW_o");
   // back to one row per position: rows that were not selected get no gradient from above (only, through
   // the attention, from the later rows that read their key and value)
   TIDE_HIP(launch_scatter_rows(T, (int)p.nq, ws + p.dA_c, ws + p.dA, (int)p.d, ws + p.dx1_c, ws + p.dx1, (const int32_t*)(ws + p.row_pos), dt, s), "scatter rows");
@@ -678,23 +691,23 @@ static int enqueue_backward(const tide_draft_config* cfg, const tide_draft_tenso
   // them zero before the contractions over all rows
   if (q.cu) TIDE_HIP(launch_zero_padding_rows(ws + p.dqkv, q.cu, q.n, T, (int64_t)(p.nqkv * p.es), s), "zero padding rows");
   { const int rc2 = enqueue_rope(cfg, q, ws, p, ws + p.dqkv, 1, shift, s); if (rc2) return rc2; }
-  TIDE_HIP(launch_gemm(gemm_args(kNN, T, p.d, p.nqkv, ws + p.dqkv, p.nqkv, P->w_qkv, p.d, ws + p.da, p.d, dt, dt), s), "gemm da");
-  TIDE_HIP(launch_gemm(full_dw(p.nqkv, p.d, ws + p.dqkv, p.nqkv, ws + p.a, p.d, G->w_qkv, p.d, acc), s), "gemm dW_qkv");
+  TIDE_HIP(run_gemm(gemm_args(kNN, T, p.d, p.nqkv, ws + p.dqkv, p.nqkv, P->w_qkv, p.d, ws + p.da, p.d, dt, dt), ws, p, s), "gemm da");
+  TIDE_HIP(run_gemm(full_dw(p.nqkv, p.d, ws + p.dqkv, p.nqkv, ws + p.a, p.d, G->w_qkv, p.d, acc), ws, p, s), "gemm dW_qkv");
   TIDE_HIP(launch_rmsnorm_bwd(T, (int)p.d, ws + p.da, ws + p.x0, P->g1, (const float*)(ws + p.r1), ws + p.dx1, ws + p.dx0, (float*)G->g1, dgp, dt, nullptr, s, acc), "rmsnorm1 bwd");
   const void* dfeat = ws + p.dx0;   // gradient of the step's input feature (feature-only model: x0 is the feature)
   if (tok) {
     // x0 = [g ; e] W_in^T: dW_in = dx0^T [g ; e] (two products into the column halves of dW_in), dg = dx0 W_in[:, :d]
     // (the embedding table is frozen)
     float* dwin = (float*)tok->grad_w_in;
-    TIDE_HIP(launch_gemm(full_dw(p.d, p.d, ws + p.dx0, p.d, ws + p.g0, p.d, dwin, 2 * p.d, acc), s), "gemm dW_in (features)");
-    TIDE_HIP(launch_gemm(full_dw(p.d, p.d, ws + p.dx0, p.d, ws + p.e0, p.d, dwin + p.d, 2 * p.d, acc), s), "gemm dW_in (embeddings)");
-    TIDE_HIP(launch_gemm(gemm_args(kNN, T, p.d, p.d, ws + p.dx0, p.d, tok->w_in, 2 * p.d, ws + p.dg0, p.d, dt, dt), s), "gemm dg");
+    TIDE_HIP(run_gemm(full_dw(p.d, p.d, ws + p.dx0, p.d, ws + p.g0, p.d, dwin, 2 * p.d, acc), ws, p, s), "gemm dW_in (features)");
+    TIDE_HIP(run_gemm(full_dw(p.d, p.d, ws + p.dx0, p.d, ws + p.e0, p.d, dwin + p.d, 2 * p.d, acc), ws, p, s), "gemm dW_in (embeddings)");
+    TIDE_HIP(run_gemm(gemm_args(kNN, T, p.d, p.d, ws + p.dx0, p.d, tok->w_in, 2 * p.d, ws + p.dg0, p.d, dt, dt), ws, p, s), "gemm dg");
     dfeat = ws + p.dg0;
   }
   if (shift == 0) {
     // the feature is Hcat W_fc^T: weight gradient only, the captured states are data (step 1 is the only one
     // that reads W_fc, so this is never an accumulation)
-    TIDE_HIP(launch_gemm(full_dw(p.d, p.KH, dfeat, p.d, hidden_buf, p.KH, G->w_fc, p.KH, 0), s), "gemm dW_fc");
+    TIDE_HIP(run_gemm(full_dw(p.d, p.KH, dfeat, p.d, hidden_buf, p.KH, G->w_fc, p.KH, 0), ws, p, s), "gemm dW_fc");
   } else {
     // the feature is the layer output of the step before: hand its gradient over, dense over that step's rows
     TIDE_HIP(launch_gather_rows(T, (int)p.d, dfeat, o.dfeat_out, 0, nullptr, nullptr, o.prev_tokens, (const uint8_t*)(o.prev_ws + p.mask_eff),
@@ -941,6 +954,8 @@ size_t tide_gemm_workspace_bytes(int layout, int64_t M, int64_t N, int64_t K, in
   if (layout < 0 || layout > 2 || M <= 0 || N <= 0 || K <= 0) return 0;
   const int64_t lda = layout == kTN ? M : K, ldb = layout == kNT ? K : N;
   GemmArgs g = gemm_args(layout, M, N, K, (void*)256, lda, (void*)256, ldb, (void*)256, N, kBF16, out_dtype);
+  // a bf16 result of a whole round of 256 x 256 tiles or more asks for nothing here
+  if (out_dtype == TIDE_DTYPE_BF16 && ((M + 255) / 256) * ((N + 255) / 256) >= 256) return 0;
   return gemm_splitk_scratch_bytes(g);
 }
 

@@ -66,3 +66,82 @@ def test_fp32_products_at_the_edges_of_their_tiles(B, layout, M, N, K):
     _gemm(B, layout, M, N, K, a, b, c, "fp32", "fp32", alpha=-1.5, residual=res, accumulate=1)
     want = -1.5 * ref + res.double() + c0.double()
     assert float((c.double() - want).abs().max()) < 2e-6 * max(1.0, float(want.abs().max()))
+
+
+@pytest.mark.parametrize("layout", [0, 1, 2])
+@pytest.mark.parametrize("M,N,K,split", [(8, 8, 704, False), (8, 8, 1408, True), (136, 264, 2056, True), (304, 4096, 4104, True),
+                                         (169, 688, 2560, True), (1024, 1000, 8000, True), (3000, 1032, 800, False)])
+def test_small_results_split_over_k(B, layout, M, N, K, split):
+    """Fewer tiles of 128 than the chip runs at a time: with a workspace each tile's K range is shared by several blocks
+    and a second kernel adds the partial sums.  Odd M, ragged K; residual, alpha and accumulation in the second kernel; and
+    the same call without a workspace."""
+    if layout == B.LAYOUT_TN and M % 8:
+        M += 8 - M % 8
+    a, b, ref = _operands(B, layout, M, N, K, "bf16", M + 7 * K)
+    g = torch.Generator(device=DEV).manual_seed(9)
+    top = float(ref.abs().max())
+    tiles, slabs = ((M + 127) // 128) * ((N + 127) // 128), (K + 63) // 64
+    need = B.tide_gemm_workspace_bytes(layout, M, N, K, 0)
+    assert need % (tiles * 65536) == 0 and (need > 0) == split     # whole partial sums, and two parts or more
+    assert need <= min(512, tiles * slabs // 4) * 65536
+    for out in ("fp32", "bf16"):
+        dt = DT[out][1]
+        res, c0 = (torch.randn(M, N, device=DEV, generator=g).to(dt) for _ in range(2))
+        tol = 2e-5 if out == "fp32" else 6e-3      # bf16: the rounding of the result
+        c = torch.full((M, N), float("nan"), device=DEV, dtype=dt)
+        _gemm(B, layout, M, N, K, a, b, c, "bf16", out)
+        assert float((c.double() - ref).abs().max()) < tol * top
+        plain = torch.full((M, N), float("nan"), device=DEV, dtype=dt)
+        B.tide_gemm(layout, M, N, K, 1.0, a, b, plain, None, 1, DT[out][0], 0, stream())
+        sync()
+        assert float((plain.double() - c.double()).abs().max()) < (5e-6 if out == "fp32" else tol) * top
+        c = c0.clone()
+        _gemm(B, layout, M, N, K, a, b, c, "bf16", out, alpha=0.5, residual=res, accumulate=1)
+        want = 0.5 * ref + res.double() + c0.double()
+        assert float((c.double() - want).abs().max()) < tol * float(want.abs().max())
+
+
+@pytest.mark.parametrize("layout", [0, 1, 2])
+@pytest.mark.parametrize("M,N,K", [(1000, 512, 32008), (2040, 1544, 20000), (2296, 1016, 12288)])
+def test_large_tiles_split_over_k(B, layout, M, N, K):
+    """Few tiles with a long contraction, where the split runs on 256 x 256 tiles.  Ragged M, N and K, bf16 and fp32 results,
+    residual and alpha in the second kernel."""
+    assert B.tide_gemm_workspace_bytes(layout, M, N, K, 1) > 0
+    a, b, ref = _operands(B, layout, M, N, K, "bf16", M + K)
+    for out, tol in (("fp32", 2e-5), ("bf16", 6e-3)):
+        dt = DT[out][1]
+        res = torch.randn(M, N, device=DEV).to(dt)
+        c = torch.full((M, N), float("nan"), device=DEV, dtype=dt)
+        _gemm(B, layout, M, N, K, a, b, c, "bf16", out, alpha=0.25, residual=res)
+        want = 0.25 * ref + res.double()
+        assert float((c.double() - want).abs().max()) < tol * float(want.abs().max())
+
+
+def test_split_products_of_a_training_step_with_few_kept_rows():
+    """The number of rows behind the attention is on the device only: with one sequence in eight carrying loss, the same
+    launches come out with other numbers of parts.  Against the oracle."""
+    import numpy as np
+    from oracle import tide_oracle as O
+    from paper_2602_05145_amd import runtime, workloads as W
+    cfg = W.get_config("small", batch=8, seq=96, target_hidden=512, hidden=512, n_heads=4, n_kv_heads=2, head_dim=128, ffn=2048, vocab=8008,
+                       mask="none", seed=31)
+    wl = W.make_workload(cfg)
+    for kept in (8, 1, 0):
+        mask = np.zeros_like(wl["mask"])
+        mask[:kept] = 1
+        tr = runtime.DraftTrainer(cfg, wl["params"])
+        tr.set_batch(wl["hidden"], wl["tokens"], mask)
+        tr.workspace.fill_(0xFF)
+        print(f"split step kept={kept}", flush=True)
+        tr.train_step(cfg["lr"])
+        sync()
+        p0 = {k: np.asarray(v, np.float64) for k, v in wl["params"].items()}
+        z = {k: np.zeros_like(v) for k, v in p0.items()}
+        loss, grads, *_ = O.train_step(cfg, p0, z, z, 0, wl["hidden"].astype(np.float64), wl["tokens"], mask, cfg["lr"])
+        assert abs(float(tr.loss.item()) - loss) <= 1e-2 * abs(loss)
+        for k, r in grads.items():
+            g, r = tr.host(tr.grads)[k].reshape(-1), r.reshape(-1)
+            if kept:
+                assert g @ r / (np.linalg.norm(g) * np.linalg.norm(r)) > 0.999, (kept, k)
+            else:
+                assert not g.any(), k
