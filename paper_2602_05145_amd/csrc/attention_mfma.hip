@@ -24,10 +24,12 @@
 // fragments and two 32x128 accumulators), i.e. one block per CU with nothing to hide the exponentials behind;
 // the two halves need 168 and 212, run 3 and 2 blocks per CU, and together take 0.7x the fused time although
 // S = Q K^T is computed twice.
+// Where blocks are few, a block is 64 keys and eight waves in four sets that share the query tiles (kFewKW, kFewNS).
 // Every streamed tile reaches LDS by LDS-DMA loads (no staging registers); operand fragments are read from LDS
 // through small register rings, a few MFMAs ahead of their use.
 // Causality: tiles entirely above the diagonal are never loaded; heavy blocks are scheduled first; the
 // per-element causal test is made only by the (wave-uniformly chosen) tiles that touch the diagonal.
+#include <algorithm>
 #include <type_traits>
 
 #include "kernels.h"
@@ -133,7 +135,7 @@ __device__ __forceinline__ int acc_row(int q, int g) { return 8 * (q >> 2) + 4 *
 // Staging of a tile of 64 or 32 rows x D columns (bf16) of a row-major global matrix in LDS, without registers:
 // LDS-DMA loads (16 bytes per lane straight into LDS, written as instructions so that the waits are this file's
 // own: the compiler does not see that they write LDS).  A 64-row tile with its 272-byte (D = 64: 144-byte)
-// pitch is 17 (9) chunks of 1 KiB of consecutive LDS bytes; wave w issues the chunks w, w + 4, ... and lane l of chunk c
+// pitch is 17 (9) chunks of 1 KiB of consecutive LDS bytes; wave w of NW issues the chunks w, w + NW, ... and lane l of chunk c
 // fills the bytes c * 1024 + 16 l .. + 16, i.e. LDS row (c * 1024 + 16 l) / 272 = tile row perm(LDS row), 16-byte
 // piece ((c * 1024 + 16 l) % 272) / 16; the last piece of a row is its padding and loads from beyond the buffer
 // (zeros).  Rows past the end of the sequence lie beyond the buffer as well.
@@ -150,17 +152,17 @@ __device__ __forceinline__ uint32_t lds_address(const bf16_t* p) {
   typedef __attribute__((address_space(3))) const bf16_t* lds_p;
   return (uint32_t)(uintptr_t)(lds_p)p;
 }
-template <int ROWS, int D>   // rows of the tile (64, or 32: 8.5 or 4.5 chunks, the second half of the last is not part of the tile)
+template <int ROWS, int D, int NW = 4>   // NW: waves that share the loads; rows of the tile (64, or 32: 8.5 or 4.5 chunks, the second half of the last is not part of the tile)
 struct TileDma {
   static constexpr int PITCH = pitch(D);
   static constexpr int BYTES = ROWS * PITCH * 2;
   static constexpr int CHUNKS = (BYTES + 1023) / 1024;   // D = 128: 17 / 9, D = 64: 9 / 5
-  static constexpr int PER_WAVE = (CHUNKS + 3) / 4;      // 5 / 3 and 3 / 2 (the last only in wave 0)
+  static constexpr int PER_WAVE = (CHUNKS + NW - 1) / NW;   // the last not in every wave
   uint32_t voff[PER_WAVE];   // byte offset of the lane's piece from the tile's first element (beyond any buffer: padding)
   __device__ __forceinline__ void init(int ld, int wave, int lane) {
 #pragma unroll
     for (int i = 0; i < PER_WAVE; ++i) {
-      const int o = (wave + 4 * i) * 1024 + lane * 16;
+      const int o = (wave + NW * i) * 1024 + lane * 16;
       const int R = o / (PITCH * 2), piece = (o % (PITCH * 2)) / 16;
       // 2^31 plus any offset inside a sequence (below 2^31, see attn_mfma_supported) stays beyond the buffer and does not wrap
       voff[i] = (piece < D / 8 && o < BYTES) ? (uint32_t)(perm(R) * ld + piece * 8) * 2u : 0x80000000u;
@@ -171,13 +173,13 @@ struct TileDma {
     const uint32_t base = lds_address(tile);
 #pragma unroll
     for (int i = 0; i < PER_WAVE; ++i)
-      if (wave_s + 4 * i < CHUNKS) dma16(rs, base + (uint32_t)(wave_s + 4 * i) * 1024u, voff[i] + tile_bytes);
+      if (wave_s + NW * i < CHUNKS) dma16(rs, base + (uint32_t)(wave_s + NW * i) * 1024u, voff[i] + tile_bytes);
   }
 };
 #define TIDE_ATTN_WAIT_DMA() __builtin_amdgcn_s_waitcnt(0x0F70)   /* vmcnt(0) */
 
 // Write a wave's 32 x D result, held transposed in D / 32 accumulators (acc[ct] = rows ct*32.., column =
-// lane % 32 = the wave-local output row), into an LDS tile [128][pitch] at rows wave*32.. as bf16.
+// lane % 32 = the wave-local output row), into an LDS tile [rows][pitch] at rows wave*32.. as bf16.
 template <int D>
 __device__ __forceinline__ void stage_out(bf16_t* tile, const f32x16_t (&acc)[D / 32], float mul, int wave, int lane) {
   const int g = lane >> 5, r = wave * 32 + (lane & 31);
@@ -193,15 +195,15 @@ __device__ __forceinline__ void stage_out(bf16_t* tile, const f32x16_t (&acc)[D 
     }
 }
 
-// Copy the staged [128][D] tile to global rows row0.. (< row_end) of a matrix with leading dim ld.
-template <int D>
+// Copy the staged [ROWS][D] tile to global rows row0.. (< row_end) of a matrix with leading dim ld; NT threads.
+template <int D, int ROWS = 128, int NT = 256>
 __device__ __forceinline__ void copy_out(const bf16_t* tile, bf16_t* dst, int64_t row0, int64_t row_end, int ld,
                                          int col0, int tid) {
 #pragma unroll
-  for (int i = 0; i < D / 16; ++i) {
-    const int p = tid + i * 256;
+  for (int i = 0; i < (ROWS * D / 8 + NT - 1) / NT; ++i) {
+    const int p = tid + i * NT;
     const int row = p / (D / 8), piece = p % (D / 8);
-    if (row0 + row < row_end)
+    if (row < ROWS && row0 + row < row_end)
       *reinterpret_cast<i32x4_t*>(dst + (size_t)(row0 + row) * ld + col0 + piece * 8) =
           *reinterpret_cast<const i32x4_t*>(tile + row * pitch(D) + piece * 8);
   }
@@ -537,30 +539,41 @@ namespace {
 #ifndef TIDE_ATTN_DK_ROWS
 #define TIDE_ATTN_DK_ROWS 64
 #endif
+// (with several sets of waves per block, 32 in both passes: the sets' stages have to fit the LDS)
+template <int WHICH, int NS>
+constexpr int dkv_rows() { return WHICH == 1 && NS == 1 ? TIDE_ATTN_DK_ROWS : TIDE_ATTN_DV_ROWS; }
 template <int BI, int D> struct DkvStage {
   static constexpr int Q_TILE = TileDma<BI, D>::CHUNKS * 512;   // elements: the tile rounded up to whole 1 KiB chunks of the LDS-DMA loads
   static constexpr int STAGE = 2 * Q_TILE + 4 * BI;          // Q tile, dO tile, then lse[BI] and delta[BI] as floats
 };
 }  // namespace
 
+// Two forms of a block.  KW = 4, NS = 1: 128 keys on four waves, every wave walks all query tiles; two or three blocks
+// share a CU and hide each other's waits.  With few blocks (a handful of sequences) there is nobody to share with, and the
+// pass takes as long as the longest chain of query tiles, G heads times the sequence: KW = 2, NS = 4 has 64 keys on two
+// waves, four such sets, each with LDS stages of its own, take every fourth query tile, and the sets' sums are added through
+// LDS at the end, in a fixed order.
+constexpr int kFewKW = 2, kFewNS = 4;
 // One gradient per pass (WHICH = 0: dV, 1: dK).  Half the accumulators and, for dV, half the operand
 // registers of the fused kernel: the pass fits 256 VGPRs, two blocks share a CU, and one block's
 // exponentials overlap the other's MFMAs.  The price is that S = Q K^T is computed in both passes.
-template <int WHICH, int D>
-__global__ __launch_bounds__(256, WHICH == 0 ? blocks_per_cu(D, 4, 3) : blocks_per_cu(D, 3, 2)) void attn_dkv_mfma_kernel(const bf16_t* __restrict__ qkv, const bf16_t* __restrict__ dout,
+template <int WHICH, int D, int KW, int NS>
+__global__ __launch_bounds__(KW * NS * 64, NS > 1 ? 1 : WHICH == 0 ? blocks_per_cu(D, 4, 3) : blocks_per_cu(D, 3, 2)) void attn_dkv_mfma_kernel(const bf16_t* __restrict__ qkv, const bf16_t* __restrict__ dout,
                                                             const float* __restrict__ lse, const float* __restrict__ delta,
                                                             bf16_t* __restrict__ dqkv, int Smax, int nh, int nkv,
                                                             const int* __restrict__ cu, int64_t T, int nseq) {
   extern __shared__ __attribute__((aligned(16))) bf16_t smem[];
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  constexpr int KB = KW * 32, SET = KW * 64;   // keys of the block, threads of a set
+  const int set = NS > 1 ? __builtin_amdgcn_readfirstlane(threadIdx.x / SET) : 0;
+  const int tid = threadIdx.x - set * SET, lane = tid & 63, wave = tid >> 6;   // inside the set
   const int lr = lane & 31, g = lane >> 5, plr = perm(lr);
-  const Work3 wk = xcd_group_work((Smax + 127) / 128, nkv, nseq, 1);
+  const Work3 wk = xcd_group_work((Smax + KB - 1) / KB, nkv, nseq, 1);
   const int jb = wk.x, kh = wk.y, b = wk.z;  // early key blocks are the heavy ones
   const SeqView sv = seq_view(cu, b, Smax, T);
   const int S = sv.len;
   const int G = nh / nkv;
   const int ld = (nh + 2 * nkv) * D, ldo = nh * D;
-  const int j0 = jb * 128, jw = j0 + wave * 32, jk = jw + lr;
+  const int j0 = jb * KB, jw = j0 + wave * 32, jk = jw + lr;
   if (j0 >= S) return;   // the whole block, before any barrier
   const __amdgpu_buffer_rsrc_t rs = rsrc(qkv + (size_t)sv.row0 * ld, (uint32_t)((size_t)S * ld * 2));
   const int kcol = (nh + kh) * D, vcol = (nh + nkv + kh) * D;
@@ -568,7 +581,7 @@ __global__ __launch_bounds__(256, WHICH == 0 ? blocks_per_cu(D, 4, 3) : blocks_p
   const float c = kLog2e * scale;
 
   constexpr bool DK = WHICH == 1;
-  constexpr int BI = DK ? TIDE_ATTN_DK_ROWS : TIDE_ATTN_DV_ROWS;
+  constexpr int BI = dkv_rows<WHICH, NS>();
   constexpr int NK = D / 16, NC = D / 32;
   constexpr int Q_TILE = DkvStage<BI, D>::Q_TILE, DKV_STAGE = DkvStage<BI, D>::STAGE;
   u32x4_t kf[NK], vf[DK ? NK : 1];
@@ -590,9 +603,10 @@ __global__ __launch_bounds__(256, WHICH == 0 ? blocks_per_cu(D, 4, 3) : blocks_p
   const i32x4_t rsq = rsrc_words(qkv + (size_t)sv.row0 * ld, (uint32_t)((size_t)S * ld * 2));
   const i32x4_t rsdo = rsrc_words(dout + (size_t)sv.row0 * ldo, (uint32_t)((size_t)S * ldo * 2));
   const int wave_s = __builtin_amdgcn_readfirstlane(wave);
-  TileDma<BI, D> dmq, dmo;   // LDS-DMA loads of the Q and the dO tile (their row pitches in memory differ)
+  TileDma<BI, D, KW> dmq, dmo;   // LDS-DMA loads of the Q and the dO tile (their row pitches in memory differ)
   dmq.init(ld, wave, lane);
   dmo.init(ldo, wave, lane);
+  bf16_t* stages = smem + set * 2 * DKV_STAGE;
   float stat = 0.f;  // threads 0..BI-1 carry lse, BI..2BI-1 carry delta of the staged tile
   // Query tiles are walked from the END of the sequence down to the first one that sees this block's keys: the key
   // blocks of a kv head run side by side on one XCD, and this way all of them want the same Q / dO tile at about
@@ -604,7 +618,7 @@ __global__ __launch_bounds__(256, WHICH == 0 ? blocks_per_cu(D, 4, 3) : blocks_p
   auto gload = [&](int u, int st) {   // tile u into stage st (whose last readers have passed a barrier)
     const int hh = kh * G + u % G;
     const int i0 = tile_i0(u);
-    bf16_t* base = smem + st * DKV_STAGE;
+    bf16_t* base = stages + st * DKV_STAGE;
     dmq.issue(rsq, base, ((uint32_t)i0 * (uint32_t)ld + (uint32_t)(hh * D)) * 2u, wave_s);
     dmo.issue(rsdo, base + Q_TILE, ((uint32_t)i0 * (uint32_t)ldo + (uint32_t)(hh * D)) * 2u, wave_s);
     if (tid < 2 * BI) {
@@ -615,23 +629,26 @@ __global__ __launch_bounds__(256, WHICH == 0 ? blocks_per_cu(D, 4, 3) : blocks_p
     }
   };
   auto sstore = [&](int st) {
-    bf16_t* base = smem + st * DKV_STAGE;
+    bf16_t* base = stages + st * DKV_STAGE;
     if (tid < 2 * BI) reinterpret_cast<float*>(base + 2 * Q_TILE)[tid] = stat * ((tid < BI) ? kLog2e : 1.f);   // lse * log2(e), delta
   };
 
-  gload(0, 0);
-  sstore(0);
+  if (set < ntiles) {
+    gload(set, 0);
+    sstore(0);
+  }
   __builtin_amdgcn_s_waitcnt(0x0F70);   // vmcnt(0): the tile and the K / V fragments have arrived before the loop
   __syncthreads();
-  for (int u = 0; u < ntiles; ++u) {
-    const int st = u & 1;
-    if (u + 1 < ntiles) gload(u + 1, st ^ 1);
-    const int it0 = tile_i0(u);
+  // (the sets' trip counts differ by one at most: every set passes every barrier)
+  for (int r = 0; r * NS < ntiles; ++r) {
+    const int st = r & 1, u = r * NS + set;
+    if (u + NS < ntiles) gload(u + NS, st ^ 1);
+    const int it0 = u < ntiles ? tile_i0(u) : S;   // past the end: no half of the tile is entered
 #pragma unroll
     for (int hf = 0; hf < BI / 32; ++hf) {
     const int i0 = it0 + hf * 32;   // this half's first query
     if (i0 + 31 >= jw && i0 < S) {  // wave-uniform: some query of the half sees some key of this wave
-      const bf16_t* Qt = smem + st * DKV_STAGE;
+      const bf16_t* Qt = stages + st * DKV_STAGE;
       const bf16_t* dOt = Qt + Q_TILE;
       const float* stats = reinterpret_cast<const float*>(Qt + 2 * Q_TILE) + hf * 32;
       f32x16_t s, dp;
@@ -691,14 +708,36 @@ __global__ __launch_bounds__(256, WHICH == 0 ? blocks_per_cu(D, 4, 3) : blocks_p
         for (int ks = 0; ks < 2; ++ks) dacc[ct] = mfma_parts(frag_tr<D>(Xt, hf * 32 + ks * 16, ct * 32, lane), pf[ks], dacc[ct]);
     }
     }
-    if (u + 1 < ntiles) sstore(st ^ 1);
+    if (u + NS < ntiles) sstore(st ^ 1);
     TIDE_ATTN_WAIT_DMA();
     __syncthreads();
   }
-  const int64_t r0 = sv.row0 + j0, r1 = sv.row0 + min(S, j0 + 128);
-  stage_out<D>(smem, dacc, DK ? scale : 1.0f, wave, lane);
+  if constexpr (NS > 1) {
+    // sets n .. 2n - 1 hand their sums to sets 0 .. n - 1, for n = NS / 2, NS / 4, ... (every stage is free by now)
+    float* sums = reinterpret_cast<float*>(smem);
+#pragma unroll
+    for (int n = NS / 2; n >= 1; n /= 2) {
+      float* mine = sums + ((size_t)((set % n) * KW + wave) * NC * 16) * 64 + lane;
+      if (set >= n && set < 2 * n) {
+#pragma unroll
+        for (int ct = 0; ct < NC; ++ct)
+#pragma unroll
+          for (int q = 0; q < 16; ++q) mine[(ct * 16 + q) * 64] = dacc[ct][q];
+      }
+      __syncthreads();
+      if (set < n) {
+#pragma unroll
+        for (int ct = 0; ct < NC; ++ct)
+#pragma unroll
+          for (int q = 0; q < 16; ++q) dacc[ct][q] += mine[(ct * 16 + q) * 64];
+      }
+      __syncthreads();
+    }
+  }
+  const int64_t r0 = sv.row0 + j0, r1 = sv.row0 + min(S, j0 + KB);
+  if (set == 0) stage_out<D>(smem, dacc, DK ? scale : 1.0f, wave, lane);
   __syncthreads();
-  copy_out<D>(smem, dqkv, r0, r1, ld, DK ? kcol : vcol, tid);
+  copy_out<D, KB, SET * NS>(smem, dqkv, r0, r1, ld, DK ? kcol : vcol, threadIdx.x);
 }
 
 
@@ -715,10 +754,12 @@ bool attn_mfma_supported(const AttnArgs& a) {
 
 namespace {
 constexpr size_t fwd_smem(int D) { return (size_t)4 * kv_tile(D) * sizeof(bf16_t); }   // 69632 / 36864 B (>= the 128 x pitch output tile)
-template <int BI, int D>
+template <int WHICH, int D, int KW, int NS>
 constexpr size_t dkv_smem() {
-  const size_t st = (size_t)2 * DkvStage<BI, D>::STAGE * sizeof(bf16_t), out = (size_t)128 * pitch(D) * sizeof(bf16_t);
-  return st > out ? st : out;
+  const size_t st = (size_t)NS * 2 * DkvStage<dkv_rows<WHICH, NS>(), D>::STAGE * sizeof(bf16_t), out = (size_t)KW * 32 * pitch(D) * sizeof(bf16_t);
+  const size_t sums = NS > 1 ? (size_t)(NS / 2) * KW * (D / 32) * 16 * 64 * sizeof(float) : 0;
+  const size_t m = st > out ? st : out;
+  return m > sums ? m : sums;
 }
 
 hipError_t set_smem(const void* f, size_t bytes, bool& done) {
@@ -739,15 +780,26 @@ hipError_t launch_fwd(const AttnArgs& a, hipStream_t s) {
   return hipGetLastError();
 }
 
+template <int WHICH, int D, int KW, int NS>
+hipError_t launch_dkv(const AttnArgs& a, hipStream_t s) {
+  constexpr size_t smem = dkv_smem<WHICH, D, KW, NS>();
+  static_assert(smem <= 160 * 1024, "LDS of a CU");
+  static bool done = false;
+  const hipError_t e = set_smem((const void*)attn_dkv_mfma_kernel<WHICH, D, KW, NS>, smem, done);
+  if (e != hipSuccess) return e;
+  const dim3 grid((unsigned)((int64_t)((a.S + KW * 32 - 1) / (KW * 32)) * a.nkv * a.B));
+  hipLaunchKernelGGL((attn_dkv_mfma_kernel<WHICH, D, KW, NS>), grid, dim3(KW * NS * 64), smem, s, (const bf16_t*)a.qkv, (const bf16_t*)a.dout, a.lse, a.delta, (bf16_t*)a.dqkv, a.S, a.nh, a.nkv, a.cu_seqlens, a.total_rows, a.B);
+  return hipGetLastError();
+}
+
 template <int D>
 hipError_t launch_bwd(const AttnArgs& a, hipStream_t s) {
-  constexpr size_t kDvSmem = dkv_smem<TIDE_ATTN_DV_ROWS, D>(), kDkSmem = dkv_smem<TIDE_ATTN_DK_ROWS, D>();
-  static bool done_q = false, done_v = false, done_k = false;
+  static bool done_q = false;
   hipError_t e = launch_attn_delta(a, s);
   if (e != hipSuccess) return e;
   e = set_smem((const void*)attn_dq_mfma_kernel<D>, fwd_smem(D), done_q);
   if (e != hipSuccess) return e;
-  const dim3 gq((unsigned)((int64_t)((a.S + BQ - 1) / BQ) * a.nh * a.B)), gkv((unsigned)((int64_t)((a.S + 127) / 128) * a.nkv * a.B));
+  const dim3 gq((unsigned)((int64_t)((a.S + BQ - 1) / BQ) * a.nh * a.B));
   const double pairs = (double)a.B * a.nh * D * (double)a.S * (a.S + 1) / 2.0;  // (query, key, channel) triples
   {
     ProfScope ps("attn_dq_mfma", 6.0 * pairs, 0, s);   // S, dP and dQ products
@@ -755,14 +807,23 @@ hipError_t launch_bwd(const AttnArgs& a, hipStream_t s) {
     e = hipGetLastError();
     if (e != hipSuccess) return e;
   }
-  e = set_smem((const void*)attn_dkv_mfma_kernel<0, D>, kDvSmem, done_v);
-  if (e != hipSuccess) return e;
-  e = set_smem((const void*)attn_dkv_mfma_kernel<1, D>, kDkSmem, done_k);
-  if (e != hipSuccess) return e;
   ProfScope ps("attn_dkv_mfma", 10.0 * pairs, 0, s);   // dV pass: S, dV; dK pass: S, dP, dK
-  hipLaunchKernelGGL((attn_dkv_mfma_kernel<0, D>), gkv, dim3(256), kDvSmem, s, (const bf16_t*)a.qkv, (const bf16_t*)a.dout, a.lse, a.delta, (bf16_t*)a.dqkv, a.S, a.nh, a.nkv, a.cu_seqlens, a.total_rows, a.B);
-  hipLaunchKernelGGL((attn_dkv_mfma_kernel<1, D>), gkv, dim3(256), kDkSmem, s, (const bf16_t*)a.qkv, (const bf16_t*)a.dout, a.lse, a.delta, (bf16_t*)a.dqkv, a.S, a.nh, a.nkv, a.cu_seqlens, a.total_rows, a.B);
-  return hipGetLastError();
+  // blocks of 128 keys that have rows: a packed batch holds at most one partly filled block per sequence
+  const int64_t blocks = a.nkv * (a.cu_seqlens ? std::min<int64_t>(a.total_rows / 128 + a.B, (int64_t)((a.S + 127) / 128) * a.B)
+                                               : (int64_t)((a.S + 127) / 128) * a.B);
+  const int64_t chain = (int64_t)(a.nh / a.nkv) * ((a.S + 31) / 32);
+  // Which form of the dK / dV passes: blocks of 128 keys, and the longest chain of 32-query tiles (heads of the group times
+  // sequence).  Whole backward, us, four-wave blocks / four sets, 32 / 8 heads: 2 x 1024 (128 blocks, chain 128) 294 / 158,
+  // 4 x 512 (128, 64) 162 / 97, 4 x 1024 (256, 128) 336 / 279, 8 x 512 (256, 64) 191 / 183, 1 x 8192 (512, 1024) 2706 / 2365,
+  // 8 x 1024 (512, 128) 460 / 476, 16 x 512 (512, 64) 280 / 333, 8 x 2048 (1024, 256) 1408 / 1540; 64 x 117 with 16 / 4
+  // heads of 64 (256, 16) 62 / 66.
+  const bool few = blocks <= 128 || (blocks <= 256 && chain >= 32) || (blocks <= 512 && chain >= 256);
+  if (few) {
+    e = launch_dkv<0, D, kFewKW, kFewNS>(a, s);
+    return e == hipSuccess ? launch_dkv<1, D, kFewKW, kFewNS>(a, s) : e;
+  }
+  e = launch_dkv<0, D, 4, 1>(a, s);
+  return e == hipSuccess ? launch_dkv<1, D, 4, 1>(a, s) : e;
 }
 }  // namespace
 

@@ -75,3 +75,25 @@ def test_head_size_64_in_a_packed_training_step(lens, tail):
     for k, ref in grads.items():
         a, b = tr.host(tr.grads)[k].reshape(-1), ref.reshape(-1)
         assert a @ b / (np.linalg.norm(a) * np.linalg.norm(b)) > 0.999, k
+
+
+def test_both_forms_of_the_key_gradient_passes_agree(B):
+    """The dK / dV passes take four sets of waves per block when blocks are few, four waves otherwise: the same sequence
+    alone (one sequence: few) and as one of many (the other form) gives the same gradients up to the order of the fp32 sums."""
+    S, nh, nkv, dh, many = 300, 8, 8, 128, 48
+    g = torch.Generator(device=DEV).manual_seed(3)
+    qkv = torch.randn(S, (nh + 2 * nkv) * dh, device=DEV, generator=g).bfloat16()
+    dout = torch.randn(S, nh * dh, device=DEV, generator=g).bfloat16()
+    got = []
+    for bt in (1, many):
+        q, do = qkv.repeat(bt, 1), dout.repeat(bt, 1)
+        out, dq = torch.empty_like(do), torch.full_like(q, float("nan"))
+        lse, delta = torch.empty(bt, nh, S, device=DEV), torch.empty(bt, nh, S, device=DEV)
+        print(f"dK/dV forms batch={bt}", flush=True)
+        B.tide_attention_fwd(bt, S, nh, nkv, dh, q, out, lse, 1, stream())
+        B.tide_attention_bwd(bt, S, nh, nkv, dh, q, out, do, lse, delta, dq, 1, stream())
+        sync()
+        got.append(dq.view(bt, S, -1).double())
+    assert float((got[1] - got[1][:1]).abs().max()) == 0.0
+    diff, top = (got[0][0] - got[1][0]).abs(), got[1][0].abs().max()
+    assert float(diff.max()) < 2.0 ** -7 * float(top)      # one step of bf16 at most
