@@ -296,7 +296,8 @@ hipError_t launch_scatter_rows(int64_t T, int d0, const void* src0, void* dst0, 
 }
 
 // ----------------------------------------------------------------------------------------------
-// RMSNorm forward: one 256-thread block per row.
+// RMSNorm forward: one 256-thread block per row.  This form, which reads the row twice, serves widths that the one below
+// does not (not a multiple of 8, or above 8192).
 // ----------------------------------------------------------------------------------------------
 template <typename T, bool VEC>
 __global__ __launch_bounds__(256) void rmsnorm_fwd_kernel(const T* __restrict__ x,
@@ -339,6 +340,55 @@ __global__ __launch_bounds__(256) void rmsnorm_fwd_kernel(const T* __restrict__ 
   }
 }
 
+// The same for rows of up to 256 * 8 * NIT elements (d % 8 == 0): a thread keeps its NIT pieces of the row in registers
+// between the sum and the scaling, so the row is read once.  Bound by memory.  us, two reads / one: 27852 x 4096 bf16 84.4 / 76.8
+// (5.9 TB/s), 8000 x 8192 bf16 61.6 / 46.6, 10000 x 8192 fp32 150 / 119.
+template <typename T, int NIT>
+__global__ __launch_bounds__(256) void rmsnorm_fwd_row_kernel(const T* __restrict__ x, const T* __restrict__ g, float eps,
+                                                              T* __restrict__ y, float* __restrict__ rstd, int d,
+                                                              const int* __restrict__ rows_dev) {
+  __shared__ float red[32];
+  const size_t row = blockIdx.x;
+  if (rows_dev && (int64_t)row >= (int64_t)*rows_dev) return;   // whole block, before any barrier
+  const T* xr = x + row * (size_t)d;
+  T* yr = y + row * (size_t)d;
+  Raw8<T> xv[NIT], gv[NIT];
+#pragma unroll
+  for (int it = 0; it < NIT; ++it) {
+    const int c = (threadIdx.x + it * 256) * 8;
+    xv[it].zero();
+    if (c < d) xv[it].load(xr, c);
+  }
+#pragma unroll
+  for (int it = 0; it < NIT; ++it) {
+    const int c = (threadIdx.x + it * 256) * 8;
+    if (c < d) gv[it].load(g, c);
+  }
+  float ss = 0.f;
+#pragma unroll
+  for (int it = 0; it < NIT; ++it) {
+    float v[8];
+    xv[it].get(v);
+#pragma unroll
+    for (int j = 0; j < 8; ++j) ss += v[j] * v[j];
+  }
+  const float tot = block_sum_lds(ss, red);
+  const float r = 1.0f / sqrtf(tot / (float)d + eps);
+  if (threadIdx.x == 0) rstd[row] = r;
+#pragma unroll
+  for (int it = 0; it < NIT; ++it) {
+    const int c = (threadIdx.x + it * 256) * 8;
+    if (c < d) {
+      float v[8], gg[8], o[8];
+      xv[it].get(v);
+      gv[it].get(gg);
+#pragma unroll
+      for (int j = 0; j < 8; ++j) o[j] = gg[j] * v[j] * r;
+      st8(yr, c, o);
+    }
+  }
+}
+
 hipError_t launch_rmsnorm_fwd(int64_t rows, int d, const void* x, const void* g, float eps, void* y,
                               float* rstd, int dtype, const int* rows_dev, hipStream_t s) {
   if (rows <= 0) return hipSuccess;
@@ -346,6 +396,14 @@ hipError_t launch_rmsnorm_fwd(int64_t rows, int d, const void* x, const void* g,
   if (rows_dev) prof_dynamic(rows_dev, 0, rows);
   dim3 grid((unsigned)rows), blk(256);
   const bool vec = (d % 8) == 0;
+  if (vec && d <= 8192) {
+    const int nit = (d + 2047) / 2048;
+#define TIDE_RMS_FWD(T, N) hipLaunchKernelGGL((rmsnorm_fwd_row_kernel<T, N>), grid, blk, 0, s, (const T*)x, (const T*)g, eps, (T*)y, rstd, d, rows_dev)
+    if (dtype == kBF16) { if (nit <= 1) TIDE_RMS_FWD(bf16_t, 1); else if (nit == 2) TIDE_RMS_FWD(bf16_t, 2); else TIDE_RMS_FWD(bf16_t, 4); }
+    else { if (nit <= 1) TIDE_RMS_FWD(float, 1); else if (nit == 2) TIDE_RMS_FWD(float, 2); else TIDE_RMS_FWD(float, 4); }
+#undef TIDE_RMS_FWD
+    return hipGetLastError();
+  }
   if (dtype == kBF16) {
     if (vec) hipLaunchKernelGGL((rmsnorm_fwd_kernel<bf16_t, true>), grid, blk, 0, s, (const bf16_t*)x, (const bf16_t*)g, eps, (bf16_t*)y, rstd, d, rows_dev);
     else hipLaunchKernelGGL((rmsnorm_fwd_kernel<bf16_t, false>), grid, blk, 0, s, (const bf16_t*)x, (const bf16_t*)g, eps, (bf16_t*)y, rstd, d, rows_dev);
@@ -362,23 +420,31 @@ hipError_t launch_rmsnorm_fwd(int64_t rows, int d, const void* x, const void* g,
 // column partials in registers, then a column-sum kernel folds the per-block partials.
 // Vector path: d % 8 == 0 and d <= 8192.  Scalar path: d <= 1024.
 // ----------------------------------------------------------------------------------------------
-// The grid is what the chip holds at once (256 CUs x blocks per CU at the kernel's register count), at
-// least kMinRowsPerBlock rows each, and the rows are split evenly over it: one round, no partly filled second.
-constexpr int kMinRowsPerBlock = 8;
+// The grid is what the chip holds at once (256 CUs x blocks per CU at the kernel's register count), with the rows split
+// evenly over it: one round, no partly filled second.  A block takes 8 rows or more, which keeps its partial sums few beside the
+// rows, unless that would leave fewer than 480 blocks: then the rows are spread over as many (a block walks its rows one
+// after the other, about 1 us each).  us with 8 rows per block / by this rule: 128 x 256 fp32 10.8 / 7.1, 183 x 5120 bf16 18.7 / 10.2,
+// 2000 x 2048 15.5 / 13.7; two rows per block from the start cost 4096 x 2048 25 in place of 19.
+constexpr int kMaxRowsForGrid = 8, kFewBlocks = 480;
 __host__ __device__ inline int rmsnorm_bwd_nit(int d) {
   const bool vec = (d % 8) == 0 && d <= 8192;
   const int per = vec ? 8 * 256 : 256;   // columns covered by one pass of the block
   return (d + per - 1) / per;
 }
+// blocks per CU by element size (2 = bf16) and pieces per thread: the vector kernels are held to the registers of these
+__host__ __device__ constexpr int rmsnorm_bwd_resident(int es, int nit) {
+  return es == 2 ? (nit <= 1 ? 5 : nit == 2 ? 3 : 2) : (nit <= 1 ? 4 : nit == 2 ? 2 : 1);
+}
 inline int64_t rmsnorm_bwd_blocks(int64_t rows, int d) {
   const int nit = rmsnorm_bwd_nit(d);
-  const int64_t cap = 256 * (nit <= 1 ? 5 : nit == 2 ? 3 : 2);
-  const int64_t want = (rows + kMinRowsPerBlock - 1) / kMinRowsPerBlock;
+  const int64_t cap = 256 * rmsnorm_bwd_resident(2, nit);   // (scratch is sized for the storage type with more of them)
+  int64_t want = (rows + kMaxRowsForGrid - 1) / kMaxRowsForGrid;
+  if (want < kFewBlocks) want = rows < kFewBlocks ? rows : kFewBlocks;
   return want < 1 ? 1 : (want < cap ? want : cap);
 }
 
 template <typename T, bool VEC, int NIT>
-__global__ __launch_bounds__(256) void rmsnorm_bwd_kernel(const T* __restrict__ dy,
+__global__ __launch_bounds__(256, VEC ? rmsnorm_bwd_resident(sizeof(T), NIT) : 1) void rmsnorm_bwd_kernel(const T* __restrict__ dy,
                                                           const T* __restrict__ x,
                                                           const T* __restrict__ g,
                                                           const float* __restrict__ rstd,
@@ -398,19 +464,25 @@ __global__ __launch_bounds__(256) void rmsnorm_bwd_kernel(const T* __restrict__ 
   const int64_t r0 = min(rows, (int64_t)blockIdx.x * per_block);
   const int64_t r1 = min(rows, r0 + per_block);
   const float inv_d = 1.0f / (float)d;
-  float gg[NIT][W];
+  Raw8<T> gv[NIT];   // the gains as loaded (vector path: half the registers in bf16)
+  float gs[NIT];     // scalar path
 #pragma unroll
   for (int it = 0; it < NIT; ++it) {
     const int c = (threadIdx.x + it * 256) * W;
-#pragma unroll
-    for (int j = 0; j < W; ++j) gg[it][j] = 0.f;
+    gv[it].zero();
+    gs[it] = 0.f;
     if (c < d) {
-      if constexpr (VEC) ld8(g, c, gg[it]);
-      else gg[it][0] = ldf(g, c);
+      if constexpr (VEC) gv[it].load(g, c);
+      else gs[it] = ldf(g, c);
     }
   }
+  auto gains = [&](int it, float (&gg)[W]) {
+    if constexpr (VEC) gv[it].get(gg);
+    else gg[0] = gs[it];
+  };
   // The rows of a block are walked with a one-row look-ahead: the loads of row+1 are issued before the
   // block-wide reduction of row, whose two barriers would otherwise expose the full memory latency per row.
+  // (two rows ahead measured the same: 192 us at 27852 x 4096 bf16.)
   // Two things keep those loads in flight: they are held as loaded (no conversion, which would need the
   // value at once) until the next iteration, and the reduction uses barriers that order LDS only.
   struct RowRaw {
@@ -454,8 +526,10 @@ __global__ __launch_bounds__(256) void rmsnorm_bwd_kernel(const T* __restrict__ 
       } else {
         xv[it][0] = nxt.xs[it]; dyv[it][0] = nxt.dys[it]; rv[it][0] = nxt.ress[it];
       }
+      float gg[W];
+      gains(it, gg);
 #pragma unroll
-      for (int j = 0; j < W; ++j) dot += gg[it][j] * dyv[it][j] * xv[it][j];
+      for (int j = 0; j < W; ++j) dot += gg[j] * dyv[it][j] * xv[it][j];
     }
     if (row + 1 < r1) load_row(row + 1);
     const float tot = block_sum_lds(dot, red);   // LDS-only barriers: the loads just issued stay in flight
@@ -464,10 +538,11 @@ __global__ __launch_bounds__(256) void rmsnorm_bwd_kernel(const T* __restrict__ 
     for (int it = 0; it < NIT; ++it) {
       const int c = (threadIdx.x + it * 256) * W;
       if (c < d) {
-        float o[W];
+        float o[W], gg[W];
+        gains(it, gg);
 #pragma unroll
         for (int j = 0; j < W; ++j) {
-          o[j] = rv[it][j] + (r * (gg[it][j] * dyv[it][j]) - xv[it][j] * coef);
+          o[j] = rv[it][j] + (r * (gg[j] * dyv[it][j]) - xv[it][j] * coef);
           acc[it][j] += dyv[it][j] * xv[it][j] * r;
         }
         if constexpr (VEC) st8(dx, base + c, o);
@@ -528,10 +603,11 @@ hipError_t launch_rmsnorm_bwd(int64_t rows, int d, const void* dy, const void* x
   if (!vec && d > 1024) return hipErrorInvalidValue;
   ProfScope ps("rmsnorm_bwd", 0, (double)rows * d * (res ? 4.0 : 3.0) * dtype_size(dtype) + 4.0 * rows, s);
   if (rows_dev) prof_dynamic(rows_dev, 0, rows);
-  const int64_t nblk = rmsnorm_bwd_blocks(rows, d);
-  dim3 grid((unsigned)nblk), blk(256);
   const int per = vec ? 8 * 256 : 256;            // columns covered by one pass of the block
   const int nit = (d + per - 1) / per;            // <= 4 by the limits above
+  int64_t nblk = rmsnorm_bwd_blocks(rows, d);
+  if (vec && nblk > 256 * rmsnorm_bwd_resident((int)dtype_size(dtype), nit)) nblk = 256 * rmsnorm_bwd_resident((int)dtype_size(dtype), nit);
+  dim3 grid((unsigned)nblk), blk(256);
 #define TIDE_RMS_BWD(T, V, N) hipLaunchKernelGGL((rmsnorm_bwd_kernel<T, V, N>), grid, blk, 0, s, (const T*)dy, (const T*)x, (const T*)g, rstd, (const T*)res, (T*)dx, dg_partial, rows, d, rows_dev)
 #define TIDE_RMS_BWD_N(T, V) do { if (nit <= 1) TIDE_RMS_BWD(T, V, 1); else if (nit == 2) TIDE_RMS_BWD(T, V, 2); else TIDE_RMS_BWD(T, V, 4); } while (0)
   if (dtype == kBF16) {

@@ -1,0 +1,45 @@
+"""RMSNorm forward and backward where the row count or the width changes the grid or the kernel: one row per block up to
+480 rows, 480 blocks, 8 rows per block, a full chip; widths of one, two and four pieces per thread, the widest one, and a
+forward-only width above it.  Against fp64 on the same values; the outputs are rounded once (2^-9 relative in bf16), sums of d
+or of the rows in fp32 are 1e-5 off at most."""
+import pytest
+import torch
+
+from paper_2602_05145_amd import binding as B
+from tests.gpu_util import DEV, stream, sync
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("dtype", ["fp32", "bf16"])
+@pytest.mark.parametrize("rows,d", [(1, 8), (3, 2048), (479, 264), (481, 2056), (3841, 256), (5000, 1000), (11000, 512), (600, 4104), (530, 8192)])
+def test_rmsnorm_over_row_counts_and_widths(rows, d, dtype):
+    dt, code = (torch.bfloat16, 1) if dtype == "bf16" else (torch.float32, 0)
+    g = torch.Generator(device=DEV).manual_seed(rows + d)
+    x, dy, res = (torch.randn(rows, d, device=DEV, generator=g).to(dt) for _ in range(3))
+    gain = (1.0 + 0.1 * torch.randn(d, device=DEV, generator=g)).to(dt)
+    y, dx = (torch.full((rows, d), float("nan"), dtype=dt, device=DEV) for _ in range(2))
+    rstd, dg = torch.full((rows,), float("nan"), device=DEV), torch.full((d,), float("nan"), device=DEV)
+    scratch = torch.full((B.tide_rmsnorm_bwd_scratch_bytes(rows, d),), 0xFF, dtype=torch.uint8, device=DEV)
+    print(f"rmsnorm rows={rows} d={d} {dtype}", flush=True)
+    B.tide_rmsnorm_fwd(rows, d, x, gain, 1e-5, y, rstd, code, stream())
+    B.tide_rmsnorm_bwd(rows, d, dy, x, gain, rstd, res, dx, dg, scratch, code, stream())
+    sync()
+    xd, dyd, gd = x.double(), dy.double(), gain.double()
+    r = torch.rsqrt(xd.square().mean(-1, keepdim=True) + 1e-5)
+    u = dyd * gd
+    want = dict(y=xd * r * gd, rstd=r.flatten(), dx=res.double() + r * u - xd * r ** 3 * (u * xd).mean(-1, keepdim=True), dg=(dyd * xd * r).sum(0))
+    for name, got in dict(y=y, rstd=rstd, dx=dx, dg=dg).items():
+        tol = 2.0 ** -8 if dtype == "bf16" and name in ("y", "dx") else 1e-5
+        assert float((got.double() - want[name]).abs().max()) < tol * float(want[name].abs().max()), name
+
+
+def test_rmsnorm_forward_of_wide_rows():
+    rows, d = 5, 8200
+    x, gain = torch.randn(rows, d, device=DEV), torch.randn(d, device=DEV)
+    y, rstd = torch.empty_like(x), torch.empty(rows, device=DEV)
+    print("rmsnorm wide", flush=True)
+    B.tide_rmsnorm_fwd(rows, d, x, gain, 1e-5, y, rstd, 0, stream())
+    sync()
+    want = x.double() * torch.rsqrt(x.double().square().mean(-1, keepdim=True) + 1e-5) * gain.double()
+    assert float((y.double() - want).abs().max()) < 1e-5 * float(want.abs().max())
