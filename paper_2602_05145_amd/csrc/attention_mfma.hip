@@ -400,11 +400,13 @@ __global__ __launch_bounds__(256, blocks_per_cu(D, 4, 2)) void attn_fwd_mfma_ker
 }
 
 // ------------------------------------------------------------------------------------------------
-// backward, dQ: same streaming structure as the forward pass
+// backward, dQ: same streaming structure as the forward pass.  It also makes delta = rowsum(dO * O), which the dK / dV
+// passes read: the dO fragments are in registers anyway, so O is all that is loaded for it (a pass of its own
+// read dO again: 100 us at 16 x 2048, 32 heads, against 45 us more in this kernel).
 // ------------------------------------------------------------------------------------------------
 template <int D>
-__global__ __launch_bounds__(256, blocks_per_cu(D, 3, 2)) void attn_dq_mfma_kernel(const bf16_t* __restrict__ qkv, const bf16_t* __restrict__ dout,
-                                                           const float* __restrict__ lse, const float* __restrict__ delta,
+__global__ __launch_bounds__(256, blocks_per_cu(D, 3, 2)) void attn_dq_mfma_kernel(const bf16_t* __restrict__ qkv, const bf16_t* __restrict__ out, const bf16_t* __restrict__ dout,
+                                                           const float* __restrict__ lse, float* __restrict__ delta,
                                                            bf16_t* __restrict__ dqkv, int Smax, int nh, int nkv,
                                                            const int* __restrict__ cu, int64_t T, int nseq) {
   constexpr int NK = D / 16, NC = D / 32;   // k16 steps of a score product, 32-column tiles of a result
@@ -439,7 +441,23 @@ __global__ __launch_bounds__(256, blocks_per_cu(D, 3, 2)) void attn_dq_mfma_kern
   const bool valid = iq < S;
   const bool edge_q = qw + 32 > S;   // wave-uniform: some query row of this wave lies past the sequence
   const float lse_i = valid ? lse[stat_index(cu, T, sv, b, h, nh, Smax, iq)] * kLog2e : 0.f;
-  const float del_i = valid ? delta[stat_index(cu, T, sv, b, h, nh, Smax, iq)] : 0.f;
+  float del_i = 0.f;   // a row past the end loads zeros
+  {
+    const __amdgpu_buffer_rsrc_t rsout = rsrc(out + (size_t)sv.row0 * ldo, (uint32_t)((size_t)S * ldo * 2));
+    u32x4_t of[NK];
+#pragma unroll
+    for (int kk = 0; kk < NK; ++kk)
+      of[kk] = __builtin_bit_cast(u32x4_t, __builtin_amdgcn_raw_buffer_load_b128(rsout, ((uint32_t)iq * (uint32_t)ldo + (uint32_t)(h * D + kk * 16 + g * 8)) * 2u, 0, 0));
+#pragma unroll
+    for (int kk = 0; kk < NK; ++kk)
+#pragma unroll
+      for (int w = 0; w < 4; ++w) {
+        del_i = fmaf(__uint_as_float(of[kk][w] << 16), __uint_as_float(dof[kk][w] << 16), del_i);
+        del_i = fmaf(__uint_as_float(of[kk][w] & 0xFFFF0000u), __uint_as_float(dof[kk][w] & 0xFFFF0000u), del_i);
+      }
+    del_i += __shfl_xor(del_i, 32, 64);
+    if (valid && g == 0) delta[stat_index(cu, T, sv, b, h, nh, Smax, iq)] = del_i;
+  }
 
   f32x16_t dq[NC];
 #pragma unroll
@@ -633,7 +651,7 @@ __global__ __launch_bounds__(KW * NS * 64, NS > 1 ? 1 : WHICH == 0 ? blocks_per_
     if (tid < 2 * BI) reinterpret_cast<float*>(base + 2 * Q_TILE)[tid] = stat * ((tid < BI) ? kLog2e : 1.f);   // lse * log2(e), delta
   };
 
-  if (set < ntiles) {
+  if (NS == 1 || set < ntiles) {   // (one set: there is always a tile)
     gload(set, 0);
     sstore(0);
   }
@@ -643,7 +661,7 @@ __global__ __launch_bounds__(KW * NS * 64, NS > 1 ? 1 : WHICH == 0 ? blocks_per_
   for (int r = 0; r * NS < ntiles; ++r) {
     const int st = r & 1, u = r * NS + set;
     if (u + NS < ntiles) gload(u + NS, st ^ 1);
-    const int it0 = u < ntiles ? tile_i0(u) : S;   // past the end: no half of the tile is entered
+    const int it0 = NS == 1 || u < ntiles ? tile_i0(u) : S;   // past the end: no half of the tile is entered
 #pragma unroll
     for (int hf = 0; hf < BI / 32; ++hf) {
     const int i0 = it0 + hf * 32;   // this half's first query
@@ -795,15 +813,13 @@ hipError_t launch_dkv(const AttnArgs& a, hipStream_t s) {
 template <int D>
 hipError_t launch_bwd(const AttnArgs& a, hipStream_t s) {
   static bool done_q = false;
-  hipError_t e = launch_attn_delta(a, s);
-  if (e != hipSuccess) return e;
-  e = set_smem((const void*)attn_dq_mfma_kernel<D>, fwd_smem(D), done_q);
+  hipError_t e = set_smem((const void*)attn_dq_mfma_kernel<D>, fwd_smem(D), done_q);
   if (e != hipSuccess) return e;
   const dim3 gq((unsigned)((int64_t)((a.S + BQ - 1) / BQ) * a.nh * a.B));
   const double pairs = (double)a.B * a.nh * D * (double)a.S * (a.S + 1) / 2.0;  // (query, key, channel) triples
   {
     ProfScope ps("attn_dq_mfma", 6.0 * pairs, 0, s);   // S, dP and dQ products
-    hipLaunchKernelGGL(attn_dq_mfma_kernel<D>, gq, dim3(256), fwd_smem(D), s, (const bf16_t*)a.qkv, (const bf16_t*)a.dout, a.lse, a.delta, (bf16_t*)a.dqkv, a.S, a.nh, a.nkv, a.cu_seqlens, a.total_rows, a.B);
+    hipLaunchKernelGGL(attn_dq_mfma_kernel<D>, gq, dim3(256), fwd_smem(D), s, (const bf16_t*)a.qkv, (const bf16_t*)a.out, (const bf16_t*)a.dout, a.lse, a.delta, (bf16_t*)a.dqkv, a.S, a.nh, a.nkv, a.cu_seqlens, a.total_rows, a.B);
     e = hipGetLastError();
     if (e != hipSuccess) return e;
   }

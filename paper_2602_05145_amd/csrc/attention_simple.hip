@@ -269,7 +269,7 @@ hipError_t launch_attn_fwd_simple(const AttnArgs& a, hipStream_t s) {
   return hipGetLastError();
 }
 
-hipError_t launch_attn_delta(const AttnArgs& a, hipStream_t s) {
+static hipError_t launch_attn_delta(const AttnArgs& a, hipStream_t s) {   // delta = rowsum(dO * O)
   ProfScope ps("attn_delta", 0, 2.0 * a.B * a.S * a.nh * a.dh * dtype_size(a.dtype), s);
   const int lph = a.dh / 8;
   if (a.dh % 8 == 0 && lph >= 1 && lph <= 64 && (lph & (lph - 1)) == 0 &&

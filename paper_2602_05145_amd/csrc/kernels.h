@@ -150,7 +150,6 @@ struct AttnArgs {
   int64_t total_rows = 0;
 };
 bool attn_mfma_supported(const AttnArgs& a);
-hipError_t launch_attn_delta(const AttnArgs& a, hipStream_t s);  // delta = rowsum(dO * O)
 hipError_t launch_attn_fwd_simple(const AttnArgs& a, hipStream_t s);
 hipError_t launch_attn_bwd_simple(const AttnArgs& a, hipStream_t s);
 hipError_t launch_attn_fwd_mfma(const AttnArgs& a, hipStream_t s);
