@@ -1,304 +1,400 @@
-// Shape-agnostic causal grouped-query attention for gfx950: one wavefront per query row (forward, dQ)
-// or per key row (dK, dV), fp32 arithmetic, any head_dim <= 256 and any sequence length.  It is the
-// attention path of fp32 mode and the bf16 fallback for head sizes the MFMA kernel does not take.
-// Deterministic: no atomics; every output element is produced by exactly one wave in a fixed order.
+// Shape-agnostic causal grouped-query attention for gfx950 in fp32 arithmetic: any head_dim <= 256, any sequence length,
+// fp32 or bf16 storage.  It is the attention path of fp32 mode and the bf16 path for head sizes the flash kernels do not
+// take.  Deterministic: no atomics; every output element is produced by one block in a fixed order.
 //
 // Activation layout: qkv [B*S, (nh + 2 nkv) dh] with q heads first, then k heads, then v heads; query
 // head h reads kv head h / (nh / nkv).  lse[b, h, i] is the log-sum-exp of the scaled scores of row i.
 // Packed batches (cu_seqlens given): sequence b owns rows [cu[b], cu[b+1]) and lse / delta are [nh, T].
+//
+// All products run on v_mfma_f32_16x16x4_f32 (fp32 products and sums).  A block is four waves and 16 rows: 16 queries of a
+// head (forward, dQ) or 16 keys of a kv head (dK, dV).  It walks the other side in tiles of 64, 16 rows per wave for the
+// score products (their contraction runs over the head, 16 channels at a time, fragments straight from L2 into
+// registers), passes the 16 x 64 probabilities or score gradients through LDS, and the waves share the columns of the
+// second product.  What bounds it at the sizes it serves (the fp32 configuration has 64 to 1024 positions and 4 heads)
+// is latency, so there are one or two barriers per tile and no staging of operands.  fp32, forward + backward, us, one
+// wavefront per row on the vector units before / now: 2 x 64, 4 / 2 heads of 64: 6 + 37 / 6 + 17; 1 x 1024: 101 + 1382 / 45 + 163;
+// 2 x 1024, 16 / 8 heads of 128: 1287 + 24316 / 258 + 1053.
+#include <type_traits>
+
 #include "kernels.h"
 #include "prof.h"
 #include "tide_common.h"
 
 namespace tide {
 
+namespace {
+
 constexpr int kMaxDh = 256;
-constexpr int kDhSlots = kMaxDh / 64;
+constexpr int BR = 16, BT = 64;      // rows of a block, rows of a tile of the other side
+constexpr int PP = BT + 4;           // LDS pitch of the 16 x 64 exchange (the 16-byte reads of 16 rows hit 16 bank groups)
+typedef float f32x4_t __attribute__((ext_vector_type(4)));
 
-template <typename T>
-__global__ __launch_bounds__(64) void attn_fwd_simple_kernel(const T* __restrict__ qkv, T* __restrict__ out,
-                                                             float* __restrict__ lse, int Smax, int nh, int nkv,
-                                                             int dh, const int* __restrict__ cu, int64_t Trows) {
-  __shared__ float qs[kMaxDh];
-  __shared__ float ps[64];
-  const int i = blockIdx.x, h = blockIdx.y, b = blockIdx.z;
-  const SeqView sv = seq_view(cu, b, Smax, Trows);
-  if (i >= sv.len) return;   // whole block: the sequence is shorter than the grid
-  const size_t row0 = (size_t)sv.row0;
-  const int lane = threadIdx.x;
-  const int G = nh / nkv, kh = h / G;
-  const int ld = (nh + 2 * nkv) * dh;
-  const float scale = 1.0f / sqrtf((float)dh);
-  const size_t rowq = (row0 + i) * ld;
-  for (int c = lane; c < dh; c += 64) qs[c] = ldf(qkv, rowq + (size_t)h * dh + c) * scale;
-  __syncthreads();
-  const size_t koff = (size_t)(nh + kh) * dh, voff = (size_t)(nh + nkv + kh) * dh;
-  float m = -INFINITY, l = 0.f;
-  float o[kDhSlots];
+// four consecutive channels c .. c+3 of a row, zeros past dh; VEC: they are aligned to 16 (fp32) or 8 (bf16) bytes
+template <bool VEC>
+__device__ __forceinline__ f32x4_t row4(const float* p, int c, int dh) {
+  f32x4_t v = {0.f, 0.f, 0.f, 0.f};
+  if (VEC) {
+    if (c < dh) v = *reinterpret_cast<const f32x4_t*>(p + c);
+  } else {
 #pragma unroll
-  for (int t = 0; t < kDhSlots; ++t) o[t] = 0.f;
-  for (int j0 = 0; j0 <= i; j0 += 64) {
-    const int j = j0 + lane;
-    float sc = -INFINITY;
-    if (j <= i) {
-      const size_t rk = (row0 + j) * ld + koff;
-      float a = 0.f;
-      for (int c = 0; c < dh; ++c) a = fmaf(qs[c], ldf(qkv, rk + c), a);
-      sc = a;
+    for (int e = 0; e < 4; ++e)
+      if (c + e < dh) v[e] = p[c + e];
+  }
+  return v;
+}
+template <bool VEC>
+__device__ __forceinline__ f32x4_t row4(const bf16_t* p, int c, int dh) {
+  f32x4_t v = {0.f, 0.f, 0.f, 0.f};
+  if (VEC) {
+    if (c < dh) {
+      const uint2 w = *reinterpret_cast<const uint2*>(p + c);
+      v = f32x4_t{__uint_as_float(w.x << 16), __uint_as_float(w.x & 0xFFFF0000u), __uint_as_float(w.y << 16), __uint_as_float(w.y & 0xFFFF0000u)};
     }
-    const float nm = fmaxf(m, wave_max(sc));
-    const float corr = __expf(m - nm);  // first chunk: exp(-inf) = 0
-    const float pj = (j <= i) ? __expf(sc - nm) : 0.f;
-    l = l * corr + wave_sum(pj);
-    m = nm;
-    __syncthreads();
-    ps[lane] = pj;
-    __syncthreads();
-    const int jn = min(64, i - j0 + 1);
+  } else {
 #pragma unroll
-    for (int t = 0; t < kDhSlots; ++t) {
-      const int c = lane + 64 * t;
-      if (c < dh) {
-        float a = o[t] * corr;
-        for (int jj = 0; jj < jn; ++jj)
-          a = fmaf(ps[jj], ldf(qkv, (row0 + j0 + jj) * ld + voff + c), a);
-        o[t] = a;
+    for (int e = 0; e < 4; ++e)
+      if (c + e < dh) v[e] = bf2f(p[c + e]);
+  }
+  return v;
+}
+
+// acc += A B^T over the 16 channels of one group: both fragments hold, for row l % 16, channels 4 (l / 16) .. + 3
+__device__ __forceinline__ f32x4_t mma16(f32x4_t a, f32x4_t b, f32x4_t acc) {
+#pragma unroll
+  for (int e = 0; e < 4; ++e) acc = __builtin_amdgcn_mfma_f32_16x16x4f32(a[e], b[e], acc, 0, 0, 0);
+  return acc;
+}
+
+// Register q of a 16 x 16 result in lane l is row 4 (l / 16) + q, column l % 16.
+struct Geo {
+  int lane, wave, lr, g;
+  __device__ Geo() : lane(threadIdx.x & 63), wave(threadIdx.x >> 6), lr(lane & 15), g(lane >> 4) {}
+};
+
+// the wave's columns of the second product: acc[t] += X[16 x 64] Y[64 x 16 columns], X from the exchange in LDS, Y's rows
+// r0 .. r0 + 63 from memory (zeros from row `rows` on).  first: the last of Y's rows that row 0 of X may see, row r seeing r
+// more; a probability past that is zero, but zero times a later position's infinity or NaN is not, so a tile on the
+// diagonal that holds one is summed element by element.
+template <int NCT, typename T>
+__device__ __forceinline__ void second_product(const Geo& z, const float* x, const T* y, size_t ld, int r0, int rows, int dh, f32x4_t (&acc)[NCT],
+                                               int first = 0x7fffff00) {
+#pragma unroll
+  for (int t = 0; t < NCT; ++t) {
+    const int col = (z.wave + 4 * t) * 16 + z.lr;
+    f32x4_t v[4];
+#pragma unroll
+    for (int grp = 0; grp < 4; ++grp)
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        const int r = r0 + grp * 16 + 4 * z.g + e;
+        v[grp][e] = (r < rows && col < dh) ? ldf(y, (size_t)r * ld + col) : 0.f;
+      }
+    if (r0 + BT - 1 > first) {   // block-uniform
+      bool odd = false;
+#pragma unroll
+      for (int grp = 0; grp < 4; ++grp)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) odd |= !(fabsf(v[grp][e]) <= 3.4028235e38f);
+      if (__builtin_amdgcn_ballot_w64(odd) != 0) {
+        if (col < dh)
+          for (int q = 0; q < 4; ++q)
+            for (int r = r0; r <= min(min(first + 4 * z.g + q, rows - 1), r0 + BT - 1); ++r)
+              acc[t][q] = fmaf(x[(4 * z.g + q) * PP + r - r0], ldf(y, (size_t)r * ld + col), acc[t][q]);
+        continue;
       }
     }
-  }
-  const float inv = 1.0f / l;
 #pragma unroll
-  for (int t = 0; t < kDhSlots; ++t) {
-    const int c = lane + 64 * t;
-    if (c < dh) stf(out, (row0 + i) * ((size_t)nh * dh) + (size_t)h * dh + c, o[t] * inv);
-  }
-  if (lane == 0) lse[stat_index(cu, Trows, sv, b, h, nh, Smax, i)] = m + logf(l);
-}
-
-// delta[b,h,i] = sum_c dO[i,h,c] * O[i,h,c]
-template <typename T>
-__global__ __launch_bounds__(64) void attn_delta_kernel(const T* __restrict__ out, const T* __restrict__ dout,
-                                                        float* __restrict__ delta, int Smax, int nh, int dh,
-                                                        const int* __restrict__ cu, int64_t Trows) {
-  const int i = blockIdx.x, h = blockIdx.y, b = blockIdx.z;
-  const SeqView sv = seq_view(cu, b, Smax, Trows);
-  if (i >= sv.len) return;
-  const size_t row0 = (size_t)sv.row0;
-  const size_t base = (row0 + i) * ((size_t)nh * dh) + (size_t)h * dh;
-  float a = 0.f;
-  for (int c = threadIdx.x; c < dh; c += 64) a += ldf(out, base + c) * ldf(dout, base + c);
-  a = wave_sum(a);
-  if (threadIdx.x == 0) delta[stat_index(cu, Trows, sv, b, h, nh, Smax, i)] = a;
-}
-
-// The same for head sizes whose 16-byte pieces form a power-of-two group of lanes (8 <= dh <= 512): one
-// block per row, 8 channels per lane, the dh/8 lanes of a head combine by shuffles.
-template <typename T>
-__global__ __launch_bounds__(256) void attn_delta_vec_kernel(const T* __restrict__ out, const T* __restrict__ dout,
-                                                             float* __restrict__ delta, int Smax, int nh, int dh,
-                                                             const int* __restrict__ cu, int64_t Trows) {
-  const int i = blockIdx.x, b = blockIdx.y;
-  const SeqView sv = seq_view(cu, b, Smax, Trows);
-  if (i >= sv.len) return;
-  const int lph = dh >> 3;                         // lanes per head
-  const int width = nh * dh;
-  const size_t base = ((size_t)sv.row0 + i) * (size_t)width;
-  for (int c0 = 0; c0 < width; c0 += 256 * 8) {    // uniform trip count: the shuffles below are wave-wide
-    const int c = c0 + (int)threadIdx.x * 8;
-    float a = 0.f;
-    if (c < width) {
-      float o[8], g[8];
-      ld8(out, base + c, o);
-      ld8(dout, base + c, g);
-#pragma unroll
-      for (int j = 0; j < 8; ++j) a += o[j] * g[j];
-    }
-    for (int off = lph >> 1; off > 0; off >>= 1) a += __shfl_xor(a, off, 64);
-    if (c < width && (threadIdx.x & (lph - 1)) == 0) delta[stat_index(cu, Trows, sv, b, c / dh, nh, Smax, i)] = a;
+    for (int grp = 0; grp < 4; ++grp) acc[t] = mma16(*reinterpret_cast<const f32x4_t*>(x + z.lr * PP + grp * 16 + 4 * z.g), v[grp], acc[t]);
   }
 }
 
-template <typename T>
-__global__ __launch_bounds__(64) void attn_dq_simple_kernel(const T* __restrict__ qkv, const T* __restrict__ dout,
-                                                            const float* __restrict__ lse,
-                                                            const float* __restrict__ delta, T* __restrict__ dqkv,
-                                                            int Smax, int nh, int nkv, int dh,
-                                                            const int* __restrict__ cu, int64_t Trows) {
-  __shared__ float qs[kMaxDh], dos[kMaxDh];
-  __shared__ float dss[64];
-  const int i = blockIdx.x, h = blockIdx.y, b = blockIdx.z;
-  const SeqView sv = seq_view(cu, b, Smax, Trows);
-  if (i >= sv.len) return;
-  const size_t row0 = (size_t)sv.row0;
-  const int lane = threadIdx.x;
-  const int G = nh / nkv, kh = h / G;
-  const int ld = (nh + 2 * nkv) * dh;
-  const float scale = 1.0f / sqrtf((float)dh);
-  const size_t rowq = (row0 + i) * ld;
-  const size_t rowo = (row0 + i) * ((size_t)nh * dh) + (size_t)h * dh;
-  for (int c = lane; c < dh; c += 64) {
-    qs[c] = ldf(qkv, rowq + (size_t)h * dh + c) * scale;
-    dos[c] = ldf(dout, rowo + c);
-  }
-  __syncthreads();
-  const size_t koff = (size_t)(nh + kh) * dh, voff = (size_t)(nh + nkv + kh) * dh;
-  const float L = lse[stat_index(cu, Trows, sv, b, h, nh, Smax, i)];
-  const float D = delta[stat_index(cu, Trows, sv, b, h, nh, Smax, i)];
-  float dq[kDhSlots];
+__device__ __forceinline__ float max16(float v) {   // over the 16 lanes of a group
 #pragma unroll
-  for (int t = 0; t < kDhSlots; ++t) dq[t] = 0.f;
-  for (int j0 = 0; j0 <= i; j0 += 64) {
-    const int j = j0 + lane;
-    float ds = 0.f;
-    if (j <= i) {
-      const size_t rk = (row0 + j) * ld;
-      float a = 0.f, dp = 0.f;
-      for (int c = 0; c < dh; ++c) {
-        a = fmaf(qs[c], ldf(qkv, rk + koff + c), a);
-        dp = fmaf(dos[c], ldf(qkv, rk + voff + c), dp);
-      }
-      ds = __expf(a - L) * (dp - D);
-    }
-    __syncthreads();
-    dss[lane] = ds;
-    __syncthreads();
-    const int jn = min(64, i - j0 + 1);
+  for (int o = 8; o > 0; o >>= 1) v = fmaxf(v, __shfl_xor(v, o, 64));
+  return v;
+}
+__device__ __forceinline__ float sum16(float v) {
 #pragma unroll
-    for (int t = 0; t < kDhSlots; ++t) {
-      const int c = lane + 64 * t;
-      if (c < dh) {
-        float a = dq[t];
-        for (int jj = 0; jj < jn; ++jj)
-          a = fmaf(dss[jj], ldf(qkv, (row0 + j0 + jj) * ld + koff + c), a);
-        dq[t] = a;
-      }
-    }
-  }
-#pragma unroll
-  for (int t = 0; t < kDhSlots; ++t) {
-    const int c = lane + 64 * t;
-    if (c < dh) stf(dqkv, rowq + (size_t)h * dh + c, dq[t] * scale);
-  }
+  for (int o = 8; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
+  return v;
 }
 
-template <typename T>
-__global__ __launch_bounds__(64) void attn_dkv_simple_kernel(const T* __restrict__ qkv, const T* __restrict__ dout,
-                                                             const float* __restrict__ lse,
-                                                             const float* __restrict__ delta, T* __restrict__ dqkv,
-                                                             int Smax, int nh, int nkv, int dh,
-                                                             const int* __restrict__ cu, int64_t Trows) {
-  __shared__ float ks[kMaxDh], vs[kMaxDh];
-  __shared__ float pss[64], dss[64];
-  const int j = blockIdx.x, kh = blockIdx.y, b = blockIdx.z;
+}  // namespace
+
+// NG groups of 16 channels (dh <= 16 NG), NCT = NG / 4 column tiles per wave
+template <typename T, int NG, bool VEC>
+__global__ __launch_bounds__(256) void attn_fwd_simple_kernel(const T* __restrict__ qkv, T* __restrict__ out, float* __restrict__ lse,
+                                                              int Smax, int nh, int nkv, int dh, const int* __restrict__ cu, int64_t Trows) {
+  constexpr int NCT = NG / 4;
+  __shared__ __attribute__((aligned(16))) float ps[2][BR * PP];
+  __shared__ float red[2][4][BR];
+  const int i0 = blockIdx.x * BR, h = blockIdx.y, b = blockIdx.z;
   const SeqView sv = seq_view(cu, b, Smax, Trows);
   const int S = sv.len;
-  if (j >= S) return;
-  const size_t row0 = (size_t)sv.row0;
-  const int lane = threadIdx.x;
-  const int G = nh / nkv;
-  const int ld = (nh + 2 * nkv) * dh;
+  if (i0 >= S) return;   // whole block: the sequence is shorter than the grid
+  const Geo z;
+  const int kh = h / (nh / nkv);
+  const size_t ld = (size_t)(nh + 2 * nkv) * dh;
   const float scale = 1.0f / sqrtf((float)dh);
-  const size_t koff = (size_t)(nh + kh) * dh, voff = (size_t)(nh + nkv + kh) * dh;
-  const size_t rowk = (row0 + j) * ld;
-  for (int c = lane; c < dh; c += 64) {
-    ks[c] = ldf(qkv, rowk + koff + c) * scale;
-    vs[c] = ldf(qkv, rowk + voff + c);
+  const T* base = qkv + (size_t)sv.row0 * ld;
+  const T* K = base + (size_t)(nh + kh) * dh;
+  const T* V = base + (size_t)(nh + nkv + kh) * dh;
+  f32x4_t qf[NG];
+#pragma unroll
+  for (int c = 0; c < NG; ++c) qf[c] = row4<VEC>(base + (size_t)min(i0 + z.lr, S - 1) * ld + (size_t)h * dh, c * 16 + 4 * z.g, dh) * scale;
+  f32x4_t o[NCT], m, l;
+#pragma unroll
+  for (int q = 0; q < 4; ++q) { m[q] = -INFINITY; l[q] = 0.f; }
+#pragma unroll
+  for (int t = 0; t < NCT; ++t) o[t] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+  const int last = min(i0 + BR, S) - 1;   // last query of the block
+  for (int j0 = 0, st = 0; j0 <= last; j0 += BT, st ^= 1) {
+    const int j = j0 + z.wave * 16 + z.lr;
+    f32x4_t s = {0.f, 0.f, 0.f, 0.f};
+    const T* kr = K + (size_t)min(j, S - 1) * ld;
+#pragma unroll
+    for (int c = 0; c < NG; ++c) s = mma16(qf[c], row4<VEC>(kr, c * 16 + 4 * z.g, dh), s);
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      if (j > i0 + 4 * z.g + q || j >= S) s[q] = -INFINITY;
+      const float v = max16(s[q]);
+      if (z.lr == 0) red[st][z.wave][4 * z.g + q] = v;
+    }
+    __syncthreads();
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      const int r = 4 * z.g + q;
+      const float tm = fmaxf(fmaxf(red[st][0][r], red[st][1][r]), fmaxf(red[st][2][r], red[st][3][r]));
+      const float nm = fmaxf(m[q], tm);        // finite: key 0 is visible to every query
+      const float corr = __expf(m[q] - nm);    // first tile: exp(-inf) = 0
+      const float p = __expf(s[q] - nm);
+      l[q] = l[q] * corr + p;                  // this lane's keys only
+      m[q] = nm;
+#pragma unroll
+      for (int t = 0; t < NCT; ++t) o[t][q] *= corr;
+      ps[st][r * PP + z.wave * 16 + z.lr] = p;
+    }
+    __syncthreads();   // (the other buffer is written next: its readers pass this barrier first)
+    second_product<NCT>(z, ps[st], V, ld, j0, S, dh, o, i0);
   }
   __syncthreads();
-  float dk[kDhSlots], dv[kDhSlots];
 #pragma unroll
-  for (int t = 0; t < kDhSlots; ++t) dk[t] = dv[t] = 0.f;
-  for (int g = 0; g < G; ++g) {
-    const int h = kh * G + g;
-    for (int i0 = j; i0 < S; i0 += 64) {
-      const int i = i0 + lane;
-      float pv = 0.f, ds = 0.f;
-      if (i < S) {
-        const size_t rq = (row0 + i) * ld + (size_t)h * dh;
-        const size_t ro = (row0 + i) * ((size_t)nh * dh) + (size_t)h * dh;
-        float a = 0.f, dp = 0.f;
-        for (int c = 0; c < dh; ++c) {
-          a = fmaf(ks[c], ldf(qkv, rq + c), a);
-          dp = fmaf(vs[c], ldf(dout, ro + c), dp);
-        }
-        pv = __expf(a - lse[stat_index(cu, Trows, sv, b, h, nh, Smax, i)]);
-        ds = pv * (dp - delta[stat_index(cu, Trows, sv, b, h, nh, Smax, i)]);
-      }
-      __syncthreads();
-      pss[lane] = pv;
-      dss[lane] = ds;
-      __syncthreads();
-      const int in = min(64, S - i0);
+  for (int q = 0; q < 4; ++q) {
+    const float v = sum16(l[q]);
+    if (z.lr == 0) red[0][z.wave][4 * z.g + q] = v;
+  }
+  __syncthreads();
 #pragma unroll
-      for (int t = 0; t < kDhSlots; ++t) {
-        const int c = lane + 64 * t;
-        if (c < dh) {
-          float a = dv[t], bb = dk[t];
-          for (int ii = 0; ii < in; ++ii) {
-            const size_t rq = (row0 + i0 + ii) * ld + (size_t)h * dh;
-            const size_t ro = (row0 + i0 + ii) * ((size_t)nh * dh) + (size_t)h * dh;
-            a = fmaf(pss[ii], ldf(dout, ro + c), a);
-            bb = fmaf(dss[ii], ldf(qkv, rq + c), bb);
-          }
-          dv[t] = a;
-          dk[t] = bb;
-        }
-      }
+  for (int q = 0; q < 4; ++q) {
+    const int r = 4 * z.g + q, i = i0 + r;
+    if (i >= S) continue;
+    const float sum = (red[0][0][r] + red[0][1][r]) + (red[0][2][r] + red[0][3][r]), inv = 1.0f / sum;
+#pragma unroll
+    for (int t = 0; t < NCT; ++t) {
+      const int col = (z.wave + 4 * t) * 16 + z.lr;
+      if (col < dh) stf(out, ((size_t)sv.row0 + i) * ((size_t)nh * dh) + (size_t)h * dh + col, o[t][q] * inv);
+    }
+    if (z.wave == 0 && z.lr == 0) lse[stat_index(cu, Trows, sv, b, h, nh, Smax, i)] = m[q] + logf(sum);
+  }
+}
+
+// dQ, and delta[b,h,i] = sum_c dO[i,h,c] * O[i,h,c] for the dK / dV kernel
+template <typename T, int NG, bool VEC>
+__global__ __launch_bounds__(256) void attn_dq_simple_kernel(const T* __restrict__ qkv, const T* __restrict__ out, const T* __restrict__ dout,
+                                                             const float* __restrict__ lse, float* __restrict__ delta, T* __restrict__ dqkv,
+                                                             int Smax, int nh, int nkv, int dh, const int* __restrict__ cu, int64_t Trows) {
+  constexpr int NCT = NG / 4;
+  __shared__ __attribute__((aligned(16))) float ps[2][BR * PP];
+  const int i0 = blockIdx.x * BR, h = blockIdx.y, b = blockIdx.z;
+  const SeqView sv = seq_view(cu, b, Smax, Trows);
+  const int S = sv.len;
+  if (i0 >= S) return;
+  const Geo z;
+  const int kh = h / (nh / nkv);
+  const size_t ld = (size_t)(nh + 2 * nkv) * dh;
+  const float scale = 1.0f / sqrtf((float)dh);
+  const T* base = qkv + (size_t)sv.row0 * ld;
+  const T* K = base + (size_t)(nh + kh) * dh;
+  const T* V = base + (size_t)(nh + nkv + kh) * dh;
+  f32x4_t qf[NG], df[NG];
+  float dsum = 0.f;
+  {
+    const int i = min(i0 + z.lr, S - 1);
+    const size_t ro = ((size_t)sv.row0 + i) * ((size_t)nh * dh) + (size_t)h * dh;
+#pragma unroll
+    for (int c = 0; c < NG; ++c) {
+      qf[c] = row4<VEC>(base + (size_t)i * ld + (size_t)h * dh, c * 16 + 4 * z.g, dh) * scale;
+      df[c] = row4<VEC>(dout + ro, c * 16 + 4 * z.g, dh);
+      const f32x4_t of = row4<VEC>(out + ro, c * 16 + 4 * z.g, dh);
+#pragma unroll
+      for (int e = 0; e < 4; ++e) dsum = fmaf(of[e], df[c][e], dsum);
     }
   }
+  dsum += __shfl_xor(dsum, 16, 64);
+  dsum += __shfl_xor(dsum, 32, 64);     // every lane: the row l % 16
+  f32x4_t L, D, dq[NCT];
 #pragma unroll
-  for (int t = 0; t < kDhSlots; ++t) {
-    const int c = lane + 64 * t;
-    if (c < dh) {
-      stf(dqkv, rowk + koff + c, dk[t] * scale);
-      stf(dqkv, rowk + voff + c, dv[t]);
+  for (int q = 0; q < 4; ++q) {
+    const int i = i0 + 4 * z.g + q;
+    D[q] = __shfl(dsum, 4 * z.g + q, 64);
+    L[q] = i < S ? lse[stat_index(cu, Trows, sv, b, h, nh, Smax, i)] : 0.f;
+    if (z.wave == 0 && z.lr == 0 && i < S) delta[stat_index(cu, Trows, sv, b, h, nh, Smax, i)] = D[q];
+  }
+#pragma unroll
+  for (int t = 0; t < NCT; ++t) dq[t] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+  const int last = min(i0 + BR, S) - 1;
+  for (int j0 = 0, st = 0; j0 <= last; j0 += BT, st ^= 1) {
+    const int j = j0 + z.wave * 16 + z.lr;
+    f32x4_t s = {0.f, 0.f, 0.f, 0.f}, dp = s;
+    const size_t jr = (size_t)min(j, S - 1) * ld;
+#pragma unroll
+    for (int c = 0; c < NG; ++c) {
+      s = mma16(qf[c], row4<VEC>(K + jr, c * 16 + 4 * z.g, dh), s);
+      dp = mma16(df[c], row4<VEC>(V + jr, c * 16 + 4 * z.g, dh), dp);
+    }
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      const int i = i0 + 4 * z.g + q;
+      ps[st][(4 * z.g + q) * PP + z.wave * 16 + z.lr] = (j <= i && i < S) ? __expf(s[q] - L[q]) * (dp[q] - D[q]) : 0.f;
+    }
+    __syncthreads();   // (a buffer is written again two tiles on: its readers pass the barrier in between first)
+    second_product<NCT>(z, ps[st], K, ld, j0, S, dh, dq);
+  }
+#pragma unroll
+  for (int q = 0; q < 4; ++q) {
+    const int i = i0 + 4 * z.g + q;
+    if (i >= S) continue;
+#pragma unroll
+    for (int t = 0; t < NCT; ++t) {
+      const int col = (z.wave + 4 * t) * 16 + z.lr;
+      if (col < dh) stf(dqkv, ((size_t)sv.row0 + i) * ld + (size_t)h * dh + col, dq[t][q] * scale);
     }
   }
 }
 
-static bool simple_ok(const AttnArgs& a) {
+template <typename T, int NG, bool VEC>
+__global__ __launch_bounds__(256) void attn_dkv_simple_kernel(const T* __restrict__ qkv, const T* __restrict__ dout, const float* __restrict__ lse,
+                                                              const float* __restrict__ delta, T* __restrict__ dqkv, int Smax, int nh, int nkv,
+                                                              int dh, const int* __restrict__ cu, int64_t Trows) {
+  constexpr int NCT = NG / 4;
+  __shared__ __attribute__((aligned(16))) float ps[2][BR * PP];   // probabilities, transposed: [key][query]
+  __shared__ __attribute__((aligned(16))) float ds[2][BR * PP];   // score gradients
+  const int j0 = blockIdx.x * BR, kh = blockIdx.y, b = blockIdx.z;
+  const SeqView sv = seq_view(cu, b, Smax, Trows);
+  const int S = sv.len;
+  if (j0 >= S) return;
+  const Geo z;
+  const int G = nh / nkv;
+  const size_t ld = (size_t)(nh + 2 * nkv) * dh, ldo = (size_t)nh * dh;
+  const float scale = 1.0f / sqrtf((float)dh);
+  const T* base = qkv + (size_t)sv.row0 * ld;
+  const int j = j0 + z.lr;              // this lane's key
+  f32x4_t kf[NG], vf[NG], dk[NCT], dv[NCT];
+#pragma unroll
+  for (int c = 0; c < NG; ++c) {
+    const T* r = base + (size_t)min(j, S - 1) * ld;
+    kf[c] = row4<VEC>(r + (size_t)(nh + kh) * dh, c * 16 + 4 * z.g, dh) * scale;
+    vf[c] = row4<VEC>(r + (size_t)(nh + nkv + kh) * dh, c * 16 + 4 * z.g, dh);
+  }
+#pragma unroll
+  for (int t = 0; t < NCT; ++t) dk[t] = dv[t] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+  int st = 0;
+  for (int hh = kh * G; hh < (kh + 1) * G; ++hh) {
+    const T* Q = base + (size_t)hh * dh;
+    const T* dO = dout + (size_t)sv.row0 * ldo + (size_t)hh * dh;
+    for (int i0 = j0; i0 < S; i0 += BT, st ^= 1) {
+      const int iw = i0 + z.wave * 16;
+      const size_t ir = (size_t)min(iw + z.lr, S - 1);
+      f32x4_t s = {0.f, 0.f, 0.f, 0.f}, dp = s, p, d;
+#pragma unroll
+      for (int c = 0; c < NG; ++c) {
+        s = mma16(row4<VEC>(Q + ir * ld, c * 16 + 4 * z.g, dh), kf[c], s);
+        dp = mma16(row4<VEC>(dO + ir * ldo, c * 16 + 4 * z.g, dh), vf[c], dp);
+      }
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {
+        const int i = iw + 4 * z.g + q;
+        p[q] = d[q] = 0.f;
+        if (i < S && j <= i) {
+          const size_t at = stat_index(cu, Trows, sv, b, hh, nh, Smax, i);
+          p[q] = __expf(s[q] - lse[at]);
+          d[q] = p[q] * (dp[q] - delta[at]);
+        }
+      }
+      *reinterpret_cast<f32x4_t*>(&ps[st][z.lr * PP + z.wave * 16 + 4 * z.g]) = p;
+      *reinterpret_cast<f32x4_t*>(&ds[st][z.lr * PP + z.wave * 16 + 4 * z.g]) = d;
+      __syncthreads();   // (as in the dQ kernel)
+      second_product<NCT>(z, ps[st], dO, ldo, i0, S, dh, dv);
+      second_product<NCT>(z, ds[st], Q, ld, i0, S, dh, dk);
+    }
+  }
+#pragma unroll
+  for (int q = 0; q < 4; ++q) {
+    const int r = j0 + 4 * z.g + q;
+    if (r >= S) continue;
+#pragma unroll
+    for (int t = 0; t < NCT; ++t) {
+      const int col = (z.wave + 4 * t) * 16 + z.lr;
+      if (col >= dh) continue;
+      T* row = dqkv + ((size_t)sv.row0 + r) * ld;
+      stf(row, (size_t)(nh + kh) * dh + col, dk[t][q] * scale);
+      stf(row, (size_t)(nh + nkv + kh) * dh + col, dv[t][q]);
+    }
+  }
+}
+
+namespace {
+
+bool simple_ok(const AttnArgs& a) {
   return a.dh <= kMaxDh && a.B <= 65535 && a.nh <= 65535 && a.S > 0 && a.B > 0;
 }
+
+template <typename T, int NG, bool VEC>
+hipError_t fwd_simple(const AttnArgs& a, hipStream_t s) {
+  hipLaunchKernelGGL((attn_fwd_simple_kernel<T, NG, VEC>), dim3((unsigned)((a.S + BR - 1) / BR), a.nh, a.B), dim3(256), 0, s, (const T*)a.qkv, (T*)a.out,
+                     a.lse, a.S, a.nh, a.nkv, a.dh, a.cu_seqlens, a.total_rows);
+  return hipGetLastError();
+}
+
+template <typename T, int NG, bool VEC>
+hipError_t bwd_simple(const AttnArgs& a, hipStream_t s) {
+  const unsigned nb = (unsigned)((a.S + BR - 1) / BR);
+  hipLaunchKernelGGL((attn_dq_simple_kernel<T, NG, VEC>), dim3(nb, a.nh, a.B), dim3(256), 0, s, (const T*)a.qkv, (const T*)a.out, (const T*)a.dout, a.lse,
+                     a.delta, (T*)a.dqkv, a.S, a.nh, a.nkv, a.dh, a.cu_seqlens, a.total_rows);
+  const hipError_t e = hipGetLastError();
+  if (e != hipSuccess) return e;
+  hipLaunchKernelGGL((attn_dkv_simple_kernel<T, NG, VEC>), dim3(nb, a.nkv, a.B), dim3(256), 0, s, (const T*)a.qkv, (const T*)a.dout, a.lse, a.delta,
+                     (T*)a.dqkv, a.S, a.nh, a.nkv, a.dh, a.cu_seqlens, a.total_rows);
+  return hipGetLastError();
+}
+
+template <typename T, int NG>
+hipError_t run_simple(const AttnArgs& a, bool bwd, hipStream_t s) {
+  // every row of every head starts at a multiple of dh elements: four of them are one load when dh and the bases allow it
+  const bool vec = a.dh % 4 == 0 && (((uintptr_t)a.qkv | (uintptr_t)a.out | (uintptr_t)a.dout | (uintptr_t)a.dqkv) & 15) == 0;
+  if (bwd) return vec ? bwd_simple<T, NG, true>(a, s) : bwd_simple<T, NG, false>(a, s);
+  return vec ? fwd_simple<T, NG, true>(a, s) : fwd_simple<T, NG, false>(a, s);
+}
+
+template <typename T>
+hipError_t run_simple(const AttnArgs& a, bool bwd, hipStream_t s) {
+  if (a.dh <= 64) return run_simple<T, 4>(a, bwd, s);
+  if (a.dh <= 128) return run_simple<T, 8>(a, bwd, s);
+  return run_simple<T, 16>(a, bwd, s);
+}
+
+}  // namespace
 
 hipError_t launch_attn_fwd_simple(const AttnArgs& a, hipStream_t s) {
   if (!simple_ok(a)) return hipErrorInvalidValue;
   ProfScope ps("attn_fwd_simple", 2.0 * a.B * a.nh * a.dh * (double)a.S * (a.S + 1), 0, s);
-  dim3 grid(a.S, a.nh, a.B), blk(64);
-  if (a.dtype == kBF16) hipLaunchKernelGGL(attn_fwd_simple_kernel<bf16_t>, grid, blk, 0, s, (const bf16_t*)a.qkv, (bf16_t*)a.out, a.lse, a.S, a.nh, a.nkv, a.dh, a.cu_seqlens, a.total_rows);
-  else hipLaunchKernelGGL(attn_fwd_simple_kernel<float>, grid, blk, 0, s, (const float*)a.qkv, (float*)a.out, a.lse, a.S, a.nh, a.nkv, a.dh, a.cu_seqlens, a.total_rows);
-  return hipGetLastError();
-}
-
-static hipError_t launch_attn_delta(const AttnArgs& a, hipStream_t s) {   // delta = rowsum(dO * O)
-  ProfScope ps("attn_delta", 0, 2.0 * a.B * a.S * a.nh * a.dh * dtype_size(a.dtype), s);
-  const int lph = a.dh / 8;
-  if (a.dh % 8 == 0 && lph >= 1 && lph <= 64 && (lph & (lph - 1)) == 0 &&
-      (((uintptr_t)a.out | (uintptr_t)a.dout) & 15) == 0) {
-    dim3 grid(a.S, a.B), blk(256);
-    if (a.dtype == kBF16) hipLaunchKernelGGL(attn_delta_vec_kernel<bf16_t>, grid, blk, 0, s, (const bf16_t*)a.out, (const bf16_t*)a.dout, a.delta, a.S, a.nh, a.dh, a.cu_seqlens, a.total_rows);
-    else hipLaunchKernelGGL(attn_delta_vec_kernel<float>, grid, blk, 0, s, (const float*)a.out, (const float*)a.dout, a.delta, a.S, a.nh, a.dh, a.cu_seqlens, a.total_rows);
-    return hipGetLastError();
-  }
-  dim3 grid(a.S, a.nh, a.B), blk(64);
-  if (a.dtype == kBF16) hipLaunchKernelGGL(attn_delta_kernel<bf16_t>, grid, blk, 0, s, (const bf16_t*)a.out, (const bf16_t*)a.dout, a.delta, a.S, a.nh, a.dh, a.cu_seqlens, a.total_rows);
-  else hipLaunchKernelGGL(attn_delta_kernel<float>, grid, blk, 0, s, (const float*)a.out, (const float*)a.dout, a.delta, a.S, a.nh, a.dh, a.cu_seqlens, a.total_rows);
-  return hipGetLastError();
+  return a.dtype == kBF16 ? run_simple<bf16_t>(a, false, s) : run_simple<float>(a, false, s);
 }
 
 hipError_t launch_attn_bwd_simple(const AttnArgs& a, hipStream_t s) {
   if (!simple_ok(a)) return hipErrorInvalidValue;
-  hipError_t e = launch_attn_delta(a, s);
-  if (e != hipSuccess) return e;
   ProfScope ps("attn_bwd_simple", 7.0 * a.B * a.nh * a.dh * (double)a.S * (a.S + 1), 0, s);
-  dim3 gq(a.S, a.nh, a.B), gk(a.S, a.nkv, a.B), blk(64);
-  if (a.dtype == kBF16) {
-    hipLaunchKernelGGL(attn_dq_simple_kernel<bf16_t>, gq, blk, 0, s, (const bf16_t*)a.qkv, (const bf16_t*)a.dout, a.lse, a.delta, (bf16_t*)a.dqkv, a.S, a.nh, a.nkv, a.dh, a.cu_seqlens, a.total_rows);
-    hipLaunchKernelGGL(attn_dkv_simple_kernel<bf16_t>, gk, blk, 0, s, (const bf16_t*)a.qkv, (const bf16_t*)a.dout, a.lse, a.delta, (bf16_t*)a.dqkv, a.S, a.nh, a.nkv, a.dh, a.cu_seqlens, a.total_rows);
-  } else {
-    hipLaunchKernelGGL(attn_dq_simple_kernel<float>, gq, blk, 0, s, (const float*)a.qkv, (const float*)a.dout, a.lse, a.delta, (float*)a.dqkv, a.S, a.nh, a.nkv, a.dh, a.cu_seqlens, a.total_rows);
-    hipLaunchKernelGGL(attn_dkv_simple_kernel<float>, gk, blk, 0, s, (const float*)a.qkv, (const float*)a.dout, a.lse, a.delta, (float*)a.dqkv, a.S, a.nh, a.nkv, a.dh, a.cu_seqlens, a.total_rows);
-  }
-  return hipGetLastError();
+  return a.dtype == kBF16 ? run_simple<bf16_t>(a, true, s) : run_simple<float>(a, true, s);
 }
 
 }  // namespace tide

@@ -97,3 +97,49 @@ def test_both_forms_of_the_key_gradient_passes_agree(B):
     assert float((got[1] - got[1][:1]).abs().max()) == 0.0
     diff, top = (got[0][0] - got[1][0]).abs(), got[1][0].abs().max()
     assert float(diff.max()) < 2.0 ** -7 * float(top)      # one step of bf16 at most
+
+
+_SHAPES = [(1, 1, 1, 2), (15, 2, 1, 64), (16, 4, 2, 64), (17, 2, 2, 20), (64, 3, 1, 24), (65, 4, 2, 66), (130, 2, 1, 80), (200, 2, 1, 129), (150, 2, 2, 256)]
+
+
+@pytest.mark.parametrize("dtype,S,nh,nkv,dh", [(t, *s) for t in ("fp32", "bf16") for s in _SHAPES if t == "fp32" or s[3] != 64])
+def test_attention_in_fp32_arithmetic(B, dtype, S, nh, nkv, dh):
+    """The kernels of fp32 mode and of the other head sizes: tiles of 16 rows and 64, channel groups of 16 (padded, unaligned
+    and at the widest head), against fp64.  fp32: 1e-5 of the largest value (sums of up to 256 products and of S probabilities);
+    bf16: half a step of the result (2^-8)."""
+    bt, dt, code, tol = 2, *((torch.float32, 0, 1e-5) if dtype == "fp32" else (torch.bfloat16, 1, 2.0 ** -8))
+    g = torch.Generator(device=DEV).manual_seed(S + dh)
+    qkv = torch.randn(bt * S, (nh + 2 * nkv) * dh, device=DEV, generator=g).to(dt)
+    dout = torch.randn(bt * S, nh * dh, device=DEV, generator=g).to(dt)
+    out, dqkv = torch.full_like(dout, float("nan")), torch.full_like(qkv, float("nan"))
+    lse, delta = (torch.full((bt, nh, S), float("nan"), device=DEV) for _ in range(2))
+    print(f"attention {dtype} S={S} nh={nh} nkv={nkv} dh={dh}", flush=True)
+    B.tide_attention_fwd(bt, S, nh, nkv, dh, qkv, out, lse, code, stream())
+    sync()
+    B.tide_attention_bwd(bt, S, nh, nkv, dh, qkv, out, dout, lse, delta, dqkv, code, stream())
+    sync()
+    for b in range(bt):
+        rows = slice(b * S, (b + 1) * S)
+        ro, rl, rg = _reference(qkv[rows], dout[rows], S, nh, nkv, dh)
+        assert float((out[rows].double().cpu() - ro).abs().max()) < tol * float(ro.abs().max())
+        assert float((lse[b].double().cpu() - rl).abs().max()) < 1e-5 * max(1.0, float(rl.abs().max()))
+        # delta is made from the rounded output, which the reference does not see: 2^-8 of it on top in bf16
+        assert float((dqkv[rows].double().cpu() - rg).abs().max()) < 2 * tol * float(rg.abs().max())
+
+
+def test_later_positions_reach_nothing_before_them_in_fp32(B):
+    """NaN and infinities from position 50 on leave the outputs of the positions before it as they are."""
+    S, nh, nkv, dh = 100, 2, 1, 64
+    qkv = torch.randn(S, (nh + 2 * nkv) * dh, device=DEV)
+    bad = qkv.clone()
+    bad[50:, :] = float("nan")
+    bad[51::2, -7:] = float("inf")
+    got = []
+    for x in (qkv, bad):
+        out, lse = torch.empty(S, nh * dh, device=DEV), torch.empty(1, nh, S, device=DEV)
+        print("attention later NaN", flush=True)
+        B.tide_attention_fwd(1, S, nh, nkv, dh, x, out, lse, 0, stream())
+        sync()
+        got.append(out[:50])
+        assert x is qkv or bool(torch.isnan(out[50:]).all())
+    assert bool(torch.isfinite(got[1]).all()) and float((got[0] - got[1]).abs().max()) < 1e-5
