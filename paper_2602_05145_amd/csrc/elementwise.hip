@@ -17,8 +17,22 @@ namespace tide {
 // ----------------------------------------------------------------------------------------------
 // Two launches of 1024-thread blocks, one row per thread: block-wise counts, then every block finds its
 // offset from the counts of the blocks before it and writes its rows (a single block walking all rows took
-// 0.11 ms at 32768 rows, at the head of every call).
+// 0.11 ms at 32768 rows, at the head of every call).  Up to kPlanDirectRows rows the blocks count what lies before them
+// themselves (at most 8 rows per thread) and the first launch falls away.  The cos / sin table of RoPE is made by further
+// blocks of the second launch.  A launch that does next to nothing takes 4.5 us on the stream.
+constexpr int64_t kPlanDirectRows = 8192;
+struct RopeTable { float* cs; int S, dh; double theta; };   // cs [S, dh/2, 2]; S == 0: none
 namespace {
+// one (cos, sin) pair: position idx / (dh / 2), frequency idx % (dh / 2)
+__device__ __forceinline__ void rope_table_entry(const RopeTable& rt, int64_t idx) {
+  const int half = rt.dh / 2;
+  if (idx >= (int64_t)rt.S * half) return;
+  const int pos = (int)(idx / half), i = (int)(idx % half);
+  const double inv = pow(rt.theta, -2.0 * (double)i / (double)rt.dh);
+  const double ang = (double)pos * inv;
+  rt.cs[2 * (size_t)idx] = (float)cos(ang);
+  rt.cs[2 * (size_t)idx + 1] = (float)sin(ang);
+}
 struct RowFlags { int keep, sel; };
 __device__ __forceinline__ RowFlags row_flags(const int32_t* tokens, const uint8_t* mask, int64_t t, int64_t T, int V,
                                               int select_all, int64_t v0, int64_t v1, const uint8_t* sel_mask) {
@@ -64,11 +78,15 @@ __global__ __launch_bounds__(1024) void plan_write_kernel(const int32_t* __restr
                                                           const int* __restrict__ cu, int nseq, int max_len,
                                                           uint8_t* __restrict__ mask_eff, int* __restrict__ status,
                                                           const int* __restrict__ blk_counts,
-                                                          const uint8_t* __restrict__ sel_mask) {
-  __shared__ int red_sel[16], red_keep[16], wave_sel[16];
+                                                          const uint8_t* __restrict__ sel_mask, int nb, RopeTable rt) {
+  if ((int)blockIdx.x >= nb) {   // whole block
+    rope_table_entry(rt, ((int64_t)blockIdx.x - nb) * 1024 + threadIdx.x);
+    return;
+  }
+  __shared__ int red_sel[16], red_keep[16], wave_sel[16], wave_keep[16];
   __shared__ int bad_cu;
   const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
-  const int nb = gridDim.x, b = blockIdx.x;
+  const int b = blockIdx.x;
   const int64_t v0 = cu ? min(max((int64_t)cu[0], (int64_t)0), T) : 0;
   const int64_t v1 = cu ? min(max((int64_t)cu[nseq], v0), T) : T;
   // the offsets live on the device: block 0 checks them and reports through the status word (bit 1)
@@ -92,7 +110,15 @@ __global__ __launch_bounds__(1024) void plan_write_kernel(const int32_t* __restr
   }
   // selected / kept rows in the blocks before this one (fixed order of addition: integers, exact)
   int ps = 0, pk = 0;
-  for (int i = tid; i < b; i += 1024) { ps += blk_counts[2 * i]; pk += blk_counts[2 * i + 1]; }
+  if (blk_counts) {
+    for (int i = tid; i < b; i += 1024) { ps += blk_counts[2 * i]; pk += blk_counts[2 * i + 1]; }
+  } else {
+    for (int i = 0; i < b; ++i) {
+      const RowFlags f = row_flags(tokens, mask, (int64_t)i * 1024 + tid, T, V, select_all, v0, v1, sel_mask);
+      ps += f.sel;
+      pk += f.keep;
+    }
+  }
 #pragma unroll
   for (int o = 32; o > 0; o >>= 1) { ps += __shfl_xor(ps, o, 64); pk += __shfl_xor(pk, o, 64); }
   if (lane == 0) { red_sel[w] = ps; red_keep[w] = pk; }
@@ -104,7 +130,10 @@ __global__ __launch_bounds__(1024) void plan_write_kernel(const int32_t* __restr
     const int v = __shfl_up(incl, o, 64);
     if (lane >= o) incl += v;
   }
-  if (lane == 63) wave_sel[w] = incl;
+  int kept = f.keep;
+#pragma unroll
+  for (int o = 32; o > 0; o >>= 1) kept += __shfl_xor(kept, o, 64);
+  if (lane == 63) { wave_sel[w] = incl; wave_keep[w] = kept; }
   __syncthreads();
   int base = 0, base_keep = 0, before = 0;
   for (int i = 0; i < 16; ++i) {
@@ -123,7 +152,8 @@ __global__ __launch_bounds__(1024) void plan_write_kernel(const int32_t* __restr
     }
   }
   if (b == nb - 1 && tid == 0) {
-    const int total_sel = base + blk_counts[2 * b], total_keep = base_keep + blk_counts[2 * b + 1];
+    int total_sel = base, total_keep = base_keep;
+    for (int i = 0; i < 16; ++i) { total_sel += wave_sel[i]; total_keep += wave_keep[i]; }
     const float n = fmaxf((float)total_keep, 1.f);
     scal[0] = n;
     scal[1] = 1.f / n;
@@ -137,13 +167,18 @@ size_t plan_rows_scratch_bytes(int64_t T) { return (size_t)plan_blocks(T) * 2 * 
 hipError_t launch_plan_rows(const int32_t* tokens, const uint8_t* mask, int64_t T, int V, int select_all,
                             float* scal, int* cnt, int32_t* kept_idx, int32_t* row_pos, const int* cu, int nseq,
                             int max_len, uint8_t* mask_eff, int* status, int* blk_counts, const uint8_t* sel_mask,
-                            hipStream_t s) {
+                            int rope_len, int rope_dh, float rope_theta, float* rope_cs, hipStream_t s) {
   ProfScope ps("plan_rows", 0, 24.0 * (double)T, s);
   const unsigned nb = (unsigned)plan_blocks(T);
-  hipLaunchKernelGGL(plan_count_kernel, dim3(nb), dim3(1024), 0, s, tokens, mask, T, V, select_all, cu, nseq, blk_counts, sel_mask);
-  hipError_t e = hipGetLastError();
-  if (e != hipSuccess) return e;
-  hipLaunchKernelGGL(plan_write_kernel, dim3(nb), dim3(1024), 0, s, tokens, mask, T, V, select_all, scal, cnt, kept_idx, row_pos, cu, nseq, max_len, mask_eff, status, blk_counts, sel_mask);
+  const bool direct = T <= kPlanDirectRows;
+  if (!direct) {
+    hipLaunchKernelGGL(plan_count_kernel, dim3(nb), dim3(1024), 0, s, tokens, mask, T, V, select_all, cu, nseq, blk_counts, sel_mask);
+    const hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return e;
+  }
+  const RopeTable rt{rope_cs, rope_len, rope_dh, (double)rope_theta};
+  const unsigned table = (unsigned)(((int64_t)rope_len * (rope_dh / 2) + 1023) / 1024);
+  hipLaunchKernelGGL(plan_write_kernel, dim3(nb + table), dim3(1024), 0, s, tokens, mask, T, V, select_all, scal, cnt, kept_idx, row_pos, cu, nseq, max_len, mask_eff, status, direct ? (const int*)nullptr : blk_counts, sel_mask, (int)nb, rt);
   return hipGetLastError();
 }
 
@@ -564,8 +599,10 @@ __global__ __launch_bounds__(256, VEC ? rmsnorm_bwd_resident(sizeof(T), NIT) : 1
 // out[c] = sum_r part[r, c]; 16 columns x 16 row lanes per block, four loads in flight per thread, fixed
 // summation order.  (64 columns x 4 row lanes, i.e. 64 blocks at d = 4096 with one load in flight per thread, took
 // 49 us for the 768 x 4096 partials of the 8B shape: a fifth of the RMSNorm backward it finishes.)
-__global__ __launch_bounds__(256) void colsum_kernel(const float* __restrict__ part, int64_t nrows, int d,
-                                                     float* __restrict__ out, int accumulate) {
+// blockIdx.y: which of up to three sums of the same size (the three norms of a training step fold theirs in one launch).
+__global__ __launch_bounds__(256) void colsum_kernel(ColSums cs, int64_t nrows, int d, int accumulate) {
+  const float* __restrict__ part = cs.part[blockIdx.y];
+  float* __restrict__ out = cs.out[blockIdx.y];
   __shared__ float sm[16][17];
   const int cl = threadIdx.x & 15, rl = threadIdx.x >> 4;
   const int c = blockIdx.x * 16 + cl;
@@ -590,6 +627,19 @@ __global__ __launch_bounds__(256) void colsum_kernel(const float* __restrict__ p
   }
 }
 
+// blocks of the backward kernel, i.e. rows of its partial sums
+static int64_t rmsnorm_bwd_grid(int64_t rows, int d, int dtype) {
+  const int64_t n = rmsnorm_bwd_blocks(rows, d);
+  if (d % 8 || d > 8192) return n;
+  const int64_t cap = 256 * rmsnorm_bwd_resident((int)dtype_size(dtype), rmsnorm_bwd_nit(d));
+  return n < cap ? n : cap;
+}
+
+hipError_t launch_colsums(const ColSums& cs, int n, int64_t rows, int d, int dtype, int accumulate, hipStream_t s) {
+  hipLaunchKernelGGL(colsum_kernel, dim3((d + 15) / 16, (unsigned)n), dim3(256), 0, s, cs, rmsnorm_bwd_grid(rows, d, dtype), d, accumulate);
+  return hipGetLastError();
+}
+
 size_t rmsnorm_bwd_scratch_bytes(int64_t rows, int d) {
   const int64_t nblk = rmsnorm_bwd_blocks(rows, d);
   return (size_t)nblk * (size_t)d * sizeof(float);
@@ -597,7 +647,7 @@ size_t rmsnorm_bwd_scratch_bytes(int64_t rows, int d) {
 
 hipError_t launch_rmsnorm_bwd(int64_t rows, int d, const void* dy, const void* x, const void* g,
                               const float* rstd, const void* res, void* dx, float* dg, float* dg_partial,
-                              int dtype, const int* rows_dev, hipStream_t s, int accumulate) {
+                              int dtype, const int* rows_dev, hipStream_t s) {
   if (rows <= 0) return hipSuccess;
   const bool vec = (d % 8) == 0 && d <= 8192;
   if (!vec && d > 1024) return hipErrorInvalidValue;
@@ -605,8 +655,7 @@ hipError_t launch_rmsnorm_bwd(int64_t rows, int d, const void* dy, const void* x
   if (rows_dev) prof_dynamic(rows_dev, 0, rows);
   const int per = vec ? 8 * 256 : 256;            // columns covered by one pass of the block
   const int nit = (d + per - 1) / per;            // <= 4 by the limits above
-  int64_t nblk = rmsnorm_bwd_blocks(rows, d);
-  if (vec && nblk > 256 * rmsnorm_bwd_resident((int)dtype_size(dtype), nit)) nblk = 256 * rmsnorm_bwd_resident((int)dtype_size(dtype), nit);
+  const int64_t nblk = rmsnorm_bwd_grid(rows, d, dtype);
   dim3 grid((unsigned)nblk), blk(256);
 #define TIDE_RMS_BWD(T, V, N) hipLaunchKernelGGL((rmsnorm_bwd_kernel<T, V, N>), grid, blk, 0, s, (const T*)dy, (const T*)x, (const T*)g, rstd, (const T*)res, (T*)dx, dg_partial, rows, d, rows_dev)
 #define TIDE_RMS_BWD_N(T, V) do { if (nit <= 1) TIDE_RMS_BWD(T, V, 1); else if (nit == 2) TIDE_RMS_BWD(T, V, 2); else TIDE_RMS_BWD(T, V, 4); } while (0)
@@ -619,28 +668,23 @@ hipError_t launch_rmsnorm_bwd(int64_t rows, int d, const void* dy, const void* x
 #undef TIDE_RMS_BWD
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
-  hipLaunchKernelGGL(colsum_kernel, dim3((d + 15) / 16), dim3(256), 0, s, dg_partial, nblk, d, dg, accumulate);
-  return hipGetLastError();
+  if (!dg) return hipSuccess;   // the caller folds the partial sums later
+  const ColSums one{{dg_partial}, {dg}};
+  return launch_colsums(one, 1, rows, d, dtype, 0, s);
 }
 
 // ----------------------------------------------------------------------------------------------
 // RoPE.  The cos/sin table is built once per call in double precision (positions reach 16384, where
 // an fp32 angle would already be off by ~1e-3 rad), then applied in place to the q and k heads.
 // ----------------------------------------------------------------------------------------------
-__global__ void rope_table_kernel(int S, int half, int dh, double theta, float* __restrict__ cs) {
-  const int idx = blockIdx.x * blockDim.x + threadIdx.x;
-  if (idx >= S * half) return;
-  const int pos = idx / half, i = idx % half;
-  const double inv = pow(theta, -2.0 * (double)i / (double)dh);
-  const double ang = (double)pos * inv;
-  cs[2 * (size_t)idx] = (float)cos(ang);
-  cs[2 * (size_t)idx + 1] = (float)sin(ang);
+__global__ __launch_bounds__(256) void rope_table_kernel(RopeTable rt) {
+  rope_table_entry(rt, (int64_t)blockIdx.x * 256 + threadIdx.x);
 }
 
 hipError_t launch_rope_table(int S, int dh, float theta, float* cs, hipStream_t s) {
   const int half = dh / 2;
   const int n = S * half;
-  hipLaunchKernelGGL(rope_table_kernel, dim3((n + 255) / 256), dim3(256), 0, s, S, half, dh, (double)theta, cs);
+  hipLaunchKernelGGL(rope_table_kernel, dim3((n + 255) / 256), dim3(256), 0, s, RopeTable{cs, S, dh, (double)theta});
   return hipGetLastError();
 }
 

@@ -54,6 +54,7 @@ size_t plan_rows_scratch_bytes(int64_t T);   // blk_counts below
 hipError_t launch_plan_rows(const int32_t* tokens, const uint8_t* mask, int64_t T, int V, int select_all,
                             float* scal, int* cnt, int32_t* kept_idx, int32_t* row_pos, const int* cu, int nseq,
                             int max_len, uint8_t* mask_eff, int* status, int* blk_counts, const uint8_t* sel_mask,
+                            int rope_len, int rope_dh, float rope_theta, float* rope_cs,   // also makes launch_rope_table's table
                             hipStream_t s);
 // packed batches (cu = device offsets of nseq sequences): position of each row in its sequence, and zeroing
 // of the rows of a [T, row_bytes] array that no sequence owns
@@ -76,8 +77,10 @@ hipError_t launch_rmsnorm_fwd(int64_t rows, int d, const void* x, const void* g,
 size_t rmsnorm_bwd_scratch_bytes(int64_t rows, int d);
 hipError_t launch_rmsnorm_bwd(int64_t rows, int d, const void* dy, const void* x, const void* g,
                               const float* rstd, const void* res, void* dx, float* dg,
-                              float* dg_partial, int dtype, const int* rows_dev, hipStream_t s,
-                              int accumulate = 0);   // accumulate: dg += instead of dg =
+                              float* dg_partial, int dtype, const int* rows_dev, hipStream_t s);   // dg == NULL: leaves dg_partial to launch_colsums
+struct ColSums { const float* part[3]; float* out[3]; };
+// out[i] (accumulate: +)= the column sums of n launches' dg_partial, all over (rows, d, dtype)
+hipError_t launch_colsums(const ColSums& cs, int n, int64_t rows, int d, int dtype, int accumulate, hipStream_t s);
 hipError_t launch_rope_table(int S, int dh, float theta, float* cs, hipStream_t s);  // cs [S, dh/2, 2]
 // row_pos (optional, device): position of every row in its sequence; NULL = row % S.  pos_offset is added to
 // every position (the table must reach that far).

@@ -74,7 +74,7 @@ struct Plan {
   // offsets (bytes)
   size_t scal, adam_dyn, cnt, status, plan_cnt, kept_idx, row_pos, tokens_c, mask_c, mask_eff, seq_pos, rope_cs, x0, r1, a, qkv, attn_lse, A, A_c, x0_c, x1, r2, bn, gt, u, h, x2, r3, yhat, lse, loss_rows, hit_rows, z;
   size_t fwd_end;
-  size_t dyhat, dx2, dx1_c, dx1, dx0, dh, dbn, dA_c, dA, dqkv, da, delta, dg_partial;
+  size_t dyhat, dx2, dx1_c, dx1, dx0, dh, dbn, dA_c, dA, dqkv, da, delta, dg_partial[3];
   size_t splitk; size_t splitk_bytes;   // scratch of the weight-gradient products whose last tile round is split over K
   size_t g0, e0, dg0;   // token-input variant: projected features, looked-up embeddings, gradient of the features
   size_t total;
@@ -177,7 +177,7 @@ Plan make_plan(const tide_draft_config* c) {
   p.da = bwd_take(T * p.d * es);
   p.dg0 = bwd_take(T * p.d * es);
   p.delta = bwd_take((size_t)c->batch * c->n_heads * c->seq * 4);
-  p.dg_partial = bwd_take(rmsnorm_bwd_scratch_bytes(p.T, (int)p.d));
+  for (auto& o : p.dg_partial) o = bwd_take(rmsnorm_bwd_scratch_bytes(p.T, (int)p.d));   // one per norm
   {
     // the largest split-K scratch any product of this configuration asks for
     size_t need = 0;
@@ -312,7 +312,7 @@ int enqueue_trunk(const tide_draft_config* c, const tide_draft_tensors* P, const
   const int64_t T = p.T;
   float* scal = (float*)(ws + p.scal);
   const int shift = ur ? ur->shift : 0;
-  TIDE_HIP(launch_plan_rows(tokens, mask, T, c->vocab, select_all, scal, (int*)(ws + p.cnt), (int32_t*)(ws + p.kept_idx), (int32_t*)(ws + p.row_pos), q.cu, q.n, q.max_len, (uint8_t*)(ws + p.mask_eff), (int*)(ws + p.status), (int*)(ws + p.plan_cnt), ur ? ur->sel : nullptr, s), "plan_rows");
+  TIDE_HIP(launch_plan_rows(tokens, mask, T, c->vocab, select_all, scal, (int*)(ws + p.cnt), (int32_t*)(ws + p.kept_idx), (int32_t*)(ws + p.row_pos), q.cu, q.n, q.max_len, (uint8_t*)(ws + p.mask_eff), (int*)(ws + p.status), (int*)(ws + p.plan_cnt), ur ? ur->sel : nullptr, q.max_len + shift, c->head_dim, c->rope_theta, (float*)(ws + p.rope_cs), s), "plan_rows and rope table");
   if (q.cu) TIDE_HIP(launch_seq_pos(q.cu, q.n, T, q.max_len, (int32_t*)(ws + p.seq_pos), s), "sequence positions");
   if (shift > 0) {
     // the feature of a later step is the layer output of the step before (dense over that step's selected
@@ -339,7 +339,6 @@ int enqueue_trunk(const tide_draft_config* c, const tide_draft_tensors* P, const
   }
   TIDE_HIP(launch_rmsnorm_fwd(T, (int)p.d, ws + p.x0, P->g1, c->rms_eps, ws + p.a, (float*)(ws + p.r1), dt, nullptr, s), "rmsnorm1");
   TIDE_HIP(run_gemm(gemm_args(kNT, T, p.nqkv, p.d, ws + p.a, p.d, P->w_qkv, p.d, ws + p.qkv, p.nqkv, dt, dt), ws, p, s), "gemm qkv");
-  TIDE_HIP(launch_rope_table(q.max_len + shift, c->head_dim, c->rope_theta, (float*)(ws + p.rope_cs), s), "rope table");
   { const int rc = enqueue_rope(c, q, ws, p, ws + p.qkv, 0, shift, s); if (rc) return rc; }
   // later step of the unroll: keep the step's own key/value pair aside and attend to the step-1 keys/values
   if (shift > 0) TIDE_HIP(launch_kv_swap(T, (int)p.nq, (int)p.nk, ws + p.qkv, ur->first_ws + p.qkv, ur->own_kv[shift - 1], dt, s), "kv swap");
@@ -629,7 +628,8 @@ static int enqueue_backward(const tide_draft_config* cfg, const tide_draft_tenso
   const int64_t T = p.T;
   const int acc = o.accumulate;
   const int shift = o.ur ? o.ur->shift : 0;
-  float* dgp = (float*)(ws + p.dg_partial);
+  float* dgp[3];
+  for (int i = 0; i < 3; ++i) dgp[i] = (float*)(ws + p.dg_partial[i]);
   const int* cnt = (const int*)(ws + p.cnt);
   // Backward over the selected rows (dense, *cnt of them) down to the attention output.  dX products trim
   // their M, dW products their K.
@@ -650,7 +650,7 @@ static int enqueue_backward(const tide_draft_config* cfg, const tide_draft_tenso
     return g;
   };
   // final norm (plus, in the unroll, what the step after sends back into x2)
-  TIDE_HIP(launch_rmsnorm_bwd(T, (int)p.d, ws + p.dyhat, ws + p.x2, P->g3, (const float*)(ws + p.r3), o.dx2_extra, ws + p.dx2, (float*)G->g3, dgp, dt, cnt, s, acc), "rmsnorm3 bwd");
+  TIDE_HIP(launch_rmsnorm_bwd(T, (int)p.d, ws + p.dyhat, ws + p.x2, P->g3, (const float*)(ws + p.r3), o.dx2_extra, ws + p.dx2, nullptr, dgp[2], dt, cnt, s), "rmsnorm3 bwd");
   // x2 = x1 + h W_down^T
   TIDE_HIP(run_gemm(rows_dx(p.F, p.d, ws + p.dx2, p.d, P->w_down, p.F, ws + p.dh, p.F), ws, p, s), "gemm dh");
   TIDE_HIP(run_gemm(rows_dw(p.d, p.F, ws + p.dx2, p.d, ws + p.h, p.F, G->w_down, p.F), ws, p, s), "gemm dW_down");
@@ -663,7 +663,7 @@ static int enqueue_backward(const tide_draft_config* cfg, const tide_draft_tenso
   }
   TIDE_HIP(run_gemm(rows_dw(p.F, p.d, ws + p.gt, p.F, ws + p.bn, p.d, G->w_gate, p.d), ws, p, s), "gemm dW_gate");
   TIDE_HIP(run_gemm(rows_dw(p.F, p.d, ws + p.u, p.F, ws + p.bn, p.d, G->w_up, p.d), ws, p, s), "gemm dW_up");
-  TIDE_HIP(launch_rmsnorm_bwd(T, (int)p.d, ws + p.dbn, ws + p.x1, P->g2, (const float*)(ws + p.r2), ws + p.dx2, ws + p.dx1_c, (float*)G->g2, dgp, dt, cnt, s, acc), "rmsnorm2 bwd");
+  TIDE_HIP(launch_rmsnorm_bwd(T, (int)p.d, ws + p.dbn, ws + p.x1, P->g2, (const float*)(ws + p.r2), ws + p.dx2, ws + p.dx1_c, nullptr, dgp[1], dt, cnt, s), "rmsnorm2 bwd");
   // x1 = x0 + A W_o^T
   TIDE_HIP(run_gemm(rows_dx(p.nq, p.d, ws + p.dx1_c, p.d, P->w_o, p.nq, ws + p.dA_c, p.nq), ws, p, s), "gemm dA");
   TIDE_HIP(run_gemm(rows_dw(p.d, p.nq, ws + p.dx1_c, p.d, ws + p.A_c, p.nq, G->w_o, p.nq), ws, p, s), "gemm dW_o");
@@ -693,7 +693,12 @@ static int enqueue_backward(const tide_draft_config* cfg, const tide_draft_tenso
   { const int rc2 = enqueue_rope(cfg, q, ws, p, ws + p.dqkv, 1, shift, s); if (rc2) return rc2; }
   TIDE_HIP(run_gemm(gemm_args(kNN, T, p.d, p.nqkv, ws + p.dqkv, p.nqkv, P->w_qkv, p.d, ws + p.da, p.d, dt, dt), ws, p, s), "gemm da");
   TIDE_HIP(run_gemm(full_dw(p.nqkv, p.d, ws + p.dqkv, p.nqkv, ws + p.a, p.d, G->w_qkv, p.d, acc), ws, p, s), "gemm dW_qkv");
-  TIDE_HIP(launch_rmsnorm_bwd(T, (int)p.d, ws + p.da, ws + p.x0, P->g1, (const float*)(ws + p.r1), ws + p.dx1, ws + p.dx0, (float*)G->g1, dgp, dt, nullptr, s, acc), "rmsnorm1 bwd");
+  TIDE_HIP(launch_rmsnorm_bwd(T, (int)p.d, ws + p.da, ws + p.x0, P->g1, (const float*)(ws + p.r1), ws + p.dx1, ws + p.dx0, nullptr, dgp[0], dt, nullptr, s), "rmsnorm1 bwd");
+  {
+    // the gain gradients of the three norms
+    const ColSums cs{{dgp[0], dgp[1], dgp[2]}, {(float*)G->g1, (float*)G->g2, (float*)G->g3}};
+    TIDE_HIP(launch_colsums(cs, 3, T, (int)p.d, dt, acc, s), "gain gradients");
+  }
   const void* dfeat = ws + p.dx0;   // gradient of the step's input feature (feature-only model: x0 is the feature)
   if (tok) {
     // x0 = [g ; e] W_in^T: dW_in = dx0^T [g ; e] (two products into the column halves of dW_in), dg = dx0 W_in[:, :d]
