@@ -18,6 +18,7 @@
 #include <type_traits>
 
 #include "kernels.h"
+#include "prof.h"
 #include "tide_common.h"
 
 namespace tide {
@@ -189,7 +190,7 @@ __global__ __launch_bounds__(256, 2) void gemm_fp32_tile_kernel(Fp32GemmParams p
 
 // ---- one E x E tile per block (E = 32, or 16 with v_mfma_f32_16x16x4_f32), the contraction split over NW waves ----
 template <int E, int NW, bool AKM, bool BKM, bool VEC>
-__global__ __launch_bounds__(NW * 64) void gemm_fp32_wavek_kernel(Fp32GemmParams p) {
+__device__ __forceinline__ void wavek_tile(Fp32GemmParams p, int tile_m, int tile_n) {
   constexpr int NG = 64 / E;     // lane groups, each with four consecutive k of a group of KG
   constexpr int KG = 4 * NG;     // 8 (E = 32) or 16
   constexpr int NACC = E * E / 64;
@@ -199,7 +200,7 @@ __global__ __launch_bounds__(NW * 64) void gemm_fp32_wavek_kernel(Fp32GemmParams
   device_sizes(p);
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int lr = lane % E, g = lane / E;
-  const int m0 = blockIdx.y * E, n0 = blockIdx.x * E;
+  const int m0 = tile_m * E, n0 = tile_n * E;
   if (m0 >= p.M) return;                                        // whole block, before any barrier
   if (p.K == 0 && p.K2 == 0 && p.accumulate) return;            // nothing to add
   acc_t acc;
@@ -257,6 +258,26 @@ __global__ __launch_bounds__(NW * 64) void gemm_fp32_wavek_kernel(Fp32GemmParams
   }
 }
 
+template <int E, int NW, bool AKM, bool BKM, bool VEC>
+__global__ __launch_bounds__(NW * 64) void gemm_fp32_wavek_kernel(Fp32GemmParams p) {
+  wavek_tile<E, NW, AKM, BKM, VEC>(p, blockIdx.y, blockIdx.x);
+}
+
+// Several independent products of one layout in one launch: a product of the fp32 configuration is 4 us of launch and
+// latency, whatever its size.
+namespace {
+struct Fp32Group { Fp32GemmParams p[kMaxGemmGroup]; int first[kMaxGemmGroup + 1]; int n; };   // first tile of each
+}
+template <bool AKM, bool BKM, bool VEC>
+__global__ __launch_bounds__(256) void gemm_fp32_group_kernel(Fp32Group g) {
+  int i = 0;
+#pragma unroll
+  for (int k = 1; k < kMaxGemmGroup; ++k)
+    if (k < g.n && (int)blockIdx.x >= g.first[k]) i = k;
+  const int tile = blockIdx.x - g.first[i], tiles_n = (g.p[i].N + 15) / 16;
+  wavek_tile<16, 4, AKM, BKM, VEC>(g.p[i], tile / tiles_n, tile % tiles_n);
+}
+
 namespace {
 
 // Which kernel.  The large tile when it gives every CU one; the small one, or the 32-row tile of the split over waves,
@@ -293,13 +314,10 @@ hipError_t launch_fp32_vec(const Fp32GemmParams& p, bool vec, hipStream_t s) {
 
 }  // namespace
 
-hipError_t launch_gemm_fp32(const GemmArgs& a, hipStream_t s) {
-  if (a.M <= 0 || a.N <= 0) return hipSuccess;
-  // 32-bit row, column and k numbers here; a size beyond that stays with the kernel that counts in 64 bits
+namespace {
+bool fp32_params(const GemmArgs& a, Fp32GemmParams& p, bool& vec) {   // false: sizes beyond 32-bit counting
   const int64_t lim = (int64_t)1 << 30;
-  if (a.M >= lim || a.N >= lim || a.K >= lim || a.K2 >= lim) return launch_gemm_simple(a, s);
-  if ((a.M + 63) / 64 > 65535) return hipErrorInvalidValue;
-  Fp32GemmParams p;
+  if (a.M >= lim || a.N >= lim || a.K >= lim || a.K2 >= lim) return false;
   p.A = (const float*)a.A; p.B = (const float*)a.B; p.A2 = (const float*)a.A2; p.B2 = (const float*)a.B2;
   p.C = (float*)a.C; p.R = (const float*)a.residual; p.alpha_dev = a.alpha_dev;
   p.lda = a.lda; p.ldb = a.ldb; p.ldc = a.ldc; p.ldr = a.ldr;
@@ -307,12 +325,63 @@ hipError_t launch_gemm_fp32(const GemmArgs& a, hipStream_t s) {
   p.alpha = a.alpha; p.accumulate = a.accumulate;
   p.m_dev = a.m_dev; p.m_off = a.m_off; p.k_dev = a.k_dev; p.k_off = a.k_off;
   // 16-byte loads where every row of every operand starts on a 16-byte boundary
-  const bool vec = a.lda % 4 == 0 && a.ldb % 4 == 0 &&
-                   (((uintptr_t)a.A | (uintptr_t)a.B | (uintptr_t)a.A2 | (uintptr_t)a.B2) & 15) == 0;
+  vec = a.lda % 4 == 0 && a.ldb % 4 == 0 && (((uintptr_t)a.A | (uintptr_t)a.B | (uintptr_t)a.A2 | (uintptr_t)a.B2) & 15) == 0;
+  return true;
+}
+
+template <bool AKM, bool BKM>
+hipError_t launch_fp32_group(const Fp32Group& g, bool vec, hipStream_t s) {
+  if (vec) hipLaunchKernelGGL((gemm_fp32_group_kernel<AKM, BKM, true>), dim3((unsigned)g.first[g.n]), dim3(256), 0, s, g);
+  else hipLaunchKernelGGL((gemm_fp32_group_kernel<AKM, BKM, false>), dim3((unsigned)g.first[g.n]), dim3(256), 0, s, g);
+  return hipGetLastError();
+}
+}  // namespace
+
+hipError_t launch_gemm_fp32(const GemmArgs& a, hipStream_t s) {
+  if (a.M <= 0 || a.N <= 0) return hipSuccess;
+  Fp32GemmParams p;
+  bool vec;
+  if (!fp32_params(a, p, vec)) return launch_gemm_simple(a, s);   // the kernel that counts in 64 bits
+  if ((a.M + 63) / 64 > 65535) return hipErrorInvalidValue;
   switch (a.layout) {
     case kNT: return launch_fp32_vec<true, true>(p, vec, s);
     case kNN: return launch_fp32_vec<true, false>(p, vec, s);
     case kTN: return launch_fp32_vec<false, false>(p, vec, s);
+    default: return hipErrorInvalidValue;
+  }
+}
+
+// n independent products, one launch when all of them are fp32, of one layout and of the size that the split over four
+// waves serves alone; one by one otherwise
+hipError_t launch_gemm_group(const GemmArgs* a, int n, hipStream_t s) {
+  Fp32Group g;
+  g.n = n;
+  g.first[0] = 0;
+  bool vec = true, together = n > 1 && n <= kMaxGemmGroup;
+  double flops = 0, bytes = 0;
+  for (int i = 0; together && i < n; ++i) {
+    bool v = false;
+    together = a[i].in_dtype == kF32 && a[i].out_dtype == kF32 && a[i].layout == a[0].layout && a[i].M > 0 && a[i].N > 0 &&
+               fp32_params(a[i], g.p[i], v) && (int64_t)g.p[i].K + g.p[i].K2 < kWideK &&
+               ((a[i].M + 63) / 64) * ((a[i].N + 63) / 64) < kSmallTiles;
+    if (!together) break;
+    vec = vec && v;
+    g.first[i + 1] = g.first[i] + (int)(((a[i].M + 15) / 16) * ((a[i].N + 15) / 16));
+    flops += 2.0 * a[i].M * a[i].N * a[i].K;
+    bytes += 4.0 * (a[i].K * (double)(a[i].M + a[i].N) + a[i].M * (double)a[i].N);
+  }
+  if (!together) {
+    for (int i = 0; i < n; ++i) {
+      const hipError_t e = launch_gemm(a[i], s);
+      if (e != hipSuccess) return e;
+    }
+    return hipSuccess;
+  }
+  ProfScope ps("gemm_fp32_group", flops, bytes, s);
+  switch (a[0].layout) {
+    case kNT: return launch_fp32_group<true, true>(g, vec, s);
+    case kNN: return launch_fp32_group<true, false>(g, vec, s);
+    case kTN: return launch_fp32_group<false, false>(g, vec, s);
     default: return hipErrorInvalidValue;
   }
 }

@@ -43,6 +43,8 @@ hipError_t launch_gemm_mfma(const GemmArgs& a, hipStream_t s);
 hipError_t launch_gemm_fp32(const GemmArgs& a, hipStream_t s);     // fp32 operands and result
 hipError_t launch_gemm_simple(const GemmArgs& a, hipStream_t s);
 hipError_t launch_gemm(const GemmArgs& a, hipStream_t s);  // picks among the three
+constexpr int kMaxGemmGroup = 6;
+hipError_t launch_gemm_group(const GemmArgs* a, int n, hipStream_t s);  // independent products, in one launch where small
 
 // ---- elementwise.hip ------------------------------------------------------------------------
 // Row plan of the LM head.  keep_t = mask_t != 0 and 0 <= token_t < V.  scal[0] = N = max(1, #keep),

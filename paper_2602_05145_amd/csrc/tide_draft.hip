@@ -258,6 +258,15 @@ hipError_t run_gemm(GemmArgs g, char* ws, const Plan& p, hipStream_t s) {
   return launch_gemm(g, s);
 }
 
+// independent products, in one launch where they are small
+hipError_t run_gemms(GemmArgs* g, int n, char* ws, const Plan& p, hipStream_t s) {
+  for (int i = 0; i < n; ++i) {
+    g[i].scratch = ws + p.splitk;
+    g[i].scratch_bytes = p.splitk_bytes;
+  }
+  return launch_gemm_group(g, n, s);
+}
+
 // How the T = batch * seq rows split into sequences: the fixed layout (cu == nullptr: `n` sequences of
 // `max_len` rows each) or a packed batch (cu = device offsets of n sequences, none longer than max_len;
 // rows outside [cu[0], cu[n]) are padding).
@@ -370,8 +379,11 @@ int enqueue_trunk(const tide_draft_config* c, const tide_draft_tensors* P, const
     TIDE_HIP(run_gemm(g, ws, p, s), "gemm o");
   }
   TIDE_HIP(launch_rmsnorm_fwd(T, (int)p.d, ws + p.x1, P->g2, c->rms_eps, ws + p.bn, (float*)(ws + p.r2), dt, cnt, s), "rmsnorm2");
-  TIDE_HIP(run_gemm(rows_gemm(kNT, p.F, p.d, ws + p.bn, p.d, P->w_gate, p.d, ws + p.gt, p.F), ws, p, s), "gemm gate");
-  TIDE_HIP(run_gemm(rows_gemm(kNT, p.F, p.d, ws + p.bn, p.d, P->w_up, p.d, ws + p.u, p.F), ws, p, s), "gemm up");
+  {
+    GemmArgs g[2] = {rows_gemm(kNT, p.F, p.d, ws + p.bn, p.d, P->w_gate, p.d, ws + p.gt, p.F),
+                     rows_gemm(kNT, p.F, p.d, ws + p.bn, p.d, P->w_up, p.d, ws + p.u, p.F)};
+    TIDE_HIP(run_gemms(g, 2, ws, p, s), "gemm gate and up");
+  }
   TIDE_HIP(launch_swiglu_fwd(T * p.F, ws + p.gt, ws + p.u, ws + p.h, dt, p.F, cnt, s), "swiglu");
   {
     GemmArgs g = rows_gemm(kNT, p.d, p.F, ws + p.h, p.F, P->w_down, p.F, ws + p.x2, p.d);
@@ -649,11 +661,20 @@ static int enqueue_backward(const tide_draft_config* cfg, const tide_draft_tenso
     g.accumulate = add;
     return g;
   };
+  // In fp32 mode the weight gradients of the layer wait for each other: nothing overwrites their operands before the end,
+  // and together they are one launch (bf16: at once, while an operand of the product before is still in a cache).
+  GemmArgs later[kMaxGemmGroup];
+  int n_later = 0;
+  auto run_dw = [&](const GemmArgs& g) {
+    if (dt != TIDE_DTYPE_FP32 || n_later == kMaxGemmGroup) return run_gemm(g, ws, p, s);
+    later[n_later++] = g;
+    return hipSuccess;
+  };
   // final norm (plus, in the unroll, what the step after sends back into x2)
   TIDE_HIP(launch_rmsnorm_bwd(T, (int)p.d, ws + p.dyhat, ws + p.x2, P->g3, (const float*)(ws + p.r3), o.dx2_extra, ws + p.dx2, nullptr, dgp[2], dt, cnt, s), "rmsnorm3 bwd");
   // x2 = x1 + h W_down^T
   TIDE_HIP(run_gemm(rows_dx(p.F, p.d, ws + p.dx2, p.d, P->w_down, p.F, ws + p.dh, p.F), ws, p, s), "gemm dh");
-  TIDE_HIP(run_gemm(rows_dw(p.d, p.F, ws + p.dx2, p.d, ws + p.h, p.F, G->w_down, p.F), ws, p, s), "gemm dW_down");
+  TIDE_HIP(run_dw(rows_dw(p.d, p.F, ws + p.dx2, p.d, ws + p.h, p.F, G->w_down, p.F)), "gemm dW_down");
   TIDE_HIP(launch_swiglu_bwd(T * p.F, ws + p.dh, ws + p.gt, ws + p.u, ws + p.gt, ws + p.u, dt, p.F, cnt, s), "swiglu bwd");
   {
     // d bn = dGate W_gate + dUp W_up: one contraction over both operand pairs
@@ -661,12 +682,12 @@ static int enqueue_backward(const tide_draft_config* cfg, const tide_draft_tenso
     g.A2 = ws + p.u; g.B2 = P->w_up; g.K2 = p.F;
     TIDE_HIP(run_gemm(g, ws, p, s), "gemm dbn");
   }
-  TIDE_HIP(run_gemm(rows_dw(p.F, p.d, ws + p.gt, p.F, ws + p.bn, p.d, G->w_gate, p.d), ws, p, s), "gemm dW_gate");
-  TIDE_HIP(run_gemm(rows_dw(p.F, p.d, ws + p.u, p.F, ws + p.bn, p.d, G->w_up, p.d), ws, p, s), "gemm dW_up");
+  TIDE_HIP(run_dw(rows_dw(p.F, p.d, ws + p.gt, p.F, ws + p.bn, p.d, G->w_gate, p.d)), "gemm dW_gate");
+  TIDE_HIP(run_dw(rows_dw(p.F, p.d, ws + p.u, p.F, ws + p.bn, p.d, G->w_up, p.d)), "gemm dW_up");
   TIDE_HIP(launch_rmsnorm_bwd(T, (int)p.d, ws + p.dbn, ws + p.x1, P->g2, (const float*)(ws + p.r2), ws + p.dx2, ws + p.dx1_c, nullptr, dgp[1], dt, cnt, s), "rmsnorm2 bwd");
   // x1 = x0 + A W_o^T
   TIDE_HIP(run_gemm(rows_dx(p.nq, p.d, ws + p.dx1_c, p.d, P->w_o, p.nq, ws + p.dA_c, p.nq), ws, p, s), "gemm dA");
-  TIDE_HIP(run_gemm(rows_dw(p.d, p.nq, ws + p.dx1_c, p.d, ws + p.A_c, p.nq, G->w_o, p.nq), ws, p, s), "gemm dW_o");
+  TIDE_HIP(run_dw(rows_dw(p.d, p.nq, ws + p.dx1_c, p.d, ws + p.A_c, p.nq, G->w_o, p.nq)), "gemm dW_o");
   // back to one row per position: rows that were not selected get no gradient from above (only, through
   // the attention, from the later rows that read their key and value)
   TIDE_HIP(launch_scatter_rows(T, (int)p.nq, ws + p.dA_c, ws + p.dA, (int)p.d, ws + p.dx1_c, ws + p.dx1, (const int32_t*)(ws + p.row_pos), dt, s), "scatter rows");
@@ -692,7 +713,7 @@ static int enqueue_backward(const tide_draft_config* cfg, const tide_draft_tenso
   if (q.cu) TIDE_HIP(launch_zero_padding_rows(ws + p.dqkv, q.cu, q.n, T, (int64_t)(p.nqkv * p.es), s), "zero padding rows");
   { const int rc2 = enqueue_rope(cfg, q, ws, p, ws + p.dqkv, 1, shift, s); if (rc2) return rc2; }
   TIDE_HIP(run_gemm(gemm_args(kNN, T, p.d, p.nqkv, ws + p.dqkv, p.nqkv, P->w_qkv, p.d, ws + p.da, p.d, dt, dt), ws, p, s), "gemm da");
-  TIDE_HIP(run_gemm(full_dw(p.nqkv, p.d, ws + p.dqkv, p.nqkv, ws + p.a, p.d, G->w_qkv, p.d, acc), ws, p, s), "gemm dW_qkv");
+  TIDE_HIP(run_dw(full_dw(p.nqkv, p.d, ws + p.dqkv, p.nqkv, ws + p.a, p.d, G->w_qkv, p.d, acc)), "gemm dW_qkv");
   TIDE_HIP(launch_rmsnorm_bwd(T, (int)p.d, ws + p.da, ws + p.x0, P->g1, (const float*)(ws + p.r1), ws + p.dx1, ws + p.dx0, nullptr, dgp[0], dt, nullptr, s), "rmsnorm1 bwd");
   {
     // the gain gradients of the three norms
@@ -712,13 +733,14 @@ static int enqueue_backward(const tide_draft_config* cfg, const tide_draft_tenso
   if (shift == 0) {
     // the feature is Hcat W_fc^T: weight gradient only, the captured states are data (step 1 is the only one
     // that reads W_fc, so this is never an accumulation)
-    TIDE_HIP(run_gemm(full_dw(p.d, p.KH, dfeat, p.d, hidden_buf, p.KH, G->w_fc, p.KH, 0), ws, p, s), "gemm dW_fc");
+    TIDE_HIP(run_dw(full_dw(p.d, p.KH, dfeat, p.d, hidden_buf, p.KH, G->w_fc, p.KH, 0)), "gemm dW_fc");
   } else {
     // the feature is the layer output of the step before: hand its gradient over, dense over that step's rows
     TIDE_HIP(launch_gather_rows(T, (int)p.d, dfeat, o.dfeat_out, 0, nullptr, nullptr, o.prev_tokens, (const uint8_t*)(o.prev_ws + p.mask_eff),
                                 (const int32_t*)(o.prev_ws + p.kept_idx), (const int*)(o.prev_ws + p.cnt), (int32_t*)(o.prev_ws + p.tokens_c),
                                 (uint8_t*)(o.prev_ws + p.mask_c), dt, s), "gather feature gradient");
   }
+  if (n_later) TIDE_HIP(run_gemms(later, n_later, ws, p, s), "gemm weight gradients");
   return TIDE_OK;
 }
 

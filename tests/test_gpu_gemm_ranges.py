@@ -145,3 +145,26 @@ def test_split_products_of_a_training_step_with_few_kept_rows():
                 assert g @ r / (np.linalg.norm(g) * np.linalg.norm(r)) > 0.999, (kept, k)
             else:
                 assert not g.any(), k
+
+
+@pytest.mark.parametrize("kw", [dict(), dict(batch=3, seq=37, target_hidden=20, hidden=36, n_heads=2, n_kv_heads=1, head_dim=18, ffn=50, vocab=77),
+                                dict(batch=2, seq=520)])
+def test_grouped_weight_gradients_of_an_fp32_step(kw):
+    """The layer's weight gradients of an fp32 step in one launch (aligned and unaligned rows), and one by one where the
+    batch is too long for that (1040 rows).  Against the oracle, as the other fp32 steps: 1e-4 of the largest gradient."""
+    import numpy as np
+    from oracle import tide_oracle as O
+    from paper_2602_05145_amd import runtime, workloads as W
+    cfg = W.get_config("tiny", **dict(dict(vocab=512), **kw))
+    wl = W.make_workload(cfg)
+    tr = runtime.trainer_from_workload(cfg, wl)
+    tr.workspace.fill_(0xFF)
+    print(f"fp32 grouped step {kw}", flush=True)
+    tr.train_step(cfg["lr"])
+    sync()
+    p0 = {k: np.asarray(v, np.float64) for k, v in wl["params"].items()}
+    z = {k: np.zeros_like(v) for k, v in p0.items()}
+    _, grads, *_ = O.train_step(cfg, p0, z, z, 0, wl["hidden"].astype(np.float64), wl["tokens"], wl["mask"], cfg["lr"])
+    got = tr.host(tr.grads)
+    for k, r in grads.items():
+        assert np.abs(got[k] - r).max() <= 1e-4 * np.abs(r).max(), k
