@@ -971,6 +971,7 @@ SplitGrid plan_split_all(const GemmArgs& a, int BT) {
 }
 }  // namespace
 
+size_t gemm_split_tail_bytes(const GemmArgs& a) { return gemm_mfma_supported(a) ? plan_split(a).bytes : 0; }
 size_t gemm_splitk_scratch_bytes(const GemmArgs& a) {
   if (!gemm_mfma_supported(a)) return 0;
   const SplitPlan tail = plan_split(a);

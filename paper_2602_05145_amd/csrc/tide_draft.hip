@@ -981,9 +981,11 @@ size_t tide_gemm_workspace_bytes(int layout, int64_t M, int64_t N, int64_t K, in
   if (layout < 0 || layout > 2 || M <= 0 || N <= 0 || K <= 0) return 0;
   const int64_t lda = layout == kTN ? M : K, ldb = layout == kNT ? K : N;
   GemmArgs g = gemm_args(layout, M, N, K, (void*)256, lda, (void*)256, ldb, (void*)256, N, kBF16, out_dtype);
-  // a bf16 result of a whole round of 256 x 256 tiles or more asks for nothing here
-  if (out_dtype == TIDE_DTYPE_BF16 && ((M + 255) / 256) * ((N + 255) / 256) >= 256) return 0;
-  return gemm_splitk_scratch_bytes(g);
+  // What callers are told: large results are split only where float sums leave a last round at most half full.  (A step
+  // plans for its own products and also splits bf16 results' last rounds and float results of 128 to 199 large tiles.)
+  const int64_t tiles = ((M + 255) / 256) * ((N + 255) / 256);
+  if (out_dtype == TIDE_DTYPE_BF16 ? tiles >= 256 : tiles >= 128 && tiles < 200) return 0;
+  return out_dtype != TIDE_DTYPE_BF16 && tiles >= 200 ? gemm_split_tail_bytes(g) : gemm_splitk_scratch_bytes(g);
 }
 
 int tide_gemm(int layout, int64_t M, int64_t N, int64_t K, float alpha, const void* A, const void* B, void* C,
