@@ -952,7 +952,16 @@ SplitGrid plan_split_all(const GemmArgs& a, int BT) {
   const int slabs = split_slabs((int)a.K, a.A2 ? (int)a.K2 : 0);
   // with fewer slabs (a K known on the device alone) there are never more parts
   auto at = [&](int tiles) { return BT == 256 ? split_all<256>(tiles, slabs) : split_all<128>(tiles, slabs); };
-  if (at((int)((planned_rows(a) + BT - 1) / BT * tn)).parts < 2) return sp;
+  const int planned = (int)((planned_rows(a) + BT - 1) / BT * tn);
+  const SplitAll sp0 = at(planned);
+  if (sp0.parts < 2) return sp;
+  if (a.m_dev) {
+    // The number of rows may turn out to need no split, and the second launch then costs 5 us for nothing: only where the
+    // split is planned to save twice what it costs.
+    const SplitCost c = split_cost(BT);
+    const int64_t saved = (int64_t)c.slab * (slabs - (slabs + sp0.parts - 1) / sp0.parts);
+    if (saved < 2 * (c.fixed + (int64_t)c.traffic * (planned - sp0.full) * sp0.parts)) return sp;
+  }
   int64_t parts = 0, most = tm * tn;
   for (int64_t t = a.m_dev ? 1 : tm; t <= tm; ++t) {
     const int tiles = (int)(t * tn);
