@@ -394,6 +394,30 @@ __global__ __launch_bounds__(256, blocks_per_cu(D, 4, 2)) void attn_fwd_mfma_ker
 
   const float inv = 1.0f / l;
   stage_out<D>(smem, o, inv, wave, lane);
+  if constexpr (D == 64) {
+    // A masked key has probability zero, but zero times a NaN or an infinity of its V row is a NaN that reaches the earlier
+    // queries of its tile.  Rows that are not finite although their sum is are made again from the keys they see alone,
+    // a channel per lane.  No row of finite inputs is, and 32 multiply-adds per lane and block find out.
+    float z = 0.f;
+#pragma unroll
+    for (int ct = 0; ct < NC; ++ct)
+#pragma unroll
+      for (int q = 0; q < 16; ++q) z = fmaf(o[ct][q], 0.f, z);
+    const uint64_t bad = __builtin_amdgcn_ballot_w64(z != 0.f && l - l == 0.f && iq < S);
+    for (uint32_t rows = (uint32_t)bad | (uint32_t)(bad >> 32); rows != 0; rows &= rows - 1) {   // wave-uniform
+      const int r = __builtin_ctz(rows);
+      const float mr = __shfl(m, r, 64), ir = __shfl(inv, r, 64);
+      const float qv = bf2f(base[(size_t)(qw + r) * ld + h * D + lane]);
+      float acc = 0.f;
+#pragma unroll 1
+      for (int j = 0; j <= qw + r; ++j) {   // below S
+        const bf16_t* row = base + (size_t)j * ld;
+        acc += __builtin_amdgcn_exp2f((wave_sum(qv * bf2f(row[kcol + lane])) - mr) * c) * bf2f(row[vcol + lane]);
+      }
+      asm volatile("" ::: "memory");   // after the wave's own wider stores of the row
+      smem[(wave * 32 + r) * pitch(D) + lane] = f2bf(acc * ir);
+    }
+  }
   if (g == 0 && iq < S) lse[stat_index(cu, T, sv, b, h, nh, Smax, iq)] = m * (1.0f / sqrtf((float)D)) + logf(l);
   __syncthreads();
   copy_out<D>(smem, out, sv.row0 + q0, sv.row0 + min(S, q0 + BQ), nh * D, h * D, tid);
