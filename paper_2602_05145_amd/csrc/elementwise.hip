@@ -459,7 +459,7 @@ hipError_t launch_rmsnorm_fwd(int64_t rows, int d, const void* x, const void* g,
 // evenly over it: one round, no partly filled second.  A block takes 8 rows or more, which keeps its partial sums few beside the
 // rows, unless that would leave fewer than 480 blocks: then the rows are spread over as many (a block walks its rows one
 // after the other, about 1 us each).  us with 8 rows per block / by this rule: 128 x 256 fp32 10.8 / 7.1, 183 x 5120 bf16 18.7 / 10.2,
-// 2000 x 2048 15.5 / 13.7; two rows per block from the start cost 4096 x 2048 25 in place of 19.
+// 2000 x 2048 15.5 / 13.7; from 3361 rows on 480 blocks walk 8 rows as well (3589 x 256 14.0 / 14.2); two rows per block from the start cost 4096 x 2048 25 in place of 19.
 constexpr int kMaxRowsForGrid = 8, kFewBlocks = 480;
 __host__ __device__ inline int rmsnorm_bwd_nit(int d) {
   const bool vec = (d % 8) == 0 && d <= 8192;
@@ -474,7 +474,7 @@ inline int64_t rmsnorm_bwd_blocks(int64_t rows, int d) {
   const int nit = rmsnorm_bwd_nit(d);
   const int64_t cap = 256 * rmsnorm_bwd_resident(2, nit);   // (scratch is sized for the storage type with more of them)
   int64_t want = (rows + kMaxRowsForGrid - 1) / kMaxRowsForGrid;
-  if (want < kFewBlocks) want = rows < kFewBlocks ? rows : kFewBlocks;
+  if (rows <= kFewBlocks * (kMaxRowsForGrid - 1)) want = rows < kFewBlocks ? rows : kFewBlocks;   // (each then walks fewer rows)
   return want < 1 ? 1 : (want < cap ? want : cap);
 }
 
