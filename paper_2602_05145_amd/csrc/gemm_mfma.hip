@@ -957,7 +957,8 @@ SplitGrid plan_split_all(const GemmArgs& a, int BT) {
   if (sp0.parts < 2) return sp;
   if (a.m_dev) {
     // The number of rows may turn out to need no split, and the second launch then costs 5 us for nothing: only where the
-    // split is planned to save twice what it costs.
+    // split is planned to save twice what it costs (8 x 512 bf16 step, times as fast as one fixed older build: 1.101
+    // where it was to save its cost once, 1.115 and 1.118 so; 3 x 1333 evaluation of the 8B-shaped draft 1.018, 1.020).
     const SplitCost c = split_cost(BT);
     const int64_t saved = (int64_t)c.slab * (slabs - (slabs + sp0.parts - 1) / sp0.parts);
     if (saved < 2 * (c.fixed + (int64_t)c.traffic * (planned - sp0.full) * sp0.parts)) return sp;
