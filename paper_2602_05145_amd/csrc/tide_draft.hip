@@ -977,15 +977,20 @@ int tide_draft_train_step_packed(const tide_draft_config* cfg, tide_draft_tensor
 }
 
 // ---- building blocks ---------------------------------------------------------------------------
+// Scratch that a product takes when a program calls it by itself: the size query and the call share this rule, so a call whose
+// size is 0 is never split, however large the buffer that comes with it.  Large results are split only where float sums leave
+// a last round at most half full.  (A step plans for its own products and also splits bf16 results' last rounds and float
+// results of 128 to 199 large tiles.)
+static size_t call_scratch_bytes(const GemmArgs& g) {
+  const int64_t tiles = ((g.M + 255) / 256) * ((g.N + 255) / 256);
+  if (g.out_dtype == kBF16 ? tiles >= 256 : tiles >= 128 && tiles < 200) return 0;
+  return g.out_dtype != kBF16 && tiles >= 200 ? gemm_split_tail_bytes(g) : gemm_splitk_scratch_bytes(g);
+}
+
 size_t tide_gemm_workspace_bytes(int layout, int64_t M, int64_t N, int64_t K, int out_dtype) {
   if (layout < 0 || layout > 2 || M <= 0 || N <= 0 || K <= 0) return 0;
   const int64_t lda = layout == kTN ? M : K, ldb = layout == kNT ? K : N;
-  GemmArgs g = gemm_args(layout, M, N, K, (void*)256, lda, (void*)256, ldb, (void*)256, N, kBF16, out_dtype);
-  // What callers are told: large results are split only where float sums leave a last round at most half full.  (A step
-  // plans for its own products and also splits bf16 results' last rounds and float results of 128 to 199 large tiles.)
-  const int64_t tiles = ((M + 255) / 256) * ((N + 255) / 256);
-  if (out_dtype == TIDE_DTYPE_BF16 ? tiles >= 256 : tiles >= 128 && tiles < 200) return 0;
-  return out_dtype != TIDE_DTYPE_BF16 && tiles >= 200 ? gemm_split_tail_bytes(g) : gemm_splitk_scratch_bytes(g);
+  return call_scratch_bytes(gemm_args(layout, M, N, K, (void*)256, lda, (void*)256, ldb, (void*)256, N, kBF16, out_dtype));
 }
 
 int tide_gemm(int layout, int64_t M, int64_t N, int64_t K, float alpha, const void* A, const void* B, void* C,
@@ -998,7 +1003,9 @@ int tide_gemm(int layout, int64_t M, int64_t N, int64_t K, float alpha, const vo
   const int64_t lda = layout == kTN ? M : K, ldb = layout == kNT ? K : N;
   GemmArgs g = gemm_args(layout, M, N, K, A, lda, B, ldb, C, N, in_dtype, out_dtype);
   g.alpha = alpha; g.residual = residual; g.ldr = N; g.accumulate = accumulate;
-  if (workspace && (((uintptr_t)workspace) & 15) == 0) { g.scratch = workspace; g.scratch_bytes = workspace_bytes; }
+  // (a residual or an unaligned result can only take the split away that the query, which sees neither, allowed for)
+  const size_t need = workspace && (((uintptr_t)workspace) & 15) == 0 ? call_scratch_bytes(g) : 0;
+  if (need > 0 && workspace_bytes >= need) { g.scratch = workspace; g.scratch_bytes = need; }
   TIDE_HIP(launch_gemm(g, (hipStream_t)stream), "gemm");
   return TIDE_OK;
 }

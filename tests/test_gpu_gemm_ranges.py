@@ -117,6 +117,25 @@ def test_large_tiles_split_over_k(B, layout, M, N, K):
         assert float((c.double() - want).abs().max()) < tol * float(want.abs().max())
 
 
+@pytest.mark.parametrize("layout,M,N,K,out", [(0, 4352, 4096, 2048, "bf16"), (1, 4315, 4096, 2056, "bf16"), (2, 4096, 4352, 1999, "fp32"),
+                                              (2, 2048, 4096, 20000, "fp32")])
+def test_a_product_without_workspace_need_leaves_any_workspace_alone(B, layout, M, N, K, out):
+    """A size of 0 says that the call is never split: a large buffer that other products share is neither read nor written,
+    and the result is bit for bit that of the call without one."""
+    assert B.tide_gemm_workspace_bytes(layout, M, N, K, DT[out][0]) == 0
+    g = torch.Generator(device=DEV).manual_seed(M + K)
+    a = torch.randn((K, M) if layout == B.LAYOUT_TN else (M, K), device=DEV, generator=g).bfloat16()
+    b = torch.randn((N, K) if layout == B.LAYOUT_NT else (K, N), device=DEV, generator=g).bfloat16()
+    ws = torch.full((96 << 20,), 0xA5, dtype=torch.uint8, device=DEV)
+    got = [torch.full((M, N), float("nan"), device=DEV, dtype=DT[out][1]) for _ in range(2)]
+    for c, w in zip(got, (ws, None)):
+        print(f"gemm told 0: layout={layout} M={M} N={N} K={K} {out} workspace={w is not None}", flush=True)
+        B.tide_gemm(layout, M, N, K, 1.0, a, b, c, None, 1, DT[out][0], 0, stream(), workspace=w, workspace_bytes=0 if w is None else w.numel())
+        sync()
+    assert bool((ws == 0xA5).all())
+    assert not bool(torch.isnan(got[0]).any()) and torch.equal(got[0], got[1])
+
+
 def test_split_products_of_a_training_step_with_few_kept_rows():
     """The number of rows behind the attention is on the device only: with one sequence in eight carrying loss, the same
     launches come out with other numbers of parts.  Against the oracle."""
