@@ -367,7 +367,8 @@ int tide_gemm(int layout, int64_t M, int64_t N, int64_t K, float alpha,
 int tide_rmsnorm_fwd(int64_t rows, int64_t d, const void *x, const void *g, float eps,
                      void *y, float *rstd_out, int dtype, void *stream);
 /* dx = (residual_grad or 0) + rmsnorm input gradient; dg [d] float (overwritten).
- * dg_partial: DEVICE float scratch of tide_rmsnorm_bwd_scratch_bytes(rows, d). */
+ * dg_partial: DEVICE float scratch of tide_rmsnorm_bwd_scratch_bytes(rows, d).  The size never falls as the rows
+ * grow: a buffer made for some number of rows serves every smaller one of the same d. */
 size_t tide_rmsnorm_bwd_scratch_bytes(int64_t rows, int64_t d);
 int tide_rmsnorm_bwd(int64_t rows, int64_t d, const void *dy, const void *x, const void *g,
                      const float *rstd, const void *residual_grad, void *dx, float *dg,

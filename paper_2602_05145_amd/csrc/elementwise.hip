@@ -640,9 +640,10 @@ hipError_t launch_colsums(const ColSums& cs, int n, int64_t rows, int d, int dty
   return hipGetLastError();
 }
 
+// What the given rows take, or any smaller number of them: 3361 rows are walked by fewer blocks (421) than 3360 (480).
 size_t rmsnorm_bwd_scratch_bytes(int64_t rows, int d) {
-  const int64_t nblk = rmsnorm_bwd_blocks(rows, d);
-  return (size_t)nblk * (size_t)d * sizeof(float);
+  const int64_t most_of_few = rmsnorm_bwd_blocks(rows < kFewBlocks ? rows : kFewBlocks, d), n = rmsnorm_bwd_blocks(rows, d);
+  return (size_t)(n > most_of_few ? n : most_of_few) * (size_t)d * sizeof(float);
 }
 
 hipError_t launch_rmsnorm_bwd(int64_t rows, int d, const void* dy, const void* x, const void* g,

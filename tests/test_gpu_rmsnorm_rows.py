@@ -43,3 +43,21 @@ def test_rmsnorm_forward_of_wide_rows():
     sync()
     want = x.double() * torch.rsqrt(x.double().square().mean(-1, keepdim=True) + 1e-5) * gain.double()
     assert float((y.double() - want).abs().max()) < 1e-5 * float(want.abs().max())
+
+
+def test_rmsnorm_backward_of_fewer_rows_than_its_scratch_was_made_for():
+    """3500 rows are walked by fewer blocks than 1000: the buffer made for them serves both, and nothing past it is written."""
+    d, made_for = 264, 3500
+    size = B.tide_rmsnorm_bwd_scratch_bytes(made_for, d)
+    buf = torch.full((size + 64 * 1024,), 0xA5, dtype=torch.uint8, device=DEV)
+    for rows in (3500, 1000, 479):
+        x, dy = (torch.randn(rows, d, device=DEV) for _ in range(2))
+        gain = torch.ones(d, device=DEV)
+        y, dx, rstd, dg = torch.empty_like(x), torch.empty_like(x), torch.empty(rows, device=DEV), torch.empty(d, device=DEV)
+        print(f"rmsnorm scratch of {made_for} rows, rows={rows}", flush=True)
+        B.tide_rmsnorm_fwd(rows, d, x, gain, 1e-5, y, rstd, 0, stream())
+        B.tide_rmsnorm_bwd(rows, d, dy, x, gain, rstd, None, dx, dg, buf, 0, stream())
+        sync()
+        want = (dy.double() * x.double() * torch.rsqrt(x.double().square().mean(-1, keepdim=True) + 1e-5)).sum(0)
+        assert float((dg.double() - want).abs().max()) < 1e-5 * float(want.abs().max())
+        assert bool((buf[size:] == 0xA5).all())
