@@ -324,7 +324,8 @@ const char *tide_last_error(void);
  * with this config ("x0", "a", "qkv", "A", "x1", "bn", "gt", "u", "h", "x2",
  * "yhat", "lse", "dyhat", "dx2", "dx1", "dx0", "dqkv", ...; activations have the
  * config's dtype, "lse"/"r1"/"r2"/"r3" are float); "lm_rows" returns the number
- * of rows per logits block instead.  -1 if the name or config is unknown.  After
+ * of rows per logits block instead, "splitk_bytes" the size of the scratch of split
+ * products ("splitk").  -1 if the name or config is unknown.  After
  * a training step "gt"/"u" hold their gradients.  For tests and profiling.
  * Rows: a position without loss acts on the result only through its key and value, so everything after the
  * attention runs on the selected positions alone (those with loss; every position when top1_out is given).

@@ -33,6 +33,8 @@
 //   * Work-groups are renumbered so that each of the 8 XCDs (round-robin dispatch) gets a contiguous
 //     range of tiles, walked in groups of 4 tile-rows: neighbouring tiles share A/B panels in that
 //     XCD's L2.
+#include <algorithm>
+#include <cmath>
 #include <type_traits>
 #include <utility>
 
@@ -980,6 +982,32 @@ SplitGrid plan_split_all(const GemmArgs& a, int BT) {
   return sp;
 }
 }  // namespace
+
+// Tiles of edge BT that hold partial sums (a tile's parts times the tiles), at most, of a launch of up to `tiles` tiles and
+// `slabs` slabs: split_parts gives n parts to t tiles only with t n <= slots, n <= slabs / min_slabs, traffic t n^2 <= slab
+// slabs (so that t n <= sqrt(slab slabs t / traffic)) and where the slabs saved are worth the fixed costs.
+static int64_t split_tiles_bound(int BT, int64_t tiles, int slabs) {
+  const SplitCost c = split_cost(BT);
+  const int64_t by_k = slabs / c.min_slabs, t = std::min<int64_t>(tiles, c.slots / 2), work = (int64_t)c.slab * slabs;
+  if (by_k < 2 || work <= c.fixed) return 0;
+  int64_t root = (int64_t)std::sqrt((double)(work * t / c.traffic));
+  while ((root + 1) * (root + 1) <= work * t / c.traffic) ++root;
+  while (root * root > work * t / c.traffic) --root;
+  return std::min(std::min<int64_t>(c.slots, t * by_k), root);
+}
+
+size_t gemm_splitk_scratch_bound(const GemmArgs& a) {
+  if (!gemm_mfma_supported(a)) return 0;
+  size_t bytes = 0;
+  const int slabs = split_slabs((int)a.K, a.A2 ? (int)a.K2 : 0);
+  if (split_possible(a))
+    for (const int BT : {128, 256})
+      bytes = std::max(bytes, (size_t)split_tiles_bound(BT, tile_count(a.M, a.N, BT), slabs) * BT * BT * sizeof(float));
+  if (a.layout == kTN) return std::max(bytes, plan_split(a).bytes);   // (the number of parts grows with K)
+  if (a.out_dtype != kF32 || tile_count(a.M, a.N, 256) < 200) return bytes;
+  const int s = (int)std::min<int64_t>(8, (a.K + 31) / 32 / 32);      // plan_split's parts: s - 1 sums of each of up to 256 / s tiles
+  return s < 2 ? bytes : std::max(bytes, (size_t)(256 - 256 / s) * 65536 * sizeof(float));
+}
 
 size_t gemm_split_tail_bytes(const GemmArgs& a) { return gemm_mfma_supported(a) ? plan_split(a).bytes : 0; }
 size_t gemm_splitk_scratch_bytes(const GemmArgs& a) {

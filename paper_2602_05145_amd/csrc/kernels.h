@@ -40,6 +40,8 @@ struct GemmArgs {
 bool gemm_mfma_supported(const GemmArgs& a);
 size_t gemm_split_tail_bytes(const GemmArgs& a);       // the part of it that goes into a partly filled last round of float results
 size_t gemm_splitk_scratch_bytes(const GemmArgs& a);   // 0 when the launch would not be split
+// At least what the product asks for with any number of rows (M, of TN K) up to the given one; never falls as the rows grow.
+size_t gemm_splitk_scratch_bound(const GemmArgs& a);
 hipError_t launch_gemm_mfma(const GemmArgs& a, hipStream_t s);
 hipError_t launch_gemm_fp32(const GemmArgs& a, hipStream_t s);     // fp32 operands and result
 hipError_t launch_gemm_simple(const GemmArgs& a, hipStream_t s);

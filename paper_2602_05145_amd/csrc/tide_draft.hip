@@ -75,7 +75,7 @@ struct Plan {
   size_t scal, adam_dyn, cnt, status, plan_cnt, kept_idx, row_pos, tokens_c, mask_c, mask_eff, seq_pos, rope_cs, x0, r1, a, qkv, attn_lse, A, A_c, x0_c, x1, r2, bn, gt, u, h, x2, r3, yhat, lse, loss_rows, hit_rows, z;
   size_t fwd_end;
   size_t dyhat, dx2, dx1_c, dx1, dx0, dh, dbn, dA_c, dA, dqkv, da, delta, dg_partial[3];
-  size_t splitk; size_t splitk_bytes;   // scratch of the weight-gradient products whose last tile round is split over K
+  size_t splitk; size_t splitk_bytes;   // scratch of the products that are split over K (one at a time)
   size_t g0, e0, dg0;   // token-input variant: projected features, looked-up embeddings, gradient of the features
   size_t total;
 };
@@ -177,30 +177,30 @@ Plan make_plan(const tide_draft_config* c) {
   p.da = bwd_take(T * p.d * es);
   p.dg0 = bwd_take(T * p.d * es);
   p.delta = bwd_take((size_t)c->batch * c->n_heads * c->seq * 4);
-  for (auto& o : p.dg_partial) o = bwd_take(rmsnorm_bwd_scratch_bytes(p.T, (int)p.d));   // one per norm
+  // one per norm (not in the logit buffer: for few rows they are large beside it, and would fit it for one row count and not for
+  // the one before, so that the workspace shrank as the batch grows)
+  for (auto& o : p.dg_partial) o = b.take(rmsnorm_bwd_scratch_bytes(p.T, (int)p.d));
   {
-    // the largest split-K scratch any product of this configuration asks for
+    // the largest split-K scratch that any product of this configuration asks for, over all T rows or a block of them (a block
+    // can ask for more than all of them, which fill the chip by themselves); it never falls as T grows
     size_t need = 0;
-    auto ask = [&](int layout, int64_t M, int64_t N, int64_t K, int64_t K2, int64_t lda, int64_t ldb, int64_t ldc, bool rows_on_device) {
+    auto ask = [&](int layout, int64_t M, int64_t N, int64_t K, int64_t K2, int64_t lda, int64_t ldb, int64_t ldc) {
       GemmArgs g;
       std::memset(&g, 0, sizeof(g));
       g.layout = layout; g.M = M; g.N = N; g.K = K; g.K2 = K2; g.lda = lda; g.ldb = ldb; g.ldc = ldc;
       g.in_dtype = c->dtype == TIDE_DTYPE_BF16 ? kBF16 : kF32; g.out_dtype = layout == kTN ? kF32 : g.in_dtype;
       g.A = g.B = g.C = (void*)256;   // alignment only
       if (K2) g.A2 = g.B2 = (void*)256;
-      if (rows_on_device) g.m_dev = (const int*)256;
-      const size_t n = gemm_splitk_scratch_bytes(g);
-      if (n > need) need = n;
+      need = std::max(need, gemm_splitk_scratch_bound(g));
     };
     // weight gradients
     const int64_t dw[7][3] = {{p.V, p.d, p.ldz}, {p.d, p.F, p.d}, {p.F, p.d, p.F}, {p.d, p.nq, p.d}, {p.nqkv, p.d, p.nqkv}, {p.d, p.KH, p.d}, {p.d, p.d, p.d}};
-    for (auto& sh : dw) ask(kTN, sh[0], sh[1], p.T, 0, sh[2], sh[1], sh[1], false);
-    // forward products and input gradients: over all rows, or over the selected ones (their number is on the device; what
-    // T rows ask for then covers every smaller row block of the LM head)
-    const int64_t fwd[7][4] = {{p.d, p.KH, 0, 0}, {p.d, p.d, p.d, 0}, {p.nqkv, p.d, 0, 0}, {p.d, p.nq, 0, 1}, {p.F, p.d, 0, 1}, {p.d, p.F, 0, 1}, {p.V, p.d, 0, 1}};
-    for (auto& sh : fwd) ask(kNT, p.T, sh[0], sh[1], sh[2], sh[1], sh[2] ? 2 * p.d : sh[1], sh[0] == p.V ? p.ldz : sh[0], sh[3] != 0);
-    const int64_t dx[6][4] = {{p.d, p.V, 0, 1}, {p.F, p.d, 0, 1}, {p.d, p.F, p.F, 1}, {p.nq, p.d, 0, 1}, {p.d, p.nqkv, 0, 0}, {p.d, p.d, 0, 0}};
-    for (auto& sh : dx) ask(kNN, p.T, sh[0], sh[1], sh[2], sh[1] == p.V ? p.ldz : sh[1], sh[0], sh[0], sh[3] != 0);
+    for (auto& sh : dw) ask(kTN, sh[0], sh[1], p.T, 0, sh[2], sh[1], sh[1]);
+    // forward products and input gradients
+    const int64_t fwd[7][3] = {{p.d, p.KH, 0}, {p.d, p.d, p.d}, {p.nqkv, p.d, 0}, {p.d, p.nq, 0}, {p.F, p.d, 0}, {p.d, p.F, 0}, {p.V, p.d, 0}};
+    for (auto& sh : fwd) ask(kNT, p.T, sh[0], sh[1], sh[2], sh[1], sh[2] ? 2 * p.d : sh[1], sh[0] == p.V ? p.ldz : sh[0]);
+    const int64_t dx[6][3] = {{p.d, p.V, 0}, {p.F, p.d, 0}, {p.d, p.F, p.F}, {p.nq, p.d, 0}, {p.d, p.nqkv, 0}, {p.d, p.d, 0}};
+    for (auto& sh : dx) ask(kNN, p.T, sh[0], sh[1], sh[2], sh[1] == p.V ? p.ldz : sh[1], sh[0], sh[0]);
     p.splitk_bytes = need;
     p.splitk = b.take(need ? need : 16);
   }
@@ -480,10 +480,11 @@ int64_t tide_draft_workspace_offset(const tide_draft_config* cfg, const char* na
       {"A", p.A}, {"x1", p.x1}, {"r2", p.r2}, {"bn", p.bn}, {"gt", p.gt}, {"u", p.u}, {"h", p.h},
       {"x2", p.x2}, {"r3", p.r3}, {"yhat", p.yhat}, {"lse", p.lse}, {"loss_rows", p.loss_rows}, {"z", p.z},
       {"dyhat", p.dyhat}, {"A_c", p.A_c}, {"x0_c", p.x0_c}, {"dx1_c", p.dx1_c}, {"dA_c", p.dA_c}, {"row_pos", p.row_pos}, {"cnt", p.cnt}, {"kept_idx", p.kept_idx}, {"dx2", p.dx2}, {"dx1", p.dx1}, {"dx0", p.dx0}, {"dh", p.dh}, {"dbn", p.dbn},
-      {"dA", p.dA}, {"dqkv", p.dqkv}, {"da", p.da}, {"g0", p.g0}, {"e0", p.e0}, {"dg0", p.dg0}};
+      {"dA", p.dA}, {"dqkv", p.dqkv}, {"da", p.da}, {"g0", p.g0}, {"e0", p.e0}, {"dg0", p.dg0}, {"splitk", p.splitk}};
   for (auto& e : tab)
     if (std::strcmp(e.n, name) == 0) return (int64_t)e.o;
   if (std::strcmp(name, "lm_rows") == 0) return p.lm_rows;
+  if (std::strcmp(name, "splitk_bytes") == 0) return (int64_t)p.splitk_bytes;
   return -1;
 }
 
