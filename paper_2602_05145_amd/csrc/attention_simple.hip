@@ -72,12 +72,13 @@ struct Geo {
 };
 
 // the wave's columns of the second product: acc[t] += X[16 x 64] Y[64 x 16 columns], X from the exchange in LDS, Y's rows
-// r0 .. r0 + 63 from memory (zeros from row `rows` on).  first: the last of Y's rows that row 0 of X may see, row r seeing r
-// more; a probability past that is zero, but zero times a later position's infinity or NaN is not, so a tile on the
-// diagonal that holds one is summed element by element.
+// r0 .. r0 + 63 from memory (zeros from row `rows` on).  Row q of X may see Y's rows from + q .. upto + q only (causality,
+// from either side).  What X holds for the others is zero, but zero times a NaN or an infinity of such a row is not: where a sum
+// over a tile on the diagonal is not finite, it is made again element by element.
+constexpr int kNoBound = 0x7fffff00;
 template <int NCT, typename T>
 __device__ __forceinline__ void second_product(const Geo& z, const float* x, const T* y, size_t ld, int r0, int rows, int dh, f32x4_t (&acc)[NCT],
-                                               int first = 0x7fffff00) {
+                                               int from, int upto) {
 #pragma unroll
   for (int t = 0; t < NCT; ++t) {
     const int col = (z.wave + 4 * t) * 16 + z.lr;
@@ -86,25 +87,25 @@ __device__ __forceinline__ void second_product(const Geo& z, const float* x, con
     for (int grp = 0; grp < 4; ++grp)
 #pragma unroll
       for (int e = 0; e < 4; ++e) {
+        // (always a load, of the last row or column at most: a branch per load lets the compiler wait between them)
         const int r = r0 + grp * 16 + 4 * z.g + e;
-        v[grp][e] = (r < rows && col < dh) ? ldf(y, (size_t)r * ld + col) : 0.f;
+        const float f = ldf(y, (size_t)min(r, rows - 1) * ld + min(col, dh - 1));
+        v[grp][e] = (r < rows && col < dh) ? f : 0.f;
       }
-    if (r0 + BT - 1 > first) {   // block-uniform
-      bool odd = false;
+    f32x4_t sum = acc[t];
 #pragma unroll
-      for (int grp = 0; grp < 4; ++grp)
-#pragma unroll
-        for (int e = 0; e < 4; ++e) odd |= !(fabsf(v[grp][e]) <= 3.4028235e38f);
-      if (__builtin_amdgcn_ballot_w64(odd) != 0) {
+    for (int grp = 0; grp < 4; ++grp) sum = mma16(*reinterpret_cast<const f32x4_t*>(x + z.lr * PP + grp * 16 + 4 * z.g), v[grp], sum);
+    if (r0 + BT - 1 > upto || r0 < from + BR - 1) {   // block-uniform
+      const float odd = fmaf(sum[0], 0.f, sum[1] * 0.f) + fmaf(sum[2], 0.f, sum[3] * 0.f);
+      if (__builtin_amdgcn_ballot_w64(odd != 0.f) != 0) {
         if (col < dh)
           for (int q = 0; q < 4; ++q)
-            for (int r = r0; r <= min(min(first + 4 * z.g + q, rows - 1), r0 + BT - 1); ++r)
+            for (int r = max(r0, from + 4 * z.g + q); r <= min(min(upto + 4 * z.g + q, rows - 1), r0 + BT - 1); ++r)
               acc[t][q] = fmaf(x[(4 * z.g + q) * PP + r - r0], ldf(y, (size_t)r * ld + col), acc[t][q]);
         continue;
       }
     }
-#pragma unroll
-    for (int grp = 0; grp < 4; ++grp) acc[t] = mma16(*reinterpret_cast<const f32x4_t*>(x + z.lr * PP + grp * 16 + 4 * z.g), v[grp], acc[t]);
+    acc[t] = sum;
   }
 }
 
@@ -175,7 +176,7 @@ __global__ __launch_bounds__(256) void attn_fwd_simple_kernel(const T* __restric
       ps[st][r * PP + z.wave * 16 + z.lr] = p;
     }
     __syncthreads();   // (the other buffer is written next: its readers pass this barrier first)
-    second_product<NCT>(z, ps[st], V, ld, j0, S, dh, o, i0);
+    second_product<NCT>(z, ps[st], V, ld, j0, S, dh, o, -kNoBound, i0);
   }
   __syncthreads();
 #pragma unroll
@@ -258,7 +259,7 @@ __global__ __launch_bounds__(256) void attn_dq_simple_kernel(const T* __restrict
       ps[st][(4 * z.g + q) * PP + z.wave * 16 + z.lr] = (j <= i && i < S) ? __expf(s[q] - L[q]) * (dp[q] - D[q]) : 0.f;
     }
     __syncthreads();   // (a buffer is written again two tiles on: its readers pass the barrier in between first)
-    second_product<NCT>(z, ps[st], K, ld, j0, S, dh, dq);
+    second_product<NCT>(z, ps[st], K, ld, j0, S, dh, dq, -kNoBound, i0);
   }
 #pragma unroll
   for (int q = 0; q < 4; ++q) {
@@ -324,8 +325,8 @@ __global__ __launch_bounds__(256) void attn_dkv_simple_kernel(const T* __restric
       *reinterpret_cast<f32x4_t*>(&ps[st][z.lr * PP + z.wave * 16 + 4 * z.g]) = p;
       *reinterpret_cast<f32x4_t*>(&ds[st][z.lr * PP + z.wave * 16 + 4 * z.g]) = d;
       __syncthreads();   // (as in the dQ kernel)
-      second_product<NCT>(z, ps[st], dO, ldo, i0, S, dh, dv);
-      second_product<NCT>(z, ds[st], Q, ld, i0, S, dh, dk);
+      second_product<NCT>(z, ps[st], dO, ldo, i0, S, dh, dv, j0, kNoBound);
+      second_product<NCT>(z, ds[st], Q, ld, i0, S, dh, dk, j0, kNoBound);
     }
   }
 #pragma unroll
