@@ -209,6 +209,18 @@ __device__ __forceinline__ void copy_out(const bf16_t* tile, bf16_t* dst, int64_
   }
 }
 
+// which of the wave's 32 output rows (held as for stage_out) hold something that is not finite; `ask`: this lane's row counts
+template <int NC>
+__device__ __forceinline__ uint32_t not_finite(const f32x16_t (&acc)[NC], bool ask) {
+  float z[4] = {0.f, 0.f, 0.f, 0.f};   // four chains: the sum is on the way to the store
+#pragma unroll
+  for (int ct = 0; ct < NC; ++ct)
+#pragma unroll
+    for (int q = 0; q < 16; ++q) z[q & 3] = fmaf(acc[ct][q], 0.f, z[q & 3]);
+  const uint64_t rows = __builtin_amdgcn_ballot_w64((z[0] + z[1]) + (z[2] + z[3]) != 0.f && ask);
+  return (uint32_t)rows | (uint32_t)(rows >> 32);
+}
+
 constexpr int BQ = 128, BKV = 64;
 constexpr int kv_tile(int D) { return BKV * pitch(D); }  // elements
 
@@ -398,13 +410,7 @@ __global__ __launch_bounds__(256, blocks_per_cu(D, 4, 2)) void attn_fwd_mfma_ker
     // A masked key has probability zero, but zero times a NaN or an infinity of its V row is a NaN that reaches the earlier
     // queries of its tile.  Rows that are not finite although their sum is are made again from the keys they see alone,
     // a channel per lane.  No row of finite inputs is, and 32 multiply-adds per lane and block find out.
-    float z = 0.f;
-#pragma unroll
-    for (int ct = 0; ct < NC; ++ct)
-#pragma unroll
-      for (int q = 0; q < 16; ++q) z = fmaf(o[ct][q], 0.f, z);
-    const uint64_t bad = __builtin_amdgcn_ballot_w64(z != 0.f && l - l == 0.f && iq < S);
-    for (uint32_t rows = (uint32_t)bad | (uint32_t)(bad >> 32); rows != 0; rows &= rows - 1) {   // wave-uniform
+    for (uint32_t rows = not_finite(o, l - l == 0.f && iq < S); rows != 0; rows &= rows - 1) {   // wave-uniform
       const int r = __builtin_ctz(rows);
       const float mr = __shfl(m, r, 64), ir = __shfl(inv, r, 64);
       const float qv = bf2f(base[(size_t)(qw + r) * ld + h * D + lane]);
@@ -564,6 +570,26 @@ __global__ __launch_bounds__(256, blocks_per_cu(D, 3, 2)) void attn_dq_mfma_kern
     __syncthreads();
   }
   stage_out<D>(smem, dq, scale, wave, lane);
+  if constexpr (D == 64) {
+    // as in the forward kernel: a later key of the tile that is not finite
+    const uint32_t again = not_finite(dq, valid && lse_i - lse_i == 0.f && del_i - del_i == 0.f);
+    for (uint32_t rows = again; rows != 0; rows &= rows - 1) {   // wave-uniform
+      const int r = __builtin_ctz(rows);
+      const float L = __shfl(lse_i, r, 64), De = __shfl(del_i, r, 64);
+      const bf16_t* base = qkv + (size_t)sv.row0 * ld;
+      const float qv = bf2f(base[(size_t)(qw + r) * ld + h * D + lane]), dov = bf2f(dout[((size_t)sv.row0 + qw + r) * ldo + h * D + lane]);
+      float acc = 0.f;
+#pragma unroll 1
+      for (int j = 0; j <= qw + r; ++j) {   // below S
+        const bf16_t* row = base + (size_t)j * ld;
+        const float kv = bf2f(row[kcol + lane]), p = __builtin_amdgcn_exp2f(wave_sum(qv * kv) * c - L);
+        acc += p * (wave_sum(dov * bf2f(row[vcol + lane])) - De) * kv;
+        if (__builtin_amdgcn_ballot_w64(acc - acc == 0.f) == 0) break;
+      }
+      asm volatile("" ::: "memory");   // after the wave's own wider stores of the row
+      smem[(wave * 32 + r) * pitch(D) + lane] = f2bf(acc * scale);
+    }
+  }
   __syncthreads();
   copy_out<D>(smem, dqkv, sv.row0 + q0, sv.row0 + min(S, q0 + BQ), ld, h * D, tid);
 }
@@ -777,7 +803,44 @@ __global__ __launch_bounds__(KW * NS * 64, NS > 1 ? 1 : WHICH == 0 ? blocks_per_
     }
   }
   const int64_t r0 = sv.row0 + j0, r1 = sv.row0 + min(S, j0 + KB);
-  if (set == 0) stage_out<D>(smem, dacc, DK ? scale : 1.0f, wave, lane);
+  if (set == 0) {
+    stage_out<D>(smem, dacc, DK ? scale : 1.0f, wave, lane);
+    if constexpr (D == 64) {
+      // As in the forward kernel, from the other side: the queries jw .. j - 1 meet key j with weight zero.  Keys after the
+      // first of them that is not finite are made again from the queries that see them alone (a later query takes every
+      // key before it with it, rightly).
+      uint32_t rows = not_finite(dacc, jk < S);
+      const bf16_t *base = qkv + (size_t)sv.row0 * ld, *dob = dout + (size_t)sv.row0 * ldo;
+      if (rows != 0) {   // wave-uniform
+        int first = 31;
+#pragma unroll 1
+        for (int i = 0; i < first && jw + i < S; ++i) {
+          float odd = 0.f;
+          for (int hh = kh * G; hh < (kh + 1) * G; ++hh)
+            odd += 0.f * (bf2f(base[(size_t)(jw + i) * ld + hh * D + lane]) + bf2f(dob[(size_t)(jw + i) * ldo + hh * D + lane]) +
+                          delta[stat_index(cu, T, sv, b, hh, nh, Smax, jw + i)]);
+          if (__builtin_amdgcn_ballot_w64(odd != 0.f) != 0) first = i;
+        }
+        rows &= first == 31 ? 0u : ~((2u << first) - 1u);
+      }
+      for (; rows != 0; rows &= rows - 1) {
+        const int r = __builtin_ctz(rows), j = jw + r;
+        const float kv = bf2f(base[(size_t)j * ld + kcol + lane]), vv = bf2f(base[(size_t)j * ld + vcol + lane]);
+        float acc = 0.f;
+        for (int hh = kh * G; hh < (kh + 1) * G && __builtin_amdgcn_ballot_w64(acc - acc == 0.f) != 0; ++hh)
+#pragma unroll 1
+          for (int i = j; i < S; ++i) {
+            const float qv = bf2f(base[(size_t)i * ld + hh * D + lane]), dov = bf2f(dob[(size_t)i * ldo + hh * D + lane]);
+            const size_t at = stat_index(cu, T, sv, b, hh, nh, Smax, i);
+            const float p = __builtin_amdgcn_exp2f(wave_sum(qv * kv) * c - lse[at] * kLog2e);
+            acc += DK ? p * (wave_sum(dov * vv) - delta[at]) * qv : p * dov;
+            if (__builtin_amdgcn_ballot_w64(acc - acc == 0.f) == 0) break;
+          }
+        asm volatile("" ::: "memory");   // after the wave's own wider stores of the row
+        smem[(wave * 32 + r) * pitch(D) + lane] = f2bf(DK ? acc * scale : acc);
+      }
+    }
+  }
   __syncthreads();
   copy_out<D, KB, SET * NS>(smem, dqkv, r0, r1, ld, DK ? kcol : vcol, threadIdx.x);
 }

@@ -147,31 +147,30 @@ def test_later_positions_reach_nothing_before_them(B, bf16):
     assert bool(torch.isfinite(got[1]).all()) and bool(((got[0] - got[1]).abs() <= (2 ** -7 * got[0].abs() if bf16 else 0) + 1e-5).all())
 
 
-@pytest.mark.parametrize("dtype,dh", [("fp32", 64), ("fp32", 80), ("bf16", 80)])
-def test_no_position_reaches_a_gradient_it_has_no_part_in(B, dtype, dh):
+@pytest.mark.parametrize("dtype,dh,bt", [("fp32", 64, 1), ("fp32", 80, 1), ("bf16", 80, 1), ("bf16", 64, 1), ("bf16", 64, 70)])
+def test_no_position_reaches_a_gradient_it_has_no_part_in(B, dtype, dh, bt):
     """Causality of the backward pass where values are not finite: from a later key, value or query nothing reaches the query
     gradients of the positions before it, and from an earlier query or output gradient nothing the key and value gradients
-    of the positions after it.  Other tiles than the clean ones sum in another order: 1e-5 of the largest value in fp32, one
-    step of the type (2^-7) on top in bf16."""
+    of the positions after it.  (70 sequences: the four-wave form of the matrix-instruction dK / dV passes.)  Other tiles than
+    the clean ones sum in another order: 1e-5 of the largest value in fp32, one step of the type (2^-7) on top in bf16."""
     S, nh, nkv, dt = 100, 4, 2, torch.bfloat16 if dtype == "bf16" else torch.float32
     code, cut = int(dtype == "bf16"), 50
     g = torch.Generator(device=DEV).manual_seed(dh)
-    qkv = torch.randn(S, (nh + 2 * nkv) * dh, device=DEV, generator=g).to(dt)
-    dout = torch.randn(S, nh * dh, device=DEV, generator=g).to(dt)
-    out, lse = torch.empty_like(dout), torch.empty(1, nh, S, device=DEV)
-    B.tide_attention_fwd(1, S, nh, nkv, dh, qkv, out, lse, code, stream())
+    qkv = torch.randn(S, (nh + 2 * nkv) * dh, device=DEV, generator=g).to(dt).repeat(bt, 1)
+    dout = torch.randn(S, nh * dh, device=DEV, generator=g).to(dt).repeat(bt, 1)
+    out, lse = torch.empty_like(dout), torch.empty(bt, nh, S, device=DEV)
+    B.tide_attention_fwd(bt, S, nh, nkv, dh, qkv, out, lse, code, stream())
     sync()
 
     def backward(bad, what):
-        t = [x.clone() for x in (qkv, out, dout, lse)]
+        q, o, do, l = (x.clone() for x in (qkv.view(bt, S, -1), out.view(bt, S, -1), dout.view(bt, S, -1), lse))
         if bad is not None:
-            t[0][bad], t[1][bad], t[2][bad], t[3][..., bad] = (float("nan"),) * 4
-            odd = torch.arange(S, device=DEV)[bad][1::2]
-            t[0][odd, 3:9] = float("inf")
-            t[2][odd, -9:] = float("-inf")
-        dqkv, delta = torch.empty_like(qkv), torch.empty_like(lse)
-        print(f"attention backward {dtype} dh={dh} {what}", flush=True)
-        B.tide_attention_bwd(1, S, nh, nkv, dh, t[0], t[1], t[2], t[3], delta, dqkv, code, stream())
+            q[:, bad], o[:, bad], do[:, bad], l[:, :, bad] = (float("nan"),) * 4
+            q[:, bad[1::2], 3:9] = float("inf")
+            do[:, bad[1::2], -9:] = float("-inf")
+        dqkv, delta = torch.empty_like(q), torch.empty_like(l)
+        print(f"attention backward {dtype} dh={dh} batch={bt} {what}", flush=True)
+        B.tide_attention_bwd(bt, S, nh, nkv, dh, q, o, do, l, delta, dqkv, code, stream())
         sync()
         return dqkv.float()
 
@@ -179,8 +178,8 @@ def test_no_position_reaches_a_gradient_it_has_no_part_in(B, dtype, dh):
         assert bool(torch.isfinite(a).all())
         assert bool(((a - b).abs() <= (2.0 ** -7 * b.abs() if code else 0) + 1e-5 * b.abs().max()).all())
 
-    clean, w = backward(None, "clean"), nh * dh
-    later, earlier = backward(slice(cut, None), "later"), backward(slice(0, cut), "earlier")
-    same(later[:cut, :w], clean[:cut, :w])
-    same(earlier[cut:, w:], clean[cut:, w:])
-    assert bool(torch.isnan(later[cut:, :w]).all()) and bool(torch.isnan(earlier[:cut, w:]).all())
+    at, w, clean = torch.arange(S, device=DEV), nh * dh, backward(None, "clean")
+    later, earlier = backward(at[cut:], "later"), backward(at[:cut], "earlier")
+    same(later[:, :cut, :w], clean[:, :cut, :w])
+    same(earlier[:, cut:, w:], clean[:, cut:, w:])
+    assert bool(torch.isnan(later[:, cut:, :w]).all()) and bool(torch.isnan(earlier[:, :cut, w:]).all())
