@@ -5,6 +5,7 @@ the magnitudes; the observed error grows with sqrt(K), and 2e-5 of the largest r
 import pytest
 import torch
 
+from tests import internal_gemm as ig
 from tests.gpu_util import DEV, stream, sync
 
 pytestmark = pytest.mark.gpu
@@ -12,7 +13,7 @@ pytestmark = pytest.mark.gpu
 DT = {"fp32": (0, torch.float32), "bf16": (1, torch.bfloat16)}
 
 
-def _operands(B, layout, M, N, K, dtype, seed, pad=0):
+def _operands(B, layout, M, N, K, dtype, seed):
     g = torch.Generator(device=DEV).manual_seed(seed)
     shape_a = (K, M) if layout == B.LAYOUT_TN else (M, K)
     shape_b = (N, K) if layout == B.LAYOUT_NT else (K, N)
@@ -132,8 +133,71 @@ def test_a_product_without_workspace_need_leaves_any_workspace_alone(B, layout, 
         print(f"gemm told 0: layout={layout} M={M} N={N} K={K} {out} workspace={w is not None}", flush=True)
         B.tide_gemm(layout, M, N, K, 1.0, a, b, c, None, 1, DT[out][0], 0, stream(), workspace=w, workspace_bytes=0 if w is None else w.numel())
         sync()
-    assert bool((ws == 0xA5).all())
-    assert not bool(torch.isnan(got[0]).any()) and torch.equal(got[0], got[1])
+    untouched, finite, same = bool((ws == 0xA5).all()), not bool(torch.isnan(got[0]).any()), torch.equal(got[0], got[1])
+    assert untouched and finite and same     # (plain values: a failing assertion prints the tensors it names)
+
+
+def _launch(what, g):
+    print(f"internal gemm {what}: layout={g.layout} M={g.M} N={g.N} K={g.K}+{g.K2} out={g.out_dtype} scratch={g.scratch_bytes}", flush=True)
+    assert ig.launch(g, stream()) == 0
+    sync()
+
+
+@pytest.mark.parametrize("layout,M,N,K,pair", [(0, 4315, 4096, 2056, 0), (1, 4352, 4088, 2048, 1), (2, 4344, 4096, 4099, 0), (0, 8450, 4096, 2048, 0)])
+@pytest.mark.parametrize("out", ["bf16", "fp32"])
+def test_only_the_last_round_of_large_tiles_split(layout, M, N, K, pair, out):
+    """256 or 512 whole tiles and a few more, as a training step launches them: the whole ones first, the parts of the others
+    behind them, and the sums in a second launch with the residual (and, of bf16, the old values).  Ragged M, N and K, one and
+    two operand pairs.  fp32 results without a residual have a split of their own."""
+    dt = DT[out][1]
+    g = torch.Generator(device=DEV).manual_seed(M + N)
+    a, a2 = (torch.randn((K, M) if layout == ig.TN else (M, K), device=DEV, generator=g).bfloat16() for _ in range(2))
+    b, b2 = (torch.randn((N, K) if layout == ig.NT else (K, N), device=DEV, generator=g).bfloat16() for _ in range(2))
+    res, c0 = (torch.randn(M, N, device=DEV, generator=g).to(dt) for _ in range(2))
+
+    def product(x, y):
+        x, y = x.double(), y.double()
+        return (x.t().contiguous() if layout == ig.TN else x) @ (y.t().contiguous() if layout == ig.NT else y)
+
+    want = -0.5 * (product(a, b) + (product(a2, b2) if pair else 0.0)) + res.double() + (c0.double() if out == "bf16" else 0.0)
+    ws, got = torch.full((64 << 20,), 0xFF, dtype=torch.uint8, device=DEV), []     # NaN patterns
+    for split in (True, False):
+        c = c0.clone()
+        p = ig.args(layout, M, N, K, out=DT[out][0], K2=K if pair else 0, a=a.data_ptr(), b=b.data_ptr(), c=c.data_ptr(), alpha=-0.5,
+                    residual=res.data_ptr(), ldr=N, accumulate=int(out == "bf16"))
+        if pair:
+            p.A2, p.B2 = a2.data_ptr(), b2.data_ptr()
+        if split:
+            p.scratch, p.scratch_bytes = ws.data_ptr(), ws.numel()
+            tail = -(-M // 256) * -(-N // 256) % 256
+            need = ig.scratch_bytes(p)
+            assert need > 0 and need % (tail * 262144) == 0 and need // (tail * 262144) >= 2    # two parts or more of the last tiles alone
+        _launch("last round", p)
+        got.append(c.double())
+        assert float((got[-1] - want).abs().max()) < (2e-5 if out == "fp32" else 6e-3) * float(want.abs().max())
+    same = torch.equal(got[0], got[1])
+    assert not same                             # the split happened: another order of the sums
+
+
+@pytest.mark.parametrize("m_off", [0, 640])
+def test_last_round_of_a_row_count_known_on_the_device(m_off):
+    """The same launch, planned for 85 % of 5376 rows, with row counts on both sides of whole rounds: none, a few tiles all of
+    which are split, 192 that are not, one whole round, one and a tail, the bound.  Rows past the count stay as they were."""
+    M, N, K = 5376, 4096, 4096
+    g = torch.Generator(device=DEV).manual_seed(3)
+    a, b = torch.randn(M, K, device=DEV, generator=g).bfloat16(), torch.randn(K, N, device=DEV, generator=g).bfloat16()
+    want, ws = a.double() @ b.double(), torch.empty(64 << 20, dtype=torch.uint8, device=DEV)
+    for rows in (0, 1, 300, 1000, 3000, 4096, 4097, 4359, 5376, 6000):
+        cnt, n = torch.tensor([rows + m_off], dtype=torch.int32, device=DEV), min(rows, M)
+        c = torch.full((M, N), 7.0, device=DEV, dtype=torch.bfloat16)
+        ws.fill_(0xFF)
+        p = ig.args(ig.NN, M, N, K, a=a.data_ptr(), b=b.data_ptr(), c=c.data_ptr(), m_dev=cnt.data_ptr(), m_off=m_off,
+                    scratch=ws.data_ptr(), scratch_bytes=ws.numel())
+        assert ig.scratch_bytes(p) > 0
+        _launch(f"{rows} rows on the device", p)
+        assert n == 0 or float((c[:n].double() - want[:n]).abs().max()) < 6e-3 * float(want.abs().max()), rows
+        untouched = bool((c[n:] == 7.0).all())
+        assert untouched, rows
 
 
 def test_split_products_of_a_training_step_with_few_kept_rows():
