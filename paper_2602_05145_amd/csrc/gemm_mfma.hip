@@ -1009,6 +1009,23 @@ size_t gemm_splitk_scratch_bound(const GemmArgs& a) {
   return s < 2 ? bytes : std::max(bytes, (size_t)(256 - 256 / s) * 65536 * sizeof(float));
 }
 
+namespace {
+// What a launch does with the scratch it is given: the tile edge, and which split.
+struct LaunchPlan { int BT, split; SplitPlan tail; SplitGrid all; };
+LaunchPlan plan_launch(const GemmArgs& a) {
+  LaunchPlan lp{tile_edge(a), kSplitNone, plan_split(a), {0, 0, 0}};
+  const bool scratch_ok = a.scratch && (((uintptr_t)a.scratch) & 15) == 0;
+  if (lp.tail.s > 1) {
+    if (scratch_ok && a.scratch_bytes >= lp.tail.bytes) lp.split = kSplitTail;
+  } else {
+    lp.all = plan_split_all(a, lp.BT);
+    if (lp.all.blocks > 0 && scratch_ok && a.scratch_bytes >= lp.all.bytes) lp.split = kSplitAll;
+    else if (lp.all.blocks > 0 && tile_count(a.M, a.N, 256) < 200) lp.BT = 128;   // chosen for its split: without scratch, too few large tiles to run them whole
+  }
+  return lp;
+}
+}  // namespace
+
 size_t gemm_split_tail_bytes(const GemmArgs& a) { return gemm_mfma_supported(a) ? plan_split(a).bytes : 0; }
 size_t gemm_splitk_scratch_bytes(const GemmArgs& a) {
   if (!gemm_mfma_supported(a)) return 0;
@@ -1041,14 +1058,13 @@ bool gemm_mfma_supported(const GemmArgs& a) {
 
 namespace {
 
-// split_blocks: grid of a kSplitAll launch, whose tail is at most split_tail tiles
 template <int BT, bool AMM, bool BNM, typename TO>
-hipError_t launch_tiles(const MfmaParams& p, int64_t split_blocks, int64_t split_tail, hipStream_t s) {
+hipError_t launch_tiles(const MfmaParams& p, const SplitGrid& all, hipStream_t s) {   // all: of a kSplitAll launch
   MfmaParams q = p;
   q.tiles_m = (p.M + BT - 1) / BT;
   q.tiles_n = (p.N + BT - 1) / BT;
   const int tiles = q.tiles_m * q.tiles_n;
-  const int64_t items = q.split == kSplitAll ? split_blocks
+  const int64_t items = q.split == kSplitAll ? all.blocks
                       : q.split == kSplitTail ? q.split_full + (int64_t)(tiles - q.split_full) * q.split_s : tiles;
   // every slab whole (and K known on the host): the DMA loads of a K-major operand take loop-constant lane offsets
   // (with both operands row-major over K the two forms are the same code: one instantiation)
@@ -1057,19 +1073,19 @@ hipError_t launch_tiles(const MfmaParams& p, int64_t split_blocks, int64_t split
   else hipLaunchKernelGGL((gemm_mfma_kernel<BT, AMM, BNM, TO, false>), dim3((unsigned)items), dim3(2 * BT), 0, s, q);
   const hipError_t e = hipGetLastError();
   if (e != hipSuccess || q.split != kSplitAll) return e;
-  hipLaunchKernelGGL((splitk_reduce_kernel<TO, BT>), dim3((unsigned)(split_tail * (BT * BT / 2048))), dim3(256), 0, s, q);
+  hipLaunchKernelGGL((splitk_reduce_kernel<TO, BT>), dim3((unsigned)(all.tail * (BT * BT / 2048))), dim3(256), 0, s, q);
   return hipGetLastError();
 }
 
 template <bool AMM, bool BNM, typename TO>
-hipError_t launch_layout(const MfmaParams& p, int BT, int64_t split_blocks, int64_t split_tail, hipStream_t s) {
-  if (BT == 256) return launch_tiles<256, AMM, BNM, TO>(p, split_blocks, split_tail, s);
-  return launch_tiles<128, AMM, BNM, TO>(p, split_blocks, split_tail, s);
+hipError_t launch_layout(const MfmaParams& p, const LaunchPlan& lp, hipStream_t s) {
+  if (lp.BT == 256) return launch_tiles<256, AMM, BNM, TO>(p, lp.all, s);
+  return launch_tiles<128, AMM, BNM, TO>(p, lp.all, s);
 }
 
 const char* gemm_kernel_name(const GemmArgs& a) {
   if (!gemm_mfma_supported(a)) return a.in_dtype == kF32 && a.out_dtype == kF32 ? "gemm_fp32" : "gemm_simple";
-  const bool big = tile_edge(a) == 256;
+  const bool big = plan_launch(a).BT == 256;
   const bool f32 = a.out_dtype == kF32;
   switch (a.layout) {
     case kNT: return big ? (f32 ? "gemm_mfma_nt_256_f32out" : "gemm_mfma_nt_256_bf16out") : (f32 ? "gemm_mfma_nt_128_f32out" : "gemm_mfma_nt_128_bf16out");
@@ -1089,30 +1105,15 @@ hipError_t launch_gemm_mfma(const GemmArgs& a, hipStream_t s) {
   p.lda = (int)a.lda; p.ldb = (int)a.ldb; p.ldc = (int)a.ldc; p.ldr = (int)a.ldr;
   p.alpha = a.alpha; p.accumulate = a.accumulate; p.tiles_m = p.tiles_n = 0;
   p.m_dev = a.m_dev; p.m_off = (int)a.m_off; p.k_dev = a.k_dev; p.k_off = (int)a.k_off;
-  p.split = kSplitNone; p.split_s = 1; p.split_full = 0; p.split_scratch = nullptr;
-  int64_t split_blocks = 0, split_tail = 0;
-  const bool scratch_ok = a.scratch && (((uintptr_t)a.scratch) & 15) == 0;
-  const SplitPlan tail = plan_split(a);
-  int BT = tile_edge(a);
-  if (tail.s > 1) {
-    if (scratch_ok && a.scratch_bytes >= tail.bytes) {
-      p.split = kSplitTail; p.split_s = tail.s; p.split_full = tail.full; p.split_scratch = (float*)a.scratch;
-    }
-  } else {
-    const SplitGrid sp = plan_split_all(a, BT);
-    if (sp.blocks > 0 && scratch_ok && a.scratch_bytes >= sp.bytes) {
-      p.split = kSplitAll; p.split_scratch = (float*)a.scratch;
-      split_blocks = sp.blocks; split_tail = sp.tail;
-    } else if (sp.blocks > 0 && tile_count(a.M, a.N, 256) < 200) {
-      BT = 128;   // chosen for its split: without scratch, too few large tiles to run them whole
-    }
-  }
+  const LaunchPlan lp = plan_launch(a);
+  p.split = lp.split; p.split_s = lp.split == kSplitTail ? lp.tail.s : 1; p.split_full = lp.split == kSplitTail ? lp.tail.full : 0;
+  p.split_scratch = lp.split != kSplitNone ? (float*)a.scratch : nullptr;
   const bool f32out = a.out_dtype == kF32;
   hipError_t e = hipErrorInvalidValue;
   switch (a.layout) {
-    case kNT: e = f32out ? launch_layout<false, false, float>(p, BT, split_blocks, split_tail, s) : launch_layout<false, false, bf16_t>(p, BT, split_blocks, split_tail, s); break;
-    case kNN: e = f32out ? launch_layout<false, true, float>(p, BT, split_blocks, split_tail, s) : launch_layout<false, true, bf16_t>(p, BT, split_blocks, split_tail, s); break;
-    case kTN: e = f32out ? launch_layout<true, true, float>(p, BT, split_blocks, split_tail, s) : launch_layout<true, true, bf16_t>(p, BT, split_blocks, split_tail, s); break;
+    case kNT: e = f32out ? launch_layout<false, false, float>(p, lp, s) : launch_layout<false, false, bf16_t>(p, lp, s); break;
+    case kNN: e = f32out ? launch_layout<false, true, float>(p, lp, s) : launch_layout<false, true, bf16_t>(p, lp, s); break;
+    case kTN: e = f32out ? launch_layout<true, true, float>(p, lp, s) : launch_layout<true, true, bf16_t>(p, lp, s); break;
   }
   if (e != hipSuccess || p.split != kSplitTail) return e;
   const int tiles_n = (p.N + 255) / 256;
@@ -1128,7 +1129,7 @@ hipError_t launch_gemm(const GemmArgs& a, hipStream_t s) {
   const double es_in = (double)dtype_size(a.in_dtype), es_out = (double)dtype_size(a.out_dtype);
   const double bytes = es_in * k * ((double)a.M + (double)a.N) +
                        es_out * (double)a.M * (double)a.N * (1.0 + (a.accumulate ? 1.0 : 0.0) + (a.residual ? 1.0 : 0.0));
-  ProfScope ps(gemm_kernel_name(a), 2.0 * (double)a.M * (double)a.N * k, bytes, s);
+  ProfScope ps(prof_enabled() ? gemm_kernel_name(a) : "", 2.0 * (double)a.M * (double)a.N * k, bytes, s);
   if (a.m_dev) prof_dynamic(a.m_dev, a.m_off, a.M);
   else if (a.k_dev) prof_dynamic(a.k_dev, a.k_off, a.K);
   if (gemm_mfma_supported(a)) return launch_gemm_mfma(a, s);

@@ -105,7 +105,7 @@ def test_small_results_split_over_k(B, layout, M, N, K, split):
 @pytest.mark.parametrize("layout", [0, 1, 2])
 @pytest.mark.parametrize("M,N,K", [(1000, 512, 32008), (2040, 1544, 20000), (2296, 1016, 12288)])
 def test_large_tiles_split_over_k(B, layout, M, N, K):
-    """Few tiles with a long contraction, where the split runs on 256 x 256 tiles.  Ragged M, N and K, bf16 and fp32 results,
+    """Few tiles with a long contraction, where the split runs on 256 x 256 tiles (the first: sixteen parts of small ones).  Ragged M, N and K, bf16 and fp32 results,
     residual and alpha in the second kernel."""
     assert B.tide_gemm_workspace_bytes(layout, M, N, K, 1) > 0
     a, b, ref = _operands(B, layout, M, N, K, "bf16", M + K)
@@ -251,3 +251,17 @@ def test_grouped_weight_gradients_of_an_fp32_step(kw):
     got = tr.host(tr.grads)
     for k, r in grads.items():
         assert np.abs(got[k] - r).max() <= 1e-4 * np.abs(r).max(), k
+
+
+def test_the_profile_names_the_tile_that_ran(B):
+    """Large tiles chosen for their split over K: without a workspace the launch runs small ones, and is reported so."""
+    M, N, K = 2040, 1544, 20000
+    need = B.tide_gemm_workspace_bytes(B.LAYOUT_NN, M, N, K, 1)
+    assert need > 0
+    a, b, _ = _operands(B, B.LAYOUT_NN, M, N, K, "bf16", 1)
+    c, ws = torch.empty(M, N, device=DEV, dtype=torch.bfloat16), torch.empty(need, dtype=torch.uint8, device=DEV)
+    for w, name in ((ws, "gemm_mfma_nn_256_bf16out"), (None, "gemm_mfma_nn_128_bf16out")):
+        print(f"profiled gemm workspace={w is not None}", flush=True)
+        B.tide_profile_start()
+        B.tide_gemm(B.LAYOUT_NN, M, N, K, 1.0, a, b, c, None, 1, 1, 0, stream(), workspace=w, workspace_bytes=0 if w is None else need)
+        assert [r["kernel"] for r in B.tide_profile_stop()] == [name]
