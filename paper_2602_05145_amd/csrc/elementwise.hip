@@ -635,9 +635,14 @@ static int64_t rmsnorm_bwd_grid(int64_t rows, int d, int dtype) {
   return n < cap ? n : cap;
 }
 
-hipError_t launch_colsums(const ColSums& cs, int n, int64_t rows, int d, int dtype, int accumulate, hipStream_t s) {
+static hipError_t fold_partials(const ColSums& cs, int n, int64_t rows, int d, int dtype, int accumulate, hipStream_t s) {
   hipLaunchKernelGGL(colsum_kernel, dim3((d + 15) / 16, (unsigned)n), dim3(256), 0, s, cs, rmsnorm_bwd_grid(rows, d, dtype), d, accumulate);
   return hipGetLastError();
+}
+
+hipError_t launch_colsums(const ColSums& cs, int n, int64_t rows, int d, int dtype, int accumulate, hipStream_t s) {
+  ProfScope ps("colsums", 0, 4.0 * n * d * (double)rmsnorm_bwd_grid(rows, d, dtype), s);
+  return fold_partials(cs, n, rows, d, dtype, accumulate, s);
 }
 
 // What the given rows take, or any smaller number of them: 3361 rows are walked by fewer blocks (421) than 3360 (480).
@@ -671,7 +676,7 @@ hipError_t launch_rmsnorm_bwd(int64_t rows, int d, const void* dy, const void* x
   if (e != hipSuccess) return e;
   if (!dg) return hipSuccess;   // the caller folds the partial sums later
   const ColSums one{{dg_partial}, {dg}};
-  return launch_colsums(one, 1, rows, d, dtype, 0, s);
+  return fold_partials(one, 1, rows, d, dtype, 0, s);
 }
 
 // ----------------------------------------------------------------------------------------------

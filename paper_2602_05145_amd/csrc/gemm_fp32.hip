@@ -358,7 +358,9 @@ hipError_t launch_gemm_group(const GemmArgs* a, int n, hipStream_t s) {
   g.n = n;
   g.first[0] = 0;
   bool vec = true, together = n > 1 && n <= kMaxGemmGroup;
-  double flops = 0, bytes = 0;
+  double flops = 0, bytes = 0, fixed_flops = 0, fixed_bytes = 0;   // fixed: of products whose sizes are all known here
+  const int* dyn = nullptr;                                        // (the others of a step share one size on the device)
+  int64_t dyn_off = 0, dyn_max = 0;
   for (int i = 0; together && i < n; ++i) {
     bool v = false;
     together = a[i].in_dtype == kF32 && a[i].out_dtype == kF32 && a[i].layout == a[0].layout && a[i].M > 0 && a[i].N > 0 &&
@@ -367,8 +369,12 @@ hipError_t launch_gemm_group(const GemmArgs* a, int n, hipStream_t s) {
     if (!together) break;
     vec = vec && v;
     g.first[i + 1] = g.first[i] + (int)(((a[i].M + 15) / 16) * ((a[i].N + 15) / 16));
-    flops += 2.0 * a[i].M * a[i].N * a[i].K;
-    bytes += 4.0 * (a[i].K * (double)(a[i].M + a[i].N) + a[i].M * (double)a[i].N);
+    const double k = (double)g.p[i].K + g.p[i].K2, f = 2.0 * a[i].M * a[i].N * k, b = 4.0 * (k * (a[i].M + a[i].N) + a[i].M * (double)a[i].N);
+    flops += f;
+    bytes += b;
+    if (a[i].m_dev) { dyn = a[i].m_dev; dyn_off = a[i].m_off; dyn_max = a[i].M; }
+    else if (a[i].k_dev) { dyn = a[i].k_dev; dyn_off = a[i].k_off; dyn_max = a[i].K; }
+    else { fixed_flops += f; fixed_bytes += b; }
   }
   if (!together) {
     for (int i = 0; i < n; ++i) {
@@ -378,6 +384,7 @@ hipError_t launch_gemm_group(const GemmArgs* a, int n, hipStream_t s) {
     return hipSuccess;
   }
   ProfScope ps("gemm_fp32_group", flops, bytes, s);
+  if (dyn) prof_dynamic(dyn, dyn_off, dyn_max, fixed_flops, fixed_bytes);
   switch (a[0].layout) {
     case kNT: return launch_fp32_group<true, true>(g, vec, s);
     case kNN: return launch_fp32_group<true, false>(g, vec, s);

@@ -7,8 +7,9 @@ namespace tide {
 
 bool prof_enabled();
 void prof_begin(const char* kernel, double flops, double bytes, hipStream_t s);
-// the launch just begun works on clamp(*dev - off, 0, maxv) of the maxv units its flops/bytes were computed for
-void prof_dynamic(const int* dev, long long off, long long maxv);
+// the launch just begun works on clamp(*dev - off, 0, maxv) of the maxv units its flops/bytes were computed for, but for
+// the given parts of them, which do not depend on it
+void prof_dynamic(const int* dev, long long off, long long maxv, double fixed_flops = 0, double fixed_bytes = 0);
 void prof_end(hipStream_t s);
 
 struct ProfScope {

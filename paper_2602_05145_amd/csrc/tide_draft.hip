@@ -1129,7 +1129,7 @@ int tide_ce_train(int64_t rows, int32_t vocab, void* z, int64_t ldz, const int32
 // ---- optional per-launch profiler (prof.h) --------------------------------------------------------
 namespace tide {
 namespace {
-struct ProfRec { const char* name; double flops, bytes; hipEvent_t e0, e1; const int* dyn; long long dyn_off, dyn_max; };
+struct ProfRec { const char* name; double flops, bytes; hipEvent_t e0, e1; const int* dyn; long long dyn_off, dyn_max; double fixed_flops, fixed_bytes; };
 struct Profiler {
   std::mutex mu;
   bool on = false;
@@ -1149,18 +1149,20 @@ bool prof_enabled() { return g_prof.on; }
 
 void prof_begin(const char* kernel, double flops, double bytes, hipStream_t s) {
   std::lock_guard<std::mutex> lk(g_prof.mu);
-  ProfRec r{kernel, flops, bytes, g_prof.get(), g_prof.get(), nullptr, 0, 0};
+  ProfRec r{kernel, flops, bytes, g_prof.get(), g_prof.get(), nullptr, 0, 0, 0, 0};
   if (r.e0) (void)hipEventRecord(r.e0, s);
   g_prof.recs.push_back(r);
 }
 
-void prof_dynamic(const int* dev, long long off, long long maxv) {
+void prof_dynamic(const int* dev, long long off, long long maxv, double fixed_flops, double fixed_bytes) {
   if (!g_prof.on) return;
   std::lock_guard<std::mutex> lk(g_prof.mu);
   if (g_prof.recs.empty()) return;
   g_prof.recs.back().dyn = dev;
   g_prof.recs.back().dyn_off = off;
   g_prof.recs.back().dyn_max = maxv;
+  g_prof.recs.back().fixed_flops = fixed_flops;
+  g_prof.recs.back().fixed_bytes = fixed_bytes;
 }
 
 void prof_end(hipStream_t s) {
@@ -1212,7 +1214,9 @@ int tide_profile_stop(char* report, size_t report_bytes) {
       eff = eff < 0 ? 0 : (eff > r.dyn_max ? r.dyn_max : eff);
       scale = (double)eff / (double)r.dyn_max;
     }
-    a->n += 1; a->ms += ms; a->flops += r.flops * scale; a->bytes += r.bytes * scale;
+    a->n += 1; a->ms += ms;
+    a->flops += r.fixed_flops + (r.flops - r.fixed_flops) * scale;
+    a->bytes += r.fixed_bytes + (r.bytes - r.fixed_bytes) * scale;
     if (r.e0) g_prof.pool.push_back(r.e0);
     if (r.e1) g_prof.pool.push_back(r.e1);
   }

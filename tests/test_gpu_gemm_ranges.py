@@ -265,3 +265,25 @@ def test_the_profile_names_the_tile_that_ran(B):
         B.tide_profile_start()
         B.tide_gemm(B.LAYOUT_NN, M, N, K, 1.0, a, b, c, None, 1, 1, 0, stream(), workspace=w, workspace_bytes=0 if w is None else need)
         assert [r["kernel"] for r in B.tide_profile_stop()] == [name]
+
+
+def test_profile_of_an_fp32_step_counts_the_rows_that_ran(B):
+    """The grouped products work on the rows that carry loss, whose number is on the device; the report's flops are of those.
+    Against the count from the configuration; and the launch that folds the norms' partial sums is in the report."""
+    import numpy as np
+    from paper_2602_05145_amd import runtime, workloads as W
+    cfg = W.get_config("tiny", batch=2, seq=64)
+    wl = W.make_workload(cfg)
+    mask = np.zeros_like(wl["mask"])
+    mask[:, :13] = 1
+    tr = runtime.DraftTrainer(cfg, wl["params"])
+    tr.set_batch(wl["hidden"], np.abs(wl["tokens"]) % cfg["vocab"], mask)
+    print("profiled fp32 step", flush=True)
+    B.tide_profile_start()
+    tr.train_step(cfg["lr"])
+    got = {r["kernel"]: r for r in B.tide_profile_stop()}
+    t, rows, p = 128, 26, {k: int(np.prod(s)) for k, s in W.param_shapes(cfg).items()}
+    late = p["w_o"] + p["w_gate"] + p["w_up"] + p["w_down"] + p["w_lm"]
+    want = 4.0 * t * p["w_fc"] + 6.0 * t * p["w_qkv"] + 6.0 * rows * late
+    assert "gemm_fp32_group" in got and got["colsums"]["launches"] == 1
+    assert abs(sum(r["flops"] for k, r in got.items() if k.startswith("gemm")) - want) < 1e-5 * want
