@@ -47,10 +47,8 @@ namespace tide {
 typedef __bf16 bf16x8_t __attribute__((ext_vector_type(8)));
 typedef float f32x16_t __attribute__((ext_vector_type(16)));
 typedef unsigned u32x4_t __attribute__((ext_vector_type(4)));
-typedef __attribute__((address_space(3))) void* lds_vp;
 
 namespace {
-
 
 struct MfmaParams {
   const bf16_t* A; const bf16_t* B; const bf16_t* A2; const bf16_t* B2;
@@ -126,10 +124,6 @@ __device__ __forceinline__ void tile_coords(int v, int tiles_m, int tiles_n, int
   tile_n = in_g / gsz;
 }
 
-__device__ __forceinline__ __amdgpu_buffer_rsrc_t make_rsrc(const void* base, uint32_t bytes) {
-  return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(base), 0, (int)bytes, 0x00020000);
-}
-
 // wait until at most n of this wave's vector-memory operations are outstanding (vmcnt only)
 #define TIDE_WAIT_VMCNT(n) __builtin_amdgcn_s_waitcnt(((n) & 15) | (((n) >> 4) << 14) | (7 << 4) | (15 << 8))
 
@@ -197,22 +191,15 @@ struct Operand {
     }
   }
 
-  // The scalar part of the slab [k0, k0+BK).  tile = operand pointer already offset to the tile's first row (K-major)
-  // or first column (row-major); rows_valid = tile rows inside the matrix (K-major); cols_left = matrix columns from
-  // the tile's first column on (row-major); Kc = contraction length.  A slab with k0 >= Kc is a dummy: every load is out of
-  // range and writes zeros.
+  // The scalar part of the slab [k0, k0+BK) of a K-major operand whose last slab is ragged.  tile = operand pointer already
+  // offset to the tile's first row; rows_valid = tile rows inside the matrix; Kc = contraction length.  A slab with k0 >= Kc is
+  // a dummy: every load is out of range and writes zeros.
   // The loads are issued one by one as instructions (dma16): chunk<I> issues the wave's I-th chunk into the LDS unit at byte address `unit` (scalar); wave_s is the wave index as a scalar.
   struct SlabDesc { i32x4_t rs; int k0, Kc; };
-  static __device__ __forceinline__ SlabDesc slab_desc(const bf16_t* tile, int ld, int rows_valid, int cols_left, int k0, int Kc) {
+  static __device__ __forceinline__ SlabDesc slab_desc(const bf16_t* tile, int ld, int rows_valid, int k0, int Kc) {
     SlabDesc d;
     d.k0 = k0; d.Kc = Kc;
-    if (RMAJ) {
-      const int kv = min(BK, Kc - k0);
-      const bf16_t* base = tile + (size_t)(kv > 0 ? k0 : 0) * ld;
-      d.rs = make_rsrc_words(base, kv > 0 ? (uint32_t)(((int64_t)(kv - 1) * ld + cols_left) * 2) : 0u);
-    } else {
-      d.rs = make_rsrc_words(tile, (uint32_t)(((int64_t)(rows_valid - 1) * ld + Kc) * 2));
-    }
+    d.rs = make_rsrc_words(tile, (uint32_t)(((int64_t)(rows_valid - 1) * ld + Kc) * 2));
     return d;
   }
   // A load whose lane offset is a loop constant: a row-major operand always, a K-major one when every slab is
@@ -226,13 +213,8 @@ struct Operand {
   template <int I>
   static __device__ __forceinline__ void chunk(const SlabDesc& d, uint32_t unit, const uint32_t (&off)[PER_WAVE],
                                                const int (&piece)[PER_WAVE], int wave_s) {
-    const uint32_t lds = unit + (uint32_t)((wave_s * PER_WAVE + I) * 1024);
-    if (RMAJ) {
-      dma16(d.rs, lds, off[I]);
-    } else {
-      const bool kin = (d.k0 + piece[I] * 8) < d.Kc;
-      dma16(d.rs, lds, kin ? off[I] + (uint32_t)(d.k0 * 2) : kOobOffset);
-    }
+    const bool kin = (d.k0 + piece[I] * 8) < d.Kc;
+    dma16(d.rs, unit + (uint32_t)((wave_s * PER_WAVE + I) * 1024), kin ? off[I] + (uint32_t)(d.k0 * 2) : kOobOffset);
   }
 
   // Per-lane element offsets of the operand reads inside a stage, computed once.  K-major: one per k32 step (the swizzle
@@ -241,7 +223,6 @@ struct Operand {
   // of the stage arrays (longer chains lose it, and a read without it waits for all DMA writes in flight).
   // ---- 16x16x32 MFMA: a fragment is 16 tile rows x 32 k; lane l holds row l & 15, k = 8 * (l >> 4) .. + 7 ----
   static constexpr int NRO16 = RMAJ ? T16 : BK / 32;
-  static constexpr int kReadsPerFrag16 = RMAJ ? 2 : 1;
   static __device__ __forceinline__ void read_offsets16(int wbase, int lane, uint32_t (&ro)[NRO16]) {
     const int r16 = lane & 15, g = lane >> 4;
     if (RMAJ) {
@@ -641,7 +622,7 @@ __global__ __launch_bounds__(2 * BT) void gemm_mfma_kernel(MfmaParams p) {
       } else {
         int pr, k0, Kc;
         slab(kt, pr, k0, Kc);
-        d = OpA::slab_desc(pr ? a_tile1 : a_tile0, p.lda, a_rows, p.M - m0, k0, Kc);
+        d = OpA::slab_desc(pr ? a_tile1 : a_tile0, p.lda, a_rows, k0, Kc);
       }
       return d;
     };
@@ -653,7 +634,7 @@ __global__ __launch_bounds__(2 * BT) void gemm_mfma_kernel(MfmaParams p) {
       } else {
         int pr, k0, Kc;
         slab(kt, pr, k0, Kc);
-        d = OpB::slab_desc(pr ? b_tile1 : b_tile0, p.ldb, b_rows, p.N - n0, k0, Kc);
+        d = OpB::slab_desc(pr ? b_tile1 : b_tile0, p.ldb, b_rows, k0, Kc);
       }
       return d;
     };
