@@ -72,13 +72,11 @@ struct Geo {
 };
 
 // the wave's columns of the second product: acc[t] += X[16 x 64] Y[64 x 16 columns], X from the exchange in LDS, Y's rows
-// r0 .. r0 + 63 from memory (zeros from row `rows` on).  Row q of X may see Y's rows from + q .. upto + q only (causality,
-// from either side).  What X holds for the others is zero, but zero times a NaN or an infinity of such a row is not: where a sum
-// over a tile on the diagonal is not finite, it is made again element by element.
-constexpr int kNoBound = 0x7fffff00;
-template <int NCT, typename T>
-__device__ __forceinline__ void second_product(const Geo& z, const float* x, const T* y, size_t ld, int r0, int rows, int dh, f32x4_t (&acc)[NCT],
-                                               int from, int upto) {
+// r0 .. r0 + 63 from memory (zeros from row `rows` on).  Loads past the end are of the last row or column instead, so that
+// none is behind a branch, between which the compiler waits (bf16, 1 x 700, 8 / 2 heads of 80: 77 + 565 / 49 + 321 us); BRANCH:
+// behind branches, which take fewer registers (fp32, same, heads of 256, backward: 1053 / 794; of 18, forward 49 / 36).
+template <bool BRANCH, int NCT, typename T>
+__device__ __forceinline__ void second_product(const Geo& z, const float* x, const T* y, size_t ld, int r0, int rows, int dh, f32x4_t (&acc)[NCT]) {
 #pragma unroll
   for (int t = 0; t < NCT; ++t) {
     const int col = (z.wave + 4 * t) * 16 + z.lr;
@@ -87,26 +85,67 @@ __device__ __forceinline__ void second_product(const Geo& z, const float* x, con
     for (int grp = 0; grp < 4; ++grp)
 #pragma unroll
       for (int e = 0; e < 4; ++e) {
-        // (always a load, of the last row or column at most: a branch per load lets the compiler wait between them)
         const int r = r0 + grp * 16 + 4 * z.g + e;
-        const float f = ldf(y, (size_t)min(r, rows - 1) * ld + min(col, dh - 1));
-        v[grp][e] = (r < rows && col < dh) ? f : 0.f;
+        if constexpr (BRANCH) v[grp][e] = (r < rows && col < dh) ? ldf(y, (size_t)r * ld + col) : 0.f;
+        else {
+          const float f = ldf(y, (size_t)min(r, rows - 1) * ld + min(col, dh - 1));
+          v[grp][e] = (r < rows && col < dh) ? f : 0.f;
+        }
       }
-    f32x4_t sum = acc[t];
 #pragma unroll
-    for (int grp = 0; grp < 4; ++grp) sum = mma16(*reinterpret_cast<const f32x4_t*>(x + z.lr * PP + grp * 16 + 4 * z.g), v[grp], sum);
-    if (r0 + BT - 1 > upto || r0 < from + BR - 1) {   // block-uniform
-      const float odd = fmaf(sum[0], 0.f, sum[1] * 0.f) + fmaf(sum[2], 0.f, sum[3] * 0.f);
-      if (__builtin_amdgcn_ballot_w64(odd != 0.f) != 0) {
-        if (col < dh)
-          for (int q = 0; q < 4; ++q)
-            for (int r = max(r0, from + 4 * z.g + q); r <= min(min(upto + 4 * z.g + q, rows - 1), r0 + BT - 1); ++r)
-              acc[t][q] = fmaf(x[(4 * z.g + q) * PP + r - r0], ldf(y, (size_t)r * ld + col), acc[t][q]);
-        continue;
-      }
-    }
-    acc[t] = sum;
+    for (int grp = 0; grp < 4; ++grp) acc[t] = mma16(*reinterpret_cast<const f32x4_t*>(x + z.lr * PP + grp * 16 + 4 * z.g), v[grp], acc[t]);
   }
+}
+
+template <typename T, int NG, bool VEC>
+constexpr bool kBranchBwd = sizeof(T) == 4 && (NG == 16 || !VEC);
+
+// Causality where values are not finite.  X is zero where a position sees nothing of another, but zero times the other's NaN
+// or infinity is not: it reaches all 16 x 64 results of a tile on the diagonal.  Rows of a result that are not finite, and
+// where that can be such a tile's doing, are therefore made again at the end from the positions they see alone, by the
+// wave whose columns they are, a channel per lane.  No row of finite inputs is.
+// Bits of the block's rows (4 (l / 16) + q) in which a wave's columns hold something that is not finite; ask[q]: the row counts.
+template <int NCT>
+__device__ __forceinline__ uint32_t not_finite(const Geo& z, const f32x4_t (&acc)[NCT], const bool (&ask)[4]) {
+  uint32_t rows = 0;
+#pragma unroll
+  for (int q = 0; q < 4; ++q) {
+    float odd = 0.f;
+#pragma unroll
+    for (int t = 0; t < NCT; ++t) odd = fmaf(acc[t][q], 0.f, odd);
+    const uint64_t b = __builtin_amdgcn_ballot_w64(odd != 0.f && ask[q]);
+#pragma unroll
+    for (int g = 0; g < 4; ++g) rows |= ((b >> (16 * g)) & 0xFFFFu) != 0 ? 1u << (4 * g + q) : 0u;
+  }
+  return rows;
+}
+// what the lanes of row r hold in v
+__device__ __forceinline__ float of_row(const f32x4_t& v, int r) {
+  const int q = r & 3;
+  return __shfl(q == 0 ? v[0] : q == 1 ? v[1] : q == 2 ? v[2] : v[3], 4 * (r & 12), 64);
+}
+// channels lane, lane + 64, ... of a row
+constexpr int NU = kMaxDh / 64;
+template <typename T>
+__device__ __forceinline__ void channels(const T* row, int lane, int dh, float (&v)[NU]) {
+#pragma unroll
+  for (int u = 0; u < NU; ++u) v[u] = lane + 64 * u < dh ? ldf(row, lane + 64 * u) : 0.f;
+}
+__device__ __forceinline__ float dot(const float (&a)[NU], const float (&b)[NU]) {
+  float s = 0.f;
+#pragma unroll
+  for (int u = 0; u < NU; ++u) s = fmaf(a[u], b[u], s);
+  return wave_sum(s);
+}
+// channel lane + 64 u is one of the wave's columns: (wave + 4 t) 16 .. + 15
+__device__ __forceinline__ bool own_channel(const Geo& z, int u, int dh) { return z.g == z.wave && z.lane + 64 * u < dh; }
+// the stores of the rows as they came out are done before a row is stored again, by other lanes of the wave
+__device__ __forceinline__ void wait_stores() {
+  asm volatile("" ::: "memory");
+  __builtin_amdgcn_s_waitcnt(0x0F70);   // vmcnt(0)
+}
+__device__ __forceinline__ float times_zero(const float (&a)[NU]) {   // not zero where something is not finite
+  return fmaf(a[0], 0.f, a[1] * 0.f) + fmaf(a[2], 0.f, a[3] * 0.f);
 }
 
 __device__ __forceinline__ float max16(float v) {   // over the 16 lanes of a group
@@ -176,7 +215,7 @@ __global__ __launch_bounds__(256) void attn_fwd_simple_kernel(const T* __restric
       ps[st][r * PP + z.wave * 16 + z.lr] = p;
     }
     __syncthreads();   // (the other buffer is written next: its readers pass this barrier first)
-    second_product<NCT>(z, ps[st], V, ld, j0, S, dh, o, -kNoBound, i0);
+    second_product<sizeof(T) == 4 && !VEC, NCT>(z, ps[st], V, ld, j0, S, dh, o);
   }
   __syncthreads();
 #pragma unroll
@@ -185,17 +224,41 @@ __global__ __launch_bounds__(256) void attn_fwd_simple_kernel(const T* __restric
     if (z.lr == 0) red[0][z.wave][4 * z.g + q] = v;
   }
   __syncthreads();
+  f32x4_t sum, inv;
+  bool ask[4];
 #pragma unroll
   for (int q = 0; q < 4; ++q) {
     const int r = 4 * z.g + q, i = i0 + r;
+    sum[q] = (red[0][0][r] + red[0][1][r]) + (red[0][2][r] + red[0][3][r]);
+    inv[q] = 1.0f / sum[q];
+    ask[q] = i < S && sum[q] - sum[q] == 0.f;
     if (i >= S) continue;
-    const float sum = (red[0][0][r] + red[0][1][r]) + (red[0][2][r] + red[0][3][r]), inv = 1.0f / sum;
 #pragma unroll
     for (int t = 0; t < NCT; ++t) {
       const int col = (z.wave + 4 * t) * 16 + z.lr;
-      if (col < dh) stf(out, ((size_t)sv.row0 + i) * ((size_t)nh * dh) + (size_t)h * dh + col, o[t][q] * inv);
+      if (col < dh) stf(out, ((size_t)sv.row0 + i) * ((size_t)nh * dh) + (size_t)h * dh + col, o[t][q] * inv[q]);
     }
-    if (z.wave == 0 && z.lr == 0) lse[stat_index(cu, Trows, sv, b, h, nh, Smax, i)] = m[q] + logf(sum);
+    if (z.wave == 0 && z.lr == 0) lse[stat_index(cu, Trows, sv, b, h, nh, Smax, i)] = m[q] + logf(sum[q]);
+  }
+  for (uint32_t again = not_finite(z, o, ask); again != 0; again &= again - 1) {   // wave-uniform
+    const int r = __builtin_ctz(again), i = i0 + r;
+    const float mr = of_row(m, r), ir = of_row(inv, r);
+    float qv[NU], kv[NU], vv[NU], acc[NU] = {0.f, 0.f, 0.f, 0.f};
+    channels(base + (size_t)i * ld + (size_t)h * dh, z.lane, dh, qv);
+#pragma unroll
+    for (int u = 0; u < NU; ++u) qv[u] *= scale;
+#pragma unroll 1
+    for (int j = 0; j <= i; ++j) {
+      channels(K + (size_t)j * ld, z.lane, dh, kv);
+      channels(V + (size_t)j * ld, z.lane, dh, vv);
+      const float p = __expf(dot(qv, kv) - mr);
+#pragma unroll
+      for (int u = 0; u < NU; ++u) acc[u] = fmaf(p, vv[u], acc[u]);
+    }
+    wait_stores();
+#pragma unroll
+    for (int u = 0; u < NU; ++u)
+      if (own_channel(z, u, dh)) stf(out, ((size_t)sv.row0 + i) * ((size_t)nh * dh) + (size_t)h * dh + z.lane + 64 * u, acc[u] * ir);
   }
 }
 
@@ -259,17 +322,40 @@ __global__ __launch_bounds__(256) void attn_dq_simple_kernel(const T* __restrict
       ps[st][(4 * z.g + q) * PP + z.wave * 16 + z.lr] = (j <= i && i < S) ? __expf(s[q] - L[q]) * (dp[q] - D[q]) : 0.f;
     }
     __syncthreads();   // (a buffer is written again two tiles on: its readers pass the barrier in between first)
-    second_product<NCT>(z, ps[st], K, ld, j0, S, dh, dq, -kNoBound, i0);
+    second_product<kBranchBwd<T, NG, VEC>, NCT>(z, ps[st], K, ld, j0, S, dh, dq);
   }
+  bool ask[4];
 #pragma unroll
   for (int q = 0; q < 4; ++q) {
     const int i = i0 + 4 * z.g + q;
+    ask[q] = i < S && L[q] - L[q] == 0.f && D[q] - D[q] == 0.f;
     if (i >= S) continue;
 #pragma unroll
     for (int t = 0; t < NCT; ++t) {
       const int col = (z.wave + 4 * t) * 16 + z.lr;
       if (col < dh) stf(dqkv, ((size_t)sv.row0 + i) * ld + (size_t)h * dh + col, dq[t][q] * scale);
     }
+  }
+  for (uint32_t again = not_finite(z, dq, ask); again != 0; again &= again - 1) {   // wave-uniform
+    const int r = __builtin_ctz(again), i = i0 + r;
+    const float Lr = of_row(L, r), Dr = of_row(D, r);
+    float qv[NU], dov[NU], kv[NU], vv[NU], acc[NU] = {0.f, 0.f, 0.f, 0.f};
+    channels(base + (size_t)i * ld + (size_t)h * dh, z.lane, dh, qv);
+    channels(dout + ((size_t)sv.row0 + i) * ((size_t)nh * dh) + (size_t)h * dh, z.lane, dh, dov);
+#pragma unroll
+    for (int u = 0; u < NU; ++u) qv[u] *= scale;
+#pragma unroll 1
+    for (int j = 0; j <= i; ++j) {
+      channels(K + (size_t)j * ld, z.lane, dh, kv);
+      channels(V + (size_t)j * ld, z.lane, dh, vv);
+      const float d = __expf(dot(qv, kv) - Lr) * (dot(dov, vv) - Dr);
+#pragma unroll
+      for (int u = 0; u < NU; ++u) acc[u] = fmaf(d, kv[u], acc[u]);
+    }
+    wait_stores();
+#pragma unroll
+    for (int u = 0; u < NU; ++u)
+      if (own_channel(z, u, dh)) stf(dqkv, ((size_t)sv.row0 + i) * ld + (size_t)h * dh + z.lane + 64 * u, acc[u] * scale);
   }
 }
 
@@ -325,13 +411,15 @@ __global__ __launch_bounds__(256) void attn_dkv_simple_kernel(const T* __restric
       *reinterpret_cast<f32x4_t*>(&ps[st][z.lr * PP + z.wave * 16 + 4 * z.g]) = p;
       *reinterpret_cast<f32x4_t*>(&ds[st][z.lr * PP + z.wave * 16 + 4 * z.g]) = d;
       __syncthreads();   // (as in the dQ kernel)
-      second_product<NCT>(z, ps[st], dO, ldo, i0, S, dh, dv, j0, kNoBound);
-      second_product<NCT>(z, ds[st], Q, ld, i0, S, dh, dk, j0, kNoBound);
+      second_product<kBranchBwd<T, NG, VEC>, NCT>(z, ps[st], dO, ldo, i0, S, dh, dv);
+      second_product<kBranchBwd<T, NG, VEC>, NCT>(z, ds[st], Q, ld, i0, S, dh, dk);
     }
   }
+  bool ask[4];
 #pragma unroll
   for (int q = 0; q < 4; ++q) {
     const int r = j0 + 4 * z.g + q;
+    ask[q] = r < S;
     if (r >= S) continue;
 #pragma unroll
     for (int t = 0; t < NCT; ++t) {
@@ -340,6 +428,54 @@ __global__ __launch_bounds__(256) void attn_dkv_simple_kernel(const T* __restric
       T* row = dqkv + ((size_t)sv.row0 + r) * ld;
       stf(row, (size_t)(nh + kh) * dh + col, dk[t][q] * scale);
       stf(row, (size_t)(nh + nkv + kh) * dh + col, dv[t][q]);
+    }
+  }
+  uint32_t again = not_finite(z, dk, ask) | not_finite(z, dv, ask);
+  if (again != 0) {   // wave-uniform
+    // the queries j0 .. j - 1 meet key j with weight zero: only keys after the first of them that is not finite (a later
+    // query takes every key before it with it, rightly)
+    int first = BR - 1;
+#pragma unroll 1
+    for (int i = 0; i < first && j0 + i < S; ++i) {
+      float odd = 0.f, qv[NU], dov[NU];
+      for (int hh = kh * G; hh < (kh + 1) * G; ++hh) {
+        channels(base + (size_t)(j0 + i) * ld + (size_t)hh * dh, z.lane, dh, qv);
+        channels(dout + ((size_t)sv.row0 + j0 + i) * ldo + (size_t)hh * dh, z.lane, dh, dov);
+        odd += times_zero(qv) + times_zero(dov);
+      }
+      if (__builtin_amdgcn_ballot_w64(odd != 0.f) != 0) first = i;
+    }
+    again &= ~((2u << first) - 1u);
+  }
+  for (; again != 0; again &= again - 1) {
+    const int jr = j0 + __builtin_ctz(again);
+    float kv[NU], vv[NU], qv[NU], dov[NU], ak[NU] = {0.f, 0.f, 0.f, 0.f}, av[NU] = {0.f, 0.f, 0.f, 0.f};
+    channels(base + (size_t)jr * ld + (size_t)(nh + kh) * dh, z.lane, dh, kv);
+    channels(base + (size_t)jr * ld + (size_t)(nh + nkv + kh) * dh, z.lane, dh, vv);
+#pragma unroll
+    for (int u = 0; u < NU; ++u) kv[u] *= scale;
+    for (int hh = kh * G; hh < (kh + 1) * G; ++hh)
+#pragma unroll 1
+      for (int i = jr; i < S; ++i) {
+        channels(base + (size_t)i * ld + (size_t)hh * dh, z.lane, dh, qv);
+        channels(dout + ((size_t)sv.row0 + i) * ldo + (size_t)hh * dh, z.lane, dh, dov);
+        const size_t at = stat_index(cu, Trows, sv, b, hh, nh, Smax, i);
+        const float p = __expf(dot(qv, kv) - lse[at]), d = p * (dot(dov, vv) - delta[at]);
+#pragma unroll
+        for (int u = 0; u < NU; ++u) { ak[u] = fmaf(d, qv[u], ak[u]); av[u] = fmaf(p, dov[u], av[u]); }
+        bool live = false;   // a sum that is not finite stays so
+#pragma unroll
+        for (int u = 0; u < NU; ++u) live |= own_channel(z, u, dh) && (ak[u] - ak[u] == 0.f || av[u] - av[u] == 0.f);
+        if (__builtin_amdgcn_ballot_w64(live) == 0) break;
+      }
+    T* row = dqkv + ((size_t)sv.row0 + jr) * ld;
+    wait_stores();
+#pragma unroll
+    for (int u = 0; u < NU; ++u) {
+      const int col = z.lane + 64 * u;
+      if (!own_channel(z, u, dh)) continue;
+      stf(row, (size_t)(nh + kh) * dh + col, ak[u] * scale);
+      stf(row, (size_t)(nh + nkv + kh) * dh + col, av[u]);
     }
   }
 }
