@@ -148,15 +148,23 @@ __device__ __forceinline__ float times_zero(const float (&a)[NU]) {   // not zer
   return fmaf(a[0], 0.f, a[1] * 0.f) + fmaf(a[2], 0.f, a[3] * 0.f);
 }
 
-__device__ __forceinline__ float max16(float v) {   // over the 16 lanes of a group
-#pragma unroll
-  for (int o = 8; o > 0; o >>= 1) v = fmaxf(v, __shfl_xor(v, o, 64));
-  return v;
+// Over the 16 lanes of a group, by rotations inside the group on the vector unit (DPP row_ror), about 10 clocks a step; through
+// the LDS crossbar the four rows' chains of four steps were 0.8 us, most of what a sequence of a few positions takes.
+template <int N>
+__device__ __forceinline__ float rotate16(float v) {
+  return __uint_as_float(__builtin_amdgcn_update_dpp(0, __float_as_uint(v), 0x120 + N, 0xF, 0xF, false));
+}
+__device__ __forceinline__ float max16(float v) {
+  v = fmaxf(v, rotate16<8>(v));
+  v = fmaxf(v, rotate16<4>(v));
+  v = fmaxf(v, rotate16<2>(v));
+  return fmaxf(v, rotate16<1>(v));
 }
 __device__ __forceinline__ float sum16(float v) {
-#pragma unroll
-  for (int o = 8; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
-  return v;
+  v += rotate16<8>(v);
+  v += rotate16<4>(v);
+  v += rotate16<2>(v);
+  return v + rotate16<1>(v);
 }
 
 }  // namespace
