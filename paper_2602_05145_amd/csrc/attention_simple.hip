@@ -12,8 +12,8 @@
 // registers), passes the 16 x 64 probabilities or score gradients through LDS, and the waves share the columns of the
 // second product.  What bounds it at the sizes it serves (the fp32 configuration has 64 to 1024 positions and 4 heads)
 // is latency, so there are one or two barriers per tile and no staging of operands.  fp32, forward + backward, us, one
-// wavefront per row on the vector units before / now: 2 x 64, 4 / 2 heads of 64: 6 + 37 / 6 + 17; 1 x 1024: 101 + 1382 / 45 + 163;
-// 2 x 1024, 16 / 8 heads of 128: 1287 + 24316 / 258 + 1053.
+// wavefront per row on the vector units before / now: 2 x 64, 4 / 2 heads of 64: 6 + 37 / 6 + 17; 1 x 1024: 101 + 1382 / 39 + 155;
+// 2 x 1024, 16 / 8 heads of 128: 1287 + 24316 / 233 + 1071.
 #include <type_traits>
 
 #include "kernels.h"
