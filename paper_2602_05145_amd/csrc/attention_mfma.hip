@@ -110,7 +110,8 @@ __device__ __forceinline__ u32x4_t pack_half(const f32x16_t& v, int half) {
 // Probabilities and score gradients enter their products as bf16.  At head size 128 that is one value, rounded.  At
 // head size 64, which was served in fp32 arithmetic, each is the sum of two (the rounded value and the rounded rest, 16
 // bits of mantissa together): with one the results were 1.25 to 1.4 times as far from fp64 as in fp32 arithmetic, with
-// two they are as close (0.17 %, their own rounding); 16 x 2048, 32 / 8 heads: 0.38 + 1.53 ms with one, 0.52 + 1.89 with two.
+// two they are as close (0.155 to 0.20 %, their own rounding, over six shapes and four seeds); 16 x 2048, 32 / 8 heads: 0.38 + 1.53 ms with
+// one, 0.50 + 1.82 with two.
 constexpr int parts(int D) { return D == 64 ? 2 : 1; }
 template <int NP>
 __device__ __forceinline__ void pack_parts(const f32x16_t& v, int half, u32x4_t (&r)[NP]) {
@@ -224,10 +225,10 @@ __device__ __forceinline__ uint32_t not_finite(const f32x16_t (&acc)[NC], bool a
 constexpr int BQ = 128, BKV = 64;
 constexpr int kv_tile(int D) { return BKV * pitch(D); }  // elements
 
-// Head size 64 halves the operand and accumulator registers and the LDS tiles: 116 / 165 / 125 / 144 registers for the
+// Head size 64 halves the operand and accumulator registers and the LDS tiles: 119 / 168 / 125 / 147 registers for the
 // forward, dQ, dV and dK kernels, i.e. 4, 3, 4 and 3 blocks per CU (held to 4, 4, 5 and 3 the dQ and dV kernels spill:
 // backward 1.53 -> 2.73 ms at 16 x 2048, 32 / 8 heads, with one bf16 value per probability).  Against the one-wave-per-row kernels (attention_simple.hip) that
-// served this head size: 6 x 777, 16 / 4 heads, forward + backward 17.55 -> 0.21 ms; 16 x 2048, 32 / 8: 0.38 + 1.53 ms.
+// served this head size: 6 x 777, 16 / 4 heads, forward + backward 17.55 -> 0.147 ms.
 constexpr int blocks_per_cu(int D, int at64, int at128) { return D == 64 ? at64 : at128; }
 // Depth of the operand-fragment rings of the three kernels (0 in the dQ kernel: the plain loop).  Measured when the tiles
 // were still staged through registers, backward at 16 x 2048 / 2 x 16384: dQ 0 / dK-dV 4: 3.56 / 21.4 ms; 2 / 4: 3.48 /
