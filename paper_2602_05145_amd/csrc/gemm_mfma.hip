@@ -4,9 +4,9 @@
 //   TN  C = A[K,M]^T B[K,N]   weight gradients dW = dY^T X  (both operands contracted over rows)
 //
 // Design
-//   * A block computes a tile of 256 x 256 (8 wavefronts, the block owns its CU) or 128 x 128 (4 wavefronts, two blocks
-//     share a CU) with v_mfma_f32_16x16x32_bf16; a wave owns 128 x 64 or 64 x 64 of it.  Two waves per SIMD either way: one
-//     alone cannot issue MFMAs back to back (measured ~83 % of the multi-wave MFMA rate).
+//   * A block computes a tile of 128, 160, 192, 224 or 256 x 256 (8 wavefronts, the block owns its CU) or of 128 x 128 (4
+//     wavefronts, two blocks share a CU) with v_mfma_f32_16x16x32_bf16; a wave owns half the rows x 64 of it.  Two waves per
+//     SIMD either way: one alone cannot issue MFMAs back to back (measured ~83 % of the multi-wave MFMA rate).
 //   * K is walked in slabs of 64 through five LDS units (see the kernel), filled by LDS-DMA buffer loads (global -> LDS
 //     without passing through registers, hardware zero-fill outside the valid extent, so ragged M / N / K need no special
 //     code).  What bounds the large tile is the memory side next to the matrix pipes: with every operand row aliased to
@@ -29,7 +29,7 @@
 //     bf16 results without residual/accumulate go through a wave-private LDS patch to leave as 16-byte
 //     row segments; everything else is stored straight from the accumulators.
 //   * Tiles that do not fill the chip are split over K (two forms, see MfmaParams), and the tile is chosen with that
-//     in mind (tile_edge).
+//     in mind (tile_edge); in between, the tile's height is (tall_height).
 //   * Work-groups are renumbered so that each of the 8 XCDs (round-robin dispatch) gets a contiguous
 //     range of tiles, walked in groups of 4 tile-rows: neighbouring tiles share A/B panels in that
 //     XCD's L2.
@@ -152,11 +152,15 @@ __device__ __forceinline__ void dma16(i32x4_t rsrc, uint32_t lds_addr, uint32_t 
 // One operand (A or B) of one block: R rows (BM or BN) of the tile, either K-major or row-major over K.
 template <int R, int NW, bool RMAJ, int T16, int BK>   // T16 = 16-row MFMA fragments per wave along this dimension; BK = slab depth
 struct Operand {
-  static constexpr int STAGE = R * BK;                                   // elements per stage
+  // Rows that a stage has room for: every wave issues the same number of 1 KiB DMA instructions, and a row-major k-row is a
+  // power of two long.  The rows from R on are beyond the loads' extent and hold zeros that no read touches.
+  static constexpr int RL = RMAJ ? (R > 128 ? 256 : 128) : (R * BK * 2 + NW * 1024 - 1) / (NW * 1024) * (NW * 1024) / (BK * 2);
+  static_assert(R % 16 == 0 && R <= RL, "rows of a tile");
+  static constexpr int STAGE = RL * BK;                                  // elements per stage
   static constexpr int CHUNKS = STAGE * 2 / 1024;                        // 1 KiB DMA instructions per stage
   static constexpr int PER_WAVE = CHUNKS / NW;
   static_assert(CHUNKS % NW == 0 && PER_WAVE >= 1, "DMA chunks must split evenly over the waves");
-  static constexpr int PPR = R / 8;                                      // 16-byte pieces per k-row (row-major)
+  static constexpr int PPR = RL / 8;                                     // 16-byte pieces per k-row (row-major)
   static constexpr int RPC = 64 / PPR;                                   // k-rows per DMA chunk (row-major)
   static constexpr int KPIECES = BK / 8;                                 // 16-byte pieces per K-major row (4 or 8)
   static constexpr int KROWS = 64 / KPIECES;                             // K-major rows per DMA chunk (16 or 8)
@@ -176,7 +180,8 @@ struct Operand {
 #pragma unroll
       for (int i = 0; i < PER_WAVE; ++i) {
         const int krow = (wave * PER_WAVE + i) * RPC + kr;
-        off[i] = (uint32_t)((krow * ld + (pc ^ TIDE_RSWZ(krow)) * 8) * 2);
+        const int p = pc ^ TIDE_RSWZ(krow);
+        off[i] = R == RL || p < R / 8 ? (uint32_t)((krow * ld + p * 8) * 2) : kOobOffset;
         piece[i] = 0;
       }
     } else {
@@ -233,7 +238,7 @@ struct Operand {
       for (int i = 0; i < T16; ++i) {
         const int col = wbase + 16 * i + 4 * rq;
         const int krow = g * 8 + kq;
-        ro[i] = (uint32_t)(krow * R + ((((col >> 3) ^ TIDE_RSWZ(krow)) << 3) | (col & 7)));
+        ro[i] = (uint32_t)(krow * RL + ((((col >> 3) ^ TIDE_RSWZ(krow)) << 3) | (col & 7)));
       }
     } else {
       const int sw = (r16 >> SWZ_SHIFT) & (KPIECES - 1);
@@ -251,8 +256,8 @@ struct Operand {
       typedef __attribute__((address_space(3))) s16x4_t* lds_tr_t;
 #pragma unroll
       for (int i = 0; i < NF; ++i) {
-        const s16x4_t lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_tr_t)(stage + ro[F0 + i] + (h * 32) * R));
-        const s16x4_t hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_tr_t)(stage + ro[F0 + i] + (h * 32 + 4) * R));
+        const s16x4_t lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_tr_t)(stage + ro[F0 + i] + (h * 32) * RL));
+        const s16x4_t hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_tr_t)(stage + ro[F0 + i] + (h * 32 + 4) * RL));
         const uint2 a = __builtin_bit_cast(uint2, lo), b2 = __builtin_bit_cast(uint2, hi);
         f[i][0] = a.x; f[i][1] = a.y; f[i][2] = b2.x; f[i][3] = b2.y;
       }
@@ -271,15 +276,15 @@ struct Int : std::integral_constant<int, N> {};
 }  // namespace
 
 // ------------------------------------------------------------------------------------------------
-// Tiles of BT x BT with v_mfma_f32_16x16x32_bf16: BT = 256 on eight waves of 128 x 64, BT = 128 on four waves of 64 x 64
+// Tiles of BM x BN with v_mfma_f32_16x16x32_bf16: BN = 256 on eight waves of BM / 2 x 64, BN = 128 on four waves of 64 x 64
 // (whose five LDS units of 16 KiB let two blocks share a CU).  On this chip the matrix pipes sustain a higher rate under
 // the package power limit with this form than with 32x32x16 (a pure-MFMA loop on random operands: 2.10 against 1.88
 // PFLOP/s), while the LDS operand traffic per flop is the same (a 16-row x 32-k fragment is one 16-byte read per lane, like
-// a 32-row x 16-k one).  A wave owns (BT / 32) x 4 tiles of 16 x 16; a "quarter" of the schedule is one k32 step of four of
+// a 32-row x 16-k one).  A wave owns (BM / 32) x 4 tiles of 16 x 16; a "quarter" of the schedule is one k32 step of four of
 // its A fragments against its four B fragments: 16 MFMAs (256 clocks), with the A fragments double-buffered per quarter
-// and the B fragments per k32 step.  A slab is four quarters at BT = 256 and two at BT = 128.  The MFMAs take the B fragment
+// and the B fragments per k32 step.  A slab is four quarters at BM = 256; below, two of all its A fragments.  The MFMAs take the B fragment
 // first, so accumulator element q of lane l in tile (i, j) is row 16 i + (l & 15), column 16 j + 4 (l >> 4) + q (see the
-// epilogue).  (Four waves of 128 x 128 at BT = 256, a third less LDS traffic, measured 2.5 to 10 % slower: one wave per SIMD
+// epilogue).  (Four waves of 128 x 128 at BM = 256, a third less LDS traffic, measured 2.5 to 10 % slower: one wave per SIMD
 // leaves every wait of that wave exposed.)
 // KWHOLE: every slab of the launch is whole (K, and K2 of a second operand pair, multiples of 64 known on the
 // host).  A K-major operand's loads then need neither the per-lane test "is this piece still inside K" nor a
@@ -289,13 +294,14 @@ struct Int : std::integral_constant<int, N> {};
 // ------------------------------------------------------------------------------------------------
 typedef float f32x4_t __attribute__((ext_vector_type(4)));
 
-template <int BT, bool AMM, bool BNM, typename TO, bool KWHOLE>
-__global__ __launch_bounds__(2 * BT) void gemm_mfma_kernel(MfmaParams p) {
-  static_assert(BT == 256 || BT == 128, "tile edge");
-  constexpr int BM = BT, BN = BT, BK = 64, WAVES_M = 2, WAVES_N = BT / 64, NW = WAVES_M * WAVES_N;
-  constexpr int WM = BM / WAVES_M, WN = BN / WAVES_N;   // 128 x 64 or 64 x 64
-  constexpr int TM = WM / 16, TN = WN / 16;             // 8 x 4 or 4 x 4 tiles of 16 x 16
-  constexpr int GA = 4;                                 // A fragments per quarter
+template <int BM, int BN, bool AMM, bool BNM, typename TO, bool KWHOLE>
+__global__ __launch_bounds__(2 * BN) void gemm_mfma_kernel(MfmaParams p) {
+  static_assert(BN == 256 ? BM % 32 == 0 && BM >= 128 && BM <= 256 : BN == 128 && BM == 128, "tile edges");
+  constexpr int BK = 64, WAVES_M = 2, WAVES_N = BN / 64, NW = WAVES_M * WAVES_N;
+  constexpr int WM = BM / WAVES_M, WN = BN / WAVES_N;   // BM / 2 x 64
+  constexpr int TM = WM / 16, TN = WN / 16;             // 4 to 8 x 4 tiles of 16 x 16
+  constexpr int GA = TM == 8 ? 4 : TM;                  // A fragments per quarter
+  constexpr int TM2 = (TM + 1) / 2;                     // pairs of tile rows, the last of an odd TM half empty
   using OpA = Operand<BM, NW, AMM, TM, BK>;
   using OpB = Operand<BN, NW, BNM, TN, BK>;
   constexpr int A_STAGE = OpA::STAGE, B_STAGE = OpB::STAGE;
@@ -319,7 +325,7 @@ __global__ __launch_bounds__(2 * BT) void gemm_mfma_kernel(MfmaParams p) {
     int full = nb;                           // tiles that are not split
     if (p.split == kSplitTail) { full = p.split_full; nparts = p.split_s; }   // (never with a device-side M)
     else if (p.split == kSplitAll) {
-      const SplitAll sa = split_all<BT>(nb, split_slabs(p.K, p.A2 ? p.K2 : 0));
+      const SplitAll sa = split_all<BN>(nb, split_slabs(p.K, p.A2 ? p.K2 : 0));
       full = sa.full; nparts = sa.parts;
     }
     ntail = nb - full;
@@ -430,9 +436,9 @@ __global__ __launch_bounds__(2 * BT) void gemm_mfma_kernel(MfmaParams p) {
         constexpr int PP = WN + 8;
         bf16_t* patch = patch_mem;
 #pragma unroll
-        for (int i2 = 0; i2 < TM / 2; ++i2) {
+        for (int i2 = 0; i2 < TM2; ++i2) {
 #pragma unroll
-          for (int ih = 0; ih < 2; ++ih)
+          for (int ih = 0; ih < min(2, TM - 2 * i2); ++ih)
 #pragma unroll
             for (int j = 0; j < TN; ++j) {
               const f32x4_t v = acc[2 * i2 + ih][j];
@@ -440,7 +446,7 @@ __global__ __launch_bounds__(2 * BT) void gemm_mfma_kernel(MfmaParams p) {
                   make_uint2(f2bf2(alpha * v[0], alpha * v[1]), f2bf2(alpha * v[2], alpha * v[3]));
             }
 #pragma unroll
-          for (int t = 0; t < 32 * PIECES / 64; ++t) {
+          for (int t = 0; t < 16 * min(2, TM - 2 * i2) * PIECES / 64; ++t) {
             const int pc = lane + 64 * t;
             const int row = pc / PIECES, piece = pc % PIECES;
             const int gm = wm0 + 32 * i2 + row, gn = wn0 + piece * 8;
@@ -457,9 +463,9 @@ __global__ __launch_bounds__(2 * BT) void gemm_mfma_kernel(MfmaParams p) {
         float* patch = reinterpret_cast<float*>(patch_mem);
         const bf16_t* Rb = reinterpret_cast<const bf16_t*>(R);
 #pragma unroll
-        for (int i2 = 0; i2 < TM / 2; ++i2) {
+        for (int i2 = 0; i2 < TM2; ++i2) {
 #pragma unroll
-          for (int ih = 0; ih < 2; ++ih)
+          for (int ih = 0; ih < min(2, TM - 2 * i2); ++ih)
 #pragma unroll
             for (int j = 0; j < TN; ++j) {
               const f32x4_t v = acc[2 * i2 + ih][j];
@@ -467,7 +473,7 @@ __global__ __launch_bounds__(2 * BT) void gemm_mfma_kernel(MfmaParams p) {
                   make_float4(alpha * v[0], alpha * v[1], alpha * v[2], alpha * v[3]);
             }
 #pragma unroll
-          for (int t = 0; t < 32 * PIECES / 64; ++t) {
+          for (int t = 0; t < 16 * min(2, TM - 2 * i2) * PIECES / 64; ++t) {
             const int pc = lane + 64 * t;
             const int row = pc / PIECES, piece = pc % PIECES;
             const int gm = wm0 + 32 * i2 + row, gn = wn0 + piece * 8;
@@ -500,11 +506,11 @@ __global__ __launch_bounds__(2 * BT) void gemm_mfma_kernel(MfmaParams p) {
           pitch = BN; mo = m0; no = n0; add = false;
         }
 #pragma unroll
-        for (int i2 = 0; i2 < TM / 2; ++i2) {
+        for (int i2 = 0; i2 < TM2; ++i2) {
           float4 old[2][TN];
           if (add) {
 #pragma unroll
-            for (int ih = 0; ih < 2; ++ih)
+            for (int ih = 0; ih < min(2, TM - 2 * i2); ++ih)
 #pragma unroll
               for (int j = 0; j < TN; ++j) {
                 const int gm = wm0 + 16 * (2 * i2 + ih) + lc, gn = wn0 + 16 * j + 4 * lg;
@@ -513,7 +519,7 @@ __global__ __launch_bounds__(2 * BT) void gemm_mfma_kernel(MfmaParams p) {
               }
           }
 #pragma unroll
-          for (int ih = 0; ih < 2; ++ih)
+          for (int ih = 0; ih < min(2, TM - 2 * i2); ++ih)
 #pragma unroll
             for (int j = 0; j < TN; ++j) {
               const int gm = wm0 + 16 * (2 * i2 + ih) + lc, gn = wn0 + 16 * j + 4 * lg;
@@ -554,16 +560,13 @@ __global__ __launch_bounds__(2 * BT) void gemm_mfma_kernel(MfmaParams p) {
     // the bytes is on the one-slab clock.  Slab kt lives in deep unit kt % 3 and shallow unit kt % 2; the barrier
     // of a slab sits before its last quarter.  Loads complete in order, so waiting for "all but the youngest
     // NDEEP" means everything older than the deep operand's youngest slab has landed.
-#ifndef TIDE_RING_DEEPB
-#define TIDE_RING_DEEPB 0
-#endif
-    constexpr bool DEEPB = TIDE_RING_DEEPB != 0;   // which operand owns the three units
-    static_assert(A_STAGE == B_STAGE, "units are interchangeable");
-    __shared__ __attribute__((aligned(1024))) bf16_t ld0[A_STAGE];
-    __shared__ __attribute__((aligned(1024))) bf16_t ld1[A_STAGE];
-    __shared__ __attribute__((aligned(1024))) bf16_t ld2[A_STAGE];
-    __shared__ __attribute__((aligned(1024))) bf16_t ls0[B_STAGE];
-    __shared__ __attribute__((aligned(1024))) bf16_t ls1[B_STAGE];
+    constexpr bool DEEPB = BM < BN;   // which operand owns the three units: the larger
+    constexpr int D_STAGE = DEEPB ? B_STAGE : A_STAGE, S_STAGE = DEEPB ? A_STAGE : B_STAGE;
+    __shared__ __attribute__((aligned(1024))) bf16_t ld0[D_STAGE];
+    __shared__ __attribute__((aligned(1024))) bf16_t ld1[D_STAGE];
+    __shared__ __attribute__((aligned(1024))) bf16_t ld2[D_STAGE];
+    __shared__ __attribute__((aligned(1024))) bf16_t ls0[S_STAGE];
+    __shared__ __attribute__((aligned(1024))) bf16_t ls1[S_STAGE];
     auto deep = [&](auto U) -> bf16_t* {
       if constexpr (decltype(U)::value == 0) return ld0;
       else if constexpr (decltype(U)::value == 1) return ld1;
@@ -696,7 +699,10 @@ __global__ __launch_bounds__(2 * BT) void gemm_mfma_kernel(MfmaParams p) {
     all_deep(ld1, 1);
     all_shal(ls1, 1);
     __builtin_amdgcn_sched_barrier(0);
-    // (BT = 128: a slab is two quarters, one per k32 step; the barrier sits between them)
+    // (below eight tile rows per wave a slab is two parts, one per k32 step, with the barrier between them, and each part
+    // begins with its loads: they have to land within a slab, which is short here.  With the loads after the operand reads and
+    // the larger operand in the two units, a slab of 160 x 256 took 1.04 us where it takes 0.92 so, one of 128 x 256 0.85 / 0.74 at
+    // 256 busy CUs, and NT 8193 x 1024 x 32000 620 / 454 us on 192 / 160 rows.)
     // One slab: deep unit D, shallow unit S (fa0 / fb0 hold its first quarter's operands); the next slab's units
     // are DN, SN; DP is the deep unit the slab before vacated.
     auto step = [&](auto D, auto S, auto DN, auto SN, auto DP, int kt) {
@@ -706,9 +712,10 @@ __global__ __launch_bounds__(2 * BT) void gemm_mfma_kernel(MfmaParams p) {
         const auto dd1 = desc_deep(kt + 2);
         quarter(Int<0>{}, fa0, fb0, [&](auto X) {
           constexpr int x = decltype(X)::value;
-          if constexpr (x < GA) frag_a(ua, 1, Int<0>{}, X, fa1);
-          else if constexpr (x < GA + TN) frag_b(ubb, 1, Int<x - GA>{}, fb1);
-          else if constexpr (x < GA + TN + NDEEP) dma_deep(Int<x - GA - TN>{}, dd1, deep(DP));
+          constexpr int y = x - NDEEP;
+          if constexpr (y < 0) dma_deep(X, dd1, deep(DP));
+          else if constexpr (y < GA) frag_a(ua, 1, Int<0>{}, Int<y>{}, fa1);
+          else if constexpr (y < GA + TN) frag_b(ubb, 1, Int<y - GA>{}, fb1);
         });
         __builtin_amdgcn_s_waitcnt((NDEEP & 15) | ((NDEEP >> 4) << 14));   // as below
         __builtin_amdgcn_s_barrier();
@@ -718,9 +725,10 @@ __global__ __launch_bounds__(2 * BT) void gemm_mfma_kernel(MfmaParams p) {
         const auto ds = desc_shal(kt + 2);
         quarter(Int<0>{}, fa1, fb1, [&](auto X) {
           constexpr int x = decltype(X)::value;
-          if constexpr (x < GA) frag_a(uan, 0, Int<0>{}, X, fa0);
-          else if constexpr (x < GA + TN) frag_b(ubn, 0, Int<x - GA>{}, fb0);
-          else if constexpr (x < GA + TN + NSHAL) dma_shal(Int<x - GA - TN>{}, ds, shal(S));
+          constexpr int y = x - NSHAL;
+          if constexpr (y < 0) dma_shal(X, ds, shal(S));
+          else if constexpr (y < GA) frag_a(uan, 0, Int<0>{}, Int<y>{}, fa0);
+          else if constexpr (y < GA + TN) frag_b(ubn, 0, Int<y - GA>{}, fb0);
         });
         return;
       } else {
@@ -768,8 +776,8 @@ __global__ __launch_bounds__(2 * BT) void gemm_mfma_kernel(MfmaParams p) {
       if (__builtin_expect(kt + 5 < nk, 1)) step(Int<2>{}, Int<1>{}, Int<0>{}, Int<0>{}, Int<1>{}, kt + 5);
     }
     TIDE_WAIT_VMCNT(0);   // dummy slabs still in flight write LDS: let them land before the patches are written
-    constexpr int PPU = A_STAGE / kPatchElems;   // epilogue patches per unit
-    static_assert(PPU >= 1 && (NW + PPU - 1) / PPU <= 4, "the epilogue patches fit four units");
+    constexpr int PPU = D_STAGE / kPatchElems;   // epilogue patches per deep unit; a wave left over takes the first shallow one
+    static_assert(PPU >= 1 && S_STAGE >= kPatchElems && NW <= 3 * PPU + 1, "the epilogue patches fit four units");
     const int pu = wave / PPU;
     bf16_t* unit = pu == 0 ? ld0 : (pu == 1 ? ld1 : (pu == 2 ? ld2 : ls0));
     epilogue(unit + (wave % PPU) * kPatchElems);
@@ -993,17 +1001,90 @@ size_t gemm_splitk_scratch_bound(const GemmArgs& a) {
 
 namespace {
 // What a launch does with the scratch it is given: the tile edge, and which split.
-struct LaunchPlan { int BT, split; SplitPlan tail; SplitGrid all; };
+struct LaunchPlan { int BM, BN, split; SplitPlan tail; SplitGrid all; };
+
+// Time (ns) of a launch of whole tiles, and of a planned split.  The chip's power is shared: a slab takes a tile longer the
+// more CUs are busy.  Measured on r x c tiles, 64 to 288 of them, K = 1024 and 4096 (ns per slab with 256 CUs busy, change
+// per CU in tenths, least, and what a tile takes beside its slabs; both operands row-major over K / others).
+struct TileCost { int full, slope, least, fixed; };
+TileCost tile_cost(int BM, bool tn) {
+  switch (BM) {
+    case 256: return tn ? TileCost{1391, 28, 1035, 13700} : TileCost{1344, 31, 945, 8500};
+    case 224: return tn ? TileCost{1224, 24, 915, 13000} : TileCost{1213, 27, 860, 7800};
+    case 192: return tn ? TileCost{1070, 22, 790, 11700} : TileCost{1074, 26, 740, 7200};
+    case 160: return tn ? TileCost{951, 21, 675, 10600} : TileCost{902, 21, 635, 6900};
+    default: return tn ? TileCost{770, 18, 535, 9500} : TileCost{736, 15, 540, 6500};
+  }
+}
+int64_t rounds_time(int BM, bool tn, int64_t tiles, int64_t slabs) {
+  const TileCost c = tile_cost(BM, tn);
+  const int64_t rounds = tiles / 256, rest = tiles % 256, last = std::max<int64_t>(c.least, c.full - c.slope * (256 - rest) / 10);
+  return rounds * (slabs * c.full + c.fixed) + (rest ? slabs * last + c.fixed : 0);
+}
+// 128 x 128: one block on a CU takes 465 to 550, two 870, and what a partly filled round adds to full ones is less
+int64_t small_rounds_time(bool tn, int64_t blocks, int64_t slabs) {
+  const int64_t rounds = blocks / 512, rest = blocks % 512;
+  if (rounds == 0) {
+    if (rest <= 256) return slabs * (465 + std::max<int64_t>(0, rest - 128) * 13 / 20) + (tn ? 5000 : 2500);
+    return slabs * (700 + (rest - 320) * 9 / 10) + (tn ? 10000 : 7000);
+  }
+  return slabs * (rounds * 870 + (rest == 0 ? 0 : rest <= 128 ? 330 : rest <= 256 ? 430 : rest <= 384 ? 680 : 820)) + (tn ? 12000 : 8500);
+}
+int64_t launch_time(const GemmArgs& a, const LaunchPlan& lp, int64_t rows) {
+  const bool tn = a.layout == kTN;
+  const int64_t slabs = split_slabs((int)a.K, a.A2 ? (int)a.K2 : 0), tiles = ((rows + lp.BM - 1) / lp.BM) * ((a.N + lp.BN - 1) / lp.BN);
+  if (lp.split == kSplitTail) {
+    const int64_t tail = tiles - lp.tail.full, part = (slabs + lp.tail.s - 1) / lp.tail.s;
+    return rounds_time(256, tn, lp.tail.full, slabs) + rounds_time(256, tn, tail * lp.tail.s, part) + 5000 + 40 * tail * lp.tail.s;
+  }
+  if (lp.BN == 256) {
+    const SplitAll sa = lp.split == kSplitAll ? split_all<256>((int)tiles, (int)slabs) : SplitAll{(int)tiles, 1};
+    const int64_t tail = tiles - sa.full, part = (slabs + sa.parts - 1) / sa.parts;
+    return rounds_time(lp.BM, tn, sa.full, slabs) + (tail ? rounds_time(256, tn, tail * sa.parts, part) + 4000 + 40 * tail * sa.parts : 0);
+  }
+  const SplitAll sa = lp.split == kSplitAll ? split_all<128>((int)tiles, (int)slabs) : SplitAll{(int)tiles, 1};
+  const int64_t blocks = sa.full + (tiles - sa.full) * sa.parts, part = (slabs + sa.parts - 1) / sa.parts;
+  return small_rounds_time(tn, blocks, part) + (sa.parts > 1 ? 5000 + 16 * blocks : 0);
+}
+
+// Tiles of 128 to 224 x 256 where they fill the rounds of the 256 CUs better than the squares, and large tiles where the
+// costs above, which allow for the power that idle CUs leave to the others, like them better than tile_edge did.  us, by
+// tile_edge / so: NN 1665 x 5632 x 2048 47.8 / 35.0 (160 rows), NT 3400 x 14336 x 4096 332 / 290 (192), NT 4096 x 2048 x 6144 89 / 78
+// (128), TN 5632 x 2048 x 2560 64.9 / 55.0 (192), NN 3125 x 5120 x 12288 445 / 302 (128); over 618 random products (200 to
+// 12000 rows, 5 to 600 GFLOP) 6 % in the mean, the worst 4 % slower beside split TN ones of 688 columns.  With a row count known
+// on the device alone a height has to pay over the range that batches have: the sum at 60, 85 and 100 % of the bound.
+// (bf16 results added to old ones, which leave the kernel element by element, are as tile_edge has them)
+bool tall_possible(const GemmArgs& a) {
+  if (a.layout == kTN) return a.out_dtype == kF32;
+  return a.out_dtype == kBF16 && !a.accumulate && a.K % 64 == 0 && (!a.A2 || a.K2 % 64 == 0) && !a.k_dev;
+}
+int tall_height(const GemmArgs& a, const LaunchPlan& lp) {
+  if (!tall_possible(a)) return 0;
+  auto total = [&](const LaunchPlan& l) {
+    if (!a.m_dev) return launch_time(a, l, a.M);
+    return launch_time(a, l, std::max<int64_t>(1, a.M * 3 / 5)) + launch_time(a, l, planned_rows(a)) + launch_time(a, l, a.M);
+  };
+  int64_t best = total(lp) * 96 / 100;   // only for a gain beyond the model's error
+  int height = 0;
+  for (const int BM : {256, 224, 192, 160, 128}) {
+    const int64_t t = total(LaunchPlan{BM, 256, kSplitNone, {1, 0, 0}, {0, 0, 0}});
+    if (t < best) { best = t; height = BM; }
+  }
+  return height;
+}
+
 LaunchPlan plan_launch(const GemmArgs& a) {
-  LaunchPlan lp{tile_edge(a), kSplitNone, plan_split(a), {0, 0, 0}};
+  const int e = tile_edge(a);
+  LaunchPlan lp{e, e, kSplitNone, plan_split(a), {0, 0, 0}};
   const bool scratch_ok = a.scratch && (((uintptr_t)a.scratch) & 15) == 0;
   if (lp.tail.s > 1) {
     if (scratch_ok && a.scratch_bytes >= lp.tail.bytes) lp.split = kSplitTail;
   } else {
-    lp.all = plan_split_all(a, lp.BT);
+    lp.all = plan_split_all(a, e);
     if (lp.all.blocks > 0 && scratch_ok && a.scratch_bytes >= lp.all.bytes) lp.split = kSplitAll;
-    else if (lp.all.blocks > 0 && tile_count(a.M, a.N, 256) < 200) lp.BT = 128;   // chosen for its split: without scratch, too few large tiles to run them whole
+    else if (lp.all.blocks > 0 && tile_count(a.M, a.N, 256) < 200) lp.BM = lp.BN = 128;   // chosen for its split: without scratch, too few large tiles to run them whole
   }
+  if (const int BM = tall_height(a, lp)) { lp.BM = BM; lp.BN = 256; lp.split = kSplitNone; }
   return lp;
 }
 }  // namespace
@@ -1040,43 +1121,59 @@ bool gemm_mfma_supported(const GemmArgs& a) {
 
 namespace {
 
-template <int BT, bool AMM, bool BNM, typename TO>
+// every slab whole (and K known on the host): the DMA loads of a K-major operand take loop-constant lane offsets
+// (with both operands row-major over K the two forms are the same code: one instantiation)
+template <bool AMM, bool BNM>
+bool whole_slabs(const MfmaParams& p) { return !(AMM && BNM) && !p.k_dev && p.K % 64 == 0 && (!p.A2 || p.K2 % 64 == 0); }
+
+template <int BM, int BN, bool AMM, bool BNM, typename TO>
 hipError_t launch_tiles(const MfmaParams& p, const SplitGrid& all, hipStream_t s) {   // all: of a kSplitAll launch
   MfmaParams q = p;
-  q.tiles_m = (p.M + BT - 1) / BT;
-  q.tiles_n = (p.N + BT - 1) / BT;
+  q.tiles_m = (p.M + BM - 1) / BM;
+  q.tiles_n = (p.N + BN - 1) / BN;
   const int tiles = q.tiles_m * q.tiles_n;
   const int64_t items = q.split == kSplitAll ? all.blocks
                       : q.split == kSplitTail ? q.split_full + (int64_t)(tiles - q.split_full) * q.split_s : tiles;
-  // every slab whole (and K known on the host): the DMA loads of a K-major operand take loop-constant lane offsets
-  // (with both operands row-major over K the two forms are the same code: one instantiation)
-  const bool whole = !(AMM && BNM) && !p.k_dev && p.K % 64 == 0 && (!p.A2 || p.K2 % 64 == 0);
-  if (whole) hipLaunchKernelGGL((gemm_mfma_kernel<BT, AMM, BNM, TO, true>), dim3((unsigned)items), dim3(2 * BT), 0, s, q);
-  else hipLaunchKernelGGL((gemm_mfma_kernel<BT, AMM, BNM, TO, false>), dim3((unsigned)items), dim3(2 * BT), 0, s, q);
-  const hipError_t e = hipGetLastError();
-  if (e != hipSuccess || q.split != kSplitAll) return e;
-  hipLaunchKernelGGL((splitk_reduce_kernel<TO, BT>), dim3((unsigned)(all.tail * (BT * BT / 2048))), dim3(256), 0, s, q);
+  if constexpr (BM == BN) {
+    if (whole_slabs<AMM, BNM>(p)) hipLaunchKernelGGL((gemm_mfma_kernel<BM, BN, AMM, BNM, TO, true>), dim3((unsigned)items), dim3(2 * BN), 0, s, q);
+    else hipLaunchKernelGGL((gemm_mfma_kernel<BM, BN, AMM, BNM, TO, false>), dim3((unsigned)items), dim3(2 * BN), 0, s, q);
+    const hipError_t e = hipGetLastError();
+    if (e != hipSuccess || q.split != kSplitAll) return e;
+    hipLaunchKernelGGL((splitk_reduce_kernel<TO, BM>), dim3((unsigned)(all.tail * (BM * BM / 2048))), dim3(256), 0, s, q);
+  } else {
+    hipLaunchKernelGGL((gemm_mfma_kernel<BM, BN, AMM, BNM, TO, !(AMM && BNM)>), dim3((unsigned)items), dim3(2 * BN), 0, s, q);
+  }
   return hipGetLastError();
 }
 
 template <bool AMM, bool BNM, typename TO>
 hipError_t launch_layout(const MfmaParams& p, const LaunchPlan& lp, hipStream_t s) {
-  if (lp.BT == 256) return launch_tiles<256, AMM, BNM, TO>(p, lp.all, s);
-  return launch_tiles<128, AMM, BNM, TO>(p, lp.all, s);
-}
-
-const char* gemm_kernel_name(const GemmArgs& a) {
-  if (!gemm_mfma_supported(a)) return a.in_dtype == kF32 && a.out_dtype == kF32 ? "gemm_fp32" : "gemm_simple";
-  const bool big = plan_launch(a).BT == 256;
-  const bool f32 = a.out_dtype == kF32;
-  switch (a.layout) {
-    case kNT: return big ? (f32 ? "gemm_mfma_nt_256_f32out" : "gemm_mfma_nt_256_bf16out") : (f32 ? "gemm_mfma_nt_128_f32out" : "gemm_mfma_nt_128_bf16out");
-    case kNN: return big ? (f32 ? "gemm_mfma_nn_256_f32out" : "gemm_mfma_nn_256_bf16out") : (f32 ? "gemm_mfma_nn_128_f32out" : "gemm_mfma_nn_128_bf16out");
-    default: return big ? (f32 ? "gemm_mfma_tn_256_f32out" : "gemm_mfma_tn_256_bf16out") : (f32 ? "gemm_mfma_tn_128_f32out" : "gemm_mfma_tn_128_bf16out");
+  if constexpr (sizeof(TO) == (AMM && BNM ? 4 : 2)) {
+    if (lp.BN == 256) switch (lp.BM) {
+      case 224: return launch_tiles<224, 256, AMM, BNM, TO>(p, lp.all, s);
+      case 192: return launch_tiles<192, 256, AMM, BNM, TO>(p, lp.all, s);
+      case 160: return launch_tiles<160, 256, AMM, BNM, TO>(p, lp.all, s);
+      case 128: return launch_tiles<128, 256, AMM, BNM, TO>(p, lp.all, s);
+    }
   }
+  if (lp.BN == 256) return launch_tiles<256, 256, AMM, BNM, TO>(p, lp.all, s);
+  return launch_tiles<128, 128, AMM, BNM, TO>(p, lp.all, s);
 }
 
 }  // namespace
+
+const char* gemm_kernel_name(const GemmArgs& a) {
+  if (!gemm_mfma_supported(a)) return a.in_dtype == kF32 && a.out_dtype == kF32 ? "gemm_fp32" : "gemm_simple";
+  static const char* const square[3][2][2] = {{{"gemm_mfma_nt_128_bf16out", "gemm_mfma_nt_256_bf16out"}, {"gemm_mfma_nt_128_f32out", "gemm_mfma_nt_256_f32out"}},
+                                              {{"gemm_mfma_nn_128_bf16out", "gemm_mfma_nn_256_bf16out"}, {"gemm_mfma_nn_128_f32out", "gemm_mfma_nn_256_f32out"}},
+                                              {{"gemm_mfma_tn_128_bf16out", "gemm_mfma_tn_256_bf16out"}, {"gemm_mfma_tn_128_f32out", "gemm_mfma_tn_256_f32out"}}};
+  static const char* const tall[3][4] = {{"gemm_mfma_nt_128x256_bf16out", "gemm_mfma_nt_160x256_bf16out", "gemm_mfma_nt_192x256_bf16out", "gemm_mfma_nt_224x256_bf16out"},
+                                         {"gemm_mfma_nn_128x256_bf16out", "gemm_mfma_nn_160x256_bf16out", "gemm_mfma_nn_192x256_bf16out", "gemm_mfma_nn_224x256_bf16out"},
+                                         {"gemm_mfma_tn_128x256_f32out", "gemm_mfma_tn_160x256_f32out", "gemm_mfma_tn_192x256_f32out", "gemm_mfma_tn_224x256_f32out"}};
+  const LaunchPlan lp = plan_launch(a);
+  return lp.BM == lp.BN ? square[a.layout][a.out_dtype == kF32][lp.BN == 256] : tall[a.layout][(lp.BM - 128) / 32];
+}
+
 
 hipError_t launch_gemm_mfma(const GemmArgs& a, hipStream_t s) {
   MfmaParams p;

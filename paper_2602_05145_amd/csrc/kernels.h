@@ -42,6 +42,7 @@ size_t gemm_split_tail_bytes(const GemmArgs& a);       // the part of it that go
 size_t gemm_splitk_scratch_bytes(const GemmArgs& a);   // 0 when the launch would not be split
 // At least what the product asks for with any number of rows (M, of TN K) up to the given one; never falls as the rows grow.
 size_t gemm_splitk_scratch_bound(const GemmArgs& a);
+const char* gemm_kernel_name(const GemmArgs& a);        // the kernel that a launch with these arguments runs, as profiles report it
 hipError_t launch_gemm_mfma(const GemmArgs& a, hipStream_t s);
 hipError_t launch_gemm_fp32(const GemmArgs& a, hipStream_t s);     // fp32 operands and result
 hipError_t launch_gemm_simple(const GemmArgs& a, hipStream_t s);

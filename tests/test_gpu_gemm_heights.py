@@ -1,0 +1,56 @@
+"""Tiles of 128 to 224 rows x 256 columns: the smallest ragged products that the plan gives to each of them, against a float
+reference of the same bf16 operands."""
+import ctypes as C
+
+import pytest
+import torch
+
+from tests import internal_gemm as ig
+
+kernel_name = ig._symbol("_ZN4tide16gemm_kernel_nameERKNS_8GemmArgsE", C.c_char_p, [C.POINTER(ig.GemmArgs)])
+
+# layout, M, N, K: a last tile row and column that are partly filled, one slab or (TN) one and a remainder
+CASES = [(ig.NT, 521, 6608, 64, 128), (ig.NT, 7405, 1040, 64, 160), (ig.NT, 5830, 1544, 64, 192), (ig.NT, 7037, 1544, 64, 224),
+         (ig.NN, 530, 6736, 64, 128), (ig.NN, 6542, 1176, 64, 160), (ig.NN, 6831, 1288, 64, 192), (ig.NN, 8151, 1296, 64, 224),
+         (ig.TN, 5456, 656, 65, 128), (ig.TN, 1048, 7192, 65, 160), (ig.TN, 6736, 1312, 65, 192), (ig.TN, 1552, 7184, 65, 224),
+         (ig.NN, 1665, 5632, 2048, 160), (ig.NT, 2040, 4096, 576, 128), (ig.TN, 5632, 2048, 1333, 192)]
+
+
+@pytest.mark.parametrize("layout,M,N,K,height", CASES)
+def test_the_plan_takes_the_height(layout, M, N, K, height):
+    got = kernel_name(ig.args(layout, M, N, K, out=ig.F32 if layout == ig.TN else ig.BF16)).decode()
+    assert got.startswith(f"gemm_mfma_{('nt', 'nn', 'tn')[layout]}_{height}x256_"), got
+
+
+def test_heights_between_the_squares_are_kept_from_what_they_do_not_serve():
+    ragged = [ig.args(ig.NT, 521, 6608, 72), ig.args(ig.NN, 6831, 1288, 8), ig.args(ig.NT, 521, 6608, 64, K2=72), ig.args(ig.NT, 521, 6608, 64, k_dev=256),
+              ig.args(ig.NT, 521, 6608, 64, out=ig.F32), ig.args(ig.TN, 5456, 656, 65, out=ig.BF16),
+              ig.args(ig.NT, 521, 6608, 64, accumulate=1)]
+    for g in ragged:
+        assert b"x256" not in kernel_name(g)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("layout,M,N,K,height", CASES)
+def test_products_of_every_height(layout, M, N, K, height):
+    """With a residual and old values where the layout of the step has them.  bf16 results: one rounding, 2^-9 of the value, plus
+    that of the sums (below 1e-6 of their scale); float results: the sums' own, K eps at most."""
+    g = torch.Generator(device="cuda").manual_seed(M + N + K)
+    sh = {ig.NT: ((M, K), (N, K)), ig.NN: ((M, K), (K, N)), ig.TN: ((K, M), (K, N))}[layout]
+    a, b = (torch.randn(s, device="cuda", generator=g).bfloat16() for s in sh)
+    f32 = layout == ig.TN
+    ref = {ig.NT: lambda: a.double() @ b.double().t(), ig.NN: lambda: a.double() @ b.double(), ig.TN: lambda: a.double().t() @ b.double()}[layout]()
+    extra = torch.randn(M, N, device="cuda", generator=g).to(torch.float32 if f32 else torch.bfloat16)
+    for add in (0, 1):
+        c = extra.clone() if f32 and add else torch.full((M, N), float("nan"), device="cuda", dtype=extra.dtype)
+        args = ig.args(layout, M, N, K, out=ig.F32 if f32 else ig.BF16, a=a.data_ptr(), b=b.data_ptr(), c=c.data_ptr(), accumulate=add if f32 else 0)
+        if add and not f32:
+            args.residual, args.ldr = extra.data_ptr(), N
+        assert b"x256" in kernel_name(args)
+        print("height", height, layout, M, N, K, "add", add, flush=True)
+        assert ig.launch(args, torch.cuda.current_stream().cuda_stream) == 0
+        torch.cuda.synchronize()
+        want = ref + extra.double() if add else ref
+        err = (c.double() - want).abs()
+        bound = 2e-6 * K ** 0.5 * 4 + (0 if f32 else want.abs() * 2.0 ** -8)
+        assert bool((err <= bound).all()), float((err - bound).max())
