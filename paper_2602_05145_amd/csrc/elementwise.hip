@@ -1365,10 +1365,7 @@ __global__ __launch_bounds__(256) void adamw_kernel(AdamDev a) {
   if (base >= t.n) return;
   T* p = (T*)t.p;
   float* w = (sizeof(T) == 2) ? t.master : (float*)t.p;
-  const float omb1 = 1.f - a.beta1, omb2 = 1.f - a.beta2;
-  // (locals: writing into the by-value argument would move the whole struct to scratch memory)
-  const float lr = a.dyn ? a.dyn[0] : a.lr, decay = a.dyn ? a.dyn[1] : a.decay;
-  const float inv_bc1 = a.dyn ? a.dyn[2] : a.inv_bc1, inv_sqrt_bc2 = a.dyn ? a.dyn[3] : a.inv_sqrt_bc2;
+  const AdamRate rate = adam_rate(a);
   if (base + (kAdamGroups - 1) * 2048 + 8 <= t.n) {
     // every load of the thread's groups is issued before the first value is used
     float g[kAdamGroups][8], m[kAdamGroups][8], v[kAdamGroups][8], th[kAdamGroups][8];
@@ -1384,12 +1381,7 @@ __global__ __launch_bounds__(256) void adamw_kernel(AdamDev a) {
     for (int k = 0; k < kAdamGroups; ++k) {
       const int64_t i0 = base + k * 2048;
 #pragma unroll
-      for (int j = 0; j < 8; ++j) {
-        m[k][j] = a.beta1 * m[k][j] + omb1 * g[k][j];
-        v[k][j] = a.beta2 * v[k][j] + omb2 * g[k][j] * g[k][j];
-        const float denom = sqrtf(v[k][j]) * inv_sqrt_bc2 + a.eps;
-        th[k][j] = th[k][j] * decay - lr * (m[k][j] * inv_bc1) / denom;
-      }
+      for (int j = 0; j < 8; ++j) adam_update(rate, g[k][j], m[k][j], v[k][j], th[k][j]);
       float4* qm = reinterpret_cast<float4*>(t.m + i0);
       float4* qv = reinterpret_cast<float4*>(t.v + i0);
       float4* qw = reinterpret_cast<float4*>(w + i0);
@@ -1404,11 +1396,8 @@ __global__ __launch_bounds__(256) void adamw_kernel(AdamDev a) {
   } else {
     for (int k = 0; k < kAdamGroups; ++k)
       for (int64_t i = base + k * 2048; i < min(base + k * 2048 + 8, t.n); ++i) {
-        const float g = t.g[i];
-        const float m = a.beta1 * t.m[i] + omb1 * g;
-        const float v = a.beta2 * t.v[i] + omb2 * g * g;
-        const float denom = sqrtf(v) * inv_sqrt_bc2 + a.eps;
-        const float th = w[i] * decay - lr * (m * inv_bc1) / denom;
+        float m = t.m[i], v = t.v[i], th = w[i];
+        adam_update(rate, t.g[i], m, v, th);
         t.m[i] = m;
         t.v[i] = v;
         w[i] = th;
@@ -1429,7 +1418,7 @@ hipError_t launch_adamw(const AdamArgs& a, hipStream_t s) {
   for (int i = a.nt; i < kMaxAdamTensors; ++i) d.t[i] = AdamTensor{nullptr, nullptr, nullptr, nullptr, nullptr, 0};
   for (int i = a.nt; i <= kMaxAdamTensors; ++i) d.blk_start[i] = nb;
   d.lr = a.lr; d.beta1 = a.beta1; d.beta2 = a.beta2; d.eps = a.eps;
-  d.decay = 1.0f - a.lr * a.wd;
+  d.decay = a.decay;
   d.inv_bc1 = a.inv_bc1; d.inv_sqrt_bc2 = a.inv_sqrt_bc2;
   d.dyn = a.dyn;
   if (nb <= 0) return hipSuccess;

@@ -70,6 +70,7 @@ struct MfmaParams {
   int split, split_s, split_full;
   float* split_scratch;
 };
+struct MfmaAdamParams : MfmaParams { AdamTarget adam; };
 enum : int { kSplitNone = 0, kSplitTail = 1, kSplitAll = 2 };
 
 // How a launch whose tiles do not fill the chip is split over K.  ns, measured on 256 x 256 and on 128 x 128 tiles:
@@ -273,6 +274,31 @@ struct Operand {
 template <int N>
 struct Int : std::integral_constant<int, N> {};
 
+// A weight's state passes through once per step, and past the caches: kept in L2 it drove out the operand panels that the
+// blocks still multiplying read there (us with plain / non-temporal loads and stores, neither alone does it: 128256 x 4096 over 1700
+// rows 3910 / 3516, over 300 3262 / 3032, 32000 x 2048 over 2560 589 / 575).
+typedef float f32x4_nt __attribute__((ext_vector_type(4)));
+__device__ __forceinline__ float4 load_once(const float* q) {
+  const f32x4_nt x = __builtin_nontemporal_load(reinterpret_cast<const f32x4_nt*>(q));
+  return make_float4(x.x, x.y, x.z, x.w);
+}
+__device__ __forceinline__ void store_once(float* q, float4 v) {
+  const f32x4_nt x = {v.x, v.y, v.z, v.w};
+  __builtin_nontemporal_store(x, reinterpret_cast<f32x4_nt*>(q));
+}
+// four weights' update: g their gradient, m / v / th as loaded, at their offset
+__device__ __forceinline__ void adam_store(const AdamTarget& t, const AdamRate& rate, float* C, size_t at, float4 g, float4 m, float4 v, float4 th) {
+  adam_update(rate, g.x, m.x, v.x, th.x);
+  adam_update(rate, g.y, m.y, v.y, th.y);
+  adam_update(rate, g.z, m.z, v.z, th.z);
+  adam_update(rate, g.w, m.w, v.w, th.w);
+  store_once(C + at, g);
+  store_once(t.m + at, m);
+  store_once(t.v + at, v);
+  store_once(t.master + at, th);
+  *reinterpret_cast<uint2*>((bf16_t*)t.w + at) = make_uint2(f2bf2(th.x, th.y), f2bf2(th.z, th.w));
+}
+
 }  // namespace
 
 // ------------------------------------------------------------------------------------------------
@@ -294,8 +320,8 @@ struct Int : std::integral_constant<int, N> {};
 // ------------------------------------------------------------------------------------------------
 typedef float f32x4_t __attribute__((ext_vector_type(4)));
 
-template <int BM, int BN, bool AMM, bool BNM, typename TO, bool KWHOLE>
-__global__ __launch_bounds__(2 * BN) void gemm_mfma_kernel(MfmaParams p) {
+template <int BM, int BN, bool AMM, bool BNM, typename TO, bool KWHOLE, bool ADAM = false>
+__global__ __launch_bounds__(2 * BN) void gemm_mfma_kernel(std::conditional_t<ADAM, MfmaAdamParams, MfmaParams> p) {
   static_assert(BN == 256 ? BM % 32 == 0 && BM >= 128 && BM <= 256 : BN == 128 && BM == 128, "tile edges");
   constexpr int BK = 64, WAVES_M = 2, WAVES_N = BN / 64, NW = WAVES_M * WAVES_N;
   constexpr int WM = BM / WAVES_M, WN = BN / WAVES_N;   // BM / 2 x 64
@@ -315,7 +341,7 @@ __global__ __launch_bounds__(2 * BN) void gemm_mfma_kernel(MfmaParams p) {
 
   if (p.m_dev) p.M = max(0, min(p.M, *p.m_dev - p.m_off));
   if (p.k_dev) p.K = max(0, min(p.K, *p.k_dev - p.k_off));
-  if (p.K == 0 && p.K2 == 0 && p.accumulate && p.split != kSplitTail) return;   // nothing to add
+  if (p.K == 0 && p.K2 == 0 && p.accumulate && p.split != kSplitTail && !ADAM) return;   // nothing to add
 
   int tile_m, tile_n;
   int part = 0, nparts = 1, tail_index = 0, ntail = 0;   // split over K (see MfmaParams)
@@ -423,6 +449,50 @@ __global__ __launch_bounds__(2 * BN) void gemm_mfma_kernel(MfmaParams p) {
           if (m0 + row < p.M && n0 + col < p.N) *reinterpret_cast<f32x4_t*>(out + row * BN + col) = acc[i][j];
         }
       return;
+    }
+    if constexpr (ADAM) {
+      if (nparts == 1) {
+        // The weight's update with the gradient still in the accumulators.  Sixteen rows of the wave at a time go through its
+        // LDS patch, so that every access of the five float arrays is a 256-byte row segment; the old values of those rows are
+        // requested before the patch is written.  Bound by memory, like the separate pass, which reads the gradient again: 34
+        // bytes per weight in two kernels, 30 here (128256 x 4096 over 1400 rows 1.41 + 2.89 ms, 3.21 so; 5632 x 2048 over 2500 53 + 66 us,
+        // 112).  Two rows of four loads instead of four in flight, or the CUs started in 2 to 16 phases: no gain.
+        __builtin_amdgcn_s_barrier();
+        constexpr int PF = WN + 4, PIECES = WN / 4, NT = 16 * PIECES / 64;
+        float* patch = reinterpret_cast<float*>(patch_mem);
+        float* Cf = reinterpret_cast<float*>(C);
+        const AdamRate rate = adam_rate(p.adam);
+#pragma unroll
+        for (int i = 0; i < TM; ++i) {
+          float4 m[NT], v[NT], th[NT], old[NT];
+#pragma unroll
+          for (int t = 0; t < NT; ++t) {
+            const int pc = lane + 64 * t, gm = wm0 + 16 * i + pc / PIECES, gn = wn0 + pc % PIECES * 4;
+            const size_t at = (size_t)gm * p.ldc + gn;
+            m[t] = v[t] = th[t] = old[t] = make_float4(0.f, 0.f, 0.f, 0.f);
+            if (gm < p.M && gn < p.N) {
+              m[t] = load_once(p.adam.m + at);
+              v[t] = load_once(p.adam.v + at);
+              th[t] = load_once(p.adam.master + at);
+              if (p.accumulate) old[t] = *reinterpret_cast<const float4*>(Cf + at);
+            }
+          }
+#pragma unroll
+          for (int j = 0; j < TN; ++j) *reinterpret_cast<f32x4_t*>(patch + lc * PF + 16 * j + 4 * lg) = acc[i][j];
+#pragma unroll
+          for (int t = 0; t < NT; ++t) {
+            const int pc = lane + 64 * t, row = pc / PIECES, gm = wm0 + 16 * i + row, gn = wn0 + pc % PIECES * 4;
+            if (gm < p.M && gn < p.N) {
+              const size_t at = (size_t)gm * p.ldc + gn;
+              const float4 a = *reinterpret_cast<const float4*>(patch + row * PF + pc % PIECES * 4);
+              float4 g = make_float4(alpha * a.x, alpha * a.y, alpha * a.z, alpha * a.w);
+              if (p.accumulate) { g.x += old[t].x; g.y += old[t].y; g.z += old[t].z; g.w += old[t].w; }
+              adam_store(p.adam, rate, Cf, at, g, m[t], v[t], th[t]);
+            }
+          }
+        }
+        return;
+      }
     }
     bool staged = false;
     if constexpr (sizeof(TO) == 2) {
@@ -787,7 +857,8 @@ __global__ __launch_bounds__(2 * BN) void gemm_mfma_kernel(MfmaParams p) {
 // C[tile] += the partial sums of the later parts of every split tile, in the order of the parts (deterministic).
 // Eight blocks per split tile (32 rows each); 256 threads, a thread adds 4 consecutive columns of 4 rows at a
 // time, with the old values and every part's addends of those rows requested before the first sum.
-__global__ __launch_bounds__(256) void splitk_fixup_kernel(float* __restrict__ C, int ldc, int M, int N, int tiles_n,
+template <bool ADAM>
+__global__ __launch_bounds__(256) void splitk_fixup_kernel(AdamTarget adam, float* __restrict__ C, int ldc, int M, int N, int tiles_n,
                                                            int split_full, int split_s, const float* __restrict__ scratch) {
   const int tiles_m = (M + 255) / 256;
   const int ntail = tiles_m * tiles_n - split_full;
@@ -798,15 +869,25 @@ __global__ __launch_bounds__(256) void splitk_fixup_kernel(float* __restrict__ C
   const int c4 = (threadIdx.x & 63) * 4, r0 = rblk * 32 + (threadIdx.x >> 6);
   const int gn = n0 + c4;
   if (gn >= N) return;
+  AdamRate rate;
+  if constexpr (ADAM) rate = adam_rate(adam);
 #pragma unroll
   for (int half = 0; half < 2; ++half) {
-    float4 v[4];
+    float4 v[4], am[4], av[4], ath[4];
     bool ok[4];
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
       const int r = r0 + (half * 4 + i) * 4;
       ok[i] = m0 + r < M;
       v[i] = ok[i] ? *reinterpret_cast<const float4*>(C + (size_t)(m0 + r) * ldc + gn) : make_float4(0.f, 0.f, 0.f, 0.f);
+      if constexpr (ADAM) {
+        if (ok[i]) {
+          const size_t at = (size_t)(m0 + r) * ldc + gn;
+          am[i] = load_once(adam.m + at);
+          av[i] = load_once(adam.v + at);
+          ath[i] = load_once(adam.master + at);
+        }
+      }
     }
     for (int j = 1; j < split_s; ++j) {
       float4 x[4];
@@ -821,15 +902,17 @@ __global__ __launch_bounds__(256) void splitk_fixup_kernel(float* __restrict__ C
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
       const int r = r0 + (half * 4 + i) * 4;
-      if (ok[i]) *reinterpret_cast<float4*>(C + (size_t)(m0 + r) * ldc + gn) = v[i];
+      if (!ok[i]) continue;
+      if constexpr (ADAM) adam_store(adam, rate, C, (size_t)(m0 + r) * ldc + gn, v[i], am[i], av[i], ath[i]);
+      else *reinterpret_cast<float4*>(C + (size_t)(m0 + r) * ldc + gn) = v[i];
     }
   }
 }
 
 // C[tile] = alpha * (the partial sums of a tile's parts, in their order) + residual + old value.  A launch that came out
 // as one part per tile has written C itself.  A block covers 2048 elements of a tile; a thread owns 8 consecutive columns.
-template <typename TO, int BT>
-__global__ __launch_bounds__(256) void splitk_reduce_kernel(MfmaParams p) {
+template <typename TO, int BT, bool ADAM = false>
+__global__ __launch_bounds__(256) void splitk_reduce_kernel(std::conditional_t<ADAM, MfmaAdamParams, MfmaParams> p) {
   constexpr int PER_ROW = BT / 8, ROWS = 256 / PER_ROW, BLOCKS = BT / ROWS;
   if (p.m_dev) p.M = max(0, min(p.M, *p.m_dev - p.m_off));
   if (p.k_dev) p.K = max(0, min(p.K, *p.k_dev - p.k_off));
@@ -844,6 +927,16 @@ __global__ __launch_bounds__(256) void splitk_reduce_kernel(MfmaParams p) {
   if (gm >= p.M || gn >= p.N) return;
   const float* src = p.split_scratch + (size_t)tail * (BT * BT) + row * BT + col;
   const size_t stride = (size_t)ntail * (BT * BT);
+  const size_t at = (size_t)gm * p.ldc + gn;
+  float4 am[2], av[2], ath[2];
+  if constexpr (ADAM) {
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+      am[h] = load_once(p.adam.m + at + 4 * h);
+      av[h] = load_once(p.adam.v + at + 4 * h);
+      ath[h] = load_once(p.adam.master + at + 4 * h);
+    }
+  }
   float v[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
   for (int j = 0; j < sa.parts; j += 4) {        // four parts' loads in flight at a time
     Raw8<float> x[4];
@@ -862,13 +955,20 @@ __global__ __launch_bounds__(256) void splitk_reduce_kernel(MfmaParams p) {
   }
   float alpha = p.alpha;
   if (p.alpha_dev) alpha *= *p.alpha_dev;
-  TO* C = (TO*)p.C + (size_t)gm * p.ldc + gn;
+  TO* C = (TO*)p.C + at;
   float r[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f}, old[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
   if (p.R) ld8((const TO*)p.R, (size_t)gm * p.ldr + gn, r);
   if (p.accumulate) ld8(C, 0, old);
 #pragma unroll
   for (int e = 0; e < 8; ++e) v[e] = alpha * v[e] + r[e] + old[e];
-  st8(C, 0, v);
+  if constexpr (ADAM) {
+    const AdamRate rate = adam_rate(p.adam);
+#pragma unroll
+    for (int h = 0; h < 2; ++h)
+      adam_store(p.adam, rate, (float*)p.C, at + 4 * h, make_float4(v[4 * h], v[4 * h + 1], v[4 * h + 2], v[4 * h + 3]), am[h], av[h], ath[h]);
+  } else {
+    st8(C, 0, v);
+  }
 }
 
 namespace {
@@ -1075,7 +1175,17 @@ int tall_height(const GemmArgs& a, const LaunchPlan& lp) {
   return height;
 }
 
-LaunchPlan plan_launch(const GemmArgs& a) {
+// With the weight's update behind it a product of few rows is bound by the weight's 30 bytes per element, and two small blocks on
+// a CU overlap one's update with the other's products: us as planned otherwise / so, 128256 x 4096 over 300 rows 3090 / 2815, over
+// 1400 3318 / 3212, over 2500 3898 / 4115; 14336 x 4096 over 1400 398 / 364; 4096 x 4096 over 700 116 / 111; 5632 x 2048 (704 blocks)
+// over 700 83 / 86.
+bool update_bound(const GemmArgs& a) {
+  const int64_t rows = a.k_dev ? (a.K * 17 + 19) / 20 : a.K;   // see planned_rows
+  return rows <= 2048 && tile_count(a.M, a.N, 128) >= 1024;
+}
+
+LaunchPlan plan_launch(const GemmArgs& a, bool adam = false) {
+  if (adam && update_bound(a)) return LaunchPlan{128, 128, kSplitNone, {1, 0, 0}, {0, 0, 0}};
   const int e = tile_edge(a);
   LaunchPlan lp{e, e, kSplitNone, plan_split(a), {0, 0, 0}};
   const bool scratch_ok = a.scratch && (((uintptr_t)a.scratch) & 15) == 0;
@@ -1128,28 +1238,33 @@ namespace {
 template <bool AMM, bool BNM>
 bool whole_slabs(const MfmaParams& p) { return !(AMM && BNM) && !p.k_dev && p.K % 64 == 0 && (!p.A2 || p.K2 % 64 == 0); }
 
-template <int BM, int BN, bool AMM, bool BNM, typename TO>
-hipError_t launch_tiles(const MfmaParams& p, const SplitGrid& all, hipStream_t s) {   // all: of a kSplitAll launch
-  MfmaParams q = p;
+template <int BM, int BN, bool AMM, bool BNM, typename TO, typename P>
+hipError_t launch_tiles(const P& p, const SplitGrid& all, hipStream_t s) {   // all: of a kSplitAll launch
+  constexpr bool ADAM = std::is_same_v<P, MfmaAdamParams>;
+  P q = p;
   q.tiles_m = (p.M + BM - 1) / BM;
   q.tiles_n = (p.N + BN - 1) / BN;
   const int tiles = q.tiles_m * q.tiles_n;
   const int64_t items = q.split == kSplitAll ? all.blocks
                       : q.split == kSplitTail ? q.split_full + (int64_t)(tiles - q.split_full) * q.split_s : tiles;
   if constexpr (BM == BN) {
-    if (whole_slabs<AMM, BNM>(p)) hipLaunchKernelGGL((gemm_mfma_kernel<BM, BN, AMM, BNM, TO, true>), dim3((unsigned)items), dim3(2 * BN), 0, s, q);
-    else hipLaunchKernelGGL((gemm_mfma_kernel<BM, BN, AMM, BNM, TO, false>), dim3((unsigned)items), dim3(2 * BN), 0, s, q);
+    if constexpr (!ADAM) {
+      if (whole_slabs<AMM, BNM>(p)) hipLaunchKernelGGL((gemm_mfma_kernel<BM, BN, AMM, BNM, TO, true>), dim3((unsigned)items), dim3(2 * BN), 0, s, q);
+      else hipLaunchKernelGGL((gemm_mfma_kernel<BM, BN, AMM, BNM, TO, false>), dim3((unsigned)items), dim3(2 * BN), 0, s, q);
+    } else {
+      hipLaunchKernelGGL((gemm_mfma_kernel<BM, BN, AMM, BNM, TO, false, true>), dim3((unsigned)items), dim3(2 * BN), 0, s, q);
+    }
     const hipError_t e = hipGetLastError();
     if (e != hipSuccess || q.split != kSplitAll) return e;
-    hipLaunchKernelGGL((splitk_reduce_kernel<TO, BM>), dim3((unsigned)(all.tail * (BM * BM / 2048))), dim3(256), 0, s, q);
+    hipLaunchKernelGGL((splitk_reduce_kernel<TO, BM, ADAM>), dim3((unsigned)(all.tail * (BM * BM / 2048))), dim3(256), 0, s, q);
   } else {
-    hipLaunchKernelGGL((gemm_mfma_kernel<BM, BN, AMM, BNM, TO, !(AMM && BNM)>), dim3((unsigned)items), dim3(2 * BN), 0, s, q);
+    hipLaunchKernelGGL((gemm_mfma_kernel<BM, BN, AMM, BNM, TO, !(AMM && BNM), ADAM>), dim3((unsigned)items), dim3(2 * BN), 0, s, q);
   }
   return hipGetLastError();
 }
 
-template <bool AMM, bool BNM, typename TO>
-hipError_t launch_layout(const MfmaParams& p, const LaunchPlan& lp, hipStream_t s) {
+template <bool AMM, bool BNM, typename TO, typename P>
+hipError_t launch_layout(const P& p, const LaunchPlan& lp, hipStream_t s) {
   if constexpr (sizeof(TO) == (AMM && BNM ? 4 : 2)) {
     if (lp.BN == 256) switch (lp.BM) {
       case 224: return launch_tiles<224, 256, AMM, BNM, TO>(p, lp.all, s);
@@ -1176,9 +1291,30 @@ const char* gemm_kernel_name(const GemmArgs& a) {
   return lp.BM == lp.BN ? square[a.layout][a.out_dtype == kF32][lp.BN == 256] : tall[a.layout][(lp.BM - 128) / 32];
 }
 
+const char* gemm_adam_kernel_name(const GemmArgs& a) {
+  static const char* const updating[6] = {"gemm_mfma_tn_128x256_adamw", "gemm_mfma_tn_160x256_adamw", "gemm_mfma_tn_192x256_adamw", "gemm_mfma_tn_224x256_adamw",
+                                          "gemm_mfma_tn_256_adamw", "gemm_mfma_tn_128_adamw"};
+  const LaunchPlan lp = plan_launch(a, true);
+  return updating[lp.BN == 128 ? 5 : (lp.BM - 128) / 32];
+}
 
-hipError_t launch_gemm_mfma(const GemmArgs& a, hipStream_t s) {
-  MfmaParams p;
+
+namespace {
+// algorithmic work of the call, for the optional profiler; fixed: the bytes of a weight's update, which do not depend on the rows that ran
+struct GemmProf {
+  ProfScope ps;
+  GemmProf(const GemmArgs& a, double fixed, hipStream_t s) : ps(prof_enabled() ? (fixed > 0 ? gemm_adam_kernel_name(a) : gemm_kernel_name(a)) : "", flops(a), bytes(a) + fixed, s) {
+    if (a.m_dev) prof_dynamic(a.m_dev, a.m_off, a.M, 0, fixed);
+    else if (a.k_dev) prof_dynamic(a.k_dev, a.k_off, a.K, 0, fixed);
+  }
+  static double k_all(const GemmArgs& a) { return (double)a.K + (a.A2 ? (double)a.K2 : 0.0); }
+  static double flops(const GemmArgs& a) { return 2.0 * (double)a.M * (double)a.N * k_all(a); }
+  static double bytes(const GemmArgs& a) {
+    return (double)dtype_size(a.in_dtype) * k_all(a) * ((double)a.M + (double)a.N) +
+           (double)dtype_size(a.out_dtype) * (double)a.M * (double)a.N * (1.0 + (a.accumulate ? 1.0 : 0.0) + (a.residual ? 1.0 : 0.0));
+  }
+};
+void fill_params(MfmaParams& p, const GemmArgs& a, const LaunchPlan& lp) {
   p.A = (const bf16_t*)a.A; p.B = (const bf16_t*)a.B;
   p.A2 = (const bf16_t*)a.A2; p.B2 = (const bf16_t*)a.B2;
   p.C = a.C; p.R = a.residual; p.alpha_dev = a.alpha_dev;
@@ -1186,9 +1322,22 @@ hipError_t launch_gemm_mfma(const GemmArgs& a, hipStream_t s) {
   p.lda = (int)a.lda; p.ldb = (int)a.ldb; p.ldc = (int)a.ldc; p.ldr = (int)a.ldr;
   p.alpha = a.alpha; p.accumulate = a.accumulate; p.tiles_m = p.tiles_n = 0;
   p.m_dev = a.m_dev; p.m_off = (int)a.m_off; p.k_dev = a.k_dev; p.k_off = (int)a.k_off;
-  const LaunchPlan lp = plan_launch(a);
   p.split = lp.split; p.split_s = lp.split == kSplitTail ? lp.tail.s : 1; p.split_full = lp.split == kSplitTail ? lp.tail.full : 0;
   p.split_scratch = lp.split != kSplitNone ? (float*)a.scratch : nullptr;
+}
+template <bool ADAM>
+hipError_t launch_fixup(const MfmaParams& p, const AdamTarget& t, hipStream_t s) {
+  const int tiles_n = (p.N + 255) / 256, ntail = ((p.M + 255) / 256) * tiles_n - p.split_full;
+  hipLaunchKernelGGL(splitk_fixup_kernel<ADAM>, dim3((unsigned)ntail * 8u), dim3(256), 0, s, t, (float*)p.C, p.ldc, p.M, p.N, tiles_n,
+                     p.split_full, p.split_s, p.split_scratch);
+  return hipGetLastError();
+}
+}  // namespace
+
+hipError_t launch_gemm_mfma(const GemmArgs& a, hipStream_t s) {
+  MfmaParams p;
+  const LaunchPlan lp = plan_launch(a);
+  fill_params(p, a, lp);
   const bool f32out = a.out_dtype == kF32;
   hipError_t e = hipErrorInvalidValue;
   switch (a.layout) {
@@ -1196,23 +1345,28 @@ hipError_t launch_gemm_mfma(const GemmArgs& a, hipStream_t s) {
     case kNN: e = f32out ? launch_layout<false, true, float>(p, lp, s) : launch_layout<false, true, bf16_t>(p, lp, s); break;
     case kTN: e = f32out ? launch_layout<true, true, float>(p, lp, s) : launch_layout<true, true, bf16_t>(p, lp, s); break;
   }
-  if (e != hipSuccess || p.split != kSplitTail) return e;
-  const int tiles_n = (p.N + 255) / 256;
-  const int ntail = ((p.M + 255) / 256) * tiles_n - p.split_full;
-  hipLaunchKernelGGL(splitk_fixup_kernel, dim3((unsigned)ntail * 8u), dim3(256), 0, s, (float*)p.C, p.ldc, p.M, p.N, tiles_n,
-                     p.split_full, p.split_s, p.split_scratch);
-  return hipGetLastError();
+  return e != hipSuccess || p.split != kSplitTail ? e : launch_fixup<false>(p, AdamTarget{}, s);
+}
+
+bool gemm_adam_supported(const GemmArgs& a, const AdamTarget& t) {
+  return a.layout == kTN && a.out_dtype == kF32 && !a.residual && !a.A2 && gemm_mfma_supported(a) && a.N % 8 == 0 && a.ldc % 8 == 0 &&
+         !(((uintptr_t)a.C | (uintptr_t)t.m | (uintptr_t)t.v | (uintptr_t)t.master | (uintptr_t)t.w) & 15);
+}
+
+hipError_t launch_gemm_adam(const GemmArgs& a, const AdamTarget& t, hipStream_t s) {
+  if (!gemm_adam_supported(a, t)) return hipErrorInvalidValue;
+  MfmaAdamParams p;
+  const LaunchPlan lp = plan_launch(a, true);
+  fill_params(p, a, lp);
+  p.adam = t;
+  // beside the product's own: the two moments and the master copy read and written, the weight written
+  const GemmProf ps(a, 26.0 * (double)a.M * (double)a.N, s);
+  const hipError_t e = launch_layout<true, true, float>(p, lp, s);
+  return e != hipSuccess || p.split != kSplitTail ? e : launch_fixup<true>(p, t, s);
 }
 
 hipError_t launch_gemm(const GemmArgs& a, hipStream_t s) {
-  // algorithmic work of the call, for the optional profiler
-  const double k = (double)a.K + (a.A2 ? (double)a.K2 : 0.0);
-  const double es_in = (double)dtype_size(a.in_dtype), es_out = (double)dtype_size(a.out_dtype);
-  const double bytes = es_in * k * ((double)a.M + (double)a.N) +
-                       es_out * (double)a.M * (double)a.N * (1.0 + (a.accumulate ? 1.0 : 0.0) + (a.residual ? 1.0 : 0.0));
-  ProfScope ps(prof_enabled() ? gemm_kernel_name(a) : "", 2.0 * (double)a.M * (double)a.N * k, bytes, s);
-  if (a.m_dev) prof_dynamic(a.m_dev, a.m_off, a.M);
-  else if (a.k_dev) prof_dynamic(a.k_dev, a.k_off, a.K);
+  const GemmProf ps(a, 0, s);
   if (gemm_mfma_supported(a)) return launch_gemm_mfma(a, s);
   return a.in_dtype == kF32 && a.out_dtype == kF32 ? launch_gemm_fp32(a, s) : launch_gemm_simple(a, s);
 }

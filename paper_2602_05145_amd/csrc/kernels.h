@@ -47,6 +47,18 @@ hipError_t launch_gemm_mfma(const GemmArgs& a, hipStream_t s);
 hipError_t launch_gemm_fp32(const GemmArgs& a, hipStream_t s);     // fp32 operands and result
 hipError_t launch_gemm_simple(const GemmArgs& a, hipStream_t s);
 hipError_t launch_gemm(const GemmArgs& a, hipStream_t s);  // picks among the three
+// A weight gradient (TN, float result) whose AdamW update follows in the same launch: the product's epilogue holds the final
+// gradient, so it is written once and never read back.  m, v and master share C's layout, w is the bf16 weight re-rounded from
+// the master copy; dyn as in AdamArgs.
+struct AdamTarget {
+  float *m, *v, *master;
+  void* w;
+  const float* dyn;
+  float lr, decay, beta1, beta2, eps, inv_bc1, inv_sqrt_bc2;
+};
+const char* gemm_adam_kernel_name(const GemmArgs& a);
+bool gemm_adam_supported(const GemmArgs& a, const AdamTarget& t);
+hipError_t launch_gemm_adam(const GemmArgs& a, const AdamTarget& t, hipStream_t s);
 constexpr int kMaxGemmGroup = 6;
 hipError_t launch_gemm_group(const GemmArgs* a, int n, hipStream_t s);  // independent products, in one launch where small
 
@@ -131,7 +143,7 @@ constexpr int kMaxAdamTensors = 11;   // the ten tensors of the draft and W_in o
 struct AdamArgs {
   AdamTensor t[kMaxAdamTensors];
   int nt;
-  float lr, beta1, beta2, eps, wd, inv_bc1, inv_sqrt_bc2;
+  float lr, decay, beta1, beta2, eps, inv_bc1, inv_sqrt_bc2;   // decay = 1 - lr * weight decay
   int dtype;
   // optional (device): {lr, 1 - lr * wd, 1 / (1 - beta1^t), 1 / sqrt(1 - beta2^t)} written by launch_adam_schedule;
   // when set, the kernel takes these four from device memory instead of the host values above

@@ -122,6 +122,21 @@ __device__ __forceinline__ float block_sum_lds(float v, float* red) {
   return t;
 }
 
+// One element of AdamW: g is the gradient, th the weight (float, or the master copy of a bf16 one).
+struct AdamRate { float lr, decay, beta1, beta2, eps, inv_bc1, inv_sqrt_bc2; };
+__device__ __forceinline__ void adam_update(const AdamRate& a, float g, float& m, float& v, float& th) {
+  m = a.beta1 * m + (1.f - a.beta1) * g;
+  v = a.beta2 * v + (1.f - a.beta2) * g * g;
+  const float denom = sqrtf(v) * a.inv_sqrt_bc2 + a.eps;
+  th = th * a.decay - a.lr * (m * a.inv_bc1) / denom;
+}
+// the step-dependent four from device memory where the schedule lives there (see launch_adam_schedule)
+template <typename A>
+__device__ __forceinline__ AdamRate adam_rate(const A& a) {
+  return AdamRate{a.dyn ? a.dyn[0] : a.lr, a.dyn ? a.dyn[1] : a.decay, a.beta1, a.beta2, a.eps,
+                  a.dyn ? a.dyn[2] : a.inv_bc1, a.dyn ? a.dyn[3] : a.inv_sqrt_bc2};
+}
+
 // The rows of sequence b: fixed-length batches keep sequence b in rows [b*Smax, (b+1)*Smax); packed batches
 // give the row range through cu_seqlens (device, n_seqs+1 ascending offsets) and may hold empty sequences.
 struct SeqView {

@@ -267,6 +267,32 @@ hipError_t run_gemms(GemmArgs* g, int n, char* ws, const Plan& p, hipStream_t s)
   return launch_gemm_group(g, n, s);
 }
 
+// The AdamW update of a training step: what enqueue_adamw has to update, less the weights that the products of their own
+// gradients have updated already.  A product may do that once nothing later in the step reads the old weight, i.e. after the
+// input gradient that goes through it.
+struct Update {
+  AdamTensor t[kMaxAdamTensors];
+  int nt = 0;
+  AdamTarget rate{};       // schedule and constants (its pointers are each weight's)
+  uint32_t done = 0;       // tensors that are up to date, a bit each
+};
+enum : int { kWFc, kG1, kWQkv, kWO, kG2, kWGate, kWUp, kWDown, kG3, kWLm, kWIn };   // places in Update::t
+
+// The gradient product of weight `i` (columns from `col0` on, for a weight made by two products), with the weight's update
+// where the matrix kernels can do it.  complete: the product is the weight's last one.
+hipError_t run_dw_update(const GemmArgs& g0, Update* u, int i, int64_t col0, bool complete, char* ws, const Plan& p, hipStream_t s) {
+  if (!u || g0.in_dtype != kBF16) return run_gemm(g0, ws, p, s);
+  GemmArgs g = g0;
+  g.scratch = ws + p.splitk;
+  g.scratch_bytes = p.splitk_bytes;
+  AdamTarget t = u->rate;
+  const AdamTensor& a = u->t[i];
+  t.m = a.m + col0; t.v = a.v + col0; t.master = a.master + col0; t.w = (char*)a.p + 2 * col0;
+  if (!gemm_adam_supported(g, t)) return launch_gemm(g, s);
+  if (complete) u->done |= 1u << i;
+  return launch_gemm_adam(g, t, s);
+}
+
 // How the T = batch * seq rows split into sequences: the fixed layout (cu == nullptr: `n` sequences of
 // `max_len` rows each) or a packed batch (cu = device offsets of n sequences, none longer than max_len;
 // rows outside [cu[0], cu[n]) are padding).
@@ -403,7 +429,7 @@ int enqueue_trunk(const tide_draft_config* c, const tide_draft_tensors* P, const
 // lives on the device, so every launch is sized for the worst case and trims itself.
 int enqueue_lm_head(const tide_draft_config* c, const tide_draft_tensors* P, tide_draft_tensors* G,
                     const int32_t* tokens, const uint8_t* mask, int32_t* top1, float* loss_out, float* acc_out,
-                    char* ws, const Plan& p, bool train, hipStream_t s, float grad_weight = 1.f, bool add_to_dw = false) {
+                    char* ws, const Plan& p, bool train, hipStream_t s, Update* upd = nullptr, float grad_weight = 1.f, bool add_to_dw = false) {
   const int dt = c->dtype;
   float* scal = (float*)(ws + p.scal);
   const int* cnt = (const int*)(ws + p.cnt);
@@ -445,7 +471,7 @@ int enqueue_lm_head(const tide_draft_config* c, const tide_draft_tensors* P, tid
       g.alpha = grad_weight; g.alpha_dev = scal + 1;
       g.accumulate = blk > 0 || add_to_dw;
       g.k_dev = cnt; g.k_off = r0;
-      TIDE_HIP(run_gemm(g, ws, p, s), "gemm dW_lm");
+      TIDE_HIP(run_dw_update(g, r0 + p.lm_rows >= p.T ? upd : nullptr, kWLm, 0, true, ws, p, s), "gemm dW_lm");
     }
   }
   if (train && all_rows) {
@@ -454,7 +480,7 @@ int enqueue_lm_head(const tide_draft_config* c, const tide_draft_tensors* P, tid
     g.alpha = grad_weight; g.alpha_dev = scal + 1;
     g.accumulate = add_to_dw;
     g.k_dev = cnt; g.k_off = 0;
-    TIDE_HIP(run_gemm(g, ws, p, s), "gemm dW_lm");
+    TIDE_HIP(run_dw_update(g, upd, kWLm, 0, true, ws, p, s), "gemm dW_lm");
   }
   TIDE_HIP(launch_loss_reduce(loss_rows, hit_rows, cnt, scal, loss_out, acc_out, (int*)(ws + p.status), s), "loss reduce");
   return TIDE_OK;
@@ -631,6 +657,7 @@ struct BwdOpts {
   void* dfeat_out = nullptr;
   char* prev_ws = nullptr;
   const int32_t* prev_tokens = nullptr;
+  Update* upd = nullptr;            // weights to update with their (then final) gradients
 };
 
 // Backward pass of one step from dyhat (left by the LM head) to the weight gradients.
@@ -666,8 +693,8 @@ static int enqueue_backward(const tide_draft_config* cfg, const tide_draft_tenso
   // and together they are one launch (bf16: at once, while an operand of the product before is still in a cache).
   GemmArgs later[kMaxGemmGroup];
   int n_later = 0;
-  auto run_dw = [&](const GemmArgs& g) {
-    if (dt != TIDE_DTYPE_FP32 || n_later == kMaxGemmGroup) return run_gemm(g, ws, p, s);
+  auto run_dw = [&](const GemmArgs& g, int weight) {
+    if (dt != TIDE_DTYPE_FP32 || n_later == kMaxGemmGroup) return run_dw_update(g, o.upd, weight, 0, true, ws, p, s);
     later[n_later++] = g;
     return hipSuccess;
   };
@@ -675,7 +702,7 @@ static int enqueue_backward(const tide_draft_config* cfg, const tide_draft_tenso
   TIDE_HIP(launch_rmsnorm_bwd(T, (int)p.d, ws + p.dyhat, ws + p.x2, P->g3, (const float*)(ws + p.r3), o.dx2_extra, ws + p.dx2, nullptr, dgp[2], dt, cnt, s), "rmsnorm3 bwd");
   // x2 = x1 + h W_down^T
   TIDE_HIP(run_gemm(rows_dx(p.F, p.d, ws + p.dx2, p.d, P->w_down, p.F, ws + p.dh, p.F), ws, p, s), "gemm dh");
-  TIDE_HIP(run_dw(rows_dw(p.d, p.F, ws + p.dx2, p.d, ws + p.h, p.F, G->w_down, p.F)), "gemm dW_down");
+  TIDE_HIP(run_dw(rows_dw(p.d, p.F, ws + p.dx2, p.d, ws + p.h, p.F, G->w_down, p.F), kWDown), "gemm dW_down");
   TIDE_HIP(launch_swiglu_bwd(T * p.F, ws + p.dh, ws + p.gt, ws + p.u, ws + p.gt, ws + p.u, dt, p.F, cnt, s), "swiglu bwd");
   {
     // d bn = dGate W_gate + dUp W_up: one contraction over both operand pairs
@@ -683,12 +710,12 @@ static int enqueue_backward(const tide_draft_config* cfg, const tide_draft_tenso
     g.A2 = ws + p.u; g.B2 = P->w_up; g.K2 = p.F;
     TIDE_HIP(run_gemm(g, ws, p, s), "gemm dbn");
   }
-  TIDE_HIP(run_dw(rows_dw(p.F, p.d, ws + p.gt, p.F, ws + p.bn, p.d, G->w_gate, p.d)), "gemm dW_gate");
-  TIDE_HIP(run_dw(rows_dw(p.F, p.d, ws + p.u, p.F, ws + p.bn, p.d, G->w_up, p.d)), "gemm dW_up");
+  TIDE_HIP(run_dw(rows_dw(p.F, p.d, ws + p.gt, p.F, ws + p.bn, p.d, G->w_gate, p.d), kWGate), "gemm dW_gate");
+  TIDE_HIP(run_dw(rows_dw(p.F, p.d, ws + p.u, p.F, ws + p.bn, p.d, G->w_up, p.d), kWUp), "gemm dW_up");
   TIDE_HIP(launch_rmsnorm_bwd(T, (int)p.d, ws + p.dbn, ws + p.x1, P->g2, (const float*)(ws + p.r2), ws + p.dx2, ws + p.dx1_c, nullptr, dgp[1], dt, cnt, s), "rmsnorm2 bwd");
   // x1 = x0 + A W_o^T
   TIDE_HIP(run_gemm(rows_dx(p.nq, p.d, ws + p.dx1_c, p.d, P->w_o, p.nq, ws + p.dA_c, p.nq), ws, p, s), "gemm dA");
-  TIDE_HIP(run_dw(rows_dw(p.d, p.nq, ws + p.dx1_c, p.d, ws + p.A_c, p.nq, G->w_o, p.nq)), "gemm dW_o");
+  TIDE_HIP(run_dw(rows_dw(p.d, p.nq, ws + p.dx1_c, p.d, ws + p.A_c, p.nq, G->w_o, p.nq), kWO), "gemm dW_o");
   // back to one row per position: rows that were not selected get no gradient from above (only, through
   // the attention, from the later rows that read their key and value)
   TIDE_HIP(launch_scatter_rows(T, (int)p.nq, ws + p.dA_c, ws + p.dA, (int)p.d, ws + p.dx1_c, ws + p.dx1, (const int32_t*)(ws + p.row_pos), dt, s), "scatter rows");
@@ -714,7 +741,7 @@ static int enqueue_backward(const tide_draft_config* cfg, const tide_draft_tenso
   if (q.cu) TIDE_HIP(launch_zero_padding_rows(ws + p.dqkv, q.cu, q.n, T, (int64_t)(p.nqkv * p.es), s), "zero padding rows");
   { const int rc2 = enqueue_rope(cfg, q, ws, p, ws + p.dqkv, 1, shift, s); if (rc2) return rc2; }
   TIDE_HIP(run_gemm(gemm_args(kNN, T, p.d, p.nqkv, ws + p.dqkv, p.nqkv, P->w_qkv, p.d, ws + p.da, p.d, dt, dt), ws, p, s), "gemm da");
-  TIDE_HIP(run_dw(full_dw(p.nqkv, p.d, ws + p.dqkv, p.nqkv, ws + p.a, p.d, G->w_qkv, p.d, acc)), "gemm dW_qkv");
+  TIDE_HIP(run_dw(full_dw(p.nqkv, p.d, ws + p.dqkv, p.nqkv, ws + p.a, p.d, G->w_qkv, p.d, acc), kWQkv), "gemm dW_qkv");
   TIDE_HIP(launch_rmsnorm_bwd(T, (int)p.d, ws + p.da, ws + p.x0, P->g1, (const float*)(ws + p.r1), ws + p.dx1, ws + p.dx0, nullptr, dgp[0], dt, nullptr, s), "rmsnorm1 bwd");
   {
     // the gain gradients of the three norms
@@ -726,15 +753,15 @@ static int enqueue_backward(const tide_draft_config* cfg, const tide_draft_tenso
     // x0 = [g ; e] W_in^T: dW_in = dx0^T [g ; e] (two products into the column halves of dW_in), dg = dx0 W_in[:, :d]
     // (the embedding table is frozen)
     float* dwin = (float*)tok->grad_w_in;
-    TIDE_HIP(run_gemm(full_dw(p.d, p.d, ws + p.dx0, p.d, ws + p.g0, p.d, dwin, 2 * p.d, acc), ws, p, s), "gemm dW_in (features)");
-    TIDE_HIP(run_gemm(full_dw(p.d, p.d, ws + p.dx0, p.d, ws + p.e0, p.d, dwin + p.d, 2 * p.d, acc), ws, p, s), "gemm dW_in (embeddings)");
     TIDE_HIP(run_gemm(gemm_args(kNN, T, p.d, p.d, ws + p.dx0, p.d, tok->w_in, 2 * p.d, ws + p.dg0, p.d, dt, dt), ws, p, s), "gemm dg");
+    TIDE_HIP(run_dw_update(full_dw(p.d, p.d, ws + p.dx0, p.d, ws + p.g0, p.d, dwin, 2 * p.d, acc), o.upd, kWIn, 0, false, ws, p, s), "gemm dW_in (features)");
+    TIDE_HIP(run_dw_update(full_dw(p.d, p.d, ws + p.dx0, p.d, ws + p.e0, p.d, dwin + p.d, 2 * p.d, acc), o.upd, kWIn, p.d, true, ws, p, s), "gemm dW_in (embeddings)");
     dfeat = ws + p.dg0;
   }
   if (shift == 0) {
     // the feature is Hcat W_fc^T: weight gradient only, the captured states are data (step 1 is the only one
     // that reads W_fc, so this is never an accumulation)
-    TIDE_HIP(run_dw(full_dw(p.d, p.KH, dfeat, p.d, hidden_buf, p.KH, G->w_fc, p.KH, 0)), "gemm dW_fc");
+    TIDE_HIP(run_dw(full_dw(p.d, p.KH, dfeat, p.d, hidden_buf, p.KH, G->w_fc, p.KH, 0), kWFc), "gemm dW_fc");
   } else {
     // the feature is the layer output of the step before: hand its gradient over, dense over that step's rows
     TIDE_HIP(launch_gather_rows(T, (int)p.d, dfeat, o.dfeat_out, 0, nullptr, nullptr, o.prev_tokens, (const uint8_t*)(o.prev_ws + p.mask_eff),
@@ -745,44 +772,50 @@ static int enqueue_backward(const tide_draft_config* cfg, const tide_draft_tenso
   return TIDE_OK;
 }
 
-// AdamW over all tensors in one launch
 // Device-resident schedule of a training step (the graph-capturable form): learning rate and step count live in
 // device memory, are read by the kernels of the launch, and the count is advanced on the device.
 struct DevSchedule { const float* lr; int64_t* step; float* dyn; };
 
-static int enqueue_adamw(const tide_draft_config* cfg, tide_draft_tensors* params, tide_draft_tensors* G, tide_adam_state* st,
-                         const tide_token_input* tok, float lr, const Plan& p, hipStream_t s,
-                         const DevSchedule* dev = nullptr) {
+static Update make_update(const tide_draft_config* cfg, tide_draft_tensors* params, tide_draft_tensors* G, tide_adam_state* st,
+                          const tide_token_input* tok, float lr, const Plan& p, const DevSchedule* dev) {
   const int dt = cfg->dtype;
-  AdamArgs a;
-  std::memset(&a, 0, sizeof(a));
+  Update u;
   void* pp[10] = {params->w_fc, params->g1, params->w_qkv, params->w_o, params->g2, params->w_gate, params->w_up, params->w_down, params->g3, params->w_lm};
   void* gg[10] = {G->w_fc, G->g1, G->w_qkv, G->w_o, G->g2, G->w_gate, G->w_up, G->w_down, G->g3, G->w_lm};
   void* mm[10] = {st->m.w_fc, st->m.g1, st->m.w_qkv, st->m.w_o, st->m.g2, st->m.w_gate, st->m.w_up, st->m.w_down, st->m.g3, st->m.w_lm};
   void* vv[10] = {st->v.w_fc, st->v.g1, st->v.w_qkv, st->v.w_o, st->v.g2, st->v.w_gate, st->v.w_up, st->v.w_down, st->v.g3, st->v.w_lm};
   void* ms[10] = {st->master.w_fc, st->master.g1, st->master.w_qkv, st->master.w_o, st->master.g2, st->master.w_gate, st->master.w_up, st->master.w_down, st->master.g3, st->master.w_lm};
   const int64_t nn[10] = {p.d * p.KH, p.d, p.nqkv * p.d, p.d * p.nq, p.d, p.F * p.d, p.F * p.d, p.d * p.F, p.d, p.V * p.d};
-  for (int i = 0; i < 10; ++i) a.t[i] = AdamTensor{pp[i], (const float*)gg[i], (float*)mm[i], (float*)vv[i], dt == TIDE_DTYPE_BF16 ? (float*)ms[i] : nullptr, nn[i]};
-  a.nt = 10;
+  for (int i = 0; i < 10; ++i) u.t[i] = AdamTensor{pp[i], (const float*)gg[i], (float*)mm[i], (float*)vv[i], dt == TIDE_DTYPE_BF16 ? (float*)ms[i] : nullptr, nn[i]};
+  u.nt = 10;
   if (tok) {
-    a.t[10] = AdamTensor{tok->w_in, (const float*)tok->grad_w_in, (float*)tok->m_w_in, (float*)tok->v_w_in,
-                         dt == TIDE_DTYPE_BF16 ? (float*)tok->master_w_in : nullptr, 2 * p.d * p.d};
-    a.nt = 11;
+    u.t[kWIn] = AdamTensor{tok->w_in, (const float*)tok->grad_w_in, (float*)tok->m_w_in, (float*)tok->v_w_in,
+                           dt == TIDE_DTYPE_BF16 ? (float*)tok->master_w_in : nullptr, 2 * p.d * p.d};
+    u.nt = 11;
   }
-  a.beta1 = cfg->beta1; a.beta2 = cfg->beta2; a.eps = cfg->adam_eps; a.wd = cfg->weight_decay;
-  a.dtype = dt;
+  u.rate.beta1 = cfg->beta1; u.rate.beta2 = cfg->beta2; u.rate.eps = cfg->adam_eps;
   if (dev) {
-    TIDE_HIP(launch_adam_schedule(dev->lr, dev->step, cfg->beta1, cfg->beta2, cfg->weight_decay, dev->dyn, s), "adam schedule");
-    a.dyn = dev->dyn;
-    TIDE_HIP(launch_adamw(a, s), "adamw");
-    return TIDE_OK;
+    u.rate.dyn = dev->dyn;
+    return u;
   }
   const long long t = (long long)(st->step + 1);
-  a.lr = lr;
-  a.inv_bc1 = (float)(1.0 / (1.0 - pow_int((double)cfg->beta1, t)));
-  a.inv_sqrt_bc2 = (float)(1.0 / std::sqrt(1.0 - pow_int((double)cfg->beta2, t)));
+  u.rate.lr = lr;
+  u.rate.decay = 1.0f - lr * cfg->weight_decay;
+  u.rate.inv_bc1 = (float)(1.0 / (1.0 - pow_int((double)cfg->beta1, t)));
+  u.rate.inv_sqrt_bc2 = (float)(1.0 / std::sqrt(1.0 - pow_int((double)cfg->beta2, t)));
+  return u;
+}
+
+// AdamW over the tensors that are left, in one launch
+static int enqueue_adamw(const Update& u, int dtype, hipStream_t s) {
+  AdamArgs a;
+  std::memset(&a, 0, sizeof(a));
+  for (int i = 0; i < u.nt; ++i)
+    if (!(u.done >> i & 1)) a.t[a.nt++] = u.t[i];
+  a.lr = u.rate.lr; a.decay = u.rate.decay; a.inv_bc1 = u.rate.inv_bc1; a.inv_sqrt_bc2 = u.rate.inv_sqrt_bc2;
+  a.beta1 = u.rate.beta1; a.beta2 = u.rate.beta2; a.eps = u.rate.eps;
+  a.dtype = dtype; a.dyn = u.rate.dyn;
   TIDE_HIP(launch_adamw(a, s), "adamw");
-  st->step += 1;
   return TIDE_OK;
 }
 
@@ -810,15 +843,19 @@ static int train_impl(const tide_draft_config* cfg, tide_draft_tensors* params, 
   char* ws = (char*)workspace;
   rc = enqueue_trunk(cfg, params, tok, hidden_buf, tokens, loss_mask, 0, q, ws, p, s);
   if (rc) return rc;
-  rc = enqueue_lm_head(cfg, params, grads, tokens, loss_mask, nullptr, loss_out, nullptr, ws, p, true, s);
+  const DevSchedule dev{lr_dev, step_dev, (float*)(ws + p.adam_dyn)};
+  Update upd = make_update(cfg, params, grads, st, tok, lr, p, lr_dev ? &dev : nullptr);
+  // before the first product that updates its weight
+  if (lr_dev) TIDE_HIP(launch_adam_schedule(dev.lr, dev.step, cfg->beta1, cfg->beta2, cfg->weight_decay, dev.dyn, s), "adam schedule");
+  rc = enqueue_lm_head(cfg, params, grads, tokens, loss_mask, nullptr, loss_out, nullptr, ws, p, true, s, &upd);
   if (rc) return rc;
-  rc = enqueue_backward(cfg, params, grads, tok, hidden_buf, q, ws, p, s, BwdOpts{});
+  BwdOpts opts;
+  opts.upd = &upd;
+  rc = enqueue_backward(cfg, params, grads, tok, hidden_buf, q, ws, p, s, opts);
   if (rc) return rc;
-  if (lr_dev) {
-    const DevSchedule dev{lr_dev, step_dev, (float*)(ws + p.adam_dyn)};
-    return enqueue_adamw(cfg, params, grads, st, tok, 0.f, p, s, &dev);
-  }
-  return enqueue_adamw(cfg, params, grads, st, tok, lr, p, s);
+  rc = enqueue_adamw(upd, cfg->dtype, s);
+  if (rc == TIDE_OK && !lr_dev) st->step += 1;
+  return rc;
 }
 
 static int train_unroll_impl(const tide_draft_config* cfg, tide_draft_tensors* params, tide_draft_tensors* grads,
@@ -864,7 +901,7 @@ static int train_unroll_impl(const tide_draft_config* cfg, tide_draft_tensors* p
     if (k) ur[k].own_kv[k - 1] = ek + u.own_kv;
     rc = enqueue_trunk(cfg, params, tok ? &tk[k] : nullptr, hidden_buf, tokens_s, mask_s, 0, q, wk, p, s, &ur[k]);
     if (rc) return rc;
-    rc = enqueue_lm_head(cfg, params, grads, tokens_s, mask_s, nullptr, loss_out + k, nullptr, wk, p, true, s,
+    rc = enqueue_lm_head(cfg, params, grads, tokens_s, mask_s, nullptr, loss_out + k, nullptr, wk, p, true, s, nullptr,
                          step_weights ? step_weights[k] : 1.f, k > 0);
     if (rc) return rc;
   }
@@ -887,7 +924,10 @@ static int train_unroll_impl(const tide_draft_config* cfg, tide_draft_tensors* p
     rc = enqueue_backward(cfg, params, grads, tok ? &tk[k] : nullptr, hidden_buf, q, wk, p, s, o);
     if (rc) return rc;
   }
-  return enqueue_adamw(cfg, params, grads, st, tok, lr, p, s);
+  // (the weights' gradients are sums over the steps, and an earlier step's backward reads the weights)
+  rc = enqueue_adamw(make_update(cfg, params, grads, st, tok, lr, p, nullptr), cfg->dtype, s);
+  if (rc == TIDE_OK) st->step += 1;
+  return rc;
 }
 
 int tide_draft_eval_unroll(const tide_draft_config* cfg, const tide_draft_tensors* params, const tide_token_input* tok,

@@ -1,0 +1,110 @@
+"""Weight gradients whose AdamW update follows in the same launch: the gradient against a float64 product, the update against the
+formula in float64 on the gradient that was written."""
+import ctypes as C
+
+import numpy as np
+import pytest
+import torch
+
+from paper_2602_05145_amd import workloads as W
+from tests import internal_gemm as ig
+
+
+class AdamTarget(C.Structure):
+    _fields_ = [(n, C.c_void_p) for n in ("m", "v", "master", "w", "dyn")] + [(n, C.c_float) for n in ("lr", "decay", "beta1", "beta2", "eps", "c1", "c2")]
+
+
+supported = ig._symbol("_ZN4tide19gemm_adam_supportedERKNS_8GemmArgsERKNS_10AdamTargetE", C.c_bool, [C.POINTER(ig.GemmArgs), C.POINTER(AdamTarget)])
+launch = ig._symbol("_ZN4tide16launch_gemm_adamERKNS_8GemmArgsERKNS_10AdamTargetEP12ihipStream_t", C.c_int,
+                    [C.POINTER(ig.GemmArgs), C.POINTER(AdamTarget), C.c_void_p])
+name = ig._symbol("_ZN4tide21gemm_adam_kernel_nameERKNS_8GemmArgsE", C.c_char_p, [C.POINTER(ig.GemmArgs)])
+RATE = dict(lr=1e-3, decay=1 - 1e-5, beta1=0.9, beta2=0.999, eps=1e-8, c1=1 / (1 - 0.9 ** 3), c2=(1 - 0.999 ** 3) ** -0.5)
+
+
+def test_what_a_product_with_update_serves():
+    ok = AdamTarget(m=256, v=256, master=256, w=256)
+    assert supported(ig.args(ig.TN, 264, 136, 77, out=ig.F32), ok)
+    for g in (ig.args(ig.NT, 264, 136, 64, out=ig.F32), ig.args(ig.TN, 264, 136, 77), ig.args(ig.TN, 260, 136, 77, out=ig.F32),
+              ig.args(ig.TN, 264, 132, 77, out=ig.F32), ig.args(ig.TN, 264, 136, 77, out=ig.F32, ldc=140), ig.args(ig.TN, 264, 136, 77, out=ig.F32, c=264),
+              ig.args(ig.TN, 264, 136, 77, out=ig.F32, residual=256), ig.args(ig.TN, 264, 136, 77, out=ig.F32, in_dtype=ig.F32)):
+        assert not supported(g, ok)
+    for f in ("m", "v", "master", "w"):
+        assert not supported(ig.args(ig.TN, 264, 136, 77, out=ig.F32), AdamTarget(**dict(dict(m=256, v=256, master=256, w=256), **{f: 264})))
+
+
+# M, N, K, the number of rows on the device (None: known to the host), old values, columns of the weight, kernel, scratch
+CASES = [(264, 136, 77, None, 0, 136, "128", 0), (264, 136, 77, None, 1, 272, "128", 0), (264, 136, 77, 13, 1, 136, "128", 0), (264, 136, 77, 0, 0, 136, "128", 0),
+         (264, 136, 77, 0, 1, 136, "128", 0), (4096, 4104, 40, 33, 0, 4104, "128", 0), (5456, 656, 65, None, 1, 656, "128x256", 0),
+         (1048, 7192, 65, None, 0, 7192, "160x256", 0), (6736, 1312, 65, 1, 1, 1312, "192x256", 0), (1552, 7184, 65, None, 0, 7184, "224x256", 0),
+         (248, 688, 30000, None, 1, 688, "128", 1), (248, 688, 30000, 777, 0, 688, "128", 1), (2040, 1544, 8000, None, 1, 1544, "256", 1), (2040, 1544, 8000, 4321, 0, 1544, "256", 1), (4344, 4096, 8000, None, 1, 4096, "256", 1)]
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("M,N,K,rows,add,ld,kernel,split", CASES)
+def test_gradient_and_update(M, N, K, rows, add, ld, kernel, split):
+    g = torch.Generator(device="cuda").manual_seed(M + N + K)
+    dev = dict(device="cuda")
+    a, b = torch.randn(K, M, generator=g, **dev).bfloat16(), (torch.randn(K, N, generator=g, **dev) * 0.1).bfloat16()
+    k = K if rows is None else rows
+    grad, m, v, master = (torch.randn(M, ld, generator=g, **dev) * s for s in (1.0, 0.1, 1.0, 0.02))
+    v = v.square() * 1e-2
+    w = master.bfloat16()
+    col = ld - N                                          # a column half of a wider weight, as a two-part input projection has it
+    old = [x.clone() for x in (grad, m, v, master, w)]
+    cnt = torch.tensor([k], dtype=torch.int32, **dev)
+    dyn = torch.tensor([RATE["lr"], RATE["decay"], RATE["c1"], RATE["c2"]], **dev) if rows is not None else None
+    scratch = torch.full((64 << 20,), 0xFF, dtype=torch.uint8, **dev)
+    p = ig.args(ig.TN, M, N, K, out=ig.F32, ldc=ld, a=a.data_ptr(), b=b.data_ptr(), c=grad[:, col:].data_ptr(), alpha=-0.5, accumulate=add)
+    if rows is not None:
+        p.k_dev = cnt.data_ptr()
+    if split:
+        p.scratch, p.scratch_bytes = scratch.data_ptr(), scratch.numel()
+        assert ig.scratch_bytes(p) > 0
+    t = AdamTarget(m=m[:, col:].data_ptr(), v=v[:, col:].data_ptr(), master=master[:, col:].data_ptr(), w=w[:, col:].data_ptr(),
+                   dyn=None if dyn is None else dyn.data_ptr(), **(RATE if dyn is None else dict(beta1=0.9, beta2=0.999, eps=1e-8)))
+    assert name(p).decode() == f"gemm_mfma_tn_{kernel}_adamw"
+    print("update", M, N, K, rows, add, kernel, flush=True)
+    assert launch(p, t, torch.cuda.current_stream().cuda_stream) == 0
+    torch.cuda.synchronize()
+    for x, y in zip((grad, m, v, master, w), old):
+        assert torch.equal(x[:, :col], y[:, :col])       # the other columns are not this product's
+    grad, m, v, master, w = (x[:, col:] for x in (grad, m, v, master, w))
+    g0, m0, v0, th0 = (x[:, col:].double() for x in old[:4])
+    want = -0.5 * (a[:k].double().t() @ b[:k].double()) + add * g0
+    # sums of k products of size 0.1 in float: sqrt(k) roundings of at most the sum's own size each, times four
+    assert float((grad.double() - want).abs().max()) < 4 * 6e-8 * (max(k, 1) ** 0.5 * max(k, 1) ** 0.5 * 0.1 + 4)
+    gd = grad.double()
+    b1, b2 = float(np.float32(0.9)), float(np.float32(0.999))
+    m1, v1 = b1 * m0 + (1 - b1) * gd, b2 * v0 + (1 - b2) * gd * gd
+    u = RATE["lr"] * m1 * RATE["c1"] / (v1.sqrt() * RATE["c2"] + 1e-8)
+    th1 = th0 * RATE["decay"] - u
+    eps = 2.0 ** -22                                      # the constants' own rounding and three or four of the formula's
+    assert bool(((m.double() - m1).abs() <= eps * (m0.abs() + gd.abs())).all())
+    assert bool(((v.double() - v1).abs() <= eps * (v0 + gd * gd)).all())
+    assert bool(((master.double() - th1).abs() <= eps * (th0.abs() + 4 * u.abs() + 4 * RATE["lr"] * RATE["c1"] * (m0.abs() + gd.abs()) / (v1.sqrt() * RATE["c2"] + 1e-8))).all())
+    assert torch.equal(w, master.bfloat16())
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("kw,block", [(dict(), 0), (dict(batch=3, seq=37), 64), (dict(hidden=264, n_heads=2, n_kv_heads=1, head_dim=132, ffn=332), 0)])
+def test_a_step_updates_every_weight_once(kw, block):
+    """Weights whose product can carry the update and (ffn 332: rows no 16-byte piece fits) weights whose product cannot, in one step; LM head in
+    blocks, of which the last carries it.  Against the update in float64 from the gradients that the step returned."""
+    from paper_2602_05145_amd import runtime
+    cfg = W.get_config("small", **dict(dict(batch=2, seq=64, target_hidden=256, hidden=256, n_heads=2, n_kv_heads=1, head_dim=128, ffn=512, vocab=2048), **kw))
+    wl = W.make_workload(cfg)
+    cfg["lm_block_rows"] = block
+    tr = runtime.trainer_from_workload(cfg, wl)
+    before = {k: x.astype(np.float64) for k, x in tr.host(tr.master).items()}
+    print("step", kw, block, flush=True)
+    tr.train_step(cfg["lr"])
+    torch.cuda.synchronize()
+    grads, master, params = (tr.host(x) for x in (tr.grads, tr.master, tr.params))
+    for k, g in grads.items():
+        g = g.astype(np.float64)
+        want = before[k] * (1 - cfg["lr"] * cfg["weight_decay"]) - cfg["lr"] * g / (np.abs(g) + cfg["adam_eps"])
+        # the first step divides a gradient by its own magnitude: a rounding of either counts against lr; float gradients below
+        # 1e-18 have squares that underflow
+        ok = (np.abs(master[k] - want) <= 2.0 ** -22 * (np.abs(before[k]) + 4 * cfg["lr"])) | (np.abs(g) < 1e-16)
+        assert ok.all(), (k, np.abs(master[k] - want).max())
+        assert np.array_equal(params[k], W.round_to_bf16(master[k])), k
