@@ -16,8 +16,8 @@
 // ds_read_b64_tr_b16, so nothing is ever transposed through registers or HBM.
 //
 // Tiles.  Forward and dQ: one block = 128 queries of one head (4 waves x 32 queries, Q in registers; capped
-// at 256 VGPRs so that two blocks share a CU and one block's softmax overlaps the other's MFMAs),
-// K/V streamed in 64-key tiles, double buffered in LDS.  dK/dV: one block = 128 keys of one kv
+// at 256 VGPRs so that two blocks share a CU and one block's softmax overlaps the other's MFMAs; the forward of head size 128
+// also makes the next tile's scores beside a tile's exponentials), K/V streamed in 64-key tiles, double buffered in LDS.  dK/dV: one block = 128 keys of one kv
 // head (4 waves x 32 keys, K [and V] in registers), Q/dO streamed in tiles of 32 (dV pass) or 64 (dK pass)
 // queries for each of the G query heads of the group, so dK/dV are summed over the group in registers: no
 // atomics, deterministic.  dV and dK are two launches of one template: a fused pass needs 350 registers (K, V
@@ -165,16 +165,18 @@ struct TileDma {
     for (int i = 0; i < PER_WAVE; ++i) {
       const int o = (wave + NW * i) * 1024 + lane * 16;
       const int R = o / (PITCH * 2), piece = (o % (PITCH * 2)) / 16;
-      // 2^31 plus any offset inside a sequence (below 2^31, see attn_mfma_supported) stays beyond the buffer and does not wrap
+      // (2^31 is beyond any sequence, see attn_mfma_supported)
       voff[i] = (piece < D / 8 && o < BYTES) ? (uint32_t)(perm(R) * ld + piece * 8) * 2u : 0x80000000u;
     }
   }
-  // tile_bytes: byte offset of the tile's first element in the buffer; wave_s: the wave index as a scalar
-  __device__ __forceinline__ void issue(i32x4_t rs, const bf16_t* tile, uint32_t tile_bytes, int wave_s) const {
+  // tile_bytes: byte offset of the tile's first element from src, whose `bytes` bytes may be read; wave_s: the wave index as a
+  // scalar.  The tile's place goes into the descriptor (scalar operations), so that the lane offsets are loop constants.
+  __device__ __forceinline__ void issue(const bf16_t* src, uint32_t bytes, const bf16_t* tile, uint32_t tile_bytes, int wave_s) const {
+    const i32x4_t rs = rsrc_words((const char*)src + tile_bytes, bytes - tile_bytes);
     const uint32_t base = lds_address(tile);
 #pragma unroll
-    for (int i = 0; i < PER_WAVE; ++i)
-      if (wave_s + NW * i < CHUNKS) dma16(rs, base + (uint32_t)(wave_s + NW * i) * 1024u, voff[i] + tile_bytes);
+    for (int i = 0; i < PER_WAVE; ++i)   // (the test is for the last round of chunks alone)
+      if (NW * (i + 1) <= CHUNKS || wave_s + NW * i < CHUNKS) dma16(rs, base + (uint32_t)(wave_s + NW * i) * 1024u, voff[i]);
   }
 };
 #define TIDE_ATTN_WAIT_DMA() __builtin_amdgcn_s_waitcnt(0x0F70)   /* vmcnt(0) */
@@ -223,6 +225,27 @@ __device__ __forceinline__ uint32_t not_finite(const f32x16_t (&acc)[NC], bool a
 }
 
 constexpr int BQ = 128, BKV = 64;
+constexpr float kLag = 8.0f;   // log2; see the forward kernel
+
+// The waves of a SIMD belong to two blocks: the one in a phase of MFMAs alone goes before the other's vector instructions, which
+// then run under them (head size 128: forward 2 to 4 %, backward 1 to 2 %; head size 64, three or four blocks: backward 1 % slower).
+template <int D>
+__device__ __forceinline__ void matrix_phase(bool on) {
+  if constexpr (D == 128) {
+    if (on) __builtin_amdgcn_s_setprio(1);
+    else __builtin_amdgcn_s_setprio(0);
+  }
+}
+
+// the value of lane ^ 32, and the larger of it and this lane's, without the LDS round trip of a shuffle
+__device__ __forceinline__ float swap_halves(float x) {
+  const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(x), __float_as_uint(x), false, false);   // {lower half twice, upper half twice}
+  return __uint_as_float((threadIdx.x & 32) ? r[0] : r[1]);
+}
+__device__ __forceinline__ float row_max(float x) {
+  const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(x), __float_as_uint(x), false, false);
+  return fmaxf(__uint_as_float(r[0]), __uint_as_float(r[1]));
+}
 constexpr int kv_tile(int D) { return BKV * pitch(D); }  // elements
 
 // Head size 64 halves the operand and accumulator registers and the LDS tiles: 119 / 168 / 125 / 147 registers for the
@@ -239,9 +262,6 @@ constexpr int blocks_per_cu(int D, int at64, int at128) { return D == 64 ? at64 
 #endif
 #ifndef TIDE_ATTN_DKV_RING
 #define TIDE_ATTN_DKV_RING 4
-#endif
-#ifndef TIDE_ATTN_KRING
-#define TIDE_ATTN_KRING 4
 #endif
 // Work item (x, y, z) of an nx * ny * nz problem from the block's place in the 1-D dispatch order.
 // Work-groups go to the 8 XCDs round-robin and every XCD has its own L2.  The blocks of a "group" (all x of gy
@@ -311,99 +331,236 @@ __global__ __launch_bounds__(256, blocks_per_cu(D, 4, 2)) void attn_fwd_mfma_ker
   for (int ct = 0; ct < NC; ++ct)
 #pragma unroll
     for (int q = 0; q < 16; ++q) o[ct][q] = 0.f;
-  float m = -INFINITY, l = 0.f;
+  float m = -INFINITY, l = 0.f;   // l: this lane's share of the row's sum (its partner, lane ^ 32, has the rest)
 
   const int kv_end = min(S, q0 + BQ);
   const int nt = (kv_end + BKV - 1) / BKV;
-  const i32x4_t rsw = rsrc_words(base, (uint32_t)((size_t)S * ld * 2));
+  const uint32_t seq_bytes = (uint32_t)((size_t)S * ld * 2);
   const int wave_s = __builtin_amdgcn_readfirstlane(wave);
   TileDma<64, D> dma;
   dma.init(ld, wave, lane);
-  dma.issue(rsw, sK, (uint32_t)kcol * 2u, wave_s);
-  dma.issue(rsw, sV, (uint32_t)vcol * 2u, wave_s);
+  auto fetch_k = [&](int t) {
+    if (t < nt) dma.issue(base, seq_bytes, sK + (t & 1) * KV_TILE, ((uint32_t)(t * BKV) * (uint32_t)ld + (uint32_t)kcol) * 2u, wave_s);
+  };
+  auto fetch_v = [&](int t) {
+    if (t < nt) dma.issue(base, seq_bytes, sV + (t & 1) * KV_TILE, ((uint32_t)(t * BKV) * (uint32_t)ld + (uint32_t)vcol) * 2u, wave_s);
+  };
+  // The sums are kept relative to m, which follows the running maximum (of the row) once it has fallen behind by kLag:
+  // probabilities are then at most 2^8, with the same relative precision, and the accumulators are rescaled once or twice per
+  // row, not in nearly every tile (one of 32 rows nearly always finds a new maximum).
+  auto follow = [&](float tm) {
+    const bool moved = (tm - m) * c > kLag;   // the first tile: m = -inf, and key 0 is visible to every query
+    if (__builtin_amdgcn_ballot_w64(moved) != 0) {   // wave-uniform
+      const float mn = moved ? tm : m, alpha = __builtin_amdgcn_exp2f((m - mn) * c);
+      l *= alpha;
+      m = mn;
+#pragma unroll
+      for (int ct = 0; ct < NC; ++ct)
+#pragma unroll
+        for (int q = 0; q < 16; ++q) o[ct][q] *= alpha;
+    }
+  };
+  constexpr int RING = 4, NP = parts(D);
+  auto k_frag = [&](const bf16_t* K, int i) { return frag<D>(K, (i / NK) * 32, plr, (i % NK) * 16 + g * 8); };
+  fetch_k(0);
+  if constexpr (D == 64) fetch_v(0);
   // vmcnt(0): nothing of the prologue is in flight inside the loop.  The Q (and dO) fragments are first used there, so
   // the compiler issues their loads last and, at the loop's head, still counts them as outstanding; inside the loop
   // the next tile's eight loads are then younger than they are, and the waits it puts in front of the first MFMAs
   // ("all but 7, 6, ... 0 loads done") make every tile wait for the tile after it to arrive from memory.
   __builtin_amdgcn_s_waitcnt(0x0F70);
   __syncthreads();
-
-  for (int t = 0; t < nt; ++t) {
-    const int st = t & 1;
-    const int j0 = t * BKV;
-    if (t + 1 < nt) {   // the next tile, into the stage whose last readers passed the barrier at the end of the step before
-      const uint32_t row_bytes = (uint32_t)(j0 + BKV) * (uint32_t)ld * 2u;
-      dma.issue(rsw, sK + (st ^ 1) * KV_TILE, row_bytes + (uint32_t)kcol * 2u, wave_s);
-      dma.issue(rsw, sV + (st ^ 1) * KV_TILE, row_bytes + (uint32_t)vcol * 2u, wave_s);
-    }
-    if (j0 <= qw + 31) {  // wave-uniform: the tile has at least one unmasked key for this wave
-      const bf16_t* K = sK + st * KV_TILE;
-      const bf16_t* V = sV + st * KV_TILE;
-      f32x16_t s[2];
-#pragma unroll
-      for (int jt = 0; jt < 2; ++jt)
-#pragma unroll
-        for (int q = 0; q < 16; ++q) s[jt][q] = 0.f;
-      {
-        // the 2 NK K fragments of the tile through a ring of TIDE_ATTN_KRING registers sets: a fragment is requested
-        // that many MFMAs before its own (read, wait, MFMA one after the other leaves the LDS latency, three
-        // MFMA times, exposed at every step)
-        constexpr int RING = TIDE_ATTN_KRING;
-        u32x4_t kb[RING];
-#pragma unroll
-        for (int i = 0; i < RING; ++i) kb[i] = frag<D>(K, (i / NK) * 32, plr, (i % NK) * 16 + g * 8);
-#pragma unroll
-        for (int i = 0; i < 2 * NK; ++i) {
-          s[i / NK] = mfma(kb[i % RING], qf[i % NK], s[i / NK]);
-          if (i + RING < 2 * NK) kb[i % RING] = frag<D>(K, ((i + RING) / NK) * 32, plr, ((i + RING) % NK) * 16 + g * 8);
-          __builtin_amdgcn_sched_barrier(0);
-        }
-      }
-      if (j0 + BKV - 1 > qw) {  // the tile touches the diagonal of this wave
+  if constexpr (D == 64) {
+    // Four blocks share a CU (the pipelined form below needs 197 registers, two blocks: 16 x 2048, 32 / 8 heads 541 -> 574 us).
+    for (int t = 0; t < nt; ++t) {
+      const int j0 = t * BKV;
+      fetch_k(t + 1);   // into the stage whose last readers passed the barrier at the end of the step before
+      fetch_v(t + 1);
+      if (j0 <= qw + 31) {  // wave-uniform: the tile has at least one unmasked key for this wave
+        const bf16_t* K = sK + (t & 1) * KV_TILE;
+        const bf16_t* V = sV + (t & 1) * KV_TILE;
+        f32x16_t s[2];
 #pragma unroll
         for (int jt = 0; jt < 2; ++jt)
 #pragma unroll
-          for (int q = 0; q < 16; ++q)
-            if (j0 + jt * 32 + acc_row(q, g) > iq) s[jt][q] = -INFINITY;
-      }
-      float tm = -INFINITY;
+          for (int q = 0; q < 16; ++q) s[jt][q] = 0.f;
+        {
+          // the K fragments through a ring: a fragment is requested RING MFMAs before its own (read, wait, MFMA one after
+          // the other leaves the LDS latency, three MFMA times, exposed at every step)
+          u32x4_t kb[RING];
 #pragma unroll
-      for (int jt = 0; jt < 2; ++jt)
+          for (int i = 0; i < RING; ++i) kb[i] = k_frag(K, i);
 #pragma unroll
-        for (int q = 0; q < 16; ++q) tm = fmaxf(tm, s[jt][q]);
-      tm = fmaxf(tm, __shfl_xor(tm, 32, 64));
-      const float mn = fmaxf(m, tm);          // finite: key 0 is visible to every query
-      const float alpha = __builtin_amdgcn_exp2f((m - mn) * c);
-      const float mc = mn * c;
-      float ps = 0.f;
-#pragma unroll
-      for (int jt = 0; jt < 2; ++jt)
-#pragma unroll
-        for (int q = 0; q < 16; ++q) {
-          const float p = __builtin_amdgcn_exp2f(s[jt][q] * c - mc);
-          s[jt][q] = p;
-          ps += p;
+          for (int i = 0; i < 2 * NK; ++i) {
+            s[i / NK] = mfma(kb[i % RING], qf[i % NK], s[i / NK]);
+            if (i + RING < 2 * NK) kb[i % RING] = k_frag(K, i + RING);
+            __builtin_amdgcn_sched_barrier(0);
+          }
         }
-      ps += __shfl_xor(ps, 32, 64);
-      l = l * alpha + ps;
-      m = mn;
-      if (__builtin_amdgcn_ballot_w64(alpha != 1.0f) != 0) {   // wave-uniform: some row's running max moved
+        if (j0 + BKV - 1 > qw) {  // the tile touches the diagonal of this wave
+#pragma unroll
+          for (int jt = 0; jt < 2; ++jt)
+#pragma unroll
+            for (int q = 0; q < 16; ++q)
+              if (j0 + jt * 32 + acc_row(q, g) > iq) s[jt][q] = -INFINITY;
+        }
+        float tm = -INFINITY;
+#pragma unroll
+        for (int jt = 0; jt < 2; ++jt)
+#pragma unroll
+          for (int q = 0; q < 16; ++q) tm = fmaxf(tm, s[jt][q]);
+        follow(row_max(tm));
+        const float mc = m * c;
+        float ps[2] = {0.f, 0.f};
+#pragma unroll
+        for (int jt = 0; jt < 2; ++jt)
+#pragma unroll
+          for (int q = 0; q < 16; ++q) {
+            const float p = __builtin_amdgcn_exp2f(s[jt][q] * c - mc);
+            s[jt][q] = p;
+            ps[q & 1] += p;
+          }
+        l += ps[0] + ps[1];
+        u32x4_t pf[4][NP];
+#pragma unroll
+        for (int ks = 0; ks < 4; ++ks) pack_parts(s[ks >> 1], ks & 1, pf[ks]);
 #pragma unroll
         for (int ct = 0; ct < NC; ++ct)
 #pragma unroll
-          for (int q = 0; q < 16; ++q) o[ct][q] *= alpha;
+          for (int ks = 0; ks < 4; ++ks) o[ct] = mfma_parts(frag_tr<D>(V, ks * 16, ct * 32, lane), pf[ks], o[ct]);
       }
-      u32x4_t pf[4][parts(D)];
+      TIDE_ATTN_WAIT_DMA();
+      __syncthreads();
+    }
+  } else {
+    fetch_k(1);
+    fetch_v(0);
+
+    // One tile is two MFMA phases: the scores of tile t + 1 (2 NK MFMAs) beside the exponentials of tile t, then its P V beside
+    // the row maxima of the scores just made.  The order of MFMAs, operand reads (a ring of four fragments) and vector
+    // instructions is written out and pinned: left to two waves of a SIMD that took turns by chance, the matrix pipes were 40 % and
+    // the vector units 50 % busy, one after the other.  us before / now, with the rescaling above: 16 x 2048, 32 / 8 heads 757 / 685,
+    // 4 x 1024 69 / 57 (the larger one sits at the power limit: without exponentials it takes 645, without operand reads 618).
+    // A ring of six: the same; of eight: spills.  The same order in the dQ kernel (halves of a tile) gave nothing.
+    constexpr int NS = 2 * NK, EPM = 32 / NS;   // MFMAs of a score tile, exponentials beside each
+    f32x16_t sa[2], sb[2];
+    float tma = -INFINITY, tmb = -INFINITY;   // this lane's maximum of sa, sb
+    auto v_frag = [&](const bf16_t* V, int i) { return frag_tr<D>(V, (i / NC) * 16, (i % NC) * 32, lane); };   // k16 step i / NC, columns i % NC
+    {
+      const bf16_t* K = sK;   // tile 0: every wave sees key 0
+      u32x4_t kb[RING];
 #pragma unroll
-      for (int ks = 0; ks < 4; ++ks) pack_parts(s[ks >> 1], ks & 1, pf[ks]);
+      for (int i = 0; i < RING; ++i) kb[i] = k_frag(K, i);
 #pragma unroll
-      for (int ct = 0; ct < NC; ++ct)
+      for (int jt = 0; jt < 2; ++jt)
 #pragma unroll
-        for (int ks = 0; ks < 4; ++ks) o[ct] = mfma_parts(frag_tr<D>(V, ks * 16, ct * 32, lane), pf[ks], o[ct]);
+        for (int q = 0; q < 16; ++q) sa[jt][q] = 0.f;
+#pragma unroll
+      for (int i = 0; i < NS; ++i) {
+        sa[i / NK] = mfma(kb[i % RING], qf[i % NK], sa[i / NK]);
+        if (i + RING < NS) kb[i % RING] = k_frag(K, i + RING);
+        __builtin_amdgcn_sched_barrier(0);
+      }
+#pragma unroll
+      for (int q = 0; q < 32; ++q) tma = fmaxf(tma, sa[q / 16][q % 16]);
     }
     TIDE_ATTN_WAIT_DMA();
     __syncthreads();
+
+    auto step = [&](f32x16_t (&s)[2], float tm, f32x16_t (&sn)[2], float& tmn, int t) {
+      const int j0 = t * BKV;
+      // (K(t) was last read in the step before, V(t - 1) as well: the barrier at its end has passed)
+      auto fetch = [&] { fetch_k(t + 2); fetch_v(t + 1); };
+      if (j0 > qw + 31) {
+        fetch();
+      } else {   // wave-uniform: the tile has at least one unmasked key for this wave
+        const bf16_t* K = sK + ((t + 1) & 1) * KV_TILE;
+        const bf16_t* V = sV + (t & 1) * KV_TILE;
+        const bool more = t + 1 < nt && j0 + BKV <= qw + 31;   // the next tile has one, too
+        u32x4_t ring[RING];
+        if (more) {
+#pragma unroll
+          for (int i = 0; i < RING; ++i) ring[i] = k_frag(K, i);
+        }
+        __builtin_amdgcn_sched_barrier(0);
+        fetch();   // behind the first operand reads, which arrive meanwhile
+        if (j0 + BKV - 1 > qw) {  // the tile touches the diagonal of this wave
+          tm = -INFINITY;
+#pragma unroll
+          for (int jt = 0; jt < 2; ++jt)
+#pragma unroll
+            for (int q = 0; q < 16; ++q) {
+              if (j0 + jt * 32 + acc_row(q, g) > iq) s[jt][q] = -INFINITY;
+              tm = fmaxf(tm, s[jt][q]);
+            }
+        }
+        tm = row_max(tm);
+        follow(tm);
+        const float mc = m * c;
+        u32x4_t pf[4][NP];
+        float ps[2] = {0.f, 0.f};
+        float mcx = mc;
+        auto prob = [&](int e) {   // element e = 0 .. 31 of the lane; every eighth completes an operand of P V
+          const float p = __builtin_amdgcn_exp2f(fmaf(s[e / 16][e % 16], c, -mcx));
+          s[e / 16][e % 16] = p;
+          ps[e & 1] += p;
+        };
+        if (more) {
+          asm volatile("" : "+v"(mcx));   // (or the multiply-adds, which both branches have, move out of them and ahead of the MFMAs)
+#pragma unroll
+          for (int jt = 0; jt < 2; ++jt)
+#pragma unroll
+            for (int q = 0; q < 16; ++q) sn[jt][q] = 0.f;
+#pragma unroll
+          for (int i = 0; i < NS; ++i) {
+            sn[i / NK] = mfma(ring[i % RING], qf[i % NK], sn[i / NK]);
+            ring[i % RING] = i + RING < NS ? k_frag(K, i + RING) : v_frag(V, i + RING - NS);
+#pragma unroll
+            for (int u = 0; u < EPM; ++u) prob(i * EPM + u);
+            if ((i + 1) * EPM % 8 == 0) pack_parts(s[i * EPM / 16], i * EPM % 16 / 8, pf[i * EPM / 8]);
+            __builtin_amdgcn_sched_barrier(0);
+          }
+        } else {
+#pragma unroll
+          for (int i = 0; i < RING; ++i) ring[i] = v_frag(V, i);
+#pragma unroll
+          for (int e = 0; e < 32; ++e) prob(e);
+#pragma unroll
+          for (int ks = 0; ks < 4; ++ks) pack_parts(s[ks >> 1], ks & 1, pf[ks]);
+        }
+        l += ps[0] + ps[1];
+        matrix_phase<D>(true);
+        constexpr int NV = 4 * NC, MPM = (32 + NV - 1) / NV;   // fragments of V, maxima beside each
+        float mx[2] = {-INFINITY, -INFINITY};
+        auto pv = [&](auto MORE) {
+#pragma unroll
+          for (int i = 0; i < NV; ++i) {
+            o[i % NC] = mfma_parts(ring[i % RING], pf[i / NC], o[i % NC]);
+            if (i + RING < NV) ring[i % RING] = v_frag(V, i + RING);
+            if constexpr (decltype(MORE)::value) {
+#pragma unroll
+              for (int u = 0; u < MPM; ++u) {
+                const int e = i * MPM + u;
+                if (e < 32) mx[u & 1] = fmaxf(mx[u & 1], sn[e / 16][e % 16]);
+              }
+            }
+            __builtin_amdgcn_sched_barrier(0);
+          }
+        };
+        if (more) pv(std::true_type{});
+        else pv(std::false_type{});
+        matrix_phase<D>(false);
+        tmn = fmaxf(mx[0], mx[1]);
+      }
+      TIDE_ATTN_WAIT_DMA();
+      __syncthreads();
+    };
+    for (int t = 0; t < nt; t += 2) {
+      step(sa, tma, sb, tmb, t);
+      if (t + 1 < nt) step(sb, tmb, sa, tma, t + 1);
+    }
   }
+  l += swap_halves(l);
 
   const float inv = 1.0f / l;
   stage_out<D>(smem, o, inv, wave, lane);
@@ -498,12 +655,13 @@ __global__ __launch_bounds__(256, blocks_per_cu(D, 3, 2)) void attn_dq_mfma_kern
 
   const int kv_end = min(S, q0 + BQ);
   const int nt = (kv_end + BKV - 1) / BKV;
-  const i32x4_t rsw = rsrc_words(qkv + (size_t)sv.row0 * ld, (uint32_t)((size_t)S * ld * 2));
+  const bf16_t* seq = qkv + (size_t)sv.row0 * ld;
+  const uint32_t seq_bytes = (uint32_t)((size_t)S * ld * 2);
   const int wave_s = __builtin_amdgcn_readfirstlane(wave);
   TileDma<64, D> dma;
   dma.init(ld, wave, lane);
-  dma.issue(rsw, sK, (uint32_t)kcol * 2u, wave_s);
-  dma.issue(rsw, sV, (uint32_t)vcol * 2u, wave_s);
+  dma.issue(seq, seq_bytes, sK, (uint32_t)kcol * 2u, wave_s);
+  dma.issue(seq, seq_bytes, sV, (uint32_t)vcol * 2u, wave_s);
   __builtin_amdgcn_s_waitcnt(0x0F70);   // vmcnt(0): nothing of the prologue is in flight inside the loop (see the forward kernel)
   __syncthreads();
 
@@ -512,8 +670,8 @@ __global__ __launch_bounds__(256, blocks_per_cu(D, 3, 2)) void attn_dq_mfma_kern
     const int j0 = t * BKV;
     if (t + 1 < nt) {
       const uint32_t row_bytes = (uint32_t)(j0 + BKV) * (uint32_t)ld * 2u;
-      dma.issue(rsw, sK + (st ^ 1) * KV_TILE, row_bytes + (uint32_t)kcol * 2u, wave_s);
-      dma.issue(rsw, sV + (st ^ 1) * KV_TILE, row_bytes + (uint32_t)vcol * 2u, wave_s);
+      dma.issue(seq, seq_bytes, sK + (st ^ 1) * KV_TILE, row_bytes + (uint32_t)kcol * 2u, wave_s);
+      dma.issue(seq, seq_bytes, sV + (st ^ 1) * KV_TILE, row_bytes + (uint32_t)vcol * 2u, wave_s);
     }
     if (j0 <= qw + 31) {
       const bf16_t* K = sK + st * KV_TILE;
@@ -562,10 +720,12 @@ __global__ __launch_bounds__(256, blocks_per_cu(D, 3, 2)) void attn_dq_mfma_kern
         pack_parts(s, 0, dsf[2 * jt]);
         pack_parts(s, 1, dsf[2 * jt + 1]);
       }
+      matrix_phase<D>(true);
 #pragma unroll
       for (int ct = 0; ct < NC; ++ct)
 #pragma unroll
         for (int ks = 0; ks < 4; ++ks) dq[ct] = mfma_parts(frag_tr<D>(K, ks * 16, ct * 32, lane), dsf[ks], dq[ct]);
+      matrix_phase<D>(false);
     }
     TIDE_ATTN_WAIT_DMA();
     __syncthreads();
@@ -669,8 +829,8 @@ __global__ __launch_bounds__(KW * NS * 64, NS > 1 ? 1 : WHICH == 0 ? blocks_per_
   const int nit = (S - i_begin + BI - 1) / BI;         // query tiles per head
   const int ntiles = G * nit;
 
-  const i32x4_t rsq = rsrc_words(qkv + (size_t)sv.row0 * ld, (uint32_t)((size_t)S * ld * 2));
-  const i32x4_t rsdo = rsrc_words(dout + (size_t)sv.row0 * ldo, (uint32_t)((size_t)S * ldo * 2));
+  const bf16_t *seq = qkv + (size_t)sv.row0 * ld, *seq_do = dout + (size_t)sv.row0 * ldo;
+  const uint32_t seq_bytes = (uint32_t)((size_t)S * ld * 2), seq_do_bytes = (uint32_t)((size_t)S * ldo * 2);
   const int wave_s = __builtin_amdgcn_readfirstlane(wave);
   TileDma<BI, D, KW> dmq, dmo;   // LDS-DMA loads of the Q and the dO tile (their row pitches in memory differ)
   dmq.init(ld, wave, lane);
@@ -688,8 +848,8 @@ __global__ __launch_bounds__(KW * NS * 64, NS > 1 ? 1 : WHICH == 0 ? blocks_per_
     const int hh = kh * G + u % G;
     const int i0 = tile_i0(u);
     bf16_t* base = stages + st * DKV_STAGE;
-    dmq.issue(rsq, base, ((uint32_t)i0 * (uint32_t)ld + (uint32_t)(hh * D)) * 2u, wave_s);
-    dmo.issue(rsdo, base + Q_TILE, ((uint32_t)i0 * (uint32_t)ldo + (uint32_t)(hh * D)) * 2u, wave_s);
+    dmq.issue(seq, seq_bytes, base, ((uint32_t)i0 * (uint32_t)ld + (uint32_t)(hh * D)) * 2u, wave_s);
+    dmo.issue(seq_do, seq_do_bytes, base + Q_TILE, ((uint32_t)i0 * (uint32_t)ldo + (uint32_t)(hh * D)) * 2u, wave_s);
     if (tid < 2 * BI) {
       const int i = i0 + (tid & (BI - 1));
       const float* src = (tid < BI) ? lse : delta;
@@ -771,10 +931,12 @@ __global__ __launch_bounds__(KW * NS * 64, NS > 1 ? 1 : WHICH == 0 ? blocks_per_
       pack_parts(s, 0, pf[0]);
       pack_parts(s, 1, pf[1]);
       const bf16_t* Xt = DK ? Qt : dOt;   // dK += dS^T Q, dV += P^T dO
+      matrix_phase<D>(true);
 #pragma unroll
       for (int ct = 0; ct < NC; ++ct)
 #pragma unroll
         for (int ks = 0; ks < 2; ++ks) dacc[ct] = mfma_parts(frag_tr<D>(Xt, hf * 32 + ks * 16, ct * 32, lane), pf[ks], dacc[ct]);
+      matrix_phase<D>(false);
     }
     }
     if (u + NS < ntiles) sstore(st ^ 1);
