@@ -623,7 +623,15 @@ __global__ __launch_bounds__(256) void colsum_kernel(ColSums cs, int64_t nrows, 
     float v = 0.f;
 #pragma unroll
     for (int i = 0; i < 16; ++i) v += sm[i][cl];
-    out[c] = accumulate ? out[c] + v : v;
+    v = accumulate ? out[c] + v : v;
+    out[c] = v;
+    const AdamTarget& t = cs.upd[blockIdx.y];
+    if (t.m) {
+      float m = t.m[c], s = t.v[c], th = t.master[c];
+      adam_update(adam_rate(t), v, m, s, th);
+      t.m[c] = m; t.v[c] = s; t.master[c] = th;
+      if (t.w) ((bf16_t*)t.w)[c] = f2bf(th);
+    }
   }
 }
 
@@ -771,7 +779,6 @@ hipError_t launch_rope(int B, int S, int nh, int nkv, int dh, const float* cs, v
 // ----------------------------------------------------------------------------------------------
 // SwiGLU
 // ----------------------------------------------------------------------------------------------
-__device__ __forceinline__ float sigmoidf_(float x) { return 1.0f / (1.0f + __expf(-x)); }
 
 template <typename T>
 __global__ __launch_bounds__(256) void swiglu_fwd_kernel(const T* __restrict__ gt, const T* __restrict__ u,

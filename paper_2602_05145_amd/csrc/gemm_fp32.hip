@@ -37,6 +37,8 @@ struct Fp32GemmParams {
   int accumulate;
   const int* m_dev; int64_t m_off;
   const int* k_dev; int64_t k_off;
+  // SwiGLU's backward behind the product of dh (EXT instantiations): gt and u share C's layout and become dgate and dup
+  float *gt, *u;
 };
 
 // sizes that are only known on the device (block-uniform)
@@ -57,12 +59,25 @@ __device__ __forceinline__ f32x4_t load4(const float* p, int64_t i, int left) {
   return v;
 }
 
-__device__ __forceinline__ void store_c(const Fp32GemmParams& p, float alpha, int gm, int gn, float acc) {
+// gate and up of an element of dh, requested ahead of it: behind it they are one more latency at the end of the launch
+__device__ __forceinline__ float2 load_behind(const Fp32GemmParams& p, int gm, int gn) {
+  const size_t at = (size_t)gm * p.ldc + gn;
+  return gm < p.M && gn < p.N ? make_float2(p.gt[at], p.u[at]) : make_float2(0.f, 0.f);
+}
+
+template <bool EXT>
+__device__ __forceinline__ void store_c(const Fp32GemmParams& p, float alpha, int gm, int gn, float acc, float2 x = make_float2(0.f, 0.f)) {
   float v = alpha * acc;
   if (p.R) v += p.R[(size_t)gm * p.ldr + gn];
-  float* c = p.C + (size_t)gm * p.ldc + gn;
+  const size_t at = (size_t)gm * p.ldc + gn;
+  float* c = p.C + at;
   if (p.accumulate) v += *c;
   *c = v;
+  if constexpr (EXT) {
+    const float sg = sigmoidf_(x.x);
+    p.gt[at] = v * x.y * sg * (1.f + x.x * (1.f - sg));
+    p.u[at] = v * x.x * sg;
+  }
 }
 
 }  // namespace
@@ -183,26 +198,21 @@ __global__ __launch_bounds__(256, 2) void gemm_fp32_tile_kernel(Fp32GemmParams p
 #pragma unroll
       for (int j = 0; j < T; ++j) {
         const int gn = n0 + wn + 32 * j + lr;
-        if (gm < p.M && gn < p.N) store_c(p, alpha, gm, gn, acc[i][j][q]);
+        if (gm < p.M && gn < p.N) store_c<false>(p, alpha, gm, gn, acc[i][j][q]);
       }
     }
 }
 
 // ---- one E x E tile per block (E = 32, or 16 with v_mfma_f32_16x16x4_f32), the contraction split over NW waves ----
+// wave `wave`'s share of the tile at (m0, n0), left in its part
 template <int E, int NW, bool AKM, bool BKM, bool VEC>
-__device__ __forceinline__ void wavek_tile(Fp32GemmParams p, int tile_m, int tile_n) {
+__device__ __forceinline__ void wavek_share(const Fp32GemmParams& p, int m0, int n0, int wave, int lane, float* part) {
   constexpr int NG = 64 / E;     // lane groups, each with four consecutive k of a group of KG
   constexpr int KG = 4 * NG;     // 8 (E = 32) or 16
   constexpr int NACC = E * E / 64;
   typedef float acc_t __attribute__((ext_vector_type(NACC)));
-  __shared__ __attribute__((aligned(16))) float part[NW][E * E];
   constexpr int U = 4;   // groups whose loads are issued together
-  device_sizes(p);
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int lr = lane % E, g = lane / E;
-  const int m0 = tile_m * E, n0 = tile_n * E;
-  if (m0 >= p.M) return;                                        // whole block, before any barrier
-  if (p.K == 0 && p.K2 == 0 && p.accumulate) return;            // nothing to add
   acc_t acc;
 #pragma unroll
   for (int q = 0; q < NACC; ++q) acc[q] = 0.f;
@@ -245,22 +255,71 @@ __device__ __forceinline__ void wavek_tile(Fp32GemmParams p, int tile_m, int til
   }
   // register q of lane (lr, g) is row 4 g + q (E = 16) or 8 (q / 4) + 4 g + q % 4 (E = 32), column lr
 #pragma unroll
-  for (int q = 0; q < NACC; ++q) part[wave][(8 * (q >> 2) + 4 * g + (q & 3)) * E + lr] = acc[q];
+  for (int q = 0; q < NACC; ++q) part[(8 * (q >> 2) + 4 * g + (q & 3)) * E + lr] = acc[q];
+}
+
+template <int E, int NW, bool AKM, bool BKM, bool VEC, bool EXT>
+__device__ __forceinline__ void wavek_tile(Fp32GemmParams p, int tile_m, int tile_n) {
+  __shared__ __attribute__((aligned(16))) float part[NW][E * E];
+  device_sizes(p);
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int m0 = tile_m * E, n0 = tile_n * E;
+  if (m0 >= p.M) return;                                        // whole block, before any barrier
+  if (p.K == 0 && p.K2 == 0 && p.accumulate) return;            // nothing to add
+  constexpr int PE = (E * E + NW * 64 - 1) / (NW * 64);   // elements of C per thread
+  float2 behind[PE];
+  if constexpr (EXT) {
+#pragma unroll
+    for (int i = 0; i < PE; ++i) {
+      const int e = threadIdx.x + i * NW * 64;
+      behind[i] = load_behind(p, e < E * E ? m0 + e / E : p.M, n0 + e % E);
+    }
+  }
+  wavek_share<E, NW, AKM, BKM, VEC>(p, m0, n0, wave, lane, part[wave]);
   __syncthreads();
   float alpha = p.alpha;
   if (p.alpha_dev) alpha *= *p.alpha_dev;
-  for (int e = threadIdx.x; e < E * E; e += NW * 64) {
+#pragma unroll
+  for (int i = 0; i < PE; ++i) {
+    const int e = threadIdx.x + i * NW * 64;
+    if (e >= E * E) break;
     float v = 0.f;
 #pragma unroll
     for (int w = 0; w < NW; ++w) v += part[w][e];
     const int gm = m0 + e / E, gn = n0 + e % E;
-    if (gm < p.M && gn < p.N) store_c(p, alpha, gm, gn, v);
+    if (gm < p.M && gn < p.N) store_c<EXT>(p, alpha, gm, gn, v, behind[i]);
   }
 }
 
-template <int E, int NW, bool AKM, bool BKM, bool VEC>
+template <int E, int NW, bool AKM, bool BKM, bool VEC, bool EXT = false>
 __global__ __launch_bounds__(NW * 64) void gemm_fp32_wavek_kernel(Fp32GemmParams p) {
-  wavek_tile<E, NW, AKM, BKM, VEC>(p, blockIdx.y, blockIdx.x);
+  wavek_tile<E, NW, AKM, BKM, VEC, EXT>(p, blockIdx.y, blockIdx.x);
+}
+
+// Gate and up products (NT, same sizes and left operand) and h = silu(gate) up: tiles of 16 x 16, four waves for either.
+template <bool VEC>
+__global__ __launch_bounds__(512) void gemm_fp32_swiglu_kernel(Fp32GemmParams p, const float* B_up, float* C_up, float* h) {
+  __shared__ __attribute__((aligned(16))) float part[8][256];
+  __shared__ float gate[256];
+  device_sizes(p);
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), e = threadIdx.x & 255;
+  const bool up = wave >= 4;
+  const int m0 = blockIdx.y * 16, n0 = blockIdx.x * 16;
+  if (m0 >= p.M) return;   // whole block, before any barrier
+  if (up) { p.B = B_up; p.C = C_up; }
+  wavek_share<16, 4, true, true, VEC>(p, m0, n0, wave & 3, lane, part[wave]);
+  __syncthreads();
+  float v = 0.f;
+#pragma unroll
+  for (int w = 0; w < 4; ++w) v += part[(up ? 4 : 0) + w][e];
+  v *= p.alpha;
+  if (!up) gate[e] = v;
+  __syncthreads();
+  const int gm = m0 + e / 16, gn = n0 + e % 16;
+  if (gm >= p.M || gn >= p.N) return;
+  const size_t at = (size_t)gm * p.ldc + gn;
+  p.C[at] = v;
+  if (up) h[at] = gate[e] * sigmoidf_(gate[e]) * v;
 }
 
 // Several independent products of one layout in one launch: a product of the fp32 configuration is 4 us of launch and
@@ -275,7 +334,7 @@ __global__ __launch_bounds__(256) void gemm_fp32_group_kernel(Fp32Group g) {
   for (int k = 1; k < kMaxGemmGroup; ++k)
     if (k < g.n && (int)blockIdx.x >= g.first[k]) i = k;
   const int tile = blockIdx.x - g.first[i], tiles_n = (g.p[i].N + 15) / 16;
-  wavek_tile<16, 4, AKM, BKM, VEC>(g.p[i], tile / tiles_n, tile % tiles_n);
+  wavek_tile<16, 4, AKM, BKM, VEC, false>(g.p[i], tile / tiles_n, tile % tiles_n);
 }
 
 namespace {
@@ -290,26 +349,34 @@ namespace {
 constexpr int64_t kBigTiles = 256, kSmallTiles = 192;
 constexpr int64_t kWideK = 1024;
 
-template <int E, bool AKM, bool BKM, bool VEC>
+template <int E, bool AKM, bool BKM, bool VEC, bool EXT>
 void launch_wavek(const Fp32GemmParams& p, dim3 grid, hipStream_t s) {
-  if ((int64_t)p.K + p.K2 >= kWideK) hipLaunchKernelGGL((gemm_fp32_wavek_kernel<E, 16, AKM, BKM, VEC>), grid, dim3(1024), 0, s, p);
-  else hipLaunchKernelGGL((gemm_fp32_wavek_kernel<E, 4, AKM, BKM, VEC>), grid, dim3(256), 0, s, p);
+  if ((int64_t)p.K + p.K2 >= kWideK) hipLaunchKernelGGL((gemm_fp32_wavek_kernel<E, 16, AKM, BKM, VEC, EXT>), grid, dim3(1024), 0, s, p);
+  else hipLaunchKernelGGL((gemm_fp32_wavek_kernel<E, 4, AKM, BKM, VEC, EXT>), grid, dim3(256), 0, s, p);
 }
 
-template <bool AKM, bool BKM, bool VEC>
+template <bool AKM, bool BKM, bool VEC, bool EXT>
 hipError_t launch_fp32_layout(const Fp32GemmParams& p, hipStream_t s) {
   auto tiles = [&](int64_t e) { return ((p.M + e - 1) / e) * ((p.N + e - 1) / e); };
   auto grid = [&](int e) { return dim3((unsigned)((p.N + e - 1) / e), (unsigned)((p.M + e - 1) / e)); };
-  if (tiles(128) >= kBigTiles) hipLaunchKernelGGL((gemm_fp32_tile_kernel<2, AKM, BKM, VEC>), grid(128), dim3(256), 0, s, p);
-  else if (tiles(64) >= kSmallTiles) hipLaunchKernelGGL((gemm_fp32_tile_kernel<1, AKM, BKM, VEC>), grid(64), dim3(256), 0, s, p);
-  else if (tiles(32) >= kSmallTiles) launch_wavek<32, AKM, BKM, VEC>(p, grid(32), s);
-  else launch_wavek<16, AKM, BKM, VEC>(p, grid(16), s);
+  if constexpr (!EXT) {   // (see gemm_swiglu_supported)
+    if (tiles(128) >= kBigTiles) {
+      hipLaunchKernelGGL((gemm_fp32_tile_kernel<2, AKM, BKM, VEC>), grid(128), dim3(256), 0, s, p);
+      return hipGetLastError();
+    }
+    if (tiles(64) >= kSmallTiles) {
+      hipLaunchKernelGGL((gemm_fp32_tile_kernel<1, AKM, BKM, VEC>), grid(64), dim3(256), 0, s, p);
+      return hipGetLastError();
+    }
+  }
+  if (tiles(32) >= kSmallTiles) launch_wavek<32, AKM, BKM, VEC, EXT>(p, grid(32), s);
+  else launch_wavek<16, AKM, BKM, VEC, EXT>(p, grid(16), s);
   return hipGetLastError();
 }
 
-template <bool AKM, bool BKM>
+template <bool AKM, bool BKM, bool EXT = false>
 hipError_t launch_fp32_vec(const Fp32GemmParams& p, bool vec, hipStream_t s) {
-  return vec ? launch_fp32_layout<AKM, BKM, true>(p, s) : launch_fp32_layout<AKM, BKM, false>(p, s);
+  return vec ? launch_fp32_layout<AKM, BKM, true, EXT>(p, s) : launch_fp32_layout<AKM, BKM, false, EXT>(p, s);
 }
 
 }  // namespace
@@ -324,6 +391,7 @@ bool fp32_params(const GemmArgs& a, Fp32GemmParams& p, bool& vec) {   // false: 
   p.M = (int)a.M; p.N = (int)a.N; p.K = (int)a.K; p.K2 = a.A2 ? (int)a.K2 : 0;
   p.alpha = a.alpha; p.accumulate = a.accumulate;
   p.m_dev = a.m_dev; p.m_off = a.m_off; p.k_dev = a.k_dev; p.k_off = a.k_off;
+  p.gt = p.u = nullptr;
   // 16-byte loads where every row of every operand starts on a 16-byte boundary
   vec = a.lda % 4 == 0 && a.ldb % 4 == 0 && (((uintptr_t)a.A | (uintptr_t)a.B | (uintptr_t)a.A2 | (uintptr_t)a.B2) & 15) == 0;
   return true;
@@ -336,6 +404,40 @@ hipError_t launch_fp32_group(const Fp32Group& g, bool vec, hipStream_t s) {
   return hipGetLastError();
 }
 }  // namespace
+
+// The sizes whose products run on tiles of 16 or 32: there a launch of its own is what the pass over the activations costs, and it
+// waits for the products' last block (a step of 128 rows: 181.0 us with the two passes of SwiGLU as launches, 178.0 without).
+// AdamW behind the weight gradients in the same way was slower (179.9): it is bound by memory, and these kernels have few loads in flight.
+bool gemm_swiglu_supported(const GemmArgs& a) {
+  Fp32GemmParams p;
+  bool vec;
+  return a.in_dtype == kF32 && a.out_dtype == kF32 && a.M > 0 && a.N > 0 && !a.residual && !a.A2 && !a.accumulate && !a.alpha_dev &&
+         fp32_params(a, p, vec) && a.K < kWideK && ((a.M + 63) / 64) * ((a.N + 63) / 64) < kSmallTiles;
+}
+
+hipError_t launch_gemm_swiglu_fwd(const GemmArgs& a, const GemmArgs& up, float* h, hipStream_t s) {
+  Fp32GemmParams p, q;
+  bool vec, vec_up;
+  if (!gemm_swiglu_supported(a) || !gemm_swiglu_supported(up) || a.layout != kNT || up.layout != kNT || up.A != a.A || up.M != a.M || up.N != a.N ||
+      up.K != a.K || up.lda != a.lda || up.ldb != a.ldb || up.ldc != a.ldc || up.m_dev != a.m_dev || up.m_off != a.m_off ||
+      !fp32_params(a, p, vec) || !fp32_params(up, q, vec_up)) return hipErrorInvalidValue;
+  ProfScope ps("gemm_fp32_swiglu", 4.0 * a.M * a.N * (double)a.K, 4.0 * (a.K * (a.M + 2.0 * a.N) + 3.0 * a.M * a.N), s);
+  if (a.m_dev) prof_dynamic(a.m_dev, a.m_off, a.M);
+  const dim3 grid((unsigned)((a.N + 15) / 16), (unsigned)((a.M + 15) / 16));
+  if (vec && vec_up) hipLaunchKernelGGL(gemm_fp32_swiglu_kernel<true>, grid, dim3(512), 0, s, p, q.B, q.C, h);
+  else hipLaunchKernelGGL(gemm_fp32_swiglu_kernel<false>, grid, dim3(512), 0, s, p, q.B, q.C, h);
+  return hipGetLastError();
+}
+
+hipError_t launch_gemm_swiglu_bwd(const GemmArgs& a, float* gt, float* u, hipStream_t s) {
+  Fp32GemmParams p;
+  bool vec;
+  if (!gemm_swiglu_supported(a) || a.layout != kNN || !fp32_params(a, p, vec)) return hipErrorInvalidValue;
+  ProfScope ps("gemm_fp32_swiglu_bwd", 2.0 * a.M * a.N * (double)a.K, 4.0 * (a.K * (a.M + (double)a.N) + 5.0 * a.M * a.N), s);
+  if (a.m_dev) prof_dynamic(a.m_dev, a.m_off, a.M);
+  p.gt = gt; p.u = u;
+  return launch_fp32_vec<true, false, true>(p, vec, s);
+}
 
 hipError_t launch_gemm_fp32(const GemmArgs& a, hipStream_t s) {
   if (a.M <= 0 || a.N <= 0) return hipSuccess;

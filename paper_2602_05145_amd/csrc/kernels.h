@@ -49,7 +49,7 @@ hipError_t launch_gemm_simple(const GemmArgs& a, hipStream_t s);
 hipError_t launch_gemm(const GemmArgs& a, hipStream_t s);  // picks among the three
 // A weight gradient (TN, float result) whose AdamW update follows in the same launch: the product's epilogue holds the final
 // gradient, so it is written once and never read back.  m, v and master share C's layout, w is the bf16 weight re-rounded from
-// the master copy; dyn as in AdamArgs.
+// the master copy (of an fp32 gain: master is the gain itself, w NULL); dyn as in AdamArgs.
 struct AdamTarget {
   float *m, *v, *master;
   void* w;
@@ -61,6 +61,11 @@ bool gemm_adam_supported(const GemmArgs& a, const AdamTarget& t);
 hipError_t launch_gemm_adam(const GemmArgs& a, const AdamTarget& t, hipStream_t s);
 constexpr int kMaxGemmGroup = 6;
 hipError_t launch_gemm_group(const GemmArgs* a, int n, hipStream_t s);  // independent products, in one launch where small
+// fp32, both sizes of the MLP's activations at once.  Forward: gate and up products and h = silu(gate) up in one launch; backward:
+// the product of dh, with dgate and dup written over gate and up.  False where the sizes call for separate launches.
+bool gemm_swiglu_supported(const GemmArgs& gate_or_dh);
+hipError_t launch_gemm_swiglu_fwd(const GemmArgs& gate, const GemmArgs& up, float* h, hipStream_t s);
+hipError_t launch_gemm_swiglu_bwd(const GemmArgs& dh, float* gt, float* u, hipStream_t s);
 
 // ---- elementwise.hip ------------------------------------------------------------------------
 // Row plan of the LM head.  keep_t = mask_t != 0 and 0 <= token_t < V.  scal[0] = N = max(1, #keep),
@@ -96,7 +101,10 @@ size_t rmsnorm_bwd_scratch_bytes(int64_t rows, int d);
 hipError_t launch_rmsnorm_bwd(int64_t rows, int d, const void* dy, const void* x, const void* g,
                               const float* rstd, const void* res, void* dx, float* dg,
                               float* dg_partial, int dtype, const int* rows_dev, hipStream_t s);   // dg == NULL: leaves dg_partial to launch_colsums
-struct ColSums { const float* part[3]; float* out[3]; };
+struct ColSums {
+  const float* part[3]; float* out[3];
+  AdamTarget upd[3];   // optional (m set): the update of the gain whose gradient out[i] is
+};
 // out[i] (accumulate: +)= the column sums of n launches' dg_partial, all over (rows, d, dtype)
 hipError_t launch_colsums(const ColSums& cs, int n, int64_t rows, int d, int dtype, int accumulate, hipStream_t s);
 hipError_t launch_rope_table(int S, int dh, float theta, float* cs, hipStream_t s);  // cs [S, dh/2, 2]

@@ -122,6 +122,8 @@ __device__ __forceinline__ float block_sum_lds(float v, float* red) {
   return t;
 }
 
+__device__ __forceinline__ float sigmoidf_(float x) { return 1.0f / (1.0f + __expf(-x)); }
+
 // One element of AdamW: g is the gradient, th the weight (float, or the master copy of a bf16 one).
 struct AdamRate { float lr, decay, beta1, beta2, eps, inv_bc1, inv_sqrt_bc2; };
 __device__ __forceinline__ void adam_update(const AdamRate& a, float g, float& m, float& v, float& th) {

@@ -278,16 +278,24 @@ struct Update {
 };
 enum : int { kWFc, kG1, kWQkv, kWO, kG2, kWGate, kWUp, kWDown, kG3, kWLm, kWIn };   // places in Update::t
 
+// Where tensor `i`, from element `off` on, is updated
+AdamTarget target(const Update& u, int i, int64_t off) {
+  AdamTarget t = u.rate;
+  const AdamTensor& a = u.t[i];
+  t.m = a.m + off; t.v = a.v + off;
+  t.master = a.master ? a.master + off : (float*)a.p + off;
+  t.w = a.master ? (char*)a.p + 2 * off : nullptr;
+  return t;
+}
+
 // The gradient product of weight `i` (columns from `col0` on, for a weight made by two products), with the weight's update
-// where the matrix kernels can do it.  complete: the product is the weight's last one.
+// where the kernels can do it.  complete: the product is the weight's last one.
 hipError_t run_dw_update(const GemmArgs& g0, Update* u, int i, int64_t col0, bool complete, char* ws, const Plan& p, hipStream_t s) {
   if (!u || g0.in_dtype != kBF16) return run_gemm(g0, ws, p, s);
   GemmArgs g = g0;
   g.scratch = ws + p.splitk;
   g.scratch_bytes = p.splitk_bytes;
-  AdamTarget t = u->rate;
-  const AdamTensor& a = u->t[i];
-  t.m = a.m + col0; t.v = a.v + col0; t.master = a.master + col0; t.w = (char*)a.p + 2 * col0;
+  const AdamTarget t = target(*u, i, col0);
   if (!gemm_adam_supported(g, t)) return launch_gemm(g, s);
   if (complete) u->done |= 1u << i;
   return launch_gemm_adam(g, t, s);
@@ -408,9 +416,13 @@ int enqueue_trunk(const tide_draft_config* c, const tide_draft_tensors* P, const
   {
     GemmArgs g[2] = {rows_gemm(kNT, p.F, p.d, ws + p.bn, p.d, P->w_gate, p.d, ws + p.gt, p.F),
                      rows_gemm(kNT, p.F, p.d, ws + p.bn, p.d, P->w_up, p.d, ws + p.u, p.F)};
-    TIDE_HIP(run_gemms(g, 2, ws, p, s), "gemm gate and up");
+    if (gemm_swiglu_supported(g[0])) {
+      TIDE_HIP(launch_gemm_swiglu_fwd(g[0], g[1], (float*)(ws + p.h), s), "gemm gate and up, swiglu");
+    } else {
+      TIDE_HIP(run_gemms(g, 2, ws, p, s), "gemm gate and up");
+      TIDE_HIP(launch_swiglu_fwd(T * p.F, ws + p.gt, ws + p.u, ws + p.h, dt, p.F, cnt, s), "swiglu");
+    }
   }
-  TIDE_HIP(launch_swiglu_fwd(T * p.F, ws + p.gt, ws + p.u, ws + p.h, dt, p.F, cnt, s), "swiglu");
   {
     GemmArgs g = rows_gemm(kNT, p.d, p.F, ws + p.h, p.F, P->w_down, p.F, ws + p.x2, p.d);
     g.residual = ws + p.x1; g.ldr = p.d;
@@ -701,9 +713,12 @@ static int enqueue_backward(const tide_draft_config* cfg, const tide_draft_tenso
   // final norm (plus, in the unroll, what the step after sends back into x2)
   TIDE_HIP(launch_rmsnorm_bwd(T, (int)p.d, ws + p.dyhat, ws + p.x2, P->g3, (const float*)(ws + p.r3), o.dx2_extra, ws + p.dx2, nullptr, dgp[2], dt, cnt, s), "rmsnorm3 bwd");
   // x2 = x1 + h W_down^T
-  TIDE_HIP(run_gemm(rows_dx(p.F, p.d, ws + p.dx2, p.d, P->w_down, p.F, ws + p.dh, p.F), ws, p, s), "gemm dh");
+  const GemmArgs dh = rows_dx(p.F, p.d, ws + p.dx2, p.d, P->w_down, p.F, ws + p.dh, p.F);
+  const bool swiglu_inside = gemm_swiglu_supported(dh);
+  if (swiglu_inside) TIDE_HIP(launch_gemm_swiglu_bwd(dh, (float*)(ws + p.gt), (float*)(ws + p.u), s), "gemm dh, swiglu bwd");
+  else TIDE_HIP(run_gemm(dh, ws, p, s), "gemm dh");
   TIDE_HIP(run_dw(rows_dw(p.d, p.F, ws + p.dx2, p.d, ws + p.h, p.F, G->w_down, p.F), kWDown), "gemm dW_down");
-  TIDE_HIP(launch_swiglu_bwd(T * p.F, ws + p.dh, ws + p.gt, ws + p.u, ws + p.gt, ws + p.u, dt, p.F, cnt, s), "swiglu bwd");
+  if (!swiglu_inside) TIDE_HIP(launch_swiglu_bwd(T * p.F, ws + p.dh, ws + p.gt, ws + p.u, ws + p.gt, ws + p.u, dt, p.F, cnt, s), "swiglu bwd");
   {
     // d bn = dGate W_gate + dUp W_up: one contraction over both operand pairs
     GemmArgs g = rows_dx(p.d, p.F, ws + p.gt, p.F, P->w_gate, p.d, ws + p.dbn, p.d);
@@ -745,7 +760,12 @@ static int enqueue_backward(const tide_draft_config* cfg, const tide_draft_tenso
   TIDE_HIP(launch_rmsnorm_bwd(T, (int)p.d, ws + p.da, ws + p.x0, P->g1, (const float*)(ws + p.r1), ws + p.dx1, ws + p.dx0, nullptr, dgp[0], dt, nullptr, s), "rmsnorm1 bwd");
   {
     // the gain gradients of the three norms
-    const ColSums cs{{dgp[0], dgp[1], dgp[2]}, {(float*)G->g1, (float*)G->g2, (float*)G->g3}};
+    ColSums cs{{dgp[0], dgp[1], dgp[2]}, {(float*)G->g1, (float*)G->g2, (float*)G->g3}};
+    if (o.upd)   // (nothing later reads the gains)
+      for (const int i : {kG1, kG2, kG3}) {
+        cs.upd[i == kG1 ? 0 : i == kG2 ? 1 : 2] = target(*o.upd, i, 0);
+        o.upd->done |= 1u << i;
+      }
     TIDE_HIP(launch_colsums(cs, 3, T, (int)p.d, dt, acc, s), "gain gradients");
   }
   const void* dfeat = ws + p.dx0;   // gradient of the step's input feature (feature-only model: x0 is the feature)
@@ -812,6 +832,7 @@ static int enqueue_adamw(const Update& u, int dtype, hipStream_t s) {
   std::memset(&a, 0, sizeof(a));
   for (int i = 0; i < u.nt; ++i)
     if (!(u.done >> i & 1)) a.t[a.nt++] = u.t[i];
+  if (a.nt == 0) return TIDE_OK;
   a.lr = u.rate.lr; a.decay = u.rate.decay; a.inv_bc1 = u.rate.inv_bc1; a.inv_sqrt_bc2 = u.rate.inv_sqrt_bc2;
   a.beta1 = u.rate.beta1; a.beta2 = u.rate.beta2; a.eps = u.rate.eps;
   a.dtype = dtype; a.dyn = u.rate.dyn;
