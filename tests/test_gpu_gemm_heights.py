@@ -12,7 +12,7 @@ kernel_name = ig._symbol("_ZN4tide16gemm_kernel_nameERKNS_8GemmArgsE", C.c_char_
 # layout, M, N, K: a last tile row and column that are partly filled, one slab or (TN) one and a remainder
 CASES = [(ig.NT, 521, 6608, 64, 128), (ig.NT, 7405, 1040, 64, 160), (ig.NT, 5830, 1544, 64, 192), (ig.NT, 7037, 1544, 64, 224),
          (ig.NN, 530, 6736, 64, 128), (ig.NN, 6542, 1176, 64, 160), (ig.NN, 6831, 1288, 64, 192), (ig.NN, 8151, 1296, 64, 224),
-         (ig.TN, 5456, 656, 65, 128), (ig.TN, 1048, 7192, 65, 160), (ig.TN, 6736, 1312, 65, 192), (ig.TN, 1552, 7184, 65, 224),
+         (ig.TN, 5456, 656, 65, 128), (ig.TN, 1048, 7192, 65, 160), (ig.TN, 1288, 7240, 301, 192), (ig.TN, 2192, 5392, 515, 224),
          (ig.NN, 1665, 5632, 2048, 160), (ig.NT, 2040, 4096, 576, 128), (ig.TN, 5632, 2048, 1333, 192)]
 
 

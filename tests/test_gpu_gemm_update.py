@@ -35,7 +35,7 @@ def test_what_a_product_with_update_serves():
 # M, N, K, the number of rows on the device (None: known to the host), old values, columns of the weight, kernel, scratch
 CASES = [(264, 136, 77, None, 0, 136, "128", 0), (264, 136, 77, None, 1, 272, "128", 0), (264, 136, 77, 13, 1, 136, "128", 0), (264, 136, 77, 0, 0, 136, "128", 0),
          (264, 136, 77, 0, 1, 136, "128", 0), (4096, 4104, 40, 33, 0, 4104, "128", 0), (5456, 656, 65, None, 1, 656, "128x256", 0),
-         (1048, 7192, 65, None, 0, 7192, "160x256", 0), (6736, 1312, 65, 1, 1, 1312, "192x256", 0), (1552, 7184, 65, None, 0, 7184, "224x256", 0),
+         (1048, 7192, 65, None, 0, 7192, "160x256", 0), (1288, 7240, 301, 1, 1, 7240, "192x256", 0), (2192, 5392, 515, None, 0, 5392, "224x256", 0),
          (248, 688, 30000, None, 1, 688, "128", 1), (248, 688, 30000, 777, 0, 688, "128", 1), (2040, 1544, 8000, None, 1, 1544, "256", 1), (2040, 1544, 8000, 4321, 0, 1544, "256", 1), (4344, 4096, 8000, None, 1, 4096, "256", 1)]
 
 
