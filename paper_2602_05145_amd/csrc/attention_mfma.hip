@@ -248,10 +248,10 @@ __device__ __forceinline__ float row_max(float x) {
 }
 constexpr int kv_tile(int D) { return BKV * pitch(D); }  // elements
 
-// Head size 64 halves the operand and accumulator registers and the LDS tiles: 119 / 168 / 125 / 147 registers for the
+// Head size 64 halves the operand and accumulator registers and the LDS tiles: 114 / 167 / 125 / 147 registers for the
 // forward, dQ, dV and dK kernels, i.e. 4, 3, 4 and 3 blocks per CU (held to 4, 4, 5 and 3 the dQ and dV kernels spill:
 // backward 1.53 -> 2.73 ms at 16 x 2048, 32 / 8 heads, with one bf16 value per probability).  Against the one-wave-per-row kernels (attention_simple.hip) that
-// served this head size: 6 x 777, 16 / 4 heads, forward + backward 17.55 -> 0.147 ms.
+// served this head size: 6 x 777, 16 / 4 heads, forward + backward 17.55 -> 0.144 ms.
 constexpr int blocks_per_cu(int D, int at64, int at128) { return D == 64 ? at64 : at128; }
 // Depth of the operand-fragment rings of the three kernels (0 in the dQ kernel: the plain loop).  Measured when the tiles
 // were still staged through registers, backward at 16 x 2048 / 2 x 16384: dQ 0 / dK-dV 4: 3.56 / 21.4 ms; 2 / 4: 3.48 /
