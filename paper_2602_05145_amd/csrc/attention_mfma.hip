@@ -225,7 +225,8 @@ __device__ __forceinline__ uint32_t not_finite(const f32x16_t (&acc)[NC], bool a
 }
 
 constexpr int BQ = 128, BKV = 64;
-constexpr float kLag = 8.0f;   // log2; see the forward kernel
+// By how much (log2) the reference that a row's sums are kept relative to may fall behind the running maximum; see the forward kernel.
+constexpr float lag(int D) { return D == 64 ? 8.0f : 0.0f; }
 
 // The waves of a SIMD belong to two blocks: the one in a phase of MFMAs alone goes before the other's vector instructions, which
 // then run under them (head size 128: forward 2 to 4 %, backward 1 to 2 %; head size 64, three or four blocks: backward 1 % slower).
@@ -345,11 +346,13 @@ __global__ __launch_bounds__(256, blocks_per_cu(D, 4, 2)) void attn_fwd_mfma_ker
   auto fetch_v = [&](int t) {
     if (t < nt) dma.issue(base, seq_bytes, sV + (t & 1) * KV_TILE, ((uint32_t)(t * BKV) * (uint32_t)ld + (uint32_t)vcol) * 2u, wave_s);
   };
-  // The sums are kept relative to m, which follows the running maximum (of the row) once it has fallen behind by kLag:
-  // probabilities are then at most 2^8, with the same relative precision, and the accumulators are rescaled once or twice per
-  // row, not in nearly every tile (one of 32 rows nearly always finds a new maximum).
+  // The sums are kept relative to m, which follows the running maximum of the row.  At head size 64 it may fall behind by 2^8: the
+  // accumulators are then rescaled once or twice per row, not in nearly every tile (one of 32 rows nearly always finds a new
+  // maximum; 6 x 777 30.4 -> 29.0 us).  At head size 128, where a probability is one bf16 value, that of the largest score has to
+  // stay the exact 1 it is relative to the maximum itself: with a lag the results were 2 % (flat scores) to 17 % (peaked ones) further from
+  // 64 bits (and 16 x 2048 took 700 us, 745 without).
   auto follow = [&](float tm) {
-    const bool moved = (tm - m) * c > kLag;   // the first tile: m = -inf, and key 0 is visible to every query
+    const bool moved = (tm - m) * c > lag(D);   // the first tile: m = -inf, and key 0 is visible to every query
     if (__builtin_amdgcn_ballot_w64(moved) != 0) {   // wave-uniform
       const float mn = moved ? tm : m, alpha = __builtin_amdgcn_exp2f((m - mn) * c);
       l *= alpha;
@@ -439,8 +442,8 @@ __global__ __launch_bounds__(256, blocks_per_cu(D, 4, 2)) void attn_fwd_mfma_ker
     // One tile is two MFMA phases: the scores of tile t + 1 (2 NK MFMAs) beside the exponentials of tile t, then its P V beside
     // the row maxima of the scores just made.  The order of MFMAs, operand reads (a ring of four fragments) and vector
     // instructions is written out and pinned: left to two waves of a SIMD that took turns by chance, the matrix pipes were 40 % and
-    // the vector units 50 % busy, one after the other.  us before / now, with the rescaling above: 16 x 2048, 32 / 8 heads 757 / 685,
-    // 4 x 1024 69 / 57 (the larger one sits at the power limit: without exponentials it takes 645, without operand reads 618).
+    // the vector units 50 % busy, one after the other.  us before / now: 16 x 2048, 32 / 8 heads 770 / 745, 4 x 1024 68.6 / 65.1
+    // (the larger one sits at the power limit: without exponentials it takes 7 % less, without operand reads 11).
     // A ring of six: the same; of eight: spills.  The same order in the dQ kernel (halves of a tile) gave nothing.
     constexpr int NS = 2 * NK, EPM = 32 / NS;   // MFMAs of a score tile, exponentials beside each
     f32x16_t sa[2], sb[2];
