@@ -438,7 +438,7 @@ __global__ __launch_bounds__(2 * BN) void gemm_mfma_kernel(std::conditional_t<AD
     TO* C = (TO*)p.C;
     const TO* R = (const TO*)p.R;
     const int wm0 = m0 + wave_m * WM, wn0 = n0 + wave_n * WN;
-    if (p.split == kSplitAll && nparts > 1) {
+    if (!ADAM && p.split == kSplitAll && nparts > 1) {
       // the partial sum as it is, tile-local; rows and columns past the matrix are not read back
       float* out = p.split_scratch + ((size_t)part * ntail + tail_index) * (size_t)(BM * BN);
 #pragma unroll
@@ -911,8 +911,8 @@ __global__ __launch_bounds__(256) void splitk_fixup_kernel(AdamTarget adam, floa
 
 // C[tile] = alpha * (the partial sums of a tile's parts, in their order) + residual + old value.  A launch that came out
 // as one part per tile has written C itself.  A block covers 2048 elements of a tile; a thread owns 8 consecutive columns.
-template <typename TO, int BT, bool ADAM = false>
-__global__ __launch_bounds__(256) void splitk_reduce_kernel(std::conditional_t<ADAM, MfmaAdamParams, MfmaParams> p) {
+template <typename TO, int BT>
+__global__ __launch_bounds__(256) void splitk_reduce_kernel(MfmaParams p) {
   constexpr int PER_ROW = BT / 8, ROWS = 256 / PER_ROW, BLOCKS = BT / ROWS;
   if (p.m_dev) p.M = max(0, min(p.M, *p.m_dev - p.m_off));
   if (p.k_dev) p.K = max(0, min(p.K, *p.k_dev - p.k_off));
@@ -927,16 +927,6 @@ __global__ __launch_bounds__(256) void splitk_reduce_kernel(std::conditional_t<A
   if (gm >= p.M || gn >= p.N) return;
   const float* src = p.split_scratch + (size_t)tail * (BT * BT) + row * BT + col;
   const size_t stride = (size_t)ntail * (BT * BT);
-  const size_t at = (size_t)gm * p.ldc + gn;
-  float4 am[2], av[2], ath[2];
-  if constexpr (ADAM) {
-#pragma unroll
-    for (int h = 0; h < 2; ++h) {
-      am[h] = load_once(p.adam.m + at + 4 * h);
-      av[h] = load_once(p.adam.v + at + 4 * h);
-      ath[h] = load_once(p.adam.master + at + 4 * h);
-    }
-  }
   float v[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
   for (int j = 0; j < sa.parts; j += 4) {        // four parts' loads in flight at a time
     Raw8<float> x[4];
@@ -955,20 +945,13 @@ __global__ __launch_bounds__(256) void splitk_reduce_kernel(std::conditional_t<A
   }
   float alpha = p.alpha;
   if (p.alpha_dev) alpha *= *p.alpha_dev;
-  TO* C = (TO*)p.C + at;
+  TO* C = (TO*)p.C + (size_t)gm * p.ldc + gn;
   float r[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f}, old[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
   if (p.R) ld8((const TO*)p.R, (size_t)gm * p.ldr + gn, r);
   if (p.accumulate) ld8(C, 0, old);
 #pragma unroll
   for (int e = 0; e < 8; ++e) v[e] = alpha * v[e] + r[e] + old[e];
-  if constexpr (ADAM) {
-    const AdamRate rate = adam_rate(p.adam);
-#pragma unroll
-    for (int h = 0; h < 2; ++h)
-      adam_store(p.adam, rate, (float*)p.C, at + 4 * h, make_float4(v[4 * h], v[4 * h + 1], v[4 * h + 2], v[4 * h + 3]), am[h], av[h], ath[h]);
-  } else {
-    st8(C, 0, v);
-  }
+  st8(C, 0, v);
 }
 
 namespace {
@@ -1250,16 +1233,12 @@ hipError_t launch_tiles(const P& p, const SplitGrid& all, hipStream_t s) {   // 
   const int tiles = q.tiles_m * q.tiles_n;
   const int64_t items = q.split == kSplitAll ? all.blocks
                       : q.split == kSplitTail ? q.split_full + (int64_t)(tiles - q.split_full) * q.split_s : tiles;
-  if constexpr (BM == BN) {
-    if constexpr (!ADAM) {
-      if (whole_slabs<AMM, BNM>(p)) hipLaunchKernelGGL((gemm_mfma_kernel<BM, BN, AMM, BNM, TO, true>), dim3((unsigned)items), dim3(2 * BN), 0, s, q);
-      else hipLaunchKernelGGL((gemm_mfma_kernel<BM, BN, AMM, BNM, TO, false>), dim3((unsigned)items), dim3(2 * BN), 0, s, q);
-    } else {
-      hipLaunchKernelGGL((gemm_mfma_kernel<BM, BN, AMM, BNM, TO, false, true>), dim3((unsigned)items), dim3(2 * BN), 0, s, q);
-    }
+  if constexpr (BM == BN && !ADAM) {
+    if (whole_slabs<AMM, BNM>(p)) hipLaunchKernelGGL((gemm_mfma_kernel<BM, BN, AMM, BNM, TO, true>), dim3((unsigned)items), dim3(2 * BN), 0, s, q);
+    else hipLaunchKernelGGL((gemm_mfma_kernel<BM, BN, AMM, BNM, TO, false>), dim3((unsigned)items), dim3(2 * BN), 0, s, q);
     const hipError_t e = hipGetLastError();
     if (e != hipSuccess || q.split != kSplitAll) return e;
-    hipLaunchKernelGGL((splitk_reduce_kernel<TO, BM, ADAM>), dim3((unsigned)(all.tail * (BM * BM / 2048))), dim3(256), 0, s, q);
+    hipLaunchKernelGGL((splitk_reduce_kernel<TO, BM>), dim3((unsigned)(all.tail * (BM * BM / 2048))), dim3(256), 0, s, q);
   } else {
     hipLaunchKernelGGL((gemm_mfma_kernel<BM, BN, AMM, BNM, TO, !(AMM && BNM), ADAM>), dim3((unsigned)items), dim3(2 * BN), 0, s, q);
   }
@@ -1351,10 +1330,18 @@ hipError_t launch_gemm_mfma(const GemmArgs& a, hipStream_t s) {
   return e != hipSuccess || p.split != kSplitTail ? e : launch_fixup<false>(p, AdamTarget{}, s);
 }
 
+// (a product whose tiles are all split is left as it is: the update in the kernel that adds the parts took longer than the pass
+// over the weight, 8000 rows of a 1280 / 3440 wide step 3736 us so, 3613 with the pass)
 bool gemm_adam_supported(const GemmArgs& a, const AdamTarget& t) {
   return a.layout == kTN && a.out_dtype == kF32 && !a.residual && !a.A2 && gemm_mfma_supported(a) && a.N % 8 == 0 && a.ldc % 8 == 0 &&
-         !(((uintptr_t)a.C | (uintptr_t)t.m | (uintptr_t)t.v | (uintptr_t)t.master | (uintptr_t)t.w) & 15);
+         !(((uintptr_t)a.C | (uintptr_t)t.m | (uintptr_t)t.v | (uintptr_t)t.master | (uintptr_t)t.w) & 15) && plan_launch(a, true).split != kSplitAll;
 }
+
+// A tile's update takes its CU 8 to 12 us (128 x 128) with the rest of the chip idle or not; one pass over the weights left takes 5 us and
+// 34 bytes per element.  Whole steps (us; no update in a product / in all / from half the CUs' worth of tiles on): width 256, 64 rows 228 /
+// 289 / 227; width 512, 1000 rows 628 / 630 / 582; 768, 300 rows 631 / 598 / 555; 1024, 1000 rows 1011 / 911 / 907; 1536, 300 rows
+// 1089 / 931 / 935.  With a bound of 4 M elements the last takes 965, with 1 M the one of width 768 takes 578.
+bool gemm_adam_pays(const GemmArgs& a) { return tile_count(a.M, a.N, 128) > 128; }
 
 hipError_t launch_gemm_adam(const GemmArgs& a, const AdamTarget& t, hipStream_t s) {
   if (!gemm_adam_supported(a, t)) return hipErrorInvalidValue;

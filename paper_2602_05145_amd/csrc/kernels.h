@@ -58,6 +58,7 @@ struct AdamTarget {
 };
 const char* gemm_adam_kernel_name(const GemmArgs& a);
 bool gemm_adam_supported(const GemmArgs& a, const AdamTarget& t);
+bool gemm_adam_pays(const GemmArgs& a);                  // faster than the product and a share of the pass over all weights
 hipError_t launch_gemm_adam(const GemmArgs& a, const AdamTarget& t, hipStream_t s);
 constexpr int kMaxGemmGroup = 6;
 hipError_t launch_gemm_group(const GemmArgs* a, int n, hipStream_t s);  // independent products, in one launch where small

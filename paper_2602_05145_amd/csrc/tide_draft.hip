@@ -289,14 +289,14 @@ AdamTarget target(const Update& u, int i, int64_t off) {
 }
 
 // The gradient product of weight `i` (columns from `col0` on, for a weight made by two products), with the weight's update
-// where the kernels can do it.  complete: the product is the weight's last one.
+// where the kernels can do it and it pays.  complete: the product is the weight's last one.
 hipError_t run_dw_update(const GemmArgs& g0, Update* u, int i, int64_t col0, bool complete, char* ws, const Plan& p, hipStream_t s) {
   if (!u || g0.in_dtype != kBF16) return run_gemm(g0, ws, p, s);
   GemmArgs g = g0;
   g.scratch = ws + p.splitk;
   g.scratch_bytes = p.splitk_bytes;
   const AdamTarget t = target(*u, i, col0);
-  if (!gemm_adam_supported(g, t)) return launch_gemm(g, s);
+  if (!gemm_adam_pays(g) || !gemm_adam_supported(g, t)) return launch_gemm(g, s);
   if (complete) u->done |= 1u << i;
   return launch_gemm_adam(g, t, s);
 }

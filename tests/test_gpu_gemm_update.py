@@ -17,6 +17,7 @@ class AdamTarget(C.Structure):
 supported = ig._symbol("_ZN4tide19gemm_adam_supportedERKNS_8GemmArgsERKNS_10AdamTargetE", C.c_bool, [C.POINTER(ig.GemmArgs), C.POINTER(AdamTarget)])
 launch = ig._symbol("_ZN4tide16launch_gemm_adamERKNS_8GemmArgsERKNS_10AdamTargetEP12ihipStream_t", C.c_int,
                     [C.POINTER(ig.GemmArgs), C.POINTER(AdamTarget), C.c_void_p])
+pays = ig._symbol("_ZN4tide14gemm_adam_paysERKNS_8GemmArgsE", C.c_bool, [C.POINTER(ig.GemmArgs)])
 name = ig._symbol("_ZN4tide21gemm_adam_kernel_nameERKNS_8GemmArgsE", C.c_char_p, [C.POINTER(ig.GemmArgs)])
 RATE = dict(lr=1e-3, decay=1 - 1e-5, beta1=0.9, beta2=0.999, eps=1e-8, c1=1 / (1 - 0.9 ** 3), c2=(1 - 0.999 ** 3) ** -0.5)
 
@@ -32,11 +33,28 @@ def test_what_a_product_with_update_serves():
         assert not supported(ig.args(ig.TN, 264, 136, 77, out=ig.F32), AdamTarget(**dict(dict(m=256, v=256, master=256, w=256), **{f: 264})))
 
 
+def test_few_tiles_and_split_ones_leave_the_update_to_the_pass_over_all_weights():
+    """A tile's update keeps its CU busy for 8 us and more however idle the others are: not with less than half of them at work."""
+    for m, n, k in ((256, 256, 64), (688, 256, 1000), (1376, 512, 300), (1024, 1024, 5000), (2048, 1024, 64)):
+        assert not pays(ig.args(ig.TN, m, n, k, out=ig.F32)), (m, n, k)
+    for m, n, k in ((2816, 1024, 64), (1536, 1536, 300), (5632, 2048, 2560), (128256, 4096, 1700)):
+        assert pays(ig.args(ig.TN, m, n, k, out=ig.F32)), (m, n, k)
+    ok = AdamTarget(m=256, v=256, master=256, w=256)
+    for m, n, k, k_dev in ((248, 688, 30000, 0), (2040, 1544, 8000, 256), (2816, 1024, 5000, 0), (3440, 1280, 8000, 0)):
+        g = ig.args(ig.TN, m, n, k, out=ig.F32, k_dev=k_dev)
+        assert supported(g, ok)
+        g.scratch, g.scratch_bytes = 256, ig.scratch_bytes(g)
+        assert g.scratch_bytes > 0 and not supported(g, ok), (m, n, k)     # all tiles split: a kernel of its own adds the parts
+    g = ig.args(ig.TN, 4344, 4096, 8000, out=ig.F32)
+    g.scratch, g.scratch_bytes = 256, ig.scratch_bytes(g)
+    assert g.scratch_bytes > 0 and supported(g, ok)                        # the last round alone: 16 of 272 tiles
+
+
 # M, N, K, the number of rows on the device (None: known to the host), old values, columns of the weight, kernel, scratch
 CASES = [(264, 136, 77, None, 0, 136, "128", 0), (264, 136, 77, None, 1, 272, "128", 0), (264, 136, 77, 13, 1, 136, "128", 0), (264, 136, 77, 0, 0, 136, "128", 0),
          (264, 136, 77, 0, 1, 136, "128", 0), (4096, 4104, 40, 33, 0, 4104, "128", 0), (5456, 656, 65, None, 1, 656, "128x256", 0),
          (1048, 7192, 65, None, 0, 7192, "160x256", 0), (1288, 7240, 301, 1, 1, 7240, "192x256", 0), (2192, 5392, 515, None, 0, 5392, "224x256", 0),
-         (248, 688, 30000, None, 1, 688, "128", 1), (248, 688, 30000, 777, 0, 688, "128", 1), (2040, 1544, 8000, None, 1, 1544, "256", 1), (2040, 1544, 8000, 4321, 0, 1544, "256", 1), (4344, 4096, 8000, None, 1, 4096, "256", 1)]
+         (248, 688, 30000, None, 1, 688, "128", 0), (2040, 1544, 8000, 4321, 0, 1544, "128", 0), (4344, 4096, 8000, None, 1, 4096, "256", 1)]
 
 
 @pytest.mark.gpu
@@ -86,14 +104,16 @@ def test_gradient_and_update(M, N, K, rows, add, ld, kernel, split):
 
 
 @pytest.mark.gpu
-@pytest.mark.parametrize("kw,block", [(dict(), 0), (dict(batch=3, seq=37), 64), (dict(hidden=264, n_heads=2, n_kv_heads=1, head_dim=132, ffn=332), 0)])
+@pytest.mark.parametrize("kw,block", [(dict(), 0), (dict(batch=3, seq=37), 64), (dict(hidden=264, n_heads=2, n_kv_heads=1, head_dim=132, ffn=332), 0),
+                                      (dict(ffn=16640, vocab=512), 0), (dict(ffn=16652), 0)])
 def test_a_step_updates_every_weight_once(kw, block):
-    """Weights whose product can carry the update and (ffn 332: rows no 16-byte piece fits) weights whose product cannot, in one step; LM head in
-    blocks, of which the last carries it.  Against the update in float64 from the gradients that the step returned."""
+    """Weights whose product carries the update (W_lm; with ffn 16640 the MLP's) and weights whose product does not (few tiles; ffn 332 and 16652:
+    rows no 16-byte piece fits), in one step; LM head in blocks, of which the last carries it.  Against the update in float64 from the gradients that the step returned."""
     from paper_2602_05145_amd import runtime
-    cfg = W.get_config("small", **dict(dict(batch=2, seq=64, target_hidden=256, hidden=256, n_heads=2, n_kv_heads=1, head_dim=128, ffn=512, vocab=2048), **kw))
+    cfg = W.get_config("small", **dict(dict(batch=2, seq=64, target_hidden=256, hidden=256, n_heads=2, n_kv_heads=1, head_dim=128, ffn=512, vocab=16640), **kw))
     wl = W.make_workload(cfg)
     cfg["lm_block_rows"] = block
+    assert pays(ig.args(ig.TN, max(cfg["vocab"], cfg["ffn"]), cfg["hidden"], cfg["batch"] * cfg["seq"], out=ig.F32))
     tr = runtime.trainer_from_workload(cfg, wl)
     before = {k: x.astype(np.float64) for k, x in tr.host(tr.master).items()}
     print("step", kw, block, flush=True)
@@ -108,3 +128,23 @@ def test_a_step_updates_every_weight_once(kw, block):
         ok = (np.abs(master[k] - want) <= 2.0 ** -22 * (np.abs(before[k]) + 4 * cfg["lr"])) | (np.abs(g) < 1e-16)
         assert ok.all(), (k, np.abs(master[k] - want).max())
         assert np.array_equal(params[k], W.round_to_bf16(master[k])), k
+
+
+@pytest.mark.gpu
+def test_an_input_projection_is_updated_by_its_two_products():
+    """W_in, whose column halves are two products (144 tiles each), against the update in float64 from the gradient that the step returned."""
+    from tests.test_gpu_token_input import _setup
+    cfg = W.get_config("small", batch=2, seq=33, target_hidden=64, hidden=1536, n_heads=12, n_kv_heads=4, head_dim=128, ffn=256, vocab=512)
+    assert pays(ig.args(ig.TN, cfg["hidden"], cfg["hidden"], 66, out=ig.F32, ldc=2 * cfg["hidden"]))
+    wl, ti, tr, *_ = _setup(cfg, embed_rows=57)
+    tr.set_token_input(ti["embed"], ti["input_ids"], ti["w_in"])
+    before = tr.master_w_in.double()
+    print("token-input step", flush=True)
+    tr.train_step_tok(cfg["lr"])
+    torch.cuda.synchronize()
+    g = tr.grad_w_in.double()
+    want = before * (1 - cfg["lr"] * cfg["weight_decay"]) - cfg["lr"] * g / (g.abs() + cfg["adam_eps"])
+    # as above
+    ok = ((tr.master_w_in.double() - want).abs() <= 2.0 ** -22 * (before.abs() + 4 * cfg["lr"])) | ((g.abs() < 1e-16) & (g != 0))
+    assert bool(ok.all()) and float(g.abs().max()) > 0
+    assert torch.equal(tr.w_in, tr.master_w_in.bfloat16())
