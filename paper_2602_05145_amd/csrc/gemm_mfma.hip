@@ -1099,9 +1099,9 @@ TileCost tile_cost(int BM, bool tn) {
     default: return tn ? TileCost{770, 18, 535, 9500} : TileCost{736, 15, 540, 6500};
   }
 }
-int64_t rounds_time(int BM, bool tn, int64_t tiles, int64_t slabs) {
+int64_t rounds_time(int BM, bool tn, int64_t tiles, int64_t slabs, int64_t fed = 0) {   // fed: the least that a slab's operands take to arrive
   const TileCost c = tile_cost(BM, tn);
-  const int64_t rounds = tiles / 256, rest = tiles % 256, last = std::max<int64_t>(c.least, c.full - c.slope * (256 - rest) / 10);
+  const int64_t rounds = tiles / 256, rest = tiles % 256, last = std::max({(int64_t)c.least, c.full - c.slope * (256 - rest) / 10, fed});
   // behind full rounds a partly filled one has the memory for its float results nearly to itself (TN 14336 x 4096 x 915, 3.5 rounds: 131 us,
   // in four full ones of 224 rows 136)
   const int64_t fixed = tn && rounds ? c.fixed * (90 + rest * 166 / 256) / 256 : c.fixed;
@@ -1126,7 +1126,11 @@ int64_t launch_time(const GemmArgs& a, const LaunchPlan& lp, int64_t rows) {
   if (lp.BN == 256) {
     const SplitAll sa = lp.split == kSplitAll ? split_all<256>((int)tiles, (int)slabs) : SplitAll{(int)tiles, 1};
     const int64_t tail = tiles - sa.full, part = (slabs + sa.parts - 1) / sa.parts;
-    return rounds_time(lp.BM, tn, sa.full, slabs) + (tail ? rounds_time(256, tn, tail * sa.parts, part) + 4000 + 40 * tail * sa.parts : 0);
+    // One row of tiles reads B once, from memory where it is larger than the 256 MB of the last cache.  A CU receives about 28 GB/s of
+    // that, so that fewer than 168 do not reach the 4.7 TB/s of the chip (us, small tiles, split / 125 large ones: NT 39 x 32000 x 6144
+    // 83 / 111, NN 157 x 32000 x 25600 355 / 438; small ones / 197 large ones: NT 127 x 50304 x 14336 334 / 308)
+    const int64_t fed = rows <= lp.BM && tiles < 168 && 2 * a.N * slabs * 64 > 256000000 ? 1170 : 0;
+    return rounds_time(lp.BM, tn, sa.full, slabs, fed) + (tail ? rounds_time(256, tn, tail * sa.parts, part) + 4000 + 40 * tail * sa.parts : 0);
   }
   const SplitAll sa = lp.split == kSplitAll ? split_all<128>((int)tiles, (int)slabs) : SplitAll{(int)tiles, 1};
   const int64_t blocks = sa.full + (tiles - sa.full) * sa.parts, part = (slabs + sa.parts - 1) / sa.parts;
@@ -1137,8 +1141,8 @@ int64_t launch_time(const GemmArgs& a, const LaunchPlan& lp, int64_t rows) {
 // costs above, which allow for the power that idle CUs leave to the others, like them better than tile_edge did.  us, by
 // tile_edge / so: NN 1665 x 5632 x 2048 47.8 / 35.0 (160 rows), NT 3400 x 14336 x 4096 332 / 290 (192), NT 4096 x 2048 x 6144 89 / 78
 // (128), TN 5632 x 2048 x 2560 64.9 / 55.0 (192), NN 3125 x 5120 x 12288 445 / 302 (128); over 618 random products (200 to
-// 12000 rows, 5 to 600 GFLOP) 6 % in the mean, the worst 4 % slower beside split TN ones of 688 columns.  With a row count known
-// on the device alone a height has to pay over the range that batches have: the sum at 60, 85 and 100 % of the bound.
+// 12000 rows, 5 to 600 GFLOP) 6 % in the mean; of 44 TN products of 256 to 32000 columns whose split gave way the slowest takes 1.02 times
+// as long.  With a row count known on the device alone a height has to pay over the range that batches have: the sum at 60, 85 and 100 % of the bound.
 // (bf16 results added to old ones, which leave the kernel element by element, are as tile_edge has them)
 bool tall_possible(const GemmArgs& a) {
   if (a.layout == kTN) return a.out_dtype == kF32;
@@ -1151,8 +1155,10 @@ int tall_height(const GemmArgs& a, const LaunchPlan& lp) {
     return launch_time(a, l, std::max<int64_t>(1, a.M * 3 / 5)) + launch_time(a, l, planned_rows(a)) + launch_time(a, l, a.M);
   };
   // Only for a gain beyond the model's error, which is larger beside a split of the last round (us, split / so: TN 4096 x 5120 x
-  // 4929 169 / 177 and 4096 x 5632 x 6231 226 / 229 on 192 rows, both 4 % cheaper by the model).
-  int64_t best = total(lp) * (lp.split == kSplitTail ? 85 : 96) / 100;
+  // 4929 169 / 177 and 4096 x 5632 x 6231 226 / 229 on 192 rows, both 4 % cheaper by the model) and beside small tiles that are split (NT
+  // 688 x 5120 x 5632 50.5 / 54.9 and 3887 x 1024 x 5632 53.2 / 55.4, 5 and 7 % cheaper).
+  const int percent = lp.split == kSplitTail ? 85 : lp.split == kSplitAll && lp.BN == 128 ? 92 : 96;
+  int64_t best = total(lp) * percent / 100;
   int height = 0;
   for (const int BM : {256, 224, 192, 160, 128}) {
     const int64_t t = total(LaunchPlan{BM, 256, kSplitNone, {1, 0, 0}, {0, 0, 0}});

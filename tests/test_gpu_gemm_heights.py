@@ -30,6 +30,26 @@ def test_heights_between_the_squares_are_kept_from_what_they_do_not_serve():
         assert b"x256" not in kernel_name(g)
 
 
+def planned(layout, M, N, K, **more):
+    """The kernel of a product that is given the scratch it asks for."""
+    g = ig.args(layout, M, N, K, out=ig.F32 if layout == ig.TN else ig.BF16, **more)
+    g.scratch, g.scratch_bytes = 256, ig.scratch_bytes(g)
+    return kernel_name(g).decode()
+
+
+@pytest.mark.parametrize("layout,M,N,K", [(ig.NT, 39, 32000, 6144), (ig.NN, 25, 32000, 5632), (ig.NT, 103, 32000, 6144), (ig.NN, 157, 32000, 25600),
+                                          (ig.NT, 160, 32000, 14336), (ig.NT, 688, 5120, 5632), (ig.NT, 3887, 1024, 5632)])
+def test_a_split_is_kept_where_it_is_faster(layout, M, N, K):
+    """One row of 125 tiles that streams its operand from memory on half the CUs; small tiles whose split is nearly as cheap by the model."""
+    assert "x256" not in planned(layout, M, N, K)
+
+
+@pytest.mark.parametrize("layout,M,N,K,height", [(ig.NT, 127, 50304, 14336, 128), (ig.NT, 76, 128256, 2048, 128), (ig.NN, 140, 25600, 4096, 160),
+                                                 (ig.NT, 1283, 5120, 12288, 128), (ig.TN, 1024, 5120, 6041, 128)])
+def test_a_split_gives_way_where_a_height_is_faster(layout, M, N, K, height):
+    assert f"_{height}x256_" in planned(layout, M, N, K)
+
+
 @pytest.mark.gpu
 @pytest.mark.parametrize("layout,M,N,K,height", CASES)
 def test_products_of_every_height(layout, M, N, K, height):
