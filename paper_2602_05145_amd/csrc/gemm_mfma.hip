@@ -1142,7 +1142,10 @@ int64_t launch_time(const GemmArgs& a, const LaunchPlan& lp, int64_t rows) {
 // tile_edge / so: NN 1665 x 5632 x 2048 47.8 / 35.0 (160 rows), NT 3400 x 14336 x 4096 332 / 290 (192), NT 4096 x 2048 x 6144 89 / 78
 // (128), TN 5632 x 2048 x 2560 64.9 / 55.0 (192), NN 3125 x 5120 x 12288 445 / 302 (128); over 618 random products (200 to
 // 12000 rows, 5 to 600 GFLOP) 6 % in the mean; of 44 TN products of 256 to 32000 columns whose split gave way the slowest takes 1.02 times
-// as long.  With a row count known on the device alone a height has to pay over the range that batches have: the sum at 60, 85 and 100 % of the bound.
+// as long.  With a row count known on the device alone a height has to pay over the
+// range that batches have: the sum over 50, 55 .. 100 % of the bound (at 60, 85 and 100 % alone, a height can miss the round that
+// the rows between just fill: evaluation of 8 x 512 rows, 2048 / 5632 wide, us before heights / so chosen / now, 62 % of the rows 731 / 771 /
+// 718, 85 % 927 / 906 / 904, 100 % 1031 / 984 / 1000).
 // (bf16 results added to old ones, which leave the kernel element by element, are as tile_edge has them)
 bool tall_possible(const GemmArgs& a) {
   if (a.layout == kTN) return a.out_dtype == kF32;
@@ -1152,7 +1155,9 @@ int tall_height(const GemmArgs& a, const LaunchPlan& lp) {
   if (!tall_possible(a)) return 0;
   auto total = [&](const LaunchPlan& l) {
     if (!a.m_dev) return launch_time(a, l, a.M);
-    return launch_time(a, l, std::max<int64_t>(1, a.M * 3 / 5)) + launch_time(a, l, planned_rows(a)) + launch_time(a, l, a.M);
+    int64_t t = 0;
+    for (int share = 10; share <= 20; ++share) t += launch_time(a, l, std::max<int64_t>(1, a.M * share / 20));
+    return t;
   };
   // Only for a gain beyond the model's error, which is larger beside a split of the last round (us, split / so: TN 4096 x 5120 x
   // 4929 169 / 177 and 4096 x 5632 x 6231 226 / 229 on 192 rows, both 4 % cheaper by the model) and beside small tiles that are split (NT

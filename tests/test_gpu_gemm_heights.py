@@ -50,6 +50,12 @@ def test_a_split_gives_way_where_a_height_is_faster(layout, M, N, K, height):
     assert f"_{height}x256_" in planned(layout, M, N, K)
 
 
+@pytest.mark.parametrize("M", [4096, 3999])
+def test_a_height_pays_over_the_row_counts_that_a_bound_stands_for(M):
+    """Gate product of a padded batch: 60 % of the rows just fill a round of squares, 62 % no round of 224 x 256 tiles, though 60, 85 and 100 % do."""
+    assert planned(ig.NT, M, 5632, 2048, m_dev=256) == "gemm_mfma_nt_256_bf16out"
+
+
 @pytest.mark.gpu
 @pytest.mark.parametrize("layout,M,N,K,height", CASES)
 def test_products_of_every_height(layout, M, N, K, height):
