@@ -772,18 +772,21 @@ __global__ __launch_bounds__(2 * BN) void gemm_mfma_kernel(std::conditional_t<AD
     // (below eight tile rows per wave a slab is two parts, one per k32 step, with the barrier between them, and each part
     // begins with its loads: they have to land within a slab, which is short here.  With the loads after the operand reads and
     // the larger operand in the two units, a slab of 160 x 256 took 1.04 us where it takes 0.92 so, one of 128 x 256 0.85 / 0.74 at
-    // 256 busy CUs, and NT 8193 x 1024 x 32000 620 / 454 us on 192 / 160 rows.)
+    // 256 busy CUs, and NT 8193 x 1024 x 32000 620 / 454 us on 192 / 160 rows.  Loads that test every lane against a ragged K would
+    // hold up the reads: they go behind the reads of A.  Us, loads last / first / so, at most 128 blocks of 128 x 128: NT 2165 x 256 x 688
+    // 8.8 / 9.1 / 8.8, NN 176 x 4096 x 688 8.4 / 8.7 / 8.5; 200 blocks: NN 36 x 25600 x 688 10.2 / 9.7 / 9.9.)
     // One slab: deep unit D, shallow unit S (fa0 / fb0 hold its first quarter's operands); the next slab's units
     // are DN, SN; DP is the deep unit the slab before vacated.
     auto step = [&](auto D, auto S, auto DN, auto SN, auto DP, int kt) {
       const bf16_t* ua = unit_a(D, S);
       const bf16_t* ubb = unit_b(D, S);
       if constexpr (TM == GA) {
+        constexpr int READS_AHEAD = WALK_A && WALK_B ? 0 : GA;
         const auto dd1 = desc_deep(kt + 2);
         quarter(Int<0>{}, fa0, fb0, [&](auto X) {
           constexpr int x = decltype(X)::value;
-          constexpr int y = x - NDEEP;
-          if constexpr (y < 0) dma_deep(X, dd1, deep(DP));
+          constexpr int z = x - READS_AHEAD, y = z < 0 ? x : x - NDEEP;
+          if constexpr (z >= 0 && z < NDEEP) dma_deep(Int<z>{}, dd1, deep(DP));
           else if constexpr (y < GA) frag_a(ua, 1, Int<0>{}, Int<y>{}, fa1);
           else if constexpr (y < GA + TN) frag_b(ubb, 1, Int<y - GA>{}, fb1);
         });
@@ -795,8 +798,8 @@ __global__ __launch_bounds__(2 * BN) void gemm_mfma_kernel(std::conditional_t<AD
         const auto ds = desc_shal(kt + 2);
         quarter(Int<0>{}, fa1, fb1, [&](auto X) {
           constexpr int x = decltype(X)::value;
-          constexpr int y = x - NSHAL;
-          if constexpr (y < 0) dma_shal(X, ds, shal(S));
+          constexpr int z = x - READS_AHEAD, y = z < 0 ? x : x - NSHAL;
+          if constexpr (z >= 0 && z < NSHAL) dma_shal(Int<z>{}, ds, shal(S));
           else if constexpr (y < GA) frag_a(uan, 0, Int<0>{}, Int<y>{}, fa0);
           else if constexpr (y < GA + TN) frag_b(ubn, 0, Int<y - GA>{}, fb0);
         });
