@@ -351,8 +351,13 @@ constexpr int64_t kWideK = 1024;
 
 template <int E, bool AKM, bool BKM, bool VEC, bool EXT>
 void launch_wavek(const Fp32GemmParams& p, dim3 grid, hipStream_t s) {
-  if ((int64_t)p.K + p.K2 >= kWideK) hipLaunchKernelGGL((gemm_fp32_wavek_kernel<E, 16, AKM, BKM, VEC, EXT>), grid, dim3(1024), 0, s, p);
-  else hipLaunchKernelGGL((gemm_fp32_wavek_kernel<E, 4, AKM, BKM, VEC, EXT>), grid, dim3(256), 0, s, p);
+  if constexpr (!EXT) {   // (see gemm_swiglu_supported)
+    if ((int64_t)p.K + p.K2 >= kWideK) {
+      hipLaunchKernelGGL((gemm_fp32_wavek_kernel<E, 16, AKM, BKM, VEC>), grid, dim3(1024), 0, s, p);
+      return;
+    }
+  }
+  hipLaunchKernelGGL((gemm_fp32_wavek_kernel<E, 4, AKM, BKM, VEC, EXT>), grid, dim3(256), 0, s, p);
 }
 
 template <bool AKM, bool BKM, bool VEC, bool EXT>

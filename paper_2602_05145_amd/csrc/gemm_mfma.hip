@@ -1234,9 +1234,7 @@ bool gemm_mfma_supported(const GemmArgs& a) {
 namespace {
 
 // every slab whole (and K known on the host): the DMA loads of a K-major operand take loop-constant lane offsets
-// (with both operands row-major over K the two forms are the same code: one instantiation)
-template <bool AMM, bool BNM>
-bool whole_slabs(const MfmaParams& p) { return !(AMM && BNM) && !p.k_dev && p.K % 64 == 0 && (!p.A2 || p.K2 % 64 == 0); }
+bool whole_slabs(const MfmaParams& p) { return !p.k_dev && p.K % 64 == 0 && (!p.A2 || p.K2 % 64 == 0); }
 
 template <int BM, int BN, bool AMM, bool BNM, typename TO, typename P>
 hipError_t launch_tiles(const P& p, const SplitGrid& all, hipStream_t s) {   // all: of a kSplitAll launch
@@ -1248,8 +1246,12 @@ hipError_t launch_tiles(const P& p, const SplitGrid& all, hipStream_t s) {   // 
   const int64_t items = q.split == kSplitAll ? all.blocks
                       : q.split == kSplitTail ? q.split_full + (int64_t)(tiles - q.split_full) * q.split_s : tiles;
   if constexpr (BM == BN && !ADAM) {
-    if (whole_slabs<AMM, BNM>(p)) hipLaunchKernelGGL((gemm_mfma_kernel<BM, BN, AMM, BNM, TO, true>), dim3((unsigned)items), dim3(2 * BN), 0, s, q);
-    else hipLaunchKernelGGL((gemm_mfma_kernel<BM, BN, AMM, BNM, TO, false>), dim3((unsigned)items), dim3(2 * BN), 0, s, q);
+    // (with both operands row-major over K the two forms are the same code: one instantiation)
+    auto* kernel = gemm_mfma_kernel<BM, BN, AMM, BNM, TO, false>;
+    if constexpr (!(AMM && BNM)) {
+      if (whole_slabs(p)) kernel = gemm_mfma_kernel<BM, BN, AMM, BNM, TO, true>;
+    }
+    hipLaunchKernelGGL(kernel, dim3((unsigned)items), dim3(2 * BN), 0, s, q);
     const hipError_t e = hipGetLastError();
     if (e != hipSuccess || q.split != kSplitAll) return e;
     hipLaunchKernelGGL((splitk_reduce_kernel<TO, BM>), dim3((unsigned)(all.tail * (BM * BM / 2048))), dim3(256), 0, s, q);
