@@ -356,8 +356,9 @@ int64_t tide_draft_workspace_offset(const tide_draft_config *cfg, const char *na
  * the workspace and are added in a fixed order by a second small kernel (deterministic).  tide_gemm_workspace_bytes
  * gives the bytes that takes (0: the call is never split and leaves any workspace alone; bf16 inputs are assumed);
  * with workspace NULL or smaller than that, nothing is split and the result is the same up to the order of the fp32
- * additions.  What is beyond those bytes is not touched.  Calls that overlap (on several streams) and have a size
- * above 0 each need a workspace of their own. */
+ * additions.  A call that is expected to be faster on whole tiles of another shape leaves the workspace unused.  What
+ * is beyond those bytes is not touched.  Calls that overlap (on several streams) and have a size above 0 each need a
+ * workspace of their own. */
 size_t tide_gemm_workspace_bytes(int layout, int64_t M, int64_t N, int64_t K, int out_dtype);
 int tide_gemm(int layout, int64_t M, int64_t N, int64_t K, float alpha,
               const void *A, const void *B, void *C, const void *residual,

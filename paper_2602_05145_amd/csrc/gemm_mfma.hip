@@ -1001,8 +1001,9 @@ int64_t tile_count(int64_t M, int64_t N, int e) { return ((M + e - 1) / e) * ((N
 // without a split, the small one in doubt.  With t tiles of 128 x 128 the chip runs rounds of 512 at the rate of two per
 // CU (950 ns per slab) and the rest at that of one (580) up to 256, in between (800) up to 400.  Both operands row-major
 // over K (TN) cost two LDS reads per fragment: 1050 / 700 ns, and 1470 on a large tile.  us, small / large tile: NN 2560 x
-// 2048 x 32000: 400 / 258 (80 tiles in three parts), NT 1999 x 4096 x 12288: 191 / 160 (two), NN 2560 x 2048 x 11264: 136 / 102 (three),
-// NN 1665 x 5632 x 2048: 46 / 52 (154 tiles, whole).
+// 2048 x 32000: 400 / 258 (80 tiles in three parts), NT 1999 x 4096 x 12288: 191 / 160 (two), NN 2560 x 2048 x 11264: 136 / 102 (three).
+// These costs decide between the squares and their splits, and the sizes of scratch that callers keep follow from them; tall_height, with
+// costs of its own, measured at the number of CUs that are busy, then weighs the outcome against whole tiles of every height.
 int tile_edge(const GemmArgs& a) {
   if (tile_count(a.M, a.N, 256) >= 200) return 256;
   const int64_t rows = planned_rows(a), t256 = tile_count(rows, a.N, 256), t128 = tile_count(rows, a.N, 128);
@@ -1178,7 +1179,7 @@ int tall_height(const GemmArgs& a, const LaunchPlan& lp) {
 // With the weight's update behind it a product of few rows is bound by the weight's 30 bytes per element, and two small blocks on
 // a CU overlap one's update with the other's products: us as planned otherwise / so, 128256 x 4096 over 300 rows 3090 / 2815, over
 // 1400 3318 / 3212, over 2500 3898 / 4115; 14336 x 4096 over 1400 398 / 364; 4096 x 4096 over 700 116 / 111; 5632 x 2048 (704 blocks)
-// over 700 83 / 86.
+// over 700 83 / 86.  Otherwise tiles and split are those of the product alone: its costs have no term for the update.
 bool update_bound(const GemmArgs& a) {
   const int64_t rows = a.k_dev ? (a.K * 17 + 19) / 20 : a.K;   // see planned_rows
   return rows <= 2048 && tile_count(a.M, a.N, 128) >= 1024;

@@ -33,13 +33,15 @@ struct GemmArgs {
   const int* m_dev; int64_t m_off;
   const int* k_dev; int64_t k_off;
   // Optional device scratch (16-byte aligned) of gemm_splitk_scratch_bytes(args) bytes: with it, a launch whose tiles
-  // do not fill the 256 CUs, or leave its last round partly filled, splits those tiles over K (the partial sums are
-  // added in a fixed order by a second small kernel).  Without it nothing is split.
+  // do not fill the 256 CUs, or leave its last round partly filled, splits those tiles over K where that is the cheapest (the
+  // partial sums are added in a fixed order by a second small kernel).  Without it nothing is split.
   void* scratch; size_t scratch_bytes;
 };
 bool gemm_mfma_supported(const GemmArgs& a);
 size_t gemm_split_tail_bytes(const GemmArgs& a);       // the part of it that goes into a partly filled last round of float results
-size_t gemm_splitk_scratch_bytes(const GemmArgs& a);   // 0 when the launch would not be split
+// 0: the launch is never split.  The bytes are those of the split of square tiles, also where whole tiles of another height then
+// turn out cheaper than that split and leave them unused: sizes that callers keep do not follow the choice of heights.
+size_t gemm_splitk_scratch_bytes(const GemmArgs& a);
 // At least what the product asks for with any number of rows (M, of TN K) up to the given one; never falls as the rows grow.
 size_t gemm_splitk_scratch_bound(const GemmArgs& a);
 const char* gemm_kernel_name(const GemmArgs& a);        // the kernel that a launch with these arguments runs, as profiles report it
