@@ -1,13 +1,10 @@
 """Tiles of 128 to 224 rows x 256 columns: the smallest ragged products that the plan gives to each of them, against a float
 reference of the same bf16 operands."""
-import ctypes as C
-
 import pytest
 import torch
 
 from tests import internal_gemm as ig
-
-kernel_name = ig._symbol("_ZN4tide16gemm_kernel_nameERKNS_8GemmArgsE", C.c_char_p, [C.POINTER(ig.GemmArgs)])
+from tests.internal_gemm import kernel_name
 
 # layout, M, N, K: a last tile row and column that are partly filled, one slab or (TN) one and a remainder
 CASES = [(ig.NT, 521, 6608, 64, 128), (ig.NT, 7405, 1040, 64, 160), (ig.NT, 5830, 1544, 64, 192), (ig.NT, 7037, 1544, 64, 224),
@@ -59,8 +56,8 @@ def test_a_height_pays_over_the_row_counts_that_a_bound_stands_for(M):
 @pytest.mark.gpu
 @pytest.mark.parametrize("layout,M,N,K,height", CASES)
 def test_products_of_every_height(layout, M, N, K, height):
-    """With a residual and old values where the layout of the step has them.  bf16 results: one rounding, 2^-9 of the value, plus
-    that of the sums (below 1e-6 of their scale); float results: the sums' own, K eps at most."""
+    """With a residual and old values where the layout of the step has them.  bf16 results: one rounding, half a step of 8 significant bits
+    (up to 2^-8 of the value), plus that of the sums (below 1e-6 of their scale); float results: the sums' own, K eps at most."""
     g = torch.Generator(device="cuda").manual_seed(M + N + K)
     sh = {ig.NT: ((M, K), (N, K)), ig.NN: ((M, K), (K, N)), ig.TN: ((K, M), (K, N))}[layout]
     a, b = (torch.randn(s, device="cuda", generator=g).bfloat16() for s in sh)
@@ -80,3 +77,103 @@ def test_products_of_every_height(layout, M, N, K, height):
         err = (c.double() - want).abs()
         bound = 2e-6 * K ** 0.5 * 4 + (0 if f32 else want.abs() * 2.0 ** -8)
         assert bool((err <= bound).all()), float((err - bound).max())
+
+
+# numbers of slabs that end in every phase of the ring of three and two units and of its loop of six; TN has one row in the last slab
+RING = [(ig.NT, 397, 8248, 128), (ig.NT, 1029, 7224, 160), (ig.NT, 8240, 1032, 192), (ig.NT, 8077, 1296, 224),
+        (ig.NN, 385, 8480, 128), (ig.NN, 1038, 7192, 160), (ig.NN, 8305, 1032, 192), (ig.NN, 8148, 1296, 224),
+        (ig.TN, 8272, 392, 128), (ig.TN, 7176, 1032, 160), (ig.TN, 8408, 1032, 192), (ig.TN, 8200, 1416, 224)]
+
+
+def _depths(layout):
+    return [64 * slabs - 63 for slabs in range(9, 15)] if layout == ig.TN else [64 * slabs for slabs in range(7, 13)]
+
+
+def _run(g):
+    assert ig.launch(g, torch.cuda.current_stream().cuda_stream) == 0
+    torch.cuda.synchronize()
+
+
+def _bound(K, want, bf16):
+    return 2e-6 * K ** 0.5 * 4 + (want.abs() * 2.0 ** -8 if bf16 else 0)     # as above
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("layout,M,N,height,K", [(*x, k) for x in RING for k in _depths(x[0])])
+def test_every_phase_of_the_ring(layout, M, N, height, K):
+    g = torch.Generator(device="cuda").manual_seed(M + N + K)
+    sh = {ig.NT: ((M, K), (N, K)), ig.NN: ((M, K), (K, N)), ig.TN: ((K, M), (K, N))}[layout]
+    a, b = (torch.randn(s, device="cuda", generator=g).bfloat16() for s in sh)
+    f32 = layout == ig.TN
+    c = torch.full((M, N), float("nan"), device="cuda", dtype=torch.float32 if f32 else torch.bfloat16)
+    args = ig.args(layout, M, N, K, out=ig.F32 if f32 else ig.BF16, a=a.data_ptr(), b=b.data_ptr(), c=c.data_ptr())
+    assert f"_{height}x256_" in kernel_name(args).decode()
+    print("ring", height, layout, M, N, K, flush=True)
+    _run(args)
+    ad, bd = a.double(), b.double()
+    want = (ad.t() if f32 else ad) @ (bd.t() if layout == ig.NT else bd)
+    assert bool(((c.double() - want).abs() <= _bound(K, want, not f32)).all())
+
+
+ROWS = [(ig.NT, 705, 8256, 128), (ig.NT, 1026, 7200, 160), (ig.NT, 5809, 1560, 192), (ig.NT, 1371, 8216, 224),
+        (ig.NN, 707, 8432, 128), (ig.NN, 1044, 7272, 160), (ig.NN, 5140, 1800, 192), (ig.NN, 3668, 3104, 224)]
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("layout,M,N,height", ROWS)
+def test_a_number_of_rows_known_on_the_device(layout, M, N, height):
+    """None, one, up to inside a tile, the bound and beyond it, less an offset; the rows from there on stay as they are."""
+    K, off = 448, 5
+    g = torch.Generator(device="cuda").manual_seed(M + N)
+    a, b = torch.randn(M, K, device="cuda", generator=g).bfloat16(), torch.randn((N, K) if layout == ig.NT else (K, N), device="cuda", generator=g).bfloat16()
+    res = torch.randn(M, N, device="cuda", generator=g).bfloat16()
+    product = a.double() @ (b.double().t() if layout == ig.NT else b.double())
+    cnt = torch.zeros(1, dtype=torch.int32, device="cuda")
+    for rows, r in ((0, None), (1, None), (height + 37, None), (height + 37, res), (M - 1, None), (M, res), (M + 9, None), (-3, None)):
+        c = torch.full((M, N), 7.0, device="cuda", dtype=torch.bfloat16)
+        cnt.fill_(rows + off)
+        args = ig.args(layout, M, N, K, a=a.data_ptr(), b=b.data_ptr(), c=c.data_ptr(), m_dev=cnt.data_ptr(), m_off=off)
+        if r is not None:
+            args.residual, args.ldr = r.data_ptr(), N
+        assert f"_{height}x256_" in kernel_name(args).decode()
+        print("rows on the device", height, layout, M, N, rows, r is not None, flush=True)
+        _run(args)
+        n = max(0, min(M, rows))
+        want = product[:n] + (0 if r is None else r[:n].double())
+        assert bool(((c[:n].double() - want).abs() <= _bound(K, want, True)).all())
+        assert bool((c[n:] == 7.0).all())
+
+
+PAIRS = [(ig.NT, 389, 8240, 128), (ig.NT, 1159, 6416, 160), (ig.NT, 5870, 1560, 192), (ig.NT, 1734, 6448, 224),
+         (ig.NN, 386, 8344, 128), (ig.NN, 899, 8200, 160), (ig.NN, 5863, 1544, 192), (ig.NN, 5428, 2056, 224)]
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("K,K2", [(448, 192), (192, 448), (64, 448)])
+@pytest.mark.parametrize("layout,M,N,height", PAIRS)
+def test_a_second_operand_pair(layout, M, N, height, K, K2):
+    """Pairs of unequal depth, whose seam falls into another phase of the ring each time."""
+    lda, g = max(K, K2), torch.Generator(device="cuda").manual_seed(M + N + K)
+    a, a2 = (torch.randn(M, lda, device="cuda", generator=g).bfloat16() for _ in range(2))
+    b, b2 = (torch.randn((N, lda) if layout == ig.NT else (k, N), device="cuda", generator=g).bfloat16() for k in (K, K2))
+    c = torch.full((M, N), float("nan"), device="cuda", dtype=torch.bfloat16)
+    args = ig.args(layout, M, N, K, K2=K2, lda=lda, ldb=lda if layout == ig.NT else N, a=a.data_ptr(), b=b.data_ptr(), c=c.data_ptr())
+    args.A2, args.B2 = a2.data_ptr(), b2.data_ptr()
+    assert f"_{height}x256_" in kernel_name(args).decode()
+    print("pairs", height, layout, M, N, K, K2, flush=True)
+    _run(args)
+    want = sum(x[:, :k].double() @ (y[:, :k].double().t() if layout == ig.NT else y.double()) for x, y, k in ((a, b, K), (a2, b2, K2)))
+    assert bool(((c.double() - want).abs() <= _bound(K + K2, want, True)).all())
+
+
+def test_the_cases_above_are_what_they_say():
+    for layout, M, N, height in RING:
+        for K in _depths(layout):
+            g = ig.args(layout, M, N, K, out=ig.F32 if layout == ig.TN else ig.BF16)
+            assert f"_{height}x256_" in kernel_name(g).decode(), (layout, M, N, K, kernel_name(g))
+    for layout, M, N, height in ROWS:
+        assert f"_{height}x256_" in kernel_name(ig.args(layout, M, N, 448, m_dev=256)).decode(), (layout, M, N)
+    for layout, M, N, height in PAIRS:
+        for k, k2 in ((448, 192), (192, 448), (64, 448)):
+            g = ig.args(layout, M, N, k, K2=k2, lda=max(k, k2), ldb=max(k, k2) if layout == ig.NT else N)
+            assert f"_{height}x256_" in kernel_name(g).decode(), (layout, M, N, k, k2, kernel_name(g))
