@@ -38,11 +38,16 @@ def B():
     return binding
 
 
-@pytest.mark.parametrize("M,N,K", [(264, 520, 1), (264, 520, 31), (264, 520, 33), (136, 72, 1999), (3720, 3656, 65), (3720, 3656, 127),
-                                   (4312, 4088, 2051)])
+@pytest.mark.parametrize("M,N,K,tile,split", [(264, 520, 1, "128", False), (264, 520, 31, "128", False), (264, 520, 33, "128", False),
+                                              (136, 72, 1999, "128", True), (3720, 3656, 65, "256", False), (3720, 3656, 127, "256", False),
+                                              (4312, 4088, 2051, "160x256", False), (4344, 4096, 4099, "256", True)])
 @pytest.mark.parametrize("accumulate", [0, 1])
-def test_weight_gradient_over_any_number_of_rows(B, M, N, K, accumulate):
-    """TN with K (the rows of a batch) of any remainder, on the small- and the large-tile kernel, split and not split."""
+def test_weight_gradient_over_any_number_of_rows(B, M, N, K, tile, split, accumulate):
+    """TN with K (the rows of a batch) of any remainder, on the small, the large and an intermediate tile, whole, split into parts
+    everywhere (136 x 72) and in the last round alone (4344 x 4096)."""
+    plan = ig.args(ig.TN, M, N, K, out=ig.F32, accumulate=accumulate)
+    plan.scratch, plan.scratch_bytes = 256, B.tide_gemm_workspace_bytes(B.LAYOUT_TN, M, N, K, 0)
+    assert ig.kernel_name(plan).decode() == f"gemm_mfma_tn_{tile}_f32out" and (plan.scratch_bytes > 0 and "x" not in tile) == split
     a, b, ref = _operands(B, B.LAYOUT_TN, M, N, K, "bf16", 3 * K + M)
     c = torch.full((M, N), 0.5 if accumulate else float("nan"), device=DEV)
     _gemm(B, B.LAYOUT_TN, M, N, K, a, b, c, "bf16", "fp32", accumulate=accumulate)

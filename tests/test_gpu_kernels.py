@@ -5,6 +5,7 @@ import pytest
 import torch
 
 from oracle import tide_oracle as O
+from tests import internal_gemm as ig
 from tests.gpu_util import DEV, cosine, quantize, rel_max, stream, sync, to_dev, to_host
 
 pytestmark = pytest.mark.gpu
@@ -54,13 +55,16 @@ def test_gemm_bf16_small_tiles(B, layout, shape):
     assert cosine(got, ref) > 0.99999
 
 
+@pytest.mark.parametrize("M,N,tiles", [(3720, 3656, "256 224x256"), (4040, 3336, "256")])
 @pytest.mark.parametrize("layout", [0, 1, 2])
 @pytest.mark.parametrize("K", [200, 192, 448])
-def test_gemm_bf16_large_tiles_ragged(B, layout, K):
-    # >= 200 tiles of 256x256 selects the large-tile kernel; M and N ragged w.r.t. 256, K ragged w.r.t. the slab
+def test_gemm_bf16_large_tiles_ragged(B, layout, K, M, N, tiles):
+    # >= 200 tiles of 256x256 select the large-tile kernel; M and N ragged w.r.t. 256, K ragged w.r.t. the slab
     # depth of 64 (200) or a whole number of slabs (192, 448: the path with loop-constant load offsets; 3 slabs
-    # and 7 slabs end in different positions of the ring)
-    M, N = 3720, 3656
+    # and 7 slabs end in different positions of the ring).  bf16 NT and NN products of 3720 x 3656 over whole slabs
+    # take tiles of 224 x 256.
+    names = [ig.kernel_name(ig.args(layout, M, N, K, out=o, accumulate=int(o == ig.F32))).decode().split("_")[3] for o in (ig.F32, ig.BF16)]
+    assert names == ["256", tiles.split()[-1] if layout != B.LAYOUT_TN and K % 64 == 0 else "256"]
     got, ref = _gemm_case(B, layout, M, N, K, "bf16", "fp32", seed=31 + layout, accumulate=True)
     assert rel_max(got, ref) < 2e-5
     got, ref = _gemm_case(B, layout, M, N, K, "bf16", "bf16", seed=41 + layout)
@@ -73,7 +77,7 @@ def test_gemm_bf16_large_tiles_ragged(B, layout, K):
 def test_gemm_split_of_the_last_tile_round(B, layout, accumulate, K):
     """fp32 results whose tiles leave the last round of the 256 compute units at most half full: with a workspace
     those tiles are split over K and a second kernel adds the partial sums.  Against the oracle product, and
-    against the unsplit launch (same tiles, different order of the fp32 additions).  17 x 16 tiles of 256 =
+    against the unsplit launch (another order of the fp32 additions; NT and NN on the same tiles, TN on tiles of 160 x 256).  17 x 16 tiles of 256 =
     272 = one round + 16 tiles, split four ways (a part keeps at least 1024 of K); ragged M and N; K ragged (4408)
     or a whole number of 64-deep slabs (4416: the launches whose loads take loop-constant offsets)."""
     M, N = 17 * 256 - 40, 16 * 256 - 8
@@ -81,6 +85,11 @@ def test_gemm_split_of_the_last_tile_round(B, layout, accumulate, K):
     assert need == 3 * 16 * 256 * 256 * 4
     assert B.tide_gemm_workspace_bytes(layout, M, N, K, DT["bf16"]) == 0             # bf16 results are never split
     assert B.tide_gemm_workspace_bytes(layout, 16 * 256, 16 * 256, K, DT["fp32"]) == 0   # a full round
+    plan = ig.args(layout, M, N, K, out=ig.F32, accumulate=int(accumulate))
+    whole = ig.kernel_name(plan).decode()
+    plan.scratch, plan.scratch_bytes = 256, need
+    tail = ig.kernel_name(plan).decode()
+    assert tail.endswith("_256_f32out") and whole == (tail if layout != B.LAYOUT_TN else "gemm_mfma_tn_160x256_f32out")
     rng = np.random.default_rng(71 + layout)
     shapeA = (K, M) if layout == B.LAYOUT_TN else (M, K)
     shapeB = (N, K) if layout == B.LAYOUT_NT else (K, N)
