@@ -15,19 +15,21 @@
 // K^T, dO^T, Q^T) is read from the row-major LDS tile with the transposing LDS read
 // ds_read_b64_tr_b16, so nothing is ever transposed through registers or HBM.
 //
-// Tiles.  Forward and dQ: one block = 128 queries of one head (4 waves x 32 queries, Q in registers; capped
-// at 256 VGPRs so that two blocks share a CU and one block's softmax overlaps the other's MFMAs; the forward of head size 128
-// also makes the next tile's scores beside a tile's exponentials), K/V streamed in 64-key tiles, double buffered in LDS.  dK/dV: one block = 128 keys of one kv
+// Tiles.  Forward and dQ: one block = four items of 32 queries of one head (a wave each, Q in registers) that read the same keys
+// (see row_item); K/V streamed in steps of 32 keys, double buffered in LDS.  What bounds a full chip is the sum of the matrix and
+// vector work of a SIMD's two or three waves (16 x 2048, 32 / 8 heads: forward 47 and 63 % of the cycles, the clock at 1.8 GHz under the power limit), so registers are
+// kept for three waves in the forward: with steps of 64 keys and two waves, whose MFMAs and exponentials were interleaved by hand, it took 727 us, so 620.
+// dK/dV: one block = 128 keys of one kv
 // head (4 waves x 32 keys, K [and V] in registers), Q/dO streamed in tiles of 32 (dV pass) or 64 (dK pass)
 // queries for each of the G query heads of the group, so dK/dV are summed over the group in registers: no
-// atomics, deterministic.  dV and dK are two launches of one template: a fused pass needs 350 registers (K, V
+// atomics, deterministic.  At head size 128 dV and dK are two launches of one template: a fused pass needs 350 registers (K, V
 // fragments and two 32x128 accumulators), i.e. one block per CU with nothing to hide the exponentials behind;
-// the two halves need 168 and 212, run 3 and 2 blocks per CU, and together take 0.7x the fused time although
-// S = Q K^T is computed twice.
-// Where blocks are few, a block is 64 keys and eight waves in four sets that share the query tiles (kFewKW, kFewNS).
+// the two halves need 168 and 229, run 3 and 2 blocks per CU, and together take 0.7x the fused time although
+// S = Q K^T is computed twice.  At head size 64 (199 registers) one launch makes both.
+// Where blocks are few, sets of waves share the keys (forward, dQ) or the query tiles (dK / dV): see launch_fwd_form, launch_bwd.
 // Every streamed tile reaches LDS by LDS-DMA loads (no staging registers); operand fragments are read from LDS
 // through small register rings, a few MFMAs ahead of their use.
-// Causality: tiles entirely above the diagonal are never loaded; heavy blocks are scheduled first; the
+// Causality: tiles entirely above the diagonal are never loaded; heavy blocks are scheduled first (see WorkMap); the
 // per-element causal test is made only by the (wave-uniformly chosen) tiles that touch the diagonal.
 #include <algorithm>
 #include <type_traits>
@@ -179,6 +181,13 @@ struct TileDma {
       if (NW * (i + 1) <= CHUNKS || wave_s + NW * i < CHUNKS) dma16(rs, base + (uint32_t)(wave_s + NW * i) * 1024u, voff[i]);
   }
 };
+// a barrier between reads of LDS and what other waves' loads write there next: every operand read has returned (its MFMA has been
+// issued), and loads in flight stay in flight (__syncthreads() would wait for them)
+__device__ __forceinline__ void lds_barrier() {
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
+  __builtin_amdgcn_s_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
+}
 #define TIDE_ATTN_WAIT_DMA() __builtin_amdgcn_s_waitcnt(0x0F70)   /* vmcnt(0) */
 
 // Write a wave's 32 x D result, held transposed in D / 32 accumulators (acc[ct] = rows ct*32.., column =
@@ -198,20 +207,6 @@ __device__ __forceinline__ void stage_out(bf16_t* tile, const f32x16_t (&acc)[D 
     }
 }
 
-// Copy the staged [ROWS][D] tile to global rows row0.. (< row_end) of a matrix with leading dim ld; NT threads.
-template <int D, int ROWS = 128, int NT = 256>
-__device__ __forceinline__ void copy_out(const bf16_t* tile, bf16_t* dst, int64_t row0, int64_t row_end, int ld,
-                                         int col0, int tid) {
-#pragma unroll
-  for (int i = 0; i < (ROWS * D / 8 + NT - 1) / NT; ++i) {
-    const int p = tid + i * NT;
-    const int row = p / (D / 8), piece = p % (D / 8);
-    if (row < ROWS && row0 + row < row_end)
-      *reinterpret_cast<i32x4_t*>(dst + (size_t)(row0 + row) * ld + col0 + piece * 8) =
-          *reinterpret_cast<const i32x4_t*>(tile + row * pitch(D) + piece * 8);
-  }
-}
-
 // which of the wave's 32 output rows (held as for stage_out) hold something that is not finite; `ask`: this lane's row counts
 template <int NC>
 __device__ __forceinline__ uint32_t not_finite(const f32x16_t (&acc)[NC], bool ask) {
@@ -224,7 +219,6 @@ __device__ __forceinline__ uint32_t not_finite(const f32x16_t (&acc)[NC], bool a
   return (uint32_t)rows | (uint32_t)(rows >> 32);
 }
 
-constexpr int BQ = 128, BKV = 64;
 // By how much (log2) the reference that a row's sums are kept relative to may fall behind the running maximum; see the forward kernel.
 constexpr float lag(int D) { return D == 64 ? 8.0f : 0.0f; }
 
@@ -247,85 +241,164 @@ __device__ __forceinline__ float row_max(float x) {
   const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(x), __float_as_uint(x), false, false);
   return fmaxf(__uint_as_float(r[0]), __uint_as_float(r[1]));
 }
-constexpr int kv_tile(int D) { return BKV * pitch(D); }  // elements
 
-// Head size 64 halves the operand and accumulator registers and the LDS tiles: 114 / 167 / 125 / 147 registers for the
-// forward, dQ, dV and dK kernels, i.e. 4, 3, 4 and 3 blocks per CU (held to 4, 4, 5 and 3 the dQ and dV kernels spill:
-// backward 1.53 -> 2.73 ms at 16 x 2048, 32 / 8 heads, with one bf16 value per probability).  Against the one-wave-per-row kernels (attention_simple.hip) that
-// served this head size: 6 x 777, 16 / 4 heads, forward + backward 17.55 -> 0.144 ms.
+// Head size 64 halves the operand and accumulator registers and the LDS tiles: 111 registers in the forward and 154 in the dQ
+// kernel, i.e. 4 and 3 blocks per CU.  Against the one-wave-per-row kernels (attention_simple.hip) that
+// served this head size: 6 x 777, 16 / 4 heads, forward + backward 17.55 -> 0.097 ms.
 constexpr int blocks_per_cu(int D, int at64, int at128) { return D == 64 ? at64 : at128; }
-// Depth of the operand-fragment rings of the three kernels (0 in the dQ kernel: the plain loop).  Measured when the tiles
-// were still staged through registers, backward at 16 x 2048 / 2 x 16384: dQ 0 / dK-dV 4: 3.56 / 21.4 ms; 2 / 4: 3.48 /
-// 21.0; 4 / 4: 3.79 / 22.7 (the dQ kernel, then at 256 registers, spilled with a ring of four); 0 / 2: 3.60 / 21.2;
-// before the rings 3.65 / 21.6.  With LDS-DMA tile loads (dQ at 233 registers) depths of 2 to 6 measure the same.
-#ifndef TIDE_ATTN_DQ_RING
-#define TIDE_ATTN_DQ_RING 2
-#endif
+// Depth of the operand-fragment rings of the dK / dV passes.  Measured when the tiles were still staged through registers,
+// backward at 16 x 2048 / 2 x 16384: 4: 3.48 / 21.0 ms; 2: 3.60 / 21.2; none 3.65 / 21.6.  With LDS-DMA tile loads depths of 2 to 6
+// measure the same.
 #ifndef TIDE_ATTN_DKV_RING
 #define TIDE_ATTN_DKV_RING 4
 #endif
+// Waves that a SIMD has to hold at least, and depth of the operand rings, in the forward and dQ kernels (NS: sets of waves per block).
+constexpr int row_waves(int D, int NS) { return blocks_per_cu(D, 4, NS == 1 ? 3 : 2); }
+constexpr int dq_waves(int D, int NS) { return NS == 1 ? blocks_per_cu(D, 3, 2) : 2; }
+constexpr int kRowRing = 4;
+constexpr int dq_ring(int D) { return D == 64 ? 8 : 4; }
 // Work item (x, y, z) of an nx * ny * nz problem from the block's place in the 1-D dispatch order.
-// Work-groups go to the 8 XCDs round-robin and every XCD has its own L2.  The blocks of a "group" (all x of gy
-// consecutive y of one z: the query blocks of the heads that share a kv head, or the key blocks of one kv
-// head) stream the same K/V resp. Q/dO rows, so a whole group is given to ONE XCD, group after group, x
-// fastest.  With the plain (x, y, z) order the 16 key blocks of a kv head were spread over all XCDs and the
-// dK / dV passes hit L2 on 2 % of their requests.  Falls back to the plain order when the number of
-// groups is not a multiple of 8.
-struct Work3 { int x, y, z; };
-__device__ __forceinline__ Work3 xcd_group_work(int nx, int ny, int nz, int gy) {
+// Work-groups go to the 8 XCDs round-robin and every XCD has its own L2.  The nx blocks of a group (y, z: a kv head of a sequence)
+// stream the same K/V resp. Q/dO rows, so a whole group is given to one XCD; groups that are few and no multiple of 8 are left to the
+// plain order.  x counts from the heaviest block of a group down.  An XCD takes its groups in chunks, and of a chunk all
+// heaviest blocks first, so that what ends last is light blocks of many groups: group after group, the last groups'
+// heaviest blocks began when the others had nothing left to do.  us, a group / a chunk at a time: backward of 16 x 2048, 32 / 8 heads of 128 2430 / 2180, of 16 x 1024
+// 725 / 634, of 7 x 979, 32 heads of 64 277 / 183; forward of 13 x 759, 16 / 4 heads of 128 60 / 48.
+struct Work3 { int x, y, z; bool on; };
+struct WorkMap { int nx, ny, groups, per_xcd, chunk; };   // per_xcd 0: groups are not dealt to XCDs
+__host__ __device__ inline WorkMap work_map(int nx, int ny, int nz) {
+  const int groups = ny * nz;
+  return WorkMap{nx, ny, groups, groups % 8 == 0 || groups >= 32 ? (groups + 7) / 8 : 0, 1};
+}
+inline int64_t work_blocks(const WorkMap& w) { return (int64_t)w.nx * (w.per_xcd ? 8 * w.per_xcd : w.groups); }
+__device__ __forceinline__ Work3 work_item(const WorkMap& w) {
   const int n = blockIdx.x;
-  const int per_group = nx * gy, groups_per_z = ny / gy, ngroups = groups_per_z * nz;
-  int grp, in_g;
-  if ((ngroups & 7) == 0) {
-    const int xcd = n & 7, slot = n >> 3;
-    grp = (slot / per_group) * 8 + xcd;
-    in_g = slot % per_group;
+  int x, grp;
+  if (w.per_xcd) {
+    const int slot = n >> 3, first = slot / (w.chunk * w.nx) * w.chunk, in = slot - first * w.nx, size = min(w.chunk, w.per_xcd - first);
+    x = in / size;
+    grp = (first + in - x * size) * 8 + (n & 7);
   } else {
-    grp = n / per_group;
-    in_g = n % per_group;
+    x = n / w.groups;
+    grp = n - x * w.groups;
   }
-  Work3 w;
-  w.x = in_g % nx;
-  w.y = (grp % groups_per_z) * gy + in_g / nx;
-  w.z = grp / groups_per_z;
-  return w;
+  const int z = grp / w.ny;
+  return Work3{x, grp - z * w.ny, z, grp < w.groups};
 }
 
 }  // namespace
 
+// The rows that a wave of the forward and dQ kernels owns: 32 queries of one head.  The query heads of a kv head read the same
+// keys, so its items are counted block of 32 queries by block, the heads of the group fastest, and a block's KW waves take KW
+// consecutive ones, from the end of the sequence down: with four heads per group all four waves stop at the same key (with 128
+// queries of one head per block, two of them sat out the last tile).
+struct RowItem { int h, qw; bool on; int kv_end; };   // head, first query, whether there is one; end of the keys that the block's waves see
+template <int KW>
+__device__ __forceinline__ RowItem row_item(int x, int wave_s, int kh, int G, int S) {
+  const int first = (S + 31) / 32 * G - 1 - x * KW, i = first - wave_s, qb = i / G;
+  return RowItem{kh * G + (i - qb * G), i >= 0 ? qb * 32 : -32, i >= 0, min(S, first / G * 32 + 32)};
+}
+template <int KW>
+__host__ __device__ constexpr int row_blocks(int S, int G) { return ((S + 31) / 32 * G + KW - 1) / KW; }
+// The keys and values that a step of the forward and dQ kernels takes: 32 of each, side by side in LDS (rows 0 .. 31 the keys, 32 .. 63
+// the values), i.e. one 64-row tile of 17 (9) whole chunks, double buffered.  (Three stages, with the loads two steps ahead: no gain with a
+// full chip, 1 x 526 positions of head size 64 13.4 -> 14.6 us.)
+template <int D, int KW>
+struct KvDma {
+  static constexpr int STAGE = 64 * pitch(D);   // elements
+  TileDma<64, D, KW> dma;
+  __device__ __forceinline__ void init(int ld, int v_off, int wave, int lane) {   // v_off: bytes from a row's key to its value
+    using Dma = TileDma<64, D, KW>;
+#pragma unroll
+    for (int i = 0; i < Dma::PER_WAVE; ++i) {
+      const int o = (wave + KW * i) * 1024 + lane * 16, R = o / (pitch(D) * 2), piece = o % (pitch(D) * 2) / 16;
+      dma.voff[i] = piece < D / 8 && o < Dma::BYTES ? (uint32_t)(perm(R & 31) * ld + piece * 8) * 2u + (R >= 32 ? (uint32_t)v_off : 0u) : 0x80000000u;
+    }
+  }
+};
+
+// a wave's own 32 staged rows (stage_out) to global memory, rows past the sequence left out
+template <int D>
+__device__ __forceinline__ void copy_rows(const bf16_t* tile, bf16_t* dst, int64_t row0, int rows, int ld, int col0, int wave, int lane) {
+  asm volatile("" ::: "memory");   // behind the wave's narrower writes of the rows (LDS operations of a wave stay in order)
+#pragma unroll
+  for (int i = 0; i < 32 * (D / 8) / 64; ++i) {
+    const int p = lane + 64 * i, row = p / (D / 8), piece = p % (D / 8);
+    if (row < rows)
+      *reinterpret_cast<i32x4_t*>(dst + (size_t)(row0 + row) * ld + col0 + piece * 8) =
+          *reinterpret_cast<const i32x4_t*>(tile + (wave * 32 + row) * pitch(D) + piece * 8);
+  }
+}
+
+// The sums of the sets of a block: sets n .. 2n - 1 hand theirs to sets 0 .. n - 1, for n = NS / 2, NS / 4, ..., and set 0 has the whole.  In
+// a fixed order; every LDS stage is free by then.
+template <int KW, int NS, int N>
+__device__ __forceinline__ void merge_sets(bf16_t* smem, f32x16_t (&acc)[N], int set, int wave, int lane) {
+  float* sums = reinterpret_cast<float*>(smem);
+#pragma unroll
+  for (int n = NS / 2; n >= 1; n /= 2) {
+    float* mine = sums + ((set % n) * KW + wave) * N * 16 * 64 + lane;
+    if (set >= n && set < 2 * n) {
+#pragma unroll
+      for (int ct = 0; ct < N; ++ct)
+#pragma unroll
+        for (int q = 0; q < 16; ++q) mine[(ct * 16 + q) * 64] = acc[ct][q];
+    }
+    __syncthreads();
+    if (set < n) {
+#pragma unroll
+      for (int ct = 0; ct < N; ++ct)
+#pragma unroll
+        for (int q = 0; q < 16; ++q) acc[ct][q] += mine[(ct * 16 + q) * 64];
+    }
+    __syncthreads();
+  }
+}
+
 // ------------------------------------------------------------------------------------------------
 // forward
 // ------------------------------------------------------------------------------------------------
-template <int D>
-__global__ __launch_bounds__(256, blocks_per_cu(D, 4, 2)) void attn_fwd_mfma_kernel(const bf16_t* __restrict__ qkv, bf16_t* __restrict__ out,
+template <int D, int KW, int NS>
+__global__ __launch_bounds__(KW * NS * 64, row_waves(D, NS)) void attn_fwd_mfma_kernel(const bf16_t* __restrict__ qkv, bf16_t* __restrict__ out,
                                                             float* __restrict__ lse, int Smax, int nh, int nkv,
-                                                            const int* __restrict__ cu, int64_t T, int nseq) {
-  constexpr int NK = D / 16, NC = D / 32;   // k16 steps of a score product, 32-column tiles of a result
-  constexpr int KV_TILE = kv_tile(D);
+                                                            const int* __restrict__ cu, int64_t T, WorkMap map) {
+  constexpr int NK = D / 16, NC = D / 32, BK = 32;   // k16 steps of a score product, 32-column tiles of a result, keys per step
+  using Kv = KvDma<D, KW>;
   extern __shared__ __attribute__((aligned(16))) bf16_t smem[];
-  bf16_t* sK = smem;                 // [2][KV_TILE]
-  bf16_t* sV = smem + 2 * KV_TILE;   // [2][KV_TILE]
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int wave_all = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), set = NS > 1 ? wave_all / KW : 0, wave_s = wave_all - set * KW;
+  const int lane = threadIdx.x & 63, wave = wave_s;
+  bf16_t* stages = smem + set * 2 * Kv::STAGE;
   const int lr = lane & 31, g = lane >> 5, plr = perm(lr);
-  const int nqb = (Smax + BQ - 1) / BQ;
-  const Work3 wk = xcd_group_work(nqb, nh, nseq, nh / nkv);
-  const int qb = nqb - 1 - wk.x;  // heavy (late) query blocks first
-  const int h = wk.y, b = wk.z;
+  const int G = nh / nkv;
+  const Work3 wk = work_item(map);
+  if (!wk.on) return;
+  const int kh = wk.y, b = wk.z;
   const SeqView sv = seq_view(cu, b, Smax, T);
   const int S = sv.len;
-  const int G = nh / nkv, kh = h / G;
   const int ld = (nh + 2 * nkv) * D;
-  const int q0 = qb * BQ, qw = q0 + wave * 32, iq = qw + lr;
-  if (q0 >= S) return;   // the whole block, before any barrier: this sequence is shorter
+  if (wk.x >= row_blocks<KW>(S, G)) return;   // the whole block, before any barrier: this sequence is shorter
+  const RowItem item = row_item<KW>(wk.x, wave_s, kh, G, S);
+  const int h = item.h, qw = item.qw, iq = qw + lr;
+  const bool valid = item.on && iq < S;
   const bf16_t* base = qkv + (size_t)sv.row0 * ld;
   const __amdgpu_buffer_rsrc_t rs = rsrc(base, (uint32_t)((size_t)S * ld * 2));
   const int kcol = (nh + kh) * D, vcol = (nh + nkv + kh) * D;
   const float c = kLog2e / sqrtf((float)D);
 
+  const int nt = (item.kv_end + BK - 1) / BK, nr = (nt + NS - 1) / NS;   // tiles, and rounds of them: set s takes tiles s, s + NS, ...
+  const uint32_t seq_bytes = (uint32_t)((size_t)S * ld * 2);
+  Kv kv;
+  kv.init(ld, (vcol - kcol) * 2, wave, lane);
+  auto fetch = [&](int t) {   // the set's t-th tile
+    const int tile = set + NS * t;
+    if (tile < nt) kv.dma.issue(base, seq_bytes, stages + (t & 1) * Kv::STAGE, ((uint32_t)(tile * BK) * (uint32_t)ld + (uint32_t)kcol) * 2u, wave_s);
+  };
+  fetch(0);
+
   u32x4_t qf[NK];
 #pragma unroll
-  for (int kk = 0; kk < NK; ++kk)
-    qf[kk] = __builtin_bit_cast(u32x4_t, __builtin_amdgcn_raw_buffer_load_b128(rs, ((uint32_t)iq * (uint32_t)ld + (uint32_t)(h * D + kk * 16 + g * 8)) * 2u, 0, 0));
+  for (int kk = 0; kk < NK; ++kk)   // (a row past the sequence is beyond the buffer: zeros)
+    qf[kk] = __builtin_bit_cast(u32x4_t, __builtin_amdgcn_raw_buffer_load_b128(rs, ((uint32_t)(item.on ? iq : S) * (uint32_t)ld + (uint32_t)(h * D + kk * 16 + g * 8)) * 2u, 0, 0));
 
   f32x16_t o[NC];
 #pragma unroll
@@ -334,27 +407,18 @@ __global__ __launch_bounds__(256, blocks_per_cu(D, 4, 2)) void attn_fwd_mfma_ker
     for (int q = 0; q < 16; ++q) o[ct][q] = 0.f;
   float m = -INFINITY, l = 0.f;   // l: this lane's share of the row's sum (its partner, lane ^ 32, has the rest)
 
-  const int kv_end = min(S, q0 + BQ);
-  const int nt = (kv_end + BKV - 1) / BKV;
-  const uint32_t seq_bytes = (uint32_t)((size_t)S * ld * 2);
-  const int wave_s = __builtin_amdgcn_readfirstlane(wave);
-  TileDma<64, D> dma;
-  dma.init(ld, wave, lane);
-  auto fetch_k = [&](int t) {
-    if (t < nt) dma.issue(base, seq_bytes, sK + (t & 1) * KV_TILE, ((uint32_t)(t * BKV) * (uint32_t)ld + (uint32_t)kcol) * 2u, wave_s);
-  };
-  auto fetch_v = [&](int t) {
-    if (t < nt) dma.issue(base, seq_bytes, sV + (t & 1) * KV_TILE, ((uint32_t)(t * BKV) * (uint32_t)ld + (uint32_t)vcol) * 2u, wave_s);
-  };
   // The sums are kept relative to m, which follows the running maximum of the row.  At head size 64 it may fall behind by 2^8: the
   // accumulators are then rescaled once or twice per row, not in nearly every tile (one of 32 rows nearly always finds a new
   // maximum; 6 x 777 30.4 -> 29.0 us).  At head size 128, where a probability is one bf16 value, that of the largest score has to
   // stay the exact 1 it is relative to the maximum itself: with a lag the results were 2 % (flat scores) to 17 % (peaked ones) further from
   // 64 bits (and 16 x 2048 took 700 us, 745 without).
+  // (The first tile of a set after the first may show some of a wave's queries no key at all: their m stays at -inf, and the
+  // scores are then taken relative to 0.)
+  auto reference = [&] { return NS > 1 && m == -INFINITY ? 0.f : m * c; };
   auto follow = [&](float tm) {
-    const bool moved = (tm - m) * c > lag(D);   // the first tile: m = -inf, and key 0 is visible to every query
+    const bool moved = (tm - m) * c > lag(D);   // the first tile: m = -inf
     if (__builtin_amdgcn_ballot_w64(moved) != 0) {   // wave-uniform
-      const float mn = moved ? tm : m, alpha = __builtin_amdgcn_exp2f((m - mn) * c);
+      const float mn = moved ? tm : m, alpha = NS == 1 || moved ? __builtin_amdgcn_exp2f((m - mn) * c) : 1.f;
       l *= alpha;
       m = mn;
 #pragma unroll
@@ -363,205 +427,100 @@ __global__ __launch_bounds__(256, blocks_per_cu(D, 4, 2)) void attn_fwd_mfma_ker
         for (int q = 0; q < 16; ++q) o[ct][q] *= alpha;
     }
   };
-  constexpr int RING = 4, NP = parts(D);
-  auto k_frag = [&](const bf16_t* K, int i) { return frag<D>(K, (i / NK) * 32, plr, (i % NK) * 16 + g * 8); };
-  fetch_k(0);
-  if constexpr (D == 64) fetch_v(0);
   // vmcnt(0): nothing of the prologue is in flight inside the loop.  The Q (and dO) fragments are first used there, so
   // the compiler issues their loads last and, at the loop's head, still counts them as outstanding; inside the loop
-  // the next tile's eight loads are then younger than they are, and the waits it puts in front of the first MFMAs
-  // ("all but 7, 6, ... 0 loads done") make every tile wait for the tile after it to arrive from memory.
+  // the next tiles' loads are then younger than they are, and the waits it puts in front of the first MFMAs
+  // make every tile wait for the tile after it to arrive from memory.
   __builtin_amdgcn_s_waitcnt(0x0F70);
-  __syncthreads();
-  if constexpr (D == 64) {
-    // Four blocks share a CU (the pipelined form below needs 197 registers, two blocks: 16 x 2048, 32 / 8 heads 541 -> 574 us).
-    for (int t = 0; t < nt; ++t) {
-      const int j0 = t * BKV;
-      fetch_k(t + 1);   // into the stage whose last readers passed the barrier at the end of the step before
-      fetch_v(t + 1);
-      if (j0 <= qw + 31) {  // wave-uniform: the tile has at least one unmasked key for this wave
-        const bf16_t* K = sK + (t & 1) * KV_TILE;
-        const bf16_t* V = sV + (t & 1) * KV_TILE;
-        f32x16_t s[2];
+  lds_barrier();
+  constexpr int NP = parts(D), NV = 2 * NC, RK = kRowRing, RV = 4;
+  for (int t = 0; t < nr; ++t) {
+    const int j0 = (set + NS * t) * BK;
+    fetch(t + 1);   // into the stage whose last readers passed the barrier at the end of the step before
+    if (j0 <= qw + 31) {  // wave-uniform: the tile has at least one unmasked key for this wave
+      const bf16_t *K = stages + (t & 1) * Kv::STAGE, *V = K + 32 * pitch(D);
+      auto k_frag = [&](int i) { return frag<D>(K, 0, plr, i * 16 + g * 8); };
+      auto v_frag = [&](int i) { return frag_tr<D>(V, (i / NC) * 16, (i % NC) * 32, lane); };   // k16 step i / NC, columns i % NC
+      f32x16_t s;
 #pragma unroll
-        for (int jt = 0; jt < 2; ++jt)
+      for (int q = 0; q < 16; ++q) s[q] = 0.f;
+      u32x4_t kb[RK], vb[RV];
+      // the K fragments through a ring: a fragment is requested RK MFMAs before its own (read, wait, MFMA one after
+      // the other leaves the LDS latency, three MFMA times, exposed at every step)
 #pragma unroll
-          for (int q = 0; q < 16; ++q) s[jt][q] = 0.f;
-        {
-          // the K fragments through a ring: a fragment is requested RING MFMAs before its own (read, wait, MFMA one after
-          // the other leaves the LDS latency, three MFMA times, exposed at every step)
-          u32x4_t kb[RING];
+      for (int i = 0; i < RK; ++i) kb[i] = k_frag(i);
+      matrix_phase<D>(true);
 #pragma unroll
-          for (int i = 0; i < RING; ++i) kb[i] = k_frag(K, i);
+      for (int i = 0; i < NK; ++i) {
+        s = mfma(kb[i % RK], qf[i], s);
+        if (i + RK < NK) kb[i % RK] = k_frag(i + RK);
+        __builtin_amdgcn_sched_barrier(0);
+      }
+      matrix_phase<D>(false);
 #pragma unroll
-          for (int i = 0; i < 2 * NK; ++i) {
-            s[i / NK] = mfma(kb[i % RING], qf[i % NK], s[i / NK]);
-            if (i + RING < 2 * NK) kb[i % RING] = k_frag(K, i + RING);
-            __builtin_amdgcn_sched_barrier(0);
-          }
-        }
-        if (j0 + BKV - 1 > qw) {  // the tile touches the diagonal of this wave
+      for (int i = 0; i < RV; ++i) vb[i] = v_frag(i);   // arrive beside the exponentials
+      __builtin_amdgcn_sched_barrier(0);
+      if (j0 + BK - 1 > qw) {  // the tile touches the diagonal of this wave
 #pragma unroll
-          for (int jt = 0; jt < 2; ++jt)
+        for (int q = 0; q < 16; ++q)
+          if (j0 + acc_row(q, g) > iq) s[q] = -INFINITY;
+      }
+      float tm[2] = {-INFINITY, -INFINITY};
 #pragma unroll
-            for (int q = 0; q < 16; ++q)
-              if (j0 + jt * 32 + acc_row(q, g) > iq) s[jt][q] = -INFINITY;
-        }
-        float tm = -INFINITY;
+      for (int q = 0; q < 16; ++q) tm[q & 1] = fmaxf(tm[q & 1], s[q]);
+      follow(row_max(fmaxf(tm[0], tm[1])));
+      const float mc = reference();
+      float ps[2] = {0.f, 0.f};
 #pragma unroll
-        for (int jt = 0; jt < 2; ++jt)
+      for (int q = 0; q < 16; ++q) {
+        const float p = __builtin_amdgcn_exp2f(s[q] * c - mc);
+        s[q] = p;
+        ps[q & 1] += p;
+      }
+      l += ps[0] + ps[1];
+      u32x4_t pf[2][NP];
+      pack_parts(s, 0, pf[0]);
+      pack_parts(s, 1, pf[1]);
+      matrix_phase<D>(true);
 #pragma unroll
-          for (int q = 0; q < 16; ++q) tm = fmaxf(tm, s[jt][q]);
-        follow(row_max(tm));
-        const float mc = m * c;
-        float ps[2] = {0.f, 0.f};
+      for (int i = 0; i < NV; ++i) {
+        o[i % NC] = mfma_parts(vb[i % RV], pf[i / NC], o[i % NC]);
+        if (i + RV < NV) vb[i % RV] = v_frag(i + RV);
+        __builtin_amdgcn_sched_barrier(0);
+      }
+      matrix_phase<D>(false);
+    }
+    TIDE_ATTN_WAIT_DMA();
+    lds_barrier();
+  }
+  if constexpr (NS > 1) {
+    // sets n .. 2n - 1 hand their maxima and sums to sets 0 .. n - 1, for n = NS / 2, NS / 4, ... (every stage is free by now)
+    float* sums = reinterpret_cast<float*>(smem);
 #pragma unroll
-        for (int jt = 0; jt < 2; ++jt)
-#pragma unroll
-          for (int q = 0; q < 16; ++q) {
-            const float p = __builtin_amdgcn_exp2f(s[jt][q] * c - mc);
-            s[jt][q] = p;
-            ps[q & 1] += p;
-          }
-        l += ps[0] + ps[1];
-        u32x4_t pf[4][NP];
-#pragma unroll
-        for (int ks = 0; ks < 4; ++ks) pack_parts(s[ks >> 1], ks & 1, pf[ks]);
+    for (int n = NS / 2; n >= 1; n /= 2) {
+      float* mine = sums + ((set % n) * KW + wave) * (NC * 16 + 2) * 64 + lane;
+      if (set >= n && set < 2 * n) {
 #pragma unroll
         for (int ct = 0; ct < NC; ++ct)
 #pragma unroll
-          for (int ks = 0; ks < 4; ++ks) o[ct] = mfma_parts(frag_tr<D>(V, ks * 16, ct * 32, lane), pf[ks], o[ct]);
+          for (int q = 0; q < 16; ++q) mine[(ct * 16 + q) * 64] = o[ct][q];
+        mine[NC * 16 * 64] = m;
+        mine[(NC * 16 + 1) * 64] = l;
       }
-      TIDE_ATTN_WAIT_DMA();
+      __syncthreads();
+      if (set < n) {
+        const float mo = mine[NC * 16 * 64], lo = mine[(NC * 16 + 1) * 64], mn = fmaxf(m, mo);
+        const float wa = m == -INFINITY ? 0.f : __builtin_amdgcn_exp2f((m - mn) * c), wb = mo == -INFINITY ? 0.f : __builtin_amdgcn_exp2f((mo - mn) * c);
+        m = mn;
+        l = l * wa + lo * wb;
+#pragma unroll
+        for (int ct = 0; ct < NC; ++ct)
+#pragma unroll
+          for (int q = 0; q < 16; ++q) o[ct][q] = o[ct][q] * wa + mine[(ct * 16 + q) * 64] * wb;
+      }
       __syncthreads();
     }
-  } else {
-    fetch_k(1);
-    fetch_v(0);
-
-    // One tile is two MFMA phases: the scores of tile t + 1 (2 NK MFMAs) beside the exponentials of tile t, then its P V beside
-    // the row maxima of the scores just made.  The order of MFMAs, operand reads (a ring of four fragments) and vector
-    // instructions is written out and pinned: left to two waves of a SIMD that took turns by chance, the matrix pipes were 40 % and
-    // the vector units 50 % busy, one after the other.  us before / now: 16 x 2048, 32 / 8 heads 770 / 745, 4 x 1024 68.6 / 65.1
-    // (the larger one sits at the power limit: without exponentials it takes 7 % less, without operand reads 11).
-    // A ring of six: the same; of eight: spills.  The same order in the dQ kernel (halves of a tile) gave nothing.
-    constexpr int NS = 2 * NK, EPM = 32 / NS;   // MFMAs of a score tile, exponentials beside each
-    f32x16_t sa[2], sb[2];
-    float tma = -INFINITY, tmb = -INFINITY;   // this lane's maximum of sa, sb
-    auto v_frag = [&](const bf16_t* V, int i) { return frag_tr<D>(V, (i / NC) * 16, (i % NC) * 32, lane); };   // k16 step i / NC, columns i % NC
-    {
-      const bf16_t* K = sK;   // tile 0: every wave sees key 0
-      u32x4_t kb[RING];
-#pragma unroll
-      for (int i = 0; i < RING; ++i) kb[i] = k_frag(K, i);
-#pragma unroll
-      for (int jt = 0; jt < 2; ++jt)
-#pragma unroll
-        for (int q = 0; q < 16; ++q) sa[jt][q] = 0.f;
-#pragma unroll
-      for (int i = 0; i < NS; ++i) {
-        sa[i / NK] = mfma(kb[i % RING], qf[i % NK], sa[i / NK]);
-        if (i + RING < NS) kb[i % RING] = k_frag(K, i + RING);
-        __builtin_amdgcn_sched_barrier(0);
-      }
-#pragma unroll
-      for (int q = 0; q < 32; ++q) tma = fmaxf(tma, sa[q / 16][q % 16]);
-    }
-    TIDE_ATTN_WAIT_DMA();
-    __syncthreads();
-
-    auto step = [&](f32x16_t (&s)[2], float tm, f32x16_t (&sn)[2], float& tmn, int t) {
-      const int j0 = t * BKV;
-      // (K(t) was last read in the step before, V(t - 1) as well: the barrier at its end has passed)
-      auto fetch = [&] { fetch_k(t + 2); fetch_v(t + 1); };
-      if (j0 > qw + 31) {
-        fetch();
-      } else {   // wave-uniform: the tile has at least one unmasked key for this wave
-        const bf16_t* K = sK + ((t + 1) & 1) * KV_TILE;
-        const bf16_t* V = sV + (t & 1) * KV_TILE;
-        const bool more = t + 1 < nt && j0 + BKV <= qw + 31;   // the next tile has one, too
-        u32x4_t ring[RING];
-        if (more) {
-#pragma unroll
-          for (int i = 0; i < RING; ++i) ring[i] = k_frag(K, i);
-        }
-        __builtin_amdgcn_sched_barrier(0);
-        fetch();   // behind the first operand reads, which arrive meanwhile
-        if (j0 + BKV - 1 > qw) {  // the tile touches the diagonal of this wave
-          tm = -INFINITY;
-#pragma unroll
-          for (int jt = 0; jt < 2; ++jt)
-#pragma unroll
-            for (int q = 0; q < 16; ++q) {
-              if (j0 + jt * 32 + acc_row(q, g) > iq) s[jt][q] = -INFINITY;
-              tm = fmaxf(tm, s[jt][q]);
-            }
-        }
-        tm = row_max(tm);
-        follow(tm);
-        const float mc = m * c;
-        u32x4_t pf[4][NP];
-        float ps[2] = {0.f, 0.f};
-        float mcx = mc;
-        auto prob = [&](int e) {   // element e = 0 .. 31 of the lane; every eighth completes an operand of P V
-          const float p = __builtin_amdgcn_exp2f(fmaf(s[e / 16][e % 16], c, -mcx));
-          s[e / 16][e % 16] = p;
-          ps[e & 1] += p;
-        };
-        if (more) {
-          asm volatile("" : "+v"(mcx));   // (or the multiply-adds, which both branches have, move out of them and ahead of the MFMAs)
-#pragma unroll
-          for (int jt = 0; jt < 2; ++jt)
-#pragma unroll
-            for (int q = 0; q < 16; ++q) sn[jt][q] = 0.f;
-#pragma unroll
-          for (int i = 0; i < NS; ++i) {
-            sn[i / NK] = mfma(ring[i % RING], qf[i % NK], sn[i / NK]);
-            ring[i % RING] = i + RING < NS ? k_frag(K, i + RING) : v_frag(V, i + RING - NS);
-#pragma unroll
-            for (int u = 0; u < EPM; ++u) prob(i * EPM + u);
-            if ((i + 1) * EPM % 8 == 0) pack_parts(s[i * EPM / 16], i * EPM % 16 / 8, pf[i * EPM / 8]);
-            __builtin_amdgcn_sched_barrier(0);
-          }
-        } else {
-#pragma unroll
-          for (int i = 0; i < RING; ++i) ring[i] = v_frag(V, i);
-#pragma unroll
-          for (int e = 0; e < 32; ++e) prob(e);
-#pragma unroll
-          for (int ks = 0; ks < 4; ++ks) pack_parts(s[ks >> 1], ks & 1, pf[ks]);
-        }
-        l += ps[0] + ps[1];
-        matrix_phase<D>(true);
-        constexpr int NV = 4 * NC, MPM = (32 + NV - 1) / NV;   // fragments of V, maxima beside each
-        float mx[2] = {-INFINITY, -INFINITY};
-        auto pv = [&](auto MORE) {
-#pragma unroll
-          for (int i = 0; i < NV; ++i) {
-            o[i % NC] = mfma_parts(ring[i % RING], pf[i / NC], o[i % NC]);
-            if (i + RING < NV) ring[i % RING] = v_frag(V, i + RING);
-            if constexpr (decltype(MORE)::value) {
-#pragma unroll
-              for (int u = 0; u < MPM; ++u) {
-                const int e = i * MPM + u;
-                if (e < 32) mx[u & 1] = fmaxf(mx[u & 1], sn[e / 16][e % 16]);
-              }
-            }
-            __builtin_amdgcn_sched_barrier(0);
-          }
-        };
-        if (more) pv(std::true_type{});
-        else pv(std::false_type{});
-        matrix_phase<D>(false);
-        tmn = fmaxf(mx[0], mx[1]);
-      }
-      TIDE_ATTN_WAIT_DMA();
-      __syncthreads();
-    };
-    for (int t = 0; t < nt; t += 2) {
-      step(sa, tma, sb, tmb, t);
-      if (t + 1 < nt) step(sb, tmb, sa, tma, t + 1);
-    }
+    if (set != 0) return;
   }
   l += swap_halves(l);
 
@@ -571,7 +530,7 @@ __global__ __launch_bounds__(256, blocks_per_cu(D, 4, 2)) void attn_fwd_mfma_ker
     // A masked key has probability zero, but zero times a NaN or an infinity of its V row is a NaN that reaches the earlier
     // queries of its tile.  Rows that are not finite although their sum is are made again from the keys they see alone,
     // a channel per lane.  No row of finite inputs is, and 32 multiply-adds per lane and block find out.
-    for (uint32_t rows = not_finite(o, l - l == 0.f && iq < S); rows != 0; rows &= rows - 1) {   // wave-uniform
+    for (uint32_t rows = not_finite(o, l - l == 0.f && valid); rows != 0; rows &= rows - 1) {   // wave-uniform
       const int r = __builtin_ctz(rows);
       const float mr = __shfl(m, r, 64), ir = __shfl(inv, r, 64);
       const float qv = bf2f(base[(size_t)(qw + r) * ld + h * D + lane]);
@@ -585,9 +544,8 @@ __global__ __launch_bounds__(256, blocks_per_cu(D, 4, 2)) void attn_fwd_mfma_ker
       smem[(wave * 32 + r) * pitch(D) + lane] = f2bf(acc * ir);
     }
   }
-  if (g == 0 && iq < S) lse[stat_index(cu, T, sv, b, h, nh, Smax, iq)] = m * (1.0f / sqrtf((float)D)) + logf(l);
-  __syncthreads();
-  copy_out<D>(smem, out, sv.row0 + q0, sv.row0 + min(S, q0 + BQ), nh * D, h * D, tid);
+  if (g == 0 && valid) lse[stat_index(cu, T, sv, b, h, nh, Smax, iq)] = m * (1.0f / sqrtf((float)D)) + logf(l);
+  if (item.on) copy_rows<D>(smem, out, sv.row0 + qw, S - qw, nh * D, h * D, wave, lane);
 }
 
 // ------------------------------------------------------------------------------------------------
@@ -595,28 +553,28 @@ __global__ __launch_bounds__(256, blocks_per_cu(D, 4, 2)) void attn_fwd_mfma_ker
 // passes read: the dO fragments are in registers anyway, so O is all that is loaded for it (a pass of its own
 // read dO again: 100 us at 16 x 2048, 32 heads, against 45 us more in this kernel).
 // ------------------------------------------------------------------------------------------------
-template <int D>
-__global__ __launch_bounds__(256, blocks_per_cu(D, 3, 2)) void attn_dq_mfma_kernel(const bf16_t* __restrict__ qkv, const bf16_t* __restrict__ out, const bf16_t* __restrict__ dout,
+template <int D, int KW, int NS>
+__global__ __launch_bounds__(KW * NS * 64, dq_waves(D, NS)) void attn_dq_mfma_kernel(const bf16_t* __restrict__ qkv, const bf16_t* __restrict__ out, const bf16_t* __restrict__ dout,
                                                            const float* __restrict__ lse, float* __restrict__ delta,
                                                            bf16_t* __restrict__ dqkv, int Smax, int nh, int nkv,
-                                                           const int* __restrict__ cu, int64_t T, int nseq) {
-  constexpr int NK = D / 16, NC = D / 32;   // k16 steps of a score product, 32-column tiles of a result
-  constexpr int KV_TILE = kv_tile(D);
+                                                           const int* __restrict__ cu, int64_t T, WorkMap map) {
+  constexpr int NK = D / 16, NC = D / 32, BK = 32;   // as in the forward kernel
+  using Kv = KvDma<D, KW>;
   extern __shared__ __attribute__((aligned(16))) bf16_t smem[];
-  bf16_t* sK = smem;
-  bf16_t* sV = smem + 2 * KV_TILE;
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int wave_all = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), set = NS > 1 ? wave_all / KW : 0, wave_s = wave_all - set * KW;
+  const int lane = threadIdx.x & 63, wave = wave_s;
+  bf16_t* stages = smem + set * 2 * Kv::STAGE;
   const int lr = lane & 31, g = lane >> 5, plr = perm(lr);
-  const int nqb = (Smax + BQ - 1) / BQ;
-  const Work3 wk = xcd_group_work(nqb, nh, nseq, nh / nkv);
-  const int qb = nqb - 1 - wk.x;
-  const int h = wk.y, b = wk.z;
+  const int G = nh / nkv;
+  const Work3 wk = work_item(map);
+  if (!wk.on) return;
+  const int kh = wk.y, b = wk.z;
   const SeqView sv = seq_view(cu, b, Smax, T);
   const int S = sv.len;
-  const int G = nh / nkv, kh = h / G;
   const int ld = (nh + 2 * nkv) * D, ldo = nh * D;
-  const int q0 = qb * BQ, qw = q0 + wave * 32, iq = qw + lr;
-  if (q0 >= S) return;   // the whole block, before any barrier
+  if (wk.x >= row_blocks<KW>(S, G)) return;   // the whole block, before any barrier
+  const RowItem item = row_item<KW>(wk.x, wave_s, kh, G, S);
+  const int h = item.h, qw = item.qw, iq = qw + lr, row = item.on ? iq : S;
   const __amdgpu_buffer_rsrc_t rs = rsrc(qkv + (size_t)sv.row0 * ld, (uint32_t)((size_t)S * ld * 2));
   const __amdgpu_buffer_rsrc_t rso = rsrc(dout + (size_t)sv.row0 * ldo, (uint32_t)((size_t)S * ldo * 2));
   const int kcol = (nh + kh) * D, vcol = (nh + nkv + kh) * D;
@@ -626,10 +584,10 @@ __global__ __launch_bounds__(256, blocks_per_cu(D, 3, 2)) void attn_dq_mfma_kern
   u32x4_t qf[NK], dof[NK];
 #pragma unroll
   for (int kk = 0; kk < NK; ++kk) {
-    qf[kk] = __builtin_bit_cast(u32x4_t, __builtin_amdgcn_raw_buffer_load_b128(rs, ((uint32_t)iq * (uint32_t)ld + (uint32_t)(h * D + kk * 16 + g * 8)) * 2u, 0, 0));
-    dof[kk] = __builtin_bit_cast(u32x4_t, __builtin_amdgcn_raw_buffer_load_b128(rso, ((uint32_t)iq * (uint32_t)ldo + (uint32_t)(h * D + kk * 16 + g * 8)) * 2u, 0, 0));
+    qf[kk] = __builtin_bit_cast(u32x4_t, __builtin_amdgcn_raw_buffer_load_b128(rs, ((uint32_t)row * (uint32_t)ld + (uint32_t)(h * D + kk * 16 + g * 8)) * 2u, 0, 0));
+    dof[kk] = __builtin_bit_cast(u32x4_t, __builtin_amdgcn_raw_buffer_load_b128(rso, ((uint32_t)row * (uint32_t)ldo + (uint32_t)(h * D + kk * 16 + g * 8)) * 2u, 0, 0));
   }
-  const bool valid = iq < S;
+  const bool valid = item.on && iq < S;
   const bool edge_q = qw + 32 > S;   // wave-uniform: some query row of this wave lies past the sequence
   const float lse_i = valid ? lse[stat_index(cu, T, sv, b, h, nh, Smax, iq)] * kLog2e : 0.f;
   float del_i = 0.f;   // a row past the end loads zeros
@@ -638,7 +596,7 @@ __global__ __launch_bounds__(256, blocks_per_cu(D, 3, 2)) void attn_dq_mfma_kern
     u32x4_t of[NK];
 #pragma unroll
     for (int kk = 0; kk < NK; ++kk)
-      of[kk] = __builtin_bit_cast(u32x4_t, __builtin_amdgcn_raw_buffer_load_b128(rsout, ((uint32_t)iq * (uint32_t)ldo + (uint32_t)(h * D + kk * 16 + g * 8)) * 2u, 0, 0));
+      of[kk] = __builtin_bit_cast(u32x4_t, __builtin_amdgcn_raw_buffer_load_b128(rsout, ((uint32_t)row * (uint32_t)ldo + (uint32_t)(h * D + kk * 16 + g * 8)) * 2u, 0, 0));
 #pragma unroll
     for (int kk = 0; kk < NK; ++kk)
 #pragma unroll
@@ -647,7 +605,7 @@ __global__ __launch_bounds__(256, blocks_per_cu(D, 3, 2)) void attn_dq_mfma_kern
         del_i = fmaf(__uint_as_float(of[kk][w] & 0xFFFF0000u), __uint_as_float(dof[kk][w] & 0xFFFF0000u), del_i);
       }
     del_i += __shfl_xor(del_i, 32, 64);
-    if (valid && g == 0) delta[stat_index(cu, T, sv, b, h, nh, Smax, iq)] = del_i;
+    if (valid && g == 0 && set == 0) delta[stat_index(cu, T, sv, b, h, nh, Smax, iq)] = del_i;
   }
 
   f32x16_t dq[NC];
@@ -656,82 +614,76 @@ __global__ __launch_bounds__(256, blocks_per_cu(D, 3, 2)) void attn_dq_mfma_kern
 #pragma unroll
     for (int q = 0; q < 16; ++q) dq[ct][q] = 0.f;
 
-  const int kv_end = min(S, q0 + BQ);
-  const int nt = (kv_end + BKV - 1) / BKV;
+  const int nt = (item.kv_end + BK - 1) / BK, nr = (nt + NS - 1) / NS;   // set s takes tiles s, s + NS, ...
   const bf16_t* seq = qkv + (size_t)sv.row0 * ld;
   const uint32_t seq_bytes = (uint32_t)((size_t)S * ld * 2);
-  const int wave_s = __builtin_amdgcn_readfirstlane(wave);
-  TileDma<64, D> dma;
-  dma.init(ld, wave, lane);
-  dma.issue(seq, seq_bytes, sK, (uint32_t)kcol * 2u, wave_s);
-  dma.issue(seq, seq_bytes, sV, (uint32_t)vcol * 2u, wave_s);
+  Kv kv;
+  kv.init(ld, (vcol - kcol) * 2, wave, lane);
+  auto fetch = [&](int t) {
+    const int tile = set + NS * t;
+    if (tile < nt) kv.dma.issue(seq, seq_bytes, stages + (t & 1) * Kv::STAGE, ((uint32_t)(tile * BK) * (uint32_t)ld + (uint32_t)kcol) * 2u, wave_s);
+  };
+  fetch(0);
   __builtin_amdgcn_s_waitcnt(0x0F70);   // vmcnt(0): nothing of the prologue is in flight inside the loop (see the forward kernel)
-  __syncthreads();
+  lds_barrier();
 
-  for (int t = 0; t < nt; ++t) {
-    const int st = t & 1;
-    const int j0 = t * BKV;
-    if (t + 1 < nt) {
-      const uint32_t row_bytes = (uint32_t)(j0 + BKV) * (uint32_t)ld * 2u;
-      dma.issue(seq, seq_bytes, sK + (st ^ 1) * KV_TILE, row_bytes + (uint32_t)kcol * 2u, wave_s);
-      dma.issue(seq, seq_bytes, sV + (st ^ 1) * KV_TILE, row_bytes + (uint32_t)vcol * 2u, wave_s);
-    }
+  constexpr int NP = parts(D), NX = 2 * NC, RING = dq_ring(D), RX = 4;
+  for (int t = 0; t < nr; ++t) {
+    const int j0 = (set + NS * t) * BK;
+    fetch(t + 1);
     if (j0 <= qw + 31) {
-      const bf16_t* K = sK + st * KV_TILE;
-      const bf16_t* V = sV + st * KV_TILE;
-      const bool diag = j0 + BKV - 1 > qw;
-      u32x4_t dsf[4][parts(D)];
+      const bf16_t *K = stages + (t & 1) * Kv::STAGE, *V = K + 32 * pitch(D);
+      const bool diag = j0 + BK - 1 > qw;
+      auto x_frag = [&](int i) { return frag_tr<D>(K, (i / NC) * 16, (i % NC) * 32, lane); };   // of K^T
+      u32x4_t fb[RING], xb[RX];
+      f32x16_t s, dp;
 #pragma unroll
-      for (int jt = 0; jt < 2; ++jt) {
-        f32x16_t s, dp;
+      for (int q = 0; q < 16; ++q) { s[q] = 0.f; dp[q] = 0.f; }
+      // K and V fragments alternately through a ring, each requested RING MFMAs ahead (see the forward kernel)
+      auto fetch_frag = [&](int i) { return frag<D>((i & 1) ? V : K, 0, plr, (i >> 1) * 16 + g * 8); };
 #pragma unroll
-        for (int q = 0; q < 16; ++q) { s[q] = 0.f; dp[q] = 0.f; }
-#if TIDE_ATTN_DQ_RING == 0
-#pragma unroll
-        for (int kk = 0; kk < NK; ++kk) {
-          s = mfma(frag<D>(K, jt * 32, plr, kk * 16 + g * 8), qf[kk], s);
-          dp = mfma(frag<D>(V, jt * 32, plr, kk * 16 + g * 8), dof[kk], dp);
-        }
-#else
-        {
-          // K and V fragments alternately through a ring, each requested TIDE_ATTN_DQ_RING MFMAs ahead (see the forward kernel)
-          constexpr int RING = TIDE_ATTN_DQ_RING;
-          u32x4_t fb[RING];
-          auto fetch = [&](int i) { return frag<D>((i & 1) ? V : K, jt * 32, plr, (i >> 1) * 16 + g * 8); };
-#pragma unroll
-          for (int i = 0; i < RING; ++i) fb[i] = fetch(i);
-#pragma unroll
-          for (int i = 0; i < 2 * NK; ++i) {
-            if (i & 1) dp = mfma(fb[i % RING], dof[i >> 1], dp);
-            else s = mfma(fb[i % RING], qf[i >> 1], s);
-            if (i + RING < 2 * NK) fb[i % RING] = fetch(i + RING);
-            __builtin_amdgcn_sched_barrier(0);
-          }
-        }
-#endif
-        if (diag || edge_q) {   // wave-uniform: only a tile on the diagonal or the last query block needs per-element tests (-4.5 %)
-#pragma unroll
-          for (int q = 0; q < 16; ++q) {
-            float p = __builtin_amdgcn_exp2f(s[q] * c - lse_i);
-            if (!valid || (diag && (j0 + jt * 32 + acc_row(q, g) > iq))) p = 0.f;
-            s[q] = p * (dp[q] - del_i);
-          }
-        } else {
-#pragma unroll
-          for (int q = 0; q < 16; ++q) s[q] = __builtin_amdgcn_exp2f(s[q] * c - lse_i) * (dp[q] - del_i);
-        }
-        pack_parts(s, 0, dsf[2 * jt]);
-        pack_parts(s, 1, dsf[2 * jt + 1]);
-      }
+      for (int i = 0; i < RING; ++i) fb[i] = fetch_frag(i);
       matrix_phase<D>(true);
 #pragma unroll
-      for (int ct = 0; ct < NC; ++ct)
+      for (int i = 0; i < 2 * NK; ++i) {
+        if (i & 1) dp = mfma(fb[i % RING], dof[i >> 1], dp);
+        else s = mfma(fb[i % RING], qf[i >> 1], s);
+        if (i + RING < 2 * NK) fb[i % RING] = fetch_frag(i + RING);
+        __builtin_amdgcn_sched_barrier(0);
+      }
+      matrix_phase<D>(false);
 #pragma unroll
-        for (int ks = 0; ks < 4; ++ks) dq[ct] = mfma_parts(frag_tr<D>(K, ks * 16, ct * 32, lane), dsf[ks], dq[ct]);
+      for (int i = 0; i < RX; ++i) xb[i] = x_frag(i);   // arrive beside the exponentials
+      __builtin_amdgcn_sched_barrier(0);
+      if (diag || edge_q) {   // wave-uniform: only a tile on the diagonal or the last query block needs per-element tests (-4.5 %)
+#pragma unroll
+        for (int q = 0; q < 16; ++q) {
+          float p = __builtin_amdgcn_exp2f(s[q] * c - lse_i);
+          if (!valid || (diag && (j0 + acc_row(q, g) > iq))) p = 0.f;
+          s[q] = p * (dp[q] - del_i);
+        }
+      } else {
+#pragma unroll
+        for (int q = 0; q < 16; ++q) s[q] = __builtin_amdgcn_exp2f(s[q] * c - lse_i) * (dp[q] - del_i);
+      }
+      u32x4_t dsf[2][NP];
+      pack_parts(s, 0, dsf[0]);
+      pack_parts(s, 1, dsf[1]);
+      matrix_phase<D>(true);
+#pragma unroll
+      for (int i = 0; i < NX; ++i) {
+        dq[i % NC] = mfma_parts(xb[i % RX], dsf[i / NC], dq[i % NC]);
+        if (i + RX < NX) xb[i % RX] = x_frag(i + RX);
+        __builtin_amdgcn_sched_barrier(0);
+      }
       matrix_phase<D>(false);
     }
     TIDE_ATTN_WAIT_DMA();
-    __syncthreads();
+    lds_barrier();
+  }
+  if constexpr (NS > 1) {
+    merge_sets<KW, NS, NC>(smem, dq, set, wave, lane);
+    if (set != 0) return;
   }
   stage_out<D>(smem, dq, scale, wave, lane);
   if constexpr (D == 64) {
@@ -754,8 +706,7 @@ __global__ __launch_bounds__(256, blocks_per_cu(D, 3, 2)) void attn_dq_mfma_kern
       smem[(wave * 32 + r) * pitch(D) + lane] = f2bf(acc * scale);
     }
   }
-  __syncthreads();
-  copy_out<D>(smem, dqkv, sv.row0 + q0, sv.row0 + min(S, q0 + BQ), ld, h * D, tid);
+  if (item.on) copy_rows<D>(smem, dqkv, sv.row0 + qw, S - qw, ld, h * D, wave, lane);
 }
 
 // ------------------------------------------------------------------------------------------------
@@ -763,7 +714,7 @@ __global__ __launch_bounds__(256, blocks_per_cu(D, 3, 2)) void attn_dq_mfma_kern
 // ------------------------------------------------------------------------------------------------
 namespace {
 // Query rows per streamed tile (32 or 64: two halves of 32 between two barriers) of the dV and of the dK pass.
-// Measured, backward at 16 x 2048 / 2 x 16384 (dV rows / dK rows): 32 / 32: 3.18 / 18.2 ms; 32 / 64: 3.08 / 18.0;
+// Measured at head size 128, backward at 16 x 2048 / 2 x 16384 (dV rows / dK rows): 32 / 32: 3.18 / 18.2 ms; 32 / 64: 3.08 / 18.0;
 // 64 / 32: 3.14 / 18.7; 64 / 64: 3.09 / 18.5 (with 64 rows the dV pass loses its third block per CU to the LDS).
 #ifndef TIDE_ATTN_DV_ROWS
 #define TIDE_ATTN_DV_ROWS 32
@@ -772,11 +723,13 @@ namespace {
 #define TIDE_ATTN_DK_ROWS 64
 #endif
 // (with several sets of waves per block, 32 in both passes: the sets' stages have to fit the LDS)
+enum : int { kValueGrad = 0, kKeyGrad = 1, kBothGrads = 2 };   // what a launch makes
 template <int WHICH, int NS>
-constexpr int dkv_rows() { return WHICH == 1 && NS == 1 ? TIDE_ATTN_DK_ROWS : TIDE_ATTN_DV_ROWS; }
+constexpr int dkv_rows() { return WHICH == kKeyGrad && NS == 1 ? TIDE_ATTN_DK_ROWS : TIDE_ATTN_DV_ROWS; }
+constexpr int dkv_waves(int WHICH, int NS) { return NS > 1 ? 1 : WHICH == kValueGrad ? 3 : 2; }
 template <int BI, int D> struct DkvStage {
   static constexpr int Q_TILE = TileDma<BI, D>::CHUNKS * 512;   // elements: the tile rounded up to whole 1 KiB chunks of the LDS-DMA loads
-  static constexpr int STAGE = 2 * Q_TILE + 4 * BI;          // Q tile, dO tile, then lse[BI] and delta[BI] as floats
+  static constexpr int STAGE = 2 * Q_TILE + 4 * BI;          // Q tile, dO tile, then BI floats from lse and BI from delta, see sstore
 };
 }  // namespace
 
@@ -786,20 +739,24 @@ template <int BI, int D> struct DkvStage {
 // waves, four such sets, each with LDS stages of its own, take every fourth query tile, and the sets' sums are added through
 // LDS at the end, in a fixed order.
 constexpr int kFewKW = 2, kFewNS = 4;
-// One gradient per pass (WHICH = 0: dV, 1: dK).  Half the accumulators and, for dV, half the operand
+// At head size 128 one gradient per pass.  Half the accumulators and, for dV, half the operand
 // registers of the fused kernel: the pass fits 256 VGPRs, two blocks share a CU, and one block's
-// exponentials overlap the other's MFMAs.  The price is that S = Q K^T is computed in both passes.
+// exponentials overlap the other's MFMAs.  The price is that S = Q K^T is computed in both passes.  At head size 64 both in
+// one (6 x 777, 16 / 4 heads: 34 + 41 us in two launches, 46 in one).  The score products begin from - lse and - delta, which their
+// rows' accumulators read from LDS (16 to 32 vector instructions fewer per 32 x 32 scores than zeros and two subtractions), and
+// the walk over tiles and heads is a counter (a division by G per tile was 100 scalar instructions): 16 x 2048, 32 / 8 heads of 128: 688 + 923 -> 649 + 900 us.
 template <int WHICH, int D, int KW, int NS>
-__global__ __launch_bounds__(KW * NS * 64, NS > 1 ? 1 : WHICH == 0 ? blocks_per_cu(D, 4, 3) : blocks_per_cu(D, 3, 2)) void attn_dkv_mfma_kernel(const bf16_t* __restrict__ qkv, const bf16_t* __restrict__ dout,
+__global__ __launch_bounds__(KW * NS * 64, dkv_waves(WHICH, NS)) void attn_dkv_mfma_kernel(const bf16_t* __restrict__ qkv, const bf16_t* __restrict__ dout,
                                                             const float* __restrict__ lse, const float* __restrict__ delta,
                                                             bf16_t* __restrict__ dqkv, int Smax, int nh, int nkv,
-                                                            const int* __restrict__ cu, int64_t T, int nseq) {
+                                                            const int* __restrict__ cu, int64_t T, WorkMap map) {
   extern __shared__ __attribute__((aligned(16))) bf16_t smem[];
   constexpr int KB = KW * 32, SET = KW * 64;   // keys of the block, threads of a set
   const int set = NS > 1 ? __builtin_amdgcn_readfirstlane(threadIdx.x / SET) : 0;
   const int tid = threadIdx.x - set * SET, lane = tid & 63, wave = tid >> 6;   // inside the set
   const int lr = lane & 31, g = lane >> 5, plr = perm(lr);
-  const Work3 wk = xcd_group_work((Smax + KB - 1) / KB, nkv, nseq, 1);
+  const Work3 wk = work_item(map);
+  if (!wk.on) return;
   const int jb = wk.x, kh = wk.y, b = wk.z;  // early key blocks are the heavy ones
   const SeqView sv = seq_view(cu, b, Smax, T);
   const int S = sv.len;
@@ -812,7 +769,7 @@ __global__ __launch_bounds__(KW * NS * 64, NS > 1 ? 1 : WHICH == 0 ? blocks_per_
   const float scale = 1.0f / sqrtf((float)D);
   const float c = kLog2e * scale;
 
-  constexpr bool DK = WHICH == 1;
+  constexpr bool DV = WHICH != kKeyGrad, DK = WHICH != kValueGrad, BOTH = DV && DK;
   constexpr int BI = dkv_rows<WHICH, NS>();
   constexpr int NK = D / 16, NC = D / 32;
   constexpr int Q_TILE = DkvStage<BI, D>::Q_TILE, DKV_STAGE = DkvStage<BI, D>::STAGE;
@@ -822,9 +779,10 @@ __global__ __launch_bounds__(KW * NS * 64, NS > 1 ? 1 : WHICH == 0 ? blocks_per_
     kf[kk] = __builtin_bit_cast(u32x4_t, __builtin_amdgcn_raw_buffer_load_b128(rs, ((uint32_t)jk * (uint32_t)ld + (uint32_t)(kcol + kk * 16 + g * 8)) * 2u, 0, 0));
     if constexpr (DK) vf[kk] = __builtin_bit_cast(u32x4_t, __builtin_amdgcn_raw_buffer_load_b128(rs, ((uint32_t)jk * (uint32_t)ld + (uint32_t)(vcol + kk * 16 + g * 8)) * 2u, 0, 0));
   }
-  f32x16_t dacc[NC];   // dK or dV of this wave's 32 keys
+  constexpr int NA = BOTH ? 2 * NC : NC, KC = BOTH ? NC : 0;   // accumulators; where those of dK begin
+  f32x16_t dacc[NA];   // dV and / or dK of this wave's 32 keys
 #pragma unroll
-  for (int ct = 0; ct < NC; ++ct)
+  for (int ct = 0; ct < NA; ++ct)
 #pragma unroll
     for (int q = 0; q < 16; ++q) dacc[ct][q] = 0.f;
 
@@ -846,10 +804,15 @@ __global__ __launch_bounds__(KW * NS * 64, NS > 1 ? 1 : WHICH == 0 ? blocks_per_
   // passes fetched nearly every tile through the fabric: 3.8 GB per launch at the 8B shape, L2 hits 21 %).
   // (and tile by tile over the G query heads, not head by head: blocks with fewer tiles would otherwise move on
   // to the next head early)
-  auto tile_i0 = [&](int u) { return i_begin + (nit - 1 - u / G) * BI; };
-  auto gload = [&](int u, int st) {   // tile u into stage st (whose last readers have passed a barrier)
-    const int hh = kh * G + u % G;
-    const int i0 = tile_i0(u);
+  struct Place { int hg, i0; };   // head of the group and first query of a tile
+  Place at = {0, i_begin + (nit - 1) * BI};
+  auto advance = [&](Place& p, int n) {   // n tiles further on
+    p.hg += n;
+    while (p.hg >= G) { p.hg -= G; p.i0 -= BI; }
+  };
+  const float to_scores = -sqrtf((float)D);
+  auto gload = [&](const Place& p, int st) {   // a tile into stage st (whose last readers have passed a barrier)
+    const int hh = kh * G + p.hg, i0 = p.i0;
     bf16_t* base = stages + st * DKV_STAGE;
     dmq.issue(seq, seq_bytes, base, ((uint32_t)i0 * (uint32_t)ld + (uint32_t)(hh * D)) * 2u, wave_s);
     dmo.issue(seq_do, seq_do_bytes, base + Q_TILE, ((uint32_t)i0 * (uint32_t)ldo + (uint32_t)(hh * D)) * 2u, wave_s);
@@ -860,13 +823,16 @@ __global__ __launch_bounds__(KW * NS * 64, NS > 1 ? 1 : WHICH == 0 ? blocks_per_
       stat = (i < S) ? src[stat_index(cu, T, sv, b, hh, nh, Smax, i)] : ((tid < BI) ? INFINITY : 0.f);
     }
   };
+  // What the score products begin from, in place of zeros: - lse sqrt(D), so that S comes out as (q k / sqrt(D) - lse) sqrt(D) and the
+  // probability is exp2 of it times one constant, and - delta.
   auto sstore = [&](int st) {
     bf16_t* base = stages + st * DKV_STAGE;
-    if (tid < 2 * BI) reinterpret_cast<float*>(base + 2 * Q_TILE)[tid] = stat * ((tid < BI) ? kLog2e : 1.f);   // lse * log2(e), delta
+    if (tid < 2 * BI) reinterpret_cast<float*>(base + 2 * Q_TILE)[tid] = stat * ((tid < BI) ? to_scores : -1.f);
   };
 
   if (NS == 1 || set < ntiles) {   // (one set: there is always a tile)
-    gload(set, 0);
+    advance(at, set);
+    gload(at, 0);
     sstore(0);
   }
   __builtin_amdgcn_s_waitcnt(0x0F70);   // vmcnt(0): the tile and the K / V fragments have arrived before the loop
@@ -874,8 +840,11 @@ __global__ __launch_bounds__(KW * NS * 64, NS > 1 ? 1 : WHICH == 0 ? blocks_per_
   // (the sets' trip counts differ by one at most: every set passes every barrier)
   for (int r = 0; r * NS < ntiles; ++r) {
     const int st = r & 1, u = r * NS + set;
-    if (u + NS < ntiles) gload(u + NS, st ^ 1);
-    const int it0 = NS == 1 || u < ntiles ? tile_i0(u) : S;   // past the end: no half of the tile is entered
+    const int it0 = NS == 1 || u < ntiles ? at.i0 : S;   // past the end: no half of the tile is entered
+    if (u + NS < ntiles) {
+      advance(at, NS);
+      gload(at, st ^ 1);
+    }
 #pragma unroll
     for (int hf = 0; hf < BI / 32; ++hf) {
     const int i0 = it0 + hf * 32;   // this half's first query
@@ -885,7 +854,14 @@ __global__ __launch_bounds__(KW * NS * 64, NS > 1 ? 1 : WHICH == 0 ? blocks_per_
       const float* stats = reinterpret_cast<const float*>(Qt + 2 * Q_TILE) + hf * 32;
       f32x16_t s, dp;
 #pragma unroll
-      for (int q = 0; q < 16; ++q) { s[q] = 0.f; dp[q] = 0.f; }
+      for (int qq = 0; qq < 4; ++qq) {   // row 8 qq + 4 g + e is register 4 qq + e
+        const float4 l4 = *reinterpret_cast<const float4*>(stats + 8 * qq + 4 * g);
+        s[4 * qq] = l4.x; s[4 * qq + 1] = l4.y; s[4 * qq + 2] = l4.z; s[4 * qq + 3] = l4.w;
+        if constexpr (DK) {
+          const float4 d4 = *reinterpret_cast<const float4*>(stats + BI + 8 * qq + 4 * g);
+          dp[4 * qq] = d4.x; dp[4 * qq + 1] = d4.y; dp[4 * qq + 2] = d4.z; dp[4 * qq + 3] = d4.w;
+        }
+      }
       {
         // Q (and, in the dK pass, dO) fragments through a ring, each requested TIDE_ATTN_DKV_RING MFMAs ahead
         constexpr int RING = TIDE_ATTN_DKV_RING, NF = DK ? 2 * NK : NK;
@@ -913,32 +889,30 @@ __global__ __launch_bounds__(KW * NS * 64, NS > 1 ? 1 : WHICH == 0 ? blocks_per_
       const bool diag = i0 < jw + 32;  // some (query, key) pair of the half is above the diagonal
       auto probs = [&](auto MASK) {
 #pragma unroll
-        for (int qq = 0; qq < 4; ++qq) {
-          const float4 l4 = *reinterpret_cast<const float4*>(stats + 8 * qq + 4 * g);   // lse * log2(e), see sstore
-          const float4 d4 = *reinterpret_cast<const float4*>(stats + BI + 8 * qq + 4 * g);
-          const float lv4[4] = {l4.x, l4.y, l4.z, l4.w}, dv4[4] = {d4.x, d4.y, d4.z, d4.w};
-#pragma unroll
-          for (int e = 0; e < 4; ++e) {
-            const int q = qq * 4 + e;
-            float p = __builtin_amdgcn_exp2f(s[q] * c - lv4[e]);
-            if constexpr (decltype(MASK)::value) {
-              if (i0 + 8 * qq + 4 * g + e < jk) p = 0.f;
-            }
-            s[q] = DK ? p * (dp[q] - dv4[e]) : p;   // dS for the dK pass, P for the dV pass
+        for (int q = 0; q < 16; ++q) {
+          float p = __builtin_amdgcn_exp2f(s[q] * c);
+          if constexpr (decltype(MASK)::value) {
+            if (i0 + acc_row(q, g) < jk) p = 0.f;
           }
+          s[q] = p;                           // P for dV
+          if constexpr (DK) dp[q] = p * dp[q];   // dS for dK
         }
       };
       if (diag) probs(std::true_type{});
       else probs(std::false_type{});
-      u32x4_t pf[2][parts(D)];
-      pack_parts(s, 0, pf[0]);
-      pack_parts(s, 1, pf[1]);
-      const bf16_t* Xt = DK ? Qt : dOt;   // dK += dS^T Q, dV += P^T dO
       matrix_phase<D>(true);
+      // dV += P^T dO, dK += dS^T Q
+      auto product = [&](const f32x16_t& x, const bf16_t* Xt, int c0) {
+        u32x4_t pf[2][parts(D)];
+        pack_parts(x, 0, pf[0]);
+        pack_parts(x, 1, pf[1]);
 #pragma unroll
-      for (int ct = 0; ct < NC; ++ct)
+        for (int ct = 0; ct < NC; ++ct)
 #pragma unroll
-        for (int ks = 0; ks < 2; ++ks) dacc[ct] = mfma_parts(frag_tr<D>(Xt, hf * 32 + ks * 16, ct * 32, lane), pf[ks], dacc[ct]);
+          for (int ks = 0; ks < 2; ++ks) dacc[c0 + ct] = mfma_parts(frag_tr<D>(Xt, hf * 32 + ks * 16, ct * 32, lane), pf[ks], dacc[c0 + ct]);
+      };
+      if constexpr (DV) product(s, dOt, 0);
+      if constexpr (DK) product(dp, Qt, KC);
       matrix_phase<D>(false);
     }
     }
@@ -947,35 +921,20 @@ __global__ __launch_bounds__(KW * NS * 64, NS > 1 ? 1 : WHICH == 0 ? blocks_per_
     __syncthreads();
   }
   if constexpr (NS > 1) {
-    // sets n .. 2n - 1 hand their sums to sets 0 .. n - 1, for n = NS / 2, NS / 4, ... (every stage is free by now)
-    float* sums = reinterpret_cast<float*>(smem);
-#pragma unroll
-    for (int n = NS / 2; n >= 1; n /= 2) {
-      float* mine = sums + ((size_t)((set % n) * KW + wave) * NC * 16) * 64 + lane;
-      if (set >= n && set < 2 * n) {
-#pragma unroll
-        for (int ct = 0; ct < NC; ++ct)
-#pragma unroll
-          for (int q = 0; q < 16; ++q) mine[(ct * 16 + q) * 64] = dacc[ct][q];
-      }
-      __syncthreads();
-      if (set < n) {
-#pragma unroll
-        for (int ct = 0; ct < NC; ++ct)
-#pragma unroll
-          for (int q = 0; q < 16; ++q) dacc[ct][q] += mine[(ct * 16 + q) * 64];
-      }
-      __syncthreads();
-    }
+    merge_sets<KW, NS, NA>(smem, dacc, set, wave, lane);
+    if (set != 0) return;
   }
-  const int64_t r0 = sv.row0 + j0, r1 = sv.row0 + min(S, j0 + KB);
-  if (set == 0) {
-    stage_out<D>(smem, dacc, DK ? scale : 1.0f, wave, lane);
+  // one result after the other through the wave's own 32 rows of LDS
+  auto store = [&](auto C0, auto ISK) {
+    constexpr int c0 = decltype(C0)::value;
+    constexpr bool is_k = decltype(ISK)::value;
+    f32x16_t (&acc)[NC] = *reinterpret_cast<f32x16_t (*)[NC]>(&dacc[c0]);
+    stage_out<D>(smem, acc, is_k ? scale : 1.0f, wave, lane);
     if constexpr (D == 64) {
       // As in the forward kernel, from the other side: the queries jw .. j - 1 meet key j with weight zero.  Keys after the
       // first of them that is not finite are made again from the queries that see them alone (a later query takes every
       // key before it with it, rightly).
-      uint32_t rows = not_finite(dacc, jk < S);
+      uint32_t rows = not_finite(acc, jk < S);
       const bf16_t *base = qkv + (size_t)sv.row0 * ld, *dob = dout + (size_t)sv.row0 * ldo;
       if (rows != 0) {   // wave-uniform
         int first = 31;
@@ -992,23 +951,25 @@ __global__ __launch_bounds__(KW * NS * 64, NS > 1 ? 1 : WHICH == 0 ? blocks_per_
       for (; rows != 0; rows &= rows - 1) {
         const int r = __builtin_ctz(rows), j = jw + r;
         const float kv = bf2f(base[(size_t)j * ld + kcol + lane]), vv = bf2f(base[(size_t)j * ld + vcol + lane]);
-        float acc = 0.f;
-        for (int hh = kh * G; hh < (kh + 1) * G && __builtin_amdgcn_ballot_w64(acc - acc == 0.f) != 0; ++hh)
+        float sum = 0.f;
+        for (int hh = kh * G; hh < (kh + 1) * G && __builtin_amdgcn_ballot_w64(sum - sum == 0.f) != 0; ++hh)
 #pragma unroll 1
           for (int i = j; i < S; ++i) {
             const float qv = bf2f(base[(size_t)i * ld + hh * D + lane]), dov = bf2f(dob[(size_t)i * ldo + hh * D + lane]);
             const size_t at = stat_index(cu, T, sv, b, hh, nh, Smax, i);
             const float p = __builtin_amdgcn_exp2f(wave_sum(qv * kv) * c - lse[at] * kLog2e);
-            acc += DK ? p * (wave_sum(dov * vv) - delta[at]) * qv : p * dov;
-            if (__builtin_amdgcn_ballot_w64(acc - acc == 0.f) == 0) break;
+            sum += is_k ? p * (wave_sum(dov * vv) - delta[at]) * qv : p * dov;
+            if (__builtin_amdgcn_ballot_w64(sum - sum == 0.f) == 0) break;
           }
         asm volatile("" ::: "memory");   // after the wave's own wider stores of the row
-        smem[(wave * 32 + r) * pitch(D) + lane] = f2bf(DK ? acc * scale : acc);
+        smem[(wave * 32 + r) * pitch(D) + lane] = f2bf(is_k ? sum * scale : sum);
       }
     }
-  }
-  __syncthreads();
-  copy_out<D, KB, SET * NS>(smem, dqkv, r0, r1, ld, DK ? kcol : vcol, threadIdx.x);
+    copy_rows<D>(smem, dqkv, sv.row0 + jw, S - jw, ld, is_k ? kcol : vcol, wave, lane);
+    asm volatile("" ::: "memory");
+  };
+  if constexpr (DV) store(std::integral_constant<int, 0>{}, std::false_type{});
+  if constexpr (DK) store(std::integral_constant<int, KC>{}, std::true_type{});
 }
 
 
@@ -1019,18 +980,22 @@ bool attn_mfma_supported(const AttnArgs& a) {
   const int64_t ld = (int64_t)(a.nh + 2 * a.nkv) * a.dh;
   if ((int64_t)a.S * ld * 2 >= ((int64_t)1 << 31)) return false;   // 32-bit offsets inside one sequence
   if (((uintptr_t)a.qkv | (uintptr_t)a.out | (uintptr_t)a.dout | (uintptr_t)a.dqkv) & 15) return false;
-  if ((int64_t)((a.S + BQ - 1) / BQ) * a.nh * a.B >= ((int64_t)1 << 31)) return false;   // 1-D grids
+  if ((int64_t)((a.S + 127) / 128) * a.nh * a.B >= ((int64_t)1 << 31)) return false;   // 1-D grids
   return true;
 }
 
 namespace {
-constexpr size_t fwd_smem(int D) { return (size_t)4 * kv_tile(D) * sizeof(bf16_t); }   // 69632 / 36864 B (>= the 128 x pitch output tile)
+template <int D, int KW, int NS>
+constexpr size_t row_smem() {   // of the forward and dQ kernels
+  const size_t st = (size_t)NS * 2 * KvDma<D, KW>::STAGE * sizeof(bf16_t), out = (size_t)KW * 32 * pitch(D) * sizeof(bf16_t);
+  const size_t sums = NS > 1 ? (size_t)(NS / 2) * KW * (D / 32 * 16 + 2) * 64 * sizeof(float) : 0;
+  return std::max({st, out, sums});
+}
 template <int WHICH, int D, int KW, int NS>
 constexpr size_t dkv_smem() {
   const size_t st = (size_t)NS * 2 * DkvStage<dkv_rows<WHICH, NS>(), D>::STAGE * sizeof(bf16_t), out = (size_t)KW * 32 * pitch(D) * sizeof(bf16_t);
-  const size_t sums = NS > 1 ? (size_t)(NS / 2) * KW * (D / 32) * 16 * 64 * sizeof(float) : 0;
-  const size_t m = st > out ? st : out;
-  return m > sums ? m : sums;
+  const size_t sums = NS > 1 ? (size_t)(NS / 2) * KW * (WHICH == 2 ? 2 : 1) * (D / 32) * 16 * 64 * sizeof(float) : 0;
+  return std::max({st, out, sums});
 }
 
 hipError_t set_smem(const void* f, size_t bytes, bool& done) {
@@ -1040,14 +1005,55 @@ hipError_t set_smem(const void* f, size_t bytes, bool& done) {
   return e;
 }
 
-template <int D>
+// Groups in a chunk (see WorkMap), equal chunks.  Forward and dQ: all of an XCD's where they are three rounds of blocks or fewer; of more, as many as
+// have 4 MB of keys and values, the L2 of an XCD, two to eight (64 x 199, 32 / 8 heads, forward, 4 / 8 / 16 / 64 of 64 groups: 57 / 56 / 65 / 71 us; 16 x 2048, 1 / 4 / 16 of
+// 16: 659 / 620 / 651).  dK / dV, which read more per block: sixteen (backward of 32 x 512, 4 / 8 / 16 / 32 of 32: 453 / 448 / 425 / 433).
+int row_chunk(int per_xcd, int nx, int slots, int64_t kv_bytes) {
+  if (per_xcd * (int64_t)nx <= 3 * slots) return std::max(1, per_xcd);
+  const int most = (int)std::min<int64_t>(8, std::max<int64_t>(2, (4 << 20) / kv_bytes)), n = (per_xcd + most - 1) / most;
+  return (per_xcd + n - 1) / n;
+}
+int key_chunk(int per_xcd) {
+  const int n = std::max(1, (per_xcd + 15) / 16);
+  return std::max(1, (per_xcd + n - 1) / n);
+}
+template <int D, int KW, int NS>
+WorkMap row_map(const AttnArgs& a, int waves) {
+  WorkMap map = work_map(row_blocks<KW>(a.S, a.nh / a.nkv), a.nkv, a.B);
+  map.chunk = row_chunk(map.per_xcd, map.nx, 32 * 4 * waves / (KW * NS), (int64_t)a.S * D * 4);
+  return map;
+}
+template <int KW>
+WorkMap key_map(const AttnArgs& a) {
+  WorkMap map = work_map((a.S + KW * 32 - 1) / (KW * 32), a.nkv, a.B);
+  map.chunk = key_chunk(map.per_xcd);
+  return map;
+}
+template <int D, int KW, int NS>
 hipError_t launch_fwd(const AttnArgs& a, hipStream_t s) {
+  constexpr size_t smem = row_smem<D, KW, NS>();
+  static_assert(smem <= 160 * 1024, "LDS of a CU");
   static bool done = false;
-  hipError_t e = set_smem((const void*)attn_fwd_mfma_kernel<D>, fwd_smem(D), done);
+  const hipError_t e = set_smem((const void*)attn_fwd_mfma_kernel<D, KW, NS>, smem, done);
   if (e != hipSuccess) return e;
-  const dim3 grid((unsigned)((int64_t)((a.S + BQ - 1) / BQ) * a.nh * a.B));   // 1-D: the kernel maps blocks to work itself
+  const WorkMap map = row_map<D, KW, NS>(a, row_waves(D, NS));
+  const dim3 grid((unsigned)work_blocks(map));   // 1-D: the kernel maps blocks to work itself
   ProfScope ps("attn_fwd_mfma", 2.0 * a.B * a.nh * D * (double)a.S * (a.S + 1), 0, s);
-  hipLaunchKernelGGL(attn_fwd_mfma_kernel<D>, grid, dim3(256), fwd_smem(D), s, (const bf16_t*)a.qkv, (bf16_t*)a.out, a.lse, a.S, a.nh, a.nkv, a.cu_seqlens, a.total_rows, a.B);
+  hipLaunchKernelGGL((attn_fwd_mfma_kernel<D, KW, NS>), grid, dim3(KW * NS * 64), smem, s, (const bf16_t*)a.qkv, (bf16_t*)a.out, a.lse, a.S, a.nh, a.nkv, a.cu_seqlens, a.total_rows, map);
+  return hipGetLastError();
+}
+
+template <int D, int KW, int NS>
+hipError_t launch_dq(const AttnArgs& a, hipStream_t s) {
+  constexpr size_t smem = row_smem<D, KW, NS>();
+  static_assert(smem <= 160 * 1024, "LDS of a CU");
+  static bool done = false;
+  const hipError_t e = set_smem((const void*)attn_dq_mfma_kernel<D, KW, NS>, smem, done);
+  if (e != hipSuccess) return e;
+  const WorkMap map = row_map<D, KW, NS>(a, dq_waves(D, NS));
+  const dim3 grid((unsigned)work_blocks(map));
+  ProfScope ps("attn_dq_mfma", 3.0 * a.B * a.nh * D * (double)a.S * (a.S + 1), 0, s);   // S, dP and dQ products
+  hipLaunchKernelGGL((attn_dq_mfma_kernel<D, KW, NS>), grid, dim3(KW * NS * 64), smem, s, (const bf16_t*)a.qkv, (const bf16_t*)a.out, (const bf16_t*)a.dout, a.lse, a.delta, (bf16_t*)a.dqkv, a.S, a.nh, a.nkv, a.cu_seqlens, a.total_rows, map);
   return hipGetLastError();
 }
 
@@ -1058,45 +1064,82 @@ hipError_t launch_dkv(const AttnArgs& a, hipStream_t s) {
   static bool done = false;
   const hipError_t e = set_smem((const void*)attn_dkv_mfma_kernel<WHICH, D, KW, NS>, smem, done);
   if (e != hipSuccess) return e;
-  const dim3 grid((unsigned)((int64_t)((a.S + KW * 32 - 1) / (KW * 32)) * a.nkv * a.B));
-  hipLaunchKernelGGL((attn_dkv_mfma_kernel<WHICH, D, KW, NS>), grid, dim3(KW * NS * 64), smem, s, (const bf16_t*)a.qkv, (const bf16_t*)a.dout, a.lse, a.delta, (bf16_t*)a.dqkv, a.S, a.nh, a.nkv, a.cu_seqlens, a.total_rows, a.B);
+  const WorkMap map = key_map<KW>(a);
+  const dim3 grid((unsigned)work_blocks(map));
+  hipLaunchKernelGGL((attn_dkv_mfma_kernel<WHICH, D, KW, NS>), grid, dim3(KW * NS * 64), smem, s, (const bf16_t*)a.qkv, (const bf16_t*)a.dout, a.lse, a.delta, (bf16_t*)a.dqkv, a.S, a.nh, a.nkv, a.cu_seqlens, a.total_rows, map);
   return hipGetLastError();
 }
 
+// Blocks of four items that have rows, and the steps of the longest.  A packed batch holds at most one partly filled item of every head per sequence.
+struct RowWork { int64_t blocks; int steps; };
+RowWork row_work(const AttnArgs& a) {
+  const int64_t per_seq = (a.S + 31) / 32, items = a.cu_seqlens ? std::min<int64_t>(a.total_rows / 32 + a.B, per_seq * a.B) : per_seq * a.B;
+  return RowWork{(items * a.nh + 3) / 4, (int)per_seq};
+}
+// Which form of the forward and dQ kernels: four waves that walk all keys; or, where blocks are few and a block is a long chain of steps,
+// sets of waves that share the steps.  Over 113 shapes (1 .. 64 sequences of 48 .. 7570 positions, five head counts; form that is
+// fastest on each = 0): forward of head size 128 3.4 % lost with one form, 0.2 with these three; of 64 10.1 and 0.9; backward with the dQ form alone
+// changed 4.4 and 0.9, 9.0 and 1.1.  us, four waves / two sets of two / two sets of four: forward of head size 128, 32 / 8 heads 2 x 905 (464 blocks of 29 steps)
+// 28.0 / 31.2 / 28.1, 16 / 4 heads 1 x 2665 (336, 84) 65.9 / 47.5 / 51.8, 16 / 8 heads 1 x 4603 (576, 144) 118.9 / 117.9 / 115.1, 32 / 8 heads 5 x 214 (280, 7) 11.0 / 15.9 / 13.7; of 64,
+// 16 / 8 heads 1 x 526 (68, 17) 13.5 / 9.4 / 12.1, 32 / 8 heads 7 x 641 (1176, 21) 28.1 / 32.6 / 32.5.  Backward, four waves / two sets of two / four sets of two
+// (head size 64): 1 x 727 with 32 / 8 heads (184, 23) 95.2 / 80.9 / 76.6, 6 x 777 with 16 / 4 (600, 25) 104 / 90 / 109.
+template <int D>
+hipError_t launch_fwd_form(const AttnArgs& a, hipStream_t s) {
+  const RowWork w = row_work(a);
+  if (D == 64 ? w.blocks <= 640 && w.steps >= 6 : w.blocks <= 256 && w.steps >= 4) return launch_fwd<D, 2, 2>(a, s);
+  if constexpr (D == 128)
+    if (w.blocks <= 640 && w.steps >= 20) return launch_fwd<D, 4, 2>(a, s);
+  return launch_fwd<D, 4, 1>(a, s);
+}
+template <int D>
+hipError_t launch_dq_form(const AttnArgs& a, hipStream_t s) {
+  const RowWork w = row_work(a);
+  if constexpr (D == 64) {
+    if (w.blocks <= 224 && w.steps >= 4) return launch_dq<D, 2, 4>(a, s);
+    if (w.blocks <= 1024 && w.steps >= 8) return launch_dq<D, 2, 2>(a, s);
+  } else {
+    if (w.blocks <= 1024 && w.steps >= 10) return launch_dq<D, 2, 2>(a, s);
+  }
+  return launch_dq<D, 4, 1>(a, s);
+}
 template <int D>
 hipError_t launch_bwd(const AttnArgs& a, hipStream_t s) {
-  static bool done_q = false;
-  hipError_t e = set_smem((const void*)attn_dq_mfma_kernel<D>, fwd_smem(D), done_q);
+  hipError_t e = launch_dq_form<D>(a, s);
   if (e != hipSuccess) return e;
-  const dim3 gq((unsigned)((int64_t)((a.S + BQ - 1) / BQ) * a.nh * a.B));
   const double pairs = (double)a.B * a.nh * D * (double)a.S * (a.S + 1) / 2.0;  // (query, key, channel) triples
-  {
-    ProfScope ps("attn_dq_mfma", 6.0 * pairs, 0, s);   // S, dP and dQ products
-    hipLaunchKernelGGL(attn_dq_mfma_kernel<D>, gq, dim3(256), fwd_smem(D), s, (const bf16_t*)a.qkv, (const bf16_t*)a.out, (const bf16_t*)a.dout, a.lse, a.delta, (bf16_t*)a.dqkv, a.S, a.nh, a.nkv, a.cu_seqlens, a.total_rows, a.B);
-    e = hipGetLastError();
-    if (e != hipSuccess) return e;
+  // blocks of n keys that have rows: a packed batch holds at most one partly filled block per sequence
+  auto key_blocks = [&](int n) {
+    const int64_t all = (int64_t)((a.S + n - 1) / n) * a.B;
+    return a.nkv * (a.cu_seqlens ? std::min<int64_t>(a.total_rows / n + a.B, all) : all);
+  };
+  const int64_t chain = (int64_t)(a.nh / a.nkv) * ((a.S + 31) / 32);   // the longest: 32-query tiles, heads of the group times sequence
+  if constexpr (D == 64) {
+    // Whole backward, us, blocks of 64 keys with four, two sets and one: 1 x 727 with 32 / 8 heads (96 blocks, chain 92) 74.7 / 92.8 / 128,
+    // 5 x 787 (520, 100) 103 / 113 / 150, 27 x 113 with 16 / 8 (432, 8) 28.0 / 25.0 / 26.4, 12 x 486 with 40 / 8 (768, 80) 118 / 114 / 138,
+    // 61 x 156 (1464, 25) 125 / 105 / 101; a block of 128 keys on four waves is within 3 % of the last where that is the fastest.
+    ProfScope ps("attn_dkv_mfma", 8.0 * pairs, 0, s);   // S, dP, dV and dK products
+    const int64_t blocks = key_blocks(64);
+    if (blocks <= 424 || (blocks <= 544 && chain >= 32)) return launch_dkv<kBothGrads, D, 2, 4>(a, s);
+    if (blocks <= 1000) return launch_dkv<kBothGrads, D, 2, 2>(a, s);
+    return launch_dkv<kBothGrads, D, 2, 1>(a, s);
+  } else {
+    ProfScope ps("attn_dkv_mfma", 10.0 * pairs, 0, s);   // dV pass: S, dV; dK pass: S, dP, dK
+    // Whole backward, us, four sets / four waves, blocks of 128 keys and chain: 32 / 8 heads 2 x 905 (128, 116) 146 / 239, 16 x 181 (256, 24) 71.9 / 75.6,
+    // 16 / 8 heads 18 x 209 (288, 14) 65.7 / 55.9, 1 x 5876 (368, 368) 782 / 925, 11 x 815 (616, 52) 227 / 183, 40 / 8 heads 20 x 149 (320, 25) 85.0 / 89.0, 5 x 1601 (520,
+    // 255) 670 / 671, 7 x 1489 (672, 235) 853 / 733.
+    const int64_t blocks = key_blocks(128);
+    const bool few = blocks <= 128 || (blocks <= 256 && chain >= 18) || (blocks <= 440 && chain >= 64) || (blocks <= 512 && chain >= 256);
+    if (few) {
+      e = launch_dkv<kValueGrad, D, kFewKW, kFewNS>(a, s);
+      return e == hipSuccess ? launch_dkv<kKeyGrad, D, kFewKW, kFewNS>(a, s) : e;
+    }
+    e = launch_dkv<kValueGrad, D, 4, 1>(a, s);
+    return e == hipSuccess ? launch_dkv<kKeyGrad, D, 4, 1>(a, s) : e;
   }
-  ProfScope ps("attn_dkv_mfma", 10.0 * pairs, 0, s);   // dV pass: S, dV; dK pass: S, dP, dK
-  // blocks of 128 keys that have rows: a packed batch holds at most one partly filled block per sequence
-  const int64_t blocks = a.nkv * (a.cu_seqlens ? std::min<int64_t>(a.total_rows / 128 + a.B, (int64_t)((a.S + 127) / 128) * a.B)
-                                               : (int64_t)((a.S + 127) / 128) * a.B);
-  const int64_t chain = (int64_t)(a.nh / a.nkv) * ((a.S + 31) / 32);
-  // Which form of the dK / dV passes: blocks of 128 keys, and the longest chain of 32-query tiles (heads of the group times
-  // sequence).  Whole backward, us, four-wave blocks / four sets, 32 / 8 heads: 2 x 1024 (128 blocks, chain 128) 294 / 158,
-  // 4 x 512 (128, 64) 162 / 97, 4 x 1024 (256, 128) 336 / 279, 8 x 512 (256, 64) 191 / 183, 1 x 8192 (512, 1024) 2706 / 2365,
-  // 8 x 1024 (512, 128) 460 / 476, 16 x 512 (512, 64) 280 / 333, 8 x 2048 (1024, 256) 1408 / 1540; 64 x 117 with 16 / 4
-  // heads of 64 (256, 16) 62 / 66.
-  const bool few = blocks <= 128 || (blocks <= 256 && chain >= 32) || (blocks <= 512 && chain >= 256);
-  if (few) {
-    e = launch_dkv<0, D, kFewKW, kFewNS>(a, s);
-    return e == hipSuccess ? launch_dkv<1, D, kFewKW, kFewNS>(a, s) : e;
-  }
-  e = launch_dkv<0, D, 4, 1>(a, s);
-  return e == hipSuccess ? launch_dkv<1, D, 4, 1>(a, s) : e;
 }
 }  // namespace
 
-hipError_t launch_attn_fwd_mfma(const AttnArgs& a, hipStream_t s) { return a.dh == 64 ? launch_fwd<64>(a, s) : launch_fwd<128>(a, s); }
+hipError_t launch_attn_fwd_mfma(const AttnArgs& a, hipStream_t s) { return a.dh == 64 ? launch_fwd_form<64>(a, s) : launch_fwd_form<128>(a, s); }
 hipError_t launch_attn_bwd_mfma(const AttnArgs& a, hipStream_t s) { return a.dh == 64 ? launch_bwd<64>(a, s) : launch_bwd<128>(a, s); }
 
 }  // namespace tide

@@ -1,0 +1,101 @@
+"""The forms of the bf16 attention kernels: blocks of four waves that walk every key, and sets of waves that share the keys (forward, dQ) or
+the queries (dK / dV) where blocks are few.  Each against fp64 at the edges of its items (32 queries of one head, several heads side by side)
+and of its steps; and one sequence alone against the same sequence as one of many."""
+import pytest
+import torch
+
+from tests.gpu_util import DEV, stream, sync
+from tests.test_gpu_attention_heads import _reference
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def B():
+    from paper_2602_05145_amd import binding
+    return binding
+
+
+def _run(B, qkv, dout, bt, S, nh, nkv, dh):
+    out, dqkv = torch.full_like(dout, float("nan")), torch.full_like(qkv, float("nan"))
+    lse, delta = (torch.full((bt, nh, S), float("nan"), device=DEV) for _ in range(2))
+    print(f"attention forms batch={bt} S={S} heads={nh}/{nkv} dh={dh}", flush=True)
+    B.tide_attention_fwd(bt, S, nh, nkv, dh, qkv, out, lse, 1, stream())
+    sync()
+    B.tide_attention_bwd(bt, S, nh, nkv, dh, qkv, out, dout, lse, delta, dqkv, 1, stream())
+    sync()
+    return out, lse, dqkv
+
+
+# items of a block from several heads and query blocks (groups of 3, 5 and 7 heads), steps that the sets share unevenly, one step fewer than sets
+@pytest.mark.parametrize("dh", [64, 128])
+@pytest.mark.parametrize("bt,S,nh,nkv", [(1, 97, 3, 1), (1, 161, 5, 1), (3, 225, 7, 1), (1, 321, 10, 2), (2, 650, 20, 4), (9, 640, 8, 2), (40, 33, 6, 2), (33, 70, 4, 4)])
+def test_every_form_at_its_edges(B, dh, bt, S, nh, nkv):
+    g = torch.Generator(device=DEV).manual_seed(S + nh + dh)
+    qkv = torch.randn(S, (nh + 2 * nkv) * dh, device=DEV, generator=g).bfloat16()
+    dout = torch.randn(S, nh * dh, device=DEV, generator=g).bfloat16()
+    out, lse, dqkv = _run(B, qkv.repeat(bt, 1), dout.repeat(bt, 1), bt, S, nh, nkv, dh)
+    for x, shape in ((out, (bt, S, -1)), (lse, (bt, nh, S)), (dqkv, (bt, S, -1))):   # every sequence of the batch the same bits
+        assert float((x.view(*shape) - x.view(*shape)[:1]).abs().max()) == 0.0
+    ro, rl, rg = _reference(qkv, dout, S, nh, nkv, dh)
+    w = nh * dh
+    # as in the tests of the tiles' edges: 1 % of the largest value is three times what bf16 outputs and probabilities show
+    assert float((out[:S].double().cpu() - ro).abs().max()) < 1e-2 * float(ro.abs().max())
+    assert float((lse[0].double().cpu() - rl).abs().max()) < 1e-5 * float(rl.abs().max())
+    for part in (slice(0, w), slice(w, w + nkv * dh), slice(w + nkv * dh, None)):
+        assert float((dqkv[:S, part].double().cpu() - rg[:, part]).abs().max()) < 1e-2 * float(rg[:, part].abs().max())
+
+
+@pytest.mark.parametrize("dh", [64, 128])
+def test_sets_and_single_waves_agree(B, dh):
+    """A sequence alone takes the sets, as one of 90 the four-wave blocks: the same results but for the order of the fp32 sums and what the
+    running maximum was when a probability was rounded (one step of bf16, 2^-7 of the largest value, at most)."""
+    S, nh, nkv = 420, 8, 2
+    g = torch.Generator(device=DEV).manual_seed(dh)
+    qkv = torch.randn(S, (nh + 2 * nkv) * dh, device=DEV, generator=g).bfloat16()
+    dout = torch.randn(S, nh * dh, device=DEV, generator=g).bfloat16()
+    one = _run(B, qkv, dout, 1, S, nh, nkv, dh)
+    many = _run(B, qkv.repeat(90, 1), dout.repeat(90, 1), 90, S, nh, nkv, dh)
+    for a, b, n in zip(one, many, (S, 1, S)):
+        a, b = a.double(), b[:n].double()
+        assert float((a - b).abs().max()) < 2.0 ** -7 * float(b.abs().max())
+
+
+def test_later_positions_reach_nothing_before_them_across_sets(B):
+    """As for one set: NaN from position 200 on leave the outputs of the rows before it as they are up to a step of the type, also where
+    the sets' sums are merged (head size 64)."""
+    S, nh, nkv, dh, cut = 333, 4, 2, 64, 200
+    g = torch.Generator(device=DEV).manual_seed(1)
+    qkv = torch.randn(S, (nh + 2 * nkv) * dh, device=DEV, generator=g).bfloat16()
+    dout = torch.randn(S, nh * dh, device=DEV, generator=g).bfloat16()
+    bad = qkv.clone()
+    bad[cut:] = float("nan")
+    bad[cut + 1::2, -7:] = float("inf")
+    clean, got = _run(B, qkv, dout, 1, S, nh, nkv, dh), _run(B, bad, dout, 1, S, nh, nkv, dh)
+    assert bool(torch.isnan(got[0][cut:]).all())
+    for a, b in ((got[0][:cut].float(), clean[0][:cut].float()), (got[2][:cut, :nh * dh].float(), clean[2][:cut, :nh * dh].float())):
+        assert bool(torch.isfinite(a).all()) and bool(((a - b).abs() <= 2.0 ** -7 * b.abs() + 1e-5 * b.abs().max()).all())
+
+
+@pytest.mark.parametrize("dh,nh,nkv", [(64, 10, 2), (128, 6, 2)])
+def test_packed_lengths_in_a_training_step(B, dh, nh, nkv):
+    """Sequences of many lengths, from one row to several items, with groups of five and three heads, against the oracle."""
+    from paper_2602_05145_amd import runtime, workloads as W
+    import numpy as np
+    lens = [1, 31, 32, 33, 95, 250, 64, 7]
+    T = sum(lens)
+    cfg = W.get_config("small", batch=1, seq=T, target_hidden=256, hidden=nh * dh, n_heads=nh, n_kv_heads=nkv, head_dim=dh, ffn=512, vocab=1024, mask="none", seed=5)
+    wl = W.make_workload(cfg)
+    cu = np.concatenate([[0], np.cumsum(lens)]).astype(np.int32)
+    tr = runtime.trainer_from_workload(cfg, wl)
+    tr.set_packed(cu)
+    print(f"packed forms dh={dh}", flush=True)
+    tr.train_step_packed(cfg["lr"])
+    sync()
+    from oracle import tide_oracle as O
+    p0 = {k: np.asarray(v, np.float64) for k, v in wl["params"].items()}
+    loss, grads = O.train_quantities_packed(cfg, p0, wl["hidden"].astype(np.float64), wl["tokens"], wl["mask"], cu)[:2]
+    assert abs(float(tr.loss.item()) - loss) < 1e-2 * abs(loss)
+    for k, ref in grads.items():
+        a, b = tr.host(tr.grads)[k].reshape(-1), ref.reshape(-1)
+        assert a @ b / (np.linalg.norm(a) * np.linalg.norm(b)) > 0.999, k
