@@ -320,8 +320,8 @@ __device__ __forceinline__ void adam_store(const AdamTarget& t, const AdamRate& 
 // ------------------------------------------------------------------------------------------------
 typedef float f32x4_t __attribute__((ext_vector_type(4)));
 
-template <int BM, int BN, bool AMM, bool BNM, typename TO, bool KWHOLE, bool ADAM = false>
-__global__ __launch_bounds__(2 * BN) void gemm_mfma_kernel(std::conditional_t<ADAM, MfmaAdamParams, MfmaParams> p) {
+template <int BM, int BN, bool AMM, bool BNM, typename TO, bool KWHOLE, bool ADAM>
+__device__ __forceinline__ void gemm_block(std::conditional_t<ADAM, MfmaAdamParams, MfmaParams> p, int pid) {   // pid: which of the launch's blocks
   static_assert(BN == 256 ? BM % 32 == 0 && BM >= 128 && BM <= 256 : BN == 128 && BM == 128, "tile edges");
   constexpr int BK = 64, WAVES_M = 2, WAVES_N = BN / 64, NW = WAVES_M * WAVES_N;
   constexpr int WM = BM / WAVES_M, WN = BN / WAVES_N;   // BM / 2 x 64
@@ -356,7 +356,6 @@ __global__ __launch_bounds__(2 * BN) void gemm_mfma_kernel(std::conditional_t<AD
     }
     ntail = nb - full;
     const int items = full + ntail * nparts;
-    int pid = blockIdx.x;
     if (pid >= items) return;
     // Work-groups go to the XCDs round-robin in the order of their index: the whole tiles (a multiple of 256)
     // come first and each XCD gets a contiguous range of them; the parts of the split tiles come last, again
@@ -855,6 +854,25 @@ __global__ __launch_bounds__(2 * BN) void gemm_mfma_kernel(std::conditional_t<AD
     bf16_t* unit = pu == 0 ? ld0 : (pu == 1 ? ld1 : (pu == 2 ? ld2 : ls0));
     epilogue(unit + (wave % PPU) * kPatchElems);
   }
+}
+
+template <int BM, int BN, bool AMM, bool BNM, typename TO, bool KWHOLE, bool ADAM = false>
+__global__ __launch_bounds__(2 * BN) void gemm_mfma_kernel(std::conditional_t<ADAM, MfmaAdamParams, MfmaParams> p) {
+  gemm_block<BM, BN, AMM, BNM, TO, KWHOLE, ADAM>(p, blockIdx.x);
+}
+
+// The weight gradients of a layer with their updates, product after product over the blocks of one launch.  A product of few rows is
+// bound by its weight's 30 bytes per element, and with a launch each its first tiles all multiply while the memory waits, its last ones update
+// while the matrix pipes wait, and partly filled rounds come on top.  Six weights of 0.06 G elements together, us, a launch each / one: over 132
+// rows 429 / 341 (5.3 TB/s of state), over 4096 681 / 612; of 0.27 G elements over 1999 rows 2115 / 1864.
+struct MfmaAdamGroup { MfmaAdamParams p[kMaxGemmGroup]; int first[kMaxGemmGroup + 1]; int n; };   // first block of each, a multiple of 8 (XCDs)
+template <int BM, int BN>
+__global__ __launch_bounds__(2 * BN) void gemm_mfma_adam_group_kernel(MfmaAdamGroup g) {
+  int i = 0;
+#pragma unroll
+  for (int k = 1; k < kMaxGemmGroup; ++k)
+    if (k < g.n && (int)blockIdx.x >= g.first[k]) i = k;
+  gemm_block<BM, BN, true, true, float, false, true>(g.p[i], blockIdx.x - g.first[i]);
 }
 
 // C[tile] += the partial sums of the later parts of every split tile, in the order of the parts (deterministic).
@@ -1370,6 +1388,52 @@ hipError_t launch_gemm_adam(const GemmArgs& a, const AdamTarget& t, hipStream_t 
   const GemmProf ps(a, 26.0 * (double)a.M * (double)a.N, s);
   const hipError_t e = launch_layout<true, true, float>(p, lp, s);
   return e != hipSuccess || p.split != kSplitTail ? e : launch_fixup<true>(p, t, s);
+}
+
+namespace {
+template <int BM, int BN>
+hipError_t launch_adam_group(MfmaAdamGroup& g, hipStream_t s) {
+  g.first[0] = 0;
+  for (int i = 0; i < g.n; ++i) {
+    MfmaAdamParams& p = g.p[i];
+    p.tiles_m = (p.M + BM - 1) / BM;
+    p.tiles_n = (p.N + BN - 1) / BN;
+    g.first[i + 1] = g.first[i] + (p.tiles_m * p.tiles_n + 7) / 8 * 8;
+  }
+  hipLaunchKernelGGL((gemm_mfma_adam_group_kernel<BM, BN>), dim3((unsigned)g.first[g.n]), dim3(2 * BN), 0, s, g);
+  return hipGetLastError();
+}
+}  // namespace
+
+// Whole steps, us, a launch each / one on 160 x 256 / on 256 x 256 tiles (on 128 x 128 and 192 x 256 nowhere better than the best of these by more than
+// the spread): 2048 / 5632 wide, 132 rows 1125 / 1070 / 1085, 700 1455 / 1380 / 1395, 1900 2087 / 1980 / 2010, 3000 2320 / 2249 / 2267, 6000 4320 /
+// 4210 / 4165; 4096 / 14336 wide, 300 rows 5516 / 5451 / 5580, 1000 7466 / 7300 / 7395, 1999 10470 / 10226 / 10355, 3000 13517 / 13212 / 13180,
+// 4200 20020 / 19900 / 19790, 8000 31130 / 31385 / 30970, 32768 102950 / 105100 / 103240: there a launch each finds an operand of the product
+// before still in a cache.
+bool gemm_adam_group_pays(int64_t rows) { return rows <= 8192; }
+
+hipError_t launch_gemm_adam_group(const GemmArgs* a, const AdamTarget* t, int n, hipStream_t s) {
+  if (n < 1 || n > kMaxGemmGroup) return hipErrorInvalidValue;
+  MfmaAdamGroup g;
+  g.n = n;
+  int64_t rows = 0;
+  double flops = 0, bytes = 0, fixed_flops = 0, fixed_bytes = 0;   // fixed: of products whose sizes are all known here, and of the updates
+  const GemmArgs* dyn = nullptr;                                   // (the others of a step share one size on the device)
+  for (int i = 0; i < n; ++i) {
+    if (!gemm_adam_supported(a[i], t[i])) return hipErrorInvalidValue;
+    fill_params(g.p[i], a[i], LaunchPlan{128, 128, kSplitNone, {1, 0, 0}, {0, 0, 0}});
+    g.p[i].adam = t[i];
+    rows = std::max(rows, a[i].K);
+    const double update = 26.0 * (double)a[i].M * (double)a[i].N, f = GemmProf::flops(a[i]), b = GemmProf::bytes(a[i]);
+    flops += f;
+    bytes += b + update;
+    fixed_bytes += update;
+    if (a[i].k_dev) dyn = &a[i];
+    else { fixed_flops += f; fixed_bytes += b; }
+  }
+  ProfScope ps("gemm_mfma_tn_group_adamw", flops, bytes, s);
+  if (dyn) prof_dynamic(dyn->k_dev, dyn->k_off, dyn->K, fixed_flops, fixed_bytes);
+  return rows <= 4096 ? launch_adam_group<160, 256>(g, s) : launch_adam_group<256, 256>(g, s);
 }
 
 hipError_t launch_gemm(const GemmArgs& a, hipStream_t s) {

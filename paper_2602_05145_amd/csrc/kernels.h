@@ -63,6 +63,9 @@ bool gemm_adam_supported(const GemmArgs& a, const AdamTarget& t);
 bool gemm_adam_pays(const GemmArgs& a);                  // faster than the product and a share of the pass over all weights
 hipError_t launch_gemm_adam(const GemmArgs& a, const AdamTarget& t, hipStream_t s);
 constexpr int kMaxGemmGroup = 6;
+// Products with updates (each gemm_adam_supported), all in one launch; whether that beats a launch each over a batch of `rows` rows.
+bool gemm_adam_group_pays(int64_t rows);
+hipError_t launch_gemm_adam_group(const GemmArgs* a, const AdamTarget* t, int n, hipStream_t s);
 hipError_t launch_gemm_group(const GemmArgs* a, int n, hipStream_t s);  // independent products, in one launch where small
 // fp32, both sizes of the MLP's activations at once.  Forward: gate and up products and h = silu(gate) up in one launch; backward:
 // the product of dh, with dgate and dup written over gate and up.  False where the sizes call for separate launches.

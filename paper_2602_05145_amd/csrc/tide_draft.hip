@@ -701,11 +701,23 @@ static int enqueue_backward(const tide_draft_config* cfg, const tide_draft_tenso
     g.accumulate = add;
     return g;
   };
-  // In fp32 mode the weight gradients of the layer wait for each other: nothing overwrites their operands before the end,
-  // and together they are one launch (bf16: at once, while an operand of the product before is still in a cache).
+  // The weight gradients of the layer wait for each other where one launch of all is faster: nothing overwrites their operands
+  // before the end.  fp32: always; bf16: those that update their weights, over a batch that is not too large (otherwise at once, while an
+  // operand of the product before is still in a cache).
   GemmArgs later[kMaxGemmGroup];
+  AdamTarget later_upd[kMaxGemmGroup];
   int n_later = 0;
+  const bool group_updates = dt == TIDE_DTYPE_BF16 && o.upd && gemm_adam_group_pays(T);
   auto run_dw = [&](const GemmArgs& g, int weight) {
+    if (group_updates && n_later < kMaxGemmGroup) {
+      const AdamTarget t = target(*o.upd, weight, 0);
+      if (gemm_adam_pays(g) && gemm_adam_supported(g, t)) {
+        o.upd->done |= 1u << weight;
+        later[n_later] = g;
+        later_upd[n_later++] = t;
+        return hipSuccess;
+      }
+    }
     if (dt != TIDE_DTYPE_FP32 || n_later == kMaxGemmGroup) return run_dw_update(g, o.upd, weight, 0, true, ws, p, s);
     later[n_later++] = g;
     return hipSuccess;
@@ -788,7 +800,8 @@ static int enqueue_backward(const tide_draft_config* cfg, const tide_draft_tenso
                                 (const int32_t*)(o.prev_ws + p.kept_idx), (const int*)(o.prev_ws + p.cnt), (int32_t*)(o.prev_ws + p.tokens_c),
                                 (uint8_t*)(o.prev_ws + p.mask_c), dt, s), "gather feature gradient");
   }
-  if (n_later) TIDE_HIP(run_gemms(later, n_later, ws, p, s), "gemm weight gradients");
+  if (n_later && dt == TIDE_DTYPE_BF16) TIDE_HIP(launch_gemm_adam_group(later, later_upd, n_later, s), "gemm weight gradients");
+  else if (n_later) TIDE_HIP(run_gemms(later, n_later, ws, p, s), "gemm weight gradients");
   return TIDE_OK;
 }
 

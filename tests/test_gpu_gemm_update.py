@@ -19,6 +19,8 @@ launch = ig._symbol("_ZN4tide16launch_gemm_adamERKNS_8GemmArgsERKNS_10AdamTarget
                     [C.POINTER(ig.GemmArgs), C.POINTER(AdamTarget), C.c_void_p])
 pays = ig._symbol("_ZN4tide14gemm_adam_paysERKNS_8GemmArgsE", C.c_bool, [C.POINTER(ig.GemmArgs)])
 name = ig._symbol("_ZN4tide21gemm_adam_kernel_nameERKNS_8GemmArgsE", C.c_char_p, [C.POINTER(ig.GemmArgs)])
+launch_group = ig._symbol("_ZN4tide22launch_gemm_adam_groupEPKNS_8GemmArgsEPKNS_10AdamTargetEiP12ihipStream_t", C.c_int,
+                          [C.POINTER(ig.GemmArgs), C.POINTER(AdamTarget), C.c_int, C.c_void_p])
 RATE = dict(lr=1e-3, decay=1 - 1e-5, beta1=0.9, beta2=0.999, eps=1e-8, c1=1 / (1 - 0.9 ** 3), c2=(1 - 0.999 ** 3) ** -0.5)
 
 
@@ -104,6 +106,51 @@ def test_gradient_and_update(M, N, K, rows, add, ld, kernel, split):
     assert bool(((v.double() - v1).abs() <= eps * (v0 + gd * gd)).all())
     assert bool(((master.double() - th1).abs() <= eps * (th0.abs() + 4 * u.abs() + 4 * RATE["lr"] * RATE["c1"] * (m0.abs() + gd.abs()) / (v1.sqrt() * RATE["c2"] + 1e-8))).all())
     assert torch.equal(w, master.bfloat16())
+
+
+def test_a_group_takes_products_that_it_can_update_alone():
+    ok, bad = ig.args(ig.TN, 264, 136, 77, out=ig.F32), ig.args(ig.NT, 264, 136, 64, out=ig.F32)
+    t = AdamTarget(m=256, v=256, master=256, w=256)
+    for gs in ((), (ok, bad), (ok,) * 7):
+        assert launch_group((ig.GemmArgs * 7)(*gs), (AdamTarget * 7)(*[t] * len(gs)), len(gs), None) != 0
+
+
+# (M, N, old values, rows of the batch rather than all) of each product; upper bound of the rows (4096 is where the tiles change), rows on the device
+GROUPS = [([(264, 136, 0, 0)], 77, 70), ([(8, 8, 0, 1), (1288, 1544, 1, 0), (160, 256, 0, 1), (168, 264, 0, 1), (2056, 520, 0, 0), (320, 512, 1, 1)], 65, 0),
+          ([(8, 8, 0, 1), (1288, 1544, 1, 0), (160, 256, 0, 1), (168, 264, 0, 1), (2056, 520, 0, 0), (320, 512, 1, 1)], 4096, 3001),
+          ([(8, 8, 0, 1), (1288, 1544, 1, 0), (256, 256, 0, 1), (264, 264, 0, 1), (2056, 520, 0, 0), (512, 512, 1, 1)], 4097, 4001)]
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("shapes,K,rows", GROUPS)
+def test_a_group_gives_what_a_launch_each_gives(shapes, K, rows):
+    """Bit for bit: an element's sum runs over the rows in the same order on every tile."""
+    g = torch.Generator(device="cuda").manual_seed(K + rows)
+    dev = dict(device="cuda")
+    cnt = torch.tensor([rows], dtype=torch.int32, **dev)
+    group, single = [], []
+    stream = torch.cuda.current_stream().cuda_stream
+    for M, N, add, trimmed in shapes:
+        a, b = torch.randn(K, M, generator=g, **dev).bfloat16(), (torch.randn(K, N, generator=g, **dev) * 0.1).bfloat16()
+        grad, m, v, master = (torch.randn(M, N, generator=g, **dev) * s for s in (1.0, 0.1, 1.0, 0.02))
+        state = [grad, m, v.square() * 1e-2, master, master.bfloat16()]
+        for out in (group, single):
+            out.append([x.clone() for x in state] + [a, b])
+    def arguments(state, shape):
+        M, N, add, trimmed = shape
+        grad, m, v, master, w, a, b = (x.data_ptr() for x in state)
+        p = ig.args(ig.TN, M, N, K, out=ig.F32, a=a, b=b, c=grad, alpha=-0.5, accumulate=add)
+        if trimmed:
+            p.k_dev = cnt.data_ptr()
+        return p, AdamTarget(m=m, v=v, master=master, w=w, **RATE)
+    print("group", len(shapes), K, rows, flush=True)
+    for state, shape in zip(single, shapes):
+        assert launch(*arguments(state, shape), stream) == 0
+    gs, ts = zip(*(arguments(state, shape) for state, shape in zip(group, shapes)))
+    assert launch_group((ig.GemmArgs * len(gs))(*gs), (AdamTarget * len(ts))(*ts), len(gs), stream) == 0
+    torch.cuda.synchronize()
+    for x, y, shape in zip(group, single, shapes):
+        assert all(torch.equal(p, q) for p, q in zip(x, y)), shape
 
 
 @pytest.mark.gpu
