@@ -19,13 +19,10 @@
 // (see row_item); K/V streamed in steps of 32 keys, double buffered in LDS.  What bounds a full chip is the sum of the matrix and
 // vector work of a SIMD's two or three waves (16 x 2048, 32 / 8 heads: forward 47 and 63 % of the cycles, the clock at 1.8 GHz under the power limit), so registers are
 // kept for three waves in the forward: with steps of 64 keys and two waves, whose MFMAs and exponentials were interleaved by hand, it took 727 us, so 620.
-// dK/dV: one block = 128 keys of one kv
-// head (4 waves x 32 keys, K [and V] in registers), Q/dO streamed in tiles of 32 (dV pass) or 64 (dK pass)
-// queries for each of the G query heads of the group, so dK/dV are summed over the group in registers: no
-// atomics, deterministic.  At head size 128 dV and dK are two launches of one template: a fused pass needs 350 registers (K, V
-// fragments and two 32x128 accumulators), i.e. one block per CU with nothing to hide the exponentials behind;
-// the two halves need 168 and 229, run 3 and 2 blocks per CU, and together take 0.7x the fused time although
-// S = Q K^T is computed twice.  At head size 64 (199 registers) one launch makes both.
+// dK/dV: the keys of a block stay in registers, Q/dO are streamed in tiles of 32 queries for each of the G query heads of the group, so
+// dK/dV are summed over the group in registers: no atomics, deterministic.  At head size 64 (199 registers) a wave makes both.  At head size 128
+// that takes 350 registers, so two waves share 32 keys, one for S, P and dV, one for dP, dS and dK, and P goes through LDS (168 registers, three
+// waves per SIMD); the two passes that this replaces, one per gradient, made S and its exponentials twice.
 // Where blocks are few, sets of waves share the keys (forward, dQ) or the query tiles (dK / dV): see launch_fwd_form, launch_bwd.
 // Every streamed tile reaches LDS by LDS-DMA loads (no staging registers); operand fragments are read from LDS
 // through small register rings, a few MFMAs ahead of their use.
@@ -246,12 +243,6 @@ __device__ __forceinline__ float row_max(float x) {
 // kernel, i.e. 4 and 3 blocks per CU.  Against the one-wave-per-row kernels (attention_simple.hip) that
 // served this head size: 6 x 777, 16 / 4 heads, forward + backward 17.55 -> 0.097 ms.
 constexpr int blocks_per_cu(int D, int at64, int at128) { return D == 64 ? at64 : at128; }
-// Depth of the operand-fragment rings of the dK / dV passes.  Measured when the tiles were still staged through registers,
-// backward at 16 x 2048 / 2 x 16384: 4: 3.48 / 21.0 ms; 2: 3.60 / 21.2; none 3.65 / 21.6.  With LDS-DMA tile loads depths of 2 to 6
-// measure the same.
-#ifndef TIDE_ATTN_DKV_RING
-#define TIDE_ATTN_DKV_RING 4
-#endif
 // Waves that a SIMD has to hold at least, and depth of the operand rings, in the forward and dQ kernels (NS: sets of waves per block).
 constexpr int row_waves(int D, int NS) { return blocks_per_cu(D, 4, NS == 1 ? 3 : 2); }
 constexpr int dq_waves(int D, int NS) { return NS == 1 ? blocks_per_cu(D, 3, 2) : 2; }
@@ -713,43 +704,26 @@ __global__ __launch_bounds__(KW * NS * 64, dq_waves(D, NS)) void attn_dq_mfma_ke
 // backward, dK and dV
 // ------------------------------------------------------------------------------------------------
 namespace {
-// Query rows per streamed tile (32 or 64: two halves of 32 between two barriers) of the dV and of the dK pass.
-// Measured at head size 128, backward at 16 x 2048 / 2 x 16384 (dV rows / dK rows): 32 / 32: 3.18 / 18.2 ms; 32 / 64: 3.08 / 18.0;
-// 64 / 32: 3.14 / 18.7; 64 / 64: 3.09 / 18.5 (with 64 rows the dV pass loses its third block per CU to the LDS).
-#ifndef TIDE_ATTN_DV_ROWS
-#define TIDE_ATTN_DV_ROWS 32
-#endif
-#ifndef TIDE_ATTN_DK_ROWS
-#define TIDE_ATTN_DK_ROWS 64
-#endif
-// (with several sets of waves per block, 32 in both passes: the sets' stages have to fit the LDS)
-enum : int { kValueGrad = 0, kKeyGrad = 1, kBothGrads = 2 };   // what a launch makes
-template <int WHICH, int NS>
-constexpr int dkv_rows() { return WHICH == kKeyGrad && NS == 1 ? TIDE_ATTN_DK_ROWS : TIDE_ATTN_DV_ROWS; }
-constexpr int dkv_waves(int WHICH, int NS) { return NS > 1 ? 1 : WHICH == kValueGrad ? 3 : 2; }
-template <int BI, int D> struct DkvStage {
+template <int D> struct DkvStage {
+  static constexpr int BI = 32;                              // queries per streamed tile
   static constexpr int Q_TILE = TileDma<BI, D>::CHUNKS * 512;   // elements: the tile rounded up to whole 1 KiB chunks of the LDS-DMA loads
   static constexpr int STAGE = 2 * Q_TILE + 4 * BI;          // Q tile, dO tile, then BI floats from lse and BI from delta, see sstore
 };
+// LDS of a set of the pair kernel, elements: two stages, then 4 KB of probabilities per pair
+template <int KW> constexpr int pair_set() { return 2 * DkvStage<128>::STAGE + KW * 2048; }
 }  // namespace
 
-// Two forms of a block.  KW = 4, NS = 1: 128 keys on four waves, every wave walks all query tiles; two or three blocks
-// share a CU and hide each other's waits.  With few blocks (a handful of sequences) there is nobody to share with, and the
-// pass takes as long as the longest chain of query tiles, G heads times the sequence: KW = 2, NS = 4 has 64 keys on two
-// waves, four such sets, each with LDS stages of its own, take every fourth query tile, and the sets' sums are added through
-// LDS at the end, in a fixed order.
-constexpr int kFewKW = 2, kFewNS = 4;
-// At head size 128 one gradient per pass.  Half the accumulators and, for dV, half the operand
-// registers of the fused kernel: the pass fits 256 VGPRs, two blocks share a CU, and one block's
-// exponentials overlap the other's MFMAs.  The price is that S = Q K^T is computed in both passes.  At head size 64 both in
-// one (6 x 777, 16 / 4 heads: 34 + 41 us in two launches, 46 in one).  The score products begin from - lse and - delta, which their
-// rows' accumulators read from LDS (16 to 32 vector instructions fewer per 32 x 32 scores than zeros and two subtractions), and
-// the walk over tiles and heads is a counter (a division by G per tile was 100 scalar instructions): 16 x 2048, 32 / 8 heads of 128: 688 + 923 -> 649 + 900 us.
-template <int WHICH, int D, int KW, int NS>
-__global__ __launch_bounds__(KW * NS * 64, dkv_waves(WHICH, NS)) void attn_dkv_mfma_kernel(const bf16_t* __restrict__ qkv, const bf16_t* __restrict__ dout,
+// Head size 64.  KW waves of 32 keys; NS sets of them, each with LDS stages of its own, take every NS-th query tile, and the sets' sums are added
+// through LDS at the end, in a fixed order: with few blocks there is nobody to share a CU with, and the kernel takes as long as the longest
+// chain of query tiles, G heads times the sequence.  dK and dV in two launches: 6 x 777, 34 + 41 us, in one 46.  The score products begin from - lse and
+// - delta, which their rows' accumulators read from LDS (16 to 32 vector instructions fewer per 32 x 32 scores than zeros and two
+// subtractions), and the walk over tiles and heads is a counter (a division by G per tile was 100 scalar instructions).
+template <int KW, int NS>
+__global__ __launch_bounds__(KW * NS * 64, NS > 1 ? 1 : 2) void attn_dkv_mfma_kernel(const bf16_t* __restrict__ qkv, const bf16_t* __restrict__ dout,
                                                             const float* __restrict__ lse, const float* __restrict__ delta,
                                                             bf16_t* __restrict__ dqkv, int Smax, int nh, int nkv,
                                                             const int* __restrict__ cu, int64_t T, WorkMap map) {
+  constexpr int D = 64;
   extern __shared__ __attribute__((aligned(16))) bf16_t smem[];
   constexpr int KB = KW * 32, SET = KW * 64;   // keys of the block, threads of a set
   const int set = NS > 1 ? __builtin_amdgcn_readfirstlane(threadIdx.x / SET) : 0;
@@ -769,18 +743,16 @@ __global__ __launch_bounds__(KW * NS * 64, dkv_waves(WHICH, NS)) void attn_dkv_m
   const float scale = 1.0f / sqrtf((float)D);
   const float c = kLog2e * scale;
 
-  constexpr bool DV = WHICH != kKeyGrad, DK = WHICH != kValueGrad, BOTH = DV && DK;
-  constexpr int BI = dkv_rows<WHICH, NS>();
-  constexpr int NK = D / 16, NC = D / 32;
-  constexpr int Q_TILE = DkvStage<BI, D>::Q_TILE, DKV_STAGE = DkvStage<BI, D>::STAGE;
-  u32x4_t kf[NK], vf[DK ? NK : 1];
+  constexpr int BI = DkvStage<D>::BI, NK = D / 16, NC = D / 32;
+  constexpr int Q_TILE = DkvStage<D>::Q_TILE, DKV_STAGE = DkvStage<D>::STAGE;
+  u32x4_t kf[NK], vf[NK];
 #pragma unroll
   for (int kk = 0; kk < NK; ++kk) {
     kf[kk] = __builtin_bit_cast(u32x4_t, __builtin_amdgcn_raw_buffer_load_b128(rs, ((uint32_t)jk * (uint32_t)ld + (uint32_t)(kcol + kk * 16 + g * 8)) * 2u, 0, 0));
-    if constexpr (DK) vf[kk] = __builtin_bit_cast(u32x4_t, __builtin_amdgcn_raw_buffer_load_b128(rs, ((uint32_t)jk * (uint32_t)ld + (uint32_t)(vcol + kk * 16 + g * 8)) * 2u, 0, 0));
+    vf[kk] = __builtin_bit_cast(u32x4_t, __builtin_amdgcn_raw_buffer_load_b128(rs, ((uint32_t)jk * (uint32_t)ld + (uint32_t)(vcol + kk * 16 + g * 8)) * 2u, 0, 0));
   }
-  constexpr int NA = BOTH ? 2 * NC : NC, KC = BOTH ? NC : 0;   // accumulators; where those of dK begin
-  f32x16_t dacc[NA];   // dV and / or dK of this wave's 32 keys
+  constexpr int NA = 2 * NC;
+  f32x16_t dacc[NA];   // dV and dK of this wave's 32 keys
 #pragma unroll
   for (int ct = 0; ct < NA; ++ct)
 #pragma unroll
@@ -840,53 +812,39 @@ __global__ __launch_bounds__(KW * NS * 64, dkv_waves(WHICH, NS)) void attn_dkv_m
   // (the sets' trip counts differ by one at most: every set passes every barrier)
   for (int r = 0; r * NS < ntiles; ++r) {
     const int st = r & 1, u = r * NS + set;
-    const int it0 = NS == 1 || u < ntiles ? at.i0 : S;   // past the end: no half of the tile is entered
+    const int i0 = NS == 1 || u < ntiles ? at.i0 : S;   // past the end: not entered
     if (u + NS < ntiles) {
       advance(at, NS);
       gload(at, st ^ 1);
     }
-#pragma unroll
-    for (int hf = 0; hf < BI / 32; ++hf) {
-    const int i0 = it0 + hf * 32;   // this half's first query
-    if (i0 + 31 >= jw && i0 < S) {  // wave-uniform: some query of the half sees some key of this wave
+    if (i0 + 31 >= jw && i0 < S) {  // wave-uniform: some query of the tile sees some key of this wave
       const bf16_t* Qt = stages + st * DKV_STAGE;
       const bf16_t* dOt = Qt + Q_TILE;
-      const float* stats = reinterpret_cast<const float*>(Qt + 2 * Q_TILE) + hf * 32;
+      const float* stats = reinterpret_cast<const float*>(Qt + 2 * Q_TILE);
       f32x16_t s, dp;
 #pragma unroll
       for (int qq = 0; qq < 4; ++qq) {   // row 8 qq + 4 g + e is register 4 qq + e
-        const float4 l4 = *reinterpret_cast<const float4*>(stats + 8 * qq + 4 * g);
+        const float4 l4 = *reinterpret_cast<const float4*>(stats + 8 * qq + 4 * g), d4 = *reinterpret_cast<const float4*>(stats + BI + 8 * qq + 4 * g);
         s[4 * qq] = l4.x; s[4 * qq + 1] = l4.y; s[4 * qq + 2] = l4.z; s[4 * qq + 3] = l4.w;
-        if constexpr (DK) {
-          const float4 d4 = *reinterpret_cast<const float4*>(stats + BI + 8 * qq + 4 * g);
-          dp[4 * qq] = d4.x; dp[4 * qq + 1] = d4.y; dp[4 * qq + 2] = d4.z; dp[4 * qq + 3] = d4.w;
-        }
+        dp[4 * qq] = d4.x; dp[4 * qq + 1] = d4.y; dp[4 * qq + 2] = d4.z; dp[4 * qq + 3] = d4.w;
       }
       {
-        // Q (and, in the dK pass, dO) fragments through a ring, each requested TIDE_ATTN_DKV_RING MFMAs ahead
-        constexpr int RING = TIDE_ATTN_DKV_RING, NF = DK ? 2 * NK : NK;
+        // Q and dO fragments alternately through a ring, each requested RING MFMAs ahead (depths of 2 to 6 measure the same)
+        constexpr int RING = 4, NF = 2 * NK;
         u32x4_t fb[RING];
-        auto fetch = [&](int i) {
-          if constexpr (DK) return frag<D>((i & 1) ? dOt : Qt, hf * 32, plr, (i >> 1) * 16 + g * 8);
-          else return frag<D>(Qt, hf * 32, plr, i * 16 + g * 8);
-        };
+        auto fetch = [&](int i) { return frag<D>((i & 1) ? dOt : Qt, 0, plr, (i >> 1) * 16 + g * 8); };
 #pragma unroll
         for (int i = 0; i < RING; ++i) fb[i] = fetch(i);
 #pragma unroll
         for (int i = 0; i < NF; ++i) {
-          if constexpr (DK) {
-            if (i & 1) dp = mfma(fb[i % RING], vf[i >> 1], dp);
-            else s = mfma(fb[i % RING], kf[i >> 1], s);
-          } else {
-            s = mfma(fb[i % RING], kf[i], s);
-          }
+          if (i & 1) dp = mfma(fb[i % RING], vf[i >> 1], dp);
+          else s = mfma(fb[i % RING], kf[i >> 1], s);
           if (i + RING < NF) fb[i % RING] = fetch(i + RING);
           __builtin_amdgcn_sched_barrier(0);
         }
       }
       // Rows past the end of the sequence carry lse = +inf (see sstore), i.e. p = 0 without a test; the causal test is
-      // per element, and only a half that touches the diagonal makes it (wave-uniform branch).
-      const bool diag = i0 < jw + 32;  // some (query, key) pair of the half is above the diagonal
+      // per element, and only a tile that touches the diagonal makes it (wave-uniform branch).
       auto probs = [&](auto MASK) {
 #pragma unroll
         for (int q = 0; q < 16; ++q) {
@@ -894,13 +852,12 @@ __global__ __launch_bounds__(KW * NS * 64, dkv_waves(WHICH, NS)) void attn_dkv_m
           if constexpr (decltype(MASK)::value) {
             if (i0 + acc_row(q, g) < jk) p = 0.f;
           }
-          s[q] = p;                           // P for dV
-          if constexpr (DK) dp[q] = p * dp[q];   // dS for dK
+          s[q] = p;            // P for dV
+          dp[q] = p * dp[q];   // dS for dK
         }
       };
-      if (diag) probs(std::true_type{});
+      if (i0 < jw + 32) probs(std::true_type{});   // some (query, key) pair of the tile is above the diagonal
       else probs(std::false_type{});
-      matrix_phase<D>(true);
       // dV += P^T dO, dK += dS^T Q
       auto product = [&](const f32x16_t& x, const bf16_t* Xt, int c0) {
         u32x4_t pf[2][parts(D)];
@@ -909,12 +866,10 @@ __global__ __launch_bounds__(KW * NS * 64, dkv_waves(WHICH, NS)) void attn_dkv_m
 #pragma unroll
         for (int ct = 0; ct < NC; ++ct)
 #pragma unroll
-          for (int ks = 0; ks < 2; ++ks) dacc[c0 + ct] = mfma_parts(frag_tr<D>(Xt, hf * 32 + ks * 16, ct * 32, lane), pf[ks], dacc[c0 + ct]);
+          for (int ks = 0; ks < 2; ++ks) dacc[c0 + ct] = mfma_parts(frag_tr<D>(Xt, ks * 16, ct * 32, lane), pf[ks], dacc[c0 + ct]);
       };
-      if constexpr (DV) product(s, dOt, 0);
-      if constexpr (DK) product(dp, Qt, KC);
-      matrix_phase<D>(false);
-    }
+      product(s, dOt, 0);
+      product(dp, Qt, NC);
     }
     if (u + NS < ntiles) sstore(st ^ 1);
     TIDE_ATTN_WAIT_DMA();
@@ -930,7 +885,7 @@ __global__ __launch_bounds__(KW * NS * 64, dkv_waves(WHICH, NS)) void attn_dkv_m
     constexpr bool is_k = decltype(ISK)::value;
     f32x16_t (&acc)[NC] = *reinterpret_cast<f32x16_t (*)[NC]>(&dacc[c0]);
     stage_out<D>(smem, acc, is_k ? scale : 1.0f, wave, lane);
-    if constexpr (D == 64) {
+    {
       // As in the forward kernel, from the other side: the queries jw .. j - 1 meet key j with weight zero.  Keys after the
       // first of them that is not finite are made again from the queries that see them alone (a later query takes every
       // key before it with it, rightly).
@@ -968,10 +923,181 @@ __global__ __launch_bounds__(KW * NS * 64, dkv_waves(WHICH, NS)) void attn_dkv_m
     copy_rows<D>(smem, dqkv, sv.row0 + jw, S - jw, ld, is_k ? kcol : vcol, wave, lane);
     asm volatile("" ::: "memory");
   };
-  if constexpr (DV) store(std::integral_constant<int, 0>{}, std::false_type{});
-  if constexpr (DK) store(std::integral_constant<int, KC>{}, std::true_type{});
+  store(std::integral_constant<int, 0>{}, std::false_type{});
+  store(std::integral_constant<int, NC>{}, std::true_type{});
 }
 
+
+// Head size 128.  Two waves share 32 keys: the value wave makes S = Q K^T, the probabilities and dV += P^T dO, the key wave dP = dO V^T, dS = P (dP - delta)
+// and dK += dS^T Q.  P goes from one to the other through LDS in fp32, 16 registers per lane in the layout that both products have.  KW pairs
+// and NS sets as above.  Against a launch per gradient (16 and 24 MFMAs per 32 x 32 scores, S and its exponentials in both), forward and
+// backward, us: 16 x 2048, 32 / 8 heads 2818 -> 2573; 5 x 1601, 40 / 8 832 -> 663; 42 x 190, 16 / 8 113 -> 92; 1 x 500, 32 / 8 88 -> 65; eighteen shapes 1.22 times as fast in the mean.
+// What bounds it at 16 x 2048 (matrix pipes 48 % busy at 1.9 GHz): 2561 us are 2246 without its tile loads, 2522 without the exponentials, 2483
+// without the exchange of P.  128 keys per block (8 waves, one block per CU) halve the loads, but nobody is there at its two barriers: 2674 for 2582.
+template <int KW, int NS>
+__global__ __launch_bounds__(KW * NS * 128, NS == 1 ? 3 : 2) void attn_dkv_pair_kernel(const bf16_t* __restrict__ qkv, const bf16_t* __restrict__ dout,
+                                                            const float* __restrict__ lse, const float* __restrict__ delta,
+                                                            bf16_t* __restrict__ dqkv, int Smax, int nh, int nkv,
+                                                            const int* __restrict__ cu, int64_t T, WorkMap map) {
+  constexpr int D = 128, BI = DkvStage<D>::BI, NW = 2 * KW, NK = D / 16, NC = D / 32;   // NW: waves of a set
+  constexpr int TILE = DkvStage<D>::Q_TILE, STAGE = DkvStage<D>::STAGE;
+  static_assert(KW == 1 || KW == 2, "one or two key waves share the loads");
+  extern __shared__ __attribute__((aligned(16))) bf16_t smem[];
+  const int wave_all = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), set = NS > 1 ? wave_all / NW : 0, wave_s = wave_all - set * NW;
+  const int lane = threadIdx.x & 63, lr = lane & 31, g = lane >> 5, plr = perm(lr);
+  const bool is_k = wave_s >= KW;   // which wave of its pair
+  const int pair = is_k ? wave_s - KW : wave_s;
+  const Work3 wk = work_item(map);
+  if (!wk.on) return;
+  const int kh = wk.y, b = wk.z, j0 = wk.x * KW * 32, jw = j0 + pair * 32, jk = jw + lr;   // early key blocks are the heavy ones
+  const SeqView sv = seq_view(cu, b, Smax, T);
+  const int S = sv.len, G = nh / nkv;
+  const int ld = (nh + 2 * nkv) * D, ldo = nh * D;
+  if (j0 >= S) return;   // the whole block, before any barrier
+  const bf16_t *seq = qkv + (size_t)sv.row0 * ld, *seq_do = dout + (size_t)sv.row0 * ldo;
+  const uint32_t seq_bytes = (uint32_t)((size_t)S * ld * 2), seq_do_bytes = (uint32_t)((size_t)S * ldo * 2);
+  const __amdgpu_buffer_rsrc_t rs = rsrc(seq, seq_bytes);
+  const int col = (is_k ? nh + nkv + kh : nh + kh) * D;   // of what the wave holds: the key wave V, the value wave K
+  const float scale = 1.0f / sqrtf((float)D);
+  const float c = kLog2e * scale;
+
+  u32x4_t f[NK];
+#pragma unroll
+  for (int kk = 0; kk < NK; ++kk)
+    f[kk] = __builtin_bit_cast(u32x4_t, __builtin_amdgcn_raw_buffer_load_b128(rs, ((uint32_t)jk * (uint32_t)ld + (uint32_t)(col + kk * 16 + g * 8)) * 2u, 0, 0));
+  f32x16_t dacc[NC];   // dV or dK of the pair's 32 keys
+#pragma unroll
+  for (int ct = 0; ct < NC; ++ct)
+#pragma unroll
+    for (int q = 0; q < 16; ++q) dacc[ct][q] = 0.f;
+
+  // tiles from the end of the sequence down, over the G heads, as at head size 64
+  const int nit = (S - j0 + BI - 1) / BI, ntiles = G * nit;   // (j0 is a multiple of BI)
+  bf16_t* stages = smem + set * pair_set<KW>();
+  float4* probs = reinterpret_cast<float4*>(stages + 2 * STAGE) + pair * 256 + lane;
+  struct Place { int hg, i0; };
+  Place at = {0, j0 + (nit - 1) * BI};
+  auto advance = [&](int n) {
+    at.hg += n;
+    while (at.hg >= G) { at.hg -= G; at.i0 -= BI; }
+  };
+  // The key waves load: they have nothing to do while the value waves make the probabilities.  Of two, the first the Q tile, the second the dO tile.
+  const bool load_q = KW == 1 || pair == 0, load_do = KW == 1 || pair == 1;
+  TileDma<BI, D, 1> dma[3 - KW];
+  if constexpr (KW == 1) {
+    dma[0].init(ld, 0, lane);
+    dma[1].init(ldo, 0, lane);
+  } else {
+    dma[0].init(load_q ? ld : ldo, 0, lane);
+  }
+  const float to_scores = -sqrtf((float)D);
+  float stat = 0.f;   // of the key wave that loads Q: lanes below BI carry lse, the others delta
+  auto gload = [&](int st) {   // the tile at `at` into stage st, whose last readers have passed a barrier
+    if (!is_k) return;
+    const int hh = kh * G + at.hg;
+    bf16_t* base = stages + st * STAGE;
+    if (load_q) {
+      dma[0].issue(seq, seq_bytes, base, ((uint32_t)at.i0 * (uint32_t)ld + (uint32_t)(hh * D)) * 2u, 0);
+      const int i = at.i0 + (lane & (BI - 1));
+      const float* src = lane < BI ? lse : delta;   // (used in sstore only; a row past the sequence gets lse = +inf, delta = 0)
+      stat = i < S ? src[stat_index(cu, T, sv, b, hh, nh, Smax, i)] : lane < BI ? INFINITY : 0.f;
+    }
+    if (load_do) dma[2 - KW].issue(seq_do, seq_do_bytes, base + TILE, ((uint32_t)at.i0 * (uint32_t)ldo + (uint32_t)(hh * D)) * 2u, 0);
+  };
+  auto sstore = [&](int st) {   // what the score products begin from, as at head size 64
+    if (is_k && load_q) reinterpret_cast<float*>(stages + st * STAGE + 2 * TILE)[lane] = stat * (lane < BI ? to_scores : -1.f);
+  };
+  if (NS == 1 || set < ntiles) {   // (one set: there is always a tile)
+    advance(set);
+    gload(0);
+    sstore(0);
+  }
+  __builtin_amdgcn_s_waitcnt(0x0F70);   // vmcnt(0): the tile and the fragments have arrived before the loop
+  __syncthreads();
+  constexpr int RING = 4, NX = 2 * NC;
+  // (the sets' trip counts differ by one at most: every wave passes every barrier)
+  for (int r = 0; r * NS < ntiles; ++r) {
+    const int st = r & 1, u = r * NS + set;
+    const int i0 = NS == 1 || u < ntiles ? at.i0 : S;
+    const bool live = i0 + 31 >= jw && i0 < S;   // wave-uniform, the same for both waves of a pair: some query of the tile sees some key of theirs
+    const bf16_t *Qt = stages + st * STAGE, *dOt = Qt + TILE;
+    const bf16_t *Xt = is_k ? dOt : Qt, *Yt = is_k ? Qt : dOt;   // rows of the first product, columns of the second
+    f32x16_t s;
+    u32x4_t xb[RING];
+    auto y_frag = [&](int i) { return frag_tr<D>(Yt, (i / NC) * 16, (i % NC) * 32, lane); };   // k16 step i / NC, columns i % NC
+    if (live) {
+      const float* stats = reinterpret_cast<const float*>(Qt + 2 * TILE) + (is_k ? BI : 0);
+#pragma unroll
+      for (int qq = 0; qq < 4; ++qq) {   // row 8 qq + 4 g + e is register 4 qq + e
+        const float4 l4 = *reinterpret_cast<const float4*>(stats + 8 * qq + 4 * g);
+        s[4 * qq] = l4.x; s[4 * qq + 1] = l4.y; s[4 * qq + 2] = l4.z; s[4 * qq + 3] = l4.w;
+      }
+      u32x4_t fb[RING];
+      auto x_frag = [&](int i) { return frag<D>(Xt, 0, plr, i * 16 + g * 8); };
+#pragma unroll
+      for (int i = 0; i < RING; ++i) fb[i] = x_frag(i);
+      matrix_phase<D>(true);
+#pragma unroll
+      for (int i = 0; i < NK; ++i) {
+        s = mfma(fb[i % RING], f[i], s);
+        if (i + RING < NK) fb[i % RING] = x_frag(i + RING);
+        __builtin_amdgcn_sched_barrier(0);
+      }
+      matrix_phase<D>(false);
+#pragma unroll
+      for (int i = 0; i < RING; ++i) xb[i] = y_frag(i);   // arrive beside the exponentials
+      __builtin_amdgcn_sched_barrier(0);
+      if (!is_k) {
+        if (i0 < jw + 32) {   // some (query, key) pair of the tile is above the diagonal
+#pragma unroll
+          for (int q = 0; q < 16; ++q) {
+            const float p = __builtin_amdgcn_exp2f(s[q] * c);
+            s[q] = i0 + acc_row(q, g) < jk ? 0.f : p;
+          }
+        } else {
+#pragma unroll
+          for (int q = 0; q < 16; ++q) s[q] = __builtin_amdgcn_exp2f(s[q] * c);
+        }
+#pragma unroll
+        for (int qq = 0; qq < 4; ++qq) probs[64 * qq] = make_float4(s[4 * qq], s[4 * qq + 1], s[4 * qq + 2], s[4 * qq + 3]);
+      }
+    }
+    if (u + NS < ntiles) {
+      advance(NS);
+      gload(st ^ 1);
+    }
+    lds_barrier();   // P is there
+    if (live) {
+      if (is_k) {
+#pragma unroll
+        for (int qq = 0; qq < 4; ++qq) {
+          const float4 p4 = probs[64 * qq];
+          s[4 * qq] *= p4.x; s[4 * qq + 1] *= p4.y; s[4 * qq + 2] *= p4.z; s[4 * qq + 3] *= p4.w;
+        }
+      }
+      u32x4_t pf[2][parts(D)];
+      pack_parts(s, 0, pf[0]);
+      pack_parts(s, 1, pf[1]);
+      matrix_phase<D>(true);
+#pragma unroll
+      for (int i = 0; i < NX; ++i) {
+        dacc[i % NC] = mfma_parts(xb[i % RING], pf[i / NC], dacc[i % NC]);
+        if (i + RING < NX) xb[i % RING] = y_frag(i + RING);
+        __builtin_amdgcn_sched_barrier(0);
+      }
+      matrix_phase<D>(false);
+    }
+    if (u + NS < ntiles) sstore(st ^ 1);
+    TIDE_ATTN_WAIT_DMA();
+    __syncthreads();   // the stage and the probabilities are read, the next tile is there
+  }
+  if constexpr (NS > 1) {
+    merge_sets<NW, NS, NC>(smem, dacc, set, wave_s, lane);
+    if (set != 0) return;
+  }
+  stage_out<D>(smem, dacc, is_k ? scale : 1.0f, wave_s, lane);
+  copy_rows<D>(smem, dqkv, sv.row0 + jw, S - jw, ld, (is_k ? nh + kh : nh + nkv + kh) * D, wave_s, lane);
+}
 
 // ------------------------------------------------------------------------------------------------
 bool attn_mfma_supported(const AttnArgs& a) {
@@ -991,11 +1117,11 @@ constexpr size_t row_smem() {   // of the forward and dQ kernels
   const size_t sums = NS > 1 ? (size_t)(NS / 2) * KW * (D / 32 * 16 + 2) * 64 * sizeof(float) : 0;
   return std::max({st, out, sums});
 }
-template <int WHICH, int D, int KW, int NS>
-constexpr size_t dkv_smem() {
-  const size_t st = (size_t)NS * 2 * DkvStage<dkv_rows<WHICH, NS>(), D>::STAGE * sizeof(bf16_t), out = (size_t)KW * 32 * pitch(D) * sizeof(bf16_t);
-  const size_t sums = NS > 1 ? (size_t)(NS / 2) * KW * (WHICH == 2 ? 2 : 1) * (D / 32) * 16 * 64 * sizeof(float) : 0;
-  return std::max({st, out, sums});
+// of the dK / dV kernels: waves of a set, a set's LDS, and the accumulators that sets merge
+template <int D>
+constexpr size_t dkv_smem(int waves, int NS, int set_elems, int accumulators) {
+  const size_t st = (size_t)NS * set_elems * sizeof(bf16_t), out = (size_t)waves * 32 * pitch(D) * sizeof(bf16_t);
+  return std::max({st, out, (size_t)(NS / 2) * waves * accumulators * 16 * 64 * sizeof(float)});
 }
 
 hipError_t set_smem(const void* f, size_t bytes, bool& done) {
@@ -1007,14 +1133,17 @@ hipError_t set_smem(const void* f, size_t bytes, bool& done) {
 
 // Groups in a chunk (see WorkMap), equal chunks.  Forward and dQ: all of an XCD's where they are three rounds of blocks or fewer; of more, as many as
 // have 4 MB of keys and values, the L2 of an XCD, two to eight (64 x 199, 32 / 8 heads, forward, 4 / 8 / 16 / 64 of 64 groups: 57 / 56 / 65 / 71 us; 16 x 2048, 1 / 4 / 16 of
-// 16: 659 / 620 / 651).  dK / dV, which read more per block: sixteen (backward of 32 x 512, 4 / 8 / 16 / 32 of 32: 453 / 448 / 425 / 433).
+// 16: 659 / 620 / 651).  dK / dV, which read more per block: sixteen at head size 64 (backward of
+// 32 x 512, 4 / 8 / 16 / 32 of 32: 453 / 448 / 425 / 433); at 128 all where they are three rounds of blocks or fewer, otherwise eight (forward and backward of 16 x 2048,
+// 2 / 4 / 8 / 16 of 16: 2581 / 2529 / 2522 / 2582; of 11 x 815, 16 / 8 heads, 4 / 6 / 11 of 11: 206 / 194 / 191).
 int row_chunk(int per_xcd, int nx, int slots, int64_t kv_bytes) {
   if (per_xcd * (int64_t)nx <= 3 * slots) return std::max(1, per_xcd);
   const int most = (int)std::min<int64_t>(8, std::max<int64_t>(2, (4 << 20) / kv_bytes)), n = (per_xcd + most - 1) / most;
   return (per_xcd + n - 1) / n;
 }
-int key_chunk(int per_xcd) {
-  const int n = std::max(1, (per_xcd + 15) / 16);
+int key_chunk(int per_xcd, int nx, int D) {
+  const int most = D == 64 ? 16 : per_xcd * (int64_t)nx <= 3 * 32 * 3 ? std::max(1, per_xcd) : 8;
+  const int n = std::max(1, (per_xcd + most - 1) / most);
   return std::max(1, (per_xcd + n - 1) / n);
 }
 template <int D, int KW, int NS>
@@ -1023,10 +1152,10 @@ WorkMap row_map(const AttnArgs& a, int waves) {
   map.chunk = row_chunk(map.per_xcd, map.nx, 32 * 4 * waves / (KW * NS), (int64_t)a.S * D * 4);
   return map;
 }
-template <int KW>
+template <int KW, int D>
 WorkMap key_map(const AttnArgs& a) {
   WorkMap map = work_map((a.S + KW * 32 - 1) / (KW * 32), a.nkv, a.B);
-  map.chunk = key_chunk(map.per_xcd);
+  map.chunk = key_chunk(map.per_xcd, map.nx, D);
   return map;
 }
 template <int D, int KW, int NS>
@@ -1057,16 +1186,28 @@ hipError_t launch_dq(const AttnArgs& a, hipStream_t s) {
   return hipGetLastError();
 }
 
-template <int WHICH, int D, int KW, int NS>
-hipError_t launch_dkv(const AttnArgs& a, hipStream_t s) {
-  constexpr size_t smem = dkv_smem<WHICH, D, KW, NS>();
+template <int KW, int NS>
+hipError_t launch_dkv(const AttnArgs& a, hipStream_t s) {   // head size 64
+  constexpr size_t smem = dkv_smem<64>(KW, NS, 2 * DkvStage<64>::STAGE, 4);
   static_assert(smem <= 160 * 1024, "LDS of a CU");
   static bool done = false;
-  const hipError_t e = set_smem((const void*)attn_dkv_mfma_kernel<WHICH, D, KW, NS>, smem, done);
+  const hipError_t e = set_smem((const void*)attn_dkv_mfma_kernel<KW, NS>, smem, done);
   if (e != hipSuccess) return e;
-  const WorkMap map = key_map<KW>(a);
+  const WorkMap map = key_map<KW, 64>(a);
   const dim3 grid((unsigned)work_blocks(map));
-  hipLaunchKernelGGL((attn_dkv_mfma_kernel<WHICH, D, KW, NS>), grid, dim3(KW * NS * 64), smem, s, (const bf16_t*)a.qkv, (const bf16_t*)a.dout, a.lse, a.delta, (bf16_t*)a.dqkv, a.S, a.nh, a.nkv, a.cu_seqlens, a.total_rows, map);
+  hipLaunchKernelGGL((attn_dkv_mfma_kernel<KW, NS>), grid, dim3(KW * NS * 64), smem, s, (const bf16_t*)a.qkv, (const bf16_t*)a.dout, a.lse, a.delta, (bf16_t*)a.dqkv, a.S, a.nh, a.nkv, a.cu_seqlens, a.total_rows, map);
+  return hipGetLastError();
+}
+template <int KW, int NS>
+hipError_t launch_dkv_pair(const AttnArgs& a, hipStream_t s) {   // head size 128
+  constexpr size_t smem = dkv_smem<128>(2 * KW, NS, pair_set<KW>(), 4);
+  static_assert(smem <= 160 * 1024, "LDS of a CU");
+  static bool done = false;
+  const hipError_t e = set_smem((const void*)attn_dkv_pair_kernel<KW, NS>, smem, done);
+  if (e != hipSuccess) return e;
+  const WorkMap map = key_map<KW, 128>(a);
+  const dim3 grid((unsigned)work_blocks(map));
+  hipLaunchKernelGGL((attn_dkv_pair_kernel<KW, NS>), grid, dim3(KW * NS * 128), smem, s, (const bf16_t*)a.qkv, (const bf16_t*)a.dout, a.lse, a.delta, (bf16_t*)a.dqkv, a.S, a.nh, a.nkv, a.cu_seqlens, a.total_rows, map);
   return hipGetLastError();
 }
 
@@ -1119,22 +1260,18 @@ hipError_t launch_bwd(const AttnArgs& a, hipStream_t s) {
     // 61 x 156 (1464, 25) 125 / 105 / 101; a block of 128 keys on four waves is within 3 % of the last where that is the fastest.
     ProfScope ps("attn_dkv_mfma", 8.0 * pairs, 0, s);   // S, dP, dV and dK products
     const int64_t blocks = key_blocks(64);
-    if (blocks <= 424 || (blocks <= 544 && chain >= 32)) return launch_dkv<kBothGrads, D, 2, 4>(a, s);
-    if (blocks <= 1000) return launch_dkv<kBothGrads, D, 2, 2>(a, s);
-    return launch_dkv<kBothGrads, D, 2, 1>(a, s);
+    if (blocks <= 424 || (blocks <= 544 && chain >= 32)) return launch_dkv<2, 4>(a, s);
+    if (blocks <= 1000) return launch_dkv<2, 2>(a, s);
+    return launch_dkv<2, 1>(a, s);
   } else {
-    ProfScope ps("attn_dkv_mfma", 10.0 * pairs, 0, s);   // dV pass: S, dV; dK pass: S, dP, dK
-    // Whole backward, us, four sets / four waves, blocks of 128 keys and chain: 32 / 8 heads 2 x 905 (128, 116) 146 / 239, 16 x 181 (256, 24) 71.9 / 75.6,
-    // 16 / 8 heads 18 x 209 (288, 14) 65.7 / 55.9, 1 x 5876 (368, 368) 782 / 925, 11 x 815 (616, 52) 227 / 183, 40 / 8 heads 20 x 149 (320, 25) 85.0 / 89.0, 5 x 1601 (520,
-    // 255) 670 / 671, 7 x 1489 (672, 235) 853 / 733.
-    const int64_t blocks = key_blocks(128);
-    const bool few = blocks <= 128 || (blocks <= 256 && chain >= 18) || (blocks <= 440 && chain >= 64) || (blocks <= 512 && chain >= 256);
-    if (few) {
-      e = launch_dkv<kValueGrad, D, kFewKW, kFewNS>(a, s);
-      return e == hipSuccess ? launch_dkv<kKeyGrad, D, kFewKW, kFewNS>(a, s) : e;
-    }
-    e = launch_dkv<kValueGrad, D, 4, 1>(a, s);
-    return e == hipSuccess ? launch_dkv<kKeyGrad, D, 4, 1>(a, s) : e;
+    // Forward and backward, us, one set of two pairs / two sets / two sets of one pair, blocks of 64 keys and chain: 1 x 500 with 32 / 8 heads (64, 64) 89 / 73 / 67,
+    // 2 x 905 (240, 116) 162 / 138 / 129, 7 x 405 with 40 / 8 (392, 65) 139 / 125 / 143, 1 x 6341 with 16 / 4 (400, 796) 1110 / 902 / 1124, 3 x 1333 (504, 168) 302 / 270 / 332,
+    // 16 x 181 (384, 24) 70 / 69 / 76, 18 x 209 with 16 / 8 (576, 14) 55 / 58 / 66, 1 x 5876 (736, 368) 748 / 748 / 937, 5 x 1601 with 40 / 8 (1040, 255) 656 / 709 / 907.
+    ProfScope ps("attn_dkv_mfma", 8.0 * pairs, 0, s);   // S, dP, dV and dK products
+    const int64_t blocks = key_blocks(64);
+    if (blocks <= 256 && chain >= 8) return launch_dkv_pair<1, 2>(a, s);
+    if (blocks <= 520 && chain >= 16) return launch_dkv_pair<2, 2>(a, s);
+    return launch_dkv_pair<2, 1>(a, s);
   }
 }
 }  // namespace
