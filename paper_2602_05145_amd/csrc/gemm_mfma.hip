@@ -320,7 +320,7 @@ __device__ __forceinline__ void adam_store(const AdamTarget& t, const AdamRate& 
 // ------------------------------------------------------------------------------------------------
 typedef float f32x4_t __attribute__((ext_vector_type(4)));
 
-template <int BM, int BN, bool AMM, bool BNM, typename TO, bool KWHOLE, bool ADAM>
+template <int BM, int BN, bool AMM, bool BNM, typename TO, bool KWHOLE, bool ADAM, bool LONG = false>
 __device__ __forceinline__ void gemm_block(std::conditional_t<ADAM, MfmaAdamParams, MfmaParams> p, int pid) {   // pid: which of the launch's blocks
   static_assert(BN == 256 ? BM % 32 == 0 && BM >= 128 && BM <= 256 : BN == 128 && BM == 128, "tile edges");
   constexpr int BK = 64, WAVES_M = 2, WAVES_N = BN / 64, NW = WAVES_M * WAVES_N;
@@ -636,14 +636,26 @@ __device__ __forceinline__ void gemm_block(std::conditional_t<ADAM, MfmaAdamPara
     __shared__ __attribute__((aligned(1024))) bf16_t ld2[D_STAGE];
     __shared__ __attribute__((aligned(1024))) bf16_t ls0[S_STAGE];
     __shared__ __attribute__((aligned(1024))) bf16_t ls1[S_STAGE];
+    // the units that only the long rings have (A: ld0 .. ld4, B: ls0 .. ls4)
+    __shared__ __attribute__((aligned(1024))) bf16_t ld3[LONG ? D_STAGE : 1];
+    __shared__ __attribute__((aligned(1024))) bf16_t ld4[LONG ? D_STAGE : 1];
+    __shared__ __attribute__((aligned(1024))) bf16_t ls2[LONG ? S_STAGE : 1];
+    __shared__ __attribute__((aligned(1024))) bf16_t ls3[LONG ? S_STAGE : 1];
+    __shared__ __attribute__((aligned(1024))) bf16_t ls4[LONG ? S_STAGE : 1];
+    static_assert(!LONG || (!DEEPB && TM == GA), "long rings: squares of 128");
     auto deep = [&](auto U) -> bf16_t* {
       if constexpr (decltype(U)::value == 0) return ld0;
       else if constexpr (decltype(U)::value == 1) return ld1;
-      else return ld2;
+      else if constexpr (decltype(U)::value == 2) return ld2;
+      else if constexpr (decltype(U)::value == 3) return ld3;
+      else return ld4;
     };
     auto shal = [&](auto U) -> bf16_t* {
       if constexpr (decltype(U)::value == 0) return ls0;
-      else return ls1;
+      else if constexpr (decltype(U)::value == 1) return ls1;
+      else if constexpr (decltype(U)::value == 2) return ls2;
+      else if constexpr (decltype(U)::value == 3) return ls3;
+      else return ls4;
     };
     auto unit_a = [&](auto D, auto S) -> bf16_t* { if constexpr (DEEPB) return shal(S); else return deep(D); };
     auto unit_b = [&](auto D, auto S) -> bf16_t* { if constexpr (DEEPB) return deep(D); else return shal(S); };
@@ -758,6 +770,50 @@ __device__ __forceinline__ void gemm_block(std::conditional_t<ADAM, MfmaAdamPara
       }(std::make_integer_sequence<int, NMF>{});
     };
 
+    if constexpr (LONG) {
+      // ---- five units for either operand: slab kt lives in unit kt % 5.  A's next slab (kt + 4) is requested in the first part of
+      // slab kt, B's (kt + 5) in the second, into the units that slabs kt - 1 and kt have left at their barriers: four slabs ahead.
+      constexpr int NL = NVA + NVB;
+      all_shal(ls0, 0); all_deep(ld0, 0);
+      all_shal(ls1, 1); all_deep(ld1, 1);
+      all_shal(ls2, 2); all_deep(ld2, 2);
+      all_shal(ls3, 3); all_deep(ld3, 3);
+      all_shal(ls4, 4);
+      TIDE_WAIT_VMCNT(3 * NL + NVB);
+      __builtin_amdgcn_s_barrier();
+      __builtin_amdgcn_sched_barrier(0);
+      frags_a(ld0, 0, Int<0>{}, fa0);
+      frags_b(ls0, 0, fb0);
+      __builtin_amdgcn_sched_barrier(0);
+      auto step = [&](auto U, int kt) {
+        constexpr int u = decltype(U)::value;
+        const auto da = desc_deep(kt + 4);
+        quarter(Int<0>{}, fa0, fb0, [&](auto X) {
+          constexpr int x = decltype(X)::value;
+          if constexpr (x < GA) frag_a(deep(U), 1, Int<0>{}, X, fa1);
+          else if constexpr (x < GA + TN) frag_b(shal(U), 1, Int<x - GA>{}, fb1);
+          else if constexpr (x < GA + TN + NVA) dma_deep(Int<x - GA - TN>{}, da, deep(Int<(u + 4) % 5>{}));
+        });
+        // the wave's operand reads have returned, and its loads of the next slab have landed: those of the three after it may be in flight
+        __builtin_amdgcn_s_waitcnt(((3 * NL) & 15) | (((3 * NL) >> 4) << 14));   // vmcnt, lgkmcnt(0), expcnt(0)
+        __builtin_amdgcn_s_barrier();
+        __builtin_amdgcn_sched_barrier(0);
+        const auto db = desc_shal(kt + 5);
+        quarter(Int<0>{}, fa1, fb1, [&](auto X) {
+          constexpr int x = decltype(X)::value;
+          if constexpr (x < GA) frag_a(deep(Int<(u + 1) % 5>{}), 0, Int<0>{}, X, fa0);
+          else if constexpr (x < GA + TN) frag_b(shal(Int<(u + 1) % 5>{}), 0, Int<x - GA>{}, fb0);
+          else if constexpr (x < GA + TN + NVB) dma_shal(Int<x - GA - TN>{}, db, shal(U));
+        });
+      };
+      for (int kt = 0; kt < nk; kt += 5) {
+        step(Int<0>{}, kt);
+        if (__builtin_expect(kt + 1 < nk, 1)) step(Int<1>{}, kt + 1);
+        if (__builtin_expect(kt + 2 < nk, 1)) step(Int<2>{}, kt + 2);
+        if (__builtin_expect(kt + 3 < nk, 1)) step(Int<3>{}, kt + 3);
+        if (__builtin_expect(kt + 4 < nk, 1)) step(Int<4>{}, kt + 4);
+      }
+    } else {
     all_deep(ld0, 0);
     all_shal(ls0, 0);
     TIDE_WAIT_VMCNT(0);
@@ -847,6 +903,7 @@ __device__ __forceinline__ void gemm_block(std::conditional_t<ADAM, MfmaAdamPara
       if (__builtin_expect(kt + 4 < nk, 1)) step(Int<1>{}, Int<0>{}, Int<2>{}, Int<1>{}, Int<0>{}, kt + 4);
       if (__builtin_expect(kt + 5 < nk, 1)) step(Int<2>{}, Int<1>{}, Int<0>{}, Int<0>{}, Int<1>{}, kt + 5);
     }
+    }
     TIDE_WAIT_VMCNT(0);   // dummy slabs still in flight write LDS: let them land before the patches are written
     constexpr int PPU = D_STAGE / kPatchElems;   // epilogue patches per deep unit; a wave left over takes the first shallow one
     static_assert(PPU >= 1 && S_STAGE >= kPatchElems && NW <= 3 * PPU + 1, "the epilogue patches fit four units");
@@ -859,6 +916,11 @@ __device__ __forceinline__ void gemm_block(std::conditional_t<ADAM, MfmaAdamPara
 template <int BM, int BN, bool AMM, bool BNM, typename TO, bool KWHOLE, bool ADAM = false>
 __global__ __launch_bounds__(2 * BN) void gemm_mfma_kernel(std::conditional_t<ADAM, MfmaAdamParams, MfmaParams> p) {
   gemm_block<BM, BN, AMM, BNM, TO, KWHOLE, ADAM>(p, blockIdx.x);
+}
+// squares of 128, one block on a CU (see few_blocks)
+template <bool AMM, bool BNM, typename TO, bool KWHOLE>
+__global__ __launch_bounds__(256) void gemm_mfma_few_kernel(MfmaParams p) {
+  gemm_block<128, 128, AMM, BNM, TO, KWHOLE, false, true>(p, blockIdx.x);
 }
 
 // The weight gradients of a layer with their updates, product after product over the blocks of one launch.  A product of few rows is
@@ -1255,6 +1317,16 @@ namespace {
 // every slab whole (and K known on the host): the DMA loads of a K-major operand take loop-constant lane offsets
 bool whole_slabs(const MfmaParams& p) { return !p.k_dev && p.K % 64 == 0 && (!p.A2 || p.K2 % 64 == 0); }
 
+// Squares of 128 that leave CUs idle have a CU's whole LDS to themselves: rings of five units per operand, four slabs ahead.  The weights
+// of a step come from memory, and with the three and two units that fit twice into a CU a slab waits for them: us in a step, 3 + 2 units / 5 + 5,
+// 132 blocks of 32 slabs 27.3 / 19.5, 96 27.5 / 18.7, 48 30.2 / 21.6; 192 blocks of 64 slabs, alone and repeated, 34.4 / 28.6.  Evaluation of 2 x 144
+// rows, 2048 / 5632 wide, 247 / 214; steps of 132 to 1000 rows 0.6 to 2.3 % less.  Not below 16 slabs, where filling the rings shows (8 slabs and fewer, 8.1 / 8.4 to
+// 13.1 / 13.7), nor with nearly every CU busy (250 blocks of 32 slabs 23.3 / 24.1).
+bool few_blocks(const MfmaParams& p, int64_t blocks, int tiles) {
+  const int slabs = split_slabs(p.K, p.A2 ? p.K2 : 0), parts = std::max<int>(1, (int)(blocks / std::max(1, tiles)));
+  return blocks <= 224 && slabs / parts >= 16;
+}
+
 template <int BM, int BN, bool AMM, bool BNM, typename TO, typename P>
 hipError_t launch_tiles(const P& p, const SplitGrid& all, hipStream_t s) {   // all: of a kSplitAll launch
   constexpr bool ADAM = std::is_same_v<P, MfmaAdamParams>;
@@ -1269,6 +1341,14 @@ hipError_t launch_tiles(const P& p, const SplitGrid& all, hipStream_t s) {   // 
     auto* kernel = gemm_mfma_kernel<BM, BN, AMM, BNM, TO, false>;
     if constexpr (!(AMM && BNM)) {
       if (whole_slabs(p)) kernel = gemm_mfma_kernel<BM, BN, AMM, BNM, TO, true>;
+    }
+    if constexpr (BM == 128) {
+      if (few_blocks(p, items, tiles)) {
+        kernel = gemm_mfma_few_kernel<AMM, BNM, TO, false>;
+        if constexpr (!(AMM && BNM)) {
+          if (whole_slabs(p)) kernel = gemm_mfma_few_kernel<AMM, BNM, TO, true>;
+        }
+      }
     }
     hipLaunchKernelGGL(kernel, dim3((unsigned)items), dim3(2 * BN), 0, s, q);
     const hipError_t e = hipGetLastError();

@@ -177,3 +177,48 @@ def test_the_cases_above_are_what_they_say():
         for k, k2 in ((448, 192), (192, 448), (64, 448)):
             g = ig.args(layout, M, N, k, K2=k2, lda=max(k, k2), ldb=max(k, k2) if layout == ig.NT else N)
             assert f"_{height}x256_" in kernel_name(g).decode(), (layout, M, N, k, k2, kernel_name(g))
+
+
+# Squares of 128 on at most 224 CUs, 16 slabs or more: rings of five units for either operand.  Numbers of slabs in every phase of them, whole and with
+# a remainder of 8 (TN: 1); a depth on the device of no, one and a few slabs; a seam between operand pairs in every phase.
+@pytest.mark.gpu
+@pytest.mark.parametrize("layout", [ig.NT, ig.NN, ig.TN])
+@pytest.mark.parametrize("slabs", range(16, 21))
+def test_every_phase_of_the_long_rings(layout, slabs):
+    M, N = (264, 264)
+    g = torch.Generator(device="cuda").manual_seed(slabs)
+    for K in (64 * slabs, 64 * slabs - (63 if layout == ig.TN else 56)):
+        sh = {ig.NT: ((M, K), (N, K)), ig.NN: ((M, K), (K, N)), ig.TN: ((K, M), (K, N))}[layout]
+        a, b = (torch.randn(s, device="cuda", generator=g).bfloat16() for s in sh)
+        ad, bd = a.double(), b.double()
+        for out in (ig.F32, ig.BF16):
+            for k in (None, 0, 1, 200, K - 1) if layout == ig.TN else (None,):
+                c = torch.full((M, N), float("nan"), device="cuda", dtype=torch.float32 if out == ig.F32 else torch.bfloat16)
+                args = ig.args(layout, M, N, K, out=out, a=a.data_ptr(), b=b.data_ptr(), c=c.data_ptr())
+                cnt = torch.tensor([k or 0], dtype=torch.int32, device="cuda")
+                if k is not None:
+                    args.k_dev = cnt.data_ptr()
+                assert "_128_" in kernel_name(args).decode()
+                print("long rings", layout, K, out, k, flush=True)
+                _run(args)
+                n = K if k is None else k
+                want = ad[:n].t() @ bd[:n] if layout == ig.TN else ad @ (bd.t() if layout == ig.NT else bd)
+                assert bool(((c.double() - want).abs() <= _bound(K, want, out == ig.BF16)).all())
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("layout", [ig.NT, ig.NN])
+@pytest.mark.parametrize("K,K2", [(64, 1216), (640, 576), (704, 512), (832, 640), (960, 320), (1032, 200)])
+def test_a_second_operand_pair_on_the_long_rings(layout, K, K2):
+    M, N, rows, lda, g = 300, 264, 141, max(K, K2), torch.Generator(device="cuda").manual_seed(K)
+    a, a2 = (torch.randn(M, lda, device="cuda", generator=g).bfloat16() for _ in range(2))
+    b, b2 = (torch.randn((N, lda) if layout == ig.NT else (k, N), device="cuda", generator=g).bfloat16() for k in (K, K2))
+    c = torch.full((M, N), 7.0, device="cuda", dtype=torch.bfloat16)
+    cnt = torch.tensor([rows], dtype=torch.int32, device="cuda")
+    args = ig.args(layout, M, N, K, K2=K2, lda=lda, ldb=lda if layout == ig.NT else N, a=a.data_ptr(), b=b.data_ptr(), c=c.data_ptr(), m_dev=cnt.data_ptr())
+    args.A2, args.B2 = a2.data_ptr(), b2.data_ptr()
+    assert "_128_" in kernel_name(args).decode()
+    print("pairs on the long rings", layout, K, K2, flush=True)
+    _run(args)
+    want = sum(x[:rows, :k].double() @ (y[:, :k].double().t() if layout == ig.NT else y.double()) for x, y, k in ((a, b, K), (a2, b2, K2)))
+    assert bool(((c[:rows].double() - want).abs() <= _bound(K + K2, want, True)).all()) and bool((c[rows:] == 7.0).all())
