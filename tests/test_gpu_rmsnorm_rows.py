@@ -34,6 +34,13 @@ def test_rmsnorm_over_row_counts_and_widths(rows, d, dtype):
         assert float((got.double() - want[name]).abs().max()) < tol * float(want[name].abs().max()), name
 
 
+# a row per wave: forward up to 2048 columns (512, 1024 and 2048 per form), backward up to 2 KB; blocks whose rows are no multiple of its four waves
+@pytest.mark.parametrize("dtype", ["fp32", "bf16"])
+@pytest.mark.parametrize("rows,d", [(1, 512), (2, 520), (5, 1024), (481, 504), (1443, 1016), (3365, 1032), (10246, 512), (3, 2040)])
+def test_rmsnorm_with_a_row_per_wave(rows, d, dtype):
+    test_rmsnorm_over_row_counts_and_widths(rows, d, dtype)
+
+
 def test_rmsnorm_forward_of_wide_rows():
     rows, d = 5, 8200
     x, gain = torch.randn(rows, d, device=DEV), torch.randn(d, device=DEV)
