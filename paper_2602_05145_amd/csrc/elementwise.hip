@@ -330,6 +330,35 @@ hipError_t launch_scatter_rows(int64_t T, int d0, const void* src0, void* dst0, 
   return hipGetLastError();
 }
 
+// Eight elements that nothing reads again soon: past the caches, which then keep what is
+typedef unsigned u32x4_nt __attribute__((ext_vector_type(4)));
+typedef float f32x4_nt __attribute__((ext_vector_type(4)));
+__device__ __forceinline__ void load_once(Raw8<bf16_t>& r, const bf16_t* p, size_t i) {
+  const u32x4_nt v = __builtin_nontemporal_load(reinterpret_cast<const u32x4_nt*>(p + i));
+  r.a = make_uint4(v.x, v.y, v.z, v.w);
+}
+__device__ __forceinline__ void load_once(Raw8<float>& r, const float* p, size_t i) {
+  const f32x4_nt *q = reinterpret_cast<const f32x4_nt*>(p + i), a = __builtin_nontemporal_load(q), b = __builtin_nontemporal_load(q + 1);
+  r.a = make_float4(a.x, a.y, a.z, a.w);
+  r.b = make_float4(b.x, b.y, b.z, b.w);
+}
+__device__ __forceinline__ void store_once(bf16_t* p, size_t i, const float (&v)[8]) {
+  const u32x4_nt w = {f2bf2(v[0], v[1]), f2bf2(v[2], v[3]), f2bf2(v[4], v[5]), f2bf2(v[6], v[7])};
+  __builtin_nontemporal_store(w, reinterpret_cast<u32x4_nt*>(p + i));
+}
+__device__ __forceinline__ void store_once(float* p, size_t i, const float (&v)[8]) {
+  const f32x4_nt a = {v[0], v[1], v[2], v[3]}, b = {v[4], v[5], v[6], v[7]};
+  __builtin_nontemporal_store(a, reinterpret_cast<f32x4_nt*>(p + i));
+  __builtin_nontemporal_store(b, reinterpret_cast<f32x4_nt*>(p + i) + 1);
+}
+
+// Whether a pass's n arrays together are larger than the 256 MB of the last cache.  Of the forward pass then y passes by the caches, of the backward pass dy, the
+// residual gradient and dx, so that x, which both read, may still be there the second time.  Forward and backward, us, neither / backward / both: 27852 x 4096 bf16
+// 267 / 258 / 208, 20000 x 5120 242 / 218 / 188, 16000 x 4096 fp32 313 / 328 / 275, 30000 x 2560 bf16 183 / 154 / 149, 9000 x 4096 84.4 / 76.4 / 75.9 (y is below the line); 3000
+// x 4096, which the cache holds, 32.3 / 33.9.  In a training step, whose next product reads what the pass
+// writes, the backward gains nothing (10000 rows 35.90 / 36.00 ms) and keeps to the caches; the forward is even (32768 rows 102.6 / 102.7).
+inline bool passes_caches(int n, int64_t rows, int d, int dtype) { return n * rows * d * (int64_t)dtype_size(dtype) > ((int64_t)256 << 20); }
+
 // ----------------------------------------------------------------------------------------------
 // RMSNorm forward: one 256-thread block per row.  This form, which reads the row twice, serves widths that the one below
 // does not (not a multiple of 8, or above 8192).
@@ -378,7 +407,7 @@ __global__ __launch_bounds__(256) void rmsnorm_fwd_kernel(const T* __restrict__ 
 // The same for rows of up to 256 * 8 * NIT elements (d % 8 == 0): a thread keeps its NIT pieces of the row in registers
 // between the sum and the scaling, so the row is read once.  Bound by memory.  us, two reads / one: 27852 x 4096 bf16 84.4 / 76.8
 // (5.9 TB/s), 8000 x 8192 bf16 61.6 / 46.6, 10000 x 8192 fp32 150 / 119.
-template <typename T, int NIT>
+template <typename T, int NIT, bool ONCE = false>
 __global__ __launch_bounds__(256) void rmsnorm_fwd_row_kernel(const T* __restrict__ x, const T* __restrict__ g, float eps,
                                                               T* __restrict__ y, float* __restrict__ rstd, int d,
                                                               const int* __restrict__ rows_dev) {
@@ -419,7 +448,8 @@ __global__ __launch_bounds__(256) void rmsnorm_fwd_row_kernel(const T* __restric
       gv[it].get(gg);
 #pragma unroll
       for (int j = 0; j < 8; ++j) o[j] = gg[j] * v[j] * r;
-      st8(yr, c, o);
+      if constexpr (ONCE) store_once(yr, c, o);
+      else st8(yr, c, o);
     }
   }
 }
@@ -488,7 +518,8 @@ hipError_t launch_rmsnorm_fwd(int64_t rows, int d, const void* x, const void* g,
   }
   if (vec && d <= 8192) {
     const int nit = (d + 2047) / 2048;
-#define TIDE_RMS_FWD(T, N) hipLaunchKernelGGL((rmsnorm_fwd_row_kernel<T, N>), grid, blk, 0, s, (const T*)x, (const T*)g, eps, (T*)y, rstd, d, rows_dev)
+    const bool once = passes_caches(2, rows, d, dtype);
+#define TIDE_RMS_FWD(T, N) hipLaunchKernelGGL((once ? rmsnorm_fwd_row_kernel<T, N, true> : rmsnorm_fwd_row_kernel<T, N>), grid, blk, 0, s, (const T*)x, (const T*)g, eps, (T*)y, rstd, d, rows_dev)
     if (dtype == kBF16) { if (nit == 2) TIDE_RMS_FWD(bf16_t, 2); else TIDE_RMS_FWD(bf16_t, 4); }
     else { if (nit == 2) TIDE_RMS_FWD(float, 2); else TIDE_RMS_FWD(float, 4); }
 #undef TIDE_RMS_FWD
@@ -533,7 +564,7 @@ inline int64_t rmsnorm_bwd_blocks(int64_t rows, int d) {
   return want < 1 ? 1 : (want < cap ? want : cap);
 }
 
-template <typename T, bool VEC, int NIT>
+template <typename T, bool VEC, int NIT, bool ONCE = false>   // ONCE: see passes_caches
 __global__ __launch_bounds__(256, VEC ? rmsnorm_bwd_resident(sizeof(T), NIT) : 1) void rmsnorm_bwd_kernel(const T* __restrict__ dy,
                                                           const T* __restrict__ x,
                                                           const T* __restrict__ g,
@@ -589,9 +620,14 @@ __global__ __launch_bounds__(256, VEC ? rmsnorm_bwd_resident(sizeof(T), NIT) : 1
       if constexpr (VEC) {
         nxt.x[it].zero(); nxt.dy[it].zero(); nxt.res[it].zero();
         if (c < d) {
-          nxt.dy[it].load(dy, base + c);
+          if constexpr (ONCE) load_once(nxt.dy[it], dy, base + c);
+          else nxt.dy[it].load(dy, base + c);
           nxt.x[it].load(x, base + c);
-          if (res) nxt.res[it].load(res, base + c);
+          if constexpr (ONCE) {
+            if (res) load_once(nxt.res[it], res, base + c);
+          } else {
+            if (res) nxt.res[it].load(res, base + c);
+          }
         }
       } else {
         nxt.xs[it] = nxt.dys[it] = nxt.ress[it] = 0.f;
@@ -635,7 +671,8 @@ __global__ __launch_bounds__(256, VEC ? rmsnorm_bwd_resident(sizeof(T), NIT) : 1
           o[j] = rv[it][j] + (r * (gg[j] * dyv[it][j]) - xv[it][j] * coef);
           acc[it][j] += dyv[it][j] * xv[it][j] * r;
         }
-        if constexpr (VEC) st8(dx, base + c, o);
+        if constexpr (VEC && ONCE) store_once(dx, base + c, o);
+        else if constexpr (VEC) st8(dx, base + c, o);
         else stf(dx, base + c, o[0]);
       }
     }
@@ -824,6 +861,7 @@ hipError_t launch_rmsnorm_bwd(int64_t rows, int d, const void* dy, const void* x
   const int nit = (d + per - 1) / per;            // <= 4 by the limits above
   const int64_t nblk = rmsnorm_bwd_grid(rows, d, dtype);
   dim3 grid((unsigned)nblk), blk(256);
+  const bool once = vec && dg && passes_caches(4, rows, d, dtype);   // (a step folds its gains' gradients later, and its next product reads dx at once)
   if (vec && (int64_t)d * (int64_t)dtype_size(dtype) <= kWaveRowBytes) {
 #define TIDE_RMS_BWD(T, N) hipLaunchKernelGGL((rmsnorm_bwd_wave_kernel<T, N>), grid, blk, 0, s, (const T*)dy, (const T*)x, (const T*)g, rstd, (const T*)res, (T*)dx, dg_partial, rows, d, rows_dev)
     if (dtype == kF32) TIDE_RMS_BWD(float, 1);
@@ -831,7 +869,7 @@ hipError_t launch_rmsnorm_bwd(int64_t rows, int d, const void* dy, const void* x
     else TIDE_RMS_BWD(bf16_t, 2);
 #undef TIDE_RMS_BWD
   } else {
-#define TIDE_RMS_BWD(T, V, N) hipLaunchKernelGGL((rmsnorm_bwd_kernel<T, V, N>), grid, blk, 0, s, (const T*)dy, (const T*)x, (const T*)g, rstd, (const T*)res, (T*)dx, dg_partial, rows, d, rows_dev)
+#define TIDE_RMS_BWD(T, V, N) hipLaunchKernelGGL((once ? rmsnorm_bwd_kernel<T, V, N, V> : rmsnorm_bwd_kernel<T, V, N>), grid, blk, 0, s, (const T*)dy, (const T*)x, (const T*)g, rstd, (const T*)res, (T*)dx, dg_partial, rows, d, rows_dev)
 #define TIDE_RMS_BWD_N(T, V) do { if (nit <= 1) TIDE_RMS_BWD(T, V, 1); else if (nit == 2) TIDE_RMS_BWD(T, V, 2); else TIDE_RMS_BWD(T, V, 4); } while (0)
   if (dtype == kBF16) {
     if (vec) TIDE_RMS_BWD_N(bf16_t, true); else TIDE_RMS_BWD_N(bf16_t, false);
