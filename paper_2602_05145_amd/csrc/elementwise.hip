@@ -356,7 +356,7 @@ __device__ __forceinline__ void store_once(float* p, size_t i, const float (&v)[
 // residual gradient and dx, so that x, which both read, may still be there the second time.  Forward and backward, us, neither / backward / both: 27852 x 4096 bf16
 // 267 / 258 / 208, 20000 x 5120 242 / 218 / 188, 16000 x 4096 fp32 313 / 328 / 275, 30000 x 2560 bf16 183 / 154 / 149, 9000 x 4096 84.4 / 76.4 / 75.9 (y is below the line); 3000
 // x 4096, which the cache holds, 32.3 / 33.9.  In a training step, whose next product reads what the pass
-// writes, the backward gains nothing (10000 rows 35.90 / 36.00 ms) and keeps to the caches; the forward is even (32768 rows 102.6 / 102.7).
+// writes, the backward gains nothing and keeps to the caches; the forward is even (32768 rows 102.6 / 102.7 ms).
 inline bool passes_caches(int n, int64_t rows, int d, int dtype) { return n * rows * d * (int64_t)dtype_size(dtype) > ((int64_t)256 << 20); }
 
 // ----------------------------------------------------------------------------------------------
