@@ -29,6 +29,7 @@
 // Causality: tiles entirely above the diagonal are never loaded; heavy blocks are scheduled first (see WorkMap); the
 // per-element causal test is made only by the (wave-uniformly chosen) tiles that touch the diagonal.
 #include <algorithm>
+#include <cfloat>
 #include <type_traits>
 
 #include "kernels.h"
@@ -396,20 +397,20 @@ __global__ __launch_bounds__(KW * NS * 64, row_waves(D, NS)) void attn_fwd_mfma_
   for (int ct = 0; ct < NC; ++ct)
 #pragma unroll
     for (int q = 0; q < 16; ++q) o[ct][q] = 0.f;
-  float m = -INFINITY, l = 0.f;   // l: this lane's share of the row's sum (its partner, lane ^ 32, has the rest)
+  // The reference begins below every score that is a number: where all keys of the first steps score -inf (a product of finite inputs can
+  // overflow to it), or a set's first step shows a query no key at all, the scores are then relative to that and weigh nothing.  (From -inf it was -inf less
+  // -inf, a NaN that stayed in the row.)
+  float m = -FLT_MAX, l = 0.f;   // l: this lane's share of the row's sum (its partner, lane ^ 32, has the rest)
 
   // The sums are kept relative to m, which follows the running maximum of the row.  At head size 64 it may fall behind by 2^8: the
   // accumulators are then rescaled once or twice per row, not in nearly every tile (one of 32 rows nearly always finds a new
   // maximum; 6 x 777 30.4 -> 29.0 us).  At head size 128, where a probability is one bf16 value, that of the largest score has to
   // stay the exact 1 it is relative to the maximum itself: with a lag the results were 2 % (flat scores) to 17 % (peaked ones) further from
   // 64 bits (and 16 x 2048 took 700 us, 745 without).
-  // (The first tile of a set after the first may show some of a wave's queries no key at all: their m stays at -inf, and the
-  // scores are then taken relative to 0.)
-  auto reference = [&] { return NS > 1 && m == -INFINITY ? 0.f : m * c; };
   auto follow = [&](float tm) {
-    const bool moved = (tm - m) * c > lag(D);   // the first tile: m = -inf
+    const bool moved = (tm - m) * c > lag(D);
     if (__builtin_amdgcn_ballot_w64(moved) != 0) {   // wave-uniform
-      const float mn = moved ? tm : m, alpha = NS == 1 || moved ? __builtin_amdgcn_exp2f((m - mn) * c) : 1.f;
+      const float mn = moved ? tm : m, alpha = __builtin_amdgcn_exp2f((m - mn) * c);
       l *= alpha;
       m = mn;
 #pragma unroll
@@ -460,7 +461,7 @@ __global__ __launch_bounds__(KW * NS * 64, row_waves(D, NS)) void attn_fwd_mfma_
 #pragma unroll
       for (int q = 0; q < 16; ++q) tm[q & 1] = fmaxf(tm[q & 1], s[q]);
       follow(row_max(fmaxf(tm[0], tm[1])));
-      const float mc = reference();
+      const float mc = m * c;
       float ps[2] = {0.f, 0.f};
 #pragma unroll
       for (int q = 0; q < 16; ++q) {
@@ -501,7 +502,7 @@ __global__ __launch_bounds__(KW * NS * 64, row_waves(D, NS)) void attn_fwd_mfma_
       __syncthreads();
       if (set < n) {
         const float mo = mine[NC * 16 * 64], lo = mine[(NC * 16 + 1) * 64], mn = fmaxf(m, mo);
-        const float wa = m == -INFINITY ? 0.f : __builtin_amdgcn_exp2f((m - mn) * c), wb = mo == -INFINITY ? 0.f : __builtin_amdgcn_exp2f((mo - mn) * c);
+        const float wa = __builtin_amdgcn_exp2f((m - mn) * c), wb = __builtin_amdgcn_exp2f((mo - mn) * c);
         m = mn;
         l = l * wa + lo * wb;
 #pragma unroll

@@ -107,3 +107,20 @@ def test_packed_lengths_in_a_training_step(B, dh, nh, nkv):
     for k, ref in grads.items():
         a, b = tr.host(tr.grads)[k].reshape(-1), ref.reshape(-1)
         assert a @ b / (np.linalg.norm(a) * np.linalg.norm(b)) > 0.999, k
+
+
+@pytest.mark.parametrize("dh", [64, 128])
+@pytest.mark.parametrize("bt,S,nh,nkv", [(1, 160, 2, 2), (1, 700, 8, 2), (80, 160, 8, 2)])
+def test_a_first_step_whose_scores_are_all_minus_infinity(B, dh, bt, S, nh, nkv):
+    """The products of the queries with the first 32 keys overflow to -inf: those keys weigh nothing with the queries that see others too, in
+    the blocks of four waves as in the sets."""
+    g = torch.Generator(device=DEV).manual_seed(3)
+    qkv = torch.randn(S, (nh + 2 * nkv) * dh, device=DEV, generator=g).bfloat16()
+    heads = qkv.view(S, nh + 2 * nkv, dh)
+    heads[:, :nh, 0], heads[:, nh:nh + nkv, 0], heads[:32, nh:nh + nkv, 0] = 1e20, 0.0, -3e38
+    dout = torch.randn(S, nh * dh, device=DEV, generator=g).bfloat16()
+    out, lse, dqkv = _run(B, qkv.repeat(bt, 1), dout.repeat(bt, 1), bt, S, nh, nkv, dh)
+    ro, rl, rg = (x[..., 32:] if x.shape == (nh, S) else x[32:] for x in _reference(qkv, dout, S, nh, nkv, dh))
+    w = nh * dh
+    for got, want, tol in ((out[32:S], ro, 1e-2), (lse[0, :, 32:], rl, 1e-5), (dqkv[32:S, :w], rg[:, :w], 1e-2)):   # as in the tests above
+        assert float((got.double().cpu() - want).abs().max()) < tol * float(want.abs().max())
