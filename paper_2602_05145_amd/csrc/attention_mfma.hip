@@ -1159,6 +1159,21 @@ WorkMap key_map(const AttnArgs& a) {
   map.chunk = key_chunk(map.per_xcd, map.nx, D);
   return map;
 }
+// A launch has fewer than 2^32 threads, and in a packed batch the number of sequences and the longest length are bounds that can ask for more blocks
+// than that, nearly all of them without rows: such a batch is launched as two.  (A fixed batch of so many blocks does not fit the memory.)
+bool splits_batch(const AttnArgs& a, const WorkMap& map, int threads) {
+  return a.cu_seqlens && a.B > 1 && work_blocks(map) * threads > (int64_t)UINT32_MAX;
+}
+template <typename Launch>
+hipError_t launch_halves(const AttnArgs& a, const Launch& launch) {
+  AttnArgs half = a;
+  half.B = a.B / 2;
+  const hipError_t e = launch(half);
+  if (e != hipSuccess) return e;
+  half.cu_seqlens = a.cu_seqlens + half.B;
+  half.B = a.B - half.B;
+  return launch(half);
+}
 template <int D, int KW, int NS>
 hipError_t launch_fwd(const AttnArgs& a, hipStream_t s) {
   constexpr size_t smem = row_smem<D, KW, NS>();
@@ -1167,6 +1182,7 @@ hipError_t launch_fwd(const AttnArgs& a, hipStream_t s) {
   const hipError_t e = set_smem((const void*)attn_fwd_mfma_kernel<D, KW, NS>, smem, done);
   if (e != hipSuccess) return e;
   const WorkMap map = row_map<D, KW, NS>(a, row_waves(D, NS));
+  if (splits_batch(a, map, KW * NS * 64)) return launch_halves(a, [&](const AttnArgs& half) { return launch_fwd<D, KW, NS>(half, s); });
   const dim3 grid((unsigned)work_blocks(map));   // 1-D: the kernel maps blocks to work itself
   ProfScope ps("attn_fwd_mfma", 2.0 * a.B * a.nh * D * (double)a.S * (a.S + 1), 0, s);
   hipLaunchKernelGGL((attn_fwd_mfma_kernel<D, KW, NS>), grid, dim3(KW * NS * 64), smem, s, (const bf16_t*)a.qkv, (bf16_t*)a.out, a.lse, a.S, a.nh, a.nkv, a.cu_seqlens, a.total_rows, map);
@@ -1181,6 +1197,7 @@ hipError_t launch_dq(const AttnArgs& a, hipStream_t s) {
   const hipError_t e = set_smem((const void*)attn_dq_mfma_kernel<D, KW, NS>, smem, done);
   if (e != hipSuccess) return e;
   const WorkMap map = row_map<D, KW, NS>(a, dq_waves(D, NS));
+  if (splits_batch(a, map, KW * NS * 64)) return launch_halves(a, [&](const AttnArgs& half) { return launch_dq<D, KW, NS>(half, s); });
   const dim3 grid((unsigned)work_blocks(map));
   ProfScope ps("attn_dq_mfma", 3.0 * a.B * a.nh * D * (double)a.S * (a.S + 1), 0, s);   // S, dP and dQ products
   hipLaunchKernelGGL((attn_dq_mfma_kernel<D, KW, NS>), grid, dim3(KW * NS * 64), smem, s, (const bf16_t*)a.qkv, (const bf16_t*)a.out, (const bf16_t*)a.dout, a.lse, a.delta, (bf16_t*)a.dqkv, a.S, a.nh, a.nkv, a.cu_seqlens, a.total_rows, map);
@@ -1195,6 +1212,7 @@ hipError_t launch_dkv(const AttnArgs& a, hipStream_t s) {   // head size 64
   const hipError_t e = set_smem((const void*)attn_dkv_mfma_kernel<KW, NS>, smem, done);
   if (e != hipSuccess) return e;
   const WorkMap map = key_map<KW, 64>(a);
+  if (splits_batch(a, map, KW * NS * 64)) return launch_halves(a, [&](const AttnArgs& half) { return launch_dkv<KW, NS>(half, s); });
   const dim3 grid((unsigned)work_blocks(map));
   hipLaunchKernelGGL((attn_dkv_mfma_kernel<KW, NS>), grid, dim3(KW * NS * 64), smem, s, (const bf16_t*)a.qkv, (const bf16_t*)a.dout, a.lse, a.delta, (bf16_t*)a.dqkv, a.S, a.nh, a.nkv, a.cu_seqlens, a.total_rows, map);
   return hipGetLastError();
@@ -1207,6 +1225,7 @@ hipError_t launch_dkv_pair(const AttnArgs& a, hipStream_t s) {   // head size 12
   const hipError_t e = set_smem((const void*)attn_dkv_pair_kernel<KW, NS>, smem, done);
   if (e != hipSuccess) return e;
   const WorkMap map = key_map<KW, 128>(a);
+  if (splits_batch(a, map, KW * NS * 128)) return launch_halves(a, [&](const AttnArgs& half) { return launch_dkv_pair<KW, NS>(half, s); });
   const dim3 grid((unsigned)work_blocks(map));
   hipLaunchKernelGGL((attn_dkv_pair_kernel<KW, NS>), grid, dim3(KW * NS * 128), smem, s, (const bf16_t*)a.qkv, (const bf16_t*)a.dout, a.lse, a.delta, (bf16_t*)a.dqkv, a.S, a.nh, a.nkv, a.cu_seqlens, a.total_rows, map);
   return hipGetLastError();

@@ -4,6 +4,7 @@ and of its steps; and one sequence alone against the same sequence as one of man
 import pytest
 import torch
 
+from tests import internal_attention as ia
 from tests.gpu_util import DEV, stream, sync
 from tests.test_gpu_attention_heads import _reference
 
@@ -124,3 +125,20 @@ def test_a_first_step_whose_scores_are_all_minus_infinity(B, dh, bt, S, nh, nkv)
     w = nh * dh
     for got, want, tol in ((out[32:S], ro, 1e-2), (lse[0, :, 32:], rl, 1e-5), (dqkv[32:S, :w], rg[:, :w], 1e-2)):   # as in the tests above
         assert float((got.double().cpu() - want).abs().max()) < tol * float(want.abs().max())
+
+
+@pytest.mark.parametrize("dh", [64, 128])
+def test_a_packed_batch_of_more_blocks_than_a_launch_has(B, dh):
+    """The most sequences that a call takes, nearly all of them empty, and a longest length of 16384: 2^32 threads by their bounds in the forward pass,
+    twice that for dK / dV at head size 128.  The three that have rows as by themselves (sums in another order, see above)."""
+    nh, nkv, rows, longest = 2, 2, 1200, 16384
+    g = torch.Generator(device=DEV).manual_seed(dh)
+    qkv = torch.randn(rows, (nh + 2 * nkv) * dh, device=DEV, generator=g).bfloat16()
+    dout = torch.randn(rows, nh * dh, device=DEV, generator=g).bfloat16()
+    ends, offsets = {7: 300, 40000: 1123, 65535: 1200}, [0]
+    for i in range(1, 65536):
+        offsets.append(ends.get(i, offsets[-1]))
+    print(f"packed batch of {len(offsets) - 1} sequences dh={dh}", flush=True)
+    many, few = ia.packed(qkv, dout, offsets, longest, nh, nkv, dh), ia.packed(qkv, dout, [0, 300, 1123, 1200], 823, nh, nkv, dh)
+    for a, b in zip(many, few):
+        assert float((a.double() - b.double()).abs().max()) < 2.0 ** -7 * float(b.double().abs().max())
