@@ -556,6 +556,10 @@ __host__ __device__ inline int rmsnorm_bwd_nit(int d) {
 __host__ __device__ constexpr int rmsnorm_bwd_resident(int es, int nit) {
   return es == 2 ? (nit <= 1 ? 5 : nit == 2 ? 3 : 2) : (nit <= 1 ? 4 : nit == 2 ? 2 : 1);
 }
+// the same of the kernel with a row per wave (rows of at most 2 KB in pieces of 512 columns): bf16 78 and 118 registers, fp32 103.  With the five blocks of
+// the other kernel, 1.25 rounds, bf16 rows of 513 to 1024 columns took, forward and backward, us: 10500 x 768 30.1, so 27.0; 16000 x 640 34.5, so 31.2; 30000 x 1024 71.4, so 70.2.
+constexpr int kWaveRowBytes = 2048;
+__host__ __device__ constexpr int rmsnorm_bwd_wave_resident(int es, int pieces) { return es == 2 && pieces == 1 ? 5 : 4; }
 inline int64_t rmsnorm_bwd_blocks(int64_t rows, int d) {
   const int nit = rmsnorm_bwd_nit(d);
   const int64_t cap = 256 * rmsnorm_bwd_resident(2, nit);   // (scratch is sized for the storage type with more of them)
@@ -692,9 +696,8 @@ __global__ __launch_bounds__(256, VEC ? rmsnorm_bwd_resident(sizeof(T), NIT) : 1
 // column partials are added through LDS at the end, in their order.  For rows of at most 2 KB; wider ones are better spread over a block,
 // whose threads then hold fewer sums and loads.  Forward and backward, us, block per row / wave per row: 30000 x 256 bf16 46.3 / 30.3, fp32 53.3 / 38.7;
 // 3589 x 256 17.7 / 13.6; 30000 x 1024 bf16 75.1 / 69.6, fp32 149.9 / 151.7; 30000 x 2048 bf16 148.7 / 151.4, fp32 297 / 408.
-constexpr int kWaveRowBytes = 2048;
 template <typename T, int N>
-__global__ __launch_bounds__(256, N == 1 ? 4 : 3) void rmsnorm_bwd_wave_kernel(const T* __restrict__ dy, const T* __restrict__ x, const T* __restrict__ g,
+__global__ __launch_bounds__(256, rmsnorm_bwd_wave_resident(sizeof(T), N)) void rmsnorm_bwd_wave_kernel(const T* __restrict__ dy, const T* __restrict__ x, const T* __restrict__ g,
                                                                const float* __restrict__ rstd, const T* __restrict__ res, T* __restrict__ dx,
                                                                float* __restrict__ dg_partial, int64_t rows, int d, const int* __restrict__ rows_dev) {
   __shared__ float part[3][N * 512];
@@ -829,7 +832,8 @@ __global__ __launch_bounds__(256) void colsum_kernel(ColSums cs, int64_t nrows, 
 static int64_t rmsnorm_bwd_grid(int64_t rows, int d, int dtype) {
   const int64_t n = rmsnorm_bwd_blocks(rows, d);
   if (d % 8 || d > 8192) return n;
-  const int64_t cap = 256 * rmsnorm_bwd_resident((int)dtype_size(dtype), rmsnorm_bwd_nit(d));
+  const int es = (int)dtype_size(dtype);
+  const int64_t cap = 256 * (d * es <= kWaveRowBytes ? rmsnorm_bwd_wave_resident(es, (d + 511) / 512) : rmsnorm_bwd_resident(es, rmsnorm_bwd_nit(d)));
   return n < cap ? n : cap;
 }
 
@@ -862,7 +866,7 @@ hipError_t launch_rmsnorm_bwd(int64_t rows, int d, const void* dy, const void* x
   const int64_t nblk = rmsnorm_bwd_grid(rows, d, dtype);
   dim3 grid((unsigned)nblk), blk(256);
   const bool once = vec && dg && passes_caches(4, rows, d, dtype);   // (a step folds its gains' gradients later, and its next product reads dx at once)
-  if (vec && (int64_t)d * (int64_t)dtype_size(dtype) <= kWaveRowBytes) {
+  if (vec && d * (int)dtype_size(dtype) <= kWaveRowBytes) {
 #define TIDE_RMS_BWD(T, N) hipLaunchKernelGGL((rmsnorm_bwd_wave_kernel<T, N>), grid, blk, 0, s, (const T*)dy, (const T*)x, (const T*)g, rstd, (const T*)res, (T*)dx, dg_partial, rows, d, rows_dev)
     if (dtype == kF32) TIDE_RMS_BWD(float, 1);
     else if (d <= 512) TIDE_RMS_BWD(bf16_t, 1);

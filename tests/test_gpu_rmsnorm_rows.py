@@ -74,3 +74,17 @@ def test_rmsnorm_backward_of_fewer_rows_than_its_scratch_was_made_for():
         want = (dy.double() * x.double() * torch.rsqrt(x.double().square().mean(-1, keepdim=True) + 1e-5)).sum(0)
         assert float((dg.double() - want).abs().max()) < 1e-5 * float(want.abs().max())
         assert bool((buf[size:] == 0xA5).all())
+
+
+@pytest.mark.parametrize("d,dtype,per_cu", [(512, "bf16", 5), (520, "bf16", 4), (1024, "bf16", 4), (504, "fp32", 4), (1032, "bf16", 5)])
+def test_a_full_chip_is_one_round_of_blocks(d, dtype, per_cu):
+    """A block leaves a row of partial sums; of the blocks that a CU holds at the kernel's registers there are one round, and no part of a second."""
+    rows, (dt, code) = 11000, (torch.bfloat16, 1) if dtype == "bf16" else (torch.float32, 0)
+    x, dy = (torch.randn(rows, d, device=DEV).to(dt) for _ in range(2))
+    gain, rstd = torch.ones(d, device=DEV, dtype=dt), torch.ones(rows, device=DEV)
+    dx, dg = torch.empty_like(x), torch.empty(d, device=DEV)
+    part = torch.full((B.tide_rmsnorm_bwd_scratch_bytes(rows, d) // (4 * d), d), float("nan"), device=DEV)
+    print(f"rmsnorm blocks d={d} {dtype}", flush=True)
+    B.tide_rmsnorm_bwd(rows, d, dy, x, gain, rstd, None, dx, dg, part, code, stream())
+    sync()
+    assert int(torch.isfinite(part).all(1).sum()) == 256 * per_cu
