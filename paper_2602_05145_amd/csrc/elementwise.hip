@@ -352,12 +352,17 @@ __device__ __forceinline__ void store_once(float* p, size_t i, const float (&v)[
   __builtin_nontemporal_store(b, reinterpret_cast<f32x4_nt*>(p + i) + 1);
 }
 
-// Whether a pass's n arrays together are larger than the 256 MB of the last cache.  Of the forward pass then y passes by the caches, of the backward pass dy, the
-// residual gradient and dx, so that x, which both read, may still be there the second time.  Forward and backward, us, neither / backward / both: 27852 x 4096 bf16
-// 267 / 258 / 208, 20000 x 5120 242 / 218 / 188, 16000 x 4096 fp32 313 / 328 / 275, 30000 x 2560 bf16 183 / 154 / 149, 9000 x 4096 84.4 / 76.4 / 75.9 (y is below the line); 3000
-// x 4096, which the cache holds, 32.3 / 33.9.  In a training step, whose next product reads what the pass
-// writes, the backward gains nothing and keeps to the caches; the forward is even (32768 rows 102.6 / 102.7 ms).
-inline bool passes_caches(int n, int64_t rows, int d, int dtype) { return n * rows * d * (int64_t)dtype_size(dtype) > ((int64_t)256 << 20); }
+// Whether what a pass reads and writes once goes past the caches: its n arrays are together an eighth larger than the 256 MB of the last one.  Of the
+// forward pass then y does, of the backward pass dy, the residual gradient and dx, so that x, which both read, may still be there the second time.  us,
+// past them / not: 27852 x 4096 bf16, forward 63.6 / 78.0, backward 149 / 195, one after the other 215 / 270; with a product over 512 columns of x and of y
+// and dx behind each of them 606 / 635; 12000 x 2560 fp32 backward 90.9 / 107.  Not as soon as the cache is too small, for then most of what a
+// pass leaves in it still is of use: 8300 x 4096 bf16 (272 MB) backward and a product of dx 106 / 94, 7000 x 2560 fp32 (287) backward 56.7 / 50.4,
+// 17500 x 4096 (287) forward and a product of y 113 / 106; 10000 x 4096 (328) 114 / 118, 8000 x 2560 fp32 (328) 63.2 / 64.7, 20000 x 4096 (328) 128 / 130.
+// With a number of rows known on the device alone neither: it may be small, and in a training step, where the norms over the selected rows have one, it
+// is as long either way (8192 to 32768 rows, within 0.2 %).  Rows that have a wave each keep to the caches too (not tried).
+inline bool passes_caches(int n, int64_t rows, int d, int dtype, const int* rows_dev) {
+  return !rows_dev && n * rows * d * (int64_t)dtype_size(dtype) > ((int64_t)288 << 20);
+}
 
 // ----------------------------------------------------------------------------------------------
 // RMSNorm forward: one 256-thread block per row.  This form, which reads the row twice, serves widths that the one below
@@ -518,7 +523,7 @@ hipError_t launch_rmsnorm_fwd(int64_t rows, int d, const void* x, const void* g,
   }
   if (vec && d <= 8192) {
     const int nit = (d + 2047) / 2048;
-    const bool once = passes_caches(2, rows, d, dtype);
+    const bool once = passes_caches(2, rows, d, dtype, rows_dev);
 #define TIDE_RMS_FWD(T, N) hipLaunchKernelGGL((once ? rmsnorm_fwd_row_kernel<T, N, true> : rmsnorm_fwd_row_kernel<T, N>), grid, blk, 0, s, (const T*)x, (const T*)g, eps, (T*)y, rstd, d, rows_dev)
     if (dtype == kBF16) { if (nit == 2) TIDE_RMS_FWD(bf16_t, 2); else TIDE_RMS_FWD(bf16_t, 4); }
     else { if (nit == 2) TIDE_RMS_FWD(float, 2); else TIDE_RMS_FWD(float, 4); }
@@ -865,7 +870,7 @@ hipError_t launch_rmsnorm_bwd(int64_t rows, int d, const void* dy, const void* x
   const int nit = (d + per - 1) / per;            // <= 4 by the limits above
   const int64_t nblk = rmsnorm_bwd_grid(rows, d, dtype);
   dim3 grid((unsigned)nblk), blk(256);
-  const bool once = vec && dg && passes_caches(4, rows, d, dtype);   // (a step folds its gains' gradients later, and its next product reads dx at once)
+  const bool once = vec && passes_caches(res ? 4 : 3, rows, d, dtype, rows_dev);
   if (vec && d * (int)dtype_size(dtype) <= kWaveRowBytes) {
 #define TIDE_RMS_BWD(T, N) hipLaunchKernelGGL((rmsnorm_bwd_wave_kernel<T, N>), grid, blk, 0, s, (const T*)dy, (const T*)x, (const T*)g, rstd, (const T*)res, (T*)dx, dg_partial, rows, d, rows_dev)
     if (dtype == kF32) TIDE_RMS_BWD(float, 1);

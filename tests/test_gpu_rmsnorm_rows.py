@@ -41,8 +41,9 @@ def test_rmsnorm_with_a_row_per_wave(rows, d, dtype):
     test_rmsnorm_over_row_counts_and_widths(rows, d, dtype)
 
 
-# arrays that the last cache does not hold, in the backward pass (four above 256 MB) and in the forward one (two); one, two and four pieces per thread
-@pytest.mark.parametrize("rows,d,dtype", [(32770, 1032, "bf16"), (16387, 2056, "bf16"), (32801, 2056, "bf16"), (16400, 4104, "bf16"), (32900, 1032, "fp32"), (16390, 2056, "fp32"), (8200, 4104, "fp32")])
+# arrays that the last cache does not hold, in the backward pass (four above 288 MB) and in the forward one (two), and a little less than that; one, two and four pieces per thread
+@pytest.mark.parametrize("rows,d,dtype", [(36700, 1032, "bf16"), (18400, 2056, "bf16"), (36750, 2056, "bf16"), (18400, 4104, "bf16"), (18400, 2056, "fp32"), (9200, 4104, "fp32"),
+                                          (32770, 1032, "bf16"), (16387, 2056, "bf16"), (32801, 2056, "bf16"), (16400, 4104, "bf16"), (32900, 1032, "fp32"), (16390, 2056, "fp32"), (8200, 4104, "fp32")])
 def test_rmsnorm_past_the_caches(rows, d, dtype):
     test_rmsnorm_over_row_counts_and_widths(rows, d, dtype)
 
