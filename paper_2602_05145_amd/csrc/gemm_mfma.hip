@@ -1321,11 +1321,9 @@ bool whole_slabs(const MfmaParams& p) { return !p.k_dev && p.K % 64 == 0 && (!p.
 // of a step come from memory, and with the three and two units that fit twice into a CU a slab waits for them: us in a step, 3 + 2 units / 5 + 5,
 // 132 blocks of 32 slabs 27.3 / 19.5, 96 27.5 / 18.7, 48 30.2 / 21.6; 192 blocks of 64 slabs, alone and repeated, 34.4 / 28.6.  Evaluation of 2 x 144
 // rows, 2048 / 5632 wide, 247 / 214; steps of 132 to 1000 rows 0.6 to 2.3 % less.  Not below 16 slabs, where filling the rings shows (8 slabs and fewer, 8.1 / 8.4 to
-// 13.1 / 13.7), nor with nearly every CU busy (250 blocks of 32 slabs 23.3 / 24.1).
-bool few_blocks(const MfmaParams& p, int64_t blocks, int tiles) {
-  const int slabs = split_slabs(p.K, p.A2 ? p.K2 : 0), parts = std::max<int>(1, (int)(blocks / std::max(1, tiles)));
-  return blocks <= 224 && slabs / parts >= 16;
-}
+// 13.1 / 13.7), nor with nearly every CU busy (250 blocks of 32 slabs 23.3 / 24.1).  Nor split over K: the costs of a split give no part 16 slabs as long as its
+// blocks are 224 or fewer, and one over a number of rows known on the device can have less than at the bound.
+bool few_blocks(int split, int64_t tiles, int slabs) { return split == kSplitNone && tiles <= 224 && slabs >= 16; }
 
 template <int BM, int BN, bool AMM, bool BNM, typename TO, typename P>
 hipError_t launch_tiles(const P& p, const SplitGrid& all, hipStream_t s) {   // all: of a kSplitAll launch
@@ -1343,7 +1341,7 @@ hipError_t launch_tiles(const P& p, const SplitGrid& all, hipStream_t s) {   // 
       if (whole_slabs(p)) kernel = gemm_mfma_kernel<BM, BN, AMM, BNM, TO, true>;
     }
     if constexpr (BM == 128) {
-      if (few_blocks(p, items, tiles)) {
+      if (few_blocks(q.split, tiles, split_slabs(p.K, p.A2 ? p.K2 : 0))) {
         kernel = gemm_mfma_few_kernel<AMM, BNM, TO, false>;
         if constexpr (!(AMM && BNM)) {
           if (whole_slabs(p)) kernel = gemm_mfma_few_kernel<AMM, BNM, TO, true>;
@@ -1386,6 +1384,12 @@ const char* gemm_kernel_name(const GemmArgs& a) {
                                          {"gemm_mfma_tn_128x256_f32out", "gemm_mfma_tn_160x256_f32out", "gemm_mfma_tn_192x256_f32out", "gemm_mfma_tn_224x256_f32out"}};
   const LaunchPlan lp = plan_launch(a);
   return lp.BM == lp.BN ? square[a.layout][a.out_dtype == kF32][lp.BN == 256] : tall[a.layout][(lp.BM - 128) / 32];
+}
+
+bool gemm_long_rings(const GemmArgs& a) {
+  if (!gemm_mfma_supported(a)) return false;
+  const LaunchPlan lp = plan_launch(a);
+  return lp.BN == 128 && few_blocks(lp.split, tile_count(a.M, a.N, 128), split_slabs((int)a.K, a.A2 ? (int)a.K2 : 0));
 }
 
 const char* gemm_adam_kernel_name(const GemmArgs& a) {

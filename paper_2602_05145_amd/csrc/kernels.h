@@ -45,6 +45,7 @@ size_t gemm_splitk_scratch_bytes(const GemmArgs& a);
 // At least what the product asks for with any number of rows (M, of TN K) up to the given one; never falls as the rows grow.
 size_t gemm_splitk_scratch_bound(const GemmArgs& a);
 const char* gemm_kernel_name(const GemmArgs& a);        // the kernel that a launch with these arguments runs, as profiles report it
+bool gemm_long_rings(const GemmArgs& a);                // whether it is the one of squares of 128 whose rings hold five units (profiles name both alike)
 hipError_t launch_gemm_mfma(const GemmArgs& a, hipStream_t s);
 hipError_t launch_gemm_fp32(const GemmArgs& a, hipStream_t s);     // fp32 operands and result
 hipError_t launch_gemm_simple(const GemmArgs& a, hipStream_t s);

@@ -25,6 +25,7 @@ def _symbol(name, restype, argtypes):
 scratch_bytes = _symbol("_ZN4tide25gemm_splitk_scratch_bytesERKNS_8GemmArgsE", C.c_size_t, [C.POINTER(GemmArgs)])
 scratch_bound = _symbol("_ZN4tide25gemm_splitk_scratch_boundERKNS_8GemmArgsE", C.c_size_t, [C.POINTER(GemmArgs)])
 kernel_name = _symbol("_ZN4tide16gemm_kernel_nameERKNS_8GemmArgsE", C.c_char_p, [C.POINTER(GemmArgs)])
+long_rings = _symbol("_ZN4tide15gemm_long_ringsERKNS_8GemmArgsE", C.c_bool, [C.POINTER(GemmArgs)])
 launch = _symbol("_ZN4tide11launch_gemmERKNS_8GemmArgsEP12ihipStream_t", C.c_int, [C.POINTER(GemmArgs), C.c_void_p])
 
 

@@ -198,7 +198,7 @@ def test_every_phase_of_the_long_rings(layout, slabs):
                 cnt = torch.tensor([k or 0], dtype=torch.int32, device="cuda")
                 if k is not None:
                     args.k_dev = cnt.data_ptr()
-                assert "_128_" in kernel_name(args).decode()
+                assert ig.long_rings(args) and "_128_" in kernel_name(args).decode()
                 print("long rings", layout, K, out, k, flush=True)
                 _run(args)
                 n = K if k is None else k
@@ -217,8 +217,28 @@ def test_a_second_operand_pair_on_the_long_rings(layout, K, K2):
     cnt = torch.tensor([rows], dtype=torch.int32, device="cuda")
     args = ig.args(layout, M, N, K, K2=K2, lda=lda, ldb=lda if layout == ig.NT else N, a=a.data_ptr(), b=b.data_ptr(), c=c.data_ptr(), m_dev=cnt.data_ptr())
     args.A2, args.B2 = a2.data_ptr(), b2.data_ptr()
-    assert "_128_" in kernel_name(args).decode()
+    assert ig.long_rings(args) and "_128_" in kernel_name(args).decode()
     print("pairs on the long rings", layout, K, K2, flush=True)
     _run(args)
     want = sum(x[:rows, :k].double() @ (y[:, :k].double().t() if layout == ig.NT else y.double()) for x, y, k in ((a, b, K), (a2, b2, K2)))
     assert bool(((c[:rows].double() - want).abs() <= _bound(K + K2, want, True)).all()) and bool((c[rows:] == 7.0).all())
+
+
+def test_the_long_rings_are_for_few_blocks_of_many_slabs():
+    """At most 224 squares of 128 and 16 slabs or more, also over two operand pairs: both sides of either limit; and no launch that is split."""
+    def plan(layout, M, N, K, **more):
+        g = ig.args(layout, M, N, K, out=ig.F32 if layout == ig.TN else ig.BF16, **more)
+        assert "_128_" in kernel_name(g).decode(), (layout, M, N, K, more)
+        return g
+    for layout in (ig.NT, ig.NN):
+        for K, K2, long in ((1024, 0, True), (968, 0, True), (960, 0, False), (960, 64, True), (896, 64, False)):
+            assert ig.long_rings(plan(layout, 264, 264, K, K2=K2, lda=1024, ldb=1024)) == long, (layout, K, K2)
+        for rows, columns, long in ((16, 14, True), (15, 15, False)):     # (bf16 results added to old ones: on squares alone)
+            assert ig.long_rings(plan(layout, 128 * rows, 128 * columns, 1024, accumulate=1)) == long, (layout, rows, columns)
+    assert ig.long_rings(plan(ig.TN, 264, 264, 961)) and not ig.long_rings(plan(ig.TN, 264, 264, 960))
+    for layout, M, N, K in ((ig.NT, 264, 264, 4096), (ig.NN, 104, 512, 5632), (ig.TN, 256, 1024, 4000)):
+        for more in ({}, dict(k_dev=256) if layout == ig.TN else dict(m_dev=256)):
+            g = plan(layout, M, N, K, **more)
+            assert ig.long_rings(g)
+            g.scratch, g.scratch_bytes = 256, ig.scratch_bytes(g)
+            assert g.scratch_bytes > 0 and not ig.long_rings(plan(layout, M, N, K, scratch=g.scratch, scratch_bytes=g.scratch_bytes, **more))
