@@ -1136,7 +1136,8 @@ hipError_t set_smem(const void* f, size_t bytes, bool& done) {
 // have 4 MB of keys and values, the L2 of an XCD, two to eight (64 x 199, 32 / 8 heads, forward, 4 / 8 / 16 / 64 of 64 groups: 57 / 56 / 65 / 71 us; 16 x 2048, 1 / 4 / 16 of
 // 16: 659 / 620 / 651).  dK / dV, which read more per block: sixteen at head size 64 (backward of
 // 32 x 512, 4 / 8 / 16 / 32 of 32: 453 / 448 / 425 / 433); at 128 all where they are three rounds of blocks or fewer, otherwise eight (forward and backward of 16 x 2048,
-// 2 / 4 / 8 / 16 of 16: 2581 / 2529 / 2522 / 2582; of 11 x 815, 16 / 8 heads, 4 / 6 / 11 of 11: 206 / 194 / 191).
+// 2 / 4 / 8 / 16 of 16: 2581 / 2529 / 2522 / 2582; of 11 x 815, 16 / 8 heads, 4 / 6 / 11 of 11: 206 / 194 / 191).  (Rounds of 32 CUs times the three
+// blocks that one holds of the form with one set; the forms with two sets are for fewer blocks than that in any case.)
 int row_chunk(int per_xcd, int nx, int slots, int64_t kv_bytes) {
   if (per_xcd * (int64_t)nx <= 3 * slots) return std::max(1, per_xcd);
   const int most = (int)std::min<int64_t>(8, std::max<int64_t>(2, (4 << 20) / kv_bytes)), n = (per_xcd + most - 1) / most;

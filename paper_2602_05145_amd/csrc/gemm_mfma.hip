@@ -1449,8 +1449,8 @@ hipError_t launch_gemm_mfma(const GemmArgs& a, hipStream_t s) {
   return e != hipSuccess || p.split != kSplitTail ? e : launch_fixup<false>(p, AdamTarget{}, s);
 }
 
-// (a product whose tiles are all split is left as it is: the update in the kernel that adds the parts took longer than the pass
-// over the weight, 8000 rows of a 1280 / 3440 wide step 3736 us so, 3613 with the pass)
+// (a product whose tiles are all split, which only one with scratch is, is left as it is: the update in the kernel that adds the parts took longer than
+// the pass over the weight, 8000 rows of a 1280 / 3440 wide step 3736 us so, 3613 with the pass)
 bool gemm_adam_supported(const GemmArgs& a, const AdamTarget& t) {
   return a.layout == kTN && a.out_dtype == kF32 && !a.residual && !a.A2 && gemm_mfma_supported(a) && a.N % 8 == 0 && a.ldc % 8 == 0 &&
          !(((uintptr_t)a.C | (uintptr_t)t.m | (uintptr_t)t.v | (uintptr_t)t.master | (uintptr_t)t.w) & 15) && plan_launch(a, true).split != kSplitAll;

@@ -703,7 +703,9 @@ static int enqueue_backward(const tide_draft_config* cfg, const tide_draft_tenso
   };
   // The weight gradients of the layer wait for each other where one launch of all is faster: nothing overwrites their operands
   // before the end.  fp32: always; bf16: those that update their weights, over a batch that is not too large (otherwise at once, while an
-  // operand of the product before is still in a cache).
+  // operand of the product before is still in a cache).  They are asked for without scratch, so that one whose tiles would all be split over K, and which would
+  // then leave its update to the pass over the weights, joins them whole: steps of 8000 rows, us, with such a product by itself / so, 1280 / 3440 wide
+  // 3491 / 3475, 1024 / 2816 wide 2696 / 2645, 1536 / 4096 wide 3976 / 3847.
   GemmArgs later[kMaxGemmGroup];
   AdamTarget later_upd[kMaxGemmGroup];
   int n_later = 0;
