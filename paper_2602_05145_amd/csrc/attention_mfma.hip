@@ -1245,58 +1245,69 @@ RowWork row_work(const AttnArgs& a) {
 // 28.0 / 31.2 / 28.1, 16 / 4 heads 1 x 2665 (336, 84) 65.9 / 47.5 / 51.8, 16 / 8 heads 1 x 4603 (576, 144) 118.9 / 117.9 / 115.1, 32 / 8 heads 5 x 214 (280, 7) 11.0 / 15.9 / 13.7; of 64,
 // 16 / 8 heads 1 x 526 (68, 17) 13.5 / 9.4 / 12.1, 32 / 8 heads 7 x 641 (1176, 21) 28.1 / 32.6 / 32.5.  Backward, four waves / two sets of two / four sets of two
 // (head size 64): 1 x 727 with 32 / 8 heads (184, 23) 95.2 / 80.9 / 76.6, 6 x 777 with 16 / 4 (600, 25) 104 / 90 / 109.
-template <int D>
-hipError_t launch_fwd_form(const AttnArgs& a, hipStream_t s) {
+struct Form { int kw, ns; };   // waves (dK / dV at head size 128: pairs of them) and sets
+Form fwd_form(const AttnArgs& a) {
   const RowWork w = row_work(a);
-  if (D == 64 ? w.blocks <= 640 && w.steps >= 6 : w.blocks <= 256 && w.steps >= 4) return launch_fwd<D, 2, 2>(a, s);
-  if constexpr (D == 128)
-    if (w.blocks <= 640 && w.steps >= 20) return launch_fwd<D, 4, 2>(a, s);
-  return launch_fwd<D, 4, 1>(a, s);
+  if (a.dh == 64 ? w.blocks <= 640 && w.steps >= 6 : w.blocks <= 256 && w.steps >= 4) return Form{2, 2};
+  if (a.dh == 128 && w.blocks <= 640 && w.steps >= 20) return Form{4, 2};
+  return Form{4, 1};
 }
-template <int D>
-hipError_t launch_dq_form(const AttnArgs& a, hipStream_t s) {
+Form dq_form(const AttnArgs& a) {
   const RowWork w = row_work(a);
-  if constexpr (D == 64) {
-    if (w.blocks <= 224 && w.steps >= 4) return launch_dq<D, 2, 4>(a, s);
-    if (w.blocks <= 1024 && w.steps >= 8) return launch_dq<D, 2, 2>(a, s);
-  } else {
-    if (w.blocks <= 1024 && w.steps >= 10) return launch_dq<D, 2, 2>(a, s);
-  }
-  return launch_dq<D, 4, 1>(a, s);
+  if (a.dh == 64 && w.blocks <= 224 && w.steps >= 4) return Form{2, 4};
+  if (w.blocks <= 1024 && w.steps >= (a.dh == 64 ? 8 : 10)) return Form{2, 2};
+  return Form{4, 1};
 }
-template <int D>
-hipError_t launch_bwd(const AttnArgs& a, hipStream_t s) {
-  hipError_t e = launch_dq_form<D>(a, s);
-  if (e != hipSuccess) return e;
-  const double pairs = (double)a.B * a.nh * D * (double)a.S * (a.S + 1) / 2.0;  // (query, key, channel) triples
+Form dkv_form(const AttnArgs& a) {
   // blocks of n keys that have rows: a packed batch holds at most one partly filled block per sequence
   auto key_blocks = [&](int n) {
     const int64_t all = (int64_t)((a.S + n - 1) / n) * a.B;
     return a.nkv * (a.cu_seqlens ? std::min<int64_t>(a.total_rows / n + a.B, all) : all);
   };
   const int64_t chain = (int64_t)(a.nh / a.nkv) * ((a.S + 31) / 32);   // the longest: 32-query tiles, heads of the group times sequence
-  if constexpr (D == 64) {
+  const int64_t blocks = key_blocks(64);
+  if (a.dh == 64) {
     // Whole backward, us, blocks of 64 keys with four, two sets and one: 1 x 727 with 32 / 8 heads (96 blocks, chain 92) 74.7 / 92.8 / 128,
     // 5 x 787 (520, 100) 103 / 113 / 150, 27 x 113 with 16 / 8 (432, 8) 28.0 / 25.0 / 26.4, 12 x 486 with 40 / 8 (768, 80) 118 / 114 / 138,
     // 61 x 156 (1464, 25) 125 / 105 / 101; a block of 128 keys on four waves is within 3 % of the last where that is the fastest.
-    ProfScope ps("attn_dkv_mfma", 8.0 * pairs, 0, s);   // S, dP, dV and dK products
-    const int64_t blocks = key_blocks(64);
-    if (blocks <= 424 || (blocks <= 544 && chain >= 32)) return launch_dkv<2, 4>(a, s);
-    if (blocks <= 1000) return launch_dkv<2, 2>(a, s);
-    return launch_dkv<2, 1>(a, s);
-  } else {
-    // Forward and backward, us, one set of two pairs / two sets / two sets of one pair, blocks of 64 keys and chain: 1 x 500 with 32 / 8 heads (64, 64) 89 / 73 / 67,
-    // 2 x 905 (240, 116) 162 / 138 / 129, 7 x 405 with 40 / 8 (392, 65) 139 / 125 / 143, 1 x 6341 with 16 / 4 (400, 796) 1110 / 902 / 1124, 3 x 1333 (504, 168) 302 / 270 / 332,
-    // 16 x 181 (384, 24) 70 / 69 / 76, 18 x 209 with 16 / 8 (576, 14) 55 / 58 / 66, 1 x 5876 (736, 368) 748 / 748 / 937, 5 x 1601 with 40 / 8 (1040, 255) 656 / 709 / 907.
-    ProfScope ps("attn_dkv_mfma", 8.0 * pairs, 0, s);   // S, dP, dV and dK products
-    const int64_t blocks = key_blocks(64);
-    if (blocks <= 256 && chain >= 8) return launch_dkv_pair<1, 2>(a, s);
-    if (blocks <= 520 && chain >= 16) return launch_dkv_pair<2, 2>(a, s);
-    return launch_dkv_pair<2, 1>(a, s);
+    if (blocks <= 424 || (blocks <= 544 && chain >= 32)) return Form{2, 4};
+    return blocks <= 1000 ? Form{2, 2} : Form{2, 1};
   }
+  // Forward and backward, us, one set of two pairs / two sets / two sets of one pair, blocks of 64 keys and chain: 1 x 500 with 32 / 8 heads (64, 64) 89 / 73 / 67,
+  // 2 x 905 (240, 116) 162 / 138 / 129, 7 x 405 with 40 / 8 (392, 65) 139 / 125 / 143, 1 x 6341 with 16 / 4 (400, 796) 1110 / 902 / 1124, 3 x 1333 (504, 168) 302 / 270 / 332,
+  // 16 x 181 (384, 24) 70 / 69 / 76, 18 x 209 with 16 / 8 (576, 14) 55 / 58 / 66, 1 x 5876 (736, 368) 748 / 748 / 937, 5 x 1601 with 40 / 8 (1040, 255) 656 / 709 / 907.
+  if (blocks <= 256 && chain >= 8) return Form{1, 2};
+  return blocks <= 520 && chain >= 16 ? Form{2, 2} : Form{2, 1};
+}
+
+template <int D>
+hipError_t launch_fwd_form(const AttnArgs& a, hipStream_t s) {
+  const Form f = fwd_form(a);
+  if (f.ns == 1) return launch_fwd<D, 4, 1>(a, s);
+  if constexpr (D == 128)
+    if (f.kw == 4) return launch_fwd<D, 4, 2>(a, s);
+  return launch_fwd<D, 2, 2>(a, s);
+}
+template <int D>
+hipError_t launch_bwd(const AttnArgs& a, hipStream_t s) {
+  const Form q = dq_form(a), kv = dkv_form(a);
+  hipError_t e;
+  if (q.ns == 1) e = launch_dq<D, 4, 1>(a, s);
+  else if (D == 128 || q.ns == 2) e = launch_dq<D, 2, 2>(a, s);
+  else e = launch_dq<64, 2, 4>(a, s);
+  if (e != hipSuccess) return e;
+  // S, dP, dV and dK products of every (query, key, channel) triple
+  ProfScope ps("attn_dkv_mfma", 4.0 * a.B * a.nh * D * (double)a.S * (a.S + 1), 0, s);
+  if constexpr (D == 64) return kv.ns == 4 ? launch_dkv<2, 4>(a, s) : kv.ns == 2 ? launch_dkv<2, 2>(a, s) : launch_dkv<2, 1>(a, s);
+  else return kv.ns == 1 ? launch_dkv_pair<2, 1>(a, s) : kv.kw == 1 ? launch_dkv_pair<1, 2>(a, s) : launch_dkv_pair<2, 2>(a, s);
 }
 }  // namespace
 
+int attn_mfma_form(const AttnArgs& a, int pass) {
+  if (!attn_mfma_supported(a)) return 0;
+  const Form f = pass == 0 ? fwd_form(a) : pass == 1 ? dq_form(a) : dkv_form(a);
+  return f.kw * 10 + f.ns;
+}
 hipError_t launch_attn_fwd_mfma(const AttnArgs& a, hipStream_t s) { return a.dh == 64 ? launch_fwd_form<64>(a, s) : launch_fwd_form<128>(a, s); }
 hipError_t launch_attn_bwd_mfma(const AttnArgs& a, hipStream_t s) { return a.dh == 64 ? launch_bwd<64>(a, s) : launch_bwd<128>(a, s); }
 

@@ -186,6 +186,7 @@ struct AttnArgs {
   int64_t total_rows = 0;
 };
 bool attn_mfma_supported(const AttnArgs& a);
+int attn_mfma_form(const AttnArgs& a, int pass);         // pass 0: forward, 1: dQ, 2: dK / dV; ten times a set's waves or pairs plus the sets, 0: not these kernels
 hipError_t launch_attn_fwd_simple(const AttnArgs& a, hipStream_t s);
 hipError_t launch_attn_bwd_simple(const AttnArgs& a, hipStream_t s);
 hipError_t launch_attn_fwd_mfma(const AttnArgs& a, hipStream_t s);

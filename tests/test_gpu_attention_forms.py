@@ -28,29 +28,17 @@ def _run(B, qkv, dout, bt, S, nh, nkv, dh):
     return out, lse, dqkv
 
 
-# items of a block from several heads and query blocks (groups of 3, 5 and 7 heads), steps that the sets share unevenly, one step fewer than sets
 @pytest.mark.parametrize("dh", [64, 128])
-@pytest.mark.parametrize("bt,S,nh,nkv", [(1, 97, 3, 1), (1, 161, 5, 1), (3, 225, 7, 1), (1, 321, 10, 2), (2, 650, 20, 4), (9, 640, 8, 2), (40, 33, 6, 2), (33, 70, 4, 4)])
+@pytest.mark.parametrize("bt,S,nh,nkv", ia.EDGES)
 def test_every_form_at_its_edges(B, dh, bt, S, nh, nkv):
-    g = torch.Generator(device=DEV).manual_seed(S + nh + dh)
-    qkv = torch.randn(S, (nh + 2 * nkv) * dh, device=DEV, generator=g).bfloat16()
-    dout = torch.randn(S, nh * dh, device=DEV, generator=g).bfloat16()
+    qkv, dout = ia.inputs(S, nh, nkv, dh, S + nh + dh)
     out, lse, dqkv = _run(B, qkv.repeat(bt, 1), dout.repeat(bt, 1), bt, S, nh, nkv, dh)
     for x, shape in ((out, (bt, S, -1)), (lse, (bt, nh, S)), (dqkv, (bt, S, -1))):   # every sequence of the batch the same bits
         assert float((x.view(*shape) - x.view(*shape)[:1]).abs().max()) == 0.0
-    ro, rl, rg = _reference(qkv, dout, S, nh, nkv, dh)
-    w = nh * dh
-    # as in the tests of the tiles' edges: 1 % of the largest value is three times what bf16 outputs and probabilities show
-    assert float((out[:S].double().cpu() - ro).abs().max()) < 1e-2 * float(ro.abs().max())
-    assert float((lse[0].double().cpu() - rl).abs().max()) < 1e-5 * float(rl.abs().max())
-    for part in (slice(0, w), slice(w, w + nkv * dh), slice(w + nkv * dh, None)):
-        assert float((dqkv[:S, part].double().cpu() - rg[:, part]).abs().max()) < 1e-2 * float(rg[:, part].abs().max())
+    ia.check((out[:S], lse[0], dqkv[:S]), nh, nkv, dh, qkv=qkv, dout=dout)
 
 
-# dK / dV at head size 128: pairs of waves in two sets of one pair (up to 256 blocks of 64 keys, chains of 8 query tiles), of two pairs (up to 520, chains of
-# 16) and in one set; the last keys with fewer tiles than sets, a pair without keys.  (From 32 positions on: over one, gradients of queries and keys are zero, and
-# over a few they are the rest of a cancellation against delta, which is made from outputs rounded to 2^-9: 2^-9 sqrt(128) of a row, over 1 % of it.)
-@pytest.mark.parametrize("bt,S,nh,nkv", [(1, 32, 8, 1), (1, 33, 8, 1), (1, 257, 2, 2), (1, 288, 2, 2), (33, 270, 4, 2), (33, 289, 4, 2), (130, 65, 10, 1), (66, 257, 2, 2), (200, 96, 3, 1)])
+@pytest.mark.parametrize("bt,S,nh,nkv", ia.PAIRS)
 def test_pairs_of_waves_at_their_edges(B, bt, S, nh, nkv):
     test_every_form_at_its_edges(B, 128, bt, S, nh, nkv)
 
@@ -68,6 +56,9 @@ def test_sets_and_single_waves_agree(B, dh):
     for a, b, n in zip(one, many, (S, 1, S)):
         a, b = a.double(), b[:n].double()
         assert float((a - b).abs().max()) < 2.0 ** -7 * float(b.abs().max())
+    ref = ia.reference(qkv, dout, nh, nkv, dh)   # and of every row each within its own bound
+    ia.check((one[0], one[1][0], one[2]), nh, nkv, dh, ref)
+    ia.check((many[0][:S], many[1][0], many[2][:S]), nh, nkv, dh, ref)
 
 
 def test_later_positions_reach_nothing_before_them_across_sets(B):
@@ -84,6 +75,22 @@ def test_later_positions_reach_nothing_before_them_across_sets(B):
     assert bool(torch.isnan(got[0][cut:]).all())
     for a, b in ((got[0][:cut].float(), clean[0][:cut].float()), (got[2][:cut, :nh * dh].float(), clean[2][:cut, :nh * dh].float())):
         assert bool(torch.isfinite(a).all()) and bool(((a - b).abs() <= 2.0 ** -7 * b.abs() + 1e-5 * b.abs().max()).all())
+
+
+@pytest.mark.parametrize("dh,nh,nkv,lens,form", ia.PACKED)
+def test_packed_sequences_in_every_form(B, dh, nh, nkv, lens, form):
+    """Sequences shorter than the launch's longest, blocks of them without rows, sets with fewer steps than others: each sequence as it is by itself in fp64."""
+    qkv, dout = ia.inputs(sum(lens), nh, nkv, dh, sum(lens) + nh + dh)
+    offsets = [0]
+    for n in lens:
+        offsets.append(offsets[-1] + n)
+    print(f"packed attention of {len(lens)} sequences heads={nh}/{nkv} dh={dh} {form}", flush=True)
+    assert ia.forms(len(lens), max(lens), nh, nkv, dh, sum(lens)) == form
+    out, lse, dqkv = ia.packed(qkv, dout, offsets, max(lens), nh, nkv, dh)
+    for i, (a, b) in enumerate(zip(offsets, offsets[1:])):
+        if b > a and (i < 24 or i % 7 == 0):
+            ia.check((out[a:b], lse[:, a:b], dqkv[a:b]), nh, nkv, dh, qkv=qkv[a:b], dout=dout[a:b])
+    assert bool(torch.isfinite(out).all()) and bool(torch.isfinite(dqkv).all())
 
 
 @pytest.mark.parametrize("dh,nh,nkv", [(64, 10, 2), (128, 6, 2)])
