@@ -30,6 +30,7 @@
 // per-element causal test is made only by the (wave-uniformly chosen) tiles that touch the diagonal.
 #include <algorithm>
 #include <cfloat>
+#include <numeric>
 #include <type_traits>
 
 #include "kernels.h"
@@ -256,13 +257,21 @@ constexpr int dq_ring(int D) { return D == 64 ? 8 : 4; }
 // heaviest blocks first, so that what ends last is light blocks of many groups: group after group, the last groups'
 // heaviest blocks began when the others had nothing left to do.  us, a group / a chunk at a time: backward of 16 x 2048, 32 / 8 heads of 128 2430 / 2180, of 16 x 1024
 // 725 / 634, of 7 x 979, 32 heads of 64 277 / 183; forward of 13 x 759, 16 / 4 heads of 128 60 / 48.
+// Sequences of a packed batch differ, and some may be empty.  There a group is given to one XCD only where the heads of ONE sequence keep all eight busy (their number is a
+// multiple of 8).  Otherwise all go in the plain order, with the groups counted up to a number that has as many factors of 2 as the heads have: block x of
+// group g is on XCD (x times that number + g) % 8, so that a group comes to no more XCDs than it takes for a sequence's heads to reach all.
+// (Dealt like a fixed batch, forward of one sequence of 5693 positions and 16 empty ones, 10 / 2 heads of 64, 416 us on two XCDs, so 117; backward 1037 / 449.)
 struct Work3 { int x, y, z; bool on; };
-struct WorkMap { int nx, ny, groups, per_xcd, chunk; };   // per_xcd 0: groups are not dealt to XCDs
-__host__ __device__ inline WorkMap work_map(int nx, int ny, int nz) {
+struct WorkMap { int nx, ny, groups, per_xcd, chunk, stride; };   // per_xcd 0: groups are not dealt to XCDs; stride: the groups that the plain order counts
+inline WorkMap work_map(int nx, int ny, int nz, bool packed) {
   const int groups = ny * nz;
-  return WorkMap{nx, ny, groups, groups % 8 == 0 || groups >= 32 ? (groups + 7) / 8 : 0, 1};
+  const bool dealt = packed ? ny % 8 == 0 : groups % 8 == 0 || groups >= 32;
+  int stride = groups;
+  if (packed && !dealt)
+    while (std::gcd(stride, 8) != std::gcd(ny, 8)) ++stride;
+  return WorkMap{nx, ny, groups, dealt ? (groups + 7) / 8 : 0, 1, stride};
 }
-inline int64_t work_blocks(const WorkMap& w) { return (int64_t)w.nx * (w.per_xcd ? 8 * w.per_xcd : w.groups); }
+inline int64_t work_blocks(const WorkMap& w) { return (int64_t)w.nx * (w.per_xcd ? 8 * w.per_xcd : w.stride); }
 __device__ __forceinline__ Work3 work_item(const WorkMap& w) {
   const int n = blockIdx.x;
   int x, grp;
@@ -271,8 +280,8 @@ __device__ __forceinline__ Work3 work_item(const WorkMap& w) {
     x = in / size;
     grp = (first + in - x * size) * 8 + (n & 7);
   } else {
-    x = n / w.groups;
-    grp = n - x * w.groups;
+    x = n / w.stride;
+    grp = n - x * w.stride;
   }
   const int z = grp / w.ny;
   return Work3{x, grp - z * w.ny, z, grp < w.groups};
@@ -1148,16 +1157,25 @@ int key_chunk(int per_xcd, int nx, int D) {
   const int n = std::max(1, (per_xcd + most - 1) / most);
   return std::max(1, (per_xcd + n - 1) / n);
 }
+// Of a packed batch chunks of an odd number of groups: behind a sequence's last block its turns go to blocks that end at once, and an XCD's
+// four shader engines take the blocks in turn as well: 880 and 5707 positions, 64 / 8 heads of 64, chunks of two / three, forward 604 / 424 us, backward
+// 2163 / 1408 (dK / dV in two sets there, too).
+void set_chunk(WorkMap& map, int chunk, const AttnArgs& a) {
+  map.chunk = chunk;
+  if (!a.cu_seqlens || !map.per_xcd) return;
+  map.chunk |= 1;
+  map.per_xcd = (map.per_xcd + map.chunk - 1) / map.chunk * map.chunk;
+}
 template <int D, int KW, int NS>
 WorkMap row_map(const AttnArgs& a, int waves) {
-  WorkMap map = work_map(row_blocks<KW>(a.S, a.nh / a.nkv), a.nkv, a.B);
-  map.chunk = row_chunk(map.per_xcd, map.nx, 32 * 4 * waves / (KW * NS), (int64_t)a.S * D * 4);
+  WorkMap map = work_map(row_blocks<KW>(a.S, a.nh / a.nkv), a.nkv, a.B, a.cu_seqlens != nullptr);
+  set_chunk(map, row_chunk(map.per_xcd, map.nx, 32 * 4 * waves / (KW * NS), (int64_t)a.S * D * 4), a);
   return map;
 }
 template <int KW, int D>
 WorkMap key_map(const AttnArgs& a) {
-  WorkMap map = work_map((a.S + KW * 32 - 1) / (KW * 32), a.nkv, a.B);
-  map.chunk = key_chunk(map.per_xcd, map.nx, D);
+  WorkMap map = work_map((a.S + KW * 32 - 1) / (KW * 32), a.nkv, a.B, a.cu_seqlens != nullptr);
+  set_chunk(map, key_chunk(map.per_xcd, map.nx, D), a);
   return map;
 }
 // A launch has fewer than 2^32 threads, and in a packed batch the number of sequences and the longest length are bounds that can ask for more blocks
@@ -1232,52 +1250,55 @@ hipError_t launch_dkv_pair(const AttnArgs& a, hipStream_t s) {   // head size 12
   return hipGetLastError();
 }
 
-// Blocks of four items that have rows, and the steps of the longest.  A packed batch holds at most one partly filled item of every head per sequence.
-struct RowWork { int64_t blocks; int steps; };
+// Blocks of four items that have rows, the steps of the longest, and the blocks that are launched.  A packed batch holds at most one partly filled item of
+// every head per sequence; its launch is made for sequences that are all as long as the longest.
+struct RowWork { int64_t blocks; int steps; int64_t launched; };
 RowWork row_work(const AttnArgs& a) {
   const int64_t per_seq = (a.S + 31) / 32, items = a.cu_seqlens ? std::min<int64_t>(a.total_rows / 32 + a.B, per_seq * a.B) : per_seq * a.B;
-  return RowWork{(items * a.nh + 3) / 4, (int)per_seq};
+  return RowWork{(items * a.nh + 3) / 4, (int)per_seq, (int64_t)row_blocks<4>(a.S, a.nh / a.nkv) * a.nkv * a.B};
 }
-// Which form of the forward and dQ kernels: four waves that walk all keys; or, where blocks are few and a block is a long chain of steps,
-// sets of waves that share the steps.  Over 113 shapes (1 .. 64 sequences of 48 .. 7570 positions, five head counts; form that is
-// fastest on each = 0): forward of head size 128 3.4 % lost with one form, 0.2 with these three; of 64 10.1 and 0.9; backward with the dQ form alone
-// changed 4.4 and 0.9, 9.0 and 1.1.  us, four waves / two sets of two / two sets of four: forward of head size 128, 32 / 8 heads 2 x 905 (464 blocks of 29 steps)
-// 28.0 / 31.2 / 28.1, 16 / 4 heads 1 x 2665 (336, 84) 65.9 / 47.5 / 51.8, 16 / 8 heads 1 x 4603 (576, 144) 118.9 / 117.9 / 115.1, 32 / 8 heads 5 x 214 (280, 7) 11.0 / 15.9 / 13.7; of 64,
-// 16 / 8 heads 1 x 526 (68, 17) 13.5 / 9.4 / 12.1, 32 / 8 heads 7 x 641 (1176, 21) 28.1 / 32.6 / 32.5.  Backward, four waves / two sets of two / four sets of two
-// (head size 64): 1 x 727 with 32 / 8 heads (184, 23) 95.2 / 80.9 / 76.6, 6 x 777 with 16 / 4 (600, 25) 104 / 90 / 109.
 struct Form { int kw, ns; };   // waves (dK / dV at head size 128: pairs of them) and sets
+// Which form of the forward and dQ kernels: four waves that walk all keys; or, where a block's steps are a longer chain than the blocks of a CU are many,
+// sets of waves that share the steps.  The lines run where the two take equally long over 1200 fixed batches (1 .. 96 sequences of 16 .. 4000 positions, twelve head counts).
+// A packed batch can launch many times the blocks that have rows; those end at once, but the more waves they have the longer that takes: sets only up to 4096
+// (forward; 8192 where they are at most 16 times those that have rows) and 8192 (dQ) launched blocks of four items, over 750 packed batches (up to 9000 rows, up to 200 empty sequences).  us, four waves / two sets of two / two
+// sets of four: forward of head size 128, 16 / 4 heads 1 x 2665 (336 blocks of 84 steps) 65.9 / 47.5 / 51.8, 16 / 8 heads 5 x 1021 (640, 32) 35.6 / 42.5 / 42.5, 32 / 8 heads 7 x 98 (224, 4)
+// 7.4 / 8.7 / 8.8, 6 / 6 heads, 7748 rows of 36 sequences (13176 launched) 22.2 / 45.2 / 47.9; of 64, 16 / 8 heads 1 x 526 (68, 17) 13.5 / 9.4 / 12.1, 8 / 1 heads 48 x 165 (576, 6)
+// 8.9 / 11.7 / 11.9, 16 / 8 heads, 2439 rows of 41 sequences (12792 launched) 18.4 / 31.5 / 34.3.  Backward, four waves / two sets of two / four sets of two (head size 64): 1 x 727 with
+// 32 / 8 heads (184, 23) 95.2 / 80.9 / 76.6, 6 x 777 with 16 / 4 (600, 25) 104 / 90 / 109, 5 x 103 with 40 / 8 (200, 4) 23.6 / 22.0 / 27.9; of 128, 5 x 132 with 64 / 8 (400, 5) 37.8 / 45.2.
 Form fwd_form(const AttnArgs& a) {
   const RowWork w = row_work(a);
-  if (a.dh == 64 ? w.blocks <= 640 && w.steps >= 6 : w.blocks <= 256 && w.steps >= 4) return Form{2, 2};
-  if (a.dh == 128 && w.blocks <= 640 && w.steps >= 20) return Form{4, 2};
-  return Form{4, 1};
+  if (w.launched > std::max<int64_t>(4096, std::min<int64_t>(8192, 16 * w.blocks))) return Form{4, 1};
+  if (a.dh == 64) return w.steps >= 5 && w.blocks <= std::min(960, 32 * w.steps) ? Form{2, 2} : Form{4, 1};
+  if (w.blocks <= std::min(256, 32 * w.steps) && w.steps >= 4) return Form{2, 2};
+  if (w.blocks <= 384 && w.steps >= 24) return Form{2, 2};
+  return w.blocks <= 512 && w.steps >= 28 ? Form{4, 2} : Form{4, 1};
 }
 Form dq_form(const AttnArgs& a) {
   const RowWork w = row_work(a);
-  if (a.dh == 64 && w.blocks <= 224 && w.steps >= 4) return Form{2, 4};
-  if (w.blocks <= 1024 && w.steps >= (a.dh == 64 ? 8 : 10)) return Form{2, 2};
-  return Form{4, 1};
+  if (w.launched > 8192) return Form{4, 1};
+  if (a.dh == 128) return w.steps >= 4 && w.blocks <= std::min(832, 32 * w.steps) ? Form{2, 2} : Form{4, 1};
+  if (w.steps >= 8 && w.blocks <= std::min(352, 12 * w.steps)) return Form{2, 4};
+  return w.steps >= 3 && w.blocks <= std::min(1280, 48 * w.steps) ? Form{2, 2} : Form{4, 1};
 }
+// dK / dV, likewise by the blocks of 64 keys and the chain of query tiles of the first of them, over the same shapes.  (A packed batch has fewer
+// blocks than its bound, and its longest sequence is a longer chain beside them.)
 Form dkv_form(const AttnArgs& a) {
-  // blocks of n keys that have rows: a packed batch holds at most one partly filled block per sequence
-  auto key_blocks = [&](int n) {
-    const int64_t all = (int64_t)((a.S + n - 1) / n) * a.B;
-    return a.nkv * (a.cu_seqlens ? std::min<int64_t>(a.total_rows / n + a.B, all) : all);
-  };
+  // a packed batch holds at most one partly filled block per sequence
+  const int64_t all = (int64_t)((a.S + 63) / 64) * a.B, blocks = a.nkv * (a.cu_seqlens ? std::min<int64_t>(a.total_rows / 64 + a.B, all) : all);
   const int64_t chain = (int64_t)(a.nh / a.nkv) * ((a.S + 31) / 32);   // the longest: 32-query tiles, heads of the group times sequence
-  const int64_t blocks = key_blocks(64);
   if (a.dh == 64) {
     // Whole backward, us, blocks of 64 keys with four, two sets and one: 1 x 727 with 32 / 8 heads (96 blocks, chain 92) 74.7 / 92.8 / 128,
-    // 5 x 787 (520, 100) 103 / 113 / 150, 27 x 113 with 16 / 8 (432, 8) 28.0 / 25.0 / 26.4, 12 x 486 with 40 / 8 (768, 80) 118 / 114 / 138,
-    // 61 x 156 (1464, 25) 125 / 105 / 101; a block of 128 keys on four waves is within 3 % of the last where that is the fastest.
-    if (blocks <= 424 || (blocks <= 544 && chain >= 32)) return Form{2, 4};
-    return blocks <= 1000 ? Form{2, 2} : Form{2, 1};
+    // 5 x 787 (520, 100) 103 / 113 / 150, 12 x 486 with 40 / 8 (768, 80) 118 / 114 / 138, 4 sequences of 8874 rows with 32 / 8 (1136, 436) 546 / 539 / 700; where the
+    // chain is short, 96 x 32 with 4 / 4 (384, 1) 18.2 / 13.1 / 11.7, 51 x 62 with 6 / 6 (306, 2) 22.1 / 16.9 / 15.7, 61 x 156 (1464, 25) 125 / 105 / 101.
+    if (chain >= 6 && (blocks <= 256 || blocks <= std::min<int64_t>(512, 16 * chain) || blocks <= std::min<int64_t>(1024, 5 * chain))) return Form{2, 4};
+    return chain >= 4 && blocks <= std::min<int64_t>(a.cu_seqlens ? 2560 : 1280, std::max<int64_t>(512, 40 * chain)) ? Form{2, 2} : Form{2, 1};
   }
   // Forward and backward, us, one set of two pairs / two sets / two sets of one pair, blocks of 64 keys and chain: 1 x 500 with 32 / 8 heads (64, 64) 89 / 73 / 67,
   // 2 x 905 (240, 116) 162 / 138 / 129, 7 x 405 with 40 / 8 (392, 65) 139 / 125 / 143, 1 x 6341 with 16 / 4 (400, 796) 1110 / 902 / 1124, 3 x 1333 (504, 168) 302 / 270 / 332,
-  // 16 x 181 (384, 24) 70 / 69 / 76, 18 x 209 with 16 / 8 (576, 14) 55 / 58 / 66, 1 x 5876 (736, 368) 748 / 748 / 937, 5 x 1601 with 40 / 8 (1040, 255) 656 / 709 / 907.
-  if (blocks <= 256 && chain >= 8) return Form{1, 2};
-  return blocks <= 520 && chain >= 16 ? Form{2, 2} : Form{2, 1};
+  // 16 x 181 (384, 24) 70 / 69 / 76, 18 x 209 with 16 / 8 (576, 14) 55 / 58 / 66, 4 x 2208 with 16 / 4 (560, 276; backward) 367 / 313 / 415, 5 x 1601 with 40 / 8 (1040, 255) 656 / 709 / 907.
+  if (blocks <= 256 && chain >= 4 && blocks <= std::max<int64_t>(96, 24 * chain)) return Form{1, 2};
+  return blocks <= std::min<int64_t>(512, 16 * chain) || blocks <= std::min<int64_t>(832, 8 * chain) ? Form{2, 2} : Form{2, 1};
 }
 
 template <int D>

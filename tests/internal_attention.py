@@ -107,17 +107,18 @@ def check(got, nh, nkv, dh, ref=None, qkv=None, dout=None):
 MOST = {64: dict(out=1.72e-3, dq=2.2e-3, dk=2.2e-3, dv=1.95e-3), 128: dict(out=2.2e-3, dq=3e-3, dk=3e-3, dv=2.6e-3)}
 
 # batch, positions, heads, kv heads: items of a block from several heads and query blocks (groups of 3, 5 and 7 heads), steps that the sets share unevenly, one step fewer than sets
-EDGES = [(1, 97, 3, 1), (1, 161, 5, 1), (3, 225, 7, 1), (1, 321, 10, 2), (2, 650, 20, 4), (9, 640, 8, 2), (40, 33, 6, 2), (33, 70, 4, 4), (66, 257, 2, 2), (260, 65, 10, 1), (100, 129, 8, 4)]
-# dK / dV at head size 128: pairs of waves in two sets of one pair (up to 256 blocks of 64 keys, chains of 8 query tiles), of two pairs (up to 520, chains of
-# 16) and in one set; the last keys with fewer tiles than sets, a pair without keys.  (From 32 positions on: over one, gradients of queries and keys are zero, and
+EDGES = [(1, 97, 3, 1), (1, 161, 5, 1), (3, 225, 7, 1), (1, 321, 10, 2), (2, 650, 20, 4), (9, 640, 8, 2), (40, 33, 6, 2), (33, 70, 4, 4), (66, 257, 2, 2), (260, 65, 10, 1), (100, 129, 8, 4), (4, 900, 16, 4)]
+# dK / dV at head size 128: pairs of waves in two sets of one pair, of two pairs and in one set; the last keys with fewer tiles than sets, a pair without keys.  (From 32 positions on: over one, gradients of queries and keys are zero, and
 # over a few they are the rest of a cancellation against delta.)
-PAIRS = [(1, 32, 8, 1), (1, 33, 8, 1), (1, 257, 2, 2), (1, 288, 2, 2), (33, 270, 4, 2), (33, 289, 4, 2), (130, 65, 10, 1), (66, 257, 2, 2), (200, 96, 3, 1)]
+PAIRS = [(1, 32, 8, 1), (1, 33, 8, 1), (1, 257, 2, 2), (1, 288, 2, 2), (33, 270, 4, 2), (33, 289, 4, 2), (130, 65, 10, 1), (66, 257, 2, 2), (200, 96, 3, 1), (16, 289, 8, 4), (14, 270, 8, 4)]
 
 # head size, heads, kv heads, lengths of packed sequences; waves and sets of the forward, the dQ and the dK / dV kernel that such a batch takes
 _FEW, _MANY = [1, 31, 32, 33, 95, 250, 64, 7], [1, 31, 33, 65, 129, 0, 64, 97]
-PACKED = [(128, 32, 8, [201, 1075, 261, 118, 13, 38, 293], ((4, 2), (2, 2), (2, 2))), (128, 6, 2, _FEW, ((2, 2), (4, 1), (1, 2))),
+_RAGGED = [201, 1075, 261, 118, 13, 38, 293]
+PACKED = [(128, 32, 8, _RAGGED, ((4, 1), (2, 2), (2, 2))), (128, 24, 8, _RAGGED, ((4, 2), (2, 2), (2, 2))), (128, 16, 4, _RAGGED, ((2, 2), (2, 2), (1, 2))),
           (128, 16, 4, _MANY * 22, ((4, 1), (4, 1), (2, 1))), (64, 6, 2, _FEW, ((2, 2), (2, 4), (2, 4))), (64, 16, 4, _MANY * 22, ((4, 1), (4, 1), (2, 1))),
-          (64, 16, 8, [201, 700, 261, 118, 13, 38, 293, 1, 33], ((2, 2), (2, 2), (2, 4))), (64, 16, 8, _MANY * 7, ((4, 1), (4, 1), (2, 2)))]
+          (64, 32, 8, [201, 700, 261, 118, 13, 38, 293, 1, 33], ((2, 2), (2, 2), (2, 4))), (64, 16, 8, _MANY * 5 + [400], ((4, 1), (2, 2), (2, 2))),
+          (128, 3, 3, _FEW + [0] * 30, ((2, 2), (2, 2), (1, 2))), (64, 20, 10, [0] * 9 + [517] + [0] * 8, ((2, 2), (2, 4), (2, 4)))]
 
 
 def inputs(S, nh, nkv, dh, seed, device=DEV):

@@ -79,7 +79,8 @@ def test_later_positions_reach_nothing_before_them_across_sets(B):
 
 @pytest.mark.parametrize("dh,nh,nkv,lens,form", ia.PACKED)
 def test_packed_sequences_in_every_form(B, dh, nh, nkv, lens, form):
-    """Sequences shorter than the launch's longest, blocks of them without rows, sets with fewer steps than others: each sequence as it is by itself in fp64."""
+    """Sequences shorter than the launch's longest, empty ones, blocks without rows, sets with fewer steps than others, and heads that keep all XCDs busy (8) or not: each
+    sequence as it is by itself in fp64."""
     qkv, dout = ia.inputs(sum(lens), nh, nkv, dh, sum(lens) + nh + dh)
     offsets = [0]
     for n in lens:
