@@ -1,5 +1,5 @@
 // Flash-style causal grouped-query attention for gfx950, head_dim 128 or 64, bf16 storage, fp32 softmax and
-// accumulation, v_mfma_f32_32x32x16_bf16 throughout.  Three kernels: forward, dQ, and dK/dV.  The
+// accumulation, v_mfma_f32_32x32x16_bf16 throughout.  Four kernels: forward, dQ, and dK/dV of either head size.  The
 // [S,S] score matrix never exists; only the per-row log-sum-exp is kept for the backward pass.
 //
 // Orientation.  An MFMA 32x32 result leaves each lane with ONE column (lane % 32) and 16 of the 32 rows.
@@ -17,7 +17,7 @@
 //
 // Tiles.  Forward and dQ: one block = four items of 32 queries of one head (a wave each, Q in registers) that read the same keys
 // (see row_item); K/V streamed in steps of 32 keys, double buffered in LDS.  What bounds a full chip is the sum of the matrix and
-// vector work of a SIMD's two or three waves (16 x 2048, 32 / 8 heads: forward 47 and 63 % of the cycles, the clock at 1.8 GHz under the power limit), so registers are
+// vector work of a SIMD's two or three waves (16 x 2048, 32 / 8 heads: the forward's matrix pipes are busy 53 % of the cycles, at 1.8 GHz under the power limit), so registers are
 // kept for three waves in the forward: with steps of 64 keys and two waves, whose MFMAs and exponentials were interleaved by hand, it took 727 us, so 620.
 // dK/dV: the keys of a block stay in registers, Q/dO are streamed in tiles of 32 queries for each of the G query heads of the group, so
 // dK/dV are summed over the group in registers: no atomics, deterministic.  At head size 64 (199 registers) a wave makes both.  At head size 128
@@ -942,7 +942,7 @@ __global__ __launch_bounds__(KW * NS * 64, NS > 1 ? 1 : 2) void attn_dkv_mfma_ke
 // and dK += dS^T Q.  P goes from one to the other through LDS in fp32, 16 registers per lane in the layout that both products have.  KW pairs
 // and NS sets as above.  Against a launch per gradient (16 and 24 MFMAs per 32 x 32 scores, S and its exponentials in both), forward and
 // backward, us: 16 x 2048, 32 / 8 heads 2818 -> 2573; 5 x 1601, 40 / 8 832 -> 663; 42 x 190, 16 / 8 113 -> 92; 1 x 500, 32 / 8 88 -> 65; eighteen shapes 1.22 times as fast in the mean.
-// What bounds it at 16 x 2048 (matrix pipes 48 % busy at 1.9 GHz): 2561 us are 2246 without its tile loads, 2522 without the exponentials, 2483
+// What bounds it at 16 x 2048 (matrix pipes 54 % busy, L2 hits 47 %, at 1.9 GHz): 2561 us are 2246 without its tile loads, 2522 without the exponentials, 2483
 // without the exchange of P.  128 keys per block (8 waves, one block per CU) halve the loads, but nobody is there at its two barriers: 2674 for 2582.
 template <int KW, int NS>
 __global__ __launch_bounds__(KW * NS * 128, NS == 1 ? 3 : 2) void attn_dkv_pair_kernel(const bf16_t* __restrict__ qkv, const bf16_t* __restrict__ dout,
