@@ -359,7 +359,7 @@ __device__ __forceinline__ void store_once(float* p, size_t i, const float (&v)[
 // pass leaves in it still is of use: 8300 x 4096 bf16 (272 MB) backward and a product of dx 106 / 94, 7000 x 2560 fp32 (287) backward 56.7 / 50.4,
 // 17500 x 4096 (287) forward and a product of y 113 / 106; 10000 x 4096 (328) 114 / 118, 8000 x 2560 fp32 (328) 63.2 / 64.7, 20000 x 4096 (328) 128 / 130.
 // With a number of rows known on the device alone neither: it may be small, and in a training step, where the norms over the selected rows have one, it
-// is as long either way (8192 to 32768 rows, within 0.2 %).  Rows that have a wave each keep to the caches too (not tried).
+// is as long either way (8192 to 32768 rows, within 0.2 %).  Rows that have a wave each keep to the caches too.
 inline bool passes_caches(int n, int64_t rows, int d, int dtype, const int* rows_dev) {
   return !rows_dev && n * rows * d * (int64_t)dtype_size(dtype) > ((int64_t)288 << 20);
 }
@@ -462,7 +462,10 @@ __global__ __launch_bounds__(256) void rmsnorm_fwd_row_kernel(const T* __restric
 // A row per wave (d % 8 == 0, d <= 512 N): no barrier, and rows narrower than a block's 2048 columns leave no lanes idle.  Forward and backward, us, with
 // this kernel in the place of a block per row: 30000 x 256 bf16 60.0 -> 46.3, x 1024 82.7 -> 75.1, x 2048 150.6 -> 148.7; 5000 x 2048 31.1 -> 29.5; at 4096
 // columns it lost (27852 rows 267 -> 271).
+// fp32 rows wider than 768 columns keep a block each from 6000 of them on, forward alone, us, a wave / a block: 8000 x 1280 15.0 / 14.0, 8000 x 896 11.7 / 11.1, 26000 x 1024 33.0 / 32.7; below
+// 4500 x 1024 8.0 / 8.7, 3000 x 2048 10.6 / 11.0, 15000 x 688 14.7 / 16.0; such of them as are larger than the last cache pass by it (forward and backward 32000 x 2048 321 / 271).
 constexpr int kWaveRow = 2048;
+inline bool row_per_wave(int64_t rows, int d, int dtype) { return d <= kWaveRow && (dtype == kBF16 || d <= 768 || rows < 6000); }
 template <typename T, int N>
 __global__ __launch_bounds__(256) void rmsnorm_fwd_wave_kernel(const T* __restrict__ x, const T* __restrict__ g, float eps, T* __restrict__ y,
                                                                float* __restrict__ rstd, int64_t rows, int d, const int* __restrict__ rows_dev) {
@@ -514,7 +517,7 @@ hipError_t launch_rmsnorm_fwd(int64_t rows, int d, const void* x, const void* g,
   if (rows_dev) prof_dynamic(rows_dev, 0, rows);
   dim3 grid((unsigned)rows), blk(256);
   const bool vec = (d % 8) == 0;
-  if (vec && d <= kWaveRow) {
+  if (vec && row_per_wave(rows, d, dtype)) {
 #define TIDE_RMS_FWD(T, N) hipLaunchKernelGGL((rmsnorm_fwd_wave_kernel<T, N>), dim3((unsigned)((rows + 3) / 4)), blk, 0, s, (const T*)x, (const T*)g, eps, (T*)y, rstd, rows, d, rows_dev)
     if (dtype == kBF16) { if (d <= 512) TIDE_RMS_FWD(bf16_t, 1); else if (d <= 1024) TIDE_RMS_FWD(bf16_t, 2); else TIDE_RMS_FWD(bf16_t, 4); }
     else { if (d <= 512) TIDE_RMS_FWD(float, 1); else if (d <= 1024) TIDE_RMS_FWD(float, 2); else TIDE_RMS_FWD(float, 4); }
@@ -526,7 +529,7 @@ hipError_t launch_rmsnorm_fwd(int64_t rows, int d, const void* x, const void* g,
     const bool once = passes_caches(2, rows, d, dtype, rows_dev);
 #define TIDE_RMS_FWD(T, N) hipLaunchKernelGGL((once ? rmsnorm_fwd_row_kernel<T, N, true> : rmsnorm_fwd_row_kernel<T, N>), grid, blk, 0, s, (const T*)x, (const T*)g, eps, (T*)y, rstd, d, rows_dev)
     if (dtype == kBF16) { if (nit == 2) TIDE_RMS_FWD(bf16_t, 2); else TIDE_RMS_FWD(bf16_t, 4); }
-    else { if (nit == 2) TIDE_RMS_FWD(float, 2); else TIDE_RMS_FWD(float, 4); }
+    else { if (nit == 1) TIDE_RMS_FWD(float, 1); else if (nit == 2) TIDE_RMS_FWD(float, 2); else TIDE_RMS_FWD(float, 4); }
 #undef TIDE_RMS_FWD
     return hipGetLastError();
   }

@@ -41,6 +41,12 @@ def test_rmsnorm_with_a_row_per_wave(rows, d, dtype):
     test_rmsnorm_over_row_counts_and_widths(rows, d, dtype)
 
 
+# fp32 rows of more than 768 columns, a wave each below 6000 of them, a block each from there on, and past the caches
+@pytest.mark.parametrize("rows,d", [(5999, 776), (6000, 776), (6000, 768), (6001, 2048), (36900, 1024)])
+def test_rmsnorm_of_wide_fp32_rows(rows, d):
+    test_rmsnorm_over_row_counts_and_widths(rows, d, "fp32")
+
+
 # arrays that the last cache does not hold, in the backward pass (four above 288 MB) and in the forward one (two), and a little less than that; one, two and four pieces per thread
 @pytest.mark.parametrize("rows,d,dtype", [(36700, 1032, "bf16"), (18400, 2056, "bf16"), (36750, 2056, "bf16"), (18400, 4104, "bf16"), (18400, 2056, "fp32"), (9200, 4104, "fp32"),
                                           (32770, 1032, "bf16"), (16387, 2056, "bf16"), (32801, 2056, "bf16"), (16400, 4104, "bf16"), (32900, 1032, "fp32"), (16390, 2056, "fp32"), (8200, 4104, "fp32")])
