@@ -1322,7 +1322,7 @@ bool whole_slabs(const MfmaParams& p) { return !p.k_dev && p.K % 64 == 0 && (!p.
 // 132 blocks of 32 slabs 27.3 / 19.5, 96 27.5 / 18.7, 48 30.2 / 21.6; 192 blocks of 64 slabs, alone and repeated, 34.4 / 28.6.  Evaluation of 2 x 144
 // rows, 2048 / 5632 wide, 247 / 214; steps of 132 to 1000 rows 0.6 to 2.3 % less.  Weights from memory / one product over and over in the caches: 258 x 1024 x 1024 15.3 -> 10.8
 // / 9.0 -> 9.4, 384 x 4096 x 1536 21.4 -> 18.6 / 12.5 -> 12.9, 132 x 2048 x 2048 26.8 -> 16.9 / 14.0 -> 14.3, 96 x 1024 x 5632 67.9 -> 49.6 / 30.7 -> 30.4: what up to 24 slabs lose in the
-// caches are the nine units of slabs past the last (a loop whose last steps request nothing took 10 to 15 % longer in all).  Not below 16 slabs, where filling the rings shows (8 slabs and fewer, 8.1 / 8.4 to
+// caches are the nine units of slabs past the last (last steps that request nothing, in a loop of their own, cost 1 us more at any depth, tests in the one loop 0.13 us per slab).  Not below 16 slabs, where filling the rings shows (8 slabs and fewer, 8.1 / 8.4 to
 // 13.1 / 13.7), nor with nearly every CU busy (250 blocks of 32 slabs 23.3 / 24.1).  Nor split over K: the costs of a split give no part 16 slabs as long as its
 // blocks are 224 or fewer, and one over a number of rows known on the device can have less than at the bound.
 bool few_blocks(int split, int64_t tiles, int slabs) { return split == kSplitNone && tiles <= 224 && slabs >= 16; }
